@@ -310,7 +310,7 @@ def main():
         "hbm_rooflines": {"peak_GBs": HBM_PEAK_GBS,
                           "steady_loop": hbm_steady,       # as in the timed steps: operands may sit in the memory-side cache
                           "operands_rotated": hbm_rotated},  # three operand sets in turn: every first read comes from HBM
-        "roofline": {"bound": "mfma", "kernel": ("gemm_bf16_256" if w.dtype == "bf16" and min(n, m) >= 256 and k % 64 == 0 else "gemm_kernel") + " (data block + fused syndrome partials)",
+        "roofline": {"bound": "mfma", "kernel": ("gemm_bf16_256" if w.dtype == "bf16" and min(n, m) >= 256 and k % 64 == 0 else "gemm_tile") + " (data block + fused syndrome partials)",
                      "achieved": round(achieved, 3) if achieved else None, "peak": peak, "unit": "TFLOP/s",
                      "frac": round(achieved / peak, 4) if achieved else None,
                      "kernel_ms": round(g_ms, 4) if g_ms else None,

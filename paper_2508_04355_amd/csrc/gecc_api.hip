@@ -16,6 +16,17 @@ size_t elem_size(int dtype) { return dtype == GECC_BF16 ? 2 : 4; }
 bool blocked(const gecc_ctx* c) { return c->nbi > 0; }
 int items_of(const gecc_ctx* c) { return blocked(c) ? c->nbi * c->nbj : c->p.batch; }
 
+// Workgroups per tile of a product whose tiles alone would leave compute units idle: as many as give `want`
+// workgroups in all, each with at least 128 terms of k.
+int ksplit_of(int64_t tiles, int want, int k) {
+  int s = (int)(want / tiles);
+  if (s < 1) s = 1;
+  if (s > 8) s = 8;
+  while (s > 1 && k / s < 128) --s;
+  return s;
+}
+int ksplit_128(int64_t tiles, int k) { return ksplit_of(tiles, 256, k); }
+
 void make_layout(gecc_ctx* c) {
   const gecc_params& p = c->p;
   const size_t b = p.batch, n = p.n, k = p.k, m = p.m;
@@ -45,7 +56,11 @@ void make_layout(gecc_ctx* c) {
   const size_t ra = tile_scan_row_scratch_doubles(p.trans_a ? p.k : p.n, p.trans_a ? p.n : p.k, p.dtype, p.batch);
   const size_t rb = tile_scan_row_scratch_doubles(p.trans_b ? p.m : p.k, p.trans_b ? p.k : p.m, p.dtype, p.batch);
   L.scan_row = take((ra > rb ? ra : rb) * sizeof(double));
-  L.ksplit = take(c->ksplit > 1 ? b * c->ntm * c->ntn * (size_t)c->ksplit * 128 * 128 * sizeof(float) : 0);
+  // (the contexts of k-panels run on this workspace, and a panel of a bf16 product may take the larger tile)
+  const size_t s128 = b * ((n + 127) / 128) * ((m + 127) / 128);
+  const size_t k128 = c->tile_m == 64 && p.dtype == GECC_BF16 ? s128 * (size_t)ksplit_128(s128, p.k) * 128 * 128 : 0;
+  const size_t kown = c->ksplit > 1 ? b * c->ntm * c->ntn * (size_t)c->ksplit * c->tile_m * c->tile_n : 0;
+  L.ksplit = take((k128 > kown ? k128 : kown) * sizeof(float));
   L.w_a = L.w_b = L.side_r = L.side_c = L.gate = 0;
   if (blocked(c)) {
     const size_t esz = p.dtype == GECC_BF16 ? 2 : 4;
@@ -56,6 +71,37 @@ void make_layout(gecc_ctx* c) {
     L.gate = take(256);
   }
   L.total = off;
+}
+
+// Tile of the product kernel (= granularity of the partial sums), workgroups per tile, workspace layout.
+//
+// 128 x 128: whatever the 256 x 256-tile kernel may take (its partial sums have that granularity) and blocked
+// mode; otherwise products with tiles enough for every compute unit, as long as tiles that hang over the
+// edge do not eat up what the larger tile gains (a saturated chip does a 128 x 128 tile in the time of three
+// 64 x 64 ones: fp32, 256 x 512^3, 428 against 568 us; 64 x 300^3, 61 against 46 us).  64 x 64: the rest
+// (fp32 1024^3 28 against 37 us, 128^3 7.7 against 13.8 us; bf16 1500 x 1000 x 1100 19.5 against 28 us).
+// Workgroups: fp32 tiles of 64 keep four per compute unit busy (1024^3: one workgroup per tile 40 us, two 31,
+// four 28, eight 38), bf16 ones two, to the nearest (1500 x 1000 x 1100, 432 tiles: 19.5 us, split in two 22),
+// fp32 tiles of 128 two (2000 x 1000 x 2000: 83 us, split in two 67).
+// compact: 128 x 128 tiles and 256 workgroups, the plan that needs the least workspace.
+void plan_product(gecc_ctx* c, bool compact) {
+  const gecc_params& p = c->p;
+  const int64_t t128 = (int64_t)((p.n + 127) / 128) * ((p.m + 127) / 128) * p.batch;
+  const int64_t t64 = (int64_t)((p.n + 63) / 64) * ((p.m + 63) / 64) * p.batch;
+  const bool may_be_fast = p.dtype == GECC_BF16 && p.k % 64 == 0 && p.lda % 8 == 0 && p.ldb % 8 == 0 &&
+                           (!p.trans_a || p.n % 8 == 0) && (p.trans_b || p.m % 8 == 0) && (int64_t)p.n * p.m >= 256 * 256;
+  const bool large = t128 >= 256 && p.k >= 256 && 3 * t128 < t64;
+  const int tile = compact || blocked(c) || may_be_fast || large ? 128 : 64;
+  c->tile_m = c->tile_n = tile;
+  c->ntm = (p.n + tile - 1) / tile;
+  c->ntn = (p.m + tile - 1) / tile;
+  if (blocked(c)) c->ksplit = 1;
+  else if (compact || may_be_fast) c->ksplit = ksplit_128(t128, p.k);
+  else if (tile == 64) c->ksplit = p.dtype == GECC_F32 ? ksplit_of(t64, 1024, p.k) : ksplit_of(t64, 512 + (int)(t64 < 512 ? t64 / 2 : 0), p.k);
+  else c->ksplit = p.dtype == GECC_F32 && t128 < 512 && t128 <= SCAN_DONE_WORDS ? 2 : 1;
+  make_layout(c);
+  // (a product that fits the library's static scratch in the compact plan has to fit it in any)
+  if (!compact && c->lay.total > (size_t)GECC_STATIC_SCRATCH_BYTES) plan_product(c, true);
 }
 
 int check_ws(const gecc_ctx* c) {
@@ -398,19 +444,6 @@ int gecc_create(gecc_ctx** out, const gecc_params* p) {
   c->pieces = p->dtype == GECC_BF16 ? 3 : 1;
   c->w_cols_a = (2 * c->pieces * c->nbi + 7) / 8 * 8;
   c->w_cols_b = (2 * c->pieces * c->nbj + 7) / 8 * 8;
-  c->tile_m = 128;
-  c->tile_n = 128;
-  c->ntm = (p->n + c->tile_m - 1) / c->tile_m;
-  c->ntn = (p->m + c->tile_n - 1) / c->tile_n;
-  {
-    // products with far fewer tiles than compute units split k over several workgroups per tile
-    // (128 x 128-tile kernel only; every range keeps at least 128 terms)
-    const int64_t tiles = (int64_t)c->ntm * c->ntn * p->batch;
-    int s = tiles * 2 <= 256 ? (int)(256 / tiles) : 1;
-    if (s > 8) s = 8;
-    while (s > 1 && p->k / s < 128) --s;
-    c->ksplit = p->block_n > 0 ? 1 : s;
-  }
   // slab strides of the partial sums: a multiple of 2 KiB would put the same line of every slab
   // into the same memory channel
   c->rp_ld = p->n % 256 == 0 ? p->n + 16 : p->n;
@@ -426,7 +459,7 @@ int gecc_create(gecc_ctx** out, const gecc_params* p) {
   c->ev_mask = 0;
   c->ev_cap = 0;
   c->ev_n = 0;
-  make_layout(c);
+  plan_product(c, false);
   *out = c;
   return GECC_OK;
 }
@@ -976,6 +1009,7 @@ int gecc_protected_gemm_panels(gecc_ctx* ctx, void* dev_A, void* dev_B, float* d
       q.tau_r1 *= f; q.tau_r2 *= f; q.tau_q1 *= f; q.tau_q2 *= f;
       gecc_ctx* child = nullptr;
       rc = gecc_create(&child, &q);
+      if (!rc && child->lay.total > ctx->lay.total) plan_product(child, true);
       if (rc || child->lay.total > ctx->lay.total) {
         if (child) gecc_destroy(child);
         ctx->n_panel = g;

@@ -1,331 +1,582 @@
-// The data block of the encoded product (Section III, C = A B) on the MFMA units, with the
-// row/column sums that Section V's syndromes need taken from the accumulators before C
-// leaves the compute unit, so that verification never re-reads C from HBM.
+// The data block of the encoded product (Section III, C = A B) on the MFMA units for fp32 operands and
+// for the bf16 products that the 256 x 256-tile kernel does not take (small ones, ragged k, rows that
+// are not 16-byte aligned), with the row/column sums that Section V's syndromes need taken from the
+// accumulators before C leaves the compute unit, so that verification never re-reads C from HBM.
 //
-// Per workgroup: a BM x BN tile of C.  Operand tiles are staged through LDS in a
-// k-contiguous layout (whatever the storage order of the operand is), MFMA fragments are read
-// from there.  After the k loop the tile passes through LDS once more in slabs of rows:
-// planted faults are applied, per-tile row sums (plain and weighted by the local column
-// index + 1) and column sums (plain and weighted by the local row index + 1) are formed, and
-// C is written with full-width stores.
+// Workgroup: a TILE x TILE tile of C (128 or 64), 4 wavefronts (2 x 2), MFMA 16x16x32 bf16.  Operand
+// tiles go HBM -> registers -> LDS, the next k-tile's loads in flight while this one is multiplied; two
+// to five workgroups share a compute unit and cover each other's barriers.  No load assumes an alignment
+// beyond the element's own.
+//
+// fp32 operands run on the bf16 units too: x = x1 + x2 + x3, each piece the bf16 nearest to what is left
+// (8 significand bits and a sign each, so the three hold all 24 bits of x exactly), and
+//   a b = a1 b1 + (a1 b2 + a2 b1) + (a1 b3 + a2 b2 + a3 b1) + terms below 2^-25 |a b|,
+// six exact products per pair, accumulated in fp32.  Native fp32 MFMAs do 64 flop per cycle and SIMD,
+// bf16 ones 1024: six of those are 2.7 times as fast.  Measured: 256 x 512^3 766 -> 430 us (160 TFLOP/s
+// of fp32 products, 960 of bf16 ones), 1024^3 50 -> 28 us, 128^3 28 -> 7.7 us, next to native fp32 MFMAs
+// in the kernel this one replaced, with a result closer to the fp64 product (2.1e-7 -> 6.5e-8 at 128^3,
+// 2.9e-7 -> 9e-8 at 1024^3).  bf16, 1500 x 1000 x 1100 with rows that are not 16-byte aligned: 67 -> 20 us,
+// the loads being vectors whatever the alignment.  What bounds it: the pieces (11 vector instructions per
+// two staged elements) and the two barriers per k-tile, which the other workgroups of the compute unit cover.
+// Where a piece cannot hold its part of x the tile is computed again with native fp32 MFMAs, from the
+// same operands in the same launch:
+//   - some accumulator is not finite (an infinite or NaN operand, |x| that rounds past the largest bf16,
+//     a sum that overflows): the fp32 arithmetic decides what C holds there;
+//   - the operand values a thread stages are not all zero and all below 2^-85: their low pieces get
+//     near the smallest normal number.
 #include "gecc_internal.h"
 
 namespace gecc {
 namespace {
 
+typedef __attribute__((ext_vector_type(2))) float f32x2_t;
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
-typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 
 constexpr int THREADS = 256;
-constexpr int CPAD = 4;   // padding of the C slab rows (floats)
+constexpr float TINY = 0x1p-85f;
 
 template <int DT> struct GT;
 template <> struct GT<GECC_BF16> {
   using T = uint16_t;
-  static constexpr int VEC = 8;    // elements per 16-byte load
-  static constexpr int BK = 32;
-  static constexpr int KPAD = 8;   // LDS row padding (elements)
+  static constexpr int PIECES = 1;
+  static constexpr int BK = 64;
 };
 template <> struct GT<GECC_F32> {
   using T = float;
-  static constexpr int VEC = 4;
-  static constexpr int BK = 16;
-  static constexpr int KPAD = 1;
+  static constexpr int PIECES = 3;
+  static constexpr int BK = 32;
 };
 
-// ---- staging of one operand tile: ROWS (m- or n-index) x BK, into registers then LDS -------
-// KCONTIG: element (r, kk) lives at P[r * ld + kk]; otherwise at P[kk * ld + r].
-template <int DT, int ROWS, bool KCONTIG>
-struct Stager {
-  using G = GT<DT>;
-  using T = typename G::T;
-  static constexpr int VEC = G::VEC;
-  static constexpr int BK = G::BK;
-  static constexpr int LDK = BK + G::KPAD;
-  static constexpr int CHUNKS = ROWS * BK / VEC;
-  static constexpr int PER_THREAD = CHUNKS / THREADS;
-  static_assert(CHUNKS % THREADS == 0, "tile must split evenly over the workgroup");
-  __attribute__((aligned(16))) T reg[PER_THREAD][VEC];
+// LDS of one operand: PIECES planes of tile[row][BK] bf16; the 16-byte chunks of a row are XOR-swizzled so
+// that neither the 16 rows a fragment read touches nor the 16 rows a transposed store writes meet in a bank
+template <int BK> __device__ __forceinline__ int lds_at(int row, int chunk) {
+  constexpr int ROWB = BK * 2;
+  return row * ROWB + ((chunk ^ ((row / (256 / ROWB)) & (BK / 8 - 1))) << 4);
+}
 
-  __device__ __forceinline__ void load(const T* P, int64_t ld, int r0, int k0, int rlim, int klim,
-                                       bool vec_ok) {
+// two neighbouring k-values of a row -> their PIECES packed pairs
+__device__ __forceinline__ void split2(float x0, float x1, uint32_t (&p)[3]) {
 #pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i) {
-      const int c = threadIdx.x + THREADS * i;
-      int r, kk;
-      if (KCONTIG) { r = c / (BK / VEC); kk = (c % (BK / VEC)) * VEC; }
-      else         { kk = c / (ROWS / VEC); r = (c % (ROWS / VEC)) * VEC; }
-      const int gr = r0 + r, gk = k0 + kk;
-      const T* src = KCONTIG ? P + (int64_t)gr * ld + gk : P + (int64_t)gk * ld + gr;
-      const bool full = KCONTIG ? (gr < rlim && gk + VEC <= klim) : (gk < klim && gr + VEC <= rlim);
-      if (full && vec_ok) {
-        *reinterpret_cast<uint4*>(reg[i]) = *reinterpret_cast<const uint4*>(src);
-      } else {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-          const bool in = KCONTIG ? (gr < rlim && gk + e < klim) : (gk < klim && gr + e < rlim);
-          reg[i][e] = in ? src[e] : (T)0;
-        }
-      }
-    }
-  }
-
-  __device__ __forceinline__ void store(T (*S)[LDK]) const {
-#pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i) {
-      const int c = threadIdx.x + THREADS * i;
-      if (KCONTIG) {
-        const int r = c / (BK / VEC), kk = (c % (BK / VEC)) * VEC;
-        if (DT == GECC_BF16) {
-          *reinterpret_cast<uint4*>(&S[r][kk]) = *reinterpret_cast<const uint4*>(reg[i]);
-        } else {
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) S[r][kk + e] = reg[i][e];
-        }
-      } else {
-        const int kk = c / (ROWS / VEC), r = (c % (ROWS / VEC)) * VEC;
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) S[r + e][kk] = reg[i][e];
-      }
-    }
-  }
-};
-
-// ---- one row slab of the C tile, resident in LDS: faults, partial sums, store ---------------
-// Cs holds SLAB rows x BN columns; rows slab_r0.. of the tile.  cs/cw accumulate the column
-// sums of the thread's column (threads < BN) over the slabs.
-template <int BN, int SLAB>
-__device__ __forceinline__ void slab_reduce(float (*Cs)[BN + CPAD], int slab_r0, int tile_r0,
-                                            int tile_c0, int n, int m, float* rowpart_tile,
-                                            float& cs, float& cw) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // row sums: one wavefront per row, lanes stride the columns
-  if (rowpart_tile) {
-    for (int r = wave; r < SLAB; r += THREADS / 64) {
-      float s = 0.f, w = 0.f;
-#pragma unroll
-      for (int c = lane; c < BN; c += 64) {
-        const float v = Cs[r][c];
-        s += v;
-        w = fmaf((float)(c + 1), v, w);
-      }
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) {
-        s += __shfl_down(s, off, 64);
-        w += __shfl_down(w, off, 64);
-      }
-      const int gi = tile_r0 + slab_r0 + r;
-      if (lane == 0 && gi < n) {
-        rowpart_tile[(int64_t)gi * 2] = s;
-        rowpart_tile[(int64_t)gi * 2 + 1] = w;
-      }
-    }
-    if (tid < BN) {
-#pragma unroll 8
-      for (int r = 0; r < SLAB; ++r) {
-        const float v = Cs[r][tid];
-        cs += v;
-        cw = fmaf((float)(slab_r0 + r + 1), v, cw);
-      }
-    }
+  for (int q = 0; q < 3; ++q) {
+    const f32x2_t x = {x0, x1};
+    p[q] = __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2_t));   // round to nearest even
+    x0 -= __uint_as_float(p[q] << 16);
+    x1 -= __uint_as_float(p[q] & 0xffff0000u);
   }
 }
 
-template <int BN, int SLAB>
-__device__ __forceinline__ void slab_store(float (*Cs)[BN + CPAD], int slab_r0, int tile_r0,
-                                           int tile_c0, int n, int m, float* C, int64_t ldc,
-                                           bool vec_ok) {
-  constexpr int V4 = BN / 4;
-  for (int o = threadIdx.x; o < SLAB * V4; o += THREADS) {
-    const int r = o / V4, c = (o % V4) * 4;
-    const int gi = tile_r0 + slab_r0 + r, gj = tile_c0 + c;
-    if (gi >= n || gj >= m) continue;
-    float* dst = C + (int64_t)gi * ldc + gj;
-    if (vec_ok && gj + 4 <= m) {
-      *reinterpret_cast<float4*>(dst) = *reinterpret_cast<const float4*>(&Cs[r][c]);
+// ---- staging of one operand tile: ROWS (m- or n-index) x BK ------------------------------------
+// KC: element (r, kk) lives at P[r * ld + kk]; otherwise at P[kk * ld + r].  Rows past the last one are
+// clamped to it (what they accumulate is masked in the epilogue), k past the end reads as zero.
+template <int DT, int ROWS, bool KC> struct Stager;
+
+// k contiguous: 16-byte loads, eight lanes to a row
+template <int DT, int ROWS>
+struct Stager<DT, ROWS, true> {
+  using T = typename GT<DT>::T;
+  static constexpr int BK = GT<DT>::BK, V = 16 / (int)sizeof(T), N = ROWS * BK / V / THREADS;
+  static constexpr int PLANE = ROWS * BK * 2;
+  const T* src[N];
+  uint4 reg[N];
+  float big[N];     // largest magnitude this thread has staged, per row
+  int kk, klim;
+  __device__ __forceinline__ void init(const T* P, int64_t ld, int r0, int rlim, int k_end) {
+    kk = (threadIdx.x & 7) * V;
+    klim = k_end;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      src[i] = P + (int64_t)min(r0 + (int)(threadIdx.x >> 3) + 32 * i, rlim - 1) * ld + kk;
+      big[i] = 0.f;
+    }
+  }
+  __device__ __forceinline__ void load(int k0) {
+    if (k0 + BK <= klim) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) __builtin_memcpy(&reg[i], src[i] + k0, 16);
     } else {
-      for (int e = 0; e < 4 && gj + e < m; ++e) dst[e] = Cs[r][c + e];
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        T x[V];
+#pragma unroll
+        for (int e = 0; e < V; ++e) x[e] = k0 + kk + e < klim ? src[i][k0 + e] : (T)0;
+        __builtin_memcpy(&reg[i], x, 16);
+      }
     }
   }
-}
-
-// planted faults (distinct positions): each thread takes a strided share of the list
-__device__ __forceinline__ void apply_faults(const gecc_fault* faults, int n_faults, int b,
-                                             int r_lo, int r_hi, int c_lo, int c_hi, float* Cs,
-                                             int ldcs) {
-  for (int f = threadIdx.x; f < n_faults; f += THREADS) {
-    const gecc_fault ft = faults[f];
-    if (ft.batch == b && ft.row >= r_lo && ft.row < r_hi && ft.col >= c_lo && ft.col < c_hi)
-      Cs[(ft.row - r_lo) * ldcs + (ft.col - c_lo)] += ft.offset;
+  __device__ __forceinline__ void store(char* S) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int row = (threadIdx.x >> 3) + 32 * i;
+      if constexpr (DT == GECC_BF16) {
+        *reinterpret_cast<uint4*>(S + lds_at<BK>(row, threadIdx.x & 7)) = reg[i];
+      } else {
+        const float x[4] = {__uint_as_float(reg[i].x), __uint_as_float(reg[i].y), __uint_as_float(reg[i].z), __uint_as_float(reg[i].w)};
+        uint32_t a[3], b[3];
+        split2(x[0], x[1], a);
+        split2(x[2], x[3], b);
+        big[i] = fmaxf(fmaxf(fmaxf(big[i], fabsf(x[0])), fmaxf(fabsf(x[1]), fabsf(x[2]))), fabsf(x[3]));
+        char* dst = S + lds_at<BK>(row, (threadIdx.x & 7) >> 1) + (threadIdx.x & 1) * 8;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) *reinterpret_cast<uint2*>(dst + q * PLANE) = make_uint2(a[q], b[q]);
+      }
+    }
   }
+  __device__ __forceinline__ bool tiny() const {
+    bool t = false;
+#pragma unroll
+    for (int i = 0; i < N; ++i) t = t || (big[i] > 0.f && big[i] < TINY);
+    return t;
+  }
+  // the fp32 values as they are, rows of BK + 1 floats (native fp32 pass)
+  __device__ __forceinline__ void store_plain(float* S) const {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      float* d = S + ((threadIdx.x >> 3) + 32 * i) * (BK + 1) + kk;
+      d[0] = __uint_as_float(reg[i].x); d[1] = __uint_as_float(reg[i].y);
+      d[2] = __uint_as_float(reg[i].z); d[3] = __uint_as_float(reg[i].w);
+    }
+  }
+};
+
+// r contiguous, fp32: a thread owns one row and KPT consecutive k (a wavefront reads 256 contiguous bytes
+// of a k-row per instruction), so that its stores are whole 16-byte chunks along k
+template <int ROWS>
+struct Stager<GECC_F32, ROWS, false> {
+  static constexpr int BK = GT<GECC_F32>::BK, KPT = ROWS * BK / THREADS;
+  static constexpr int PLANE = ROWS * BK * 2;
+  const float* src;
+  float reg[KPT];
+  float big;
+  int64_t ld;
+  int row, kg, klim;
+  __device__ __forceinline__ void init(const float* P, int64_t ld_, int r0, int rlim, int k_end) {
+    row = threadIdx.x & (ROWS - 1);
+    kg = __builtin_amdgcn_readfirstlane(threadIdx.x / ROWS) * KPT;     // ROWS >= 64: one k group per wavefront
+    ld = ld_; klim = k_end;
+    src = P + min(r0 + row, rlim - 1);
+    big = 0.f;
+  }
+  __device__ __forceinline__ void load(int k0) {
+    if (k0 + BK <= klim) {
+#pragma unroll
+      for (int x = 0; x < KPT; ++x) reg[x] = src[(int64_t)(k0 + kg + x) * ld];
+    } else {
+#pragma unroll
+      for (int x = 0; x < KPT; ++x) {
+        const int k = k0 + kg + x;
+        reg[x] = k < klim ? src[(int64_t)k * ld] : 0.f;
+      }
+    }
+  }
+  __device__ __forceinline__ void store(char* S) {
+#pragma unroll
+    for (int c = 0; c < KPT / 8; ++c) {
+      uint32_t p[4][3];
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        const float x0 = reg[c * 8 + 2 * h], x1 = reg[c * 8 + 2 * h + 1];
+        split2(x0, x1, p[h]);
+        big = fmaxf(fmaxf(big, fabsf(x0)), fabsf(x1));
+      }
+      char* dst = S + lds_at<BK>(row, (kg >> 3) + c);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) *reinterpret_cast<uint4*>(dst + q * PLANE) = make_uint4(p[0][q], p[1][q], p[2][q], p[3][q]);
+    }
+  }
+  __device__ __forceinline__ bool tiny() const { return big > 0.f && big < TINY; }
+  __device__ __forceinline__ void store_plain(float* S) const {
+#pragma unroll
+    for (int x = 0; x < KPT; ++x) S[row * (BK + 1) + kg + x] = reg[x];
+  }
+};
+
+// r contiguous, bf16: a thread owns two neighbouring rows (one 4-byte load per k) and KPT consecutive k
+template <int ROWS>
+struct Stager<GECC_BF16, ROWS, false> {
+  static constexpr int BK = GT<GECC_BF16>::BK, KPT = ROWS * BK / THREADS / 2;
+  static constexpr int PLANE = ROWS * BK * 2;
+  const uint16_t* src;
+  uint32_t reg[KPT];
+  int64_t ld;
+  int row, kg, klim, shift;
+  bool single;
+  __device__ __forceinline__ void init(const uint16_t* P, int64_t ld_, int r0, int rlim, int k_end) {
+    row = 2 * (threadIdx.x & (ROWS / 2 - 1));
+    kg = (threadIdx.x / (ROWS / 2)) * KPT;
+    ld = ld_; klim = k_end;
+    // the last row of an odd number of them is read as the second of a pair; an operand of one row has no pairs
+    const int r = min(r0 + row, rlim - 1), base = max(0, min(r, rlim - 2));
+    shift = r > base ? 16 : 0;
+    single = rlim < 2;
+    src = P + base;
+  }
+  __device__ __forceinline__ uint32_t pair(int k) const {
+    uint32_t v;
+    if (single) return src[(int64_t)k * ld];
+    __builtin_memcpy(&v, src + (int64_t)k * ld, 4);
+    return v >> shift;
+  }
+  __device__ __forceinline__ void load(int k0) {
+    if (k0 + BK <= klim && !single) {
+#pragma unroll
+      for (int x = 0; x < KPT; ++x) {
+        uint32_t v;
+        __builtin_memcpy(&v, src + (int64_t)(k0 + kg + x) * ld, 4);
+        reg[x] = v >> shift;
+      }
+    } else {
+#pragma unroll
+      for (int x = 0; x < KPT; ++x) reg[x] = k0 + kg + x < klim ? pair(k0 + kg + x) : 0u;
+    }
+  }
+  __device__ __forceinline__ void store(char* S) {
+#pragma unroll
+    for (int c = 0; c < KPT / 8; ++c) {
+      uint32_t lo[4], hi[4];
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        const uint32_t v0 = reg[c * 8 + 2 * h], v1 = reg[c * 8 + 2 * h + 1];
+        lo[h] = (v0 & 0xffffu) | (v1 << 16);
+        hi[h] = (v0 >> 16) | (v1 & 0xffff0000u);
+      }
+      *reinterpret_cast<uint4*>(S + lds_at<BK>(row, (kg >> 3) + c)) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+      *reinterpret_cast<uint4*>(S + lds_at<BK>(row + 1, (kg >> 3) + c)) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+    }
+  }
+};
+
+// sum over the 16 lanes of a row of lanes, in every one of them
+__device__ __forceinline__ float row16_sum(float x) {
+  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x128, 0xf, 0xf, false));   // row_ror:8
+  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x124, 0xf, 0xf, false));   // row_ror:4
+  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x122, 0xf, 0xf, false));   // row_ror:2
+  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x121, 0xf, 0xf, false));   // row_ror:1
+  return x;
 }
 
 // -------------------------------------------------------------------------------------------
-template <int DT, bool KCA, bool KCB>
-__global__ __launch_bounds__(THREADS) void gemm_kernel(GemmArgs a) {
-  using G = GT<DT>;
-  using T = typename G::T;
-  constexpr int BM = 128, BN = 128, BK = G::BK, LDK = BK + G::KPAD, SLAB = 64;
-  // k-split (products of few tiles): ksplit workgroups share a tile, one per range of k
+// Grid: one dimension, tiles x batch x ksplit workgroups.  Consecutive workgroups go to the 8 XCDs in
+// turn, so every XCD is given a contiguous range of the (item, split, tile row, tile column) sequence:
+// tiles that share operand panels share an L2.
+template <int DT, bool KCA, bool KCB, int TILE>
+__global__ __launch_bounds__(THREADS, 2) void gemm_tile(GemmArgs a) {
+  using T = typename GT<DT>::T;
+  constexpr int BK = GT<DT>::BK, PIECES = GT<DT>::PIECES, W = TILE / 2, NI = W / 16;   // W x W per wavefront
+  constexpr int PLANE = TILE * BK * 2, OPERAND = PIECES * PLANE;
+  constexpr int PLAIN = DT == GECC_F32 ? 2 * TILE * (BK + 1) * 4 : 0;
+  constexpr int FAULTS = GECC_MAX_FAULTS * 8 + 16;        // list of the faults that strike this tile
+  constexpr int SUMS = 2 * 2 * TILE * 8;                  // row and column sums of the wavefronts
+  constexpr int SM0 = 2 * OPERAND > PLAIN ? 2 * OPERAND : PLAIN;
+  constexpr int SM1 = FAULTS > SUMS ? FAULTS : SUMS;
+  __shared__ __attribute__((aligned(16))) char smem[SM0 > SM1 ? SM0 : SM1];
+  char* As = smem;
+  char* Bs = smem + OPERAND;
+
   const int S = a.ksplit > 1 ? a.ksplit : 1;
-  const int b = (int)blockIdx.z / S, split = (int)blockIdx.z % S;
+  const int ntm = (a.n + TILE - 1) / TILE, ntn = (a.m + TILE - 1) / TILE;
+  int id;
+  {
+    const int N = gridDim.x, per = N / 8, rem = N - per * 8, x = blockIdx.x & 7;
+    id = x * per + min(x, rem) + ((int)blockIdx.x >> 3);
+  }
+  const int tn = id % ntn, tm = (id / ntn) % ntm, bs = id / (ntn * ntm);
+  const int b = bs / S, split = bs - b * S;
   const int k_begin = S > 1 ? min(a.k, split * a.k_per) : 0;
   const int k_end = S > 1 ? min(a.k, k_begin + a.k_per) : a.k;
-  const int tm = blockIdx.y, tn = blockIdx.x;
-  const int tile_r0 = tm * BM, tile_c0 = tn * BN;
+  const int tile_r0 = tm * TILE, tile_c0 = tn * TILE;
   const T* A = reinterpret_cast<const T*>(a.A) + (int64_t)b * a.sa;
   const T* B = reinterpret_cast<const T*>(a.B) + (int64_t)b * a.sb;
-  float* C = a.C + (int64_t)b * a.sc;
 
-  constexpr int AB_BYTES = (BM + BN) * LDK * (int)sizeof(T);
-  constexpr int CS_BYTES = SLAB * (BN + CPAD) * (int)sizeof(float);
-  __shared__ __attribute__((aligned(16))) char smem[AB_BYTES > CS_BYTES ? AB_BYTES : CS_BYTES];
-  T (*As)[LDK] = reinterpret_cast<T (*)[LDK]>(smem);
-  T (*Bs)[LDK] = reinterpret_cast<T (*)[LDK]>(smem + BM * LDK * sizeof(T));
-  float (*Cs)[BN + CPAD] = reinterpret_cast<float (*)[BN + CPAD]>(smem);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wr = wave >> 1, wc = wave & 1;
+  const int l16 = lane & 15, lg = lane >> 4;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wr = wave >> 1, wc = wave & 1;          // 2 x 2 wavefronts, 64 x 64 each
-  const int l32 = lane & 31, lhi = lane >> 5;
-
-  const bool vecA = (reinterpret_cast<uintptr_t>(A) % 16 == 0) && (a.lda % G::VEC == 0);
-  const bool vecB = (reinterpret_cast<uintptr_t>(B) % 16 == 0) && (a.ldb % G::VEC == 0);
-
-  f32x16_t acc[2][2];
+  // acc[i][j][v] = C[16 i + 4 lg + v][16 j + l16] of the wavefront's sub-tile
+  f32x4_t acc[NI][NI];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < NI; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < NI; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+      for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
 
-  Stager<DT, BM, KCA> sa;
-  Stager<DT, BN, KCB> sb;
-  sa.load(A, a.lda, tile_r0, k_begin, a.n, k_end, vecA);
-  sb.load(B, a.ldb, tile_c0, k_begin, a.m, k_end, vecB);
+  // Second set of accumulators.  fp32: for the five small pairs, so that the large sums are rounded once
+  // per 32 terms and not six times (512^3: 1.3e-7 from the fp64 product instead of 1.6e-7, native fp32
+  // MFMAs 2.1e-7).  bf16, 64 x 64: for every other 32 terms (chains half as long).
+  constexpr bool TWO = PIECES > 1 || TILE == 64;
+  f32x4_t low[NI][NI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) low[i][j][v] = 0.f;
+
+  Stager<DT, TILE, KCA> sa;
+  Stager<DT, TILE, KCB> sb;
+  sa.init(A, a.lda, tile_r0, a.n, k_end);
+  sb.init(B, a.ldb, tile_c0, a.m, k_end);
+  if (k_begin < k_end) { sa.load(k_begin); sb.load(k_begin); }
 
   for (int k0 = k_begin; k0 < k_end; k0 += BK) {
     __syncthreads();               // previous tile fully consumed
     sa.store(As);
     sb.store(Bs);
     __syncthreads();
-    if (k0 + BK < k_end) {         // prefetch the next tile into registers
-      sa.load(A, a.lda, tile_r0, k0 + BK, a.n, k_end, vecA);
-      sb.load(B, a.ldb, tile_c0, k0 + BK, a.m, k_end, vecB);
-    }
-    if (DT == GECC_BF16) {
+    if (k0 + BK < k_end) { sa.load(k0 + BK); sb.load(k0 + BK); }
 #pragma unroll
-      for (int ks = 0; ks < BK; ks += 16) {
-        bf16x8_t fa[2], fb[2];
+    for (int ks = 0; ks < BK / 32; ++ks) {
+      bf16x8_t fb[NI][PIECES];
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-          fa[i] = *reinterpret_cast<const bf16x8_t*>(&As[wr * 64 + i * 32 + l32][ks + lhi * 8]);
+      for (int j = 0; j < NI; ++j)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-          fb[j] = *reinterpret_cast<const bf16x8_t*>(&Bs[wc * 64 + j * 32 + l32][ks + lhi * 8]);
+        for (int q = 0; q < PIECES; ++q)
+          fb[j][q] = *reinterpret_cast<const bf16x8_t*>(Bs + q * PLANE + lds_at<BK>(wc * W + j * 16 + l16, ks * 4 + lg));
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < NI; ++i) {
+        bf16x8_t fa[PIECES];
 #pragma unroll
-          for (int j = 0; j < 2; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+        for (int q = 0; q < PIECES; ++q)
+          fa[q] = *reinterpret_cast<const bf16x8_t*>(As + q * PLANE + lds_at<BK>(wr * W + i * 16 + l16, ks * 4 + lg));
+        // pairs of pieces, the small ones first
+#pragma unroll
+        for (int o = PIECES - 1; o > 0; --o)
+#pragma unroll
+          for (int q = o; q >= 0; --q)
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+              low[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[q], fb[j][o - q], low[i][j], 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+          f32x4_t& sum = PIECES == 1 && TWO && (ks & 1) ? low[i][j] : acc[i][j];
+          sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[0], fb[j][0], sum, 0, 0, 0);
+        }
       }
-    } else {
+    }
+  }
+
+  if constexpr (TWO) {
 #pragma unroll
-      for (int ks = 0; ks < BK; ks += 2) {
-        float fa[2], fb[2];
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-          fa[i] = *reinterpret_cast<const float*>(&As[wr * 64 + i * 32 + l32][ks + lhi]);
+      for (int j = 0; j < NI; ++j)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-          fb[j] = *reinterpret_cast<const float*>(&Bs[wc * 64 + j * 32 + l32][ks + lhi]);
+        for (int v = 0; v < 4; ++v) acc[i][j][v] += low[i][j][v];
+  }
+  // rows and columns past the end count as zero
+  if (tile_r0 + TILE > a.n || tile_c0 + TILE > a.m) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
-          for (int j = 0; j < 2; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i], fb[j], acc[i][j], 0, 0, 0);
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (tile_r0 + wr * W + i * 16 + lg * 4 + v >= a.n || tile_c0 + wc * W + j * 16 + l16 >= a.m) acc[i][j][v] = 0.f;
+  }
+
+  if constexpr (DT == GECC_F32) {
+    float worst = 0.f;             // 0, or NaN when some accumulator is not finite
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) worst = fmaf(acc[i][j][v], 0.f, worst);
+    if (__syncthreads_or(worst != 0.f || sa.tiny() || sb.tiny())) {
+      // native fp32 pass (see the head of this file)
+      float* Ap = reinterpret_cast<float*>(smem);
+      float* Bp = Ap + TILE * (BK + 1);
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
+      for (int k0 = k_begin; k0 < k_end; k0 += BK) {
+        sa.load(k0);
+        sb.load(k0);
+        __syncthreads();
+        sa.store_plain(Ap);
+        sb.store_plain(Bp);
+        __syncthreads();
+#pragma unroll 1
+        for (int ks = 0; ks < BK; ks += 4) {
+          float fb[NI];
+#pragma unroll
+          for (int j = 0; j < NI; ++j) fb[j] = Bp[(wc * W + j * 16 + l16) * (BK + 1) + ks + lg];
+#pragma unroll
+          for (int i = 0; i < NI; ++i) {
+            const float fa = Ap[(wr * W + i * 16 + l16) * (BK + 1) + ks + lg];
+#pragma unroll
+            for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa, fb[j], acc[i][j], 0, 0, 0);
+          }
+        }
+      }
+      if (tile_r0 + TILE > a.n || tile_c0 + TILE > a.m) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+          for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              if (tile_r0 + wr * W + i * 16 + lg * 4 + v >= a.n || tile_c0 + wc * W + j * 16 + l16 >= a.m) acc[i][j][v] = 0.f;
       }
     }
   }
 
   if (S > 1) {
-    // Every workgroup of the tile leaves its partial sums in memory; the one that arrives last adds
-    // them all up in the order of the k ranges (so the result does not depend on which one that
-    // is) and goes on with the tile.
-    const int64_t tile_id = ((int64_t)b * gridDim.y + tm) * gridDim.x + tn;
-    float* part = a.split_part + tile_id * S * (BM * BN);
-    float* mine = part + (int64_t)split * (BM * BN);
+    // k-split: every workgroup of the tile leaves its partial sums in memory (in register order: whole
+    // lines per store); the one that arrives last adds them all up in the order of the k ranges (so the
+    // result does not depend on which one that is) and goes on with the tile.
+    const int64_t tile_id = ((int64_t)b * ntm + tm) * ntn + tn;
+    float* part = a.split_part + tile_id * S * (TILE * TILE);
+    float* mine = part + (int64_t)split * (TILE * TILE) + tid;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < NI; ++j)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int r = wr * 64 + i * 32 + (v >> 2) * 8 + lhi * 4 + (v & 3);
-          store_dev(mine + r * BN + wc * 64 + j * 32 + l32, acc[i][j][v]);
-        }
+        for (int v = 0; v < 4; ++v) store_dev(mine + ((i * NI + j) * 4 + v) * THREADS, acc[i][j][v]);
     if (!arrive_last(a.split_done + tile_id, (uint32_t)S, reinterpret_cast<int*>(smem))) return;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < NI; ++j)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+        for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
     for (int q = 0; q < S; ++q) {
-      const float* src = part + (int64_t)q * (BM * BN);
+      const float* src = part + (int64_t)q * (TILE * TILE) + tid;
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < NI; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < NI; ++j)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int r = wr * 64 + i * 32 + (v >> 2) * 8 + lhi * 4 + (v & 3);
-            acc[i][j][v] += load_dev(src + r * BN + wc * 64 + j * 32 + l32);
-          }
+          for (int v = 0; v < 4; ++v) acc[i][j][v] += load_dev(src + ((i * NI + j) * 4 + v) * THREADS);
     }
   }
 
-  // ---- epilogue: the tile goes through LDS in two slabs of 64 rows -------------------------
-  const bool epi = a.rowpart != nullptr;
-  float* rowpart_tile = epi ? a.rowpart + ((int64_t)b * a.ntn + tn) * a.rp_ld * 2 : nullptr;
-  const bool vecC = (reinterpret_cast<uintptr_t>(C) % 16 == 0) && (a.ldc % 4 == 0);
-  float cs = 0.f, cw = 0.f;
-#pragma unroll
-  for (int slab = 0; slab < BM / SLAB; ++slab) {
+  // ---- epilogue, from the accumulators -------------------------------------------------------------
+  // Test faults (none in production calls): the workgroup searches the list for those that strike its
+  // tile, then every wavefront adds them to its accumulators.
+  if (a.n_faults > 0) {
+    int* hits = reinterpret_cast<int*>(smem);
+    int2* hit = reinterpret_cast<int2*>(smem + 16);
     __syncthreads();
-    if (wr == slab) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int r = i * 32 + (v >> 2) * 8 + lhi * 4 + (v & 3);
-            Cs[r][wc * 64 + j * 32 + l32] = acc[i][j][v];
-          }
+    if (tid == 0) *hits = 0;
+    __syncthreads();
+    for (int f = tid; f < a.n_faults; f += THREADS) {
+      const gecc_fault ft = a.faults[f];
+      const int r = ft.row - tile_r0, c = ft.col - tile_c0;
+      if (ft.batch == b + a.fault_bias && r >= 0 && r < min(TILE, a.n - tile_r0) && c >= 0 && c < min(TILE, a.m - tile_c0))
+        hit[atomicAdd(hits, 1)] = make_int2(r * TILE + c, __float_as_int(ft.offset));
     }
     __syncthreads();
-    const int r_lo = tile_r0 + slab * SLAB;
-    apply_faults(a.faults, a.n_faults, b + a.fault_bias, r_lo, min(r_lo + SLAB, a.n), tile_c0,
-                 min(tile_c0 + BN, a.m), &Cs[0][0], BN + CPAD);
-    if (a.n_faults > 0) __syncthreads();
-    slab_reduce<BN, SLAB>(Cs, slab * SLAB, tile_r0, tile_c0, a.n, a.m, rowpart_tile, cs, cw);
-    slab_store<BN, SLAB>(Cs, slab * SLAB, tile_r0, tile_c0, a.n, a.m, C, a.ldc, vecC);
+    const int nh = *hits;
+    for (int f = 0; f < nh; ++f) {
+      const int r = hit[f].x / TILE - wr * W, c = hit[f].x % TILE - wc * W;
+      const float off = __int_as_float(hit[f].y);
+      const bool mine = r >= 0 && r < W && c >= 0 && c < W && ((r >> 2) & 3) == lg && (c & 15) == l16;
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            if (mine && i == r >> 4 && j == c >> 4 && v == (r & 3)) acc[i][j][v] += off;
+    }
   }
-  if (epi && tid < BN && tile_c0 + tid < a.m) {
-    float* cp = a.colpart + (((int64_t)b * a.ntm + tm) * a.cp_ld + tile_c0 + tid) * 2;
-    cp[0] = cs;
-    cp[1] = cw;
+
+  // C: the registers of two neighbouring 16-column blocks first trade their odd / even groups of 16 lanes
+  // (v_permlane16_swap): each then holds 2 rows x 32 consecutive columns, two full lines per store
+  {
+    const int R0 = tile_r0 + wr * W + (lg >> 1) * 8, C0 = tile_c0 + wc * W + (lg & 1) * 16 + l16;
+    float* C = a.C + (int64_t)b * a.sc + (int64_t)R0 * a.ldc + C0;
+    const bool whole = tile_r0 + TILE <= a.n && tile_c0 + TILE <= a.m;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int jp = 0; jp < NI / 2; ++jp) {
+          float t0 = acc[i][2 * jp][v], t1 = acc[i][2 * jp + 1][v];
+          // (inline: this compiler's builtin for the swap loses its second result; the wait states are the
+          // ones a swap needs after a vector instruction wrote its operands)
+          asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(t0), "+v"(t1));
+          float* dst = C + (int64_t)(i * 16 + v) * a.ldc + jp * 32;
+          if (whole) {
+            dst[0] = t0;
+            dst[4 * a.ldc] = t1;
+          } else if (C0 + jp * 32 < a.m) {
+            if (R0 + i * 16 + v < a.n) dst[0] = t0;
+            if (R0 + i * 16 + v + 4 < a.n) dst[4 * a.ldc] = t1;
+          }
+        }
   }
-  if (epi && tm == 0 && tn == 0 && a.pg_out) form_pg(a, b, reinterpret_cast<double*>(smem));   // P_g, once per batch item
+  if (!a.rowpart) return;
+
+  // Row sums: a lane adds its columns of a row (plain, and u = sum of j x_j: the block part of the column
+  // weight), the 16 lanes of a group are added across the lanes; lane l16 of a group keeps row number
+  // l16 = 4 i + v of its 4 NI.  Column sums: in the lane, then across the four groups; group lg keeps block lg.
+  float2* rowred = reinterpret_cast<float2*>(smem);          // [2: wc][TILE]
+  float2* colred = rowred + 2 * TILE;                         // [2: wr][TILE]
+  __syncthreads();
+  {
+    float ks = 0.f, kw = 0.f;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        float s = acc[i][0][v], u = 0.f;
+#pragma unroll
+        for (int j = 1; j < NI; ++j) { s += acc[i][j][v]; u = fmaf((float)j, acc[i][j][v], u); }
+        const float w = row16_sum(fmaf((float)(l16 + 1), s, 16.f * u));
+        s = row16_sum(s);
+        if (l16 == i * 4 + v) { ks = s; kw = w; }
+      }
+    if (l16 < 4 * NI)
+      rowred[wc * TILE + wr * W + (l16 >> 2) * 16 + lg * 4 + (l16 & 3)] = make_float2(ks, fmaf((float)(wc * W), ks, kw));
+    float cs = 0.f, cw = 0.f;
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      float s = 0.f, w = 0.f;
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) { s += acc[i][j][v]; w = fmaf((float)(i * 16 + v + 1), acc[i][j][v], w); }
+      w = fmaf((float)(lg * 4), s, w);
+      s += __shfl_xor(s, 16, 64); w += __shfl_xor(w, 16, 64);
+      s += __shfl_xor(s, 32, 64); w += __shfl_xor(w, 32, 64);
+      if (lg == j) { cs = s; cw = w; }
+    }
+    if (lg < NI) colred[wr * TILE + wc * W + lg * 16 + l16] = make_float2(cs, fmaf((float)(wr * W), cs, cw));
+  }
+  __syncthreads();
+  if (tid < TILE) {
+    if (tile_r0 + tid < a.n)
+      *reinterpret_cast<float2*>(a.rowpart + (((int64_t)b * a.ntn + tn) * a.rp_ld + tile_r0 + tid) * 2) =
+          make_float2(rowred[tid].x + rowred[TILE + tid].x, rowred[tid].y + rowred[TILE + tid].y);
+  } else if (tid < 2 * TILE) {
+    const int c = tid - TILE;
+    if (tile_c0 + c < a.m)
+      *reinterpret_cast<float2*>(a.colpart + (((int64_t)b * a.ntm + tm) * a.cp_ld + tile_c0 + c) * 2) =
+          make_float2(colred[c].x + colred[TILE + c].x, colred[c].y + colred[TILE + c].y);
+  }
+  if (tm == 0 && tn == 0 && a.pg_out) {      // P_g, once per batch item
+    __syncthreads();
+    form_pg(a, b, reinterpret_cast<double*>(smem));
+  }
 }
 
 // -------------------------------------------------------------------------------------------
-// Stand-alone partial sums of a C that sits in HBM (same 128 x 128 tiling and workspace layout
-// as the fused epilogues).  HBM-bound: every thread streams 16 rows x 4 columns with 16-byte
-// loads (two full 512-byte tile rows per wavefront instruction), keeps its row and column
-// partial sums in registers, and the workgroup combines them through LDS in a fixed order.
+// Stand-alone partial sums of a C that sits in HBM (same TILE x TILE tiling and workspace layout
+// as the fused epilogues).  HBM-bound: every thread streams RPT rows x 4 columns with 16-byte
+// loads (full tile rows per wavefront instruction), keeps its row and column partial sums in
+// registers, and the workgroup combines them through LDS in a fixed order.
+template <int TILE>
 __global__ __launch_bounds__(THREADS) void partials_kernel(PartialArgs a) {
+  constexpr int CG = TILE / 4, RG = THREADS / CG, RPT = TILE / RG;   // column groups of 4, row groups of RPT
   const int b = blockIdx.z;
   if (a.gate) {
     const int32_t g = *reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(a.gate) +
@@ -333,26 +584,26 @@ __global__ __launch_bounds__(THREADS) void partials_kernel(PartialArgs a) {
     if (g != a.gate_value) return;
   }
   const int tm = blockIdx.y, tn = blockIdx.x;
-  const int tile_r0 = tm * 128, tile_c0 = tn * 128;
+  const int tile_r0 = tm * TILE, tile_c0 = tn * TILE;
   const float* C = a.C + (int64_t)b * a.sc;
   const int tid = threadIdx.x;
-  const int cg = tid & 31, rg = tid >> 5;          // 32 column groups of 4, 8 row groups of 16
+  const int cg = tid % CG, rg = tid / CG;
   const int gj = tile_c0 + cg * 4;
   const bool vec = (reinterpret_cast<uintptr_t>(C) % 16 == 0) && (a.ldc % 4 == 0) && gj + 4 <= a.m;
-  __shared__ float red_row[2][128][33];
-  __shared__ float red_col[2][8][128];
+  __shared__ float red_row[2][TILE][CG + 1];
+  __shared__ float red_col[2][RG][TILE];
   float cs[4] = {0.f, 0.f, 0.f, 0.f}, cw[4] = {0.f, 0.f, 0.f, 0.f};
-  // the kernel is a stream over C: all 16 loads of a thread are issued before the first is used
+  // the kernel is a stream over C: all loads of a thread are issued before the first is used
   // (rows past the end are clamped, not branched on, and count as zero below)
-  float4 pre[16];
+  float4 pre[RPT];
   if (vec) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
-      pre[r] = *reinterpret_cast<const float4*>(C + (int64_t)min(tile_r0 + rg * 16 + r, a.n - 1) * a.ldc + gj);
+    for (int r = 0; r < RPT; ++r)
+      pre[r] = *reinterpret_cast<const float4*>(C + (int64_t)min(tile_r0 + rg * RPT + r, a.n - 1) * a.ldc + gj);
   }
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int rl = rg * 16 + r, gi = tile_r0 + rl;
+  for (int r = 0; r < RPT; ++r) {
+    const int rl = rg * RPT + r, gi = tile_r0 + rl;
     float x[4] = {0.f, 0.f, 0.f, 0.f};
     if (gi < a.n) {
       if (vec) {
@@ -379,20 +630,20 @@ __global__ __launch_bounds__(THREADS) void partials_kernel(PartialArgs a) {
     red_col[1][rg][cg * 4 + e] = cw[e];
   }
   __syncthreads();
-  if (tid < 128) {
+  if (tid < TILE) {
     float s = 0.f, w = 0.f;
 #pragma unroll
-    for (int c = 0; c < 32; ++c) { s += red_row[0][tid][c]; w += red_row[1][tid][c]; }
+    for (int c = 0; c < CG; ++c) { s += red_row[0][tid][c]; w += red_row[1][tid][c]; }
     const int gi = tile_r0 + tid;
     if (gi < a.n) {
       float2* rp = reinterpret_cast<float2*>(a.rowpart + (((int64_t)b * a.ntn + tn) * a.rp_ld + gi) * 2);
       *rp = make_float2(s, w);
     }
-  } else {
-    const int c = tid - 128;
+  } else if (tid < 2 * TILE) {
+    const int c = tid - TILE;
     float s = 0.f, w = 0.f;
 #pragma unroll
-    for (int g = 0; g < 8; ++g) { s += red_col[0][g][c]; w += red_col[1][g][c]; }
+    for (int g = 0; g < RG; ++g) { s += red_col[0][g][c]; w += red_col[1][g][c]; }
     const int gc = tile_c0 + c;
     if (gc < a.m) {
       float2* cp = reinterpret_cast<float2*>(a.colpart + (((int64_t)b * a.ntm + tm) * a.cp_ld + gc) * 2);
@@ -401,32 +652,34 @@ __global__ __launch_bounds__(THREADS) void partials_kernel(PartialArgs a) {
   }
 }
 
-template <int DT>
-hipError_t launch_dt(const GemmArgs& a0, hipStream_t st) {
+template <int DT, int TILE>
+hipError_t launch_tile(const GemmArgs& a0, hipStream_t st) {
   GemmArgs a = a0;
-  const int ntiles = ((a.m + 127) / 128) * ((a.n + 127) / 128);
-  if (a.ksplit > 1 && a.split_part && a.split_done && (int64_t)ntiles * a.batch <= SCAN_DONE_WORDS) {
+  const int64_t tiles = (int64_t)((a.m + TILE - 1) / TILE) * ((a.n + TILE - 1) / TILE) * a.batch;
+  if (a.ksplit > 1 && a.split_part && a.split_done && tiles <= SCAN_DONE_WORDS) {
     const int bk = GT<DT>::BK;
     a.k_per = ((a.k + a.ksplit - 1) / a.ksplit + bk - 1) / bk * bk;
   } else {
     a.ksplit = 1;
   }
-  dim3 grid((a.m + 127) / 128, (a.n + 127) / 128, a.batch * a.ksplit);
+  if (tiles * a.ksplit > 0x7fffffff) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)(tiles * a.ksplit));
   // k-contiguous storage: A when not transposed, B when transposed
   const bool kca = a.trans_a == 0, kcb = a.trans_b != 0;
-  if (kca && kcb)        hipLaunchKernelGGL((gemm_kernel<DT, true, true>), grid, dim3(THREADS), 0, st, a);
-  else if (kca && !kcb)  hipLaunchKernelGGL((gemm_kernel<DT, true, false>), grid, dim3(THREADS), 0, st, a);
-  else if (!kca && kcb)  hipLaunchKernelGGL((gemm_kernel<DT, false, true>), grid, dim3(THREADS), 0, st, a);
-  else                   hipLaunchKernelGGL((gemm_kernel<DT, false, false>), grid, dim3(THREADS), 0, st, a);
+  if (kca && kcb)        hipLaunchKernelGGL((gemm_tile<DT, true, true, TILE>), grid, dim3(THREADS), 0, st, a);
+  else if (kca && !kcb)  hipLaunchKernelGGL((gemm_tile<DT, true, false, TILE>), grid, dim3(THREADS), 0, st, a);
+  else if (!kca && kcb)  hipLaunchKernelGGL((gemm_tile<DT, false, true, TILE>), grid, dim3(THREADS), 0, st, a);
+  else                   hipLaunchKernelGGL((gemm_tile<DT, false, false, TILE>), grid, dim3(THREADS), 0, st, a);
   return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t st) {
-  if (a.tile_m != 128 || a.tile_n != 128) return hipErrorInvalidValue;
+  if (a.tile_m != a.tile_n || (a.tile_m != 128 && a.tile_m != 64)) return hipErrorInvalidValue;
   if (gemm_bf16_fast_ok(a)) return launch_gemm_bf16_fast(a, st);
-  return a.dtype == GECC_BF16 ? launch_dt<GECC_BF16>(a, st) : launch_dt<GECC_F32>(a, st);
+  if (a.tile_m == 64) return a.dtype == GECC_BF16 ? launch_tile<GECC_BF16, 64>(a, st) : launch_tile<GECC_F32, 64>(a, st);
+  return a.dtype == GECC_BF16 ? launch_tile<GECC_BF16, 128>(a, st) : launch_tile<GECC_F32, 128>(a, st);
 }
 
 namespace {
@@ -459,9 +712,10 @@ hipError_t launch_accumulate(float* C, const float* P, int n, int m, int64_t ldc
 }
 
 hipError_t launch_partials(const PartialArgs& a, hipStream_t st) {
-  if (a.tile_m != 128 || a.tile_n != 128) return hipErrorInvalidValue;
+  if (a.tile_m != a.tile_n || (a.tile_m != 128 && a.tile_m != 64)) return hipErrorInvalidValue;
   dim3 grid(a.ntn, a.ntm, a.batch);
-  hipLaunchKernelGGL(partials_kernel, grid, dim3(THREADS), 0, st, a);
+  if (a.tile_m == 64) hipLaunchKernelGGL(partials_kernel<64>, grid, dim3(THREADS), 0, st, a);
+  else                hipLaunchKernelGGL(partials_kernel<128>, grid, dim3(THREADS), 0, st, a);
   return hipGetLastError();
 }
 

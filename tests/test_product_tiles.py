@@ -1,0 +1,109 @@
+"""The 64 x 64 / 128 x 128-tile product kernel (fp32 through bf16 pieces, ragged and unaligned bf16) against fp64.
+
+Tolerance, per symbol: every product is formed to 2^-24 of itself (fp32: the terms that are left out add up to
+less than 2^-25, a piece is the nearest bf16 to what it stands for; bf16: products are exact) and k of them are
+added in fp32, so |C - C64| <= (k + 4) 2^-24 (|A| |B|)."""
+import numpy as np
+import pytest
+
+from paper_2508_04355_amd import gecc, inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def _product(A, B, dtype, trans=(0, 0), pad=0, shift=0):
+    """plain product of (batch, n, k) and (batch, k, m); `pad`: extra elements per stored row, `shift`: elements
+    the operands start behind a 16-byte boundary."""
+    import torch
+    import gpu_harness as H
+    batch, n, k = A.shape
+    m = B.shape[2]
+    lda, ldb, ldc = (n if trans[0] else k) + pad, (k if trans[1] else m) + pad, m + pad
+
+    def put(x, tr, ld):
+        t = H.to_dev(x, dtype, tr, ld)
+        flat = torch.zeros(t.numel() + 8, dtype=t.dtype, device=t.device)
+        flat[shift:shift + t.numel()] = t.reshape(-1)
+        return flat[shift:shift + t.numel()]
+
+    dA, dB = put(A, trans[0], lda), put(B, trans[1], ldb)
+    ctx = gecc.Context(n, k, m, gecc.BF16 if dtype == "bf16" else gecc.F32, gecc.noise_thresholds(n, k, m, 1.0, 1.0),
+                       batch=batch, trans_a=trans[0], trans_b=trans[1], lda=lda, ldb=ldb, ldc=ldc)
+    C = ctx.alloc_c()
+    C.fill_(float("nan"))
+    ctx.plain_gemm(dA, dB, C)
+    torch.cuda.synchronize()
+    out = C.cpu().numpy().astype(np.float64)
+    assert np.isnan(out[:, :, m:]).all()                 # what lies between m and ldc is left alone
+    return out[:, :, :m]
+
+
+def _check(C, A, B):
+    A, B = A.astype(np.float64), B.astype(np.float64)
+    assert not np.isnan(C).any()
+    ref, mag = A @ B, np.abs(A) @ np.abs(B)
+    assert (np.abs(C - ref) <= (A.shape[2] + 4) * 2.0 ** -24 * mag).all(), np.max(np.abs(C - ref) / (mag + 1e-300))
+
+
+@pytest.mark.parametrize("trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape,batch", [((1, 1, 1), 1), ((2, 33, 1), 2), ((1, 65, 3), 1), ((63, 31, 65), 1), ((64, 64, 64), 3),
+                                         ((65, 129, 63), 1), ((127, 300, 129), 1),
+                                         ((250, 257, 250), 64),      # 128 x 128 tiles, fp32: k split in two
+                                         ((500, 321, 381), 48)])     # 128 x 128 tiles, one workgroup each
+def test_tiles_layouts_and_tails(shape, batch, dtype, trans):
+    n, k, m = shape
+    rng = inputs.rng_for(80, n + k)
+    law = ("normal", 1.0)
+    A, B = [np.stack(x) for x in zip(*[inputs.operands(rng, n, k, m, law, law, dtype) for _ in range(batch)])]
+    _check(_product(A, B, dtype, trans), A, B)
+    _check(_product(A, B, dtype, trans, pad=3, shift=1), A, B)       # rows that start at any element
+
+
+def test_values_the_bf16_pieces_cannot_hold():
+    """Infinities, NaN, magnitudes beyond the largest bf16 and operands far below 2^-85 go through native fp32
+    arithmetic: the same result as a chain of fp32 multiplications and additions would have."""
+    n, k, m = 200, 96, 150
+    rng = inputs.rng_for(81, 0)
+    A, B = inputs.operands(rng, n, k, m, ("normal", 1.0), ("normal", 1.0), "f32")
+    B[7, 3], B[7, 4], B[:, 5] = 1.0, 0.0, 1.0        # (exact in bf16; zero; exact in bf16)
+    X = A.copy()
+    X[10, 7] = np.inf
+    X[150, 2] = np.nan
+    X[60, 9] = np.float32(3.4e38)                    # finite, but rounds to an infinite bf16
+    Y = B.copy()
+    Y[9, :] *= np.float32(0.25)
+    C = _product(X[None], Y[None], "f32")[0]
+    with np.errstate(all="ignore"):
+        ref = X.astype(np.float64) @ Y.astype(np.float64)
+    assert np.isnan(C[150]).all() and np.isnan(C[10, 4])
+    cols = [j for j in range(m) if Y[7, j] != 0.0]
+    assert np.array_equal(C[10, cols], np.sign(Y[7, cols]) * np.inf)
+    rows = [i for i in range(n) if i not in (10, 150)]
+    mag = np.abs(X[rows].astype(np.float64)) @ np.abs(Y.astype(np.float64))
+    fine = mag < 3.3e38
+    assert np.isfinite(C[rows][fine]).all()
+    assert (np.abs(C[rows] - ref[rows])[fine] <= (k + 4) * 2.0 ** -24 * mag[fine]).all()
+    # rows of tiny operands: their low pieces would be below the smallest normal number
+    X = A.copy()
+    X[33] *= np.float32(1e-36)
+    X[180] = np.float32(2.0 ** -120)
+    _check(_product(X[None], (B * np.float32(2.0 ** 40))[None], "f32"), X[None], (B * np.float32(2.0 ** 40))[None])
+    Z = B * np.float32(1e-36)
+    _check(_product((A * np.float32(2.0 ** 30))[None], Z[None], "f32"), (A * np.float32(2.0 ** 30))[None], Z[None])
+    # zeros are no tiny operands, and an all-zero operand gives zeros
+    assert not _product(np.zeros((1, n, k), np.float32), B[None], "f32").any()
+
+
+@pytest.mark.parametrize("law", [("normal", 1.0), ("uniform", -1.0, 1.0), ("uniform", 0.0, 1.0)])
+@pytest.mark.parametrize("shape", [(128, 48, 128), (512, 512, 512), (300, 1031, 129), (1024, 1024, 1024)])
+def test_fp32_products_through_pieces_are_as_close_as_native_ones(shape, law):
+    """Relative distance from the fp64 product, next to what native fp32 MFMAs gave on such operands with the
+    sums over k split the same way: 1e-7 (k = 32 to 48), 2.0e-7 (k = 128 to 512), 2.9e-7 (k = 1024); all-positive
+    operands: 8e-8 to 1.6e-7."""
+    n, k, m = shape
+    rng = inputs.rng_for(82, k)
+    A, B = inputs.operands(rng, n, k, m, law, law, "f32")
+    C = _product(A[None], B[None], "f32")[0]
+    ref = A.astype(np.float64) @ B.astype(np.float64)
+    assert np.linalg.norm(C - ref) <= (1.0e-7 if k < 128 or law[1] == 0.0 else 2.0e-7) * np.linalg.norm(ref)
