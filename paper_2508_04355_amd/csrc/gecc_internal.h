@@ -125,7 +125,6 @@ struct ScanArgs {
   const double* w;      // [2][len] per batch item (batch stride w_stride doubles), or null
   double* out;          // [2][len_out] per batch item (batch stride out_stride doubles)
   int64_t w_stride, out_stride;
-  int vec_ok;           // set by the launcher: rows are 16-byte aligned, vector loads allowed
   double* scratch;      // coldot only: [batch][nchunk][2][Cc]
   uint32_t* done;       // coldot only: counters (coldot_done_words of them, all zero); the scan then finishes
                         // by itself.  null: the second stage is left to the caller (see launch_coldot_stage1)

@@ -107,3 +107,35 @@ def test_fp32_products_through_pieces_are_as_close_as_native_ones(shape, law):
     C = _product(A[None], B[None], "f32")[0]
     ref = A.astype(np.float64) @ B.astype(np.float64)
     assert np.linalg.norm(C - ref) <= (1.0e-7 if k < 128 or law[1] == 0.0 else 2.0e-7) * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("trans", [(0, 0), (1, 1)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape,batch", [((5, 3, 7), 2),            # rows shorter than a vector
+                                         ((64, 9, 8), 600), ((33, 259, 41), 520),   # a wavefront per rows, and the last vector overlapped
+                                         ((131, 260, 77), 1), ((70, 2053, 515), 1), ((515, 1027, 2051), 1)])
+def test_scans_of_rows_at_any_alignment(shape, batch, dtype, trans):
+    """Operand parities and parity blocks (fp64 sums) to 1e-12 and 1e-11, and an audit that finds the one wrong symbol
+    (it re-forms the stored parities bit for bit), where rows start at any element and end in mid-vector."""
+    import gpu_harness as H
+    n, k, m = shape
+    rng = inputs.rng_for(83, n + k)
+    law = ("normal", 1.0)
+    A, B = [np.stack(x) for x in zip(*[inputs.operands(rng, n, k, m, law, law, dtype) for _ in range(batch)])]
+    A2 = A.copy()
+    A2[-1, n - 1, k - 1] += 4.0
+    A2 = inputs.store(A2, dtype)
+    tau = gecc.noise_thresholds(n, k, m, 1.0, 1.0)
+    g = H.run_gpu(A, B, A2, B, [], tau, dtype, trans[0], trans[1], ld_pad=1)
+    A64, B64 = A.astype(np.float64), B.astype(np.float64)
+    wn, wm = np.arange(1, n + 1), np.arange(1, m + 1)
+    AP = np.stack([A64.sum(1), np.einsum("bnk,n->bk", A64, wn)], 1)
+    BP = np.stack([B64.sum(2), np.einsum("bkm,m->bk", B64, wm)], 1)
+    assert np.allclose(g.A_par, AP, rtol=1e-12, atol=1e-12 * np.abs(AP).max())
+    assert np.allclose(g.B_par, BP, rtol=1e-12, atol=1e-12 * np.abs(BP).max())
+    ref = np.concatenate([np.matmul(A64, BP.transpose(0, 2, 1)).transpose(0, 2, 1).reshape(batch, -1), np.matmul(AP, B64).reshape(batch, -1),
+                          np.matmul(AP, BP.transpose(0, 2, 1)).reshape(batch, -1)], 1)
+    assert np.allclose(g.C_par, ref, rtol=1e-11, atol=1e-12 * np.abs(ref).max())
+    assert all(r.status == gecc.CLEAN for r in g.reports[:-1])
+    assert g.reports[-1].status == gecc.CORRECTED and [e[:3] for e in g.reports[-1].errors()] == [(0, n - 1, k - 1)]
+    assert np.array_equal(g.A, A64)
