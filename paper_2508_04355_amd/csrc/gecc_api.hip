@@ -56,11 +56,7 @@ void make_layout(gecc_ctx* c) {
   const size_t ra = tile_scan_row_scratch_doubles(p.trans_a ? p.k : p.n, p.trans_a ? p.n : p.k, p.dtype, p.batch);
   const size_t rb = tile_scan_row_scratch_doubles(p.trans_b ? p.m : p.k, p.trans_b ? p.k : p.m, p.dtype, p.batch);
   L.scan_row = take((ra > rb ? ra : rb) * sizeof(double));
-  // (the contexts of k-panels run on this workspace, and a panel of a bf16 product may take the larger tile)
-  const size_t s128 = b * ((n + 127) / 128) * ((m + 127) / 128);
-  const size_t k128 = c->tile_m == 64 && p.dtype == GECC_BF16 ? s128 * (size_t)ksplit_128(s128, p.k) * 128 * 128 : 0;
-  const size_t kown = c->ksplit > 1 ? b * c->ntm * c->ntn * (size_t)c->ksplit * c->tile_m * c->tile_n : 0;
-  L.ksplit = take((k128 > kown ? k128 : kown) * sizeof(float));
+  L.ksplit = take(c->ksplit > 1 ? b * c->ntm * c->ntn * (size_t)c->ksplit * c->tile_m * c->tile_n * sizeof(float) : 0);
   L.w_a = L.w_b = L.side_r = L.side_c = L.gate = 0;
   if (blocked(c)) {
     const size_t esz = p.dtype == GECC_BF16 ? 2 : 4;
@@ -73,32 +69,70 @@ void make_layout(gecc_ctx* c) {
   L.total = off;
 }
 
-// Tile of the product kernel (= granularity of the partial sums), workgroups per tile, workspace layout.
-//
-// 128 x 128: whatever the 256 x 256-tile kernel may take (its partial sums have that granularity) and blocked
-// mode; otherwise products with tiles enough for every compute unit, as long as tiles that hang over the
+// Tile of the product kernel (= granularity of the partial sums), workgroups per tile, and whether the bf16
+// kernel with 256 x 256 tiles may take the product.  All figures: microseconds, product kernel alone.
+struct ProductPlan { int tile, ksplit; bool fast; };
+
+// 128 x 128 tiles of a bf16 product, k split so that few compute units idle: the number of ranges with the
+// least (rounds of workgroups) / (ranges), at most 512 workgroups.  0: fewer than 384 workgroups, or
+// ranges below 512 terms (1920 x 2176 x 512, 60 tiles: eight ranges 35 us, 64 x 64 tiles 23).
+int ksplit_bf16_128(int64_t t128, int k) {
+  int best = 0;
+  double cost = 1e30;
+  for (int s = 1; s <= 8 && t128 * s <= 512 && k / s >= 512; ++s) {
+    const int64_t per_cu = (t128 * s + 255) / 256;
+    const double c = (double)per_cu * (per_cu == 1 ? 1.25 : 1.0) / s + 0.02 * s;
+    if (t128 * s >= 384 && c < cost) { cost = c; best = s; }
+  }
+  return best;
+}
+
+// 128 x 128 tiles: products with tiles enough for every compute unit, as long as tiles that hang over the
 // edge do not eat up what the larger tile gains (a saturated chip does a 128 x 128 tile in the time of three
-// 64 x 64 ones: fp32, 256 x 512^3, 428 against 568 us; 64 x 300^3, 61 against 46 us).  64 x 64: the rest
-// (fp32 1024^3 28 against 37 us, 128^3 7.7 against 13.8 us; bf16 1500 x 1000 x 1100 19.5 against 28 us).
-// Workgroups: fp32 tiles of 64 keep four per compute unit busy (1024^3: one workgroup per tile 40 us, two 31,
-// four 28, eight 38), bf16 ones two, to the nearest (1500 x 1000 x 1100, 432 tiles: 19.5 us, split in two 22),
-// fp32 tiles of 128 two (2000 x 1000 x 2000: 83 us, split in two 67).
+// 64 x 64 ones: fp32, 256 x 512^3, 428 against 568; 64 x 300^3, 61 against 46), and bf16 products of long k
+// (1536 x 4224 x 768: 36 against 39, 16384 x 4096 x 88: 41 against 52).  64 x 64 tiles: the rest (fp32
+// 1024^3 28 against 37, 128^3 7.7 against 13.8; bf16 1500 x 1000 x 1100 19.5 against 28).
+// Workgroups: fp32 tiles of 64 keep four per compute unit busy (1024^3: one workgroup per tile 40, two 31,
+// four 28, eight 38), bf16 ones two, to the nearest (1500 x 1000 x 1100, 432 tiles: 19.5, split in two 22),
+// fp32 tiles of 128 two (2000 x 1000 x 2000: 83, split in two 67).
+ProductPlan plan_tiles(int dtype, int64_t n, int64_t k, int64_t m, int64_t batch) {
+  const int64_t t128 = ((n + 127) / 128) * ((m + 127) / 128) * batch, t64 = ((n + 63) / 64) * ((m + 63) / 64) * batch;
+  const int s_long = dtype == GECC_BF16 ? ksplit_bf16_128(t128, (int)k) : 0;
+  if (s_long > 0) return {128, s_long, false};
+  if (t128 >= 256 && k >= 256 && 3 * t128 < t64) return {128, dtype == GECC_F32 && t128 < 512 ? 2 : 1, false};
+  return {64, dtype == GECC_F32 ? ksplit_of(t64, 1024, (int)k) : ksplit_of(t64, 512 + (int)(t64 < 512 ? t64 / 2 : 0), (int)k), false};
+}
+
+// Whether the 256 x 256-tile kernel is the faster one for a bf16 product it can take: it needs a workgroup per
+// compute unit to show its rate (1300 TFLOP/s against 650 of gemm_tile), and has no k-split for fewer
+// tiles.  Both times as fitted to measurements (256 x 256 / gemm_tile): 1024^3 22 / 15, 384 x 3904 x 768
+// 62 / 24, 1536 x 4224 x 768 67 / 36, 1920 x 2176 x 512 39 / 23, 2048^3 41 / 42, 1280 x 7296 x 2304
+// 116 / 127, 3072 x 2048 x 3072 44 / 78.
+bool fast_pays(int64_t n, int64_t k, int64_t m, int64_t batch) {
+  const int64_t t256 = ((n + 255) / 256) * ((m + 255) / 256) * batch;
+  if (t256 > 128) return true;
+  const ProductPlan g = plan_tiles(GECC_BF16, n, k, m, batch);
+  const double gf = 2e-9 * (double)((n + g.tile - 1) / g.tile * g.tile) * (double)k * (double)((m + g.tile - 1) / g.tile * g.tile) * (double)batch;
+  const double t_gen = g.tile == 64 ? 6.0 + gf / 0.33 + 0.006 * (double)(k / g.ksplit) : 8.0 + gf / 0.42;
+  const double t_fast = 6.0 + (0.0148 + 0.009 * (double)t256 / 256.0) * (double)k;
+  // (by less than that the fit cannot tell them apart)
+  return t_fast - t_gen < 5.0 || t_gen > 0.85 * t_fast;
+}
+
 // compact: 128 x 128 tiles and 256 workgroups, the plan that needs the least workspace.
 void plan_product(gecc_ctx* c, bool compact) {
   const gecc_params& p = c->p;
-  const int64_t t128 = (int64_t)((p.n + 127) / 128) * ((p.m + 127) / 128) * p.batch;
-  const int64_t t64 = (int64_t)((p.n + 63) / 64) * ((p.m + 63) / 64) * p.batch;
   const bool may_be_fast = p.dtype == GECC_BF16 && p.k % 64 == 0 && p.lda % 8 == 0 && p.ldb % 8 == 0 &&
                            (!p.trans_a || p.n % 8 == 0) && (p.trans_b || p.m % 8 == 0) && (int64_t)p.n * p.m >= 256 * 256;
-  const bool large = t128 >= 256 && p.k >= 256 && 3 * t128 < t64;
-  const int tile = compact || blocked(c) || may_be_fast || large ? 128 : 64;
-  c->tile_m = c->tile_n = tile;
-  c->ntm = (p.n + tile - 1) / tile;
-  c->ntn = (p.m + tile - 1) / tile;
-  if (blocked(c)) c->ksplit = 1;
-  else if (compact || may_be_fast) c->ksplit = ksplit_128(t128, p.k);
-  else if (tile == 64) c->ksplit = p.dtype == GECC_F32 ? ksplit_of(t64, 1024, p.k) : ksplit_of(t64, 512 + (int)(t64 < 512 ? t64 / 2 : 0), p.k);
-  else c->ksplit = p.dtype == GECC_F32 && t128 < 512 && t128 <= SCAN_DONE_WORDS ? 2 : 1;
+  const int64_t t128 = (int64_t)((p.n + 127) / 128) * ((p.m + 127) / 128) * p.batch;
+  ProductPlan pl = {128, ksplit_128(t128, p.k), true};
+  if (blocked(c)) pl.ksplit = 1;
+  else if (!compact && !(may_be_fast && (c->cu_hint > 0 || fast_pays(p.n, p.k, p.m, p.batch)))) pl = plan_tiles(p.dtype, p.n, p.k, p.m, p.batch);
+  c->tile_m = c->tile_n = pl.tile;
+  c->ksplit = pl.ksplit;
+  c->fast = pl.fast;
+  c->ntm = (p.n + pl.tile - 1) / pl.tile;
+  c->ntn = (p.m + pl.tile - 1) / pl.tile;
   make_layout(c);
   // (a product that fits the library's static scratch in the compact plan has to fit it in any)
   if (!compact && c->lay.total > (size_t)GECC_STATIC_SCRATCH_BYTES) plan_product(c, true);
@@ -382,7 +416,7 @@ GemmArgs gemm_args(const gecc_ctx* c, const void* A, const void* B, float* C) {
   g.n = p.n; g.k = p.k; g.m = p.m; g.batch = p.batch;
   g.lda = p.lda; g.ldb = p.ldb; g.ldc = p.ldc;
   g.sa = p.stride_a; g.sb = p.stride_b; g.sc = p.stride_c;
-  g.tile_m = c->tile_m; g.tile_n = c->tile_n; g.ntm = c->ntm; g.ntn = c->ntn;
+  g.tile_m = c->tile_m; g.tile_n = c->tile_n; g.ntm = c->ntm; g.ntn = c->ntn; g.fast = c->fast;
   g.cu_hint = c->cu_hint; g.split_first = -1;
   if (c->ksplit > 1 && c->ws && c->ws_bytes >= c->lay.total) {
     g.ksplit = c->ksplit;
@@ -622,6 +656,25 @@ hipError_t product(gecc_ctx* ctx, const void* dev_A, const double* dev_A_par, co
   return timed_gemm(ctx, g, st);
 }
 
+// Blocked mode: the plan of a narrow product (parity columns or rows of all blocks against a whole operand).
+// Its partial tiles go where the main product's partial sums will go afterwards.
+void narrow_plan(gecc_ctx* ctx, GemmArgs& g) {
+  const gecc_params& p = ctx->p;
+  ProductPlan pl = plan_tiles(p.dtype, g.n, g.k, g.m, 1);
+  if (p.dtype == GECC_BF16 && fast_pays(g.n, g.k, g.m, 1)) pl.fast = true;
+  const size_t room = ctx->lay.synd - ctx->lay.rowpart;
+  const size_t tiles = (size_t)((g.n + pl.tile - 1) / pl.tile) * ((g.m + pl.tile - 1) / pl.tile), tile_bytes = (size_t)pl.tile * pl.tile * sizeof(float);
+  while (pl.ksplit > 1 && tiles * pl.ksplit * tile_bytes > room) --pl.ksplit;
+  g.tile_m = g.tile_n = pl.fast ? 128 : pl.tile;
+  g.ntm = (g.n + g.tile_m - 1) / g.tile_m;
+  g.ntn = (g.m + g.tile_n - 1) / g.tile_n;
+  g.fast = pl.fast;
+  g.ksplit = pl.ksplit;
+  g.split_part = reinterpret_cast<float*>(ctx->ws + ctx->lay.rowpart);
+  g.split_done = reinterpret_cast<uint32_t*>(ctx->ws + ctx->lay.done);
+  g.rowpart = nullptr; g.colpart = nullptr; g.faults = nullptr; g.n_faults = 0;
+}
+
 // Blocked mode, S3: the parity blocks of every block of C-bar on the matrix units -- the parity
 // columns of all column blocks of B-bar, split into operand-type pieces, form one narrow operand
 // W_B (and the parity rows of all row blocks of A-bar one flat operand W_A); A W_B^T and W_A B are
@@ -640,8 +693,7 @@ hipError_t blocked_multiply(gecc_ctx* ctx, const void* dev_A, const double* dev_
     if ((e = launch_split_parities(dev_B_par, WB, p.dtype, ctx->nbj, p.k, ctx->pieces, ctx->w_cols_b, st)) != hipSuccess) return e;
     GemmArgs g = gemm_args(ctx, dev_A, WB, side_r);
     g.trans_b = 1; g.m = ctx->w_cols_b; g.ldb = p.k; g.ldc = ctx->w_cols_b;
-    g.ntn = (g.m + ctx->tile_n - 1) / ctx->tile_n;
-    g.rowpart = nullptr; g.colpart = nullptr; g.faults = nullptr; g.n_faults = 0; g.ksplit = 1;
+    narrow_plan(ctx, g);
     if ((e = t.done(launch_gemm(g, st))) != hipSuccess) return e;
   }
   {
@@ -649,8 +701,7 @@ hipError_t blocked_multiply(gecc_ctx* ctx, const void* dev_A, const double* dev_
     if ((e = launch_split_parities(dev_A_par, WA, p.dtype, ctx->nbi, p.k, ctx->pieces, ctx->w_cols_a, st)) != hipSuccess) return e;
     GemmArgs g = gemm_args(ctx, WA, dev_B, side_c);
     g.trans_a = 0; g.n = ctx->w_cols_a; g.lda = p.k; g.ldc = p.m;
-    g.ntm = (g.n + ctx->tile_m - 1) / ctx->tile_m;
-    g.rowpart = nullptr; g.colpart = nullptr; g.faults = nullptr; g.n_faults = 0; g.ksplit = 1;
+    narrow_plan(ctx, g);
     if ((e = t.done(launch_gemm(g, st))) != hipSuccess) return e;
   }
   {
@@ -1009,7 +1060,9 @@ int gecc_protected_gemm_panels(gecc_ctx* ctx, void* dev_A, void* dev_B, float* d
       q.tau_r1 *= f; q.tau_r2 *= f; q.tau_q1 *= f; q.tau_q2 *= f;
       gecc_ctx* child = nullptr;
       rc = gecc_create(&child, &q);
+      // (a panel may plan more workgroups per tile than the whole product, or another tile)
       if (!rc && child->lay.total > ctx->lay.total) plan_product(child, true);
+      if (!rc && child->lay.total > ctx->lay.total) { child->ksplit = 1; make_layout(child); }
       if (rc || child->lay.total > ctx->lay.total) {
         if (child) gecc_destroy(child);
         ctx->n_panel = g;

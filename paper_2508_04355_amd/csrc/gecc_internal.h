@@ -75,6 +75,7 @@ struct gecc_ctx {
   int w_cols_a, w_cols_b;  // rows of W_A (2 * pieces * nbi) and of W_B, padded to a multiple of 8
   int tile_op;             // operand whose two reductions share one pass (GECC_MAT_A / GECC_MAT_B)
   int ksplit;              // workgroups per tile of gemm_tile (1: no split)
+  bool fast;               // bf16: the 256 x 256-tile kernel takes the product where the operands' addresses allow it
   int cu_hint;             // GECC_CU_COUNT (tests: plan the tile rounds as for that many CUs), else 0
   int64_t tile_min;        // operands of that many elements or more take the tile scan (2^25; GECC_TILE_MIN for tests)
   char* ws;                // device workspace (caller's)
@@ -198,6 +199,7 @@ struct GemmArgs {
   float* rowpart;       // null = no syndrome epilogue (plain product)
   float* colpart;
   int tile_m, tile_n, ntm, ntn;
+  bool fast;            // the 256 x 256-tile kernel may take it
   int rp_ld, cp_ld;     // lines per sub-tile slab of rowpart / colpart (n, m plus padding)
   const gecc_fault* faults;
   int n_faults;

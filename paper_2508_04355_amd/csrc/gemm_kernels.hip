@@ -677,7 +677,7 @@ hipError_t launch_tile(const GemmArgs& a0, hipStream_t st) {
 
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t st) {
   if (a.tile_m != a.tile_n || (a.tile_m != 128 && a.tile_m != 64)) return hipErrorInvalidValue;
-  if (gemm_bf16_fast_ok(a)) return launch_gemm_bf16_fast(a, st);
+  if (a.fast && gemm_bf16_fast_ok(a)) return launch_gemm_bf16_fast(a, st);
   if (a.tile_m == 64) return a.dtype == GECC_BF16 ? launch_tile<GECC_BF16, 64>(a, st) : launch_tile<GECC_F32, 64>(a, st);
   return a.dtype == GECC_BF16 ? launch_tile<GECC_BF16, 128>(a, st) : launch_tile<GECC_F32, 128>(a, st);
 }

@@ -139,3 +139,40 @@ def test_scans_of_rows_at_any_alignment(shape, batch, dtype, trans):
     assert all(r.status == gecc.CLEAN for r in g.reports[:-1])
     assert g.reports[-1].status == gecc.CORRECTED and [e[:3] for e in g.reports[-1].errors()] == [(0, n - 1, k - 1)]
     assert np.array_equal(g.A, A64)
+
+
+@pytest.mark.parametrize("trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("shape", [(256, 2176, 256), (384, 3904, 768),     # 64 x 64 tiles, k split
+                                   (1536, 4224, 768), (1000, 3584, 1000)])  # 128 x 128 tiles, k split
+def test_bf16_products_of_few_tiles_and_long_k(shape, trans):
+    """Aligned bf16 products that leave most compute units of the 256 x 256-tile kernel idle: product, decisions and
+    located errors (one in the last tile of C, one in A) next to the fp64 product."""
+    import gpu_harness as H
+    n, k, m = shape
+    rng = inputs.rng_for(84, n)
+    law = ("normal", 1.0)
+    A, B = inputs.operands(rng, n, k, m, law, law, "bf16")
+    _check(_product(A[None], B[None], "bf16", trans), A[None], B[None])
+    A2 = A.copy()
+    A2[n - 1, k - 1] = inputs.store(A2[n - 1, k - 1:k] + 4.0, "bf16")[0]
+    g = H.run_gpu(A, B, A2, B, [(0, n - 2, m - 1, 50.0)], gecc.noise_thresholds(n, k, m, 1.0, 1.0), "bf16", trans[0], trans[1])
+    assert g.reports[0].status == gecc.CORRECTED
+    assert [e[:3] for e in g.reports[0].errors()] == [(0, n - 1, k - 1), (2, n - 2, m - 1)]
+    ref = A.astype(np.float64) @ B.astype(np.float64)
+    assert np.abs(g.C[0] - ref).max() <= 1e-5 * np.abs(ref).max() and np.array_equal(g.A[0], A)
+
+
+@pytest.mark.parametrize("trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("pad", [0, 24])
+def test_ragged_tiles_in_the_kernel_with_256_by_256_tiles(pad, trans, monkeypatch):
+    """(GECC_CU_COUNT keeps the plan with 256 x 256 tiles for a product this small.)"""
+    import gpu_harness as H
+    monkeypatch.setenv("GECC_CU_COUNT", "256")
+    n, k, m = 520, 256, 264
+    rng = inputs.rng_for(85, pad)
+    A, B = inputs.operands(rng, n, k, m, ("normal", 1.0), ("normal", 1.0), "bf16")
+    cf = [(0, n - 1, m - 1, 37.5), (0, 256, 0, -12.25)]
+    tau = gecc.noise_thresholds(n, k, m, 1.0, 1.0)
+    g = H.run_gpu(A, B, A, B, cf, tau, "bf16", trans[0], trans[1], ld_pad=pad)
+    H.compare(g, H.run_oracle(A, B, A, B, cf, tau), 1e-5, what="256 tiles, pad %d" % pad)
+    assert g.pad_untouched and [e[:3] for e in g.reports[0].errors()] == [(2, 256, 0), (2, n - 1, m - 1)]
