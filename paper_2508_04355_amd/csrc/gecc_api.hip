@@ -391,23 +391,6 @@ struct ScanQueue {
   }
 };
 
-// P_r = A B_P (n x 2) and P_c = A_P B (2 x m) of C-bar; the coldot of the two goes first so that the
-// rowdot can carry its second stage
-hipError_t parity_products(gecc_ctx* c, ScanQueue& q, const void* A, const double* A_par, const void* B,
-                           const double* B_par, double* C_par) {
-  const gecc_params& p = c->p;
-  const int64_t rec = 2 * (int64_t)p.n + 2 * (int64_t)p.m + 4;
-  const ScanJob pr = scan_a_over_k(c, A, B_par, C_par, rec);
-  const ScanJob pc = scan_b_over_k(c, B, A_par, C_par + 2 * (size_t)p.n, rec);
-  hipError_t e;
-  if (!pc.rowdot && pr.rowdot) {
-    if ((e = q.run(pc)) != hipSuccess) return e;
-    return q.run(pr);
-  }
-  if ((e = q.run(pr)) != hipSuccess) return e;
-  return q.run(pc);
-}
-
 GemmArgs gemm_args(const gecc_ctx* c, const void* A, const void* B, float* C) {
   const gecc_params& p = c->p;
   GemmArgs g{};
@@ -428,9 +411,9 @@ GemmArgs gemm_args(const gecc_ctx* c, const void* A, const void* B, float* C) {
 }
 
 // the product kernel(s), bracketed by a timing record when timing is enabled
-hipError_t timed_gemm(gecc_ctx* c, const GemmArgs& g, hipStream_t st) {
+hipError_t timed_gemm(gecc_ctx* c, const GemmArgs& g, const GemmSide* side, hipStream_t st) {
   Timed t(c, GECC_K_PRODUCT, st);
-  return t.done(launch_gemm(g, st));
+  return t.done(launch_gemm(g, side, st));
 }
 
 }  // namespace
@@ -636,9 +619,11 @@ int check_multiply_args(gecc_ctx* ctx, const void* dev_A, const double* dev_A_pa
   return GECC_OK;
 }
 
-// S3 after the parity products: the data block, the fused syndrome partial sums, P_g
-hipError_t product(gecc_ctx* ctx, const void* dev_A, const double* dev_A_par, const void* dev_B,
-                   const double* dev_B_par, float* dev_C, double* dev_C_par, const gecc_fault* dev_faults,
+// S3: the parity blocks pr, pc of C-bar (null: formed already), the data block, the fused syndrome partial
+// sums, P_g.  The scans of the parity blocks ride in the product's launch where that is gemm_tile's;
+// otherwise they go first, on q.
+hipError_t product(gecc_ctx* ctx, ScanQueue& q, const ScanJob* pr, const ScanJob* pc, const void* dev_A, const double* dev_A_par,
+                   const void* dev_B, const double* dev_B_par, float* dev_C, double* dev_C_par, const gecc_fault* dev_faults,
                    int32_t n_faults, hipStream_t st) {
   const gecc_params& p = ctx->p;
   GemmArgs g = gemm_args(ctx, dev_A, dev_B, dev_C);
@@ -653,7 +638,36 @@ hipError_t product(gecc_ctx* ctx, const void* dev_A, const double* dev_A_par, co
   g.pg_out = dev_C_par + 2 * (size_t)p.n + 2 * (size_t)p.m;
   g.pg_stride = 2 * (int64_t)p.n + 2 * (int64_t)p.m + 4;
   g.state = reinterpret_cast<DecodeState*>(ctx->ws + ctx->lay.state);
-  return timed_gemm(ctx, g, st);
+  hipError_t e;
+  if (gemm_takes_256(g)) {
+    // (a column scan goes before a row scan, which can carry its second stage; two row scans: P_c first, which
+    // can carry what the encoding of B left)
+    const ScanJob* first = pr && pc && pr->rowdot ? pc : pr;
+    const ScanJob* then = first == pc ? pr : pc;
+    if (first && (e = q.run(*first)) != hipSuccess) return e;
+    if (then && (e = q.run(*then)) != hipSuccess) return e;
+    if ((e = q.flush()) != hipSuccess) return e;
+    return timed_gemm(ctx, g, nullptr, st);
+  }
+  // (the counters behind those of a k-split product)
+  const int64_t tiles = (int64_t)ctx->ntm * ctx->ntn * p.batch;
+  int used = ctx->ksplit > 1 && tiles <= SCAN_DONE_WORDS ? (int)tiles : 0;
+  GemmSide side{};
+  int at = 0;
+  const ScanJob* jobs[2] = {pc, pr};
+  for (const ScanJob* j : jobs) {
+    if (!j) continue;
+    int words = 0;
+    if (make_side_job(j->s, j->rowdot, q.done() + used, SCAN_DONE_WORDS - used, side.j[at], words)) {
+      used += words;
+      ++at;
+    } else {
+      side.j[at] = SideJob{};
+      if ((e = q.run(*j)) != hipSuccess) return e;
+    }
+  }
+  if ((e = q.flush()) != hipSuccess) return e;
+  return timed_gemm(ctx, g, &side, st);
 }
 
 // Blocked mode: the plan of a narrow product (parity columns or rows of all blocks against a whole operand).
@@ -694,7 +708,7 @@ hipError_t blocked_multiply(gecc_ctx* ctx, const void* dev_A, const double* dev_
     GemmArgs g = gemm_args(ctx, dev_A, WB, side_r);
     g.trans_b = 1; g.m = ctx->w_cols_b; g.ldb = p.k; g.ldc = ctx->w_cols_b;
     narrow_plan(ctx, g);
-    if ((e = t.done(launch_gemm(g, st))) != hipSuccess) return e;
+    if ((e = t.done(launch_gemm(g, nullptr, st))) != hipSuccess) return e;
   }
   {
     Timed t(ctx, GECC_K_PARITY_C, st);
@@ -702,7 +716,7 @@ hipError_t blocked_multiply(gecc_ctx* ctx, const void* dev_A, const double* dev_
     GemmArgs g = gemm_args(ctx, WA, dev_B, side_c);
     g.trans_a = 0; g.n = ctx->w_cols_a; g.lda = p.k; g.ldc = p.m;
     narrow_plan(ctx, g);
-    if ((e = t.done(launch_gemm(g, st))) != hipSuccess) return e;
+    if ((e = t.done(launch_gemm(g, nullptr, st))) != hipSuccess) return e;
   }
   {
     BlockedParityArgs b{};
@@ -722,7 +736,7 @@ hipError_t blocked_multiply(gecc_ctx* ctx, const void* dev_A, const double* dev_
   g.n_faults = n_faults;
   g.pg_out = nullptr;      // P_g of every block and the resets are done above
   g.state = nullptr;
-  return timed_gemm(ctx, g, st);
+  return timed_gemm(ctx, g, nullptr, st);
 }
 
 }  // namespace
@@ -736,10 +750,11 @@ int gecc_multiply(gecc_ctx* ctx, const void* dev_A, const double* dev_A_par, con
   if ((rc = prep(ctx, st))) return rc;
   if (blocked(ctx)) return hip_rc(blocked_multiply(ctx, dev_A, dev_A_par, dev_B, dev_B_par, dev_C, dev_C_par, dev_faults, n_faults, st));
   ScanQueue q{ctx, st};
-  hipError_t e;
-  if ((e = parity_products(ctx, q, dev_A, dev_A_par, dev_B, dev_B_par, dev_C_par)) != hipSuccess) return hip_rc(e);
-  if ((e = q.flush()) != hipSuccess) return hip_rc(e);
-  return hip_rc(product(ctx, dev_A, dev_A_par, dev_B, dev_B_par, dev_C, dev_C_par, dev_faults, n_faults, st));
+  const gecc_params& p = ctx->p;
+  const int64_t rec = 2 * (int64_t)p.n + 2 * (int64_t)p.m + 4;
+  const ScanJob pr = scan_a_over_k(ctx, dev_A, dev_B_par, dev_C_par, rec);
+  const ScanJob pc = scan_b_over_k(ctx, dev_B, dev_A_par, dev_C_par + 2 * (size_t)p.n, rec);
+  return hip_rc(product(ctx, q, &pr, &pc, dev_A, dev_A_par, dev_B, dev_B_par, dev_C, dev_C_par, dev_faults, n_faults, st));
 }
 
 namespace {
@@ -881,23 +896,23 @@ int encode_and_multiply(gecc_ctx* ctx, void* dev_A, void* dev_B, float* dev_C, d
     const ScanJob& po = t_is_a ? pc : pr;
     const TileScanJob to = t_is_a ? tile_job(ctx, GECC_MAT_B, dev_B, nullptr, dev_A_par, dev_C_par + 2 * (size_t)p.n, rec, nullptr)
                                   : tile_job(ctx, GECC_MAT_A, dev_A, nullptr, dev_B_par, dev_C_par, rec, nullptr);
-    if (po.rowdot && to.row_on && !to.col_on && po.s.R < 8192 && po.s.Cc >= 4096 && tile_scan_ok(to))
-      e = q.run_tile(to, po.kind);
-    else
-      e = q.run(po);
-    if (e != hipSuccess) return hip_rc(e);
-  } else {
-    // stored:        A n x k, B k x m   A n x k, B m x k   A k x n, B k x m   A k x n, B m x k
-    // rowdots:       B_P, P_r           P_r, P_c           A_P, B_P           A_P, P_c
-    const ScanJob* order[4];
-    if (!p.trans_a) { order[0] = &ea; order[1] = &eb; order[2] = &pc; order[3] = &pr; }
-    else if (!p.trans_b) { order[0] = &eb; order[1] = &pr; order[2] = &ea; order[3] = &pc; }
-    else { order[0] = &eb; order[1] = &ea; order[2] = &pr; order[3] = &pc; }
-    for (int x = 0; x < 4; ++x)
-      if ((e = q.run(*order[x])) != hipSuccess) return hip_rc(e);
+    const bool long_rows = po.rowdot && to.row_on && !to.col_on && po.s.R < 8192 && po.s.Cc >= 4096 && tile_scan_ok(to);
+    if (long_rows && (e = q.run_tile(to, po.kind)) != hipSuccess) return hip_rc(e);
+    // (P_c reads A_P, P_r reads B_P: what the tile scan left pending comes first)
+    if (!long_rows && (e = q.flush()) != hipSuccess) return hip_rc(e);
+    return hip_rc(product(ctx, q, long_rows || t_is_a ? nullptr : &pr, long_rows || !t_is_a ? nullptr : &pc, dev_A, dev_A_par,
+                          dev_B, dev_B_par, dev_C, dev_C_par, dev_faults, n_faults, st));
   }
-  if ((e = q.flush()) != hipSuccess) return hip_rc(e);
-  return hip_rc(product(ctx, dev_A, dev_A_par, dev_B, dev_B_par, dev_C, dev_C_par, dev_faults, n_faults, st));
+  if (p.trans_a && !p.trans_b && gemm_takes_256(gemm_args(ctx, dev_A, dev_B, dev_C))) {
+    // both encodings are row scans, both parity blocks column scans: in turn, so that A_P carries P_r's second stage
+    if ((e = q.run(eb)) != hipSuccess || (e = q.run(pr)) != hipSuccess || (e = q.run(ea)) != hipSuccess) return hip_rc(e);
+    return hip_rc(product(ctx, q, nullptr, &pc, dev_A, dev_A_par, dev_B, dev_B_par, dev_C, dev_C_par, dev_faults, n_faults, st));
+  }
+  // the two encodings; a column scan goes before a row scan, which can carry its second stage
+  const bool b_first = ea.rowdot && !eb.rowdot;
+  if ((e = q.run(b_first ? eb : ea)) != hipSuccess) return hip_rc(e);
+  if ((e = q.run(b_first ? ea : eb)) != hipSuccess) return hip_rc(e);
+  return hip_rc(product(ctx, q, &pr, &pc, dev_A, dev_A_par, dev_B, dev_B_par, dev_C, dev_C_par, dev_faults, n_faults, st));
 }
 
 }  // namespace
@@ -1113,7 +1128,7 @@ int gecc_plain_gemm(gecc_ctx* ctx, const void* dev_A, const void* dev_B, float* 
     const int rc = prep(ctx, (hipStream_t)stream);
     if (rc) return rc;
   }
-  return hip_rc(timed_gemm(ctx, g, (hipStream_t)stream));
+  return hip_rc(timed_gemm(ctx, g, nullptr, (hipStream_t)stream));
 }
 
 int gecc_report_to_host(gecc_ctx* ctx, const gecc_report* dev_report, gecc_report* host_report,

@@ -217,14 +217,35 @@ struct GemmArgs {
   float* split_part;    // [tiles x batch][ksplit][tile_m x tile_n]
   uint32_t* split_done; // [tiles x batch] counters, zero between launches (shared with the scans)
   // protected product only: P_g = A_P B_P goes to pg_out[b * pg_stride + 0..3], formed by the
-  // workgroup of the first tile, which also resets the decoder state of its batch item
+  // workgroup of the first tile or by one of its own, which also resets the decoder state of its batch item
   const double* A_par;
   const double* B_par;
   double* pg_out;
   int64_t pg_stride;
   DecodeState* state;
 };
-hipError_t launch_gemm(const GemmArgs& a, hipStream_t st);
+// Scans that ride in the launch of gemm_tile, as workgroups of their own spread evenly among the product's:
+// the parity blocks P_r and P_c of C-bar (vector weights; a column scan is finished by its last
+// workgroup) and P_g.  Nothing in the launch reads what they form.
+enum : int { SIDE_NONE = 0, SIDE_ROW = 1, SIDE_ROW_WAVE = 2, SIDE_COL = 3 };
+struct SideJob {
+  int kind;            // SIDE_x
+  ScanArgs s;
+  int gx, gy;          // workgroups per batch item: gx (row scan) or gx segments x gy chunks
+  int nblk;
+};
+struct GemmSide {
+  SideJob j[2];
+  int pg_items;        // batch items whose P_g is to be formed (set by the launcher)
+  int blocks;          // workgroups of the side jobs in all (set by the launcher)
+  int groups;          // the same in groups of 8, one per XCD
+  int own;             // workgroups of the product
+};
+// describes the scan as a side job; words: counters of `done` it uses.  false: it cannot finish by itself
+bool make_side_job(const ScanArgs& s, bool rowdot, uint32_t* done, int words_left, SideJob& j, int& words);
+// side: null, or the scans that ride along (gemm_tile only)
+hipError_t launch_gemm(const GemmArgs& a, const GemmSide* side, hipStream_t st);
+bool gemm_takes_256(const GemmArgs& a);      // whether launch_gemm gives the product to the 256 x 256-tile kernel
 
 #if defined(__HIPCC__)
 // "Last workgroup finishes" without cache flushes.  Results that another workgroup of the same launch

@@ -24,7 +24,7 @@
 //     a sum that overflows): the fp32 arithmetic decides what C holds there;
 //   - the operand values a thread stages are not all zero and all below 2^-85: their low pieces get
 //     near the smallest normal number.
-#include "gecc_internal.h"
+#include "scan_device.h"
 
 namespace gecc {
 namespace {
@@ -256,30 +256,60 @@ __device__ __forceinline__ float row16_sum(float x) {
   return x;
 }
 
+// workgroup v of the scans that ride along (see GemmSide).  Fewer rows in flight than in the scans' own
+// launches: more registers here would cost the product workgroups per compute unit
+template <int DT>
+__device__ __forceinline__ void side_job(const GemmArgs& a, const GemmSide& side, int v, double* lds) {
+  if (v < side.pg_items) { form_pg(a, v, lds); return; }
+  v -= side.pg_items;
+  const bool second = v >= side.j[0].nblk;
+  if (second) v -= side.j[0].nblk;
+  const SideJob& j = second ? side.j[1] : side.j[0];
+  const int per_item = j.gx * j.gy;
+  const int b = v / per_item, x = (v % per_item) % j.gx, y = (v % per_item) / j.gx;
+  if (j.kind == SIDE_ROW) rowdot_body<DT, false, RD_SMALL_RB, 1>(j.s, x, b, lds);
+  else if (j.kind == SIDE_COL) coldot_body<DT, false, DT == GECC_F32 ? 4 : 2>(j.s, j.gy, j.gx, x, y, b, lds);
+  else if constexpr (DT == GECC_F32) rowdot_wave_body<DT, false>(j.s, x, b, lds);
+}
+
 // -------------------------------------------------------------------------------------------
-// Grid: one dimension, tiles x batch x ksplit workgroups.  Consecutive workgroups go to the 8 XCDs in
-// turn, so every XCD is given a contiguous range of the (item, split, tile row, tile column) sequence:
-// tiles that share operand panels share an L2.
+// Grid: one dimension, tiles x batch x ksplit workgroups, and among them those of the scans that ride along.
+// Consecutive workgroups go to the 8 XCDs in turn, so every XCD is given a contiguous range of the (item,
+// split, tile row, tile column) sequence: tiles that share operand panels share an L2.  The scans are
+// HBM-bound and the product is not: in one launch, spread evenly, they cost little more than the
+// product alone, and a launch that waits for the one before it costs 4.5 us whatever it does.
 template <int DT, bool KCA, bool KCB, int TILE>
-__global__ __launch_bounds__(THREADS, 2) void gemm_tile(GemmArgs a) {
+__global__ __launch_bounds__(THREADS, 2) void gemm_tile(GemmArgs a, GemmSide side) {
   using T = typename GT<DT>::T;
   constexpr int BK = GT<DT>::BK, PIECES = GT<DT>::PIECES, W = TILE / 2, NI = W / 16;   // W x W per wavefront
   constexpr int PLANE = TILE * BK * 2, OPERAND = PIECES * PLANE;
   constexpr int PLAIN = DT == GECC_F32 ? 2 * TILE * (BK + 1) * 4 : 0;
   constexpr int FAULTS = GECC_MAX_FAULTS * 8 + 16;        // list of the faults that strike this tile
-  constexpr int SUMS = 2 * 2 * TILE * 8;                  // row and column sums of the wavefronts
+  constexpr int SCAN = 8 * (CD_LDS_DOUBLES > RW_LDS_DOUBLES ? CD_LDS_DOUBLES : RW_LDS_DOUBLES);
   constexpr int SM0 = 2 * OPERAND > PLAIN ? 2 * OPERAND : PLAIN;
-  constexpr int SM1 = FAULTS > SUMS ? FAULTS : SUMS;
+  constexpr int SM1 = FAULTS > SCAN ? FAULTS : SCAN;      // (the sums of the wavefronts, 32 TILE bytes, are less)
   __shared__ __attribute__((aligned(16))) char smem[SM0 > SM1 ? SM0 : SM1];
   char* As = smem;
   char* Bs = smem + OPERAND;
 
   const int S = a.ksplit > 1 ? a.ksplit : 1;
   const int ntm = (a.n + TILE - 1) / TILE, ntn = (a.m + TILE - 1) / TILE;
-  int id;
+  int id = blockIdx.x;
+  if (side.groups > 0) {
+    // groups of 8 workgroups: group g belongs to the scans where floor(g groups / G) steps
+    const int g = id >> 3, G = gridDim.x >> 3;
+    const int before = (int)((int64_t)g * side.groups / G), after = (int)((int64_t)(g + 1) * side.groups / G);
+    if (after > before) {
+      const int v = before * 8 + (id & 7);
+      if (v < side.blocks) side_job<DT>(a, side, v, reinterpret_cast<double*>(smem));
+      return;
+    }
+    id = (g - before) * 8 + (id & 7);
+    if (id >= side.own) return;
+  }
   {
-    const int N = gridDim.x, per = N / 8, rem = N - per * 8, x = blockIdx.x & 7;
-    id = x * per + min(x, rem) + ((int)blockIdx.x >> 3);
+    const int N = side.own, per = N / 8, rem = N - per * 8, x = id & 7;
+    id = x * per + min(x, rem) + (id >> 3);
   }
   const int tn = id % ntn, tm = (id / ntn) % ntm, bs = id / (ntn * ntm);
   const int b = bs / S, split = bs - b * S;
@@ -563,10 +593,6 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_tile(GemmArgs a) {
       *reinterpret_cast<float2*>(a.colpart + (((int64_t)b * a.ntm + tm) * a.cp_ld + tile_c0 + c) * 2) =
           make_float2(colred[c].x + colred[TILE + c].x, colred[c].y + colred[TILE + c].y);
   }
-  if (tm == 0 && tn == 0 && a.pg_out) {      // P_g, once per batch item
-    __syncthreads();
-    form_pg(a, b, reinterpret_cast<double*>(smem));
-  }
 }
 
 // -------------------------------------------------------------------------------------------
@@ -653,7 +679,7 @@ __global__ __launch_bounds__(THREADS) void partials_kernel(PartialArgs a) {
 }
 
 template <int DT, int TILE>
-hipError_t launch_tile(const GemmArgs& a0, hipStream_t st) {
+hipError_t launch_tile(const GemmArgs& a0, const GemmSide* side0, hipStream_t st) {
   GemmArgs a = a0;
   const int64_t tiles = (int64_t)((a.m + TILE - 1) / TILE) * ((a.n + TILE - 1) / TILE) * a.batch;
   if (a.ksplit > 1 && a.split_part && a.split_done && tiles <= SCAN_DONE_WORDS) {
@@ -662,24 +688,32 @@ hipError_t launch_tile(const GemmArgs& a0, hipStream_t st) {
   } else {
     a.ksplit = 1;
   }
-  if (tiles * a.ksplit > 0x7fffffff) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)(tiles * a.ksplit));
+  GemmSide side = side0 ? *side0 : GemmSide{};
+  side.pg_items = a.pg_out ? a.batch : 0;
+  side.blocks = side.pg_items + side.j[0].nblk + side.j[1].nblk;
+  side.groups = (side.blocks + 7) / 8;
+  const int64_t own = tiles * a.ksplit, grid_all = side.groups > 0 ? ((own + 7) / 8 + side.groups) * 8 : own;
+  if (grid_all > 0x7fffffff) return hipErrorInvalidValue;
+  side.own = (int)own;
+  const dim3 grid((unsigned)grid_all);
   // k-contiguous storage: A when not transposed, B when transposed
   const bool kca = a.trans_a == 0, kcb = a.trans_b != 0;
-  if (kca && kcb)        hipLaunchKernelGGL((gemm_tile<DT, true, true, TILE>), grid, dim3(THREADS), 0, st, a);
-  else if (kca && !kcb)  hipLaunchKernelGGL((gemm_tile<DT, true, false, TILE>), grid, dim3(THREADS), 0, st, a);
-  else if (!kca && kcb)  hipLaunchKernelGGL((gemm_tile<DT, false, true, TILE>), grid, dim3(THREADS), 0, st, a);
-  else                   hipLaunchKernelGGL((gemm_tile<DT, false, false, TILE>), grid, dim3(THREADS), 0, st, a);
+  if (kca && kcb)        hipLaunchKernelGGL((gemm_tile<DT, true, true, TILE>), grid, dim3(THREADS), 0, st, a, side);
+  else if (kca && !kcb)  hipLaunchKernelGGL((gemm_tile<DT, true, false, TILE>), grid, dim3(THREADS), 0, st, a, side);
+  else if (!kca && kcb)  hipLaunchKernelGGL((gemm_tile<DT, false, true, TILE>), grid, dim3(THREADS), 0, st, a, side);
+  else                   hipLaunchKernelGGL((gemm_tile<DT, false, false, TILE>), grid, dim3(THREADS), 0, st, a, side);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_gemm(const GemmArgs& a, hipStream_t st) {
+bool gemm_takes_256(const GemmArgs& a) { return a.fast && gemm_bf16_fast_ok(a); }
+
+hipError_t launch_gemm(const GemmArgs& a, const GemmSide* side, hipStream_t st) {
   if (a.tile_m != a.tile_n || (a.tile_m != 128 && a.tile_m != 64)) return hipErrorInvalidValue;
-  if (a.fast && gemm_bf16_fast_ok(a)) return launch_gemm_bf16_fast(a, st);
-  if (a.tile_m == 64) return a.dtype == GECC_BF16 ? launch_tile<GECC_BF16, 64>(a, st) : launch_tile<GECC_F32, 64>(a, st);
-  return a.dtype == GECC_BF16 ? launch_tile<GECC_BF16, 128>(a, st) : launch_tile<GECC_F32, 128>(a, st);
+  if (gemm_takes_256(a)) return side ? hipErrorInvalidValue : launch_gemm_bf16_fast(a, st);
+  if (a.tile_m == 64) return a.dtype == GECC_BF16 ? launch_tile<GECC_BF16, 64>(a, side, st) : launch_tile<GECC_F32, 64>(a, side, st);
+  return a.dtype == GECC_BF16 ? launch_tile<GECC_BF16, 128>(a, side, st) : launch_tile<GECC_F32, 128>(a, side, st);
 }
 
 namespace {

@@ -4,370 +4,11 @@
 // Both kernels read the operand once with 16-byte loads that are contiguous across a
 // wavefront, accumulate in fp64 and reduce in a fixed order (no floating-point atomics), so
 // that re-forming a parity from an unchanged operand reproduces it bit for bit.
-#include "gecc_internal.h"
+#include "scan_device.h"
 #include <cstdlib>
 
 namespace gecc {
 namespace {
-
-template <int DT> struct Elem;
-template <> struct Elem<GECC_F32> {
-  using type = float;
-  static constexpr int VEC = 4;
-  using raw = float4;
-  // (memcpy: rows may start at any element; the hardware takes a 16-byte load at any address)
-  static __device__ __forceinline__ raw load_raw(const float* p) { raw x; __builtin_memcpy(&x, p, 16); return x; }
-  static __device__ __forceinline__ void widen(const raw& x, double* v) {
-    v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-  }
-  static __device__ __forceinline__ void load_vec(const float* p, double* v) { widen(load_raw(p), v); }
-  static __device__ __forceinline__ double load_one(const float* p) { return (double)*p; }
-};
-template <> struct Elem<GECC_BF16> {
-  using type = uint16_t;
-  static constexpr int VEC = 8;
-  using raw = uint4;
-  static __device__ __forceinline__ raw load_raw(const uint16_t* p) { raw x; __builtin_memcpy(&x, p, 16); return x; }
-  static __device__ __forceinline__ void widen(const raw& x, double* v) {
-    uint32_t w[4] = {x.x, x.y, x.z, x.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      v[2 * i] = (double)__uint_as_float(w[i] << 16);
-      v[2 * i + 1] = (double)__uint_as_float(w[i] & 0xffff0000u);
-    }
-  }
-  static __device__ __forceinline__ void load_vec(const uint16_t* p, double* v) { widen(load_raw(p), v); }
-  static __device__ __forceinline__ double load_one(const uint16_t* p) {
-    return (double)__uint_as_float(((uint32_t)*p) << 16);
-  }
-};
-
-__device__ __forceinline__ bool gated_off(const int32_t* gate, int64_t stride, int b, int value) {
-  if (!gate) return false;
-  const int32_t g = *reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(gate) + stride * b);
-  return g != value;
-}
-
-// wavefront-local ordering of LDS traffic: the hardware keeps a wavefront's LDS instructions in
-// order; this keeps the compiler from moving them across
-// (a compiler barrier only: a fence instruction would also wait for the wavefront's outstanding
-// global loads and stores, which is exactly what the loop must not do)
-__device__ __forceinline__ void wave_lds_fence() { asm volatile("" ::: "memory"); }
-
-// The second stage of a column reduction adds the chunk partials of an output in one fixed order,
-// whoever does it (a kernel of its own, workgroups carried by a row scan, or the last workgroup of
-// the first stage): four slices, slice w over the chunks w, w + 4, ..., each with four running sums,
-// combined as ((s0 + s1) + (s2 + s3)).
-// One slice of G outputs at once (G independent chains of loads in flight); part[g]: chunk 0's
-// partial of output g, stride: doubles between chunks.
-// DEV: the partials were written by other workgroups of this launch (load_dev)
-template <int G, bool DEV>
-__device__ __forceinline__ void slice_sums(const double* const* part, int64_t stride, int nchunk, int w, double* s) {
-  double t[G][4];
-#pragma unroll
-  for (int g = 0; g < G; ++g) { t[g][0] = 0.0; t[g][1] = 0.0; t[g][2] = 0.0; t[g][3] = 0.0; }
-  int ch = w;
-  for (; ch + 12 < nchunk; ch += 16) {
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const double* q = part[g] + (int64_t)(ch + 4 * u) * stride;
-        t[g][u] += DEV ? load_dev(q) : *q;
-      }
-  }
-  for (; ch < nchunk; ch += 4) {
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const double* q = part[g] + (int64_t)ch * stride;
-      t[g][0] += DEV ? load_dev(q) : *q;
-    }
-  }
-#pragma unroll
-  for (int g = 0; g < G; ++g) s[g] = (t[g][0] + t[g][1]) + (t[g][2] + t[g][3]);
-}
-
-// Stage 2 of coldot as workgroups of its own: 64 outputs per workgroup of 256 threads, wavefront w
-// takes slice w.  scratch, out: of batch item b; red: 256 doubles of LDS.
-__device__ __forceinline__ void coldot_stage2_body(const double* scratch, double* out, int Cc, int nchunk, int blk,
-                                                   double* red) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int o = blk * 64 + lane;                   // index into [2][Cc]
-  double s = 0.0;
-  if (o < 2 * Cc) {
-    const double* part = scratch + o;
-    slice_sums<1, false>(&part, 2 * (int64_t)Cc, nchunk, wave, &s);
-  }
-  red[wave * 64 + lane] = s;
-  __syncthreads();
-  if (wave == 0 && o < 2 * Cc) out[o] = (red[lane] + red[64 + lane]) + (red[128 + lane] + red[192 + lane]);
-}
-
-// The same sums for the 2 * 64 * VEC outputs of one column segment, by the workgroup that finished
-// the segment's last chunk.  col0: first column of the segment; red: 4 * 256 doubles of LDS.
-template <int VEC>
-__device__ __forceinline__ void coldot_finish_segment(const double* scratch, double* out, int Cc, int nchunk, int col0,
-                                                      double* red) {
-  constexpr int G = 4;                              // groups of 64 outputs a thread works on at once
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  static_assert((2 * VEC) % G == 0, "groups");
-#pragma unroll 1
-  for (int g0 = 0; g0 < 2 * VEC; g0 += G) {
-    const double* part[G];
-    int o[G];
-    bool ok[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const int t = (g0 + g) / VEC, col = col0 + ((g0 + g) % VEC) * 64 + lane;
-      ok[g] = col < Cc;
-      o[g] = t * Cc + min(col, Cc - 1);
-      part[g] = scratch + o[g];
-    }
-    double s[G];
-    slice_sums<G, true>(part, 2 * (int64_t)Cc, nchunk, wave, s);
-#pragma unroll
-    for (int g = 0; g < G; ++g) red[(g * 4 + wave) * 64 + lane] = s[g];
-    __syncthreads();
-    if (wave < G) {                                 // wavefront g writes group g
-      const int g = wave;
-      if (ok[g]) out[o[g]] = (red[(g * 4 + 0) * 64 + lane] + red[(g * 4 + 1) * 64 + lane]) +
-                             (red[(g * 4 + 2) * 64 + lane] + red[(g * 4 + 3) * 64 + lane]);
-    }
-    __syncthreads();
-  }
-}
-
-// Stage 2 of the row part of tile_scan (see below): the segments of a row added in order.
-// part: [R][nseg][2], out: [2][R], both of batch item b.
-template <bool DEV>
-__device__ __forceinline__ void rowseg_sum(const double* part, double* out, int R, int nseg, int r) {
-  const double* p = part + (int64_t)r * nseg * 2;
-  double s0 = 0.0, s1 = 0.0;
-  for (int g = 0; g < nseg; ++g) {
-    s0 += DEV ? load_dev(p + 2 * g) : p[2 * g];
-    s1 += DEV ? load_dev(p + 2 * g + 1) : p[2 * g + 1];
-  }
-  out[r] = s0;
-  out[(int64_t)R + r] = s1;
-}
-// as workgroups of their own: 256 rows each
-__device__ __forceinline__ void rowseg_stage2_body(const double* part, double* out, int R, int nseg, int blk) {
-  const int r = blk * 256 + threadIdx.x;
-  if (r < R) rowseg_sum<false>(part, out, R, nseg, r);
-}
-
-// a pending second stage (column chunks and / or row segments), by workgroup index
-__device__ __forceinline__ void stage2_dispatch(const Stage2Job& j, int b, int blk, double* lds) {
-  const int col_blocks = j.Cc > 0 ? (2 * j.Cc + 63) / 64 : 0;
-  if (blk < col_blocks)
-    coldot_stage2_body(j.scratch + (int64_t)b * j.nchunk * 2 * j.Cc, j.out + (int64_t)b * j.out_stride, j.Cc,
-                       j.nchunk, blk, lds);
-  else
-    rowseg_stage2_body(j.row_scratch + (int64_t)b * j.R * j.nseg * 2, j.row_out + (int64_t)b * j.row_out_stride,
-                       j.R, j.nseg, blk - col_blocks);
-}
-
-// -------------------------------------------------------------------------------------------
-// rowdot: out[t][r] = sum_c w_t[c] X[r,c].   One workgroup owns RB rows and walks all columns;
-// a thread keeps the weights of its VEC columns in registers and reuses them for the RB rows.
-constexpr int RD_THREADS = 256;
-constexpr int RD_BIG_RB = 16, RD_BIG_U = 1, RD_SMALL_RB = 4, RD_SMALL_U = 2;
-constexpr int RD_BIG_RB_W = 8;   // with explicit weights (they take registers too)
-
-// RD_RB rows per workgroup: 16 when there are rows enough to fill the chip, else 4.  RD_U column
-// steps are taken together, so that a thread has RD_RB * RD_U independent 16-byte loads in
-// flight before the first of them is used (the kernel is a stream over the operand: what it
-// needs is memory-level parallelism, the arithmetic hides behind it).
-// The rows bx * RD_RB ... of batch item b.  red: RD_RB * RD_THREADS doubles of LDS.  The sums of a row
-// do not depend on RD_RB or RD_U (a thread adds its columns in ascending order either way).
-template <int DT, bool IDXW, int RD_RB, int RD_U>
-__device__ __forceinline__ void rowdot_body(const ScanArgs& a, int bx, int b, double* lds) {
-  using E = Elem<DT>;
-  using T = typename E::type;
-  constexpr int VEC = E::VEC;
-  constexpr int STEP = RD_THREADS * VEC;   // columns one pass of the workgroup covers
-  const T* X = reinterpret_cast<const T*>(a.X) + (int64_t)b * a.xs;
-  const double* w0 = IDXW ? nullptr : a.w + (int64_t)b * a.w_stride;
-  const double* w1 = IDXW ? nullptr : w0 + a.Cc;
-  double* out = a.out + (int64_t)b * a.out_stride;
-  const int r0 = bx * RD_RB;
-  const int tid = threadIdx.x;
-
-  double acc0[RD_RB], acc1[RD_RB];
-#pragma unroll
-  for (int r = 0; r < RD_RB; ++r) { acc0[r] = 0.0; acc1[r] = 0.0; }
-
-  // whole vectors for every thread: rows past the end are clamped to the last one (their sums
-  // are computed and never stored), so the body has no branches
-  int c0 = 0;
-  for (; c0 + RD_U * STEP <= a.Cc; c0 += RD_U * STEP) {
-    typename E::raw x[RD_U][RD_RB];
-    double wa[RD_U][VEC], wb[RD_U][VEC];
-#pragma unroll
-    for (int u = 0; u < RD_U; ++u) {
-      const int c = c0 + u * STEP + tid * VEC;
-#pragma unroll
-      for (int r = 0; r < RD_RB; ++r)
-        x[u][r] = E::load_raw(X + (int64_t)min(r0 + r, a.R - 1) * a.ld + (unsigned)c);
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) {
-        if (IDXW) { wa[u][e] = 1.0; wb[u][e] = (double)(c + e + 1); }
-        else      { wa[u][e] = w0[c + e]; wb[u][e] = w1[c + e]; }
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < RD_U; ++u) {
-#pragma unroll
-      for (int r = 0; r < RD_RB; ++r) {
-        double v[VEC];
-        E::widen(x[u][r], v);
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-          acc0[r] = IDXW ? acc0[r] + v[e] : fma(wa[u][e], v[e], acc0[r]);
-          acc1[r] = fma(wb[u][e], v[e], acc1[r]);
-        }
-        __builtin_amdgcn_sched_barrier(0);   // widen one vector at a time (registers)
-      }
-    }
-  }
-  // the remaining columns; the thread on which the row ends in mid-vector reads the row's last vector
-  // and drops the elements its neighbour has
-  for (; c0 < a.Cc; c0 += STEP) {
-    const int c_true = c0 + tid * VEC;
-    if (c_true >= a.Cc) continue;
-    if (a.Cc >= VEC) {
-      const int c = min(c_true, a.Cc - VEC), drop = c_true - c;
-      double wa[VEC], wb[VEC];
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) {
-        if (IDXW) { wa[e] = 1.0; wb[e] = (double)(c + e + 1); }
-        else      { wa[e] = w0[c + e]; wb[e] = w1[c + e]; }
-      }
-      typename E::raw x[RD_RB];
-#pragma unroll
-      for (int r = 0; r < RD_RB; ++r) x[r] = E::load_raw(X + (int64_t)min(r0 + r, a.R - 1) * a.ld + c);
-#pragma unroll
-      for (int r = 0; r < RD_RB; ++r) {
-        double v[VEC];
-        E::widen(x[r], v);
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-          const double y = e < drop ? 0.0 : v[e];
-          acc0[r] = IDXW ? acc0[r] + y : fma(wa[e], y, acc0[r]);
-          acc1[r] = fma(wb[e], y, acc1[r]);
-        }
-      }
-    } else {
-      for (int r = 0; r < RD_RB; ++r) {
-        const int row = r0 + r;
-        if (row < a.R)
-          for (int e = 0; e < a.Cc - c_true; ++e) {
-            const double v = E::load_one(X + (int64_t)row * a.ld + c_true + e);
-            acc0[r] = fma(IDXW ? 1.0 : w0[c_true + e], v, acc0[r]);
-            acc1[r] = fma(IDXW ? (double)(c_true + e + 1) : w1[c_true + e], v, acc1[r]);
-          }
-      }
-    }
-  }
-
-  // fixed-order reduction over the 256 threads, one parity kind (t) at a time
-  double (*red)[RD_THREADS] = reinterpret_cast<double (*)[RD_THREADS]>(lds);
-  const int wave = tid >> 6, lane = tid & 63;
-#pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    if (t) __syncthreads();
-#pragma unroll
-    for (int r = 0; r < RD_RB; ++r) red[r][tid] = t ? acc1[r] : acc0[r];
-    __syncthreads();
-    for (int q = wave; q < RD_RB; q += RD_THREADS / 64) {
-      double s = (red[q][lane] + red[q][lane + 64]) + (red[q][lane + 128] + red[q][lane + 192]);
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
-      const int row = r0 + q;
-      if (lane == 0 && row < a.R) out[(int64_t)t * a.R + row] = s;
-    }
-  }
-}
-
-// The same reduction with a wavefront per RB rows (4 RB rows per workgroup): no barrier, and no idle threads
-// where a row is shorter than one pass of the workgroup.
-constexpr int RW_RB = 8;
-constexpr int RW_LDS_LD = 65;
-constexpr int RW_LDS_DOUBLES = 4 * 2 * RW_RB * RW_LDS_LD;
-template <int DT, bool IDXW>
-__device__ __forceinline__ void rowdot_wave_body(const ScanArgs& a, int bx, int b, double* lds) {
-  using E = Elem<DT>;
-  using T = typename E::type;
-  constexpr int VEC = E::VEC, STEP = 64 * VEC, RB = RW_RB;
-  const T* X = reinterpret_cast<const T*>(a.X) + (int64_t)b * a.xs;
-  const double* w0 = IDXW ? nullptr : a.w + (int64_t)b * a.w_stride;
-  const double* w1 = IDXW ? nullptr : w0 + a.Cc;
-  double* out = a.out + (int64_t)b * a.out_stride;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int r0 = (bx * 4 + wave) * RB;
-  if (r0 >= a.R) return;
-  double acc0[RB], acc1[RB];
-#pragma unroll
-  for (int r = 0; r < RB; ++r) { acc0[r] = 0.0; acc1[r] = 0.0; }
-  for (int c0 = 0; c0 < a.Cc; c0 += STEP) {
-    const int c_true = c0 + lane * VEC;
-    if (a.Cc >= VEC) {
-      // (lanes past the end read the row's last vector and drop all of it)
-      const int c = min(c_true, a.Cc - VEC), drop = c_true - c;
-      typename E::raw x[RB];
-#pragma unroll
-      for (int r = 0; r < RB; ++r) x[r] = E::load_raw(X + (int64_t)min(r0 + r, a.R - 1) * a.ld + c);
-      double wa[VEC], wb[VEC];
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) {
-        if (IDXW) { wa[e] = 1.0; wb[e] = (double)(c + e + 1); }
-        else      { wa[e] = w0[c + e]; wb[e] = w1[c + e]; }
-      }
-#pragma unroll
-      for (int r = 0; r < RB; ++r) {
-        double v[VEC];
-        E::widen(x[r], v);
-        if (c0 + STEP > a.Cc) {
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) v[e] = e < drop ? 0.0 : v[e];
-        }
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-          acc0[r] = IDXW ? acc0[r] + v[e] : fma(wa[e], v[e], acc0[r]);
-          acc1[r] = fma(wb[e], v[e], acc1[r]);
-        }
-        __builtin_amdgcn_sched_barrier(0);   // widen one vector at a time (registers)
-      }
-    } else if (c_true < a.Cc) {
-#pragma unroll
-      for (int r = 0; r < RB; ++r)
-        for (int e = 0; e < a.Cc; ++e) {
-          const double v = E::load_one(X + (int64_t)min(r0 + r, a.R - 1) * a.ld + e);
-          acc0[r] = fma(IDXW ? 1.0 : w0[e], v, acc0[r]);
-          acc1[r] = fma(IDXW ? (double)(e + 1) : w1[e], v, acc1[r]);
-        }
-    }
-  }
-  // the 64 lanes' sums, transposed through the wavefront's own LDS: four lanes per output add 16 each
-  double* tr = lds + wave * (2 * RB * RW_LDS_LD);
-#pragma unroll
-  for (int r = 0; r < RB; ++r) {
-    tr[(2 * r) * RW_LDS_LD + lane] = acc0[r];
-    tr[(2 * r + 1) * RW_LDS_LD + lane] = acc1[r];
-  }
-  wave_lds_fence();
-  const int o = lane >> 2, q = lane & 3;
-  double part[16];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) part[i] = tr[o * RW_LDS_LD + q * 16 + i];
-  double s = 0.0;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) s += part[i];
-  s += __shfl_xor(s, 1, 64);
-  s += __shfl_xor(s, 2, 64);
-  const int row = r0 + (o >> 1);
-  if (q == 0 && row < a.R) out[(int64_t)(o & 1) * a.R + row] = s;
-}
 
 // GATED: the launch belongs to the operand audit and returns at once unless the decoder asked for
 // it (a separate instantiation, so that profiles list encoding and audit launches apart).
@@ -396,136 +37,12 @@ __global__ __launch_bounds__(RD_THREADS) void rowdot_kernel(ScanArgs a) {
   rowdot_body<DT, IDXW, RD_RB, RD_U>(a, blockIdx.x, b, lds);
 }
 
-// -------------------------------------------------------------------------------------------
-// coldot: out[t][c] = sum_r w_t[r] X[r,c].   Stage 1: a workgroup owns 64*VEC columns and one
-// chunk of SCAN_CHUNK_ROWS rows; its 4 wavefronts interleave the rows and are combined through
-// LDS.  Stage 2 adds the chunks in order.
-constexpr int CD_THREADS = 256;
-
-// LDS of a coldot workgroup: the four wavefronts' sums, reused by the last workgroup of a segment
-constexpr int CD_LDS_DOUBLES = 4 * 2 * 8 * 64;
-constexpr int CD_FLAG_AT = 1024;     // (behind what coldot_finish_segment uses)
-
-// Column segment bx, chunk `chunk` of batch item b.  With a.done set, the workgroup that finishes a
-// segment's last chunk also adds the chunks up (no second stage to launch).
-template <int DT, bool IDXW>
-__device__ __forceinline__ void coldot_body(const ScanArgs& a, int nchunk, int nsegx, int bx, int chunk, int b,
-                                            double* lds) {
-  using E = Elem<DT>;
-  using T = typename E::type;
-  constexpr int VEC = E::VEC;
-  const T* X = reinterpret_cast<const T*>(a.X) + (int64_t)b * a.xs;
-  const double* w0 = IDXW ? nullptr : a.w + (int64_t)b * a.w_stride;
-  const double* w1 = IDXW ? nullptr : w0 + a.R;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // first column of a lane's vector; the lane on which the row ends in mid-vector reads the row's last
-  // vector (the columns it shares with its neighbour are left to that one below)
-  auto first_col = [&](int l) { return min((bx * 64 + l) * VEC, max(a.Cc - VEC, 0)); };
-  const int c = first_col(lane);
-  const int rbeg = chunk * SCAN_CHUNK_ROWS;
-  const int rend = min(a.R, rbeg + SCAN_CHUNK_ROWS);
-  const bool owns = (bx * 64 + lane) * VEC < a.Cc;
-
-  double acc0[VEC], acc1[VEC];
-#pragma unroll
-  for (int e = 0; e < VEC; ++e) { acc0[e] = 0.0; acc1[e] = 0.0; }
-
-  if (owns && a.Cc >= VEC) {
-    // Batches of CD_NB rows per wavefront, double buffered: the loads of the next batch are in
-    // flight while this one is added up (a wavefront walks its rows one batch after the other,
-    // so without this every batch would pay the full memory latency).
-    constexpr int CD_NB = 8;
-    typename E::raw xa[CD_NB], xb[CD_NB];
-    const T* col = X + c;
-    auto load = [&](typename E::raw* x, int rr) {
-#pragma unroll
-      for (int u = 0; u < CD_NB; ++u) x[u] = E::load_raw(col + (int64_t)(rr + 4 * u) * a.ld);
-    };
-    auto add = [&](const typename E::raw* x, int rr) {
-#pragma unroll
-      for (int u = 0; u < CD_NB; ++u) {
-        double v[VEC];
-        E::widen(x[u], v);
-        const int row = rr + 4 * u;
-        const double wa = IDXW ? 1.0 : w0[row];
-        const double wb = IDXW ? (double)(row + 1) : w1[row];
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-          acc0[e] = IDXW ? acc0[e] + v[e] : fma(wa, v[e], acc0[e]);
-          acc1[e] = fma(wb, v[e], acc1[e]);
-        }
-      }
-    };
-    int r = rbeg + wave;
-    const int cnt = r < rend ? (rend - r + 3) / 4 : 0;   // rows of this wavefront
-    const int nb = cnt / CD_NB;
-    constexpr int STEP = 4 * CD_NB;
-    if (nb > 0) {
-      load(xa, r);
-      int bi = 0;
-      for (; bi + 1 < nb; bi += 2) {
-        load(xb, r + STEP);
-        add(xa, r);
-        if (bi + 2 < nb) load(xa, r + 2 * STEP);
-        add(xb, r + STEP);
-        r += 2 * STEP;
-      }
-      if (bi < nb) { add(xa, r); r += STEP; }
-    }
-    for (; r < rend; r += 4) {
-      double v[VEC];
-      E::load_vec(col + (int64_t)r * a.ld, v);
-      const double wa = IDXW ? 1.0 : w0[r];
-      const double wb = IDXW ? (double)(r + 1) : w1[r];
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) {
-        acc0[e] = IDXW ? acc0[e] + v[e] : fma(wa, v[e], acc0[e]);
-        acc1[e] = fma(wb, v[e], acc1[e]);
-      }
-    }
-  } else if (owns) {
-    for (int r = rbeg + wave; r < rend; r += 4) {
-      const double wa = IDXW ? 1.0 : w0[r];
-      const double wb = IDXW ? (double)(r + 1) : w1[r];
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) {      // (rows shorter than a vector)
-        if (e >= a.Cc) continue;
-        const double v = E::load_one(X + (int64_t)r * a.ld + c + e);
-        acc0[e] = fma(wa, v, acc0[e]);
-        acc1[e] = fma(wb, v, acc1[e]);
-      }
-    }
-  }
-
-  double (*red)[2][VEC][64] = reinterpret_cast<double (*)[2][VEC][64]>(lds);
-#pragma unroll
-  for (int e = 0; e < VEC; ++e) { red[wave][0][e][lane] = acc0[e]; red[wave][1][e][lane] = acc1[e]; }
-  __syncthreads();
-  // thread -> (t, e, lane'): 2*VEC*64 outputs, 256 threads
-  double* part = a.scratch + ((int64_t)b * nchunk + chunk) * 2 * a.Cc;
-  for (int o = tid; o < 2 * VEC * 64; o += CD_THREADS) {
-    const int l = o & 63, e0 = (o >> 6) % VEC, t = o / (64 * VEC);
-    const int col = (bx * 64 + l) * VEC + e0;
-    if (col < a.Cc) {
-      const int e = col - first_col(l);
-      const double s = (red[0][t][e][l] + red[1][t][e][l]) + (red[2][t][e][l] + red[3][t][e][l]);
-      // (written through only when another workgroup of this launch reads it: such stores cost more)
-      if (a.done) store_dev(part + (int64_t)t * a.Cc + col, s);
-      else part[(int64_t)t * a.Cc + col] = s;
-    }
-  }
-  if (a.done && arrive_last(a.done + (int64_t)b * nsegx + bx, (uint32_t)nchunk, reinterpret_cast<int*>(lds + CD_FLAG_AT)))
-    coldot_finish_segment<VEC>(a.scratch + (int64_t)b * nchunk * 2 * a.Cc, a.out + (int64_t)b * a.out_stride, a.Cc,
-                               nchunk, bx * 64 * VEC, lds);
-}
-
 template <int DT, bool IDXW, bool GATED>
 __global__ __launch_bounds__(CD_THREADS) void coldot_stage1(ScanArgs a, int nchunk) {
   __shared__ double lds[CD_LDS_DOUBLES];
   const int b = blockIdx.z;
   if (GATED && gated_off(a.gate, a.gate_stride, b, a.gate_value)) return;
-  coldot_body<DT, IDXW>(a, nchunk, gridDim.x, blockIdx.x, blockIdx.y, b, lds);
+  coldot_body<DT, IDXW, CD_ROWS>(a, nchunk, gridDim.x, blockIdx.x, blockIdx.y, b, lds);
 }
 
 __global__ __launch_bounds__(256) void coldot_stage2(Stage2Job j) {
@@ -809,7 +326,7 @@ __global__ __launch_bounds__(256, 3) void audit_pair(PairArgs p) {
     rowdot_wave_body<DT, true>(j.s, x, b, lds);
   } else if (j.kind == PJ_COL) {
     if (gated_off(j.s.gate, j.s.gate_stride, b, j.s.gate_value)) return;
-    coldot_body<DT, true>(j.s, j.gy, j.gx, x, y, b, lds);
+    coldot_body<DT, true, CD_ROWS>(j.s, j.gy, j.gx, x, y, b, lds);
   } else {
     if (gated_off(j.t.gate, j.t.gate_stride, b, j.t.gate_value)) return;
     if (j.kind == PJ_TILE_COL) tile_scan_body<DT, true, false, true, true>(j.t, x, y, b, lds);
@@ -1011,6 +528,33 @@ hipError_t launch_tile_scan(const TileScanJob& t, Stage2Job* pending, hipStream_
     pending->R = t.R; pending->nseg = a.nseg;
   }
   return hipGetLastError();
+}
+
+bool make_side_job(const ScanArgs& s, bool rowdot, uint32_t* done, int words_left, SideJob& j, int& words) {
+  j = SideJob{};
+  j.s = s;
+  j.s.carry_blocks = 0;
+  words = 0;
+  if (s.gate || !s.w) return false;
+  if (rowdot) {
+    // (no wavefront-per-rows scan of bf16 rows: its registers would halve the product's occupancy)
+    const bool wavewise = s.dtype == GECC_F32 && rowdot_wavewise(s);
+    const int rb = wavewise ? 4 * RW_RB : RD_SMALL_RB;
+    j.kind = wavewise ? SIDE_ROW_WAVE : SIDE_ROW;
+    j.gx = (s.R + rb - 1) / rb; j.gy = 1;
+  } else {
+    words = coldot_done_words(s);
+    if (words == 0 || words > words_left) return false;
+    const int vec = s.dtype == GECC_BF16 ? 8 : 4;
+    j.kind = SIDE_COL;
+    j.s.done = done;
+    j.gx = (s.Cc + 64 * vec - 1) / (64 * vec);
+    j.gy = (s.R + SCAN_CHUNK_ROWS - 1) / SCAN_CHUNK_ROWS;
+  }
+  const int64_t blocks = (int64_t)j.gx * j.gy * s.batch;
+  if (blocks > (1 << 28)) return false;
+  j.nblk = (int)blocks;
+  return true;
 }
 
 // ---- the two audits in one launch ---------------------------------------------------------------
