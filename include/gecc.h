@@ -307,8 +307,9 @@ int gecc_syndromes_to_host(gecc_ctx* ctx, double* host_syndromes, void* stream);
    recorded pairs, writes their durations in milliseconds to host_ms[0..*count) and their classes
    to host_kind[0..*count) (at most cap each; host_kind may be null) and rearms.  The product
    class brackets everything gecc_multiply's product step enqueues (the k-split tail's zeroing
-   and second launch included); a row scan that carries the second stage of a column scan is
-   timed with it. */
+   and second launch included) and the parity blocks P_r, P_c where they ride in its launch; a row
+   scan that carries the second stage of a column scan is timed with it.  A launch that does the work of
+   two classes (Section V step 2 with both re-encodings) leaves a record of each, over the same span. */
 enum {
   GECC_K_ENCODE_A = 0,  /* A_P = [P_n1; P_n2] A                          */
   GECC_K_ENCODE_B = 1,  /* B_P = B [P_m1^T P_m2^T]                       */
@@ -324,7 +325,7 @@ enum {
   GECC_K_STAGE2 = 11,   /* second stage of a scan, launched alone        */
   GECC_K_TILE_A = 12,   /* A_P and P_r in one pass over A                */
   GECC_K_TILE_B = 13,   /* B_P and P_c in one pass over B                */
-  GECC_K_AUDIT_AB = 14, /* both gated re-encodings in one launch         */
+  GECC_K_AUDIT_AB = 14, /* both gated re-encodings in one launch (with GECC_K_DECODE) */
   GECC_K_COUNT = 15
 };
 int gecc_timing_enable(gecc_ctx* ctx, int32_t max_records, uint32_t kinds_mask);

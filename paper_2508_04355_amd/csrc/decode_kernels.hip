@@ -3,7 +3,7 @@
 // errors in A and B (each column of [A; A_P] and each row of [B B_P] is a codeword with two
 // parity symbols, Section III).  All scalar decoding arithmetic is fp64; everything is
 // stream-ordered and gated on state kept in device memory, so no host round trip is needed.
-#include "gecc_internal.h"
+#include "scan_device.h"
 
 namespace gecc {
 namespace {
@@ -273,9 +273,11 @@ __device__ int accept(Est* est, int ne, const int* Er, int s, const int* Et, int
   return k;
 }
 
-// Correction rule for 1 <= s, t <= 2 (s <= t: columns carry the information; s > t mirrored).
+// Correction rule for 1 <= s, t <= 2 (s <= t: columns carry the information; s > t mirrored).  By one thread
+// of the workgroup; Er, Et and out are in LDS like the estimates here (indexed at run time, they would put
+// a quarter of a KiB of scratch under every thread of the kernel).
 __device__ int d0_correct(Est* out, const int* Er, int s, const int* Et, int t, const Synd& y) {
-  Est est[4];
+  __shared__ Est est[4], dg[4], an[4];
   if (s <= t) {
     if (s == 1) {
       for (int c = 0; c < t; ++c) est[c] = Est{Er[0], Et[c], y.q1[Et[c]], y.tq1(Et[c])};
@@ -284,8 +286,10 @@ __device__ int d0_correct(Est* out, const int* Er, int s, const int* Et, int t, 
       return k;
     }
     const int s1 = Er[0], s2 = Er[1], t1 = Et[0], t2 = Et[1];
-    Est dg[4] = {Est{s1, t1, y.q1[t1], y.tq1(t1)}, Est{s2, t2, y.q1[t2], y.tq1(t2)}};
-    Est an[4] = {Est{s1, t2, y.q1[t2], y.tq1(t2)}, Est{s2, t1, y.q1[t1], y.tq1(t1)}};
+    dg[0] = Est{s1, t1, y.q1[t1], y.tq1(t1)};
+    dg[1] = Est{s2, t2, y.q1[t2], y.tq1(t2)};
+    an[0] = Est{s1, t2, y.q1[t2], y.tq1(t2)};
+    an[1] = Est{s2, t1, y.q1[t1], y.tq1(t1)};
     const int kd = accept(dg, 2, Er, s, Et, t, y);
     const int ka = accept(an, 2, Er, s, Et, t, y);
     if (kd >= 0 && ka >= 0) return -1;   // cannot tell the two apart
@@ -312,21 +316,21 @@ __device__ int d0_correct(Est* out, const int* Er, int s, const int* Et, int t, 
   return k;
 }
 
-// fp64 dot product of row i of A with column j of B over k, by the whole workgroup
-__device__ double block_dot(const DecodeArgs& a, int b, int i, int j, double* red) {
+// fp64 dot product of row i of A with column j of B over the terms l_beg .. l_end, by the whole workgroup
+__device__ double block_dot(const DecodeArgs& a, int b, int i, int j, int l_beg, int l_end, double* red) {
   double s = 0.0;
   constexpr int U = 8;   // products per thread whose loads are issued together (one workgroup: latency-bound)
-  for (int l0 = threadIdx.x; l0 < a.p.k; l0 += U * DC_THREADS) {
+  for (int l0 = l_beg + (int)threadIdx.x; l0 < l_end; l0 += U * DC_THREADS) {
     double x[U], y[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int l = min(l0 + u * DC_THREADS, a.p.k - 1);
+      const int l = min(l0 + u * DC_THREADS, l_end - 1);
       x[u] = load_elem(a.A, a.p.dtype, a_index(a, b, i, l));
       y[u] = load_elem(a.B, a.p.dtype, b_index(a, b, l, j));
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      if (l0 + u * DC_THREADS < a.p.k) s = fma(x[u], y[u], s);
+      if (l0 + u * DC_THREADS < l_end) s = fma(x[u], y[u], s);
   }
   red[threadIdx.x] = s;
   __syncthreads();
@@ -347,8 +351,10 @@ __device__ double block_dot(const DecodeArgs& a, int b, int i, int j, double* re
 // chunk of the other-kind lines.  Returns the number of corrected symbols, or -1.
 struct LineEst { double x[2], u[2]; bool sig[2], flagged; };
 
+// pool: POOL_DOUBLES of LDS
+constexpr int POOL_DOUBLES = 2048 + 256;
 __device__ int known_lines_correct(const DecodeArgs& a, int b, DecodeState* st, gecc_report* rep,
-                                   const Synd& y, int final_pass) {
+                                   const Synd& y, int final_pass, double* pool) {
   const int n = a.p.n, m = a.p.m;
   const int s = st->s_cnt, t = st->t_cnt;
   const bool rows_known = a.p.weighted ? s <= 2 : s == 1;
@@ -380,8 +386,8 @@ __device__ int known_lines_correct(const DecodeArgs& a, int b, DecodeState* st, 
     return e;
   };
 
-  __shared__ double t2_red[8][256];
-  __shared__ int t2_cnt[2][256];
+  double (*t2_red)[256] = reinterpret_cast<double (*)[256]>(pool);             // [8][256]
+  int (*t2_cnt)[256] = reinterpret_cast<int (*)[256]>(pool + 2048);             // [2][256]
   __shared__ int t2_bad;
   const int tid = threadIdx.x, ch = (L + DC_THREADS - 1) / DC_THREADS;
   const int c0 = min(L, tid * ch), c1 = min(L, c0 + ch);
@@ -455,86 +461,46 @@ __device__ int known_lines_correct(const DecodeArgs& a, int b, DecodeState* st, 
   return total[0] + total[1];
 }
 
-// Section V step 2 for one batch item, by DC_THREADS threads.  final_pass = 0: right after
-// detection; = 1: on the residual syndromes after an operand repair (per-line allowances apply,
-// failure is final).
-__device__ void decode_c_body(const DecodeArgs& a, int b, DecodeState* st, gecc_report* rep, int final_pass) {
-  __shared__ Est fix[4];
-  __shared__ int nfix;          // -1: the rule does not apply / failed
-  __shared__ double red[256];
-  const int n = a.p.n, m = a.p.m;
-  if (st->nonfinite) {
-    // a syndrome that is not a number: no estimate can be subtracted, the product is computed again
-    if (threadIdx.x == 0) { rep->status = GECC_UNCORRECTABLE; rep->n_err = 0; rep->n_total = 0; st->phase = PH_DONE; }
-    return;
+// What Section V step 2 makes of the flagged lines: thread 0 fills fix[0 .. *nfix); *nfix = -1: the rule does
+// not apply or failed.
+__device__ void plan_fixes(const DecodeArgs& a, int b, const DecodeState* st, int final_pass, Est* fix, int* nfix) {
+  if (threadIdx.x != 0) return;
+  const int n = a.p.n, m = a.p.m, s = st->s_cnt, t = st->t_cnt;
+  *nfix = -1;
+  if (s == 0 && t == 0) {
+    *nfix = 0;
+  } else if (s >= 1 && s <= 2 && t >= 1 && t <= 2 && (a.p.weighted || (s == 1 && t == 1))) {
+    __shared__ int Er[2], Et[2];
+    for (int x = 0; x < s; ++x) Er[x] = st->rows[x];
+    for (int x = 0; x < t; ++x) Et[x] = st->cols[x];
+    sort_small(Er, s);
+    sort_small(Et, t);
+    const double* sy = synd_of(a, b);
+    const double* al = final_pass ? allow_of(a, b) : nullptr;
+    Synd y{sy, sy + n, sy + 2 * n, sy + 2 * n + m, a.p.tau_r1, a.p.tau_r2, a.p.tau_q1, a.p.tau_q2,
+           al, al ? al + n : nullptr, al ? al + 2 * n : nullptr, al ? al + 2 * n + m : nullptr,
+           a.p.tau_rel, a.p.weighted != 0};
+    const int k = d0_correct(fix, Er, s, Et, t, y);
+    if (k >= 0) *nfix = k;
   }
-  {
-    const int s = st->s_cnt, t = st->t_cnt, lo = min(s, t), hi = max(s, t);
-    // Theorem 2: many lines of one kind, at most two of the other.  Its errors all lie in C-bar,
-    // so it runs only after the operand audit (on what the repair leaves, or on the whole pattern
-    // when both operands are intact): a wrong symbol of A a few rows from a flagged row would
-    // otherwise pass for a row full of small errors of C.
-    // (single-checksum mode: one known line only, any number of the other kind -- Appendix A, case s = 1)
-    if (final_pass && (a.p.weighted ? (lo >= 1 && lo <= 2 && hi > 2) : (lo == 1 && hi >= 2))) {
-      const double* sy = synd_of(a, b);
-      const double* al = final_pass ? allow_of(a, b) : nullptr;
-      const Synd y{sy, sy + n, sy + 2 * n, sy + 2 * n + m, a.p.tau_r1, a.p.tau_r2, a.p.tau_q1, a.p.tau_q2,
-                   al, al ? al + n : nullptr, al ? al + 2 * n : nullptr, al ? al + 2 * n + m : nullptr,
-                   a.p.tau_rel, a.p.weighted != 0};
-      const int k = known_lines_correct(a, b, st, rep, y, final_pass);
-      if (threadIdx.x == 0) {
-        if (k < 0) {
-          rep->status = GECC_UNCORRECTABLE; rep->n_err = 0; rep->n_total = 0; st->phase = PH_DONE;
-        } else {
-          for (int e = 0; e < st->n_err; ++e) rep->err[e] = st->errs[e];
-          rep->n_total = st->n_err + k;
-          rep->n_err = min(rep->n_total, GECC_MAX_ERR);
-          rep->status = GECC_CORRECTED;
-          st->phase = PH_DONE;
-        }
-      }
-      return;
-    }
-  }
-  if (threadIdx.x == 0) {
-    const int s = st->s_cnt, t = st->t_cnt;
-    nfix = -1;
-    if (s == 0 && t == 0) {
-      nfix = 0;
-    } else if (s >= 1 && s <= 2 && t >= 1 && t <= 2 && (a.p.weighted || (s == 1 && t == 1))) {
-      int Er[2], Et[2];
-      for (int x = 0; x < s; ++x) Er[x] = st->rows[x];
-      for (int x = 0; x < t; ++x) Et[x] = st->cols[x];
-      sort_small(Er, s);
-      sort_small(Et, t);
-      const double* sy = synd_of(a, b);
-      const double* al = final_pass ? allow_of(a, b) : nullptr;
-      Synd y{sy, sy + n, sy + 2 * n, sy + 2 * n + m, a.p.tau_r1, a.p.tau_r2, a.p.tau_q1, a.p.tau_q2,
-             al, al ? al + n : nullptr, al ? al + 2 * n : nullptr, al ? al + 2 * n + m : nullptr,
-             a.p.tau_rel, a.p.weighted != 0};
-      Est tmp[4];
-      const int k = d0_correct(tmp, Er, s, Et, t, y);
-      if (k >= 0) {
-        for (int e = 0; e < k; ++e) fix[e] = tmp[e];
-        nfix = k;
-      }
-    }
-  }
-  __syncthreads();
-  const int k = nfix;
-  if (k < 0) {
-    if (threadIdx.x == 0) {
-      if (final_pass) { rep->status = GECC_UNCORRECTABLE; rep->n_err = 0; rep->n_total = 0; st->phase = PH_DONE; }
-      else            { st->phase = PH_AUDIT; if (a.gate_word) *a.gate_word = PH_AUDIT; }
-    }
-    return;
-  }
-  // patch C: Section V's subtraction, optionally followed by re-evaluating the symbol
+}
+
+__device__ void give_up(DecodeState* st, gecc_report* rep) {
+  rep->status = GECC_UNCORRECTABLE;
+  rep->n_err = 0;
+  rep->n_total = 0;
+  st->phase = PH_DONE;
+}
+
+// patch C: Section V's subtraction, or the symbol evaluated again (dots: what block_dot gives for every fix, or
+// null: by this workgroup); then the report
+__device__ void apply_fixes(const DecodeArgs& a, int b, DecodeState* st, gecc_report* rep, const Est* fix, int k, double* pool,
+                            const double* dots) {
   float* C = c_of(a, b);
   for (int e = 0; e < k; ++e) {
     const int64_t idx = (int64_t)fix[e].i * a.p.ldc + fix[e].j;
     if (a.p.refine) {
-      const double d = block_dot(a, b, fix[e].i, fix[e].j, red);
+      const double d = dots ? dots[e] : block_dot(a, b, fix[e].i, fix[e].j, 0, a.p.k, pool);
       if (threadIdx.x == 0) C[idx] = (float)d;
     } else if (threadIdx.x == 0) {
       C[idx] = (float)((double)C[idx] - fix[e].x);
@@ -557,6 +523,59 @@ __device__ void decode_c_body(const DecodeArgs& a, int b, DecodeState* st, gecc_
   }
 }
 
+// Section V step 2 for one batch item, by DC_THREADS threads.  final_pass = 0: right after
+// detection; = 1: on the residual syndromes after an operand repair (per-line allowances apply,
+// failure is final).  pool: POOL_DOUBLES of LDS
+__device__ void decode_c_body(const DecodeArgs& a, int b, DecodeState* st, gecc_report* rep, int final_pass, double* pool) {
+  __shared__ Est fix[4];
+  __shared__ int nfix;
+  const int n = a.p.n, m = a.p.m;
+  if (st->nonfinite) {
+    // a syndrome that is not a number: no estimate can be subtracted, the product is computed again
+    if (threadIdx.x == 0) give_up(st, rep);
+    return;
+  }
+  {
+    const int s = st->s_cnt, t = st->t_cnt, lo = min(s, t), hi = max(s, t);
+    // Theorem 2: many lines of one kind, at most two of the other.  Its errors all lie in C-bar,
+    // so it runs only after the operand audit (on what the repair leaves, or on the whole pattern
+    // when both operands are intact): a wrong symbol of A a few rows from a flagged row would
+    // otherwise pass for a row full of small errors of C.
+    // (single-checksum mode: one known line only, any number of the other kind -- Appendix A, case s = 1)
+    if (final_pass && (a.p.weighted ? (lo >= 1 && lo <= 2 && hi > 2) : (lo == 1 && hi >= 2))) {
+      const double* sy = synd_of(a, b);
+      const double* al = final_pass ? allow_of(a, b) : nullptr;
+      const Synd y{sy, sy + n, sy + 2 * n, sy + 2 * n + m, a.p.tau_r1, a.p.tau_r2, a.p.tau_q1, a.p.tau_q2,
+                   al, al ? al + n : nullptr, al ? al + 2 * n : nullptr, al ? al + 2 * n + m : nullptr,
+                   a.p.tau_rel, a.p.weighted != 0};
+      const int k = known_lines_correct(a, b, st, rep, y, final_pass, pool);
+      if (threadIdx.x == 0) {
+        if (k < 0) {
+          give_up(st, rep);
+        } else {
+          for (int e = 0; e < st->n_err; ++e) rep->err[e] = st->errs[e];
+          rep->n_total = st->n_err + k;
+          rep->n_err = min(rep->n_total, GECC_MAX_ERR);
+          rep->status = GECC_CORRECTED;
+          st->phase = PH_DONE;
+        }
+      }
+      return;
+    }
+  }
+  plan_fixes(a, b, st, final_pass, fix, &nfix);
+  __syncthreads();
+  const int k = nfix;
+  if (k < 0) {
+    if (threadIdx.x == 0) {
+      if (final_pass) give_up(st, rep);
+      else            { st->phase = PH_AUDIT; if (a.gate_word) *a.gate_word = PH_AUDIT; }
+    }
+    return;
+  }
+  apply_fixes(a, b, st, rep, fix, k, pool, nullptr);
+}
+
 // One workgroup per batch item, right after detection.  with_summary: this kernel also writes
 // the first report (saves the summary launch).
 __global__ __launch_bounds__(DC_THREADS) void decode_c_kernel(DecodeArgs a, int with_summary) {
@@ -568,7 +587,8 @@ __global__ __launch_bounds__(DC_THREADS) void decode_c_kernel(DecodeArgs a, int 
   } else {
     if (rep->status != GECC_DETECTED) return;
   }
-  decode_c_body(a, b, st, rep, 0);
+  __shared__ double pool[DC_THREADS];     // (no Theorem 2 in this pass)
+  decode_c_body(a, b, st, rep, 0, pool);
 }
 
 // ---- operand audit -----------------------------------------------------------------------------
@@ -612,6 +632,7 @@ __global__ __launch_bounds__(RP_THREADS) void repair_kernel(DecodeArgs a) {
   DecodeState* st = state_of(a, b);
   if (st->phase != PH_AUDIT) return;
   gecc_report* rep = a.report + b;
+  __shared__ double pool[4 * RP_THREADS];
   __shared__ int ok, cnt_a, cnt_b;
   __shared__ AuditHit ha[GECC_MAX_ERR], hb[GECC_MAX_ERR];
   const int n = a.p.n, m = a.p.m, k = a.p.k;
@@ -645,7 +666,7 @@ __global__ __launch_bounds__(RP_THREADS) void repair_kernel(DecodeArgs a) {
   }
   __syncthreads();
   if (!ok) {
-    if (threadIdx.x == 0) { rep->status = GECC_UNCORRECTABLE; rep->n_err = 0; rep->n_total = 0; st->phase = PH_DONE; }
+    if (threadIdx.x == 0) give_up(st, rep);
     return;
   }
   float* C = c_of(a, b);
@@ -665,7 +686,7 @@ __global__ __launch_bounds__(RP_THREADS) void repair_kernel(DecodeArgs a) {
   double* sy_r2 = sy_r1 + n;
   double* sy_q1 = sy_r1 + 2 * n;
   double* sy_q2 = sy_r1 + 2 * n + m;
-  __shared__ double red[4][RP_THREADS];
+  double (*red)[RP_THREADS] = reinterpret_cast<double (*)[RP_THREADS]>(pool);
   for (int o = threadIdx.x; o < 2 * n + 2 * m; o += blockDim.x) al_r1[o] = 0.0;
   __syncthreads();
   for (int x = 0; x < na; ++x) {
@@ -843,7 +864,103 @@ __global__ __launch_bounds__(RP_THREADS) void repair_kernel(DecodeArgs a) {
   __syncthreads();
   // ... and step 2, by the first DC_THREADS threads (the other wavefronts end here)
   if (SPLIT || threadIdx.x >= DC_THREADS) return;
-  decode_c_body(a, b, st, rep, 1);
+  decode_c_body(a, b, st, rep, 1, pool);
+}
+
+// Section V step 2 and, where it fails, the two re-encodings of the operand audit in one launch: a launch that
+// waits for the one before it costs 4.5 us whatever it does, and after a clean product this one only has the
+// report to write.  Workgroup v of the audits decides from the counters and syndromes of the threshold pass,
+// on its own and like all others, what Section V step 2 makes of its item: nothing or patches of C, or the
+// audit (done by all of them; the repair follows as a launch of its own, with more threads).  Nobody writes
+// what the others decide by.
+// A symbol of C that is evaluated again is a dot product whose one operand lies in memory with a stride: a
+// line per term, of which one compute unit keeps a few dozen on their way (k = 4096: 25 us a symbol).
+// The first workgroups of the item share it out, at least FINISH_TERMS terms each; the one that comes last
+// adds the shares up in order and patches.
+// A closed launch lasts as long as its dispatch, about 2 us per thousand workgroups (the caller keeps very
+// large pairs out).  Walking the rest with a grid that fits the chip was measured and is not kept: the
+// compiler then holds what every scan needs across the walk (226 registers instead of 168, and audits that
+// took 28 to 55 us from one build to the next instead of 24).
+static_assert(DC_THREADS <= PAIR_LDS_DOUBLES, "the decoder works in the audits' LDS");
+constexpr int FINISH_SHARES = 64, FINISH_TERMS = 64;
+struct FinishArgs {
+  DecodeArgs a;
+  PairArgs audits;
+  double* shares;        // per item 2k doubles (the audits' own, unused while C alone is patched)
+  uint32_t* share_done;  // per item a counter
+  int with_summary;
+};
+struct FinishWork {
+  int b, x, y, q;        // item, workgroup of the scan, number among the item's workgroups
+  bool second;
+};
+__device__ __forceinline__ FinishWork finish_work(const PairArgs& audits, int w) {
+  FinishWork o;
+  o.second = w >= audits.j[0].nblk;
+  const PairJob& j = o.second ? audits.j[1] : audits.j[0];
+  const int v = o.second ? w - audits.j[0].nblk : w, per_item = j.gx * j.gy;
+  o.b = v / per_item; o.x = (v % per_item) % j.gx; o.y = (v % per_item) / j.gx;
+  o.q = v % per_item + (o.second ? audits.j[0].gx * audits.j[0].gy : 0);
+  return o;
+}
+template <int DT>
+__global__ __launch_bounds__(DC_THREADS, 3) void finish_kernel(FinishArgs) {
+  // (the arguments where the launch left them: through the parameter, the compiler gives every thread a copy
+  // in scratch to write before the first decision)
+  const FinishArgs& f = *(const FinishArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  const DecodeArgs& a = f.a;
+  __shared__ double lds[PAIR_LDS_DOUBLES];
+  __shared__ Est fix[4];
+  __shared__ double dots[4];
+  __shared__ int nfix, act, flag;
+  enum { NOTHING, CLEAN, PATCH, AUDIT };
+  const FinishWork o = finish_work(f.audits, blockIdx.x);
+  DecodeState* st = state_of(a, o.b);
+  gecc_report* rep = a.report + o.b;
+  // (one thread decides for the workgroup: the item's first workgroups may be writing the report meanwhile)
+  if (threadIdx.x == 0)
+    act = f.with_summary ? (st->s_cnt != 0 || st->t_cnt != 0 ? AUDIT : o.q == 0 ? CLEAN : NOTHING)
+                         : (rep->status == GECC_DETECTED ? AUDIT : NOTHING);
+  __syncthreads();
+  if (act == NOTHING) return;
+  if (act == CLEAN) { summarize(a, o.b, st, rep); return; }
+
+  // workgroups of an item that share a dot product
+  const int per_item = f.audits.j[0].gx * f.audits.j[0].gy + f.audits.j[1].gx * f.audits.j[1].gy;
+  const int shares = a.p.refine ? max(1, min(min(per_item, FINISH_SHARES), a.p.k / FINISH_TERMS)) : 1;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    plan_fixes(a, o.b, st, 0, fix, &nfix);
+    act = !st->nonfinite && nfix < 0 ? AUDIT : o.q == 0 || (!st->nonfinite && nfix > 0 && o.q < shares) ? PATCH : NOTHING;
+  }
+  __syncthreads();
+  const int todo = act;
+  if (todo == NOTHING) return;
+  bool writes = o.q == 0;
+  const bool dot = todo == PATCH && !st->nonfinite && nfix > 0 && shares > 1;
+  if (dot) {
+    double* mine = f.shares + (int64_t)o.b * 2 * a.p.k;
+    const int per = (a.p.k + shares - 1) / shares, l0 = min(a.p.k, o.q * per), l1 = min(a.p.k, l0 + per);
+    for (int e = 0; e < nfix; ++e) {
+      const double d = l0 < l1 ? block_dot(a, o.b, fix[e].i, fix[e].j, l0, l1, lds) : 0.0;
+      if (threadIdx.x == 0) store_dev(mine + e * shares + o.q, d);
+    }
+    writes = arrive_last(f.share_done + o.b, (uint32_t)shares, &flag);
+    if (writes && (int)threadIdx.x < nfix) {
+      double d = 0.0;
+      for (int q = 0; q < shares; ++q) d += load_dev(mine + threadIdx.x * shares + q);
+      dots[threadIdx.x] = d;
+    }
+    __syncthreads();
+  }
+  if (writes) {
+    if (f.with_summary) { summarize(a, o.b, st, rep); __syncthreads(); }
+    if (todo == AUDIT) { if (threadIdx.x == 0) st->phase = PH_AUDIT; }
+    else if (!st->nonfinite) apply_fixes(a, o.b, st, rep, fix, nfix, lds, dot ? dots : nullptr);
+    else if (threadIdx.x == 0) give_up(st, rep);
+    __syncthreads();
+  }
+  if (todo == AUDIT) pair_body<DT>(o.second ? f.audits.j[1] : f.audits.j[0], o.x, o.y, o.b, lds);
 }
 
 // Blocked mode, after repair_kernel<true>: the located operand symbols are put right, once per
@@ -882,7 +999,8 @@ __global__ __launch_bounds__(DC_THREADS) void final_decode_kernel(DecodeArgs a) 
   const int b = blockIdx.x;
   DecodeState* st = state_of(a, b);
   if (st->phase != PH_REVERIFY) return;
-  decode_c_body(a, b, st, a.report + b, 1);
+  __shared__ double pool[POOL_DOUBLES];
+  decode_c_body(a, b, st, a.report + b, 1, pool);
 }
 
 // Blocked mode: syndromes of every block from the partial sums of the 128 x 128 sub-tiles (a block
@@ -1040,6 +1158,14 @@ hipError_t launch_decode_c(const DecodeArgs& a, int with_summary, hipStream_t st
 
 hipError_t launch_repair(const DecodeArgs& a, hipStream_t st) {
   hipLaunchKernelGGL(repair_kernel<false>, dim3(a.p.batch), dim3(RP_THREADS), 0, st, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_finish(const DecodeArgs& a, const PairArgs& audits, uint32_t* share_done, int with_summary, hipStream_t st) {
+  const dim3 grid(audits.j[0].nblk + audits.j[1].nblk);
+  const FinishArgs f{a, audits, const_cast<double*>(a.audit_a), share_done, with_summary};
+  if (a.p.dtype == GECC_BF16) hipLaunchKernelGGL(finish_kernel<GECC_BF16>, grid, dim3(DC_THREADS), 0, st, f);
+  else                        hipLaunchKernelGGL(finish_kernel<GECC_F32>, grid, dim3(DC_THREADS), 0, st, f);
   return hipGetLastError();
 }
 

@@ -230,23 +230,24 @@ struct ScanJob {
 };
 
 // Brackets the launches between its construction and done() with a timing record, when the
-// context records launches of that class.
+// context records launches of that class.  ahead: records that were begun before this one and are not done
+// yet (a launch that does the work of several classes leaves a record of each).
 struct Timed {
   gecc_ctx* c;
   hipStream_t st;
-  int kind;
+  int kind, at;
   bool on;
   hipError_t err;
-  Timed(gecc_ctx* ctx, int k, hipStream_t s) : c(ctx), st(s), kind(k), err(hipSuccess) {
-    on = c->ev && ((c->ev_mask >> k) & 1u) && c->ev_n < c->ev_cap;
-    if (on) err = hipEventRecord(c->ev[2 * c->ev_n], st);
+  Timed(gecc_ctx* ctx, int k, hipStream_t s, int ahead = 0) : c(ctx), st(s), kind(k), at(ctx->ev_n + ahead), err(hipSuccess) {
+    on = c->ev && ((c->ev_mask >> k) & 1u) && at < c->ev_cap;
+    if (on) err = hipEventRecord(c->ev[2 * at], st);
   }
   hipError_t done(hipError_t launch_result) {
     if (launch_result != hipSuccess) return launch_result;
     if (err != hipSuccess) return err;
     if (on) {
-      if ((err = hipEventRecord(c->ev[2 * c->ev_n + 1], st)) != hipSuccess) return err;
-      c->ev_kind[c->ev_n] = kind;
+      if ((err = hipEventRecord(c->ev[2 * at + 1], st)) != hipSuccess) return err;
+      c->ev_kind[at] = kind;
       ++c->ev_n;
     }
     return hipSuccess;
@@ -381,13 +382,6 @@ struct ScanQueue {
     if (tj.gate) f.done = done();
     Timed t(c, kind, st);
     return t.done(launch_tile_scan(f, &pending, st));
-  }
-  // both gated audits in one launch, where every column reduction among them can finish by itself
-  hipError_t run_audit_pair(const ScanPairItem& x0, const ScanPairItem& x1) {
-    hipError_t e;
-    if (pending.valid && (e = flush()) != hipSuccess) return e;
-    Timed t(c, GECC_K_AUDIT_AB, st);
-    return t.done(launch_audit_pair(x0, x1, done(), st));
   }
 };
 
@@ -798,6 +792,29 @@ int correct_impl(gecc_ctx* ctx, void* dev_A, const double* dev_A_par, void* dev_
   DecodeArgs d = decode_args(ctx, dev_A, dev_A_par, dev_B, dev_B_par, dev_C, dev_C_par, dev_report);
   const int32_t* gate = &d.state->phase;
   hipError_t e;
+  // operand audit: re-form the parities of A and B as the product read them
+  // (an encoding made by the tile scan is re-formed by the tile scan: same sums, same order)
+  ScanQueue q{ctx, st};
+  const ScanJob ja = scan_a_over_n(ctx, dev_A, nullptr, const_cast<double*>(d.audit_a), gate);
+  const ScanJob jb = scan_b_over_m(ctx, dev_B, nullptr, const_cast<double*>(d.audit_b), gate);
+  const bool t_is_a = ctx->tile_op == GECC_MAT_A;
+  const TileScanJob tj = tile_job(ctx, ctx->tile_op, t_is_a ? dev_A : dev_B,
+                                  const_cast<double*>(t_is_a ? d.audit_a : d.audit_b), nullptr, nullptr, 0, gate);
+  const bool tile = use_tile(ctx, tj);
+  if (!blocked(ctx)) {
+    // both and Section V step 2 in one launch, where every column reduction of the audits can finish by itself
+    PairArgs pair;
+    int words = 0;
+    if (make_audit_pair({tile && t_is_a ? 2 : (ja.rowdot ? 0 : 1), ja.s, tj}, {tile && !t_is_a ? 2 : (jb.rowdot ? 0 : 1), jb.s, tj},
+                        q.done(), pair, words) && words + ctx->p.batch <= SCAN_DONE_WORDS) {
+      {
+        Timed td(ctx, GECC_K_DECODE, st), ta(ctx, GECC_K_AUDIT_AB, st, td.on);
+        if ((e = ta.done(td.done(launch_finish(d, pair, q.done() + words, with_summary, st)))) != hipSuccess) return hip_rc(e);
+      }
+      Timed t(ctx, GECC_K_REPAIR, st);
+      return hip_rc(t.done(launch_repair(d, st)));
+    }
+  }
   // Section V step 2 on the flagged lines; on failure the phase becomes PH_AUDIT
   {
     Timed t(ctx, GECC_K_DECODE, st);
@@ -830,21 +847,8 @@ int correct_impl(gecc_ctx* ctx, void* dev_A, const double* dev_A_par, void* dev_
     Timed t(ctx, GECC_K_REPAIR, st);
     return hip_rc(t.done(launch_repair_blocked(d, ctx->nbi, st)));
   }
-  // operand audit: re-form the parities of A and B as the product read them
   // (the coldot of the two first, so that the rowdot carries its second stage)
-  // (an encoding made by the tile scan is re-formed by the tile scan: same sums, same order)
-  ScanQueue q{ctx, st};
-  const ScanJob ja = scan_a_over_n(ctx, dev_A, nullptr, const_cast<double*>(d.audit_a), gate);
-  const ScanJob jb = scan_b_over_m(ctx, dev_B, nullptr, const_cast<double*>(d.audit_b), gate);
-  const bool t_is_a = ctx->tile_op == GECC_MAT_A;
-  const TileScanJob tj = tile_job(ctx, ctx->tile_op, t_is_a ? dev_A : dev_B,
-                                  const_cast<double*>(t_is_a ? d.audit_a : d.audit_b), nullptr, nullptr, 0, gate);
-  const bool tile = use_tile(ctx, tj);
-  const ScanPairItem xa{tile && t_is_a ? 2 : (ja.rowdot ? 0 : 1), ja.s, tj};
-  const ScanPairItem xb{tile && !t_is_a ? 2 : (jb.rowdot ? 0 : 1), jb.s, tj};
-  if (audit_pair_ok(xa, xb)) {
-    if ((e = q.run_audit_pair(xa, xb)) != hipSuccess) return hip_rc(e);
-  } else if (tile) {
+  if (tile) {
     if ((e = q.run_tile(tj, t_is_a ? GECC_K_AUDIT_A : GECC_K_AUDIT_B)) != hipSuccess) return hip_rc(e);
     if ((e = q.run(t_is_a ? jb : ja)) != hipSuccess) return hip_rc(e);
   } else {

@@ -181,12 +181,47 @@ size_t tile_scan_row_scratch_doubles(int R, int Cc, int dtype, int batch);
 // launches the first stage and describes in *pending what is left of the second (valid = false: nothing)
 hipError_t launch_tile_scan(const TileScanJob& t, Stage2Job* pending, hipStream_t st);
 
-// The two gated re-encodings of the operand audit in one launch.  kind: 0 rowdot (s), 1 coldot (s),
-// 2 tile scan with one part on (t); index weights, same gate.  Every column reduction has to be able
-// to finish by itself (audit_pair_ok says whether); done: SCAN_DONE_WORDS zeroed counters.
+// kernel arguments of a tile scan
+struct TileScanArgs {
+  const void* X;
+  int dtype;
+  int R, Cc;
+  int64_t ld, xs;
+  int batch;
+  const double* wr;       // column part: row weights [2][R] per batch item (null: index weights)
+  int64_t wr_stride;
+  double* col_part;       // [batch][nchunk][2][Cc]
+  const double* wc;       // row part: column weights [2][Cc] per batch item (null: index weights)
+  int64_t wc_stride;
+  double* row_part;       // [batch][R][nseg][2]
+  int chunk_rows, nchunk, nseg;
+  const int32_t* gate;
+  int64_t gate_stride;
+  int gate_value;
+  // With done_col set, the last workgroup of a column segment adds the segment's chunks up; with
+  // done_row set, the last one of a chunk of rows adds the row partials of its rows: that part
+  // then has no second stage to launch.
+  uint32_t* done_col;     // [batch][nseg]
+  uint32_t* done_row;     // [batch][nchunk]
+  double* col_out; int64_t col_out_stride;
+  double* row_out; int64_t row_out_stride;
+};
+
+// The two gated re-encodings of the operand audit as jobs of the decoder's launch (launch_finish).  kind: 0
+// rowdot (s), 1 coldot (s), 2 tile scan with one part on (t); index weights, same gate.
 struct ScanPairItem { int kind; ScanArgs s; TileScanJob t; };
-bool audit_pair_ok(const ScanPairItem& x0, const ScanPairItem& x1);
-hipError_t launch_audit_pair(const ScanPairItem& x0, const ScanPairItem& x1, uint32_t* done, hipStream_t st);
+struct PairJob {
+  int kind;          // PJ_x
+  ScanArgs s;        // PJ_ROW, PJ_COL
+  TileScanArgs t;    // PJ_TILE_COL, PJ_TILE_ROW
+  int nblk;          // workgroups of this job
+  int gx, gy;        // workgroups per batch item: gx (rowdot) or gx x gy (segments x chunks)
+};
+enum : int { PJ_ROW = 0, PJ_COL = 1, PJ_TILE_COL = 2, PJ_TILE_ROW = 3, PJ_ROW_BIG = 4, PJ_ROW_WAVE = 5 };
+struct PairArgs { PairJob j[2]; };
+// done: SCAN_DONE_WORDS zeroed counters, of which `words` are used.  false: some column reduction cannot finish
+// by itself, or there are too few counters
+bool make_audit_pair(const ScanPairItem& x0, const ScanPairItem& x1, uint32_t* done, PairArgs& p, int& words);
 
 // ---- product (gemm_kernels.hip) ------------------------------------------------------------
 struct GemmArgs {
@@ -384,5 +419,7 @@ hipError_t launch_summarize(const DecodeArgs& a, hipStream_t st);
 hipError_t launch_decode_c(const DecodeArgs& a, int with_summary, hipStream_t st);
 // audit differences, operand patches, rank-one repair of C-bar and of the syndromes, Section V on the rest
 hipError_t launch_repair(const DecodeArgs& a, hipStream_t st);
+// launch_decode_c and both audits in one launch; share_done: p.batch zeroed counters
+hipError_t launch_finish(const DecodeArgs& a, const PairArgs& audits, uint32_t* share_done, int with_summary, hipStream_t st);
 
 }  // namespace gecc

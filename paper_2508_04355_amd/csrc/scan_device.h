@@ -491,5 +491,225 @@ __device__ __forceinline__ void coldot_body(const ScanArgs& a, int nchunk, int n
                                nchunk, bx * 64 * VEC, lds);
 }
 
+// -------------------------------------------------------------------------------------------
+// tile_scan: both reductions of an operand in ONE pass over it.
+//   column part  out_col[t][c] = sum_r wr_t[r] X[r,c]      (two-stage, like coldot)
+//   row part     out_row[t][r] = sum_c wc_t[c] X[r,c]      (two-stage: per 64*VEC-column segment)
+// Each part has either the index weights of Section III (1, index + 1) or two fp64 vectors.  With
+// both parts on, encoding an operand (A_P, index weights along one axis) and its parity block of
+// C-bar (P_r = A B_P, vector weights along the other) cost one read of the operand instead of two.
+// A part switched off costs nothing; a part computes the same sums in the same order whether the
+// other one is on or not, so the gated audit (one part) reproduces an encoding (maybe both) bit for
+// bit.  All products go through fma(), never a*b+c, for the same reason.
+//
+// A workgroup is four wavefronts on one segment of 64*VEC columns; each walks its own quarter of
+// the chunk's rows, TS_RB rows (loads) at a time; three wavefronts share a SIMD and cover each
+// other's waits.  The kernel is bound by its arithmetic as much as by memory: per 16 bytes a lane
+// spends 8 conversions and 32 fp64 operations, which issue at half rate, about 380 cycles per row
+// and wavefront (measured: its loads alone stream at 5.8 TB/s, the whole kernel at 4.4; more loads in
+// flight, 8-byte lanes, rows DMA'd into an LDS ring or workgroups that read 4 KiB of every row
+// change nothing).  A lane keeps the column sums of its VEC columns in registers for the whole walk.
+// The row sums of a block of rows (TS_RB rows x 2 kinds, one partial per lane) are transposed through
+// LDS and added by four lanes per output; only the wavefront's own LDS region is involved, so no
+// workgroup barrier sits in the loop.
+constexpr int TS_THREADS = 256;
+constexpr int TS_RB = 8;            // rows per block of loads
+constexpr int TS_LDS_LD = 65;       // doubles per output row of the transpose (64 lanes + 1: conflict-free)
+
+constexpr int TS_FLAG_AT = 1024;   // doubles into the LDS: behind what coldot_finish_segment uses
+
+constexpr int TS_LDS_DOUBLES = 4 * 2 * TS_RB * TS_LDS_LD;
+
+// segment `seg` of the columns, chunk `chunk` of the rows, batch item b; ts_lds: TS_LDS_DOUBLES of LDS
+template <int DT, bool COL, bool ROW, bool COL_IDX, bool ROW_IDX>
+__device__ __forceinline__ void tile_scan_body(const TileScanArgs& a, int seg, int chunk, int b, double* ts_lds) {
+  using E = Elem<DT>;
+  using T = typename E::type;
+  constexpr int VEC = E::VEC;
+  constexpr int SEG = 64 * VEC;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const T* X = reinterpret_cast<const T*>(a.X) + (int64_t)b * a.xs;
+  // columns of this lane (Cc is a multiple of VEC; lanes past the end read the last vector and drop it)
+  const int c_true = seg * SEG + lane * VEC;
+  const bool lane_ok = c_true < a.Cc;
+  const int c = lane_ok ? c_true : a.Cc - VEC;
+  const T* col = X + c;
+  // rows of this wavefront: a quarter of the chunk (multiple of TS_RB, so only the last has a tail)
+  const int rbeg = chunk * a.chunk_rows;
+  const int rend = min(a.R, rbeg + a.chunk_rows);
+  const int quarter = a.chunk_rows >> 2;
+  const int w_beg = min(rend, rbeg + wave * quarter), w_end = min(rend, w_beg + quarter);
+
+  const double* wr0 = (COL && !COL_IDX) ? a.wr + (int64_t)b * a.wr_stride : nullptr;
+  const double* wr1 = (COL && !COL_IDX) ? wr0 + a.R : nullptr;
+  double wc0[VEC], wc1[VEC];
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) {
+    if (ROW && !ROW_IDX) {
+      const double* w = a.wc + (int64_t)b * a.wc_stride;
+      wc0[e] = w[c + e]; wc1[e] = w[a.Cc + c + e];
+    } else {
+      wc0[e] = 1.0; wc1[e] = (double)(c + e + 1);
+    }
+  }
+  double ca0[VEC], ca1[VEC];
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) { ca0[e] = 0.0; ca1[e] = 0.0; }
+
+  double* tr = ts_lds + wave * (2 * TS_RB * TS_LDS_LD);     // this wavefront's transpose region
+  double* rp_out = ROW ? a.row_part + ((int64_t)b * a.R * a.nseg + seg) * 2 : nullptr;
+
+  // one row into the column sums; its two row partials go straight into the transpose region
+  auto take = [&](const typename E::raw& x, int u, double u0, double u1) {
+    double v[VEC];
+    E::widen(x, v);
+    if (COL) {
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        ca0[e] = COL_IDX ? ca0[e] + v[e] : fma(u0, v[e], ca0[e]);
+        ca1[e] = fma(u1, v[e], ca1[e]);
+        // (pins the update to this row: left alone, the compiler keeps the widened values of all
+        // the rows of a block alive and adds them up at the end, at the cost of half the occupancy)
+        asm volatile("" : "+v"(ca0[e]), "+v"(ca1[e]));
+      }
+    }
+    if (ROW) {
+      double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        s0 = ROW_IDX ? s0 + v[e] : fma(wc0[e], v[e], s0);
+        s1 = fma(wc1[e], v[e], s1);
+      }
+      tr[(2 * u) * TS_LDS_LD + lane] = lane_ok ? s0 : 0.0;
+      tr[(2 * u + 1) * TS_LDS_LD + lane] = lane_ok ? s1 : 0.0;
+    }
+  };
+  // row partials of `cnt` rows starting at r0: LDS -> four lanes per output add 16 lanes' values each
+  auto emit_rows = [&](int r0, int cnt) {
+    wave_lds_fence();
+    const int o = lane >> 2, q = lane & 3;      // output (row u = o / 2, kind t = o % 2), quarter of the lanes
+    // (all sixteen reads are issued before the first is used: one wait instead of eight)
+    double part[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) part[i] = tr[o * TS_LDS_LD + q * 16 + i];
+    __builtin_amdgcn_sched_barrier(0);
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s += part[i];
+    s += __shfl_xor(s, 1, 64);
+    s += __shfl_xor(s, 2, 64);
+    wave_lds_fence();
+    const int u = o >> 1, t = o & 1;
+    if (q == 0 && u < cnt) {
+      double* dst = rp_out + (int64_t)(r0 + u) * a.nseg * 2 + t;
+      if (a.done_row) store_dev(dst, s); else *dst = s;
+    }
+  };
+
+  int r = w_beg;
+  const int nfull = (w_end - w_beg) / TS_RB;
+  if (nfull > 0) {
+    typename E::raw xa[TS_RB];
+    auto load = [&](typename E::raw* x, int rr) {
+#pragma unroll
+      for (int u = 0; u < TS_RB; ++u) x[u] = E::load_raw(col + (int64_t)(rr + u) * a.ld);
+    };
+    auto work = [&](const typename E::raw* x, int rr) {
+      // the row weights of the whole block first (uniform loads: one wait, not one per row)
+      double u0[TS_RB], u1[TS_RB];
+#pragma unroll
+      for (int u = 0; u < TS_RB; ++u) {
+        u0[u] = (COL && !COL_IDX) ? wr0[rr + u] : 1.0;
+        u1[u] = (COL && !COL_IDX) ? wr1[rr + u] : (double)(rr + u + 1);
+      }
+#pragma unroll
+      for (int u = 0; u < TS_RB; ++u) {
+        take(x[u], u, u0[u], u1[u]);
+        __builtin_amdgcn_sched_barrier(0);   // one row at a time: widening all of them first costs the occupancy
+      }
+      if (ROW) emit_rows(rr, TS_RB);
+    };
+    for (int bi = 0; bi < nfull; ++bi) {
+      load(xa, r);
+      work(xa, r);
+      r += TS_RB;
+    }
+  }
+  if (r < w_end) {     // the last rows of the operand: fewer than TS_RB
+    const int cnt = w_end - r;
+    for (int u = 0; u < TS_RB; ++u) {
+      if (u < cnt) {
+        take(E::load_raw(col + (int64_t)(r + u) * a.ld), u, (COL && !COL_IDX) ? wr0[r + u] : 1.0,
+             (COL && !COL_IDX) ? wr1[r + u] : (double)(r + u + 1));
+      } else if (ROW) {
+        tr[(2 * u) * TS_LDS_LD + lane] = 0.0;
+        tr[(2 * u + 1) * TS_LDS_LD + lane] = 0.0;
+      }
+    }
+    if (ROW) emit_rows(r, cnt);
+  }
+
+  if (COL) {
+    // the four quarters of the chunk, combined in order
+    __syncthreads();
+    double* cb = ts_lds;                          // [4][2 * VEC][64]
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+      cb[(wave * 2 * VEC + e) * 64 + lane] = ca0[e];
+      cb[(wave * 2 * VEC + VEC + e) * 64 + lane] = ca1[e];
+    }
+    __syncthreads();
+    double* part = a.col_part + ((int64_t)b * a.nchunk + chunk) * 2 * a.Cc;
+    for (int o = threadIdx.x; o < 2 * VEC * 64; o += TS_THREADS) {
+      const int l = o & 63, e = (o >> 6) % VEC, t = o / (64 * VEC);
+      const int cc = seg * SEG + l * VEC + e;
+      if (cc < a.Cc) {
+        const int x = (t * VEC + e) * 64 + l;
+        const double v = (cb[x] + cb[2 * VEC * 64 + x]) + (cb[2 * 2 * VEC * 64 + x] + cb[3 * 2 * VEC * 64 + x]);
+        if (a.done_col) store_dev(part + (int64_t)t * a.Cc + cc, v);
+        else part[(int64_t)t * a.Cc + cc] = v;
+      }
+    }
+  }
+
+  if ((COL && a.done_col) || (ROW && a.done_row)) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's partial results have been written through
+    __syncthreads();
+    int* flag = reinterpret_cast<int*>(ts_lds + TS_FLAG_AT);
+    if (threadIdx.x == 0) {
+      flag[0] = (COL && a.done_col) ? atomicInc(a.done_col + (int64_t)b * a.nseg + seg, (uint32_t)a.nchunk - 1) == (uint32_t)a.nchunk - 1 : 0;
+      flag[1] = (ROW && a.done_row) ? atomicInc(a.done_row + (int64_t)b * a.nchunk + chunk, (uint32_t)a.nseg - 1) == (uint32_t)a.nseg - 1 : 0;
+    }
+    __syncthreads();
+    const bool last_col = flag[0] != 0, last_row = flag[1] != 0;
+    if (ROW && last_row) {
+      const double* part = a.row_part + (int64_t)b * a.R * a.nseg * 2;
+      double* out = a.row_out + (int64_t)b * a.row_out_stride;
+      for (int rr = rbeg + (int)threadIdx.x; rr < rend; rr += TS_THREADS) rowseg_sum<true>(part, out, a.R, a.nseg, rr);
+    }
+    if (COL && last_col)
+      coldot_finish_segment<VEC>(a.col_part + (int64_t)b * a.nchunk * 2 * a.Cc, a.col_out + (int64_t)b * a.col_out_stride,
+                                 a.Cc, a.nchunk, seg * SEG, ts_lds);
+  }
+}
+
+// -------------------------------------------------------------------------------------------
+// The two gated re-encodings of the operand audit, as jobs of one launch (the decoder's, see
+// decode_kernels.hip): every column reduction in here is finished by the workgroup that comes last to its
+// segment (done / done_col / done_row set).
+constexpr int PAIR_LDS_DOUBLES = TS_LDS_DOUBLES > CD_LDS_DOUBLES ? TS_LDS_DOUBLES : CD_LDS_DOUBLES;
+
+// workgroup (x, y) of batch item b
+template <int DT>
+__device__ __forceinline__ void pair_body(const PairJob& j, int x, int y, int b, double* lds) {
+  if (j.kind == PJ_ROW) rowdot_body<DT, true, RD_SMALL_RB, RD_SMALL_U>(j.s, x, b, lds);
+  else if (j.kind == PJ_ROW_BIG) rowdot_body<DT, true, RD_BIG_RB, RD_BIG_U>(j.s, x, b, lds);
+  else if (j.kind == PJ_ROW_WAVE) rowdot_wave_body<DT, true>(j.s, x, b, lds);
+  else if (j.kind == PJ_COL) coldot_body<DT, true, CD_ROWS>(j.s, j.gy, j.gx, x, y, b, lds);
+  else if (j.kind == PJ_TILE_COL) tile_scan_body<DT, true, false, true, true>(j.t, x, y, b, lds);
+  else tile_scan_body<DT, false, true, true, true>(j.t, x, y, b, lds);
+}
+
 }  // namespace
 }  // namespace gecc

@@ -52,286 +52,12 @@ __global__ __launch_bounds__(256) void coldot_stage2(Stage2Job j) {
   stage2_dispatch(j, b, blockIdx.x, lds);
 }
 
-// -------------------------------------------------------------------------------------------
-// tile_scan: both reductions of an operand in ONE pass over it.
-//   column part  out_col[t][c] = sum_r wr_t[r] X[r,c]      (two-stage, like coldot)
-//   row part     out_row[t][r] = sum_c wc_t[c] X[r,c]      (two-stage: per 64*VEC-column segment)
-// Each part has either the index weights of Section III (1, index + 1) or two fp64 vectors.  With
-// both parts on, encoding an operand (A_P, index weights along one axis) and its parity block of
-// C-bar (P_r = A B_P, vector weights along the other) cost one read of the operand instead of two.
-// A part switched off costs nothing; a part computes the same sums in the same order whether the
-// other one is on or not, so the gated audit (one part) reproduces an encoding (maybe both) bit for
-// bit.  All products go through fma(), never a*b+c, for the same reason.
-//
-// A workgroup is four wavefronts on one segment of 64*VEC columns; each walks its own quarter of
-// the chunk's rows, TS_RB rows (loads) at a time; three wavefronts share a SIMD and cover each
-// other's waits.  The kernel is bound by its arithmetic as much as by memory: per 16 bytes a lane
-// spends 8 conversions and 32 fp64 operations, which issue at half rate, about 380 cycles per row
-// and wavefront (measured: its loads alone stream at 5.8 TB/s, the whole kernel at 4.4; more loads in
-// flight, 8-byte lanes, rows DMA'd into an LDS ring or workgroups that read 4 KiB of every row
-// change nothing).  A lane keeps the column sums of its VEC columns in registers for the whole walk.
-// The row sums of a block of rows (TS_RB rows x 2 kinds, one partial per lane) are transposed through
-// LDS and added by four lanes per output; only the wavefront's own LDS region is involved, so no
-// workgroup barrier sits in the loop.
-constexpr int TS_THREADS = 256;
-constexpr int TS_RB = 8;            // rows per block of loads
-constexpr int TS_LDS_LD = 65;       // doubles per output row of the transpose (64 lanes + 1: conflict-free)
-
-struct TileScanArgs {
-  const void* X;
-  int dtype;
-  int R, Cc;
-  int64_t ld, xs;
-  int batch;
-  const double* wr;       // column part: row weights [2][R] per batch item (null: index weights)
-  int64_t wr_stride;
-  double* col_part;       // [batch][nchunk][2][Cc]
-  const double* wc;       // row part: column weights [2][Cc] per batch item (null: index weights)
-  int64_t wc_stride;
-  double* row_part;       // [batch][R][nseg][2]
-  int chunk_rows, nchunk, nseg;
-  const int32_t* gate;
-  int64_t gate_stride;
-  int gate_value;
-  // With done_col set, the last workgroup of a column segment adds the segment's chunks up; with
-  // done_row set, the last one of a chunk of rows adds the row partials of its rows: that part
-  // then has no second stage to launch.
-  uint32_t* done_col;     // [batch][nseg]
-  uint32_t* done_row;     // [batch][nchunk]
-  double* col_out; int64_t col_out_stride;
-  double* row_out; int64_t row_out_stride;
-};
-constexpr int TS_FLAG_AT = 1024;   // doubles into the LDS: behind what coldot_finish_segment uses
-
-constexpr int TS_LDS_DOUBLES = 4 * 2 * TS_RB * TS_LDS_LD;
-
-// segment `seg` of the columns, chunk `chunk` of the rows, batch item b; ts_lds: TS_LDS_DOUBLES of LDS
-template <int DT, bool COL, bool ROW, bool COL_IDX, bool ROW_IDX>
-__device__ __forceinline__ void tile_scan_body(const TileScanArgs& a, int seg, int chunk, int b, double* ts_lds) {
-  using E = Elem<DT>;
-  using T = typename E::type;
-  constexpr int VEC = E::VEC;
-  constexpr int SEG = 64 * VEC;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const T* X = reinterpret_cast<const T*>(a.X) + (int64_t)b * a.xs;
-  // columns of this lane (Cc is a multiple of VEC; lanes past the end read the last vector and drop it)
-  const int c_true = seg * SEG + lane * VEC;
-  const bool lane_ok = c_true < a.Cc;
-  const int c = lane_ok ? c_true : a.Cc - VEC;
-  const T* col = X + c;
-  // rows of this wavefront: a quarter of the chunk (multiple of TS_RB, so only the last has a tail)
-  const int rbeg = chunk * a.chunk_rows;
-  const int rend = min(a.R, rbeg + a.chunk_rows);
-  const int quarter = a.chunk_rows >> 2;
-  const int w_beg = min(rend, rbeg + wave * quarter), w_end = min(rend, w_beg + quarter);
-
-  const double* wr0 = (COL && !COL_IDX) ? a.wr + (int64_t)b * a.wr_stride : nullptr;
-  const double* wr1 = (COL && !COL_IDX) ? wr0 + a.R : nullptr;
-  double wc0[VEC], wc1[VEC];
-#pragma unroll
-  for (int e = 0; e < VEC; ++e) {
-    if (ROW && !ROW_IDX) {
-      const double* w = a.wc + (int64_t)b * a.wc_stride;
-      wc0[e] = w[c + e]; wc1[e] = w[a.Cc + c + e];
-    } else {
-      wc0[e] = 1.0; wc1[e] = (double)(c + e + 1);
-    }
-  }
-  double ca0[VEC], ca1[VEC];
-#pragma unroll
-  for (int e = 0; e < VEC; ++e) { ca0[e] = 0.0; ca1[e] = 0.0; }
-
-  double* tr = ts_lds + wave * (2 * TS_RB * TS_LDS_LD);     // this wavefront's transpose region
-  double* rp_out = ROW ? a.row_part + ((int64_t)b * a.R * a.nseg + seg) * 2 : nullptr;
-
-  // one row into the column sums; its two row partials go straight into the transpose region
-  auto take = [&](const typename E::raw& x, int u, double u0, double u1) {
-    double v[VEC];
-    E::widen(x, v);
-    if (COL) {
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) {
-        ca0[e] = COL_IDX ? ca0[e] + v[e] : fma(u0, v[e], ca0[e]);
-        ca1[e] = fma(u1, v[e], ca1[e]);
-        // (pins the update to this row: left alone, the compiler keeps the widened values of all
-        // the rows of a block alive and adds them up at the end, at the cost of half the occupancy)
-        asm volatile("" : "+v"(ca0[e]), "+v"(ca1[e]));
-      }
-    }
-    if (ROW) {
-      double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) {
-        s0 = ROW_IDX ? s0 + v[e] : fma(wc0[e], v[e], s0);
-        s1 = fma(wc1[e], v[e], s1);
-      }
-      tr[(2 * u) * TS_LDS_LD + lane] = lane_ok ? s0 : 0.0;
-      tr[(2 * u + 1) * TS_LDS_LD + lane] = lane_ok ? s1 : 0.0;
-    }
-  };
-  // row partials of `cnt` rows starting at r0: LDS -> four lanes per output add 16 lanes' values each
-  auto emit_rows = [&](int r0, int cnt) {
-    wave_lds_fence();
-    const int o = lane >> 2, q = lane & 3;      // output (row u = o / 2, kind t = o % 2), quarter of the lanes
-    // (all sixteen reads are issued before the first is used: one wait instead of eight)
-    double part[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) part[i] = tr[o * TS_LDS_LD + q * 16 + i];
-    __builtin_amdgcn_sched_barrier(0);
-    double s = 0.0;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) s += part[i];
-    s += __shfl_xor(s, 1, 64);
-    s += __shfl_xor(s, 2, 64);
-    wave_lds_fence();
-    const int u = o >> 1, t = o & 1;
-    if (q == 0 && u < cnt) {
-      double* dst = rp_out + (int64_t)(r0 + u) * a.nseg * 2 + t;
-      if (a.done_row) store_dev(dst, s); else *dst = s;
-    }
-  };
-
-  int r = w_beg;
-  const int nfull = (w_end - w_beg) / TS_RB;
-  if (nfull > 0) {
-    typename E::raw xa[TS_RB];
-    auto load = [&](typename E::raw* x, int rr) {
-#pragma unroll
-      for (int u = 0; u < TS_RB; ++u) x[u] = E::load_raw(col + (int64_t)(rr + u) * a.ld);
-    };
-    auto work = [&](const typename E::raw* x, int rr) {
-      // the row weights of the whole block first (uniform loads: one wait, not one per row)
-      double u0[TS_RB], u1[TS_RB];
-#pragma unroll
-      for (int u = 0; u < TS_RB; ++u) {
-        u0[u] = (COL && !COL_IDX) ? wr0[rr + u] : 1.0;
-        u1[u] = (COL && !COL_IDX) ? wr1[rr + u] : (double)(rr + u + 1);
-      }
-#pragma unroll
-      for (int u = 0; u < TS_RB; ++u) {
-        take(x[u], u, u0[u], u1[u]);
-        __builtin_amdgcn_sched_barrier(0);   // one row at a time: widening all of them first costs the occupancy
-      }
-      if (ROW) emit_rows(rr, TS_RB);
-    };
-    for (int bi = 0; bi < nfull; ++bi) {
-      load(xa, r);
-      work(xa, r);
-      r += TS_RB;
-    }
-  }
-  if (r < w_end) {     // the last rows of the operand: fewer than TS_RB
-    const int cnt = w_end - r;
-    for (int u = 0; u < TS_RB; ++u) {
-      if (u < cnt) {
-        take(E::load_raw(col + (int64_t)(r + u) * a.ld), u, (COL && !COL_IDX) ? wr0[r + u] : 1.0,
-             (COL && !COL_IDX) ? wr1[r + u] : (double)(r + u + 1));
-      } else if (ROW) {
-        tr[(2 * u) * TS_LDS_LD + lane] = 0.0;
-        tr[(2 * u + 1) * TS_LDS_LD + lane] = 0.0;
-      }
-    }
-    if (ROW) emit_rows(r, cnt);
-  }
-
-  if (COL) {
-    // the four quarters of the chunk, combined in order
-    __syncthreads();
-    double* cb = ts_lds;                          // [4][2 * VEC][64]
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-      cb[(wave * 2 * VEC + e) * 64 + lane] = ca0[e];
-      cb[(wave * 2 * VEC + VEC + e) * 64 + lane] = ca1[e];
-    }
-    __syncthreads();
-    double* part = a.col_part + ((int64_t)b * a.nchunk + chunk) * 2 * a.Cc;
-    for (int o = threadIdx.x; o < 2 * VEC * 64; o += TS_THREADS) {
-      const int l = o & 63, e = (o >> 6) % VEC, t = o / (64 * VEC);
-      const int cc = seg * SEG + l * VEC + e;
-      if (cc < a.Cc) {
-        const int x = (t * VEC + e) * 64 + l;
-        const double v = (cb[x] + cb[2 * VEC * 64 + x]) + (cb[2 * 2 * VEC * 64 + x] + cb[3 * 2 * VEC * 64 + x]);
-        if (a.done_col) store_dev(part + (int64_t)t * a.Cc + cc, v);
-        else part[(int64_t)t * a.Cc + cc] = v;
-      }
-    }
-  }
-
-  if ((COL && a.done_col) || (ROW && a.done_row)) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's partial results have been written through
-    __syncthreads();
-    int* flag = reinterpret_cast<int*>(ts_lds + TS_FLAG_AT);
-    if (threadIdx.x == 0) {
-      flag[0] = (COL && a.done_col) ? atomicInc(a.done_col + (int64_t)b * a.nseg + seg, (uint32_t)a.nchunk - 1) == (uint32_t)a.nchunk - 1 : 0;
-      flag[1] = (ROW && a.done_row) ? atomicInc(a.done_row + (int64_t)b * a.nchunk + chunk, (uint32_t)a.nseg - 1) == (uint32_t)a.nseg - 1 : 0;
-    }
-    __syncthreads();
-    const bool last_col = flag[0] != 0, last_row = flag[1] != 0;
-    if (ROW && last_row) {
-      const double* part = a.row_part + (int64_t)b * a.R * a.nseg * 2;
-      double* out = a.row_out + (int64_t)b * a.row_out_stride;
-      for (int rr = rbeg + (int)threadIdx.x; rr < rend; rr += TS_THREADS) rowseg_sum<true>(part, out, a.R, a.nseg, rr);
-    }
-    if (COL && last_col)
-      coldot_finish_segment<VEC>(a.col_part + (int64_t)b * a.nchunk * 2 * a.Cc, a.col_out + (int64_t)b * a.col_out_stride,
-                                 a.Cc, a.nchunk, seg * SEG, ts_lds);
-  }
-}
-
 template <int DT, bool COL, bool ROW, bool COL_IDX, bool ROW_IDX, bool GATED>
 __global__ __launch_bounds__(TS_THREADS) void tile_scan(TileScanArgs a) {
   extern __shared__ double ts_lds[];
   const int b = blockIdx.z;
   if (GATED && gated_off(a.gate, a.gate_stride, b, a.gate_value)) return;
   tile_scan_body<DT, COL, ROW, COL_IDX, ROW_IDX>(a, blockIdx.x, blockIdx.y, b, ts_lds);
-}
-
-// -------------------------------------------------------------------------------------------
-// The two gated re-encodings of the operand audit in one launch: on a clean step each of them only
-// finds its gate closed, and a dependent launch costs about 5 us of stream time whatever it does.
-// When the audit does run, every column reduction in here is finished by the workgroup that comes
-// last to its segment (a.done / done_col / done_row set): that tail costs about what the launch of a
-// second stage would, so it is used here only, where it saves a launch on every clean step.
-struct PairJob {
-  int kind;          // PJ_x
-  ScanArgs s;        // PJ_ROW, PJ_COL
-  TileScanArgs t;    // PJ_TILE_COL, PJ_TILE_ROW
-  int nblk;          // workgroups of this job
-  int gx, gy;        // workgroups per batch item: gx (rowdot) or gx x gy (segments x chunks)
-};
-enum : int { PJ_ROW = 0, PJ_COL = 1, PJ_TILE_COL = 2, PJ_TILE_ROW = 3, PJ_ROW_BIG = 4, PJ_ROW_WAVE = 5 };
-struct PairArgs { PairJob j[2]; };
-constexpr int AUDIT_PAIR_MAX_BLOCKS = 5120;
-constexpr int PAIR_LDS_DOUBLES = TS_LDS_DOUBLES > CD_LDS_DOUBLES ? TS_LDS_DOUBLES : CD_LDS_DOUBLES;
-
-// (three workgroups per compute unit: a grid whose gates are closed lasts as long as its dispatch)
-template <int DT>
-__global__ __launch_bounds__(256, 3) void audit_pair(PairArgs p) {
-  __shared__ double lds[PAIR_LDS_DOUBLES];
-  int v = blockIdx.x;
-  const bool second = v >= p.j[0].nblk;
-  if (second) v -= p.j[0].nblk;
-  const PairJob& j = second ? p.j[1] : p.j[0];
-  const int per_item = j.gx * j.gy;
-  const int b = v / per_item, x = (v % per_item) % j.gx, y = (v % per_item) / j.gx;
-  if (j.kind == PJ_ROW) {
-    if (gated_off(j.s.gate, j.s.gate_stride, b, j.s.gate_value)) return;
-    rowdot_body<DT, true, RD_SMALL_RB, RD_SMALL_U>(j.s, x, b, lds);
-  } else if (j.kind == PJ_ROW_BIG) {
-    if (gated_off(j.s.gate, j.s.gate_stride, b, j.s.gate_value)) return;
-    rowdot_body<DT, true, RD_BIG_RB, RD_BIG_U>(j.s, x, b, lds);
-  } else if (j.kind == PJ_ROW_WAVE) {
-    if (gated_off(j.s.gate, j.s.gate_stride, b, j.s.gate_value)) return;
-    rowdot_wave_body<DT, true>(j.s, x, b, lds);
-  } else if (j.kind == PJ_COL) {
-    if (gated_off(j.s.gate, j.s.gate_stride, b, j.s.gate_value)) return;
-    coldot_body<DT, true, CD_ROWS>(j.s, j.gy, j.gx, x, y, b, lds);
-  } else {
-    if (gated_off(j.t.gate, j.t.gate_stride, b, j.t.gate_value)) return;
-    if (j.kind == PJ_TILE_COL) tile_scan_body<DT, true, false, true, true>(j.t, x, y, b, lds);
-    else tile_scan_body<DT, false, true, true, true>(j.t, x, y, b, lds);
-  }
 }
 
 // A wavefront per RW_RB rows where that alone fills the chip (two workgroups per compute unit) and the rows
@@ -557,7 +283,8 @@ bool make_side_job(const ScanArgs& s, bool rowdot, uint32_t* done, int words_lef
   return true;
 }
 
-// ---- the two audits in one launch ---------------------------------------------------------------
+// ---- the two audits as jobs of the decoder's launch -----------------------------------------------
+constexpr int AUDIT_PAIR_MAX_BLOCKS = 5120;
 // fills j from x; returns the counters it uses, or -1 when x cannot finish by itself
 static int make_pair_job(const ScanPairItem& x, uint32_t* done, PairJob& j) {
   j = PairJob{};
@@ -571,6 +298,7 @@ static int make_pair_job(const ScanPairItem& x, uint32_t* done, PairJob& j) {
     if (!make_tile_args(t, j.t, fc, fr, words) || !(t.col_on ? fc : fr)) return -1;
     j.kind = t.col_on ? PJ_TILE_COL : PJ_TILE_ROW;
     j.gx = j.t.nseg; j.gy = j.t.nchunk;
+    if ((int64_t)j.gx * j.gy * t.batch > (1 << 29)) return -1;
     j.nblk = j.gx * j.gy * t.batch;
     return words;
   }
@@ -584,6 +312,7 @@ static int make_pair_job(const ScanPairItem& x, uint32_t* done, PairJob& j) {
     const int rb = wavewise ? 4 * RW_RB : small ? RD_SMALL_RB : RD_BIG_RB;
     j.kind = wavewise ? PJ_ROW_WAVE : small ? PJ_ROW : PJ_ROW_BIG;
     j.gx = (j.s.R + rb - 1) / rb; j.gy = 1;
+    if ((int64_t)j.gx * j.s.batch > (1 << 29)) return -1;
     j.nblk = j.gx * j.s.batch;
     return 0;
   }
@@ -594,33 +323,22 @@ static int make_pair_job(const ScanPairItem& x, uint32_t* done, PairJob& j) {
   j.s.done = done;
   j.gx = (j.s.Cc + 64 * vec - 1) / (64 * vec);
   j.gy = (j.s.R + SCAN_CHUNK_ROWS - 1) / SCAN_CHUNK_ROWS;
+  if ((int64_t)j.gx * j.gy * j.s.batch > (1 << 29)) return -1;
   j.nblk = j.gx * j.gy * j.s.batch;
   return words;
 }
 
 static int pair_dtype(const ScanPairItem& x) { return x.kind == 2 ? x.t.dtype : x.s.dtype; }
 
-bool audit_pair_ok(const ScanPairItem& x0, const ScanPairItem& x1) {
-  static uint32_t dummy;   // (an address that is never used: only the counts matter here)
-  PairJob j;
-  const int w0 = make_pair_job(x0, &dummy, j);
-  if (w0 < 0) return false;
-  const int nblk0 = j.nblk;
-  const int w1 = make_pair_job(x1, &dummy, j);
-  // (a closed gate still costs the dispatch of every workgroup: about 2 us per thousand, so a pair of
-  // very large grids is no cheaper than two launches)
-  return w1 >= 0 && w0 + w1 <= SCAN_DONE_WORDS && pair_dtype(x0) == pair_dtype(x1) && nblk0 + j.nblk <= AUDIT_PAIR_MAX_BLOCKS;
-}
-
-hipError_t launch_audit_pair(const ScanPairItem& x0, const ScanPairItem& x1, uint32_t* done, hipStream_t st) {
-  if (!done || !audit_pair_ok(x0, x1)) return hipErrorInvalidValue;
-  PairArgs p;
+bool make_audit_pair(const ScanPairItem& x0, const ScanPairItem& x1, uint32_t* done, PairArgs& p, int& words) {
+  if (pair_dtype(x0) != pair_dtype(x1)) return false;
   const int w0 = make_pair_job(x0, done, p.j[0]);
-  make_pair_job(x1, done + w0, p.j[1]);
-  const dim3 grid(p.j[0].nblk + p.j[1].nblk);
-  if (pair_dtype(x0) == GECC_BF16) hipLaunchKernelGGL(audit_pair<GECC_BF16>, grid, dim3(256), 0, st, p);
-  else                             hipLaunchKernelGGL(audit_pair<GECC_F32>, grid, dim3(256), 0, st, p);
-  return hipGetLastError();
+  if (w0 < 0) return false;
+  const int w1 = make_pair_job(x1, done + w0, p.j[1]);
+  words = w0 + w1;
+  // (a closed gate still costs the dispatch of every workgroup, about 2 us per thousand: a pair of very large
+  // grids is no cheaper than launches of their own)
+  return w1 >= 0 && words <= SCAN_DONE_WORDS && p.j[0].nblk + p.j[1].nblk <= AUDIT_PAIR_MAX_BLOCKS;
 }
 
 namespace {
