@@ -70,8 +70,11 @@ __global__ void reset_state_kernel(DecodeArgs a) {
 
 // partial sums -> syndromes (sum - parity, Section V step 1) -> flags
 constexpr int TH_SLICES = 4;    // wavefronts of a workgroup; each adds every 4th sub-tile of a line
-constexpr int TH_MAXLOADS = 32; // loads a thread keeps in flight
 
+// TH_MAXLOADS: loads a thread keeps in flight, chosen by the launcher to fit the number of sub-tiles along a line
+// (more than there are would only read the last one again: 256 x 512^3, four sub-tiles, 26 us with 32 of
+// them, 9 with 4).  The sums do not depend on it.
+template <int TH_MAXLOADS>
 __global__ __launch_bounds__(64 * TH_SLICES) void threshold_kernel(DecodeArgs a) {
   const int b = blockIdx.y;
   DecodeState* st = state_of(a, b);
@@ -1065,19 +1068,21 @@ __global__ __launch_bounds__(256) void threshold_blocked_kernel(DecodeArgs a, in
 
 // Blocked mode: the parity blocks of every block of C-bar from the two side products (A times the
 // parity columns of all column blocks, the parity rows of all row blocks times B), P_g in fp64,
-// and the per-block resets.  One workgroup per block.
-__global__ __launch_bounds__(256) void blocked_parities_kernel(BlockedParityArgs a) {
+// and the per-block resets.  One workgroup per block; short chains of loads are all it does, so a full
+// workgroup (224 blocks of 1024 x 1024, k = 4096: 25 us with 256 threads).
+constexpr int BP_THREADS = 1024;
+__global__ __launch_bounds__(BP_THREADS) void blocked_parities_kernel(BlockedParityArgs a) {
   const int b = blockIdx.x, I = b / a.nbj, J = b % a.nbj;
   const int nb = a.nb, mb = a.mb, S = a.pieces;
   double* cpar = a.C_par + (int64_t)b * (2 * nb + 2 * mb + 4);
-  for (int il = threadIdx.x; il < nb; il += blockDim.x) {      // 2 S consecutive floats of a row of the side product
+  for (int il = threadIdx.x; il < nb; il += BP_THREADS) {      // 2 S consecutive floats of a row of the side product
     const float* p = a.side_r + (int64_t)(I * nb + il) * a.ld_r + J * 2 * S;
     double v0 = 0.0, v1 = 0.0;
     for (int s = 0; s < S; ++s) { v0 += (double)p[s]; v1 += (double)p[S + s]; }
     cpar[il] = v0;
     cpar[nb + il] = v1;
   }
-  for (int o = threadIdx.x; o < 2 * mb; o += blockDim.x) {
+  for (int o = threadIdx.x; o < 2 * mb; o += BP_THREADS) {
     const int t = o / mb, jl = o % mb;
     const float* p = a.side_c + (int64_t)((I * 2 + t) * S) * a.ld_c + J * mb + jl;
     double v = 0.0;
@@ -1087,12 +1092,13 @@ __global__ __launch_bounds__(256) void blocked_parities_kernel(BlockedParityArgs
   const double* ap = a.A_par + (int64_t)I * 2 * a.k;
   const double* bp = a.B_par + (int64_t)J * 2 * a.k;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int l = threadIdx.x; l < a.k; l += blockDim.x) {
+#pragma unroll 4
+  for (int l = threadIdx.x; l < a.k; l += BP_THREADS) {
     const double a0 = ap[l], a1 = ap[a.k + l], b0 = bp[l], b1 = bp[a.k + l];
     acc[0] = fma(a0, b0, acc[0]); acc[1] = fma(a0, b1, acc[1]);
     acc[2] = fma(a1, b0, acc[2]); acc[3] = fma(a1, b1, acc[3]);
   }
-  __shared__ double red[4][4];
+  __shared__ double red[BP_THREADS / 64][4];
 #pragma unroll
   for (int q = 0; q < 4; ++q)
 #pragma unroll
@@ -1101,7 +1107,11 @@ __global__ __launch_bounds__(256) void blocked_parities_kernel(BlockedParityArgs
 #pragma unroll
     for (int q = 0; q < 4; ++q) red[threadIdx.x >> 6][q] = acc[q];
   __syncthreads();
-  if (threadIdx.x < 4) cpar[2 * nb + 2 * mb + threadIdx.x] = (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
+  if (threadIdx.x < 4) {
+    double v = red[0][threadIdx.x];
+    for (int w = 1; w < BP_THREADS / 64; ++w) v += red[w][threadIdx.x];
+    cpar[2 * nb + 2 * mb + threadIdx.x] = v;
+  }
   if (threadIdx.x == 0) {
     reset_state(a.state + b);
     for (int f = 0; f < 4; ++f) a.itemmax[(int64_t)b * 4 + f] = 0.0;
@@ -1142,7 +1152,10 @@ hipError_t launch_reset_state(const DecodeArgs& a, hipStream_t st) {
 
 hipError_t launch_threshold(const DecodeArgs& a, hipStream_t st) {
   dim3 grid((a.p.n + a.p.m + 63) / 64, a.p.batch);   // 64 lines per workgroup: spreads over all CUs
-  hipLaunchKernelGGL(threshold_kernel, grid, dim3(64 * TH_SLICES), 0, st, a);
+  const int nt = a.ntm > a.ntn ? a.ntm : a.ntn;
+  if (nt <= 4 * TH_SLICES)      hipLaunchKernelGGL(threshold_kernel<4>, grid, dim3(64 * TH_SLICES), 0, st, a);
+  else if (nt <= 8 * TH_SLICES) hipLaunchKernelGGL(threshold_kernel<8>, grid, dim3(64 * TH_SLICES), 0, st, a);
+  else                          hipLaunchKernelGGL(threshold_kernel<32>, grid, dim3(64 * TH_SLICES), 0, st, a);
   return hipGetLastError();
 }
 
@@ -1186,7 +1199,7 @@ hipError_t launch_threshold_blocked(const DecodeArgs& a, int n_full, int m_full,
 }
 
 hipError_t launch_blocked_parities(const BlockedParityArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(blocked_parities_kernel, dim3(a.nbi * a.nbj), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(blocked_parities_kernel, dim3(a.nbi * a.nbj), dim3(BP_THREADS), 0, st, a);
   return hipGetLastError();
 }
 
