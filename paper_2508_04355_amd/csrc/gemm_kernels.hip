@@ -620,12 +620,13 @@ __global__ __launch_bounds__(THREADS) void partials_kernel(PartialArgs a) {
   __shared__ float red_col[2][RG][TILE];
   float cs[4] = {0.f, 0.f, 0.f, 0.f}, cw[4] = {0.f, 0.f, 0.f, 0.f};
   // the kernel is a stream over C: all loads of a thread are issued before the first is used
-  // (rows past the end are clamped, not branched on, and count as zero below)
-  float4 pre[RPT];
+  // (rows past the end are clamped, not branched on, and count as zero below), and nothing it reads is kept
+  // in the caches (940 MB: 156 us = 6.0 TB/s, with ordinary loads 175)
+  f32x4_t pre[RPT];
   if (vec) {
 #pragma unroll
     for (int r = 0; r < RPT; ++r)
-      pre[r] = *reinterpret_cast<const float4*>(C + (int64_t)min(tile_r0 + rg * RPT + r, a.n - 1) * a.ldc + gj);
+      pre[r] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(C + (int64_t)min(tile_r0 + rg * RPT + r, a.n - 1) * a.ldc + gj));
   }
 #pragma unroll
   for (int r = 0; r < RPT; ++r) {
