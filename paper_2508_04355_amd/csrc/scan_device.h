@@ -7,6 +7,8 @@
 namespace gecc {
 namespace {
 
+typedef __attribute__((ext_vector_type(4))) uint32_t stream_t;
+
 template <int DT> struct Elem;
 template <> struct Elem<GECC_F32> {
   using type = float;
@@ -14,6 +16,10 @@ template <> struct Elem<GECC_F32> {
   using raw = float4;
   // (memcpy: rows may start at any element; the hardware takes a 16-byte load at any address)
   static __device__ __forceinline__ raw load_raw(const float* p) { raw x; __builtin_memcpy(&x, p, 16); return x; }
+  // (16-byte aligned; marked as not to be kept in the caches)
+  static __device__ __forceinline__ raw load_stream(const float* p) {
+    return __builtin_bit_cast(raw, __builtin_nontemporal_load(reinterpret_cast<const stream_t*>(p)));
+  }
   static __device__ __forceinline__ void widen(const raw& x, double* v) {
     v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
   }
@@ -25,6 +31,9 @@ template <> struct Elem<GECC_BF16> {
   static constexpr int VEC = 8;
   using raw = uint4;
   static __device__ __forceinline__ raw load_raw(const uint16_t* p) { raw x; __builtin_memcpy(&x, p, 16); return x; }
+  static __device__ __forceinline__ raw load_stream(const uint16_t* p) {
+    return __builtin_bit_cast(raw, __builtin_nontemporal_load(reinterpret_cast<const stream_t*>(p)));
+  }
   static __device__ __forceinline__ void widen(const raw& x, double* v) {
     uint32_t w[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
@@ -613,7 +622,7 @@ __device__ __forceinline__ void tile_scan_body(const TileScanArgs& a, int seg, i
     typename E::raw xa[TS_RB];
     auto load = [&](typename E::raw* x, int rr) {
 #pragma unroll
-      for (int u = 0; u < TS_RB; ++u) x[u] = E::load_raw(col + (int64_t)(rr + u) * a.ld);
+      for (int u = 0; u < TS_RB; ++u) x[u] = E::load_stream(col + (int64_t)(rr + u) * a.ld);
     };
     auto work = [&](const typename E::raw* x, int rr) {
       // the row weights of the whole block first (uniform loads: one wait, not one per row)
