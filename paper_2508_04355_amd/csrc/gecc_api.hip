@@ -614,8 +614,8 @@ int check_multiply_args(gecc_ctx* ctx, const void* dev_A, const double* dev_A_pa
 }
 
 // S3: the parity blocks pr, pc of C-bar (null: formed already), the data block, the fused syndrome partial
-// sums, P_g.  The scans of the parity blocks ride in the product's launch where that is gemm_tile's;
-// otherwise they go first, on q.
+// sums, P_g.  The scans of the parity blocks ride in the product's launch where that is a small one of
+// gemm_tile; otherwise they go first, on q.
 hipError_t product(gecc_ctx* ctx, ScanQueue& q, const ScanJob* pr, const ScanJob* pc, const void* dev_A, const double* dev_A_par,
                    const void* dev_B, const double* dev_B_par, float* dev_C, double* dev_C_par, const gecc_fault* dev_faults,
                    int32_t n_faults, hipStream_t st) {
@@ -633,7 +633,12 @@ hipError_t product(gecc_ctx* ctx, ScanQueue& q, const ScanJob* pr, const ScanJob
   g.pg_stride = 2 * (int64_t)p.n + 2 * (int64_t)p.m + 4;
   g.state = reinterpret_cast<DecodeState*>(ctx->ws + ctx->lay.state);
   hipError_t e;
-  if (gemm_takes_256(g)) {
+  // Whether they ride is a matter of size: up to about four rounds of workgroups the two launches saved count
+  // (1024^3 fp32, 1024 workgroups: 57 -> 53 us); a product of many rounds hides nothing that the scans'
+  // own launches, with more rows in flight, do not do faster (256 x 512^3 fp32, 4096 workgroups: 528 us one
+  // after the other, 578 in one launch).
+  const int64_t tiles = (int64_t)ctx->ntm * ctx->ntn * p.batch;
+  if (gemm_takes_256(g) || tiles * ctx->ksplit > 2048) {
     // (a column scan goes before a row scan, which can carry its second stage; two row scans: P_c first, which
     // can carry what the encoding of B left)
     const ScanJob* first = pr && pc && pr->rowdot ? pc : pr;
@@ -644,7 +649,6 @@ hipError_t product(gecc_ctx* ctx, ScanQueue& q, const ScanJob* pr, const ScanJob
     return timed_gemm(ctx, g, nullptr, st);
   }
   // (the counters behind those of a k-split product)
-  const int64_t tiles = (int64_t)ctx->ntm * ctx->ntn * p.batch;
   int used = ctx->ksplit > 1 && tiles <= SCAN_DONE_WORDS ? (int)tiles : 0;
   GemmSide side{};
   int at = 0;
