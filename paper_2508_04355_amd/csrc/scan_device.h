@@ -515,9 +515,10 @@ __device__ __forceinline__ void coldot_body(const ScanArgs& a, int nchunk, int n
 // the chunk's rows, TS_RB rows (loads) at a time; three wavefronts share a SIMD and cover each
 // other's waits.  The kernel is bound by its arithmetic as much as by memory: per 16 bytes a lane
 // spends 8 conversions and 32 fp64 operations, which issue at half rate, about 380 cycles per row
-// and wavefront (measured: its loads alone stream at 5.8 TB/s, the whole kernel at 4.4; more loads in
-// flight, 8-byte lanes, rows DMA'd into an LDS ring or workgroups that read 4 KiB of every row
-// change nothing).  A lane keeps the column sums of its VEC columns in registers for the whole walk.
+// and wavefront (measured: its loads alone stream at 5.8 TB/s, the whole kernel at 4.2, and at 4.4 with
+// loads that are not kept in the caches: 470 MB 107 us instead of 114; the row part alone over 117 MB of 28 KiB
+// rows 22.5 instead of 27.7; more loads in flight, 8-byte lanes, rows DMA'd into an LDS ring or workgroups
+// that read 4 KiB of every row change nothing).  A lane keeps the column sums of its VEC columns in registers for the whole walk.
 // The row sums of a block of rows (TS_RB rows x 2 kinds, one partial per lane) are transposed through
 // LDS and added by four lanes per output; only the wavefront's own LDS region is involved, so no
 // workgroup barrier sits in the loop.
