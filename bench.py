@@ -18,7 +18,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-PEAK_TFLOPS = {"bf16": 2500.0, "f32": 157.3}     # MI355X dense MFMA peaks
+# MI355X dense MFMA peaks; fp32 products run as six bf16 products of pieces (native fp32 MFMAs: 157.3)
+PEAK_TFLOPS = {"bf16": 2500.0, "f32": 2500.0 / 6}
 HBM_PEAK_GBS = 8000.0
 
 # Memory traffic of the product kernel per launch (bytes), from rocprofv3 --pmc FETCH_SIZE and

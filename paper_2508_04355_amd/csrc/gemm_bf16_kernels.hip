@@ -806,7 +806,7 @@ hipError_t launch_layout(const GemmArgs& a, hipStream_t st) {
 // The fast kernel needs 16-byte aligned operand rows, whole 16-byte chunks and whole pairs of
 // k-tiles: k % 64 == 0, leading dimensions % 8 == 0, n (m) % 8 == 0 for an operand stored with n (m)
 // contiguous, and operand panels that 32-bit byte offsets can address.  Partial sums are
-// produced per 128 x 128 sub-tile.  Everything else goes to the generic 128 x 128 kernel.
+// produced per 128 x 128 sub-tile.  Everything else goes to gemm_tile.
 bool gemm_bf16_fast_ok(const GemmArgs& a) {
   if (a.dtype != GECC_BF16 || a.tile_m != 128 || a.tile_n != 128) return false;
   if (a.k % (2 * BK) || a.lda % 8 || a.ldb % 8) return false;
@@ -818,7 +818,7 @@ bool gemm_bf16_fast_ok(const GemmArgs& a) {
   const int64_t span_a = (a.trans_a ? (int64_t)a.k : (int64_t)BM) * a.lda * 2;
   const int64_t span_b = (a.trans_b ? (int64_t)BN : (int64_t)a.k) * a.ldb * 2;
   if (span_a >= 0x7fffffff || span_b >= 0x7fffffff || a.ldc >= (1 << 22)) return false;
-  return (int64_t)a.n * a.m >= (int64_t)BM * BN;   // smaller problems: the 128 x 128 kernel
+  return (int64_t)a.n * a.m >= (int64_t)BM * BN;   // smaller problems: gemm_tile
 }
 
 hipError_t launch_gemm_bf16_fast(const GemmArgs& a, hipStream_t st) {
