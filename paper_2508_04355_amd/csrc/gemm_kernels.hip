@@ -600,7 +600,10 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_tile(GemmArgs a, GemmSide sid
 // as the fused epilogues).  HBM-bound: every thread streams RPT rows x 4 columns with 16-byte
 // loads (full tile rows per wavefront instruction), keeps its row and column partial sums in
 // registers, and the workgroup combines them through LDS in a fixed order.
-template <int TILE>
+// STREAM: nothing it reads is kept in the caches -- for a C well beyond the 256 MiB of the memory-side cache
+// (940 MB: 156 us = 6.0 TB/s, with ordinary loads 172 to 175; 268 MB, part of which the last writer or reader
+// left there, 44 against 41).
+template <int TILE, bool STREAM>
 __global__ __launch_bounds__(THREADS) void partials_kernel(PartialArgs a) {
   constexpr int CG = TILE / 4, RG = THREADS / CG, RPT = TILE / RG;   // column groups of 4, row groups of RPT
   const int b = blockIdx.z;
@@ -620,13 +623,14 @@ __global__ __launch_bounds__(THREADS) void partials_kernel(PartialArgs a) {
   __shared__ float red_col[2][RG][TILE];
   float cs[4] = {0.f, 0.f, 0.f, 0.f}, cw[4] = {0.f, 0.f, 0.f, 0.f};
   // the kernel is a stream over C: all loads of a thread are issued before the first is used
-  // (rows past the end are clamped, not branched on, and count as zero below), and nothing it reads is kept
-  // in the caches (940 MB: 156 us = 6.0 TB/s, with ordinary loads 175)
+  // (rows past the end are clamped, not branched on, and count as zero below)
   f32x4_t pre[RPT];
   if (vec) {
 #pragma unroll
-    for (int r = 0; r < RPT; ++r)
-      pre[r] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(C + (int64_t)min(tile_r0 + rg * RPT + r, a.n - 1) * a.ldc + gj));
+    for (int r = 0; r < RPT; ++r) {
+      const f32x4_t* src = reinterpret_cast<const f32x4_t*>(C + (int64_t)min(tile_r0 + rg * RPT + r, a.n - 1) * a.ldc + gj);
+      pre[r] = STREAM ? __builtin_nontemporal_load(src) : *src;
+    }
   }
 #pragma unroll
   for (int r = 0; r < RPT; ++r) {
@@ -694,7 +698,7 @@ hipError_t launch_tile(const GemmArgs& a0, const GemmSide* side0, hipStream_t st
   side.blocks = side.pg_items + side.j[0].nblk + side.j[1].nblk;
   side.groups = (side.blocks + 7) / 8;
   const int64_t own = tiles * a.ksplit, grid_all = side.groups > 0 ? ((own + 7) / 8 + side.groups) * 8 : own;
-  if (grid_all > 0x7fffffff) return hipErrorInvalidValue;
+  if (grid_all > 0xffffff) return hipErrorInvalidValue;      // (2^32 threads)
   side.own = (int)own;
   const dim3 grid((unsigned)grid_all);
   // k-contiguous storage: A when not transposed, B when transposed
@@ -749,8 +753,14 @@ hipError_t launch_accumulate(float* C, const float* P, int n, int m, int64_t ldc
 hipError_t launch_partials(const PartialArgs& a, hipStream_t st) {
   if (a.tile_m != a.tile_n || (a.tile_m != 128 && a.tile_m != 64)) return hipErrorInvalidValue;
   dim3 grid(a.ntn, a.ntm, a.batch);
-  if (a.tile_m == 64) hipLaunchKernelGGL(partials_kernel<64>, grid, dim3(THREADS), 0, st, a);
-  else                hipLaunchKernelGGL(partials_kernel<128>, grid, dim3(THREADS), 0, st, a);
+  const bool stream = (int64_t)a.n * a.m * a.batch > ((int64_t)96 << 20);    // 384 MiB
+  if (a.tile_m == 64) {
+    if (stream) hipLaunchKernelGGL((partials_kernel<64, true>), grid, dim3(THREADS), 0, st, a);
+    else        hipLaunchKernelGGL((partials_kernel<64, false>), grid, dim3(THREADS), 0, st, a);
+  } else {
+    if (stream) hipLaunchKernelGGL((partials_kernel<128, true>), grid, dim3(THREADS), 0, st, a);
+    else        hipLaunchKernelGGL((partials_kernel<128, false>), grid, dim3(THREADS), 0, st, a);
+  }
   return hipGetLastError();
 }
 
