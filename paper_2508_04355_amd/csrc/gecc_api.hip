@@ -398,6 +398,7 @@ GemmArgs gemm_args(const gecc_ctx* c, const void* A, const void* B, float* C) {
   if (c->ksplit > 1 && c->ws && c->ws_bytes >= c->lay.total) {
     g.ksplit = c->ksplit;
     g.split_part = reinterpret_cast<float*>(c->ws + c->lay.ksplit);
+    g.split_bytes = c->lay.total - c->lay.ksplit;    // (last in the layout but for blocked mode's, which has no split here)
     g.split_done = reinterpret_cast<uint32_t*>(c->ws + c->lay.done);
   }
   g.rp_ld = c->rp_ld; g.cp_ld = c->cp_ld;
@@ -669,22 +670,30 @@ hipError_t product(gecc_ctx* ctx, ScanQueue& q, const ScanJob* pr, const ScanJob
 }
 
 // Blocked mode: the plan of a narrow product (parity columns or rows of all blocks against a whole operand).
-// Its partial tiles go where the main product's partial sums will go afterwards.
+// The 256 x 256-tile kernel where it is the faster one and takes these operands, by its launcher's own test; else
+// gemm_tile, whose partial tiles go where the main product's partial sums will go afterwards (as many k ranges
+// as fit there in the tile that runs).
 void narrow_plan(gecc_ctx* ctx, GemmArgs& g) {
   const gecc_params& p = ctx->p;
-  ProductPlan pl = plan_tiles(p.dtype, g.n, g.k, g.m, 1);
-  if (p.dtype == GECC_BF16 && fast_pays(g.n, g.k, g.m, 1)) pl.fast = true;
-  const size_t room = ctx->lay.synd - ctx->lay.rowpart;
-  const size_t tiles = (size_t)((g.n + pl.tile - 1) / pl.tile) * ((g.m + pl.tile - 1) / pl.tile), tile_bytes = (size_t)pl.tile * pl.tile * sizeof(float);
-  while (pl.ksplit > 1 && tiles * pl.ksplit * tile_bytes > room) --pl.ksplit;
-  g.tile_m = g.tile_n = pl.fast ? 128 : pl.tile;
-  g.ntm = (g.n + g.tile_m - 1) / g.tile_m;
-  g.ntn = (g.m + g.tile_n - 1) / g.tile_n;
-  g.fast = pl.fast;
-  g.ksplit = pl.ksplit;
-  g.split_part = reinterpret_cast<float*>(ctx->ws + ctx->lay.rowpart);
-  g.split_done = reinterpret_cast<uint32_t*>(ctx->ws + ctx->lay.done);
   g.rowpart = nullptr; g.colpart = nullptr; g.faults = nullptr; g.n_faults = 0;
+  ProductPlan pl = {128, 1, p.dtype == GECC_BF16 && fast_pays(g.n, g.k, g.m, 1)};
+  auto take = [&] {
+    g.tile_m = g.tile_n = pl.tile;
+    g.ntm = (g.n + pl.tile - 1) / pl.tile;
+    g.ntn = (g.m + pl.tile - 1) / pl.tile;
+    g.fast = pl.fast;
+  };
+  take();
+  if (!gemm_takes_256(g)) {
+    pl = plan_tiles(p.dtype, g.n, g.k, g.m, 1);
+    take();
+  }
+  g.split_part = reinterpret_cast<float*>(ctx->ws + ctx->lay.rowpart);
+  g.split_bytes = ctx->lay.synd - ctx->lay.rowpart;
+  g.split_done = reinterpret_cast<uint32_t*>(ctx->ws + ctx->lay.done);
+  const size_t one_range = (size_t)g.ntm * g.ntn * pl.tile * pl.tile * sizeof(float);
+  while (pl.ksplit > 1 && pl.ksplit * one_range > g.split_bytes) --pl.ksplit;
+  g.ksplit = pl.ksplit;
 }
 
 // Blocked mode, S3: the parity blocks of every block of C-bar on the matrix units -- the parity

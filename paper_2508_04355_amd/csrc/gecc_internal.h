@@ -250,6 +250,7 @@ struct GemmArgs {
   int ksplit;           // 0 or 1: off
   int k_per;            // set by the launcher: k range of one workgroup
   float* split_part;    // [tiles x batch][ksplit][tile_m x tile_n]
+  size_t split_bytes;   // what there is room for behind split_part: the launcher refuses a plan that needs more
   uint32_t* split_done; // [tiles x batch] counters, zero between launches (shared with the scans)
   // protected product only: P_g = A_P B_P goes to pg_out[b * pg_stride + 0..3], formed by the
   // workgroup of the first tile or by one of its own, which also resets the decoder state of its batch item

@@ -688,6 +688,7 @@ hipError_t launch_tile(const GemmArgs& a0, const GemmSide* side0, hipStream_t st
   GemmArgs a = a0;
   const int64_t tiles = (int64_t)((a.m + TILE - 1) / TILE) * ((a.n + TILE - 1) / TILE) * a.batch;
   if (a.ksplit > 1 && a.split_part && a.split_done && tiles <= SCAN_DONE_WORDS) {
+    if ((size_t)tiles * a.ksplit * TILE * TILE * sizeof(float) > a.split_bytes) return hipErrorInvalidValue;
     const int bk = GT<DT>::BK;
     a.k_per = ((a.k + a.ksplit - 1) / a.ksplit + bk - 1) / bk * bk;
   } else {

@@ -154,16 +154,31 @@ def compare(g: GpuResult, o: List[oc.Result], tol_c: float, tol_mag: float = Non
             assert np.max(np.abs(g.B[b] - res.B)) <= 1e-6 * max(1.0, np.max(np.abs(res.B))), tag
 
 
-def run_gpu_blocked(A_enc, B_enc, A_mul, B_mul, c_faults, tau, dtype, block, trans_a=0, trans_b=0, staged=True):
+GUARD = 4 << 20
+
+
+def run_gpu_blocked(A_enc, B_enc, A_mul, B_mul, c_faults, tau, dtype, block, trans_a=0, trans_b=0, staged=True, shift=0):
     """Blocked grid code (one product, batch 1): block = (block_n, block_m).  c_faults: [(i, j, e)] in
-    coordinates of the whole C.  Returns (reports per block in item order, C, A, B, C_par per item, synd)."""
+    coordinates of the whole C.  shift: elements the operands start behind a 16-byte boundary.  Returns (reports per
+    block in item order, C, A, B, C_par per item, synd, whether GUARD bytes behind the workspace are as they were)."""
     A_enc, B_enc, A_mul, B_mul = [np.asarray(x, dtype=np.float32)[None] for x in (A_enc, B_enc, A_mul, B_mul)]
     _, n, k = A_enc.shape
     m = B_enc.shape[2]
     ctx = gecc.Context(n, k, m, gecc.BF16 if dtype == "bf16" else gecc.F32,
                        gecc.Thresholds(tau.r1, tau.r2, tau.q1, tau.q2, tau.op, tau.rep, tau.rel), trans_a=trans_a,
                        trans_b=trans_b, block=block)
-    dA, dB = to_dev(A_enc, dtype, trans_a), to_dev(B_enc, dtype, trans_b)
+    nbytes = gecc.lib().gecc_workspace_bytes(ctx._h)
+    ws = torch.full((nbytes + 256 + GUARD,), 0xA5, dtype=torch.uint8, device=DEV)
+    ws_at = -ws.data_ptr() % 256
+    gecc._check(gecc.lib().gecc_set_workspace(ctx._h, ws.data_ptr() + ws_at, nbytes))
+
+    def put(x, trans):
+        t = to_dev(x, dtype, trans)
+        flat = torch.zeros(t.numel() + 8, dtype=t.dtype, device=DEV)
+        flat[shift:shift + t.numel()] = t.reshape(-1)
+        return flat[shift:shift + t.numel()].view(t.shape)
+
+    dA, dB = put(A_enc, trans_a), put(B_enc, trans_b)
     A_par, B_par, C_par = ctx.alloc_parities()
     rep = ctx.alloc_report()
     Cd = ctx.alloc_c()
@@ -188,4 +203,5 @@ def run_gpu_blocked(A_enc, B_enc, A_mul, B_mul, c_faults, tau, dtype, block, tra
     return dict(reports=reports, C=Cd.cpu().numpy().astype(np.float64)[0, :, :m],
                 A=from_dev(dA, trans_a, n if trans_a else k)[0], B=from_dev(dB, trans_b, k if trans_b else m)[0],
                 A_par=A_par.cpu().numpy(), B_par=B_par.cpu().numpy(),
-                C_par=C_par.cpu().numpy().reshape(items, -1), synd=synd)
+                C_par=C_par.cpu().numpy().reshape(items, -1), synd=synd,
+                guard_untouched=bool((ws[ws_at + nbytes:] == 0xA5).all()))

@@ -689,6 +689,29 @@ def test_blocked_grid_code_random_trials(dtype, shape, block, trans):
     assert min(seen.values()) > 0, seen
 
 
+@pytest.mark.parametrize("dtype,shape,block,trans,shift", [("bf16", (4096, 264, 4096), (2048, 2048), (0, 0), 0),     # k no multiple of 64
+                                                           ("bf16", (4096, 256, 4096), (4096, 4096), (0, 0), 0),     # fewer than 256 x 256 symbols
+                                                           ("bf16", (2048, 384, 4096), (1024, 1024), (0, 0), 0),
+                                                           ("bf16", (4096, 256, 4096), (1024, 1024), (1, 1), 1),     # not 16-byte aligned
+                                                           ("f32", (4096, 512, 4096), (2048, 2048), (0, 1), 0)])
+def test_narrow_products_of_blocked_mode_with_a_split_k_range(dtype, shape, block, trans, shift):
+    """Products whose parity blocks come from narrow products with a split k range (launch_plans.cpp holds these sizes to
+    that): every block against the oracle, and nothing written behind the workspace."""
+    n, k, m = shape
+    nb, mb = block
+    rng = inputs.rng_for(97, n + k + nb)
+    F = inputs.Fault
+    faults = [F(MAT_A, n - 5, k - 1, 4.0), F(MAT_C, 1, 2, 40.0), F(MAT_C, nb - 1, mb - 1, -25.0)]
+    A, B, A2, B2, cf, eff = _trial(rng, n, k, m, dtype, ("normal", 1.0), ("normal", 1.0), faults if n > nb else faults[1:])
+    tau = gecc.noise_thresholds(nb, k, mb, 1.0, 1.0)
+    res, Cref, Ao, Bo = oc.protected_gemm_blocked(A, B, A2, B2, cf, oc.Thresholds(tau.r1, tau.r2, tau.q1, tau.q2, tau.op, tau.rep, tau.rel), nb, mb)
+    g = H.run_gpu_blocked(A, B, A2, B2, cf, tau, dtype, block, trans[0], trans[1], shift=shift)
+    assert g["guard_untouched"]
+    _blocked_compare(g, res, Cref, n, m, nb, mb, tol_mag=4 * max(tau.r1, tau.q1))
+    assert all(r.status in (gecc.CLEAN, gecc.CORRECTED) for r in g["reports"]) and g["reports"][0].status == gecc.CORRECTED
+    assert np.array_equal(g["A"], A.astype(np.float64)) and np.array_equal(g["B"], B.astype(np.float64))
+
+
 def test_blocked_grid_code_at_the_forward_shape():
     """cfg4-fwd in 1024 x 1024 blocks (16 x 14 codewords): the parity blocks of all of them come from two
     narrow products on the 256 x 256-tile kernel.  Two errors in each of five blocks, a wrong symbol of A
