@@ -22,8 +22,10 @@
 // same operands in the same launch:
 //   - some accumulator is not finite (an infinite or NaN operand, |x| that rounds past the largest bf16,
 //     a sum that overflows): the fp32 arithmetic decides what C holds there;
-//   - the operand values a thread stages are not all zero and all below 2^-85: their low pieces get
-//     near the smallest normal number.
+//   - an operand value of the tile is below 2^-110 and not zero: its last bit is below 2^-133, the smallest
+//     subnormal bf16 (the matrix units keep subnormal operands: measured, the error of one product is the
+//     same for every power of two down to 2^-110 and doubles with each one below).  One such value is enough:
+//     beside ordinary ones of its row it may meet a large value of the other operand.
 #include "scan_device.h"
 
 namespace gecc {
@@ -35,7 +37,15 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 
 constexpr int THREADS = 256;
-constexpr float TINY = 0x1p-85f;
+constexpr float TINY = 0x1p-110f;
+
+// smallest magnitude of the nonzero values seen, as an integer that has their order (zero: the largest one)
+struct Least {
+  uint32_t v = 0xffffffffu;
+  static __device__ __forceinline__ uint32_t of(float x) { return (__float_as_uint(x) << 1) - 1u; }
+  __device__ __forceinline__ void see(float x0, float x1) { v = min(min(v, of(x0)), of(x1)); }
+  __device__ __forceinline__ bool tiny() const { return v < of(TINY); }
+};
 
 template <int DT> struct GT;
 template <> struct GT<GECC_BF16> {
@@ -80,16 +90,13 @@ struct Stager<DT, ROWS, true> {
   static constexpr int PLANE = ROWS * BK * 2;
   const T* src[N];
   uint4 reg[N];
-  float big[N];     // largest magnitude this thread has staged, per row
+  Least least;      // of the values this thread has staged
   int kk, klim;
   __device__ __forceinline__ void init(const T* P, int64_t ld, int r0, int rlim, int k_end) {
     kk = (threadIdx.x & 7) * V;
     klim = k_end;
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      src[i] = P + (int64_t)min(r0 + (int)(threadIdx.x >> 3) + 32 * i, rlim - 1) * ld + kk;
-      big[i] = 0.f;
-    }
+    for (int i = 0; i < N; ++i) src[i] = P + (int64_t)min(r0 + (int)(threadIdx.x >> 3) + 32 * i, rlim - 1) * ld + kk;
   }
   __device__ __forceinline__ void load(int k0) {
     if (k0 + BK <= klim) {
@@ -116,19 +123,15 @@ struct Stager<DT, ROWS, true> {
         uint32_t a[3], b[3];
         split2(x[0], x[1], a);
         split2(x[2], x[3], b);
-        big[i] = fmaxf(fmaxf(fmaxf(big[i], fabsf(x[0])), fmaxf(fabsf(x[1]), fabsf(x[2]))), fabsf(x[3]));
+        least.see(x[0], x[1]);
+        least.see(x[2], x[3]);
         char* dst = S + lds_at<BK>(row, (threadIdx.x & 7) >> 1) + (threadIdx.x & 1) * 8;
 #pragma unroll
         for (int q = 0; q < 3; ++q) *reinterpret_cast<uint2*>(dst + q * PLANE) = make_uint2(a[q], b[q]);
       }
     }
   }
-  __device__ __forceinline__ bool tiny() const {
-    bool t = false;
-#pragma unroll
-    for (int i = 0; i < N; ++i) t = t || (big[i] > 0.f && big[i] < TINY);
-    return t;
-  }
+  __device__ __forceinline__ bool tiny() const { return least.tiny(); }
   // the fp32 values as they are, rows of BK + 1 floats (native fp32 pass)
   __device__ __forceinline__ void store_plain(float* S) const {
 #pragma unroll
@@ -148,7 +151,7 @@ struct Stager<GECC_F32, ROWS, false> {
   static constexpr int PLANE = ROWS * BK * 2;
   const float* src;
   float reg[KPT];
-  float big;
+  Least least;
   int64_t ld;
   int row, kg, klim;
   __device__ __forceinline__ void init(const float* P, int64_t ld_, int r0, int rlim, int k_end) {
@@ -156,7 +159,6 @@ struct Stager<GECC_F32, ROWS, false> {
     kg = __builtin_amdgcn_readfirstlane(threadIdx.x / ROWS) * KPT;     // ROWS >= 64: one k group per wavefront
     ld = ld_; klim = k_end;
     src = P + min(r0 + row, rlim - 1);
-    big = 0.f;
   }
   __device__ __forceinline__ void load(int k0) {
     if (k0 + BK <= klim) {
@@ -178,14 +180,14 @@ struct Stager<GECC_F32, ROWS, false> {
       for (int h = 0; h < 4; ++h) {
         const float x0 = reg[c * 8 + 2 * h], x1 = reg[c * 8 + 2 * h + 1];
         split2(x0, x1, p[h]);
-        big = fmaxf(fmaxf(big, fabsf(x0)), fabsf(x1));
+        least.see(x0, x1);
       }
       char* dst = S + lds_at<BK>(row, (kg >> 3) + c);
 #pragma unroll
       for (int q = 0; q < 3; ++q) *reinterpret_cast<uint4*>(dst + q * PLANE) = make_uint4(p[0][q], p[1][q], p[2][q], p[3][q]);
     }
   }
-  __device__ __forceinline__ bool tiny() const { return big > 0.f && big < TINY; }
+  __device__ __forceinline__ bool tiny() const { return least.tiny(); }
   __device__ __forceinline__ void store_plain(float* S) const {
 #pragma unroll
     for (int x = 0; x < KPT; ++x) S[row * (BK + 1) + kg + x] = reg[x];

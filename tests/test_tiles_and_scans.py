@@ -61,7 +61,7 @@ def test_tiles_layouts_and_tails(shape, batch, dtype, trans):
 
 
 def test_values_the_bf16_pieces_cannot_hold():
-    """Infinities, NaN, magnitudes beyond the largest bf16 and operands far below 2^-85 go through native fp32
+    """Infinities, NaN, magnitudes beyond the largest bf16 and values below 2^-110 go through native fp32
     arithmetic: the same result as a chain of fp32 multiplications and additions would have."""
     n, k, m = 200, 96, 150
     rng = inputs.rng_for(81, 0)
@@ -93,6 +93,25 @@ def test_values_the_bf16_pieces_cannot_hold():
     _check(_product((A * np.float32(2.0 ** 30))[None], Z[None], "f32"), (A * np.float32(2.0 ** 30))[None], Z[None])
     # zeros are no tiny operands, and an all-zero operand gives zeros
     assert not _product(np.zeros((1, n, k), np.float32), B[None], "f32").any()
+
+
+@pytest.mark.parametrize("trans", [(0, 0), (1, 1)])
+@pytest.mark.parametrize("e", [100, 103, 108, 112, 120, 124])
+def test_tiny_values_beside_ordinary_ones(e, trans):
+    """Columns of A scaled by 2^-e against rows of B scaled by 2^e, every other one: a row holds values whose low pieces
+    bf16 cannot hold beside ordinary ones, and both kinds of products count alike.  And where only such products count."""
+    n, k, m = 200, 96, 150
+    rng = inputs.rng_for(86, e)
+    A, B = inputs.operands(rng, n, k, m, ("normal", 1.0), ("normal", 1.0), "f32")
+    d = np.ones(k, np.float32)
+    d[::2] = np.float32(2.0 ** -e)
+    X, Y = A * d, B / d[:, None]
+    _check(_product(X[None], Y[None], "f32", trans), X[None], Y[None])
+    Y[1::2] = 0.0
+    _check(_product(X[None], Y[None], "f32", trans), X[None], Y[None])
+    X[:, 2::2], Y[2::2] = 0.0, 0.0                   # one product a symbol: rounded once (and what k - 1 zeros cannot add)
+    C, ref = _product(X[None], Y[None], "f32", trans)[0], X.astype(np.float64) @ Y.astype(np.float64)
+    assert (np.abs(C - ref) <= 2.0 ** -23 * np.abs(ref)).all()
 
 
 @pytest.mark.parametrize("law", [("normal", 1.0), ("uniform", -1.0, 1.0), ("uniform", 0.0, 1.0)])
