@@ -16,7 +16,7 @@
 // of fp32 products, 960 of bf16 ones), 1024^3 50 -> 28 us, 128^3 28 -> 7.7 us, next to native fp32 MFMAs
 // in the kernel this one replaced, with a result closer to the fp64 product (2.1e-7 -> 6.5e-8 at 128^3,
 // 2.9e-7 -> 9e-8 at 1024^3).  bf16, 1500 x 1000 x 1100 with rows that are not 16-byte aligned: 67 -> 20 us,
-// the loads being vectors whatever the alignment.  What bounds it: the pieces (11 vector instructions per
+// the loads being vectors whatever the alignment.  What bounds it: the pieces (13 vector instructions per
 // two staged elements) and the two barriers per k-tile, which the other workgroups of the compute unit cover.
 // Where a piece cannot hold its part of x the tile is computed again with native fp32 MFMAs, from the
 // same operands in the same launch:
@@ -26,6 +26,13 @@
 //     subnormal bf16 (the matrix units keep subnormal operands: measured, the error of one product is the
 //     same for every power of two down to 2^-110 and doubles with each one below).  One such value is enough:
 //     beside ordinary ones of its row it may meet a large value of the other operand.
+// k of one k-tile (32 and less) goes through fp64 MFMAs instead.  Such a sum is a few roundings of native fp32
+// products; the matrix unit's own sum of 32 products and the pairs that the six leave out are more than those where
+// one or two products decide it (values spread over 17 decades, distance from the fp64 product against native ones:
+// k = 1 2.66e-8 against 2.63e-8, k = 8 3.64e-8 against 2.94e-8, k = 32 4.73e-8 against 4.06e-8).  Rounded once it is
+// closer than either on any operands (2.5e-8 for all three; normal ones, k = 32: 2.5e-8 against 3.9e-8 through pieces).
+// Bound there by the fp64 rate or by C's stores: 8192 x k x 8192 through fp64 and through pieces, k = 1 70 against
+// 80 us, k = 8 87 against 89, k = 32 111 against 78.
 #include "scan_device.h"
 
 namespace gecc {
@@ -33,6 +40,7 @@ namespace {
 
 typedef __attribute__((ext_vector_type(2))) float f32x2_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+typedef __attribute__((ext_vector_type(4))) double f64x4_t;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 
@@ -352,7 +360,8 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_tile(GemmArgs a, GemmSide sid
   sb.init(B, a.ldb, tile_c0, a.m, k_end);
   if (k_begin < k_end) { sa.load(k_begin); sb.load(k_begin); }
 
-  for (int k0 = k_begin; k0 < k_end; k0 += BK) {
+  const bool once = DT == GECC_F32 && a.k <= BK;       // (then k is not split)
+  for (int k0 = once ? k_end : k_begin; k0 < k_end; k0 += BK) {
     __syncthreads();               // previous tile fully consumed
     sa.store(As);
     sb.store(Bs);
@@ -397,6 +406,46 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_tile(GemmArgs a, GemmSide sid
 #pragma unroll
         for (int v = 0; v < 4; ++v) acc[i][j][v] += low[i][j][v];
   }
+  if constexpr (DT == GECC_F32) {
+    if (once) {
+      // The only k-tile, as it is, through fp64 MFMAs.  Their result has row 4 v + lg where the others have 4 lg + v:
+      // lane l16 is given the row of A that makes up for it.
+      float* Ap = reinterpret_cast<float*>(smem);
+      float* Bp = Ap + TILE * (BK + 1);
+      sa.store_plain(Ap);
+      sb.store_plain(Bp);
+      __syncthreads();
+      const float* fa = Ap + (wr * W + 4 * (l16 & 3) + (l16 >> 2)) * (BK + 1) + lg;
+      const float* fb = Bp + (wc * W + l16) * (BK + 1) + lg;
+      constexpr int IB = 4 / NI;                     // four independent chains
+#pragma unroll
+      for (int i0 = 0; i0 < NI; i0 += IB) {
+        f64x4_t d[IB][NI];
+#pragma unroll
+        for (int i = 0; i < IB; ++i)
+#pragma unroll
+          for (int j = 0; j < NI; ++j) d[i][j] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+        for (int ks = 0; ks < a.k; ks += 4) {
+          double x[IB], y[NI];
+#pragma unroll
+          for (int i = 0; i < IB; ++i) x[i] = fa[(i0 + i) * 16 * (BK + 1) + ks];
+#pragma unroll
+          for (int j = 0; j < NI; ++j) y[j] = fb[j * 16 * (BK + 1) + ks];
+#pragma unroll
+          for (int i = 0; i < IB; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j) d[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[i], y[j], d[i][j], 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < IB; ++i)
+#pragma unroll
+          for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[i0 + i][j][v] = (float)d[i][j][v];
+      }
+    }
+  }
   // rows and columns past the end count as zero
   if (tile_r0 + TILE > a.n || tile_c0 + TILE > a.m) {
 #pragma unroll
@@ -416,7 +465,7 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_tile(GemmArgs a, GemmSide sid
       for (int j = 0; j < NI; ++j)
 #pragma unroll
         for (int v = 0; v < 4; ++v) worst = fmaf(acc[i][j][v], 0.f, worst);
-    if (__syncthreads_or(worst != 0.f || sa.tiny() || sb.tiny())) {
+    if (__syncthreads_or(!once && (worst != 0.f || sa.tiny() || sb.tiny()))) {
       // native fp32 pass (see the head of this file)
       float* Ap = reinterpret_cast<float*>(smem);
       float* Bp = Ap + TILE * (BK + 1);

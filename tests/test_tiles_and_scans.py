@@ -1,7 +1,7 @@
 """The 64 x 64 / 128 x 128-tile product kernel (fp32 through bf16 pieces, ragged and unaligned bf16) against fp64.
 
-Tolerance, per symbol: every product is formed to 2^-24 of itself (fp32: the terms that are left out add up to
-less than 2^-25, a piece is the nearest bf16 to what it stands for; bf16: products are exact) and k of them are
+Tolerance, per symbol: every product is formed to 2^-24 of itself (fp32: the terms that are left out add up to less
+than 2^-24 of it, a piece is the nearest bf16 to what it stands for; bf16: products are exact) and k of them are
 added in fp32, so |C - C64| <= (k + 4) 2^-24 (|A| |B|)."""
 import numpy as np
 import pytest
@@ -112,6 +112,25 @@ def test_tiny_values_beside_ordinary_ones(e, trans):
     X[:, 2::2], Y[2::2] = 0.0, 0.0                   # one product a symbol: rounded once (and what k - 1 zeros cannot add)
     C, ref = _product(X[None], Y[None], "f32", trans)[0], X.astype(np.float64) @ Y.astype(np.float64)
     assert (np.abs(C - ref) <= 2.0 ** -23 * np.abs(ref)).all()
+
+
+@pytest.mark.parametrize("trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("k", [1, 2, 5, 31, 32])
+def test_short_fp32_sums_are_rounded_once(k, trans):
+    """k <= 32: summed in fp64, so what is left is one rounding to fp32, 2^-24 of the result or half the smallest number
+    (and 2^-45 of |A| |B|, k roundings to 2^-53).  On values spread over 17 decades, near the smallest numbers, and on
+    mantissas just above 1 + 2^-8, whose second and third bf16 pieces are the largest."""
+    n, m = 200, 150
+    rng = inputs.rng_for(87, 100 * k + trans[0] * 2 + trans[1])
+    spread = [(rng.standard_normal(s) * np.exp(rng.uniform(-20, 20, s))).astype(np.float32) for s in ((n, k), (k, m))]
+    above_one = [(rng.uniform(1.0035, 1.0042, s) * rng.choice([-1.0, 1.0], s)).astype(np.float32) for s in ((n, k), (k, m))]
+    for A, B in (spread, above_one):
+        for e in (0, 50, 58, 64, 72):
+            X, Y = A * np.float32(2.0 ** -e), B * np.float32(2.0 ** -e)
+            C = _product(X[None], Y[None], "f32", trans)[0]
+            X, Y = X.astype(np.float64), Y.astype(np.float64)
+            ref = X @ Y
+            assert (np.abs(C - ref) <= np.maximum(2.0 ** -24 * np.abs(ref), 2.0 ** -150) + 2.0 ** -45 * (np.abs(X) @ np.abs(Y))).all(), e
 
 
 @pytest.mark.parametrize("law", [("normal", 1.0), ("uniform", -1.0, 1.0), ("uniform", 0.0, 1.0)])
