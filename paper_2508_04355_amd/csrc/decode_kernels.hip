@@ -3,6 +3,7 @@
 // errors in A and B (each column of [A; A_P] and each row of [B B_P] is a codeword with two
 // parity symbols, Section III).  All scalar decoding arithmetic is fp64; everything is
 // stream-ordered and gated on state kept in device memory, so no host round trip is needed.
+#include <type_traits>
 #include "scan_device.h"
 
 namespace gecc {
@@ -906,6 +907,10 @@ __device__ __forceinline__ FinishWork finish_work(const PairArgs& audits, int w)
   o.q = v % per_item + (o.second ? audits.j[0].gx * audits.j[0].gy : 0);
   return o;
 }
+template <int DT>
+__global__ __launch_bounds__(DC_THREADS, 3) void finish_kernel(FinishArgs);
+// (it reads its argument from the start of the kernel's argument segment, so it can have no other)
+static_assert(std::is_same<decltype(&finish_kernel<GECC_F32>), void (*)(FinishArgs)>::value, "FinishArgs is all of finish_kernel's arguments");
 template <int DT>
 __global__ __launch_bounds__(DC_THREADS, 3) void finish_kernel(FinishArgs) {
   // (the arguments where the launch left them: through the parameter, the compiler gives every thread a copy
