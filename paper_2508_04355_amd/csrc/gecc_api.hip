@@ -614,9 +614,28 @@ int check_multiply_args(gecc_ctx* ctx, const void* dev_A, const double* dev_A_pa
   return GECC_OK;
 }
 
+// Whether the scans of the parity blocks (`scans`: their workgroups) ride in the launch of gemm_tile.  Two launches
+// saved are 9 us and more (128^3 fp32 44 -> 31 us, bf16 1500 x 1501 x 1500 75 -> 61), but a scan's workgroup there takes
+// the place of a product's, with fewer rows in flight than in a launch of its own.  Clean passes, one after the other
+// -> in one launch, over 2300 products of all layouts (both ways 14 % faster at best; this rule 13 to 23 %, riding
+// whenever the product has at most 2048 workgroups 12 to 22 %, with products that took twice as long):
+//   - many rounds of workgroups hide nothing (256 x 512^3 fp32 603 -> 608 us), and scans of more than 16 workgroups per
+//     compute unit take longer than the product (bf16 307 x 503 x 301 x 94 193 -> 313);
+//   - bf16, 128 x 128 tiles, long ranges of k: 5064 x 3680 x 1752 171 -> 222 (2880 x 520 x 2504: 80 -> 54);
+//   - fp32 keeps four workgroups of 64 x 64 tiles on a compute unit, two of 128 x 128: scans that find no place beside
+//     them delay a product of long k (3904 x 5888 x 448 289 -> 323, 2048^3 143 -> 190), and many of them also one of
+//     128 x 128 tiles (244 x 256 x 640 x 128 170 -> 326) or of more than 512 terms (8 x 600^3 NT 81 -> 143).
+bool scans_ride(const gecc_ctx* c, int64_t scans) {
+  const int64_t own = (int64_t)c->ntm * c->ntn * c->p.batch * c->ksplit;
+  const int k_per = c->p.k / c->ksplit;
+  const bool small = c->tile_m == 64;
+  if (own > 2048 || scans > 4096) return false;
+  if (c->p.dtype == GECC_BF16) return small || k_per <= 1536;
+  return own + scans <= (small ? 1536 : 768) || (k_per <= 640 && (scans <= 1792 || (small && k_per <= 512)));
+}
+
 // S3: the parity blocks pr, pc of C-bar (null: formed already), the data block, the fused syndrome partial
-// sums, P_g.  The scans of the parity blocks ride in the product's launch where that is a small one of
-// gemm_tile; otherwise they go first, on q.
+// sums, P_g.  The scans of the parity blocks ride in the product's launch (scans_ride) or go first, on q.
 hipError_t product(gecc_ctx* ctx, ScanQueue& q, const ScanJob* pr, const ScanJob* pc, const void* dev_A, const double* dev_A_par,
                    const void* dev_B, const double* dev_B_par, float* dev_C, double* dev_C_par, const gecc_fault* dev_faults,
                    int32_t n_faults, hipStream_t st) {
@@ -634,12 +653,25 @@ hipError_t product(gecc_ctx* ctx, ScanQueue& q, const ScanJob* pr, const ScanJob
   g.pg_stride = 2 * (int64_t)p.n + 2 * (int64_t)p.m + 4;
   g.state = reinterpret_cast<DecodeState*>(ctx->ws + ctx->lay.state);
   hipError_t e;
-  // Whether they ride is a matter of size: up to about four rounds of workgroups the two launches saved count
-  // (1024^3 fp32, 1024 workgroups: 57 -> 53 us); a product of many rounds hides nothing that the scans'
-  // own launches, with more rows in flight, do not do faster (256 x 512^3 fp32, 4096 workgroups: 528 us one
-  // after the other, 578 in one launch).
+  // (the counters behind those of a k-split product)
   const int64_t tiles = (int64_t)ctx->ntm * ctx->ntn * p.batch;
-  if (gemm_takes_256(g) || tiles * ctx->ksplit > 2048) {
+  int used = ctx->ksplit > 1 && tiles <= SCAN_DONE_WORDS ? (int)tiles : 0;
+  GemmSide side{};
+  int at = 0;
+  const ScanJob* jobs[2] = {pc, pr};
+  const ScanJob* alone[2] = {nullptr, nullptr};      // scans that cannot finish by themselves
+  for (int x = 0; x < 2; ++x) {
+    if (!jobs[x]) continue;
+    int words = 0;
+    if (make_side_job(jobs[x]->s, jobs[x]->rowdot, q.done() + used, SCAN_DONE_WORDS - used, side.j[at], words)) {
+      used += words;
+      ++at;
+    } else {
+      side.j[at] = SideJob{};
+      alone[x] = jobs[x];
+    }
+  }
+  if (gemm_takes_256(g) || !scans_ride(ctx, (int64_t)side.j[0].nblk + side.j[1].nblk + p.batch)) {
     // (a column scan goes before a row scan, which can carry its second stage; two row scans: P_c first, which
     // can carry what the encoding of B left)
     const ScanJob* first = pr && pc && pr->rowdot ? pc : pr;
@@ -649,22 +681,8 @@ hipError_t product(gecc_ctx* ctx, ScanQueue& q, const ScanJob* pr, const ScanJob
     if ((e = q.flush()) != hipSuccess) return e;
     return timed_gemm(ctx, g, nullptr, st);
   }
-  // (the counters behind those of a k-split product)
-  int used = ctx->ksplit > 1 && tiles <= SCAN_DONE_WORDS ? (int)tiles : 0;
-  GemmSide side{};
-  int at = 0;
-  const ScanJob* jobs[2] = {pc, pr};
-  for (const ScanJob* j : jobs) {
-    if (!j) continue;
-    int words = 0;
-    if (make_side_job(j->s, j->rowdot, q.done() + used, SCAN_DONE_WORDS - used, side.j[at], words)) {
-      used += words;
-      ++at;
-    } else {
-      side.j[at] = SideJob{};
-      if ((e = q.run(*j)) != hipSuccess) return e;
-    }
-  }
+  for (const ScanJob* j : alone)
+    if (j && (e = q.run(*j)) != hipSuccess) return e;
   if ((e = q.flush()) != hipSuccess) return e;
   return timed_gemm(ctx, g, &side, st);
 }

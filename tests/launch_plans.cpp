@@ -17,11 +17,12 @@ using namespace gecc;
 static std::map<const void*, std::string>& names() { static std::map<const void*, std::string> m; return m; }
 static struct { dim3 grid, block; size_t lds; hipStream_t st; } g_cfg;
 static gecc_ctx* g_ctx;
-static long g_launches, g_narrow_split, g_main_split, g_bad;
+static long g_launches, g_scans, g_narrow_split, g_main_split, g_bad;
 static std::string g_case;
 
 static void look_at(const std::string& name, void** args) {
   ++g_launches;
+  if (name.find("rowdot") != std::string::npos || name.find("coldot") != std::string::npos) ++g_scans;
   if (name.find("gemm_tile") == std::string::npos) return;
   const GemmArgs& a = *static_cast<const GemmArgs*>(args[0]);
   if (a.ksplit <= 1) return;
@@ -90,6 +91,19 @@ int main() {
   if (g_narrow_split != 9) { ++g_bad; printf("BAD: %ld narrow products have a split k range, 9 should\n", g_narrow_split); }
   one(4096, 300, 4096, 1, GECC_BF16, 0, 0, 1024, 1024, 0, 0);
   one(8192, 300, 6144, 1, GECC_BF16, 0, 0, 8192, 6144, 0, 0);
+  // the scans of the parity blocks: in the product's launch where that pays, else launches of their own
+  auto scans = [](int n, int k, int m, int batch, int dtype, int ta, int tb) {
+    const long before = g_scans;
+    one(n, k, m, batch, dtype, ta, tb, 0, 0, 0, 0);
+    return g_scans - before;
+  };
+  auto expect = [](bool ok, const char* what) { if (!ok) { ++g_bad; printf("BAD: scans of %s\n", what); } };
+  expect(scans(128, 128, 128, 1, GECC_F32, 0, 0) == 0, "128^3");
+  expect(scans(1024, 1024, 1024, 1, GECC_F32, 0, 0) == 0, "1024^3");
+  expect(scans(1500, 1501, 1500, 1, GECC_BF16, 0, 1) == 0, "bf16 1500 x 1501 x 1500");
+  expect(scans(600, 600, 600, 8, GECC_F32, 0, 1) == 2, "8 x 600^3 NT");
+  expect(scans(2048, 2048, 2048, 1, GECC_F32, 0, 0) == 2, "2048^3");
+  expect(scans(503, 301, 94, 307, GECC_BF16, 0, 0) == 2, "bf16 307 x 503 x 301 x 94");
   std::mt19937 rng(7);
   auto pick = [&](int lo, int hi) { return lo + (int)(rng() % (uint32_t)(hi - lo + 1)); };
   const int pads[] = {0, 0, 3, 8};
