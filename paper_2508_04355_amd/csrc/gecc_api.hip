@@ -307,7 +307,7 @@ TileScanJob tile_job(gecc_ctx* c, int op, const void* X, double* enc_out, const 
   const bool is_a = op == GECC_MAT_A;
   const bool tr = is_a ? p.trans_a != 0 : p.trans_b != 0;
   TileScanJob t{};
-  t.X = X; t.dtype = p.dtype; t.batch = p.batch;
+  t.X = X; t.dtype = p.dtype; t.batch = p.batch; t.stream = c->stream;
   t.ld = is_a ? p.lda : p.ldb;
   t.xs = is_a ? p.stride_a : p.stride_b;
   const int len = is_a ? p.n : p.m;                 // the axis the encoding sums over
@@ -449,6 +449,11 @@ int gecc_create(gecc_ctx** out, const gecc_params* p) {
     const char* t = getenv("GECC_TILE_MIN");       // test hook: operands of that many elements or more take the one-pass scan
     c->tile_min = (t && atoll(t) > 0) ? atoll(t) : ((int64_t)1 << 25);
   }
+  // Operands that fit the 256 MiB memory-side cache, or nearly so, are still there for the product when a scan has
+  // read them; loads past the caches pay only beyond (clean passes, ordinary loads -> such loads: both operands
+  // 201 MB 4096 x 8192 x 8192 NT 443 -> 508 us, 104 MB 9000 x 4000 x 4000 508 -> 548, 335 MB 4096 x 8192 x 16384 NT
+  // 921 -> 956; 402 MB 16384 x 8192 x 8192 1600 -> 1563, 587 MB 4096 x 16384 x 14336 NT 1808 -> 1738).
+  c->stream = ((int64_t)p->n + p->m) * p->k * p->batch * (int64_t)elem_size(p->dtype) >= ((int64_t)384 << 20);
   // the larger operand is read once for both of its reductions (tile scan), the other one twice
   c->tile_op = p->n >= p->m ? GECC_MAT_A : GECC_MAT_B;
   c->nbi = p->block_n > 0 ? p->n / p->block_n : 0;

@@ -77,6 +77,7 @@ struct gecc_ctx {
   int ksplit;              // workgroups per tile of gemm_tile (1: no split)
   bool fast;               // bf16: the 256 x 256-tile kernel takes the product where the operands' addresses allow it
   int cu_hint;             // GECC_CU_COUNT (tests: plan the tile rounds as for that many CUs), else 0
+  bool stream;             // the tile scans load past the caches (see gecc_create)
   int64_t tile_min;        // operands of that many elements or more take the tile scan (2^25; GECC_TILE_MIN for tests)
   char* ws;                // device workspace (caller's)
   size_t ws_bytes;
@@ -171,6 +172,7 @@ struct TileScanJob {
   int64_t row_out_stride;
   double* col_scratch;      // coldot_scratch_doubles(R, Cc, batch)
   double* row_scratch;      // tile_scan_row_scratch_doubles(R, Cc, dtype, batch)
+  bool stream;              // loads that are not kept in the caches
   uint32_t* done;           // SCAN_DONE_WORDS zeroed counters, or null: parts that can then finish by themselves
   const int32_t* gate;
   int64_t gate_stride;
@@ -195,6 +197,7 @@ struct TileScanArgs {
   int64_t wc_stride;
   double* row_part;       // [batch][R][nseg][2]
   int chunk_rows, nchunk, nseg;
+  bool stream;
   const int32_t* gate;
   int64_t gate_stride;
   int gate_value;

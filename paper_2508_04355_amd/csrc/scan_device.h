@@ -2,6 +2,7 @@
 // (see scan_kernels.hip, which launches them on their own and in pairs, and gemm_kernels.hip, where the
 // parity blocks of C-bar ride in the product's launch).
 #pragma once
+#include <type_traits>
 #include "gecc_internal.h"
 
 namespace gecc {
@@ -516,9 +517,10 @@ __device__ __forceinline__ void coldot_body(const ScanArgs& a, int nchunk, int n
 // other's waits.  The kernel is bound by its arithmetic as much as by memory: per 16 bytes a lane
 // spends 8 conversions and 32 fp64 operations, which issue at half rate, about 380 cycles per row
 // and wavefront (measured: its loads alone stream at 5.8 TB/s, the whole kernel at 4.2, and at 4.4 with
-// loads that are not kept in the caches: 470 MB 107 us instead of 114; the row part alone over 117 MB of 28 KiB
-// rows 22.5 instead of 27.7; more loads in flight, 8-byte lanes, rows DMA'd into an LDS ring or workgroups
-// that read 4 KiB of every row change nothing).  A lane keeps the column sums of its VEC columns in registers for the whole walk.
+// loads that are not kept in the caches: 470 MB 107 us instead of 114, the row part alone over 117 MB of 28 KiB rows
+// 22.5 instead of 27.7, for the whole step a gain only where the operands are beyond the caches anyway (stream, see
+// gecc_create); more loads in flight, 8-byte lanes, rows DMA'd into an LDS ring or workgroups that read 4 KiB of
+// every row change nothing).  A lane keeps the column sums of its VEC columns in registers for the whole walk.
 // The row sums of a block of rows (TS_RB rows x 2 kinds, one partial per lane) are transposed through
 // LDS and added by four lanes per output; only the wavefront's own LDS region is involved, so no
 // workgroup barrier sits in the loop.
@@ -621,9 +623,12 @@ __device__ __forceinline__ void tile_scan_body(const TileScanArgs& a, int seg, i
   const int nfull = (w_end - w_beg) / TS_RB;
   if (nfull > 0) {
     typename E::raw xa[TS_RB];
-    auto load = [&](typename E::raw* x, int rr) {
+    auto load = [&](typename E::raw* x, int rr, auto stream) {
 #pragma unroll
-      for (int u = 0; u < TS_RB; ++u) x[u] = E::load_stream(col + (int64_t)(rr + u) * a.ld);
+      for (int u = 0; u < TS_RB; ++u) {
+        const T* src = col + (int64_t)(rr + u) * a.ld;
+        x[u] = stream.value ? E::load_stream(src) : E::load_raw(src);
+      }
     };
     auto work = [&](const typename E::raw* x, int rr) {
       // the row weights of the whole block first (uniform loads: one wait, not one per row)
@@ -640,11 +645,16 @@ __device__ __forceinline__ void tile_scan_body(const TileScanArgs& a, int seg, i
       }
       if (ROW) emit_rows(rr, TS_RB);
     };
-    for (int bi = 0; bi < nfull; ++bi) {
-      load(xa, r);
-      work(xa, r);
-      r += TS_RB;
-    }
+    // (a loop for either kind of load: a branch around the loads alone would keep them from starting early)
+    auto walk = [&](auto stream) {
+      for (int bi = 0; bi < nfull; ++bi) {
+        load(xa, r, stream);
+        work(xa, r);
+        r += TS_RB;
+      }
+    };
+    if (a.stream) walk(std::true_type{});
+    else walk(std::false_type{});
   }
   if (r < w_end) {     // the last rows of the operand: fewer than TS_RB
     const int cnt = w_end - r;

@@ -189,6 +189,7 @@ static bool make_tile_args(const TileScanJob& t, TileScanArgs& a, bool& fuse_col
   a.wr = t.wr; a.wr_stride = t.wr_stride; a.col_part = t.col_scratch;
   a.wc = t.wc; a.wc_stride = t.wc_stride; a.row_part = t.row_scratch;
   a.nseg = tile_scan_segments(t.Cc, t.dtype);
+  a.stream = t.stream;
   // (larger chunks only save column partial sums: a row part alone takes the smallest, for the balance)
   a.chunk_rows = t.col_on ? tile_scan_chunk_rows(t.R, a.nseg, t.batch) : SCAN_CHUNK_ROWS;
   a.nchunk = (t.R + a.chunk_rows - 1) / a.chunk_rows;
