@@ -622,21 +622,49 @@ int check_multiply_args(gecc_ctx* ctx, const void* dev_A, const double* dev_A_pa
 // Whether the scans of the parity blocks (`scans`: their workgroups) ride in the launch of gemm_tile.  Two launches
 // saved are 9 us and more (128^3 fp32 44 -> 31 us, bf16 1500 x 1501 x 1500 75 -> 61), but a scan's workgroup there takes
 // the place of a product's, with fewer rows in flight than in a launch of its own.  Clean passes, one after the other
-// -> in one launch, over 2300 products of all layouts (both ways 14 % faster at best; this rule 13 to 23 %, riding
+// -> in one launch, over 2300 products of all layouts (this rule 13 to 23 % faster on average, riding
 // whenever the product has at most 2048 workgroups 12 to 22 %, with products that took twice as long):
 //   - many rounds of workgroups hide nothing (256 x 512^3 fp32 603 -> 608 us), and scans of more than 16 workgroups per
 //     compute unit take longer than the product (bf16 307 x 503 x 301 x 94 193 -> 313);
-//   - bf16, 128 x 128 tiles, long ranges of k: 5064 x 3680 x 1752 171 -> 222 (2880 x 520 x 2504: 80 -> 54);
-//   - fp32 keeps four workgroups of 64 x 64 tiles on a compute unit, two of 128 x 128: scans that find no place beside
-//     them delay a product of long k (3904 x 5888 x 448 289 -> 323, 2048^3 143 -> 190), and many of them also one of
-//     128 x 128 tiles (244 x 256 x 640 x 128 170 -> 326) or of more than 512 terms (8 x 600^3 NT 81 -> 143).
-bool scans_ride(const gecc_ctx* c, int64_t scans) {
+//   - bf16, 128 x 128 tiles: long ranges of k (5064 x 3680 x 1752 171 -> 222) and more than 5 scan workgroups per
+//     compute unit (3029 x 817 x 2493 NT 77 -> 85) lose, others gain (2880 x 520 x 2504 TN 80 -> 54);
+//   - fp32 keeps four workgroups of 64 x 64 tiles on a compute unit: scans that find no place beside them delay a
+//     product of long k (3904 x 5888 x 448 289 -> 323), and many of them one of more than 512 terms (8 x 600^3 NT
+//     81 -> 143).  Of 128 x 128 tiles it keeps two: both scans together, if they are few, beside short ranges of k (68 x
+//     512 x 256 x 128 TN 90 -> 73; 2048^3 143 -> 190, 253 x 256 x 640 x 128 TN, where a tile scan has left one, 170 -> 327).
+bool scans_ride(const gecc_ctx* c, int64_t scans, bool both) {
   const int64_t own = (int64_t)c->ntm * c->ntn * c->p.batch * c->ksplit;
   const int k_per = c->p.k / c->ksplit;
   const bool small = c->tile_m == 64;
   if (own > 2048 || scans > 4096) return false;
-  if (c->p.dtype == GECC_BF16) return small || k_per <= 1536;
-  return own + scans <= (small ? 1536 : 768) || (k_per <= 640 && (scans <= 1792 || (small && k_per <= 512)));
+  if (c->p.dtype == GECC_BF16) return small || (k_per <= 1536 && scans <= 1280);
+  if (!small) return both && k_per <= 640 && scans <= 1024;
+  return own + scans <= 1536 || (k_per <= 640 && (scans <= 1792 || k_per <= 512));
+}
+
+// The scans that ride (side) and those of them that cannot finish by themselves and go first (alone).
+struct Riders { bool on; GemmSide side; const ScanJob* alone[2]; };
+Riders plan_riders(const gecc_ctx* ctx, const GemmArgs& g, uint32_t* done, const ScanJob* pr, const ScanJob* pc) {
+  Riders r{};
+  if (gemm_takes_256(g)) return r;
+  // (the counters behind those of a k-split product)
+  const int64_t tiles = (int64_t)ctx->ntm * ctx->ntn * ctx->p.batch;
+  int used = ctx->ksplit > 1 && tiles <= SCAN_DONE_WORDS ? (int)tiles : 0;
+  int at = 0;
+  const ScanJob* jobs[2] = {pc, pr};
+  for (int x = 0; x < 2; ++x) {
+    if (!jobs[x]) continue;
+    int words = 0;
+    if (make_side_job(jobs[x]->s, jobs[x]->rowdot, done + used, SCAN_DONE_WORDS - used, r.side.j[at], words)) {
+      used += words;
+      ++at;
+    } else {
+      r.side.j[at] = SideJob{};
+      r.alone[x] = jobs[x];
+    }
+  }
+  r.on = scans_ride(ctx, (int64_t)r.side.j[0].nblk + r.side.j[1].nblk + ctx->p.batch, pr && pc);
+  return r;
 }
 
 // S3: the parity blocks pr, pc of C-bar (null: formed already), the data block, the fused syndrome partial
@@ -658,25 +686,8 @@ hipError_t product(gecc_ctx* ctx, ScanQueue& q, const ScanJob* pr, const ScanJob
   g.pg_stride = 2 * (int64_t)p.n + 2 * (int64_t)p.m + 4;
   g.state = reinterpret_cast<DecodeState*>(ctx->ws + ctx->lay.state);
   hipError_t e;
-  // (the counters behind those of a k-split product)
-  const int64_t tiles = (int64_t)ctx->ntm * ctx->ntn * p.batch;
-  int used = ctx->ksplit > 1 && tiles <= SCAN_DONE_WORDS ? (int)tiles : 0;
-  GemmSide side{};
-  int at = 0;
-  const ScanJob* jobs[2] = {pc, pr};
-  const ScanJob* alone[2] = {nullptr, nullptr};      // scans that cannot finish by themselves
-  for (int x = 0; x < 2; ++x) {
-    if (!jobs[x]) continue;
-    int words = 0;
-    if (make_side_job(jobs[x]->s, jobs[x]->rowdot, q.done() + used, SCAN_DONE_WORDS - used, side.j[at], words)) {
-      used += words;
-      ++at;
-    } else {
-      side.j[at] = SideJob{};
-      alone[x] = jobs[x];
-    }
-  }
-  if (gemm_takes_256(g) || !scans_ride(ctx, (int64_t)side.j[0].nblk + side.j[1].nblk + p.batch)) {
+  const Riders r = plan_riders(ctx, g, q.done(), pr, pc);
+  if (!r.on) {
     // (a column scan goes before a row scan, which can carry its second stage; two row scans: P_c first, which
     // can carry what the encoding of B left)
     const ScanJob* first = pr && pc && pr->rowdot ? pc : pr;
@@ -686,10 +697,10 @@ hipError_t product(gecc_ctx* ctx, ScanQueue& q, const ScanJob* pr, const ScanJob
     if ((e = q.flush()) != hipSuccess) return e;
     return timed_gemm(ctx, g, nullptr, st);
   }
-  for (const ScanJob* j : alone)
+  for (const ScanJob* j : r.alone)
     if (j && (e = q.run(*j)) != hipSuccess) return e;
   if ((e = q.flush()) != hipSuccess) return e;
-  return timed_gemm(ctx, g, &side, st);
+  return timed_gemm(ctx, g, &r.side, st);
 }
 
 // Blocked mode: the plan of a narrow product (parity columns or rows of all blocks against a whole operand).
@@ -943,7 +954,7 @@ int encode_and_multiply(gecc_ctx* ctx, void* dev_A, void* dev_B, float* dev_C, d
     return hip_rc(product(ctx, q, long_rows || t_is_a ? nullptr : &pr, long_rows || !t_is_a ? nullptr : &pc, dev_A, dev_A_par,
                           dev_B, dev_B_par, dev_C, dev_C_par, dev_faults, n_faults, st));
   }
-  if (p.trans_a && !p.trans_b && gemm_takes_256(gemm_args(ctx, dev_A, dev_B, dev_C))) {
+  if (p.trans_a && !p.trans_b && !plan_riders(ctx, gemm_args(ctx, dev_A, dev_B, dev_C), q.done(), &pr, &pc).on) {
     // both encodings are row scans, both parity blocks column scans: in turn, so that A_P carries P_r's second stage
     if ((e = q.run(eb)) != hipSuccess || (e = q.run(pr)) != hipSuccess || (e = q.run(ea)) != hipSuccess) return hip_rc(e);
     return hip_rc(product(ctx, q, nullptr, &pc, dev_A, dev_A_par, dev_B, dev_B_par, dev_C, dev_C_par, dev_faults, n_faults, st));
