@@ -104,8 +104,8 @@ ProductPlan plan_tiles(int dtype, int64_t n, int64_t k, int64_t m, int64_t batch
 }
 
 // Whether the 256 x 256-tile kernel is the faster one for a bf16 product it can take: it needs a workgroup per
-// compute unit to show its rate (1300 TFLOP/s against 650 of gemm_tile), and has no k-split for fewer
-// tiles.  Both times as fitted to measurements (256 x 256 / gemm_tile): 1024^3 22 / 15, 384 x 3904 x 768
+// compute unit to show its rate (1300 TFLOP/s; gemm_tile comes to 650 on large products), and has no k-split for fewer
+// tiles.  Both times for products of few tiles, where gemm_tile does 330 (64 x 64) to 420 TFLOP/s, as fitted to measurements (256 x 256 / gemm_tile): 1024^3 22 / 15, 384 x 3904 x 768
 // 62 / 24, 1536 x 4224 x 768 67 / 36, 1920 x 2176 x 512 39 / 23, 2048^3 41 / 42, 1280 x 7296 x 2304
 // 116 / 127, 3072 x 2048 x 3072 44 / 78.
 bool fast_pays(int64_t n, int64_t k, int64_t m, int64_t batch) {

@@ -505,8 +505,9 @@ def test_results_are_reproducible_bit_for_bit():
 @pytest.mark.parametrize("dtype,shape,trans", [("f32", (1024, 1024, 1024), (0, 0)), ("bf16", (1024, 512, 768), (0, 1)),
                                                ("bf16", (768, 512, 1024), (1, 0)), ("f32", (520, 264, 392), (1, 1))])
 def test_launches_of_a_clean_step(dtype, shape, trans):
-    """Four scans (a row scan carries the second stage of a column scan where one follows it), the
-    product, the threshold pass, the first report, and two gated launches: both audits in one, the repair."""
+    """Two encodings, the product (with the parity blocks, or after two more scans; a row scan carries the second stage of
+    a column scan where one follows it), the threshold pass, the first report with both gated audits (one launch, a record
+    of either class) and the gated repair."""
     import torch
     n, k, m = shape
     rng = inputs.rng_for(2, 77)
@@ -714,7 +715,7 @@ def test_narrow_products_of_blocked_mode_with_a_split_k_range(dtype, shape, bloc
 
 def test_blocked_grid_code_at_the_forward_shape():
     """cfg4-fwd in 1024 x 1024 blocks (16 x 14 codewords): the parity blocks of all of them come from two
-    narrow products on the 256 x 256-tile kernel.  Two errors in each of five blocks, a wrong symbol of A
+    narrow products with a split k range.  Two errors in each of five blocks, a wrong symbol of A
     (seen by the 14 blocks of its row block) and one of B; every block against the oracle."""
     w = configs.CFG4_FWD
     n, k, m, nb, mb = w.n, w.k, w.m, 1024, 1024
