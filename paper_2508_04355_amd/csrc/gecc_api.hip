@@ -93,14 +93,16 @@ int ksplit_bf16_128(int64_t t128, int k) {
 // (1536 x 4224 x 768: 36 against 39, 16384 x 4096 x 88: 41 against 52).  64 x 64 tiles: the rest (fp32
 // 1024^3 28 against 37, 128^3 7.7 against 13.8; bf16 1500 x 1000 x 1100 19.5 against 28).
 // Workgroups: fp32 tiles of 64 keep four per compute unit busy (1024^3: one workgroup per tile 40, two 31,
-// four 28, eight 38), bf16 ones two, to the nearest (1500 x 1000 x 1100, 432 tiles: 19.5, split in two 22),
+// four 28, eight 38); up to one tile per compute unit three are enough, and leave the fourth place to the scans that
+// ride along (whole calls at 1024, 800 and 512 workgroups: 1024^3 48.4, 44.9 and 47.1, 900 x 1500 x 900 55.1, 53.1 and
+// 57.8, 1000 x 1031 x 777 TT 48.0, 46.4 and 50.6; with more tiles 800 are too few, 1300^3, 441 tiles, 74.0 and 80.9), bf16 ones two, to the nearest (1500 x 1000 x 1100, 432 tiles: 19.5, split in two 22),
 // fp32 tiles of 128 two (2000 x 1000 x 2000: 83, split in two 67).
 ProductPlan plan_tiles(int dtype, int64_t n, int64_t k, int64_t m, int64_t batch) {
   const int64_t t128 = ((n + 127) / 128) * ((m + 127) / 128) * batch, t64 = ((n + 63) / 64) * ((m + 63) / 64) * batch;
   const int s_long = dtype == GECC_BF16 ? ksplit_bf16_128(t128, (int)k) : 0;
   if (s_long > 0) return {128, s_long, false};
   if (t128 >= 256 && k >= 256 && 3 * t128 < t64) return {128, dtype == GECC_F32 && t128 < 512 ? 2 : 1, false};
-  return {64, dtype == GECC_F32 ? ksplit_of(t64, 1024, (int)k) : ksplit_of(t64, 512 + (int)(t64 < 512 ? t64 / 2 : 0), (int)k), false};
+  return {64, dtype == GECC_F32 ? ksplit_of(t64, t64 > 256 ? 1024 : 800, (int)k) : ksplit_of(t64, 512 + (int)(t64 < 512 ? t64 / 2 : 0), (int)k), false};
 }
 
 // Whether the 256 x 256-tile kernel is the faster one for a bf16 product it can take: it needs a workgroup per
@@ -663,7 +665,10 @@ Riders plan_riders(const gecc_ctx* ctx, const GemmArgs& g, uint32_t* done, const
       r.alone[x] = jobs[x];
     }
   }
-  r.on = scans_ride(ctx, (int64_t)r.side.j[0].nblk + r.side.j[1].nblk + ctx->p.batch, pr && pc);
+  // (the rule counts a row scan by fours of rows, which is how it was measured)
+  int64_t scans = ctx->p.batch;
+  for (const SideJob& j : r.side.j) scans += j.kind == SIDE_ROW ? (int64_t)((j.s.R + 3) / 4) * j.s.batch : j.nblk;
+  r.on = scans_ride(ctx, scans, pr && pc);
   return r;
 }
 

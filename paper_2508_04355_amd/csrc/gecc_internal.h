@@ -263,7 +263,7 @@ struct GemmArgs {
   int64_t pg_stride;
   DecodeState* state;
 };
-// Scans that ride in the launch of gemm_tile, as workgroups of their own spread evenly among the product's:
+// Scans that ride in the launch of gemm_tile, as workgroups of their own before the product's:
 // the parity blocks P_r and P_c of C-bar (vector weights; a column scan is finished by its last
 // workgroup) and P_g.  Nothing in the launch reads what they form.
 enum : int { SIDE_NONE = 0, SIDE_ROW = 1, SIDE_ROW_WAVE = 2, SIDE_COL = 3 };

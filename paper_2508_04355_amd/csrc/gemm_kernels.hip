@@ -277,19 +277,21 @@ __device__ __forceinline__ void side_job(const GemmArgs& a, const GemmSide& side
   const SideJob& j = second ? side.j[1] : side.j[0];
   const int per_item = j.gx * j.gy;
   const int b = v / per_item, x = (v % per_item) % j.gx, y = (v % per_item) / j.gx;
-  if (j.kind == SIDE_ROW) rowdot_body<DT, false, RD_SMALL_RB, 1>(j.s, x, b, lds);
+  if (j.kind == SIDE_ROW) rowdot_body<DT, false, side_rows<DT>(), 1>(j.s, x, b, lds);
   else if (j.kind == SIDE_COL) coldot_body<DT, false, DT == GECC_F32 ? 4 : 2>(j.s, j.gy, j.gx, x, y, b, lds);
   else if constexpr (DT == GECC_F32) rowdot_wave_body<DT, false>(j.s, x, b, lds);
 }
 
 // -------------------------------------------------------------------------------------------
-// Grid: one dimension, tiles x batch x ksplit workgroups, and among them those of the scans that ride along.
+// Grid: one dimension, the scans that ride along, then tiles x batch x ksplit workgroups.
 // Consecutive workgroups go to the 8 XCDs in turn, so every XCD is given a contiguous range of the (item,
 // split, tile row, tile column) sequence: tiles that share operand panels share an L2.  The scans are
-// HBM-bound and the product is not: in one launch, spread evenly, they cost little more than the
-// product alone, and a launch that waits for the one before it costs 4.5 us whatever it does.
+// HBM-bound and the product is not: in one launch they cost little more than the
+// product alone, and a launch that waits for the one before it costs 4.5 us whatever it does.  They come first: a
+// scan is over after 5 us and makes room for a workgroup of the product, which takes 20; spread evenly among those of
+// a product that fills the chip by itself, they had 230 of 1024^3's 1024 begin up to 20 us late.
 template <int DT, bool KCA, bool KCB, int TILE>
-__global__ __launch_bounds__(THREADS, 2) void gemm_tile(GemmArgs a, GemmSide side) {
+__global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : 2) void gemm_tile(GemmArgs a, GemmSide side) {
   using T = typename GT<DT>::T;
   constexpr int BK = GT<DT>::BK, PIECES = GT<DT>::PIECES, W = TILE / 2, NI = W / 16;   // W x W per wavefront
   constexpr int PLANE = TILE * BK * 2, OPERAND = PIECES * PLANE;
@@ -306,15 +308,12 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_tile(GemmArgs a, GemmSide sid
   const int ntm = (a.n + TILE - 1) / TILE, ntn = (a.m + TILE - 1) / TILE;
   int id = blockIdx.x;
   if (side.groups > 0) {
-    // groups of 8 workgroups: group g belongs to the scans where floor(g groups / G) steps
-    const int g = id >> 3, G = gridDim.x >> 3;
-    const int before = (int)((int64_t)g * side.groups / G), after = (int)((int64_t)(g + 1) * side.groups / G);
-    if (after > before) {
-      const int v = before * 8 + (id & 7);
-      if (v < side.blocks) side_job<DT>(a, side, v, reinterpret_cast<double*>(smem));
+    // the scans first, in whole groups of 8 workgroups (one per XCD)
+    if (id < side.groups * 8) {
+      if (id < side.blocks) side_job<DT>(a, side, id, reinterpret_cast<double*>(smem));
       return;
     }
-    id = (g - before) * 8 + (id & 7);
+    id -= side.groups * 8;
     if (id >= side.own) return;
   }
   {
@@ -354,6 +353,18 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_tile(GemmArgs a, GemmSide sid
 #pragma unroll
       for (int v = 0; v < 4; ++v) low[i][j][v] = 0.f;
 
+  // fp32, 64 x 64: the first half of the range in a third set, for shorter chains again (1024^3 in three ranges of k:
+  // 1.10e-7 from the fp64 product with one chain, 8.7e-8 with two; in four ranges with one 9.8e-8).
+  constexpr bool HALVES = PIECES > 1 && TILE == 64;
+  f32x4_t first[HALVES ? NI : 1][HALVES ? NI : 1];
+#pragma unroll
+  for (int i = 0; i < (HALVES ? NI : 1); ++i)
+#pragma unroll
+    for (int j = 0; j < (HALVES ? NI : 1); ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) first[i][j][v] = 0.f;
+  const int k_mid = k_begin + ((k_end - k_begin) / (2 * BK)) * BK;
+
   Stager<DT, TILE, KCA> sa;
   Stager<DT, TILE, KCB> sb;
   sa.init(A, a.lda, tile_r0, a.n, k_end);
@@ -367,6 +378,16 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_tile(GemmArgs a, GemmSide sid
     sb.store(Bs);
     __syncthreads();
     if (k0 + BK < k_end) { sa.load(k0 + BK); sb.load(k0 + BK); }
+    if constexpr (HALVES) {
+      if (k0 == k_mid) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+          for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) { first[i][j][v] = acc[i][j][v]; acc[i][j][v] = 0.f; }
+      }
+    }
 #pragma unroll
     for (int ks = 0; ks < BK / 32; ++ks) {
       bf16x8_t fb[NI][PIECES];
@@ -404,7 +425,7 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_tile(GemmArgs a, GemmSide sid
 #pragma unroll
       for (int j = 0; j < NI; ++j)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) acc[i][j][v] += low[i][j][v];
+        for (int v = 0; v < 4; ++v) acc[i][j][v] = (HALVES ? acc[i][j][v] + first[HALVES ? i : 0][HALVES ? j : 0][v] : acc[i][j][v]) + low[i][j][v];
   }
   if constexpr (DT == GECC_F32) {
     if (once) {

@@ -144,7 +144,7 @@ hipError_t launch_coldot_stage1(const ScanArgs& a0, Stage2Job* pending, hipStrea
     else          hipLaunchKernelGGL((coldot_stage1<GECC_F32, false, false>), grid, dim3(CD_THREADS), 0, st, a, nchunk);
   }
   *pending = Stage2Job{};
-  if (!a.done) {
+  if (!a.done && nchunk > 1) {
     pending->valid = true;
     pending->scratch = a.scratch; pending->out = a.out; pending->out_stride = a.out_stride;
     pending->Cc = a.Cc; pending->nchunk = nchunk; pending->batch = a.batch;
@@ -266,7 +266,7 @@ bool make_side_job(const ScanArgs& s, bool rowdot, uint32_t* done, int words_lef
   if (rowdot) {
     // (no wavefront-per-rows scan of bf16 rows: its registers would halve the product's occupancy)
     const bool wavewise = s.dtype == GECC_F32 && rowdot_wavewise(s);
-    const int rb = wavewise ? 4 * RW_RB : RD_SMALL_RB;
+    const int rb = wavewise ? 4 * RW_RB : s.dtype == GECC_F32 ? side_rows<GECC_F32>() : side_rows<GECC_BF16>();
     j.kind = wavewise ? SIDE_ROW_WAVE : SIDE_ROW;
     j.gx = (s.R + rb - 1) / rb; j.gy = 1;
   } else {
