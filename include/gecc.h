@@ -326,7 +326,9 @@ enum {
   GECC_K_TILE_A = 12,   /* A_P and P_r in one pass over A                */
   GECC_K_TILE_B = 13,   /* B_P and P_c in one pass over B                */
   GECC_K_AUDIT_AB = 14, /* both gated re-encodings in one launch (with GECC_K_DECODE) */
-  GECC_K_COUNT = 15
+  GECC_K_ENCODE_AB = 15, /* A_P and B_P in one launch                    */
+  GECC_K_PARITY_RC = 16, /* P_r and P_c in one launch                    */
+  GECC_K_COUNT = 17
 };
 int gecc_timing_enable(gecc_ctx* ctx, int32_t max_records, uint32_t kinds_mask);
 int gecc_timing_read(gecc_ctx* ctx, float* host_ms, int32_t* host_kind, int32_t cap, int32_t* count);

@@ -76,13 +76,13 @@ constexpr int TH_SLICES = 4;    // wavefronts of a workgroup; each adds every 4t
 // (more than there are would only read the last one again: 256 x 512^3, four sub-tiles, 26 us with 32 of
 // them, 9 with 4).  The sums do not depend on it.
 template <int TH_MAXLOADS>
-__global__ __launch_bounds__(64 * TH_SLICES) void threshold_kernel(DecodeArgs a) {
+__global__ __launch_bounds__(64 * TH_SLICES) void threshold_kernel(DecodeArgs a, Parts pr, Parts pc) {
   const int b = blockIdx.y;
   DecodeState* st = state_of(a, b);
   const int n = a.p.n, m = a.p.m;
   const int lane = threadIdx.x & 63, slice = threadIdx.x >> 6;
   const int o = blockIdx.x * 64 + lane;          // line: rows first, then columns
-  const double* cpar = cpar_of(a, b);
+  double* cpar = cpar_of(a, b);
   double* synd = synd_of(a, b);
   const bool is_row = o < n, valid = o < n + m;
   const bool wt = a.p.weighted != 0;     // single-checksum mode: the weighted sums are not read
@@ -114,10 +114,35 @@ __global__ __launch_bounds__(64 * TH_SLICES) void threshold_kernel(DecodeArgs a)
   __shared__ double red[2][TH_SLICES][64];
   red[0][slice][lane] = S;
   red[1][slice][lane] = W;
+  // What the scans have left of this line's two parity symbols.  Chunks: a wavefront's slice is the second stage's own;
+  // segments: one wavefront per kind.  (A second stage in a launch of its own costs 5 us for the same loads.)
+  const Parts parts = {is_row ? pr.chunks : pc.chunks, is_row ? pr.segs : pc.segs, is_row ? pr.nchunk : pc.nchunk, is_row ? pr.nseg : pc.nseg};
+  const bool in_parts = parts.nchunk > 0 || parts.nseg > 0;
+  __shared__ double par[2][TH_SLICES][64];
+  if (valid && in_parts) {
+    const int len = is_row ? n : m, i = is_row ? o : o - n;
+    if (parts.nchunk > 0) {
+      const double* p0 = parts.chunks + (int64_t)b * parts.nchunk * 2 * len + i;
+      const double* p[2] = {p0, p0 + len};
+      double s[2];
+      static_assert(TH_SLICES == 4, "slices of a column scan's second stage");
+      slice_sums<2, false>(p, 2 * (int64_t)len, parts.nchunk, slice, s);
+      par[0][slice][lane] = s[0];
+      par[1][slice][lane] = s[1];
+    } else if (slice < 2) {
+      par[slice][0][lane] = parts_sum(parts, b, len, slice, i);
+    }
+  }
   __syncthreads();
   if (slice != 0) return;
   double v1 = 0.0, v2 = 0.0;
   if (valid) {
+    if (in_parts) {
+      const int at = is_row ? o : 2 * n + (o - n), step = is_row ? n : m;
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+        cpar[at + t * step] = parts.nchunk > 0 ? (par[t][0][lane] + par[t][1][lane]) + (par[t][2][lane] + par[t][3][lane]) : par[t][0][lane];
+    }
     S = (red[0][0][lane] + red[0][1][lane]) + (red[0][2][lane] + red[0][3][lane]);
     W = (red[1][0][lane] + red[1][1][lane]) + (red[1][2][lane] + red[1][3][lane]);
     if (is_row) {
@@ -1155,12 +1180,12 @@ hipError_t launch_reset_state(const DecodeArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_threshold(const DecodeArgs& a, hipStream_t st) {
+hipError_t launch_threshold(const DecodeArgs& a, const Parts& pr, const Parts& pc, hipStream_t st) {
   dim3 grid((a.p.n + a.p.m + 63) / 64, a.p.batch);   // 64 lines per workgroup: spreads over all CUs
   const int nt = a.ntm > a.ntn ? a.ntm : a.ntn;
-  if (nt <= 4 * TH_SLICES)      hipLaunchKernelGGL(threshold_kernel<4>, grid, dim3(64 * TH_SLICES), 0, st, a);
-  else if (nt <= 8 * TH_SLICES) hipLaunchKernelGGL(threshold_kernel<8>, grid, dim3(64 * TH_SLICES), 0, st, a);
-  else                          hipLaunchKernelGGL(threshold_kernel<32>, grid, dim3(64 * TH_SLICES), 0, st, a);
+  if (nt <= 4 * TH_SLICES)      hipLaunchKernelGGL(threshold_kernel<4>, grid, dim3(64 * TH_SLICES), 0, st, a, pr, pc);
+  else if (nt <= 8 * TH_SLICES) hipLaunchKernelGGL(threshold_kernel<8>, grid, dim3(64 * TH_SLICES), 0, st, a, pr, pc);
+  else                          hipLaunchKernelGGL(threshold_kernel<32>, grid, dim3(64 * TH_SLICES), 0, st, a, pr, pc);
   return hipGetLastError();
 }
 

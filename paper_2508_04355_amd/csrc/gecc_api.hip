@@ -355,7 +355,7 @@ struct ScanQueue {
     if (!pending.valid) return hipSuccess;
     pending.valid = false;
     Timed t(c, GECC_K_STAGE2, st);
-    return t.done(launch_stage2(pending, st));
+    return t.done(launch_stage2(pending, Stage2Job{}, st));
   }
   hipError_t run(const ScanJob& j) {
     hipError_t e;
@@ -386,6 +386,28 @@ struct ScanQueue {
     return t.done(launch_tile_scan(f, &pending, st));
   }
 };
+
+// Sums that a chain of launches leaves to their readers: the operand parities A_P and B_P (read by the scans that use
+// them as weights) and the parity blocks P_r and P_c of C-bar (read by the threshold pass).
+struct Left { Parts ap, bp, pr, pc; };
+bool any(const Parts& p) { return p.nchunk > 0 || p.nseg > 0; }
+// what a second stage still has to do, in its column part and in its row part
+Parts chunks_of(const Stage2Job& j) { return j.valid && j.Cc > 0 ? Parts{j.scratch, nullptr, j.nchunk, 0} : Parts{}; }
+Parts segs_of(const Stage2Job& j) { return j.valid && j.R > 0 ? Parts{nullptr, j.row_scratch, 0, j.nseg} : Parts{}; }
+Stage2Job stage2_of(const Parts& p, double* out, int64_t out_stride, int len, int batch) {
+  Stage2Job j{};
+  j.valid = any(p);
+  j.batch = batch;
+  if (p.nchunk > 0) { j.scratch = p.chunks; j.nchunk = p.nchunk; j.out = out; j.out_stride = out_stride; j.Cc = len; }
+  else if (p.nseg > 0) { j.row_scratch = p.segs; j.nseg = p.nseg; j.row_out = out; j.row_out_stride = out_stride; j.R = len; }
+  return j;
+}
+// adds up now what p0 and p1 (A_P and B_P, or P_r and P_c) have left, in one launch
+hipError_t finish_parts(gecc_ctx* c, const Stage2Job& j0, const Stage2Job& j1, hipStream_t st) {
+  if (!j0.valid && !j1.valid) return hipSuccess;
+  Timed t(c, GECC_K_STAGE2, st);
+  return t.done(j0.valid ? launch_stage2(j0, j1, st) : launch_stage2(j1, j0, st));
+}
 
 GemmArgs gemm_args(const gecc_ctx* c, const void* A, const void* B, float* C) {
   const gecc_params& p = c->p;
@@ -646,7 +668,8 @@ bool scans_ride(const gecc_ctx* c, int64_t scans, bool both) {
 
 // The scans that ride (side) and those of them that cannot finish by themselves and go first (alone).
 struct Riders { bool on; GemmSide side; const ScanJob* alone[2]; };
-Riders plan_riders(const gecc_ctx* ctx, const GemmArgs& g, uint32_t* done, const ScanJob* pr, const ScanJob* pc) {
+// left: null, or what the operand parities have left (the riders' own chunks are then left to the threshold pass)
+Riders plan_riders(const gecc_ctx* ctx, const GemmArgs& g, uint32_t* done, const ScanJob* pr, const ScanJob* pc, const Left* left) {
   Riders r{};
   if (gemm_takes_256(g)) return r;
   // (the counters behind those of a k-split product)
@@ -657,7 +680,7 @@ Riders plan_riders(const gecc_ctx* ctx, const GemmArgs& g, uint32_t* done, const
   for (int x = 0; x < 2; ++x) {
     if (!jobs[x]) continue;
     int words = 0;
-    if (make_side_job(jobs[x]->s, jobs[x]->rowdot, done + used, SCAN_DONE_WORDS - used, r.side.j[at], words)) {
+    if (make_side_job(jobs[x]->s, left ? (x ? left->bp : left->ap) : Parts{}, jobs[x]->rowdot, left ? nullptr : done + used, SCAN_DONE_WORDS - used, r.side.j[at], words)) {
       used += words;
       ++at;
     } else {
@@ -672,9 +695,20 @@ Riders plan_riders(const gecc_ctx* ctx, const GemmArgs& g, uint32_t* done, const
   return r;
 }
 
+// Whether an operand parity in `nchunk` parts is left to its readers beside the product: a column scan reads the weights of
+// its own rows, and one workgroup adds all of them up for P_g, about 1 us a round of loads.  Up to 8 rounds beside any product,
+// 16 beside one of 2^20 symbols (bf16, finished first -> left: 300 x 6000 x 1000, 12 rounds, 51.3 -> 52.5 us, 1000 x 6000 x 300
+// 51.0 -> 55.2; 2880 x 520 x 2504, 3 of the longest, 59.9 -> 53.1, 1200 x 3000 x 1500 80.1 -> 76.7, 500 x 2000 x 4000 TT 69.4 -> 65.5).
+bool parts_beside(const gecc_ctx* c, int nchunk) {
+  const int at_once = nchunk <= 8 ? 4 : nchunk <= 16 ? 2 : 1;
+  const int64_t rounds = (2 * (int64_t)c->p.k + 256 * at_once - 1) / (256 * at_once) * (nchunk <= 16 ? 1 : 2);
+  return nchunk <= 32 && rounds <= ((int64_t)c->p.n * c->p.m >= (1 << 20) ? 16 : 8);
+}
+
 // S3: the parity blocks pr, pc of C-bar (null: formed already), the data block, the fused syndrome partial
 // sums, P_g.  The scans of the parity blocks ride in the product's launch (scans_ride) or go first, on q.
-hipError_t product(gecc_ctx* ctx, ScanQueue& q, const ScanJob* pr, const ScanJob* pc, const void* dev_A, const double* dev_A_par,
+// left: null, or what is left of A_P and B_P; what is then left of P_r and P_c is added to it.
+hipError_t product(gecc_ctx* ctx, ScanQueue& q, const ScanJob* pr, const ScanJob* pc, Left* left, const void* dev_A, const double* dev_A_par,
                    const void* dev_B, const double* dev_B_par, float* dev_C, double* dev_C_par, const gecc_fault* dev_faults,
                    int32_t n_faults, hipStream_t st) {
   const gecc_params& p = ctx->p;
@@ -691,7 +725,53 @@ hipError_t product(gecc_ctx* ctx, ScanQueue& q, const ScanJob* pr, const ScanJob
   g.pg_stride = 2 * (int64_t)p.n + 2 * (int64_t)p.m + 4;
   g.state = reinterpret_cast<DecodeState*>(ctx->ws + ctx->lay.state);
   hipError_t e;
-  const Riders r = plan_riders(ctx, g, q.done(), pr, pc);
+  Riders r = plan_riders(ctx, g, q.done(), pr, pc, left);
+  if (left) {
+    if ((e = q.flush()) != hipSuccess) return e;
+    // (a row scan, and scans in launches of their own, read their weights finished)
+    auto as_parts = [&](const Parts& w, const ScanJob* reader) { return r.on && reader && !reader->rowdot && parts_beside(ctx, w.nchunk); };
+    const int64_t k2 = 2 * (int64_t)p.k;
+    Stage2Job ja{}, jb{};
+    if (!as_parts(left->ap, pc)) { ja = stage2_of(left->ap, const_cast<double*>(dev_A_par), k2, p.k, p.batch); left->ap = Parts{}; }
+    if (!as_parts(left->bp, pr)) { jb = stage2_of(left->bp, const_cast<double*>(dev_B_par), k2, p.k, p.batch); left->bp = Parts{}; }
+    if ((e = finish_parts(ctx, ja, jb, st)) != hipSuccess) return e;
+    if (r.on) {
+      r = plan_riders(ctx, g, q.done(), pr, pc, left);
+      if (any(left->ap)) { r.side.par = left->ap; r.side.par_out = const_cast<double*>(dev_A_par); }
+      else if (any(left->bp)) { r.side.par = left->bp; r.side.par_out = const_cast<double*>(dev_B_par); }
+      int at = 0;
+      for (int x = 0; x < 2; ++x) {          // (the riders' order: P_c, P_r)
+        if (!(x ? pr : pc)) continue;
+        const SideJob& sj = r.side.j[at++];
+        if (sj.kind == SIDE_COL && sj.gy > 1) (x ? left->pr : left->pc) = Parts{sj.s.scratch, nullptr, sj.gy, 0};
+      }
+      return timed_gemm(ctx, g, &r.side, st);
+    }
+    if (pr && pc && pr->rowdot == pc->rowdot) {
+      const ScanArgs s[2] = {pr->s, pc->s};
+      const bool row[2] = {pr->rowdot, pc->rowdot};
+      Parts out[2] = {};
+      Timed t(ctx, GECC_K_PARITY_RC, st);
+      if ((e = t.done(launch_scan_pair(s, row, out, st))) != hipSuccess) return e;
+      left->pr = out[0];
+      left->pc = out[1];
+    } else if (pr && pc) {
+      // (a column scan, then a row scan that carries its second stage: in one launch they are no faster, bf16 4096^3 20.9 us and 23.8)
+      if ((e = q.run(pr->rowdot ? *pc : *pr)) != hipSuccess || (e = q.run(pr->rowdot ? *pr : *pc)) != hipSuccess || (e = q.flush()) != hipSuccess) return e;
+    } else if (pr || pc) {
+      if ((e = q.run(pr ? *pr : *pc)) != hipSuccess) return e;
+      (pr ? left->pr : left->pc) = chunks_of(q.pending);
+      q.pending = Stage2Job{};
+    }
+    // (of 64 chunks the threshold pass takes 3 us longer, a launch 5)
+    auto late = [&](const Parts& w) { return w.nchunk > 64; };
+    const Stage2Job jr = late(left->pr) ? stage2_of(left->pr, dev_C_par, g.pg_stride, p.n, p.batch) : Stage2Job{};
+    const Stage2Job jc = late(left->pc) ? stage2_of(left->pc, dev_C_par + 2 * (size_t)p.n, g.pg_stride, p.m, p.batch) : Stage2Job{};
+    if ((e = finish_parts(ctx, jr, jc, st)) != hipSuccess) return e;
+    if (jr.valid) left->pr = Parts{};
+    if (jc.valid) left->pc = Parts{};
+    return timed_gemm(ctx, g, nullptr, st);
+  }
   if (!r.on) {
     // (a column scan goes before a row scan, which can carry its second stage; two row scans: P_c first, which
     // can carry what the encoding of B left)
@@ -800,14 +880,15 @@ int gecc_multiply(gecc_ctx* ctx, const void* dev_A, const double* dev_A_par, con
   const int64_t rec = 2 * (int64_t)p.n + 2 * (int64_t)p.m + 4;
   const ScanJob pr = scan_a_over_k(ctx, dev_A, dev_B_par, dev_C_par, rec);
   const ScanJob pc = scan_b_over_k(ctx, dev_B, dev_A_par, dev_C_par + 2 * (size_t)p.n, rec);
-  return hip_rc(product(ctx, q, &pr, &pc, dev_A, dev_A_par, dev_B, dev_B_par, dev_C, dev_C_par, dev_faults, n_faults, st));
+  return hip_rc(product(ctx, q, &pr, &pc, nullptr, dev_A, dev_A_par, dev_B, dev_B_par, dev_C, dev_C_par, dev_faults, n_faults, st));
 }
 
 namespace {
 
-// S4 + S5.  summary = 0 leaves the first report to the decoder's first pass (saves a launch).
+// S4 + S5.  summary = 0 leaves the first report to the decoder's first pass (saves a launch).  left: what is
+// left of P_r and P_c, which dev_C_par then gets here.
 int verify_impl(gecc_ctx* ctx, const float* dev_C, const double* dev_C_par, gecc_report* dev_report,
-                int32_t fused, int summary, hipStream_t st) {
+                int32_t fused, int summary, const Left& left, hipStream_t st) {
   DecodeArgs d = decode_args(ctx, nullptr, nullptr, nullptr, nullptr, const_cast<float*>(dev_C),
                              const_cast<double*>(dev_C_par), dev_report);
   hipError_t e;
@@ -830,7 +911,7 @@ int verify_impl(gecc_ctx* ctx, const float* dev_C, const double* dev_C_par, gecc
   }
   {
     Timed t(ctx, GECC_K_THRESHOLD, st);
-    e = blocked(ctx) ? launch_threshold_blocked(d, ctx->p.n, ctx->p.m, st) : launch_threshold(d, st);
+    e = blocked(ctx) ? launch_threshold_blocked(d, ctx->p.n, ctx->p.m, st) : launch_threshold(d, left.pr, left.pc, st);
     if ((e = t.done(e)) != hipSuccess) return hip_rc(e);
   }
   if (!summary) return GECC_OK;
@@ -920,9 +1001,10 @@ int correct_impl(gecc_ctx* ctx, void* dev_A, const double* dev_A_par, void* dev_
 namespace {
 
 // S1-S3 as one chain of scans.  The order of the four scans depends on how the operands are stored
-// (which of them are rowdots) and on what reads what: P_r needs B_P, P_c needs A_P.
+// (which of them are rowdots) and on what reads what: P_r needs B_P, P_c needs A_P.  left: what the threshold pass
+// that follows has to add up of P_r and P_c.
 int encode_and_multiply(gecc_ctx* ctx, void* dev_A, void* dev_B, float* dev_C, double* dev_A_par,
-                        double* dev_B_par, double* dev_C_par, const gecc_fault* dev_faults, int32_t n_faults,
+                        double* dev_B_par, double* dev_C_par, const gecc_fault* dev_faults, int32_t n_faults, Left& left,
                         hipStream_t st) {
   int rc = check_multiply_args(ctx, dev_A, dev_A_par, dev_B, dev_B_par, dev_C, dev_C_par, dev_faults, n_faults);
   if (rc) return rc;
@@ -955,20 +1037,29 @@ int encode_and_multiply(gecc_ctx* ctx, void* dev_A, void* dev_B, float* dev_C, d
     const bool long_rows = po.rowdot && to.row_on && !to.col_on && po.s.R < 8192 && po.s.Cc >= 4096 && tile_scan_ok(to);
     if (long_rows && (e = q.run_tile(to, po.kind)) != hipSuccess) return hip_rc(e);
     // (P_c reads A_P, P_r reads B_P: what the tile scan left pending comes first)
-    if (!long_rows && (e = q.flush()) != hipSuccess) return hip_rc(e);
-    return hip_rc(product(ctx, q, long_rows || t_is_a ? nullptr : &pr, long_rows || !t_is_a ? nullptr : &pc, dev_A, dev_A_par,
+    if (long_rows) {
+      (t_is_a ? left.pc : left.pr) = segs_of(q.pending);
+      q.pending = Stage2Job{};
+    }
+    return hip_rc(product(ctx, q, long_rows || t_is_a ? nullptr : &pr, long_rows || !t_is_a ? nullptr : &pc, &left, dev_A, dev_A_par,
                           dev_B, dev_B_par, dev_C, dev_C_par, dev_faults, n_faults, st));
   }
-  if (p.trans_a && !p.trans_b && !plan_riders(ctx, gemm_args(ctx, dev_A, dev_B, dev_C), q.done(), &pr, &pc).on) {
-    // both encodings are row scans, both parity blocks column scans: in turn, so that A_P carries P_r's second stage
-    if ((e = q.run(eb)) != hipSuccess || (e = q.run(pr)) != hipSuccess || (e = q.run(ea)) != hipSuccess) return hip_rc(e);
-    return hip_rc(product(ctx, q, nullptr, &pc, dev_A, dev_A_par, dev_B, dev_B_par, dev_C, dev_C_par, dev_faults, n_faults, st));
+  // The two encodings in one launch.  Where the sums of a column scan have to be finished before they are read, it and then
+  // a row scan that carries its second stage are no slower (bf16 4096^3 16.6 us, in one launch 14.3 and the second stage 4.8).
+  const ScanJob& col = ea.rowdot ? eb : ea;
+  if (ea.rowdot != eb.rowdot && !(parts_beside(ctx, (col.s.R + SCAN_CHUNK_ROWS - 1) / SCAN_CHUNK_ROWS) &&
+                                  plan_riders(ctx, gemm_args(ctx, dev_A, dev_B, dev_C), q.done(), &pr, &pc, &left).on)) {
+    if ((e = q.run(ea.rowdot ? eb : ea)) != hipSuccess || (e = q.run(ea.rowdot ? ea : eb)) != hipSuccess) return hip_rc(e);
+  } else {
+    const ScanArgs s[2] = {ea.s, eb.s};
+    const bool row[2] = {ea.rowdot, eb.rowdot};
+    Parts out[2] = {};
+    Timed t(ctx, GECC_K_ENCODE_AB, st);
+    if ((e = t.done(launch_scan_pair(s, row, out, st))) != hipSuccess) return hip_rc(e);
+    left.ap = out[0];
+    left.bp = out[1];
   }
-  // the two encodings; a column scan goes before a row scan, which can carry its second stage
-  const bool b_first = ea.rowdot && !eb.rowdot;
-  if ((e = q.run(b_first ? eb : ea)) != hipSuccess) return hip_rc(e);
-  if ((e = q.run(b_first ? ea : eb)) != hipSuccess) return hip_rc(e);
-  return hip_rc(product(ctx, q, &pr, &pc, dev_A, dev_A_par, dev_B, dev_B_par, dev_C, dev_C_par, dev_faults, n_faults, st));
+  return hip_rc(product(ctx, q, &pr, &pc, &left, dev_A, dev_A_par, dev_B, dev_B_par, dev_C, dev_C_par, dev_faults, n_faults, st));
 }
 
 }  // namespace
@@ -978,7 +1069,7 @@ int gecc_verify(gecc_ctx* ctx, const float* dev_C, const double* dev_C_par, gecc
   int rc = check_ws(ctx);
   if (rc) return rc;
   if (!dev_C_par || !dev_report || (!fused && !dev_C)) return GECC_ERR_ARG;
-  return verify_impl(ctx, dev_C, dev_C_par, dev_report, fused, 1, (hipStream_t)stream);
+  return verify_impl(ctx, dev_C, dev_C_par, dev_report, fused, 1, Left{}, (hipStream_t)stream);
 }
 
 int gecc_correct(gecc_ctx* ctx, void* dev_A, const double* dev_A_par, void* dev_B,
@@ -997,10 +1088,11 @@ int gecc_protected_gemm(gecc_ctx* ctx, void* dev_A, void* dev_B, float* dev_C, d
                         double* dev_B_par, double* dev_C_par, gecc_report* dev_report, void* stream) {
   int rc;
   if (!dev_report) return GECC_ERR_ARG;
-  if ((rc = encode_and_multiply(ctx, dev_A, dev_B, dev_C, dev_A_par, dev_B_par, dev_C_par, nullptr, 0,
+  Left left{};
+  if ((rc = encode_and_multiply(ctx, dev_A, dev_B, dev_C, dev_A_par, dev_B_par, dev_C_par, nullptr, 0, left,
                                 (hipStream_t)stream)))
     return rc;
-  if ((rc = verify_impl(ctx, dev_C, dev_C_par, dev_report, 1, 0, (hipStream_t)stream))) return rc;
+  if ((rc = verify_impl(ctx, dev_C, dev_C_par, dev_report, 1, 0, left, (hipStream_t)stream))) return rc;
   return correct_impl(ctx, dev_A, dev_A_par, dev_B, dev_B_par, dev_C, dev_C_par, dev_report, 1,
                       (hipStream_t)stream);
 }
@@ -1014,13 +1106,14 @@ int gecc_protected_gemm_retry(gecc_ctx* ctx, void* dev_A, void* dev_B, float* de
   if (attempts) *attempts = 0;
   for (int32_t a = 0; a <= max_retries; ++a) {
     // the planted faults are transient: they strike the first product only
+    Left left{};
     if (a == 0)
-      rc = encode_and_multiply(ctx, dev_A, dev_B, dev_C, dev_A_par, dev_B_par, dev_C_par, dev_faults, n_faults,
+      rc = encode_and_multiply(ctx, dev_A, dev_B, dev_C, dev_A_par, dev_B_par, dev_C_par, dev_faults, n_faults, left,
                                (hipStream_t)stream);
     else
       rc = gecc_multiply(ctx, dev_A, dev_A_par, dev_B, dev_B_par, dev_C, dev_C_par, nullptr, 0, stream);
     if (rc) return rc;
-    if ((rc = verify_impl(ctx, dev_C, dev_C_par, dev_report, 1, 0, (hipStream_t)stream))) return rc;
+    if ((rc = verify_impl(ctx, dev_C, dev_C_par, dev_report, 1, 0, left, (hipStream_t)stream))) return rc;
     if ((rc = correct_impl(ctx, dev_A, dev_A_par, dev_B, dev_B_par, dev_C, dev_C_par, dev_report, 1,
                            (hipStream_t)stream)))
       return rc;
@@ -1162,8 +1255,9 @@ int gecc_protected_gemm_panels(gecc_ctx* ctx, void* dev_A, void* dev_B, float* d
     double* Bpg = dev_B_par + 2 * k0;
     double* Cpg = dev_C_par + g * rec;
     c->fault_bias = g;
-    rc = encode_and_multiply(c, Ag, Bg, Cg, Apg, Bpg, Cpg, dev_faults, n_faults, st);
-    if (!rc) rc = verify_impl(c, Cg, Cpg, dev_report + g, 1, 0, st);
+    Left left{};
+    rc = encode_and_multiply(c, Ag, Bg, Cg, Apg, Bpg, Cpg, dev_faults, n_faults, left, st);
+    if (!rc) rc = verify_impl(c, Cg, Cpg, dev_report + g, 1, 0, left, st);
     if (!rc) rc = correct_impl(c, Ag, Apg, Bg, Bpg, Cg, Cpg, dev_report + g, 1, st);
     if (!rc && g > 0) rc = hip_rc(launch_accumulate(dev_C, dev_C_partial, p.n, p.m, p.ldc, st));
     ctx->ev_n = c->ev_n;

@@ -118,6 +118,13 @@ struct Stage2Job {
   int64_t gate_stride;
   int gate_value;
 };
+// What the first stage of a reduction has left, where the kernel that reads the sums adds it up itself: partial sums
+// of `len` outputs of two kinds, in chunks or in segments (neither: nothing is left).
+struct Parts {
+  const double* chunks;       // [batch][nchunk][2][len], added in the order of a column scan's second stage
+  const double* segs;         // [batch][len][nseg][2], added in order
+  int nchunk, nseg;
+};
 struct ScanArgs {
   const void* X;
   int dtype;
@@ -145,7 +152,8 @@ hipError_t launch_rowdot(const ScanArgs& a, const Stage2Job* carry, hipStream_t 
 hipError_t launch_coldot_stage1(const ScanArgs& a, Stage2Job* pending, hipStream_t st);
 // counters a column scan needs to finish by itself; 0: it cannot (too many chunks per segment)
 int coldot_done_words(const ScanArgs& a);
-hipError_t launch_stage2(const Stage2Job& j, hipStream_t st);
+// two of them (the same batch, not gated) in one launch; j1 may have valid = false
+hipError_t launch_stage2(const Stage2Job& j0, const Stage2Job& j1, hipStream_t st);
 int stage2_blocks(const Stage2Job& j);
 // words[0 .. count) = 0 (a kernel, so that a captured call stays free of memset nodes)
 hipError_t launch_zero_words(uint32_t* words, int count, hipStream_t st);
@@ -266,22 +274,29 @@ struct GemmArgs {
 // Scans that ride in the launch of gemm_tile, as workgroups of their own before the product's:
 // the parity blocks P_r and P_c of C-bar (vector weights; a column scan is finished by its last
 // workgroup) and P_g.  Nothing in the launch reads what they form.
-enum : int { SIDE_NONE = 0, SIDE_ROW = 1, SIDE_ROW_WAVE = 2, SIDE_COL = 3 };
+enum : int { SIDE_NONE = 0, SIDE_ROW = 1, SIDE_ROW_WAVE = 2, SIDE_COL = 3, SIDE_ROW_BIG = 4 };
 struct SideJob {
   int kind;            // SIDE_x
   ScanArgs s;
+  Parts w;             // SIDE_COL beside the product: what its weights s.w are still to be added up from
   int gx, gy;          // workgroups per batch item: gx (row scan) or gx segments x gy chunks
   int nblk;
 };
 struct GemmSide {
   SideJob j[2];
+  Parts par;           // an operand parity that is still in parts: finished into par_out ([batch][2][k]) by P_g's workgroups
+  double* par_out;
   int pg_items;        // batch items whose P_g is to be formed (set by the launcher)
   int blocks;          // workgroups of the side jobs in all (set by the launcher)
   int groups;          // the same in groups of 8, one per XCD
   int own;             // workgroups of the product
 };
 // describes the scan as a side job; words: counters of `done` it uses.  false: it cannot finish by itself
-bool make_side_job(const ScanArgs& s, bool rowdot, uint32_t* done, int words_left, SideJob& j, int& words);
+// done null: its chunks are left to the threshold pass
+bool make_side_job(const ScanArgs& s, const Parts& w, bool rowdot, uint32_t* done, int words_left, SideJob& j, int& words);
+// Two scans that do not read each other's results in one launch (both with index weights or both with explicit ones, no
+// gate); left[i]: what a column scan has left to its readers
+hipError_t launch_scan_pair(const ScanArgs* s, const bool* rowdot, Parts* left, hipStream_t st);
 // side: null, or the scans that ride along (gemm_tile only)
 hipError_t launch_gemm(const GemmArgs& a, const GemmSide* side, hipStream_t st);
 bool gemm_takes_256(const GemmArgs& a);      // whether launch_gemm gives the product to the 256 x 256-tile kernel
@@ -415,8 +430,9 @@ hipError_t launch_threshold_blocked(const DecodeArgs& a, int n_full, int m_full,
 // blocked mode: the repair in three launches (own block of C-bar; operands; Section V on the rest)
 hipError_t launch_repair_blocked(const DecodeArgs& a, int nbi, hipStream_t st);
 hipError_t launch_reset_state(const DecodeArgs& a, hipStream_t st);
-// partial sums -> syndromes -> threshold flags (Section V step 1) and max |syndrome| per family
-hipError_t launch_threshold(const DecodeArgs& a, hipStream_t st);
+// partial sums -> syndromes -> threshold flags (Section V step 1) and max |syndrome| per family.  pr, pc: what is left
+// to add up of the parity blocks P_r and P_c, whose sums then go into C_par here
+hipError_t launch_threshold(const DecodeArgs& a, const Parts& pr, const Parts& pc, hipStream_t st);
 // first report (s, t, maxima, CLEAN / DETECTED) from the counters of the first threshold pass
 hipError_t launch_summarize(const DecodeArgs& a, hipStream_t st);
 // Section V step 2 right after detection.  with_summary = 1: also writes the first report

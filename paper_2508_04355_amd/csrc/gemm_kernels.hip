@@ -270,7 +270,33 @@ __device__ __forceinline__ float row16_sum(float x) {
 // launches: more registers here would cost the product workgroups per compute unit
 template <int DT>
 __device__ __forceinline__ void side_job(const GemmArgs& a, const GemmSide& side, int v, double* lds) {
-  if (v < side.pg_items) { form_pg(a, v, lds); return; }
+  if (v < side.pg_items) {
+    if (side.par_out) {
+      // (one workgroup and its latencies: as many outputs at once as 32 loads in flight allow)
+      const int len = 2 * a.k, nchunk = side.par.nchunk;
+      double* out = side.par_out + (int64_t)v * len;
+      const double* from = side.par.chunks + (int64_t)v * nchunk * len;
+      auto finish = [&](auto g_, auto max_) {
+        constexpr int G = decltype(g_)::value, MAX = decltype(max_)::value;
+        for (int o0 = threadIdx.x; o0 < len; o0 += G * THREADS) {
+          const double* part[G];
+          double s[G];
+#pragma unroll
+          for (int g = 0; g < G; ++g) part[g] = from + min(o0 + g * THREADS, len - 1);
+          chunk_sums<G, MAX>(part, len, nchunk, s);
+#pragma unroll
+          for (int g = 0; g < G; ++g)
+            if (o0 + g * THREADS < len) out[o0 + g * THREADS] = s[g];
+        }
+      };
+      if (nchunk <= 8) finish(std::integral_constant<int, 4>{}, std::integral_constant<int, 8>{});
+      else if (nchunk <= 16) finish(std::integral_constant<int, 2>{}, std::integral_constant<int, 16>{});
+      else for (int o = threadIdx.x; o < len; o += THREADS) out[o] = chunk_sum(from + o, len, nchunk);
+      __syncthreads();
+    }
+    form_pg(a, v, lds);
+    return;
+  }
   v -= side.pg_items;
   const bool second = v >= side.j[0].nblk;
   if (second) v -= side.j[0].nblk;
@@ -278,7 +304,7 @@ __device__ __forceinline__ void side_job(const GemmArgs& a, const GemmSide& side
   const int per_item = j.gx * j.gy;
   const int b = v / per_item, x = (v % per_item) % j.gx, y = (v % per_item) / j.gx;
   if (j.kind == SIDE_ROW) rowdot_body<DT, false, side_rows<DT>(), 1>(j.s, x, b, lds);
-  else if (j.kind == SIDE_COL) coldot_body<DT, false, DT == GECC_F32 ? 4 : 2>(j.s, j.gy, j.gx, x, y, b, lds);
+  else if (j.kind == SIDE_COL) coldot_body<DT, false, DT == GECC_F32 ? 4 : 2, true>(j.s, j.w, j.gy, j.gx, x, y, b, lds);
   else if constexpr (DT == GECC_F32) rowdot_wave_body<DT, false>(j.s, x, b, lds);
 }
 

@@ -110,6 +110,76 @@ __device__ __forceinline__ void coldot_stage2_body(const double* scratch, double
   if (wave == 0 && o < 2 * Cc) out[o] = (red[lane] + red[64 + lane]) + (red[128 + lane] + red[192 + lane]);
 }
 
+// The whole of that sum by one thread, sixteen loads in flight
+__device__ __forceinline__ double chunk_sum(const double* part, int64_t stride, int nchunk) {
+  double t[4][4];                                  // [slice][running sum]
+#pragma unroll
+  for (int w = 0; w < 4; ++w)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) t[w][u] = 0.0;
+#pragma unroll 1
+  for (int c0 = 0; c0 < nchunk; c0 += 16) {
+    double v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = part[(int64_t)min(c0 + i, nchunk - 1) * stride];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const bool four = c0 + w + 12 < nchunk;      // (slice_sums' first loop; its second one puts what is left into the first sum)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const double x = c0 + w + 4 * u < nchunk ? v[w + 4 * u] : 0.0;
+        if (u == 0 || !four) t[w][0] += x;
+        else t[w][u] += x;
+      }
+    }
+  }
+  double s[4];
+#pragma unroll
+  for (int w = 0; w < 4; ++w) s[w] = (t[w][0] + t[w][1]) + (t[w][2] + t[w][3]);
+  return (s[0] + s[1]) + (s[2] + s[3]);
+}
+// the same for G outputs at once and at most MAX (<= 16) chunks
+template <int G, int MAX>
+__device__ __forceinline__ void chunk_sums(const double* const* part, int64_t stride, int nchunk, double* s) {
+  double v[G][MAX];
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int i = 0; i < MAX; ++i) v[g][i] = part[g][(int64_t)min(i, nchunk - 1) * stride];
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    double t[4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      double first = 0.0, other[3] = {0.0, 0.0, 0.0};
+      const bool four = MAX > 12 && w + 12 < nchunk;
+#pragma unroll
+      for (int u = 0; w + 4 * u < MAX; ++u) {
+        const double x = w + 4 * u < nchunk ? v[g][w + 4 * u] : 0.0;
+        if (u == 0 || !four) first += x;
+        else other[u - 1] += x;
+      }
+      t[w] = (first + other[0]) + (other[1] + other[2]);
+    }
+    s[g] = (t[0] + t[1]) + (t[2] + t[3]);
+  }
+}
+// Sum of kind t of output i (of len) of batch item b
+__device__ __forceinline__ double parts_sum(const Parts& p, int b, int len, int t, int i) {
+  if (p.nchunk > 0) return chunk_sum(p.chunks + (int64_t)b * p.nchunk * 2 * len + (int64_t)t * len + i, 2 * (int64_t)len, p.nchunk);
+  const double* q = p.segs + ((int64_t)b * len + i) * p.nseg * 2 + t;
+  double s = 0.0;
+#pragma unroll 1
+  for (int g0 = 0; g0 < p.nseg; g0 += 8) {
+    double v[8];
+#pragma unroll
+    for (int g = 0; g < 8; ++g) v[g] = q[2 * min(g0 + g, p.nseg - 1)];
+#pragma unroll
+    for (int g = 0; g < 8; ++g) s += g0 + g < p.nseg ? v[g] : 0.0;
+  }
+  return s;
+}
+
 // The same sums for the 2 * 64 * VEC outputs of one column segment, by the workgroup that finished
 // the segment's last chunk.  col0: first column of the segment; red: 4 * 256 doubles of LDS.
 template <int VEC>
@@ -394,16 +464,17 @@ constexpr int CD_FLAG_AT = 1024;     // (behind what coldot_finish_segment uses)
 // Column segment bx, chunk `chunk` of batch item b.  With a.done set, the workgroup that finishes a
 // segment's last chunk also adds the chunks up (no second stage to launch).
 // CD_NB: rows a wavefront loads at once (its sums do not depend on it)
+// WPARTS: explicit weights that may still be in parts (wp).  Every workgroup adds up those of its own rows, which costs less
+// than the launch that would have to come first, and keeps them in LDS.  (Not in the scans' own launches: 117 MB bf16 29 us
+// instead of 25, for the registers.)
 constexpr int CD_ROWS = 8;
-template <int DT, bool IDXW, int CD_NB>
-__device__ __forceinline__ void coldot_body(const ScanArgs& a, int nchunk, int nsegx, int bx, int chunk, int b,
-                                            double* lds) {
+template <int DT, bool IDXW, int CD_NB, bool WPARTS = false>
+__device__ __forceinline__ void coldot_body(const ScanArgs& a, const Parts& wp, int nchunk, int nsegx, int bx, int chunk,
+                                            int b, double* lds) {
   using E = Elem<DT>;
   using T = typename E::type;
   constexpr int VEC = E::VEC;
   const T* X = reinterpret_cast<const T*>(a.X) + (int64_t)b * a.xs;
-  const double* w0 = IDXW ? nullptr : a.w + (int64_t)b * a.w_stride;
-  const double* w1 = IDXW ? nullptr : w0 + a.R;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // first column of a lane's vector; the lane on which the row ends in mid-vector reads the row's last
@@ -413,6 +484,23 @@ __device__ __forceinline__ void coldot_body(const ScanArgs& a, int nchunk, int n
   const int rbeg = chunk * SCAN_CHUNK_ROWS;
   const int rend = min(a.R, rbeg + SCAN_CHUNK_ROWS);
   const bool owns = (bx * 64 + lane) * VEC < a.Cc;
+  const double* w0 = IDXW ? nullptr : a.w + (int64_t)b * a.w_stride;
+  const double* w1 = IDXW ? nullptr : w0 + a.R;
+  const double2* wl = reinterpret_cast<const double2*>(lds);      // weights of the chunk's rows
+  if constexpr (WPARTS) {
+    const int t = tid / SCAN_CHUNK_ROWS, row = rbeg + tid % SCAN_CHUNK_ROWS;
+    static_assert(CD_THREADS == 2 * SCAN_CHUNK_ROWS, "a thread per weight");
+    if (row < rend) {
+      const bool parts = wp.nchunk > 0 || wp.nseg > 0;
+      lds[2 * (row - rbeg) + t] = parts ? parts_sum(wp, b, a.R, t, row) : (t ? w1 : w0)[row];
+    }
+    __syncthreads();
+  }
+  auto weights = [&](int row, double& wa, double& wb) {
+    if (IDXW) { wa = 1.0; wb = (double)(row + 1); }
+    else if (WPARTS) { const double2 w = wl[row - rbeg]; wa = w.x; wb = w.y; }
+    else { wa = w0[row]; wb = w1[row]; }
+  };
 
   double acc0[VEC], acc1[VEC];
 #pragma unroll
@@ -433,9 +521,8 @@ __device__ __forceinline__ void coldot_body(const ScanArgs& a, int nchunk, int n
       for (int u = 0; u < CD_NB; ++u) {
         double v[VEC];
         E::widen(x[u], v);
-        const int row = rr + 4 * u;
-        const double wa = IDXW ? 1.0 : w0[row];
-        const double wb = IDXW ? (double)(row + 1) : w1[row];
+        double wa, wb;
+        weights(rr + 4 * u, wa, wb);
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
           acc0[e] = IDXW ? acc0[e] + v[e] : fma(wa, v[e], acc0[e]);
@@ -462,8 +549,8 @@ __device__ __forceinline__ void coldot_body(const ScanArgs& a, int nchunk, int n
     for (; r < rend; r += 4) {
       double v[VEC];
       E::load_vec(col + (int64_t)r * a.ld, v);
-      const double wa = IDXW ? 1.0 : w0[r];
-      const double wb = IDXW ? (double)(r + 1) : w1[r];
+      double wa, wb;
+      weights(r, wa, wb);
 #pragma unroll
       for (int e = 0; e < VEC; ++e) {
         acc0[e] = IDXW ? acc0[e] + v[e] : fma(wa, v[e], acc0[e]);
@@ -472,8 +559,8 @@ __device__ __forceinline__ void coldot_body(const ScanArgs& a, int nchunk, int n
     }
   } else if (owns) {
     for (int r = rbeg + wave; r < rend; r += 4) {
-      const double wa = IDXW ? 1.0 : w0[r];
-      const double wb = IDXW ? (double)(r + 1) : w1[r];
+      double wa, wb;
+      weights(r, wa, wb);
 #pragma unroll
       for (int e = 0; e < VEC; ++e) {      // (rows shorter than a vector)
         if (e >= a.Cc) continue;
@@ -485,6 +572,7 @@ __device__ __forceinline__ void coldot_body(const ScanArgs& a, int nchunk, int n
   }
 
   double (*red)[2][VEC][64] = reinterpret_cast<double (*)[2][VEC][64]>(lds);
+  if (WPARTS) __syncthreads();     // every wavefront is done with the weights
 #pragma unroll
   for (int e = 0; e < VEC; ++e) { red[wave][0][e][lane] = acc0[e]; red[wave][1][e][lane] = acc1[e]; }
   __syncthreads();
@@ -733,7 +821,7 @@ __device__ __forceinline__ void pair_body(const PairJob& j, int x, int y, int b,
   if (j.kind == PJ_ROW) rowdot_body<DT, true, RD_SMALL_RB, RD_SMALL_U>(j.s, x, b, lds);
   else if (j.kind == PJ_ROW_BIG) rowdot_body<DT, true, RD_BIG_RB, RD_BIG_U>(j.s, x, b, lds);
   else if (j.kind == PJ_ROW_WAVE) rowdot_wave_body<DT, true>(j.s, x, b, lds);
-  else if (j.kind == PJ_COL) coldot_body<DT, true, CD_ROWS>(j.s, j.gy, j.gx, x, y, b, lds);
+  else if (j.kind == PJ_COL) coldot_body<DT, true, CD_ROWS>(j.s, Parts{}, j.gy, j.gx, x, y, b, lds);
   else if (j.kind == PJ_TILE_COL) tile_scan_body<DT, true, false, true, true>(j.t, x, y, b, lds);
   else tile_scan_body<DT, false, true, true, true>(j.t, x, y, b, lds);
 }

@@ -42,14 +42,37 @@ __global__ __launch_bounds__(CD_THREADS) void coldot_stage1(ScanArgs a, int nchu
   __shared__ double lds[CD_LDS_DOUBLES];
   const int b = blockIdx.z;
   if (GATED && gated_off(a.gate, a.gate_stride, b, a.gate_value)) return;
-  coldot_body<DT, IDXW, CD_ROWS>(a, nchunk, gridDim.x, blockIdx.x, blockIdx.y, b, lds);
+  coldot_body<DT, IDXW, CD_ROWS>(a, Parts{}, nchunk, gridDim.x, blockIdx.x, blockIdx.y, b, lds);
 }
 
-__global__ __launch_bounds__(256) void coldot_stage2(Stage2Job j) {
+// (own0: workgroups of j0, those of j1 come behind)
+__global__ __launch_bounds__(256) void coldot_stage2(Stage2Job j0, Stage2Job j1, int own0) {
   __shared__ double lds[256];
   const int b = blockIdx.y;
-  if (gated_off(j.gate, j.gate_stride, b, j.gate_value)) return;
-  stage2_dispatch(j, b, blockIdx.x, lds);
+  if (gated_off(j0.gate, j0.gate_stride, b, j0.gate_value)) return;
+  if ((int)blockIdx.x < own0) stage2_dispatch(j0, b, blockIdx.x, lds);
+  else stage2_dispatch(j1, b, (int)blockIdx.x - own0, lds);
+}
+
+// Two scans that do not read each other's results (both encodings, or both parity blocks): what each of them would
+// leave idle at its end the other one fills, and a launch that waits for the one before it costs 5 us whatever it does.
+// WAVE: one of them is a row scan with a wavefront per RW_RB rows, which takes a third more registers than the others.
+struct ScanPair { SideJob j[2]; };
+template <int DT, bool IDXW, bool WAVE>
+__global__ __launch_bounds__(256, WAVE ? 2 : 3) void scan_pair(ScanPair p) {
+  constexpr int BIG = IDXW ? RD_BIG_RB : RD_BIG_RB_W;
+  static_assert(BIG * RD_THREADS <= CD_LDS_DOUBLES, "LDS of a row scan");
+  __shared__ double lds[WAVE && RW_LDS_DOUBLES > CD_LDS_DOUBLES ? RW_LDS_DOUBLES : CD_LDS_DOUBLES];
+  int v = blockIdx.x;
+  const bool second = v >= p.j[0].nblk;
+  if (second) v -= p.j[0].nblk;
+  const SideJob& j = second ? p.j[1] : p.j[0];
+  const int per_item = j.gx * j.gy;
+  const int b = v / per_item, x = (v % per_item) % j.gx, y = (v % per_item) / j.gx;
+  if (j.kind == SIDE_COL) coldot_body<DT, IDXW, CD_ROWS>(j.s, Parts{}, j.gy, j.gx, x, y, b, lds);
+  else if (j.kind == SIDE_ROW) rowdot_body<DT, IDXW, RD_SMALL_RB, RD_SMALL_U>(j.s, x, b, lds);
+  else if (j.kind == SIDE_ROW_BIG) rowdot_body<DT, IDXW, BIG, RD_BIG_U>(j.s, x, b, lds);
+  else if constexpr (WAVE) rowdot_wave_body<DT, IDXW>(j.s, x, b, lds);
 }
 
 template <int DT, bool COL, bool ROW, bool COL_IDX, bool ROW_IDX, bool GATED>
@@ -257,9 +280,10 @@ hipError_t launch_tile_scan(const TileScanJob& t, Stage2Job* pending, hipStream_
   return hipGetLastError();
 }
 
-bool make_side_job(const ScanArgs& s, bool rowdot, uint32_t* done, int words_left, SideJob& j, int& words) {
+bool make_side_job(const ScanArgs& s, const Parts& w, bool rowdot, uint32_t* done, int words_left, SideJob& j, int& words) {
   j = SideJob{};
   j.s = s;
+  j.w = w;
   j.s.carry_blocks = 0;
   words = 0;
   if (s.gate || !s.w) return false;
@@ -270,8 +294,10 @@ bool make_side_job(const ScanArgs& s, bool rowdot, uint32_t* done, int words_lef
     j.kind = wavewise ? SIDE_ROW_WAVE : SIDE_ROW;
     j.gx = (s.R + rb - 1) / rb; j.gy = 1;
   } else {
-    words = coldot_done_words(s);
-    if (words == 0 || words > words_left) return false;
+    if (done) {
+      words = coldot_done_words(s);
+      if (words == 0 || words > words_left) return false;
+    }
     const int vec = s.dtype == GECC_BF16 ? 8 : 4;
     j.kind = SIDE_COL;
     j.s.done = done;
@@ -282,6 +308,50 @@ bool make_side_job(const ScanArgs& s, bool rowdot, uint32_t* done, int words_lef
   if (blocks > (1 << 28)) return false;
   j.nblk = (int)blocks;
   return true;
+}
+
+hipError_t launch_scan_pair(const ScanArgs* s, const bool* rowdot, Parts* left, hipStream_t st) {
+  ScanPair p{};
+  int64_t grid = 0;
+  for (int i = 0; i < 2; ++i) {
+    SideJob& j = p.j[i];
+    if (s[i].gate || s[i].dtype != s[0].dtype || (s[i].w == nullptr) != (s[0].w == nullptr)) return hipErrorInvalidValue;
+    j.s = s[i];
+    j.s.carry_blocks = 0;
+    j.s.done = nullptr;
+    left[i] = Parts{};
+    if (rowdot[i]) {
+      // (rows per workgroup as in launch_rowdot)
+      const bool wavewise = rowdot_wavewise(s[i]), small = (int64_t)((s[i].R + RD_BIG_RB - 1) / RD_BIG_RB) * s[i].batch < 1024;
+      const int rb = wavewise ? 4 * RW_RB : small ? RD_SMALL_RB : s[i].w ? RD_BIG_RB_W : RD_BIG_RB;
+      j.kind = wavewise ? SIDE_ROW_WAVE : small ? SIDE_ROW : SIDE_ROW_BIG;
+      j.gx = (s[i].R + rb - 1) / rb; j.gy = 1;
+    } else {
+      const int vec = s[i].dtype == GECC_BF16 ? 8 : 4;
+      j.kind = SIDE_COL;
+      j.gx = (s[i].Cc + 64 * vec - 1) / (64 * vec);
+      j.gy = (s[i].R + SCAN_CHUNK_ROWS - 1) / SCAN_CHUNK_ROWS;
+      if (j.gy > 1) { left[i].chunks = s[i].scratch; left[i].nchunk = j.gy; }
+    }
+    const int64_t blocks = (int64_t)j.gx * j.gy * s[i].batch;
+    grid += blocks;
+    if (grid > 0xffffff) return hipErrorInvalidValue;      // (2^32 threads)
+    j.nblk = (int)blocks;
+  }
+  const dim3 g((unsigned)grid), block(256);
+  const bool idx = s[0].w == nullptr, wave = p.j[0].kind == SIDE_ROW_WAVE || p.j[1].kind == SIDE_ROW_WAVE;
+#define GECC_LAUNCH_PAIR(DT, IDX)                                                            \
+  do {                                                                                       \
+    if (wave) hipLaunchKernelGGL((scan_pair<DT, IDX, true>), g, block, 0, st, p);            \
+    else      hipLaunchKernelGGL((scan_pair<DT, IDX, false>), g, block, 0, st, p);           \
+  } while (0)
+  if (s[0].dtype == GECC_BF16) {
+    if (idx) GECC_LAUNCH_PAIR(GECC_BF16, true); else GECC_LAUNCH_PAIR(GECC_BF16, false);
+  } else {
+    if (idx) GECC_LAUNCH_PAIR(GECC_F32, true); else GECC_LAUNCH_PAIR(GECC_F32, false);
+  }
+#undef GECC_LAUNCH_PAIR
+  return hipGetLastError();
 }
 
 // ---- the two audits as jobs of the decoder's launch -----------------------------------------------
@@ -357,9 +427,11 @@ int stage2_blocks(const Stage2Job& j) {
   return (j.Cc > 0 ? (2 * j.Cc + 63) / 64 : 0) + (j.R > 0 ? (j.R + 255) / 256 : 0);
 }
 
-hipError_t launch_stage2(const Stage2Job& j, hipStream_t st) {
-  dim3 g2(stage2_blocks(j), j.batch);
-  hipLaunchKernelGGL(coldot_stage2, g2, dim3(256), 0, st, j);
+hipError_t launch_stage2(const Stage2Job& j0, const Stage2Job& j1, hipStream_t st) {
+  if (j1.valid && (j0.gate || j1.gate || j0.batch != j1.batch)) return hipErrorInvalidValue;
+  const int own0 = stage2_blocks(j0);
+  dim3 g2(own0 + (j1.valid ? stage2_blocks(j1) : 0), j0.batch);
+  hipLaunchKernelGGL(coldot_stage2, g2, dim3(256), 0, st, j0, j1, own0);
   return hipGetLastError();
 }
 

@@ -533,6 +533,32 @@ def test_launches_of_a_clean_step(dtype, shape, trans):
     assert len(rec) <= 10, names
 
 
+@pytest.mark.parametrize("trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("dtype,shape,batch", [("f32", (128, 96, 130), 2), ("f32", (129, 200, 70), 3), ("f32", (1024, 40, 1030), 1),
+                                               ("f32", (1153, 2049, 70), 1), ("bf16", (70, 300, 2049), 1), ("bf16", (2100, 260, 2050), 1),
+                                               ("bf16", (4100, 120, 4230), 1),           # more chunks than readers add up
+                                               ("bf16", (1030, 4100, 1020), 1),          # more weights than one workgroup does
+                                               ("f32", (70, 8192, 66), 1), ("f32", (70, 8193, 66), 1),     # 64 and 65 chunks of k
+                                               ("f32", (2048, 2050, 2040), 1), ("bf16", (1664, 8320, 1536), 1)])   # scans of their own
+def test_sums_left_to_their_readers(dtype, shape, batch, trans):
+    """In the one call the second stages of the column scans are done by whoever reads their sums (the scans beside the
+    product, P_g's workgroup, the threshold pass), on both sides of every limit.  The orders of the sums are those of the
+    staged calls, where each is finished on its own: nothing differs by a bit."""
+    n, k, m = shape
+    rng = inputs.rng_for(97, n + k + m)
+    A, B = [np.stack(x) for x in zip(*[inputs.operands(rng, n, k, m, ("normal", 1.0), ("normal", 1.0), dtype) for _ in range(batch)])]
+    tau = gecc.noise_thresholds(n, k, m, 1.0, 1.0)
+    cf = [(batch - 1, n - 1, m // 2, 60.0)]
+    g1 = H.run_gpu(A, B, A, B, cf, tau, dtype, trans[0], trans[1], staged=True)
+    g2 = H.run_gpu(A, B, A, B, cf, tau, dtype, trans[0], trans[1], staged=False)
+    for name in ("A_par", "B_par", "C_par", "C", "synd"):
+        assert np.array_equal(getattr(g1, name), getattr(g2, name)), name
+    assert np.isfinite(g2.C_par).all() and (g2.C_par != 0).any()
+    for r1, r2 in zip(g1.reports, g2.reports):
+        assert (r1.status, r1.n_total, r1.errors()) == (r2.status, r2.n_total, r2.errors())
+    assert g2.reports[-1].status == gecc.CORRECTED
+
+
 # ---- per-k-panel verification: every partial product over a panel of k is a codeword ------------------
 @pytest.mark.parametrize("dtype,shape,trans,panels", [("bf16", (520, 512, 264), (0, 0), 4), ("bf16", (520, 512, 264), (0, 1), 2),
                                                       ("bf16", (264, 448, 520), (1, 0), 3), ("f32", (300, 200, 260), (0, 0), 3),
