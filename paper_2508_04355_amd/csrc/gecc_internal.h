@@ -299,6 +299,9 @@ bool make_side_job(const ScanArgs& s, const Parts& w, bool rowdot, uint32_t* don
 hipError_t launch_scan_pair(const ScanArgs* s, const bool* rowdot, Parts* left, hipStream_t st);
 // side: null, or the scans that ride along (gemm_tile only)
 hipError_t launch_gemm(const GemmArgs& a, const GemmSide* side, hipStream_t st);
+// fp32 product in 128 x 256 tiles (gemm_f32_kernels.hip): where it is the faster one, by sizes
+bool gemm_f32_wide_pays(const GemmArgs& a);
+hipError_t launch_gemm_f32_wide(const GemmArgs& a, hipStream_t st);
 bool gemm_takes_256(const GemmArgs& a);      // whether launch_gemm gives the product to the 256 x 256-tile kernel
 
 #if defined(__HIPCC__)
@@ -335,11 +338,12 @@ static __device__ __forceinline__ void reset_state(DecodeState* s) {
 // Global parity block P_g = A_P B_P (Section III, 2 x 2) of batch item b, in fp64 and in a fixed
 // order; thread 0 also resets the item's decoder state.  Called by every thread of one
 // workgroup of at most 256 threads, after its last use of the 16 doubles at `lds`.
-static __device__ __forceinline__ void form_pg(const GemmArgs& a, int b, double* lds) {
+static __device__ __forceinline__ void form_pg(const GemmArgs& a, int b, double* lds, int threads = 0) {
+  if (threads == 0) threads = blockDim.x;
   const double* ap = a.A_par + (int64_t)b * 2 * a.k;
   const double* bp = a.B_par + (int64_t)b * 2 * a.k;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int l = threadIdx.x; l < a.k; l += blockDim.x) {
+  for (int l = threadIdx.x; l < a.k; l += threads) {
     const double a0 = ap[l], a1 = ap[a.k + l], b0 = bp[l], b1 = bp[a.k + l];
     acc[0] = fma(a0, b0, acc[0]); acc[1] = fma(a0, b1, acc[1]);
     acc[2] = fma(a1, b0, acc[2]); acc[3] = fma(a1, b1, acc[3]);
@@ -348,7 +352,7 @@ static __device__ __forceinline__ void form_pg(const GemmArgs& a, int b, double*
   for (int q = 0; q < 4; ++q)
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) acc[q] += __shfl_down(acc[q], off, 64);
-  const int wave = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
+  const int wave = threadIdx.x >> 6, nw = (threads + 63) >> 6;
   __syncthreads();
   if ((threadIdx.x & 63) == 0)
 #pragma unroll

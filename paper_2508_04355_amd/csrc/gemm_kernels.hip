@@ -33,27 +33,10 @@
 // closer than either on any operands (2.5e-8 for all three; normal ones, k = 32: 2.5e-8 against 3.9e-8 through pieces).
 // Bound there by the fp64 rate or by C's stores: 8192 x k x 8192 through fp64 and through pieces, k = 1 70 against
 // 80 us, k = 8 87 against 89, k = 32 111 against 78.
-#include "scan_device.h"
+#include "gemm_device.h"
 
 namespace gecc {
 namespace {
-
-typedef __attribute__((ext_vector_type(2))) float f32x2_t;
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-typedef __attribute__((ext_vector_type(4))) double f64x4_t;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
-
-constexpr int THREADS = 256;
-constexpr float TINY = 0x1p-110f;
-
-// smallest magnitude of the nonzero values seen, as an integer that has their order (zero: the largest one)
-struct Least {
-  uint32_t v = 0xffffffffu;
-  static __device__ __forceinline__ uint32_t of(float x) { return (__float_as_uint(x) << 1) - 1u; }
-  __device__ __forceinline__ void see(float x0, float x1) { v = min(min(v, of(x0)), of(x1)); }
-  __device__ __forceinline__ bool tiny() const { return v < of(TINY); }
-};
 
 template <int DT> struct GT;
 template <> struct GT<GECC_BF16> {
@@ -66,24 +49,6 @@ template <> struct GT<GECC_F32> {
   static constexpr int PIECES = 3;
   static constexpr int BK = 32;
 };
-
-// LDS of one operand: PIECES planes of tile[row][BK] bf16; the 16-byte chunks of a row are XOR-swizzled so
-// that neither the 16 rows a fragment read touches nor the 16 rows a transposed store writes meet in a bank
-template <int BK> __device__ __forceinline__ int lds_at(int row, int chunk) {
-  constexpr int ROWB = BK * 2;
-  return row * ROWB + ((chunk ^ ((row / (256 / ROWB)) & (BK / 8 - 1))) << 4);
-}
-
-// two neighbouring k-values of a row -> their PIECES packed pairs
-__device__ __forceinline__ void split2(float x0, float x1, uint32_t (&p)[3]) {
-#pragma unroll
-  for (int q = 0; q < 3; ++q) {
-    const f32x2_t x = {x0, x1};
-    p[q] = __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2_t));   // round to nearest even
-    x0 -= __uint_as_float(p[q] << 16);
-    x1 -= __uint_as_float(p[q] & 0xffff0000u);
-  }
-}
 
 // ---- staging of one operand tile: ROWS (m- or n-index) x BK ------------------------------------
 // KC: element (r, kk) lives at P[r * ld + kk]; otherwise at P[kk * ld + r].  Rows past the last one are
@@ -256,15 +221,6 @@ struct Stager<GECC_BF16, ROWS, false> {
     }
   }
 };
-
-// sum over the 16 lanes of a row of lanes, in every one of them
-__device__ __forceinline__ float row16_sum(float x) {
-  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x128, 0xf, 0xf, false));   // row_ror:8
-  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x124, 0xf, 0xf, false));   // row_ror:4
-  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x122, 0xf, 0xf, false));   // row_ror:2
-  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x121, 0xf, 0xf, false));   // row_ror:1
-  return x;
-}
 
 // workgroup v of the scans that ride along (see GemmSide).  Fewer rows in flight than in the scans' own
 // launches: more registers here would cost the product workgroups per compute unit
@@ -817,7 +773,8 @@ hipError_t launch_gemm(const GemmArgs& a, const GemmSide* side, hipStream_t st) 
   if (a.tile_m != a.tile_n || (a.tile_m != 128 && a.tile_m != 64)) return hipErrorInvalidValue;
   if (gemm_takes_256(a)) return side ? hipErrorInvalidValue : launch_gemm_bf16_fast(a, st);
   if (a.tile_m == 64) return a.dtype == GECC_BF16 ? launch_tile<GECC_BF16, 64>(a, side, st) : launch_tile<GECC_F32, 64>(a, side, st);
-  return a.dtype == GECC_BF16 ? launch_tile<GECC_BF16, 128>(a, side, st) : launch_tile<GECC_F32, 128>(a, side, st);
+  if (a.dtype == GECC_BF16) return launch_tile<GECC_BF16, 128>(a, side, st);
+  return !side && gemm_f32_wide_pays(a) ? launch_gemm_f32_wide(a, st) : launch_tile<GECC_F32, 128>(a, side, st);
 }
 
 namespace {

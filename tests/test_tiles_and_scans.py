@@ -60,6 +60,41 @@ def test_tiles_layouts_and_tails(shape, batch, dtype, trans):
     _check(_product(A, B, dtype, trans, pad=3, shift=1), A, B)       # rows that start at any element
 
 
+@pytest.mark.parametrize("trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("shape", [(128, 128, 256), (127, 129, 249), (100, 160, 200), (1, 191, 129), (120, 257, 250)])
+def test_fp32_tiles_of_128_by_256(shape, trans):
+    """A round of products that fill one such tile each: every remainder of the k loop (three k-tiles in flight), rows and
+    columns past the end, operands the pieces cannot hold, faults in either half of the tile."""
+    import torch
+    import gpu_harness as H
+    n, k, m = shape
+    batch = 250
+    rng = inputs.rng_for(81, n + k)
+    A, B = rng.standard_normal((batch, n, k)).astype(np.float32), rng.standard_normal((batch, k, m)).astype(np.float32)
+    A[7, :, 3] *= np.float32(2.0 ** -120)
+    B[7, 3, :] *= np.float32(2.0 ** 120)
+    _check(_product(A, B, "f32", trans), A, B)
+    _check(_product(A, B, "f32", trans, pad=3, shift=1), A, B)
+    A[7, :, 3] *= np.float32(2.0 ** 120)
+    B[7, 3, :] *= np.float32(2.0 ** -120)
+    ctx = gecc.Context(n, k, m, gecc.F32, gecc.noise_thresholds(n, k, m, 1.0, 1.0), batch=batch, trans_a=trans[0], trans_b=trans[1])
+    dA, dB, C = H.to_dev(A, "f32", trans[0]), H.to_dev(B, "f32", trans[1]), ctx.alloc_c()
+    A_par, B_par, C_par = ctx.alloc_parities()
+    rep = ctx.alloc_report()
+    planted = {5: (n - 1, m - 1, 40.0), 11: (0, min(m - 1, 130), -25.0), 249: (n // 2, 3, 60.0)}
+    ctx.encode_a(dA, A_par)
+    ctx.encode_b(dB, B_par)
+    ctx.multiply(dA, A_par, dB, B_par, C, C_par, *gecc.make_faults([(b,) + f for b, f in planted.items()]))
+    ctx.verify(C, C_par, rep, fused=True)
+    ctx.correct(dA, A_par, dB, B_par, C, C_par, rep)
+    torch.cuda.synchronize()
+    _check(C.cpu().numpy().astype(np.float64).reshape(batch, n, m), A, B)
+    for b, r in enumerate(ctx.report_to_host(rep)):
+        assert r.status == (gecc.CORRECTED if b in planted else gecc.CLEAN), (b, r.status)
+        if b in planted:
+            assert [e[:3] for e in r.errors()] == [(2,) + planted[b][:2]]
+
+
 def test_values_the_bf16_pieces_cannot_hold():
     """Infinities, NaN, magnitudes beyond the largest bf16 and values below 2^-110 go through native fp32
     arithmetic: the same result as a chain of fp32 multiplications and additions would have."""
