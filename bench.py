@@ -296,7 +296,10 @@ def main():
     peak = PEAK_TFLOPS[w.dtype]
     # aligned bf16 operands and a 256 x 256 tile for more than half of the compute units: never gemm_tile
     tiles256 = -(-n // 256) * -(-m // 256) * batch
-    product_kernel = "gemm_tile" if w.dtype == "f32" else "gemm_bf16_256" if tiles256 > 128 and k % 64 == 0 else "product kernel"
+    # fp32: whole rounds of 128 x 256 tiles (the rule of gemm_f32_wide_pays)
+    wide = -(-n // 128) * -(-m // 256) * batch
+    f32_wide = k >= 128 and -(-wide // 256) * 471 < -(-n // 128) * -(-m // 128) * batch
+    product_kernel = ("gemm_f32_wide" if f32_wide else "gemm_tile") if w.dtype == "f32" else "gemm_bf16_256" if tiles256 > 128 and k % 64 == 0 else "product kernel"
     out = {
         "metric": "protected_gemm_tflops", "value": round(value, 3), "unit": "TFLOP/s", "n_gpus": 1,
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(ms_step, 4),
