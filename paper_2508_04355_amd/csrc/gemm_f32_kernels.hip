@@ -1,6 +1,6 @@
 // Large fp32 products: tiles of 128 x 256, 8 wavefronts (2 x 4), one workgroup per compute unit, two k-tiles in LDS; the
-// arithmetic of gemm_kernels.hip (three bf16 pieces per value, six products; a tile whose operands the pieces cannot hold
-// again with native fp32 MFMAs) in the same order, so that the results are the same to the bit.
+// arithmetic of gemm_kernels.hip (three bf16 pieces per value, six products; 128 x 128 symbols whose operands the pieces
+// cannot hold again with native fp32 MFMAs) in the same order, so that the results are the same to the bit.
 #include "gemm_device.h"
 
 namespace gecc {
@@ -74,6 +74,15 @@ struct WideStager<ROWS, true> {
     for (int i = 0; i < N; ++i) store_chunk(S, i);
   }
   __device__ __forceinline__ bool tiny() const { return least.tiny(); }
+  // the loaded values, each 128 rows into a minimum of their own
+  __device__ __forceinline__ void see(Least* of) const {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      static_assert(TILE % RSTEP == 0, "rows of one load in one half");
+      of[RSTEP * i / TILE].see(__uint_as_float(reg[i].x), __uint_as_float(reg[i].y));
+      of[RSTEP * i / TILE].see(__uint_as_float(reg[i].z), __uint_as_float(reg[i].w));
+    }
+  }
   // the fp32 values as they are, rows of BK + 1 floats (native fp32 pass)
   __device__ __forceinline__ void store_plain(float* S) const {
 #pragma unroll
@@ -132,6 +141,14 @@ struct WideStager<ROWS, false> {
     for (int c = 0; c < CHUNKS; ++c) store_chunk(S, c);
   }
   __device__ __forceinline__ bool tiny() const { return least.tiny(); }
+  __device__ __forceinline__ void see(Least* of) const {
+#pragma unroll
+    for (int h = 0; h < ROWS / TILE; ++h)
+      if (row / TILE == h) {
+#pragma unroll
+        for (int x = 0; x < KPT; x += 2) of[h].see(reg[x], reg[x + 1]);
+      }
+  }
   __device__ __forceinline__ void store_plain(float* S) const {
 #pragma unroll
     for (int x = 0; x < KPT; ++x) S[row * (BK + 1) + kg + x] = reg[x];
@@ -294,7 +311,10 @@ __global__ __launch_bounds__(NT, 2) void gemm_f32_wide(GemmArgs a, int pg_groups
 #pragma unroll
       for (int v = 0; v < 4; ++v) worst = fmaf(acc[i][j][v], 0.f, worst);
   if (__syncthreads_or((worst != 0.f || sa.tiny() || sb.tiny()))) {
-    // native fp32 pass (see the head of this file)
+    // Native fp32 pass (see the head of gemm_kernels.hip).  Each half of 128 columns takes its sums only where that half
+    // needs them and else keeps what its pieces gave, as in a tile of its own; which half a tiny value lies in is seen here
+    // (a second minimum in the k loop is a register, and there is none left).
+    Least least_a, least_b[TILE_N / TILE];
     float* Ap = reinterpret_cast<float*>(smem);
     float* Bp = Ap + TILE * (BK + 1);
 #pragma unroll
@@ -302,10 +322,12 @@ __global__ __launch_bounds__(NT, 2) void gemm_f32_wide(GemmArgs a, int pg_groups
 #pragma unroll
       for (int j = 0; j < NI; ++j)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
+        for (int v = 0; v < 4; ++v) low[i][j][v] = 0.f;
     for (int k0 = 0; k0 < a.k; k0 += BK) {
       sa.load(k0);
       sb.load(k0);
+      sa.see(&least_a);
+      sb.see(least_b);
       __syncthreads();
       sa.store_plain(Ap);
       sb.store_plain(Bp);
@@ -319,18 +341,24 @@ __global__ __launch_bounds__(NT, 2) void gemm_f32_wide(GemmArgs a, int pg_groups
         for (int i = 0; i < NI; ++i) {
           const float fa = Ap[(wr * W + i * 16 + l16) * (BK + 1) + ks + lg];
 #pragma unroll
-          for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa, fb[j], acc[i][j], 0, 0, 0);
+          for (int j = 0; j < NI; ++j) low[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa, fb[j], low[i][j], 0, 0, 0);
         }
       }
     }
-    if (tile_r0 + TILE > a.n || tile_c0 + TILE_N > a.m) {
 #pragma unroll
-      for (int i = 0; i < NI; ++i)
+    for (int h = 0; h < TILE_N / TILE; ++h) {
+      const bool mine = wc * W / TILE == h;
+      if (__syncthreads_or((mine && worst != 0.f) || least_a.tiny() || least_b[h].tiny()) && mine) {
 #pragma unroll
-        for (int j = 0; j < NI; ++j)
+        for (int i = 0; i < NI; ++i)
 #pragma unroll
-          for (int v = 0; v < 4; ++v)
-            if (tile_r0 + wr * W + i * 16 + lg * 4 + v >= a.n || tile_c0 + wc * W + j * 16 + l16 >= a.m) acc[i][j][v] = 0.f;
+          for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              const bool in = tile_r0 + wr * W + i * 16 + lg * 4 + v < a.n && tile_c0 + wc * W + j * 16 + l16 < a.m;
+              acc[i][j][v] = in ? low[i][j][v] : 0.f;
+            }
+      }
     }
   }
 

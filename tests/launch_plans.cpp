@@ -4,11 +4,15 @@
 //
 // Checked for every launch of gemm_tile with a split k range: its partial tiles, as the kernel that is launched
 // lays them out, lie inside the part of the workspace that is theirs.
+//
+// With the argument "routes" it reads calls from its input, "entry n k m batch dtype trans_a trans_b" a line, and prints
+// for each the result and the kernels launched.
 #include <cstdio>
 #include <cstring>
 #include <map>
 #include <random>
 #include <string>
+#include <vector>
 #include "gecc_internal.h"
 
 using namespace gecc;
@@ -20,8 +24,11 @@ static gecc_ctx* g_ctx;
 static long g_launches, g_scans, g_narrow_split, g_main_split, g_bad;
 static std::string g_case;
 
+static std::vector<std::string> g_names;      // kernels of the call, in order
+
 static void look_at(const std::string& name, void** args) {
   ++g_launches;
+  g_names.push_back(name);
   if (name.find("rowdot") != std::string::npos || name.find("coldot") != std::string::npos) ++g_scans;
   if (name.find("gemm_tile") == std::string::npos) return;
   const GemmArgs& a = *static_cast<const GemmArgs*>(args[0]);
@@ -62,7 +69,7 @@ hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipS
 }
 
 // one encoded product; `off`: elements the operands start behind a 16-byte boundary
-static void one(int n, int k, int m, int batch, int dtype, int ta, int tb, int bn, int bm, int pad, int off) {
+static int one(int n, int k, int m, int batch, int dtype, int ta, int tb, int bn, int bm, int pad, int off, const std::string& entry = "multiply") {
   gecc_params p{};
   p.n = n; p.k = k; p.m = m; p.batch = batch; p.dtype = dtype; p.trans_a = ta; p.trans_b = tb;
   p.lda = (ta ? n : k) + pad; p.ldb = (tb ? k : m) + pad; p.ldc = m + pad;
@@ -71,17 +78,36 @@ static void one(int n, int k, int m, int batch, int dtype, int ta, int tb, int b
   g_case = std::string(dtype == GECC_BF16 ? "bf16 " : "fp32 ") + std::to_string(n) + "x" + std::to_string(k) + "x" + std::to_string(m) + " batch " +
            std::to_string(batch) + " blocks " + std::to_string(bn) + "x" + std::to_string(bm) + " layout " + std::to_string(ta) + std::to_string(tb) +
            " pad " + std::to_string(pad) + " start " + std::to_string(off);
-  if (gecc_create(&g_ctx, &p) != GECC_OK) { ++g_bad; printf("BAD %s: refused\n", g_case.c_str()); return; }
+  g_names.clear();
+  if (gecc_create(&g_ctx, &p) != GECC_OK) { ++g_bad; printf("BAD %s: refused\n", g_case.c_str()); return GECC_ERR_ARG; }
   const uintptr_t at = (uintptr_t)1 << 40, esz = dtype == GECC_BF16 ? 2 : 4;
   auto dev = [&](int i, uintptr_t bytes) { return reinterpret_cast<void*>(at * (i + 1) + bytes); };
   int rc = gecc_set_workspace(g_ctx, dev(0, 0), gecc_workspace_bytes(g_ctx));
   double *ap = static_cast<double*>(dev(3, 0)), *bp = static_cast<double*>(dev(4, 0)), *cp = static_cast<double*>(dev(5, 0));
-  if (!rc) rc = gecc_multiply(g_ctx, dev(1, off * esz), ap, dev(2, off * esz), bp, static_cast<float*>(dev(6, 0)), cp, nullptr, 0, nullptr);
+  void *A = dev(1, off * esz), *B = dev(2, off * esz);
+  float* C = static_cast<float*>(dev(6, 0));
+  if (!rc && entry == "multiply") rc = gecc_multiply(g_ctx, A, ap, B, bp, C, cp, nullptr, 0, nullptr);
+  if (!rc && entry == "plain") rc = gecc_plain_gemm(g_ctx, A, B, C, nullptr);
+  if (!rc && entry == "protected") rc = gecc_protected_gemm(g_ctx, A, B, C, ap, bp, cp, static_cast<gecc_report*>(dev(7, 0)), nullptr);
   if (rc) { ++g_bad; printf("BAD %s: %s\n", g_case.c_str(), gecc_strerror(rc)); }
   gecc_destroy(g_ctx);
+  return rc;
 }
 
-int main() {
+static int routes() {
+  char entry[32];
+  int n, k, m, batch, dtype, ta, tb;
+  while (scanf("%31s %d %d %d %d %d %d %d", entry, &n, &k, &m, &batch, &dtype, &ta, &tb) == 8) {
+    const int rc = one(n, k, m, batch, dtype, ta, tb, 0, 0, 0, 0, entry);
+    printf("%d", rc);
+    for (const std::string& x : g_names) printf(" %s", x.c_str());
+    printf("\n");
+  }
+  return 0;
+}
+
+int main(int argc, char** argv) {
+  if (argc > 1 && std::string(argv[1]) == "routes") return routes();
   // (the sizes of test_narrow_products_of_blocked_mode_with_a_split_k_range first)
   one(4096, 264, 4096, 1, GECC_BF16, 0, 0, 2048, 2048, 0, 0);       // k no multiple of 64
   one(4096, 256, 4096, 1, GECC_BF16, 0, 0, 4096, 4096, 0, 0);       // a narrow product below 256 x 256 symbols

@@ -3,21 +3,46 @@ take.  Runs on the CPU: launch_plans.cpp stands in for the HIP runtime and looks
 import os
 import subprocess
 
+import pytest
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PKG = os.path.join(ROOT, "paper_2508_04355_amd")
 
 
-def test_partial_tiles_stay_in_their_part_of_the_workspace(tmp_path):
-    """Every k-split launch of gemm_tile (also where the kernel with 256 x 256 tiles was planned and refuses the operands)
-    writes no more than the workspace has for it."""
+@pytest.fixture(scope="module")
+def plans(tmp_path_factory):
     if not os.path.exists(os.path.join(PKG, "libgecc.so")):
         from paper_2508_04355_amd import build
         build.build(verbose=False)
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
-    exe = str(tmp_path / "launch_plans")
+    exe = str(tmp_path_factory.mktemp("plans") / "launch_plans")
     subprocess.run(["g++", "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(PKG, "csrc"),
                     "-I" + os.path.join(rocm, "include"), os.path.join(ROOT, "tests", "launch_plans.cpp"), "-o", exe, "-rdynamic",
                     "-L" + PKG, "-l:libgecc.so", "-Wl,-rpath," + PKG, "-L" + os.path.join(rocm, "lib"), "-lamdhip64",
                     "-Wl,-rpath," + os.path.join(rocm, "lib")], check=True)
-    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    return exe
+
+
+def routes(exe, calls):
+    """[(result, [kernel names])] of calls (entry, n, k, m, batch, dtype, trans_a, trans_b)."""
+    r = subprocess.run([exe, "routes"], input="\n".join(" ".join(str(x) for x in c) for c in calls), capture_output=True, text=True, timeout=120)
+    lines = [x.split() for x in r.stdout.splitlines() if not x.startswith("BAD")]
+    assert r.returncode == 0 and len(lines) == len(calls), r.stdout + r.stderr
+    return [(int(x[0]), x[1:]) for x in lines]
+
+
+def test_partial_tiles_stay_in_their_part_of_the_workspace(plans):
+    """Every k-split launch of gemm_tile (also where the kernel with 256 x 256 tiles was planned and refuses the operands)
+    writes no more than the workspace has for it."""
+    r = subprocess.run([plans], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_products_that_go_in_fp32_tiles_of_128_by_256(plans, ta, tb):
+    """The sizes that tests of that kernel use reach it (and the others, to which it is compared, do not)."""
+    from test_tiles_and_scans import HALVES_OTHER_BATCH, HALVES_SHAPES
+    for n, k, m in HALVES_SHAPES:
+        (_, wide), (_, other) = routes(plans, [("plain", n, k, m, 256, 0, ta, tb), ("plain", n, k, m, HALVES_OTHER_BATCH, 0, ta, tb)])
+        assert len(wide) == 1 and "gemm_f32_wide" in wide[0]
+        assert len(other) == 1 and "gemm_tile" in other[0] and "ELi128E" in other[0]

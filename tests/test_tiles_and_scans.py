@@ -95,6 +95,34 @@ def test_fp32_tiles_of_128_by_256(shape, trans):
             assert [e[:3] for e in r.errors()] == [(2,) + planted[b][:2]]
 
 
+HALVES_SHAPES = [(128, 256, 256), (120, 289, 250)]
+HALVES_OTHER_BATCH = 300      # too many for one round of 128 x 256 tiles: the same products in 128 x 128 ones
+
+
+@pytest.mark.parametrize("trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("shape", HALVES_SHAPES)
+def test_halves_of_an_fp32_tile_are_as_in_tiles_of_their_own(shape, trans):
+    """Which columns go through native fp32 (values the pieces cannot hold) does not depend on the tile: 128 x 256 and
+    128 x 128 tiles give the same bits."""
+    n, k, m = shape
+    rng = inputs.rng_for(82, n + k)
+    A = rng.standard_normal((HALVES_OTHER_BATCH, n, k)).astype(np.float32)
+    B = rng.standard_normal((HALVES_OTHER_BATCH, k, m)).astype(np.float32)
+    tiny = np.float32(2.0 ** -120)
+    B[3, 5, 200] = tiny                 # the second half
+    B[4, k - 1, 17] = -tiny             # the first
+    B[5, 0, 127] = B[5, 1, 128] = tiny  # both
+    A[6, n - 1, 4] = tiny               # a row of A: both
+    B[7, 9, m - 1] = np.float32(np.inf)
+    A[8, 3, 7] = np.float32(3.4e38)     # rounds to an infinite bf16
+    B[8, 7, 100] = np.float32(2.0)
+    B[9, 8, 40] = np.float32(np.nan)
+    wide, other = _product(A[:256], B[:256], "f32", trans), _product(A, B, "f32", trans)
+    for b in range(256):
+        assert np.array_equal(wide[b], other[b], equal_nan=True), (b, np.argwhere(wide[b] != other[b])[:4])
+    assert np.isnan(wide[9, :, 40]).all() and np.isinf(wide[7, :, m - 1]).all() and np.isfinite(wide[3:7]).all()
+
+
 def test_values_the_bf16_pieces_cannot_hold():
     """Infinities, NaN, magnitudes beyond the largest bf16 and values below 2^-110 go through native fp32
     arithmetic: the same result as a chain of fp32 multiplications and additions would have."""
