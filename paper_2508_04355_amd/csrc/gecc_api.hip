@@ -387,6 +387,13 @@ struct ScanQueue {
   }
 };
 
+// whether two scans that do not read each other's results may go in one launch
+bool may_pair(const ScanJob& x, const ScanJob& y) {
+  const ScanArgs s[2] = {x.s, y.s};
+  const bool row[2] = {x.rowdot, y.rowdot};
+  return scan_pair_fits(s, row);
+}
+
 // Sums that a chain of launches leaves to their readers: the operand parities A_P and B_P (read by the scans that use
 // them as weights) and the parity blocks P_r and P_c of C-bar (read by the threshold pass).
 struct Left { Parts ap, bp, pr, pc; };
@@ -747,7 +754,7 @@ hipError_t product(gecc_ctx* ctx, ScanQueue& q, const ScanJob* pr, const ScanJob
       }
       return timed_gemm(ctx, g, &r.side, st);
     }
-    if (pr && pc && pr->rowdot == pc->rowdot) {
+    if (pr && pc && pr->rowdot == pc->rowdot && may_pair(*pr, *pc)) {
       const ScanArgs s[2] = {pr->s, pc->s};
       const bool row[2] = {pr->rowdot, pc->rowdot};
       Parts out[2] = {};
@@ -1046,10 +1053,15 @@ int encode_and_multiply(gecc_ctx* ctx, void* dev_A, void* dev_B, float* dev_C, d
   }
   // The two encodings in one launch.  Where the sums of a column scan have to be finished before they are read, it and then
   // a row scan that carries its second stage are no slower (bf16 4096^3 16.6 us, in one launch 14.3 and the second stage 4.8).
-  const ScanJob& col = ea.rowdot ? eb : ea;
-  if (ea.rowdot != eb.rowdot && !(parts_beside(ctx, (col.s.R + SCAN_CHUNK_ROWS - 1) / SCAN_CHUNK_ROWS) &&
-                                  plan_riders(ctx, gemm_args(ctx, dev_A, dev_B, dev_C), q.done(), &pr, &pc, &left).on)) {
-    if ((e = q.run(ea.rowdot ? eb : ea)) != hipSuccess || (e = q.run(ea.rowdot ? ea : eb)) != hipSuccess) return hip_rc(e);
+  // (a column scan goes before a row scan)
+  const ScanJob& first = ea.rowdot && !eb.rowdot ? eb : ea;
+  const ScanJob& then = &first == &ea ? eb : ea;
+  auto late = [&] {
+    return parts_beside(ctx, (first.s.R + SCAN_CHUNK_ROWS - 1) / SCAN_CHUNK_ROWS) &&
+           plan_riders(ctx, gemm_args(ctx, dev_A, dev_B, dev_C), q.done(), &pr, &pc, &left).on;
+  };
+  if (!may_pair(ea, eb) || (ea.rowdot != eb.rowdot && !late())) {
+    if ((e = q.run(first)) != hipSuccess || (e = q.run(then)) != hipSuccess) return hip_rc(e);
   } else {
     const ScanArgs s[2] = {ea.s, eb.s};
     const bool row[2] = {ea.rowdot, eb.rowdot};

@@ -297,6 +297,8 @@ bool make_side_job(const ScanArgs& s, const Parts& w, bool rowdot, uint32_t* don
 // Two scans that do not read each other's results in one launch (both with index weights or both with explicit ones, no
 // gate); left[i]: what a column scan has left to its readers
 hipError_t launch_scan_pair(const ScanArgs* s, const bool* rowdot, Parts* left, hipStream_t st);
+// whether the workgroups of both, which such a launch counts in one dimension, are no more than one may have
+bool scan_pair_fits(const ScanArgs* s, const bool* rowdot);
 // side: null, or the scans that ride along (gemm_tile only)
 hipError_t launch_gemm(const GemmArgs& a, const GemmSide* side, hipStream_t st);
 // fp32 product in 128 x 256 tiles (gemm_f32_kernels.hip): where it is the faster one, by sizes

@@ -474,6 +474,15 @@ __global__ __launch_bounds__(NT, 2) void gemm_f32_wide(GemmArgs a, int pg_groups
 
 }  // namespace
 
+namespace {
+constexpr int64_t MAX_GRID = 0x7fffff;      // workgroups: 2^32 threads
+// the tiles and P_g's workgroups, both in whole groups of 8
+int64_t grid_of(const GemmArgs& a) {
+  const int64_t own = (int64_t)((a.m + TILE_N - 1) / TILE_N) * ((a.n + TILE - 1) / TILE) * a.batch;
+  return (own + 7) / 8 * 8 + (a.pg_out ? ((int64_t)a.batch + 7) / 8 * 8 : 0);
+}
+}  // namespace
+
 // Whether an fp32 product of 128 x 128 tiles goes in tiles of 128 x 256: a round of 256 of those, one per compute unit, is done
 // in 0.92 of the time of the same symbols in 512 of 128 x 128, two per compute unit, but has to be a whole one, while the smaller
 // ones fill gaps (product alone, us, 128 x 128 -> 128 x 256: 256 x 512^3 434 -> 398, TT 429 -> 380, 16 x 1024^3 197 -> 173, 64 x 500^3
@@ -484,15 +493,14 @@ bool gemm_f32_wide_pays(const GemmArgs& a) {
   const int64_t rows_a = a.trans_a ? a.k : 128, rows_b = a.trans_b ? 256 : a.k;
   if (rows_a * a.lda >= ((int64_t)1 << 30) || rows_b * a.ldb >= ((int64_t)1 << 30)) return false;
   const int64_t tm = (a.n + 127) / 128, narrow = tm * ((a.m + 127) / 128) * a.batch, wide = tm * ((a.m + 255) / 256) * a.batch;
-  return (wide + 255) / 256 * 471 < narrow;
+  return (wide + 255) / 256 * 471 < narrow && grid_of(a) <= MAX_GRID;
 }
 
 hipError_t launch_gemm_f32_wide(const GemmArgs& a, hipStream_t st) {
   const int64_t own = (int64_t)((a.m + TILE_N - 1) / TILE_N) * ((a.n + TILE - 1) / TILE) * a.batch;
   const int pg_groups = a.pg_out ? (a.batch + 7) / 8 : 0;
-  const int64_t grid_all = (own + 7) / 8 * 8 + (int64_t)pg_groups * 8;
-  if (grid_all > 0x7fffff) return hipErrorInvalidValue;      // (2^32 threads)
-  const dim3 grid((unsigned)grid_all), block(NT);
+  if (grid_of(a) > MAX_GRID) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)grid_of(a)), block(NT);
   // k-contiguous storage: A when not transposed, B when transposed
   const bool kca = a.trans_a == 0, kcb = a.trans_b != 0;
   if (kca && kcb)        hipLaunchKernelGGL((gemm_f32_wide<true, true>), grid, block, 0, st, a, pg_groups, (int)own);

@@ -310,12 +310,12 @@ bool make_side_job(const ScanArgs& s, const Parts& w, bool rowdot, uint32_t* don
   return true;
 }
 
-hipError_t launch_scan_pair(const ScanArgs* s, const bool* rowdot, Parts* left, hipStream_t st) {
-  ScanPair p{};
+namespace {
+// the two scans as jobs of one grid; returns its workgroups
+int64_t plan_pair(const ScanArgs* s, const bool* rowdot, ScanPair& p, Parts* left) {
   int64_t grid = 0;
   for (int i = 0; i < 2; ++i) {
     SideJob& j = p.j[i];
-    if (s[i].gate || s[i].dtype != s[0].dtype || (s[i].w == nullptr) != (s[0].w == nullptr)) return hipErrorInvalidValue;
     j.s = s[i];
     j.s.carry_blocks = 0;
     j.s.done = nullptr;
@@ -335,9 +335,24 @@ hipError_t launch_scan_pair(const ScanArgs* s, const bool* rowdot, Parts* left, 
     }
     const int64_t blocks = (int64_t)j.gx * j.gy * s[i].batch;
     grid += blocks;
-    if (grid > 0xffffff) return hipErrorInvalidValue;      // (2^32 threads)
     j.nblk = (int)blocks;
   }
+  return grid;
+}
+}  // namespace
+
+bool scan_pair_fits(const ScanArgs* s, const bool* rowdot) {
+  ScanPair p{};
+  Parts left[2];
+  return plan_pair(s, rowdot, p, left) <= 0xffffff;          // (2^32 threads)
+}
+
+hipError_t launch_scan_pair(const ScanArgs* s, const bool* rowdot, Parts* left, hipStream_t st) {
+  for (int i = 0; i < 2; ++i)
+    if (s[i].gate || s[i].dtype != s[0].dtype || (s[i].w == nullptr) != (s[0].w == nullptr)) return hipErrorInvalidValue;
+  ScanPair p{};
+  const int64_t grid = plan_pair(s, rowdot, p, left);
+  if (grid > 0xffffff) return hipErrorInvalidValue;
   const dim3 g((unsigned)grid), block(256);
   const bool idx = s[0].w == nullptr, wave = p.j[0].kind == SIDE_ROW_WAVE || p.j[1].kind == SIDE_ROW_WAVE;
 #define GECC_LAUNCH_PAIR(DT, IDX)                                                            \

@@ -46,3 +46,18 @@ def test_products_that_go_in_fp32_tiles_of_128_by_256(plans, ta, tb):
         (_, wide), (_, other) = routes(plans, [("plain", n, k, m, 256, 0, ta, tb), ("plain", n, k, m, HALVES_OTHER_BATCH, 0, ta, tb)])
         assert len(wide) == 1 and "gemm_f32_wide" in wide[0]
         assert len(other) == 1 and "gemm_tile" in other[0] and "ELi128E" in other[0]
+
+
+def test_calls_of_many_workgroups_are_taken(plans):
+    """Launches of which each fits what one may have (2^32 threads) are not put into one that does not: scans of many batch
+    items, fp32 tiles of twice the threads."""
+    calls = [("protected", 7, 4128, 7, 65535, 1, ta, tb) for ta in (0, 1) for tb in (0, 1)]
+    calls += [("protected", 23, 9514, 1, 52984, 1, 1, 0), ("protected", 11307, 9, 5, 65535, 1, 0, 1), ("protected", 4, 2, 10111, 65535, 1, 0, 1),
+              ("protected", 6, 8000, 7, 65535, 0, 1, 1)]
+    calls += [("plain", 128, 256, 1664, 1 << 20, 0, 0, 0), ("plain", 128, 256, 1664, 1290000, 0, 0, 1)]     # 7.3 and 9.0 million tiles of 128 x 256
+    r = routes(plans, calls)
+    assert [rc for rc, _ in r] == [0] * len(calls)
+    # two scans of one kind go in two launches only there
+    few = routes(plans, [("protected", 7, 4128, 7, 60, 1, 1, 0)])[0][1]
+    assert any("scan_pair" in x for x in few) and not any("scan_pair" in x for x in r[2][1])
+    assert "gemm_f32_wide" in r[-2][1][0] and "gemm_tile" in r[-1][1][0]
