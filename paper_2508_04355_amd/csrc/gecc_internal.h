@@ -339,13 +339,14 @@ static __device__ __forceinline__ void reset_state(DecodeState* s) {
 
 // Global parity block P_g = A_P B_P (Section III, 2 x 2) of batch item b, in fp64 and in a fixed
 // order; thread 0 also resets the item's decoder state.  Called by every thread of one
-// workgroup of at most 256 threads, after its last use of the 16 doubles at `lds`.
-static __device__ __forceinline__ void form_pg(const GemmArgs& a, int b, double* lds, int threads = 0) {
-  if (threads == 0) threads = blockDim.x;
+// workgroup, after its last use of lds[0 .. 4 * wavefronts); THREADS (0: all) of them add terms up, which is part
+// of the order, and the others only come to the barriers.
+template <int THREADS = 0>
+static __device__ __forceinline__ void form_pg(const GemmArgs& a, int b, double* lds) {
   const double* ap = a.A_par + (int64_t)b * 2 * a.k;
   const double* bp = a.B_par + (int64_t)b * 2 * a.k;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int l = threadIdx.x; l < a.k; l += threads) {
+  for (int l = THREADS > 0 && (int)threadIdx.x >= THREADS ? a.k : threadIdx.x; l < a.k; l += THREADS > 0 ? THREADS : blockDim.x) {
     const double a0 = ap[l], a1 = ap[a.k + l], b0 = bp[l], b1 = bp[a.k + l];
     acc[0] = fma(a0, b0, acc[0]); acc[1] = fma(a0, b1, acc[1]);
     acc[2] = fma(a1, b0, acc[2]); acc[3] = fma(a1, b1, acc[3]);
@@ -354,7 +355,7 @@ static __device__ __forceinline__ void form_pg(const GemmArgs& a, int b, double*
   for (int q = 0; q < 4; ++q)
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) acc[q] += __shfl_down(acc[q], off, 64);
-  const int wave = threadIdx.x >> 6, nw = (threads + 63) >> 6;
+  const int wave = threadIdx.x >> 6, nw = ((THREADS > 0 ? THREADS : blockDim.x) + 63) >> 6;
   __syncthreads();
   if ((threadIdx.x & 63) == 0)
 #pragma unroll

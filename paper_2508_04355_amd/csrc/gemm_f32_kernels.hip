@@ -165,7 +165,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_f32_wide(GemmArgs a, int pg_groups
   int id = blockIdx.x;
   // P_g first, in whole groups of 8 workgroups (one per XCD), then the tiles: a contiguous range for every XCD
   if (id < pg_groups * 8) {
-    if (id < a.batch && threadIdx.x < THREADS) form_pg(a, id, reinterpret_cast<double*>(smem), THREADS);
+    if (id < a.batch) form_pg<THREADS>(a, id, reinterpret_cast<double*>(smem));     // (in the order of gemm_tile's 256 threads)
     return;
   }
   id -= pg_groups * 8;
