@@ -75,14 +75,15 @@ constexpr int TH_SLICES = 4;    // wavefronts of a workgroup; each adds every 4t
 // TH_MAXLOADS: loads a thread keeps in flight, chosen by the launcher to fit the number of sub-tiles along a line
 // (more than there are would only read the last one again: 256 x 512^3, four sub-tiles, 26 us with 32 of
 // them, 9 with 4).  The sums do not depend on it.
-template <int TH_MAXLOADS>
-__global__ __launch_bounds__(64 * TH_SLICES) void threshold_kernel(DecodeArgs a, Parts pr, Parts pc) {
+// PARTS: pr and pc may hold something (kernels of their own, since the others pay 0.2 to 0.4 us for the question).
+template <int TH_MAXLOADS, bool PARTS>
+__device__ __forceinline__ void threshold_body(const DecodeArgs& a, const Parts& pr, const Parts& pc) {
   const int b = blockIdx.y;
   DecodeState* st = state_of(a, b);
   const int n = a.p.n, m = a.p.m;
   const int lane = threadIdx.x & 63, slice = threadIdx.x >> 6;
   const int o = blockIdx.x * 64 + lane;          // line: rows first, then columns
-  double* cpar = cpar_of(a, b);
+  const double* cpar = cpar_of(a, b);
   double* synd = synd_of(a, b);
   const bool is_row = o < n, valid = o < n + m;
   const bool wt = a.p.weighted != 0;     // single-checksum mode: the weighted sums are not read
@@ -117,9 +118,9 @@ __global__ __launch_bounds__(64 * TH_SLICES) void threshold_kernel(DecodeArgs a,
   // What the scans have left of this line's two parity symbols.  Chunks: a wavefront's slice is the second stage's own;
   // segments: one wavefront per kind.  (A second stage in a launch of its own costs 5 us for the same loads.)
   const Parts parts = {is_row ? pr.chunks : pc.chunks, is_row ? pr.segs : pc.segs, is_row ? pr.nchunk : pc.nchunk, is_row ? pr.nseg : pc.nseg};
-  const bool in_parts = parts.nchunk > 0 || parts.nseg > 0;
-  __shared__ double par[2][TH_SLICES][64];
-  if (valid && in_parts) {
+  const bool in_parts = PARTS && (parts.nchunk > 0 || parts.nseg > 0);
+  __shared__ double par[PARTS ? 2 : 1][TH_SLICES][64];
+  if (PARTS && valid && in_parts) {
     const int len = is_row ? n : m, i = is_row ? o : o - n;
     if (parts.nchunk > 0) {
       const double* p0 = parts.chunks + (int64_t)b * parts.nchunk * 2 * len + i;
@@ -137,18 +138,22 @@ __global__ __launch_bounds__(64 * TH_SLICES) void threshold_kernel(DecodeArgs a,
   if (slice != 0) return;
   double v1 = 0.0, v2 = 0.0;
   if (valid) {
-    if (in_parts) {
+    double sum[2];
+    if (PARTS && in_parts) {
       const int at = is_row ? o : 2 * n + (o - n), step = is_row ? n : m;
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
-        cpar[at + t * step] = parts.nchunk > 0 ? (par[t][0][lane] + par[t][1][lane]) + (par[t][2][lane] + par[t][3][lane]) : par[t][0][lane];
+      for (int t = 0; t < 2; ++t) {
+        sum[t] = parts.nchunk > 0 ? (par[t][0][lane] + par[t][1][lane]) + (par[t][2][lane] + par[t][3][lane]) : par[t][0][lane];
+        const_cast<double*>(cpar)[at + t * step] = sum[t];
+      }
     }
+    auto parity = [&](int t, int at) { return PARTS && in_parts ? sum[t] : cpar[at]; };
     S = (red[0][0][lane] + red[0][1][lane]) + (red[0][2][lane] + red[0][3][lane]);
     W = (red[1][0][lane] + red[1][1][lane]) + (red[1][2][lane] + red[1][3][lane]);
     if (is_row) {
       const int i = o;
-      v1 = S - cpar[i];
-      v2 = W - cpar[n + i];
+      v1 = S - parity(0, i);
+      v2 = W - parity(1, n + i);
       synd[i] = v1;
       synd[n + i] = v2;
       if (outside(v1, a.p.tau_r1) || (wt && outside(v2, a.p.tau_r2))) {
@@ -157,8 +162,8 @@ __global__ __launch_bounds__(64 * TH_SLICES) void threshold_kernel(DecodeArgs a,
       }
     } else {
       const int j = o - n;
-      v1 = S - cpar[2 * n + j];
-      v2 = W - cpar[2 * n + m + j];
+      v1 = S - parity(0, 2 * n + j);
+      v2 = W - parity(1, 2 * n + m + j);
       synd[2 * n + j] = v1;
       synd[2 * n + m + j] = v2;
       if (outside(v1, a.p.tau_q1) || (wt && outside(v2, a.p.tau_q2))) {
@@ -187,6 +192,11 @@ __global__ __launch_bounds__(64 * TH_SLICES) void threshold_kernel(DecodeArgs a,
     }
   }
 }
+
+template <int TH_MAXLOADS>
+__global__ __launch_bounds__(64 * TH_SLICES) void threshold_kernel(DecodeArgs a) { threshold_body<TH_MAXLOADS, false>(a, Parts{}, Parts{}); }
+template <int TH_MAXLOADS>
+__global__ __launch_bounds__(64 * TH_SLICES) void threshold_parts_kernel(DecodeArgs a, Parts pr, Parts pc) { threshold_body<TH_MAXLOADS, true>(a, pr, pc); }
 
 // first report after detection: CLEAN or DETECTED.  Called by every thread of a workgroup of 1
 // to 4 wavefronts (the family maxima are reduced over the threshold kernel's workgroups);
@@ -1183,9 +1193,15 @@ hipError_t launch_reset_state(const DecodeArgs& a, hipStream_t st) {
 hipError_t launch_threshold(const DecodeArgs& a, const Parts& pr, const Parts& pc, hipStream_t st) {
   dim3 grid((a.p.n + a.p.m + 63) / 64, a.p.batch);   // 64 lines per workgroup: spreads over all CUs
   const int nt = a.ntm > a.ntn ? a.ntm : a.ntn;
-  if (nt <= 4 * TH_SLICES)      hipLaunchKernelGGL(threshold_kernel<4>, grid, dim3(64 * TH_SLICES), 0, st, a, pr, pc);
-  else if (nt <= 8 * TH_SLICES) hipLaunchKernelGGL(threshold_kernel<8>, grid, dim3(64 * TH_SLICES), 0, st, a, pr, pc);
-  else                          hipLaunchKernelGGL(threshold_kernel<32>, grid, dim3(64 * TH_SLICES), 0, st, a, pr, pc);
+  const dim3 block(64 * TH_SLICES);
+  auto launch = [&](auto loads) {
+    constexpr int N = decltype(loads)::value;
+    if (pr.nchunk > 0 || pr.nseg > 0 || pc.nchunk > 0 || pc.nseg > 0) hipLaunchKernelGGL(threshold_parts_kernel<N>, grid, block, 0, st, a, pr, pc);
+    else hipLaunchKernelGGL(threshold_kernel<N>, grid, block, 0, st, a);
+  };
+  if (nt <= 4 * TH_SLICES)      launch(std::integral_constant<int, 4>{});
+  else if (nt <= 8 * TH_SLICES) launch(std::integral_constant<int, 8>{});
+  else                          launch(std::integral_constant<int, 32>{});
   return hipGetLastError();
 }
 
