@@ -467,8 +467,11 @@ constexpr int CD_FLAG_AT = 1024;     // (behind what coldot_finish_segment uses)
 // WPARTS: explicit weights that may still be in parts (wp).  Every workgroup adds up those of its own rows, which costs less
 // than the launch that would have to come first, and keeps them in LDS.  (Not in the scans' own launches: 117 MB bf16 29 us
 // instead of 25, for the registers.)
+// ONE: whether the one chunk of a short column (nchunk == 1) is taken for the sums themselves: never, in this launch, or where
+// it turns out to be one (0.3 us of a long column's 6 to 10, for the question)
 constexpr int CD_ROWS = 8;
-template <int DT, bool IDXW, int CD_NB, bool WPARTS = false>
+enum : int { CD_CHUNKS = 0, CD_ONE = 1, CD_ASK = 2 };
+template <int DT, bool IDXW, int CD_NB, int ONE, bool WPARTS = false>
 __device__ __forceinline__ void coldot_body(const ScanArgs& a, const Parts& wp, int nchunk, int nsegx, int bx, int chunk,
                                             int b, double* lds) {
   using E = Elem<DT>;
@@ -577,15 +580,15 @@ __device__ __forceinline__ void coldot_body(const ScanArgs& a, const Parts& wp, 
   for (int e = 0; e < VEC; ++e) { red[wave][0][e][lane] = acc0[e]; red[wave][1][e][lane] = acc1[e]; }
   __syncthreads();
   // thread -> (t, e, lane'): 2*VEC*64 outputs, 256 threads
-  // (one chunk is all there is: the sums themselves, with the zero that the second stage would have added)
-  const bool whole = nchunk == 1;
+  const bool whole = ONE == CD_ONE || (ONE == CD_ASK && nchunk == 1);
   double* part = whole ? a.out + (int64_t)b * a.out_stride : a.scratch + ((int64_t)b * nchunk + chunk) * 2 * a.Cc;
   for (int o = tid; o < 2 * VEC * 64; o += CD_THREADS) {
     const int l = o & 63, e0 = (o >> 6) % VEC, t = o / (64 * VEC);
     const int col = (bx * 64 + l) * VEC + e0;
     if (col < a.Cc) {
       const int e = col - first_col(l);
-      const double s = ((red[0][t][e][l] + red[1][t][e][l]) + (red[2][t][e][l] + red[3][t][e][l])) + 0.0;
+      double s = (red[0][t][e][l] + red[1][t][e][l]) + (red[2][t][e][l] + red[3][t][e][l]);
+      if (ONE != CD_CHUNKS) s += 0.0;        // (as the second stage would)
       // (written through only when another workgroup of this launch reads it: such stores cost more)
       if (a.done && !whole) store_dev(part + (int64_t)t * a.Cc + col, s);
       else part[(int64_t)t * a.Cc + col] = s;
@@ -821,7 +824,7 @@ __device__ __forceinline__ void pair_body(const PairJob& j, int x, int y, int b,
   if (j.kind == PJ_ROW) rowdot_body<DT, true, RD_SMALL_RB, RD_SMALL_U>(j.s, x, b, lds);
   else if (j.kind == PJ_ROW_BIG) rowdot_body<DT, true, RD_BIG_RB, RD_BIG_U>(j.s, x, b, lds);
   else if (j.kind == PJ_ROW_WAVE) rowdot_wave_body<DT, true>(j.s, x, b, lds);
-  else if (j.kind == PJ_COL) coldot_body<DT, true, CD_ROWS>(j.s, Parts{}, j.gy, j.gx, x, y, b, lds);
+  else if (j.kind == PJ_COL) coldot_body<DT, true, CD_ROWS, CD_CHUNKS>(j.s, Parts{}, j.gy, j.gx, x, y, b, lds);
   else if (j.kind == PJ_TILE_COL) tile_scan_body<DT, true, false, true, true>(j.t, x, y, b, lds);
   else tile_scan_body<DT, false, true, true, true>(j.t, x, y, b, lds);
 }

@@ -37,12 +37,12 @@ __global__ __launch_bounds__(RD_THREADS) void rowdot_kernel(ScanArgs a) {
   rowdot_body<DT, IDXW, RD_RB, RD_U>(a, blockIdx.x, b, lds);
 }
 
-template <int DT, bool IDXW, bool GATED>
+template <int DT, bool IDXW, bool GATED, bool ONE>
 __global__ __launch_bounds__(CD_THREADS) void coldot_stage1(ScanArgs a, int nchunk) {
   __shared__ double lds[CD_LDS_DOUBLES];
   const int b = blockIdx.z;
   if (GATED && gated_off(a.gate, a.gate_stride, b, a.gate_value)) return;
-  coldot_body<DT, IDXW, CD_ROWS>(a, Parts{}, nchunk, gridDim.x, blockIdx.x, blockIdx.y, b, lds);
+  coldot_body<DT, IDXW, CD_ROWS, ONE ? CD_ONE : CD_CHUNKS>(a, Parts{}, nchunk, gridDim.x, blockIdx.x, blockIdx.y, b, lds);
 }
 
 __global__ __launch_bounds__(256) void coldot_stage2(Stage2Job j) {
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(256, WAVE ? 2 : 3) void scan_pair(ScanPair p) {
   const SideJob& j = second ? p.j[1] : p.j[0];
   const int per_item = j.gx * j.gy;
   const int b = v / per_item, x = (v % per_item) % j.gx, y = (v % per_item) / j.gx;
-  if (j.kind == SIDE_COL) coldot_body<DT, IDXW, CD_ROWS>(j.s, Parts{}, j.gy, j.gx, x, y, b, lds);
+  if (j.kind == SIDE_COL) coldot_body<DT, IDXW, CD_ROWS, CD_ASK>(j.s, Parts{}, j.gy, j.gx, x, y, b, lds);
   else if (j.kind == SIDE_ROW) rowdot_body<DT, IDXW, RD_SMALL_RB, RD_SMALL_U>(j.s, x, b, lds);
   else if (j.kind == SIDE_ROW_BIG) rowdot_body<DT, IDXW, BIG, RD_BIG_U>(j.s, x, b, lds);
   else if constexpr (WAVE) rowdot_wave_body<DT, IDXW>(j.s, x, b, lds);
@@ -164,17 +164,20 @@ hipError_t launch_coldot_stage1(const ScanArgs& a0, Stage2Job* pending, hipStrea
   const bool idx = a.w == nullptr, gated = a.gate != nullptr;
   if (gated && !idx) return hipErrorInvalidValue;
   if (a.done && coldot_done_words(a) == 0) return hipErrorInvalidValue;
-  if (a.dtype == GECC_BF16) {
-    if (gated)    hipLaunchKernelGGL((coldot_stage1<GECC_BF16, true, true>), grid, dim3(CD_THREADS), 0, st, a, nchunk);
-    else if (idx) hipLaunchKernelGGL((coldot_stage1<GECC_BF16, true, false>), grid, dim3(CD_THREADS), 0, st, a, nchunk);
-    else          hipLaunchKernelGGL((coldot_stage1<GECC_BF16, false, false>), grid, dim3(CD_THREADS), 0, st, a, nchunk);
-  } else {
-    if (gated)    hipLaunchKernelGGL((coldot_stage1<GECC_F32, true, true>), grid, dim3(CD_THREADS), 0, st, a, nchunk);
-    else if (idx) hipLaunchKernelGGL((coldot_stage1<GECC_F32, true, false>), grid, dim3(CD_THREADS), 0, st, a, nchunk);
-    else          hipLaunchKernelGGL((coldot_stage1<GECC_F32, false, false>), grid, dim3(CD_THREADS), 0, st, a, nchunk);
-  }
+  // (gated ones leave a chunk of any length to the counters or to the second stage)
+  const bool one = nchunk == 1 && !gated && !a.done;
+#define GECC_LAUNCH_COLDOT(DT)                                                                                           \
+  do {                                                                                                                   \
+    if (gated)           hipLaunchKernelGGL((coldot_stage1<DT, true, true, false>), grid, dim3(CD_THREADS), 0, st, a, nchunk);   \
+    else if (idx && one) hipLaunchKernelGGL((coldot_stage1<DT, true, false, true>), grid, dim3(CD_THREADS), 0, st, a, nchunk);   \
+    else if (idx)        hipLaunchKernelGGL((coldot_stage1<DT, true, false, false>), grid, dim3(CD_THREADS), 0, st, a, nchunk);  \
+    else if (one)        hipLaunchKernelGGL((coldot_stage1<DT, false, false, true>), grid, dim3(CD_THREADS), 0, st, a, nchunk);  \
+    else                 hipLaunchKernelGGL((coldot_stage1<DT, false, false, false>), grid, dim3(CD_THREADS), 0, st, a, nchunk); \
+  } while (0)
+  if (a.dtype == GECC_BF16) GECC_LAUNCH_COLDOT(GECC_BF16); else GECC_LAUNCH_COLDOT(GECC_F32);
+#undef GECC_LAUNCH_COLDOT
   *pending = Stage2Job{};
-  if (!a.done && nchunk > 1) {
+  if (!a.done && !one) {
     pending->valid = true;
     pending->scratch = a.scratch; pending->out = a.out; pending->out_stride = a.out_stride;
     pending->Cc = a.Cc; pending->nchunk = nchunk; pending->batch = a.batch;
