@@ -271,9 +271,9 @@ struct GemmArgs {
   int64_t pg_stride;
   DecodeState* state;
 };
-// Scans that ride in the launch of gemm_tile, as workgroups of their own before the product's:
-// the parity blocks P_r and P_c of C-bar (vector weights; a column scan is finished by its last
-// workgroup) and P_g.  Nothing in the launch reads what they form.
+// Scans that ride in the launch of gemm_tile, as workgroups of their own: the parity blocks P_r and P_c of C-bar (vector
+// weights; a column scan is finished by its last workgroup, or its chunks are left to the threshold pass) and P_g, whose
+// workgroup also finishes an operand parity that is still in parts.  Nothing in the launch reads what any of them stores.
 enum : int { SIDE_NONE = 0, SIDE_ROW = 1, SIDE_ROW_WAVE = 2, SIDE_COL = 3, SIDE_ROW_BIG = 4 };
 struct SideJob {
   int kind;            // SIDE_x
@@ -289,6 +289,8 @@ struct GemmSide {
   int pg_items;        // batch items whose P_g is to be formed (set by the launcher)
   int blocks;          // workgroups of the side jobs in all (set by the launcher)
   int groups;          // the same in groups of 8, one per XCD
+  int lead_blocks;     // how many of them come before the product's workgroups, the others come behind (set by the launcher)
+  int lead;            // the same in groups of 8
   int own;             // workgroups of the product
 };
 // describes the scan as a side job; words: counters of `done` it uses.  false: it cannot finish by itself

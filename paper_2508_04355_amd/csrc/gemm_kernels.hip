@@ -265,13 +265,11 @@ __device__ __forceinline__ void side_job(const GemmArgs& a, const GemmSide& side
 }
 
 // -------------------------------------------------------------------------------------------
-// Grid: one dimension, the scans that ride along, then tiles x batch x ksplit workgroups.
+// Grid: one dimension, tiles x batch x ksplit workgroups, and the scans that ride along before or behind them.
 // Consecutive workgroups go to the 8 XCDs in turn, so every XCD is given a contiguous range of the (item,
 // split, tile row, tile column) sequence: tiles that share operand panels share an L2.  The scans are
 // HBM-bound and the product is not: in one launch they cost little more than the
-// product alone, and a launch that waits for the one before it costs 4.5 us whatever it does.  They come first: a
-// scan is over after 5 us and makes room for a workgroup of the product, which takes 20; spread evenly among those of
-// a product that fills the chip by itself, they had 230 of 1024^3's 1024 begin up to 20 us late.
+// product alone, and a launch that waits for the one before it costs 4.5 us whatever it does.
 template <int DT, bool KCA, bool KCB, int TILE>
 __global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : 2) void gemm_tile(GemmArgs a, GemmSide side) {
   using T = typename GT<DT>::T;
@@ -290,12 +288,15 @@ __global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : 2) void gemm_tile(GemmArg
   const int ntm = (a.n + TILE - 1) / TILE, ntn = (a.m + TILE - 1) / TILE;
   int id = blockIdx.x;
   if (side.groups > 0) {
-    // the scans first, in whole groups of 8 workgroups (one per XCD)
-    if (id < side.groups * 8) {
-      if (id < side.blocks) side_job<DT>(a, side, id, reinterpret_cast<double*>(smem));
+    // in whole groups of 8 workgroups (one per XCD): side.lead of P_g and, where they go first, the scans; then the
+    // product's; then the scans
+    const int first = side.lead * 8, own = (side.own + 7) / 8 * 8;
+    if (id < first || id >= first + own) {
+      const int v = id < first ? id : side.lead_blocks + id - first - own;
+      if (v < (id < first ? side.lead_blocks : side.blocks)) side_job<DT>(a, side, v, reinterpret_cast<double*>(smem));
       return;
     }
-    id -= side.groups * 8;
+    id -= first;
     if (id >= side.own) return;
   }
   {
@@ -737,6 +738,17 @@ __global__ __launch_bounds__(THREADS) void partials_kernel(PartialArgs a) {
   }
 }
 
+// The scans come first where all workgroups of the launch run at once (256 compute units with as many as their registers
+// and LDS allow): nobody waits for a place, and theirs is the longer chain.  Beyond that they come behind: what does
+// not fit at first is then short scans and not workgroups of the product that begin 5 us late and last 20.  Whole calls,
+// scans first -> behind, beyond that number: 87 products of all layouts, 0.3 % slower to 20 % faster (bf16 295 x 6020 x 4321
+// 100 -> 82 us, 2432 x 3584 x 256 56.5 -> 50.6, 4648 x 1232 x 272 NT 52.4 -> 44.0, fp32 1991 x 1907 x 220 49.7 -> 44.2); below it
+// 4 % slower (192 x 3520 x 1408 39.8 -> 41.3, TT 1216 x 960 x 576 76.8 -> 80.5) to 7 % faster.  P_g, one workgroup with a long
+// chain, goes first in either case (behind: no difference seen).  Behind, a column scan, whose workgroups take longer, comes
+// before a row scan (bf16 TT 1632 x 624 x 2328 40.9 us, the other way round 46.7; first, where it is the other way round
+// 34.7 -> 34.1 at 1536 x 1280 x 256).
+template <int DT, int TILE> constexpr int at_once() { return 256 * (TILE == 64 ? 4 : DT == GECC_BF16 ? 3 : 2); }
+
 template <int DT, int TILE>
 hipError_t launch_tile(const GemmArgs& a0, const GemmSide* side0, hipStream_t st) {
   GemmArgs a = a0;
@@ -751,8 +763,13 @@ hipError_t launch_tile(const GemmArgs& a0, const GemmSide* side0, hipStream_t st
   GemmSide side = side0 ? *side0 : GemmSide{};
   side.pg_items = a.pg_out ? a.batch : 0;
   side.blocks = side.pg_items + side.j[0].nblk + side.j[1].nblk;
-  side.groups = (side.blocks + 7) / 8;
-  const int64_t own = tiles * a.ksplit, grid_all = side.groups > 0 ? ((own + 7) / 8 + side.groups) * 8 : own;
+  const int64_t own = tiles * a.ksplit;
+  const bool behind = own + side.blocks > at_once<DT, TILE>();
+  side.lead_blocks = behind ? side.pg_items : side.blocks;
+  if (behind && side.j[0].kind != SIDE_COL && side.j[1].kind == SIDE_COL) { const SideJob row = side.j[0]; side.j[0] = side.j[1]; side.j[1] = row; }
+  side.lead = (side.lead_blocks + 7) / 8;
+  side.groups = side.lead + (side.blocks - side.lead_blocks + 7) / 8;
+  const int64_t grid_all = side.groups > 0 ? ((own + 7) / 8 + side.groups) * 8 : own;
   if (grid_all > 0xffffff) return hipErrorInvalidValue;      // (2^32 threads)
   side.own = (int)own;
   const dim3 grid((unsigned)grid_all);

@@ -21,6 +21,7 @@ using namespace gecc;
 static std::map<const void*, std::string>& names() { static std::map<const void*, std::string> m; return m; }
 static struct { dim3 grid, block; size_t lds; hipStream_t st; } g_cfg;
 static gecc_ctx* g_ctx;
+static GemmSide g_side;      // of the last launch of gemm_tile
 static long g_launches, g_scans, g_narrow_split, g_main_split, g_bad;
 static std::string g_case;
 
@@ -32,6 +33,13 @@ static void look_at(const std::string& name, void** args) {
   if (name.find("rowdot") != std::string::npos || name.find("coldot") != std::string::npos) ++g_scans;
   if (name.find("gemm_tile") == std::string::npos) return;
   const GemmArgs& a = *static_cast<const GemmArgs*>(args[0]);
+  // the scans beside the product: every one has a workgroup, before the product's or behind
+  const GemmSide& s = g_side = *static_cast<const GemmSide*>(args[1]);
+  const int64_t own = (s.own + 7) / 8 * 8, behind = (s.groups - s.lead) * 8;
+  if (s.groups > 0 && (s.lead_blocks < s.pg_items || s.lead_blocks > s.blocks || s.lead * 8 < s.lead_blocks || s.lead_blocks + behind < s.blocks ||
+                       s.lead * 8 + own + behind != (int64_t)g_cfg.grid.x)) {
+    if (++g_bad <= 8) printf("BAD %s: %d workgroups of scans, %d before the product's, grid %u\n", g_case.c_str(), s.blocks, s.lead_blocks, g_cfg.grid.x);
+  }
   if (a.ksplit <= 1) return;
   const int64_t tile = name.find("ELi128EEEv") != std::string::npos ? 128 : name.find("ELi64EEEv") != std::string::npos ? 64 : 0;
   const int64_t tiles = (a.n + tile - 1) / tile * ((a.m + tile - 1) / tile) * a.batch;
@@ -130,6 +138,12 @@ int main(int argc, char** argv) {
   expect(scans(600, 600, 600, 8, GECC_F32, 0, 1) > 0, "8 x 600^3 NT");
   expect(scans(2048, 2048, 2048, 1, GECC_F32, 0, 0) > 0, "2048^3");
   expect(scans(503, 301, 94, 307, GECC_BF16, 0, 0) > 0, "bf16 307 x 503 x 301 x 94");
+  // before the product's workgroups where all run at once, else behind; column scans before row scans
+  auto first = [&](int n, int k, int m, int ta, int tb, int dtype) { one(n, k, m, 1, dtype, ta, tb, 0, 0, 0, 0); return g_side.lead_blocks == g_side.blocks; };
+  expect(first(1024, 1024, 1024, 0, 0, GECC_F32), "1024^3, all at once");
+  expect(!first(1991, 1907, 220, 0, 0, GECC_F32) && g_side.lead_blocks == 1, "1991 x 1907 x 220, behind");
+  expect(!first(2432, 3584, 256, 0, 0, GECC_BF16) && g_side.lead_blocks == 1, "bf16 2432 x 3584 x 256, behind");
+  expect(!first(1632, 624, 2328, 1, 1, GECC_BF16) && g_side.j[0].kind == SIDE_COL && g_side.j[1].kind == SIDE_ROW, "bf16 1632 x 624 x 2328 TT, columns before rows");
   std::mt19937 rng(7);
   auto pick = [&](int lo, int hi) { return lo + (int)(rng() % (uint32_t)(hi - lo + 1)); };
   const int pads[] = {0, 0, 3, 8};
