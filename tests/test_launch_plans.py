@@ -41,11 +41,23 @@ def test_partial_tiles_stay_in_their_part_of_the_workspace(plans):
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
 def test_products_that_go_in_fp32_tiles_of_128_by_256(plans, ta, tb):
     """The sizes that tests of that kernel use reach it (and the others, to which it is compared, do not)."""
-    from test_tiles_and_scans import HALVES_OTHER_BATCH, HALVES_SHAPES
+    from test_tiles_and_scans import HALVES_OTHER_BATCH, HALVES_SHAPES, SMALL_CASES, WIDE_CASES
+    for cases, kernel in ((WIDE_CASES, "gemm_f32_wide"), (SMALL_CASES, "gemm_tileILi0ELb%dELb%dELi64E" % (not ta, tb))):
+        for entry in ("plain", "multiply"):
+            for _, names in routes(plans, [(entry,) + shape + (batch, 0, ta, tb) for shape, batch in cases]):
+                assert kernel in names[-1] and sum("gemm" in x for x in names) == 1, names
     for n, k, m in HALVES_SHAPES:
         (_, wide), (_, other) = routes(plans, [("plain", n, k, m, 256, 0, ta, tb), ("plain", n, k, m, HALVES_OTHER_BATCH, 0, ta, tb)])
         assert len(wide) == 1 and "gemm_f32_wide" in wide[0]
         assert len(other) == 1 and "gemm_tile" in other[0] and "ELi128E" in other[0]
+
+
+def test_sums_of_32_chunks_are_left_to_their_readers_and_of_33_are_not(plans):
+    """Both sides of that limit, at sizes of test_sums_left_to_their_readers: the parity blocks ride in the product's launch
+    in either case, the encodings share a launch where A_P's chunks stay as they are."""
+    (_, left), (_, done) = routes(plans, [("protected", n, 72, 130, 1, 0, 0, 0) for n in (4096, 4097)])
+    assert any("scan_pair" in x for x in left) and not any("scan_pair" in x for x in done)
+    assert len(done) == len(left) + 1 and not any("rowdot" in x or "coldot" in x for x in left)
 
 
 def test_calls_of_many_workgroups_are_taken(plans):

@@ -60,15 +60,22 @@ def test_tiles_layouts_and_tails(shape, batch, dtype, trans):
     _check(_product(A, B, dtype, trans, pad=3, shift=1), A, B)       # rows that start at any element
 
 
+# Batches that go in tiles of 128 x 256 (test_launch_plans.py holds them to it): every remainder of the k loop (three k-tiles of
+# 32 in flight), few rows, a second half with a single column, more tile columns than one, of which the last has no second half
+WIDE_CASES = [((128, 256, 256), 250), ((120, 257, 250), 250), ((127, 287, 1541), 73), ((128, 288, 193), 250), ((65, 319, 200), 250),
+              ((121, 320, 385), 125)]
+# ... and in tiles of 64 x 64, for the same values and faults
+SMALL_CASES = [((128, 128, 256), 250), ((127, 129, 249), 250), ((100, 160, 200), 250), ((1, 191, 129), 250)]
+
+
 @pytest.mark.parametrize("trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
-@pytest.mark.parametrize("shape", [(128, 128, 256), (127, 129, 249), (100, 160, 200), (1, 191, 129), (120, 257, 250)])
-def test_fp32_tiles_of_128_by_256(shape, trans):
-    """A round of products that fill one such tile each: every remainder of the k loop (three k-tiles in flight), rows and
-    columns past the end, operands the pieces cannot hold, faults in either half of the tile."""
+@pytest.mark.parametrize("shape,batch", WIDE_CASES + SMALL_CASES)
+def test_fp32_tiles_of_128_by_256(shape, batch, trans):
+    """Rounds of such tiles, and products too short for them: every remainder of the k loop, rows and columns past the end,
+    operands the pieces cannot hold, faults in either half of a tile."""
     import torch
     import gpu_harness as H
     n, k, m = shape
-    batch = 250
     rng = inputs.rng_for(81, n + k)
     A, B = rng.standard_normal((batch, n, k)).astype(np.float32), rng.standard_normal((batch, k, m)).astype(np.float32)
     A[7, :, 3] *= np.float32(2.0 ** -120)
@@ -81,7 +88,7 @@ def test_fp32_tiles_of_128_by_256(shape, trans):
     dA, dB, C = H.to_dev(A, "f32", trans[0]), H.to_dev(B, "f32", trans[1]), ctx.alloc_c()
     A_par, B_par, C_par = ctx.alloc_parities()
     rep = ctx.alloc_report()
-    planted = {5: (n - 1, m - 1, 40.0), 11: (0, min(m - 1, 130), -25.0), 249: (n // 2, 3, 60.0)}
+    planted = {5: (n - 1, m - 1, 40.0), 11: (0, min(m - 1, 130), -25.0), batch - 1: (n // 2, 3, 60.0)}
     ctx.encode_a(dA, A_par)
     ctx.encode_b(dB, B_par)
     ctx.multiply(dA, A_par, dB, B_par, C, C_par, *gecc.make_faults([(b,) + f for b, f in planted.items()]))
