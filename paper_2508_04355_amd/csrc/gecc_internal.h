@@ -296,8 +296,8 @@ struct GemmSide {
 // describes the scan as a side job; words: counters of `done` it uses.  false: it cannot finish by itself
 // done null: its chunks are left to the threshold pass
 bool make_side_job(const ScanArgs& s, const Parts& w, bool rowdot, uint32_t* done, int words_left, SideJob& j, int& words);
-// Two scans that do not read each other's results in one launch (both with index weights or both with explicit ones, no
-// gate); left[i]: what a column scan has left to its readers
+// Two scans that do not read each other's results in one launch (both with index weights, or with explicit ones and of one
+// kind; no gate); left[i]: what a column scan has left to its readers
 hipError_t launch_scan_pair(const ScanArgs* s, const bool* rowdot, Parts* left, hipStream_t st);
 // whether the workgroups of both, which such a launch counts in one dimension, are no more than one may have
 bool scan_pair_fits(const ScanArgs* s, const bool* rowdot);

@@ -63,10 +63,16 @@ __global__ __launch_bounds__(256) void coldot_stage2_pair(Stage2Job j0, Stage2Jo
 
 // Two scans that do not read each other's results (both encodings, or both parity blocks): what each of them would
 // leave idle at its end the other one fills, and a launch that waits for the one before it costs 5 us whatever it does.
-// WAVE: one of them is a row scan with a wavefront per RW_RB rows, which takes a third more registers than the others.
+// Two parity blocks are scans of one kind, and each kind has a kernel of its own: in one for both, 13 registers of the bf16 column
+// scan spilled at three wavefronts per SIMD (whole calls TN, 4096^3 155.2 -> 150.0 us, 2048^3 74.9 -> 73.1, 6144 x 2048 x 3072 148.9 ->
+// 146.9; row scans, 3072 x 2048 x 6144 NT 150.8 -> 150.0; with two per SIMD instead, those were slower, 152.5).
 struct ScanPair { SideJob j[2]; };
-template <int DT, bool IDXW, bool WAVE>
-__global__ __launch_bounds__(256, WAVE ? 2 : 3) void scan_pair(ScanPair p) {
+enum : int { PAIR_ANY = 0,       // (explicit weights: row scans)
+             PAIR_WAVE = 1,      // one of them a row scan with a wavefront per RW_RB rows, a third more registers than the others
+             PAIR_COLS = 2 };    // two column scans
+template <int DT, bool IDXW, int WHAT>
+__global__ __launch_bounds__(256, WHAT == PAIR_WAVE ? 2 : 3) void scan_pair(ScanPair p) {
+  constexpr bool WAVE = WHAT == PAIR_WAVE, COL = IDXW || WHAT == PAIR_COLS;
   constexpr int BIG = IDXW ? RD_BIG_RB : RD_BIG_RB_W;
   static_assert(BIG * RD_THREADS <= CD_LDS_DOUBLES, "LDS of a row scan");
   __shared__ double lds[WAVE && RW_LDS_DOUBLES > CD_LDS_DOUBLES ? RW_LDS_DOUBLES : CD_LDS_DOUBLES];
@@ -76,10 +82,17 @@ __global__ __launch_bounds__(256, WAVE ? 2 : 3) void scan_pair(ScanPair p) {
   const SideJob& j = second ? p.j[1] : p.j[0];
   const int per_item = j.gx * j.gy;
   const int b = v / per_item, x = (v % per_item) % j.gx, y = (v % per_item) / j.gx;
-  if (j.kind == SIDE_COL) coldot_body<DT, IDXW, CD_ROWS, CD_ASK>(j.s, Parts{}, j.gy, j.gx, x, y, b, lds);
-  else if (j.kind == SIDE_ROW) rowdot_body<DT, IDXW, RD_SMALL_RB, RD_SMALL_U>(j.s, x, b, lds);
-  else if (j.kind == SIDE_ROW_BIG) rowdot_body<DT, IDXW, BIG, RD_BIG_U>(j.s, x, b, lds);
-  else if constexpr (WAVE) rowdot_wave_body<DT, IDXW>(j.s, x, b, lds);
+  if constexpr (COL) {
+    if (WHAT == PAIR_COLS || j.kind == SIDE_COL) {
+      coldot_body<DT, IDXW, CD_ROWS, CD_ASK>(j.s, Parts{}, j.gy, j.gx, x, y, b, lds);
+      return;
+    }
+  }
+  if constexpr (WHAT != PAIR_COLS) {
+    if (j.kind == SIDE_ROW) rowdot_body<DT, IDXW, RD_SMALL_RB, RD_SMALL_U>(j.s, x, b, lds);
+    else if (j.kind == SIDE_ROW_BIG) rowdot_body<DT, IDXW, BIG, RD_BIG_U>(j.s, x, b, lds);
+    else if constexpr (WAVE) rowdot_wave_body<DT, IDXW>(j.s, x, b, lds);
+  }
 }
 
 template <int DT, bool COL, bool ROW, bool COL_IDX, bool ROW_IDX, bool GATED>
@@ -365,16 +378,16 @@ hipError_t launch_scan_pair(const ScanArgs* s, const bool* rowdot, Parts* left, 
   if (grid > 0xffffff) return hipErrorInvalidValue;
   const dim3 g((unsigned)grid), block(256);
   const bool idx = s[0].w == nullptr, wave = p.j[0].kind == SIDE_ROW_WAVE || p.j[1].kind == SIDE_ROW_WAVE;
-#define GECC_LAUNCH_PAIR(DT, IDX)                                                            \
-  do {                                                                                       \
-    if (wave) hipLaunchKernelGGL((scan_pair<DT, IDX, true>), g, block, 0, st, p);            \
-    else      hipLaunchKernelGGL((scan_pair<DT, IDX, false>), g, block, 0, st, p);           \
+  if (!idx && rowdot[0] != rowdot[1]) return hipErrorInvalidValue;
+#define GECC_LAUNCH_PAIR(DT)                                                                            \
+  do {                                                                                                  \
+    if (idx && wave)     hipLaunchKernelGGL((scan_pair<DT, true, PAIR_WAVE>), g, block, 0, st, p);      \
+    else if (idx)        hipLaunchKernelGGL((scan_pair<DT, true, PAIR_ANY>), g, block, 0, st, p);       \
+    else if (wave)       hipLaunchKernelGGL((scan_pair<DT, false, PAIR_WAVE>), g, block, 0, st, p);     \
+    else if (!rowdot[0]) hipLaunchKernelGGL((scan_pair<DT, false, PAIR_COLS>), g, block, 0, st, p);     \
+    else                 hipLaunchKernelGGL((scan_pair<DT, false, PAIR_ANY>), g, block, 0, st, p);      \
   } while (0)
-  if (s[0].dtype == GECC_BF16) {
-    if (idx) GECC_LAUNCH_PAIR(GECC_BF16, true); else GECC_LAUNCH_PAIR(GECC_BF16, false);
-  } else {
-    if (idx) GECC_LAUNCH_PAIR(GECC_F32, true); else GECC_LAUNCH_PAIR(GECC_F32, false);
-  }
+  if (s[0].dtype == GECC_BF16) GECC_LAUNCH_PAIR(GECC_BF16); else GECC_LAUNCH_PAIR(GECC_F32);
 #undef GECC_LAUNCH_PAIR
   return hipGetLastError();
 }

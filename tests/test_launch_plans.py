@@ -60,6 +60,16 @@ def test_sums_of_32_chunks_are_left_to_their_readers_and_of_33_are_not(plans):
     assert len(done) == len(left) + 1 and not any("rowdot" in x or "coldot" in x for x in left)
 
 
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_two_parity_blocks_go_in_the_kernel_of_their_kind(plans, dtype):
+    """Column scans (TN) in the one for column scans, row scans (NT) in the one for rows; many short rows in the one with
+    a wavefront for eight of them."""
+    tn, nt, short = [names for _, names in routes(plans, [("protected", 2048, 2048, 2048, 1, dtype, 1, 0), ("protected", 2048, 2048, 2048, 1, dtype, 0, 1),
+                                                          ("protected", 512, 128, 512, 256, dtype, 0, 1)])]
+    for names, kind in ((tn, 2), (nt, 0), (short, 1)):
+        assert sum("scan_pairILi%dELb0ELi%dE" % (dtype, kind) in x for x in names) == 1, names
+
+
 def test_calls_of_many_workgroups_are_taken(plans):
     """Launches of which each fits what one may have (2^32 threads) are not put into one that does not: scans of many batch
     items, fp32 tiles of twice the threads."""
