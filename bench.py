@@ -183,6 +183,8 @@ def main():
                   "parity_r": s_in * n * k * batch, "parity_c": s_in * k * m * batch,
                   "encode_a+parity_r": s_in * n * k * batch, "encode_b+parity_c": s_in * k * m * batch,
                   "encode_a+encode_b": s_in * (n + m) * k * batch, "parity_r+parity_c": s_in * (n + m) * k * batch,
+                  # (not the chunks of P_r and P_c that this pass adds up where a scan has left them to it: up to
+                  # 16 bytes per line and 128 terms of k, cfg4-fwd 7.3 MB on 29)
                   "threshold": 8 * (ntn * n + ntm * m) * batch, "partials": 4 * n * m * batch}
     scan_kinds = (gecc.K_ENCODE_A, gecc.K_ENCODE_B, gecc.K_PARITY_R, gecc.K_PARITY_C, gecc.K_THRESHOLD,
                   gecc.K_PARTIALS, gecc.K_STAGE2, gecc.K_DECODE, gecc.K_AUDIT_A, gecc.K_AUDIT_B, gecc.K_REPAIR,
@@ -296,7 +298,8 @@ def main():
     peak = PEAK_TFLOPS[w.dtype]
     # aligned bf16 operands and a 256 x 256 tile for more than half of the compute units: never gemm_tile
     tiles256 = -(-n // 256) * -(-m // 256) * batch
-    # fp32: whole rounds of 128 x 256 tiles (the rule of gemm_f32_wide_pays)
+    # fp32: whole rounds of 128 x 256 tiles (gemm_f32_wide_pays as far as the workloads here need it: it also asks for
+    # offsets of 32 bits, and products whose scans ride in their launch never come to it)
     wide = -(-n // 128) * -(-m // 256) * batch
     f32_wide = k >= 128 and -(-wide // 256) * 471 < -(-n // 128) * -(-m // 128) * batch
     product_kernel = ("gemm_f32_wide" if f32_wide else "gemm_tile") if w.dtype == "f32" else "gemm_bf16_256" if tiles256 > 128 and k % 64 == 0 else "product kernel"

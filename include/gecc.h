@@ -309,7 +309,11 @@ int gecc_syndromes_to_host(gecc_ctx* ctx, double* host_syndromes, void* stream);
    class brackets everything gecc_multiply's product step enqueues (the k-split tail's zeroing
    and second launch included) and the parity blocks P_r, P_c where they ride in its launch; a row
    scan that carries the second stage of a column scan is timed with it.  A launch that does the work of
-   two classes (Section V step 2 with both re-encodings) leaves a record of each, over the same span. */
+   two classes (Section V step 2 with both re-encodings) leaves a record of each, over the same span.
+   In the one call the two encodings, the two parity blocks, or one of each, may share a launch: it is then
+   one record of ENCODE_AB, PARITY_RC, TILE_A or TILE_B and none of ENCODE_A/B and PARITY_R/C, so that
+   a mask meant for all of them has all eight bits.  What is left of a column scan is added up by its
+   reader where that pays, and is part of the reader's time. */
 enum {
   GECC_K_ENCODE_A = 0,  /* A_P = [P_n1; P_n2] A                          */
   GECC_K_ENCODE_B = 1,  /* B_P = B [P_m1^T P_m2^T]                       */

@@ -705,7 +705,8 @@ Riders plan_riders(const gecc_ctx* ctx, const GemmArgs& g, uint32_t* done, const
 // Whether an operand parity in `nchunk` parts is left to its readers beside the product: a column scan reads the weights of
 // its own rows, and one workgroup adds all of them up for P_g, about 1 us a round of loads.  Up to 8 rounds beside any product,
 // 16 beside one of 2^20 symbols (bf16, finished first -> left: 300 x 6000 x 1000, 12 rounds, 51.3 -> 52.5 us, 1000 x 6000 x 300
-// 51.0 -> 55.2; 2880 x 520 x 2504, 3 of the longest, 59.9 -> 53.1, 1200 x 3000 x 1500 80.1 -> 76.7, 500 x 2000 x 4000 TT 69.4 -> 65.5).
+// 51.0 -> 55.2; 2880 x 520 x 2504, 3 of the longest, 59.9 -> 53.1, 1200 x 3000 x 1500 80.1 -> 76.7, 500 x 2000 x 4000 TT 69.4 -> 65.5; all with
+// the scans before the product's workgroups, which made 1200 x 3000 x 1500 no faster than it had been: behind them 66.3).
 bool parts_beside(const gecc_ctx* c, int nchunk) {
   const int at_once = nchunk <= 8 ? 4 : nchunk <= 16 ? 2 : 1;
   const int64_t rounds = (2 * (int64_t)c->p.k + 256 * at_once - 1) / (256 * at_once) * (nchunk <= 16 ? 1 : 2);

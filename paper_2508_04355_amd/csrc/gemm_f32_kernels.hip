@@ -1,6 +1,7 @@
 // Large fp32 products: tiles of 128 x 256, 8 wavefronts (2 x 4), one workgroup per compute unit, two k-tiles in LDS; the
 // arithmetic of gemm_kernels.hip (three bf16 pieces per value, six products; 128 x 128 symbols whose operands the pieces
 // cannot hold again with native fp32 MFMAs) in the same order, so that the results are the same to the bit.
+// Beside gemm_kernels.hip and not in it: as one template, that kernel's bf16 instances took 188 registers for 157.
 #include "gemm_device.h"
 
 namespace gecc {
@@ -208,11 +209,11 @@ __global__ __launch_bounds__(NT, 2) void gemm_f32_wide(GemmArgs a, int pg_groups
   sb.load(0);
 
   // Two k-tiles in LDS, one barrier per k-tile: while one is multiplied the next one's pieces are formed from registers,
-  // three vector instructions behind every MFMA, and the registers are loaded again for the one after it.  Before, with
-  // 128 x 128 tiles, matrix pipes (44 % of the cycles) and vector units (39 %) took turns: 256 x 512^3 434 us, now 398.
-  // What bounds it: registers (with B's fragments of all four column blocks held at once a few spill, and a reload waits
-  // for every load from memory that was issued before it: 495 us), the first fragment reads behind each barrier (500 cycles
-  // of some 4500) and prologue and epilogue, which nothing else on the compute unit covers.
+  // three vector instructions behind every MFMA, and the registers are loaded again for the one after it.  With 128 x 128
+  // tiles, matrix pipes (44 % of the cycles) and vector units (39 %) took turns: 256 x 512^3 434 us, here (49 and 27 %) 398.
+  // What bounds it: registers (with B's fragments of all four column blocks held at once more of them spill, and a reload
+  // waits for every load from memory that was issued before it: 495 us; as it is NN and TN spill none, TT two and NT six),
+  // the first fragment reads behind each barrier and prologue and epilogue, which nothing else on the compute unit covers.
   // The MFMAs of one k-tile that lies in LDS; between(s): what comes with those of section s, a block of 16 rows and half of
   // the wavefront's columns.
   constexpr int NJ = NI / 2, SECTIONS = 2 * NI;
