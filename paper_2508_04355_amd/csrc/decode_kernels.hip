@@ -265,37 +265,39 @@ struct Synd {
   __device__ double tq2(int j) const { return b_q2 + (a_q2 ? a_q2[j] : 0.0) + rel * fabs(q2[j]); }
 };
 
+// The syndromes of the flagged lines alone: kind 0 and 1 of a line and how far each is trusted, rows [0], columns [1], in the
+// order of Er and Et
+struct FlagSynd {
+  double v[2][2][2];                        // [rows, columns][line][kind]
+  double tr[2][2][2];
+  bool wt;
+};
+
 // every syndrome of a flagged line has to be explained by the estimate, within the thresholds
 // widened by the uncertainty the estimate itself carries
 __device__ bool residual_ok(const Est* est, int ne, const int* Er, int s, const int* Et, int t,
-                            const Synd& y) {
-  for (int a = 0; a < s; ++a) {
-    const int i = Er[a];
+                            const FlagSynd& y) {
+#pragma unroll 1
+  for (int x = 0; x < s + t; ++x) {
+    const bool row = x < s;
+    const int c = row ? x : x - s, line = row ? Er[c] : Et[c];
     double sx = 0, su = 0, wx = 0, wu = 0;
+#pragma unroll 1
     for (int e = 0; e < ne; ++e)
-      if (est[e].i == i) {
+      if ((row ? est[e].i : est[e].j) == line) {
+        const double w = (double)((row ? est[e].j : est[e].i) + 1);
         sx += est[e].x; su += est[e].u;
-        wx += (est[e].j + 1) * est[e].x; wu += (est[e].j + 1) * est[e].u;
+        wx += w * est[e].x; wu += w * est[e].u;
       }
-    if (fabs(y.r1[i] - sx) > y.tr1(i) + su) return false;
-    if (y.wt && fabs(y.r2[i] - wx) > y.tr2(i) + wu) return false;
-  }
-  for (int c = 0; c < t; ++c) {
-    const int j = Et[c];
-    double sx = 0, su = 0, wx = 0, wu = 0;
-    for (int e = 0; e < ne; ++e)
-      if (est[e].j == j) {
-        sx += est[e].x; su += est[e].u;
-        wx += (est[e].i + 1) * est[e].x; wu += (est[e].i + 1) * est[e].u;
-      }
-    if (fabs(y.q1[j] - sx) > y.tq1(j) + su) return false;
-    if (y.wt && fabs(y.q2[j] - wx) > y.tq2(j) + wu) return false;
+    const double *v = y.v[row ? 0 : 1][c], *tr = y.tr[row ? 0 : 1][c];
+    if (fabs(v[0] - sx) > tr[0] + su) return false;
+    if (y.wt && fabs(v[1] - wx) > tr[1] + wu) return false;
   }
   return true;
 }
 
 // drops insignificant parts, verifies, sorts by (i, j).  Returns the count or -1.
-__device__ int accept(Est* est, int ne, const int* Er, int s, const int* Et, int t, const Synd& y) {
+__device__ int accept(Est* est, int ne, const int* Er, int s, const int* Et, int t, const FlagSynd& y) {
   int k = 0;
   for (int e = 0; e < ne; ++e)
     if (fabs(est[e].x) > est[e].u) est[k++] = est[e];
@@ -315,42 +317,42 @@ __device__ int accept(Est* est, int ne, const int* Er, int s, const int* Et, int
 // Correction rule for 1 <= s, t <= 2 (s <= t: columns carry the information; s > t mirrored).  By one thread
 // of the workgroup; Er, Et and out are in LDS like the estimates here (indexed at run time, they would put
 // a quarter of a KiB of scratch under every thread of the kernel).
-__device__ int d0_correct(Est* out, const int* Er, int s, const int* Et, int t, const Synd& y) {
+__device__ __noinline__ int d0_correct(Est* out, const int* Er, int s, const int* Et, int t, const FlagSynd& y) {
   __shared__ Est est[4], dg[4], an[4];
-  if (s <= t) {
-    if (s == 1) {
-      for (int c = 0; c < t; ++c) est[c] = Est{Er[0], Et[c], y.q1[Et[c]], y.tq1(Et[c])};
-      const int k = accept(est, t, Er, s, Et, t, y);
-      for (int e = 0; e < k; ++e) out[e] = est[e];
-      return k;
-    }
-    const int s1 = Er[0], s2 = Er[1], t1 = Et[0], t2 = Et[1];
-    dg[0] = Est{s1, t1, y.q1[t1], y.tq1(t1)};
-    dg[1] = Est{s2, t2, y.q1[t2], y.tq1(t2)};
-    an[0] = Est{s1, t2, y.q1[t2], y.tq1(t2)};
-    an[1] = Est{s2, t1, y.q1[t1], y.tq1(t1)};
-    const int kd = accept(dg, 2, Er, s, Et, t, y);
-    const int ka = accept(an, 2, Er, s, Et, t, y);
-    if (kd >= 0 && ka >= 0) return -1;   // cannot tell the two apart
-    if (kd >= 0) { for (int e = 0; e < kd; ++e) out[e] = dg[e]; return kd; }
-    if (ka >= 0) { for (int e = 0; e < ka; ++e) out[e] = an[e]; return ka; }
-    const double w1 = s1 + 1.0, w2 = s2 + 1.0;
-    int ne = 0;
-    for (int c = 0; c < 2; ++c) {
-      const int j = Et[c];
-      const double e2 = (y.q2[j] - w1 * y.q1[j]) / (w2 - w1);
-      const double e1 = y.q1[j] - e2;
-      const double u2 = (y.tq2(j) + w1 * y.tq1(j)) / (w2 - w1);
-      const double u1 = y.tq1(j) + u2;
-      est[ne++] = Est{s1, j, e1, u1};
-      est[ne++] = Est{s2, j, e2, u2};
-    }
-    const int k = accept(est, ne, Er, s, Et, t, y);
+  const int few = s <= t ? s : t;
+  if (few == 1) {
+    // one line of one kind: each line of the other kind (columns, where there is one of each) holds one error
+    const bool row = s <= t;
+    const int many = row ? t : s;
+    for (int c = 0; c < many; ++c)
+      est[c] = Est{row ? Er[0] : Er[c], row ? Et[c] : Et[0], y.v[row ? 1 : 0][c][0], y.tr[row ? 1 : 0][c][0]};
+    const int k = accept(est, many, Er, s, Et, t, y);
     for (int e = 0; e < k; ++e) out[e] = est[e];
     return k;
   }
-  for (int r = 0; r < s; ++r) est[r] = Est{Er[r], Et[0], y.r1[Er[r]], y.tr1(Er[r])};
-  const int k = accept(est, s, Er, s, Et, t, y);
+  const int s1 = Er[0], s2 = Er[1];
+  for (int c = 0; c < 2; ++c) {
+    dg[c] = Est{Er[c], Et[c], y.v[1][c][0], y.tr[1][c][0]};
+    an[c] = Est{Er[c], Et[1 - c], y.v[1][1 - c][0], y.tr[1][1 - c][0]};
+  }
+  const int kd = accept(dg, 2, Er, s, Et, t, y);
+  const int ka = accept(an, 2, Er, s, Et, t, y);
+  if (kd >= 0 && ka >= 0) return -1;   // cannot tell the two apart
+  if (kd >= 0) { for (int e = 0; e < kd; ++e) out[e] = dg[e]; return kd; }
+  if (ka >= 0) { for (int e = 0; e < ka; ++e) out[e] = an[e]; return ka; }
+  const double w1 = s1 + 1.0, w2 = s2 + 1.0;
+  int ne = 0;
+  for (int c = 0; c < 2; ++c) {
+    const int j = Et[c];
+    const double q1 = y.v[1][c][0], q2 = y.v[1][c][1], t1 = y.tr[1][c][0], t2 = y.tr[1][c][1];
+    const double e2 = (q2 - w1 * q1) / (w2 - w1);
+    const double e1 = q1 - e2;
+    const double u2 = (t2 + w1 * t1) / (w2 - w1);
+    const double u1 = t1 + u2;
+    est[ne++] = Est{s1, j, e1, u1};
+    est[ne++] = Est{s2, j, e2, u2};
+  }
+  const int k = accept(est, ne, Er, s, Et, t, y);
   for (int e = 0; e < k; ++e) out[e] = est[e];
   return k;
 }
@@ -380,6 +382,30 @@ __device__ double block_dot(const DecodeArgs& a, int b, int i, int j, int l_beg,
   const double r = red[0];
   __syncthreads();
   return r;
+}
+
+// a lane's terms of that product over l_beg .. l_end, by one wavefront
+__device__ double wave_dot(const DecodeArgs& a, int b, int i, int j, int l_beg, int l_end) {
+  double s = 0.0;
+  constexpr int U = 8;
+  for (int l0 = l_beg + (int)(threadIdx.x & 63); l0 < l_end; l0 += U * 64) {
+    double x[U], y[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int l = min(l0 + u * 64, l_end - 1);
+      x[u] = load_elem(a.A, a.p.dtype, a_index(a, b, i, l));
+      y[u] = load_elem(a.B, a.p.dtype, b_index(a, b, l, j));
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (l0 + u * 64 < l_end) s = fma(x[u], y[u], s);
+  }
+  return s;
+}
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
 }
 
 // Theorem 2 (Appendix B): min(s, t) <= 2 < max(s, t).  The at most two flagged lines of the
@@ -501,27 +527,32 @@ __device__ int known_lines_correct(const DecodeArgs& a, int b, DecodeState* st, 
 }
 
 // What Section V step 2 makes of the flagged lines: thread 0 fills fix[0 .. *nfix); *nfix = -1: the rule does
-// not apply or failed.
-__device__ void plan_fixes(const DecodeArgs& a, int b, const DecodeState* st, int final_pass, Est* fix, int* nfix) {
-  if (threadIdx.x != 0) return;
-  const int n = a.p.n, m = a.p.m, s = st->s_cnt, t = st->t_cnt;
-  *nfix = -1;
-  if (s == 0 && t == 0) {
-    *nfix = 0;
-  } else if (s >= 1 && s <= 2 && t >= 1 && t <= 2 && (a.p.weighted || (s == 1 && t == 1))) {
-    __shared__ int Er[2], Et[2];
-    for (int x = 0; x < s; ++x) Er[x] = st->rows[x];
-    for (int x = 0; x < t; ++x) Et[x] = st->cols[x];
-    sort_small(Er, s);
-    sort_small(Et, t);
-    const double* sy = synd_of(a, b);
-    const double* al = final_pass ? allow_of(a, b) : nullptr;
-    Synd y{sy, sy + n, sy + 2 * n, sy + 2 * n + m, a.p.tau_r1, a.p.tau_r2, a.p.tau_q1, a.p.tau_q2,
-           al, al ? al + n : nullptr, al ? al + 2 * n : nullptr, al ? al + 2 * n + m : nullptr,
-           a.p.tau_rel, a.p.weighted != 0};
-    const int k = d0_correct(fix, Er, s, Et, t, y);
-    if (k >= 0) *nfix = k;
+// not apply or failed.  By all threads of the workgroup (the flagged lines' syndromes are loaded side by side, past the caches:
+// other workgroups of the launch may have written them), which meet at a barrier before they read fix and *nfix.
+__device__ void plan_fixes(const DecodeArgs& a, int b, int s, int t, const int* rows, const int* cols, int final_pass, Est* fix, int* nfix) {
+  const int n = a.p.n, m = a.p.m;
+  if (!(s >= 1 && s <= 2 && t >= 1 && t <= 2 && (a.p.weighted || (s == 1 && t == 1)))) {
+    if (threadIdx.x == 0) *nfix = s == 0 && t == 0 ? 0 : -1;
+    return;
   }
+  __shared__ int E[2][2];
+  __shared__ FlagSynd y;
+  if (threadIdx.x < 8) {
+    const int col = threadIdx.x >> 2, at = (threadIdx.x >> 1) & 1, kind = threadIdx.x & 1;
+    const int cnt = col ? t : s, *list = col ? cols : rows;
+    if (at < cnt) {
+      const int x0 = list[0], x1 = list[cnt - 1], line = at == 0 ? min(x0, x1) : max(x0, x1);
+      const int64_t idx = (col ? 2 * (int64_t)n : 0) + (kind ? (col ? m : n) : 0) + line;
+      const double v = load_dev(synd_of(a, b) + idx), al = final_pass ? load_dev(allow_of(a, b) + idx) : 0.0;
+      const double tau = col ? (kind ? a.p.tau_q2 : a.p.tau_q1) : (kind ? a.p.tau_r2 : a.p.tau_r1);
+      y.v[col][at][kind] = v;
+      y.tr[col][at][kind] = tau + al + a.p.tau_rel * fabs(v);
+      E[col][at] = line;
+    }
+    if (threadIdx.x == 0) y.wt = a.p.weighted != 0;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) *nfix = d0_correct(fix, E[0], s, E[1], t, y);
 }
 
 __device__ void give_up(DecodeState* st, gecc_report* rep) {
@@ -542,7 +573,7 @@ __device__ void apply_fixes(const DecodeArgs& a, int b, DecodeState* st, gecc_re
       const double d = dots ? dots[e] : block_dot(a, b, fix[e].i, fix[e].j, 0, a.p.k, pool);
       if (threadIdx.x == 0) C[idx] = (float)d;
     } else if (threadIdx.x == 0) {
-      C[idx] = (float)((double)C[idx] - fix[e].x);
+      C[idx] = (float)((double)load_dev(C + idx) - fix[e].x);
     }
   }
   if (threadIdx.x == 0) {
@@ -582,6 +613,8 @@ __device__ void decode_c_body(const DecodeArgs& a, int b, DecodeState* st, gecc_
     // otherwise pass for a row full of small errors of C.
     // (single-checksum mode: one known line only, any number of the other kind -- Appendix A, case s = 1)
     if (final_pass && (a.p.weighted ? (lo >= 1 && lo <= 2 && hi > 2) : (lo == 1 && hi >= 2))) {
+      // (the launch's other workgroups have written through what this reads, by all of its lines)
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
       const double* sy = synd_of(a, b);
       const double* al = final_pass ? allow_of(a, b) : nullptr;
       const Synd y{sy, sy + n, sy + 2 * n, sy + 2 * n + m, a.p.tau_r1, a.p.tau_r2, a.p.tau_q1, a.p.tau_q2,
@@ -602,7 +635,7 @@ __device__ void decode_c_body(const DecodeArgs& a, int b, DecodeState* st, gecc_
       return;
     }
   }
-  plan_fixes(a, b, st, final_pass, fix, &nfix);
+  plan_fixes(a, b, st->s_cnt, st->t_cnt, st->rows, st->cols, final_pass, fix, &nfix);
   __syncthreads();
   const int k = nfix;
   if (k < 0) {
@@ -633,13 +666,10 @@ __global__ __launch_bounds__(DC_THREADS) void decode_c_kernel(DecodeArgs a, int 
 // ---- operand audit -----------------------------------------------------------------------------
 // A single wrong symbol of a line (column l of A, row l of B) shows as (u1, u2) = (e, (pos+1) e)
 // in the difference of re-formed and stored parities.
-__device__ AuditHit audit_line(const double* cur, const double* ref, int k, int l, int len, double tau,
-                               bool wt, bool* hit) {
-  const double u1 = cur[l] - ref[l], u2 = cur[k + l] - ref[k + l];
+__device__ __forceinline__ AuditHit located(double u1, double u2, int l, int len, double tau) {
   AuditHit h;
   h.line = l; h.pos = -1; h.e = u1;
-  *hit = outside(u1, tau) || (wt && outside(u2, tau));
-  if (*hit && fabs(u1) > tau && finite2(u1, u2)) {
+  if (fabs(u1) > tau && finite2(u1, u2)) {
     const double rho = u2 / u1, w = rint(rho);
     if (fabs(rho - w) < 0.25 && w >= 1.0 && w <= (double)len) h.pos = (int)w - 1;
   }
@@ -658,42 +688,74 @@ __device__ void sort_hits(AuditHit* h, int cnt) {
 // Remove the rank-one footprint of every audit hit from C-bar, then patch the operands.
 // Order (it absorbs the cross term when an A hit and a B hit share the index l): rows of the
 // A hits first, using B as the product read it; then columns of the B hits, using the
-// corrected A.  The operands themselves are written last, so nothing here depends on a
-// store becoming visible to another wavefront.
-constexpr int RP_THREADS = 1024;   // one workgroup per batch item: latency-bound loops, so a full one
-constexpr int RP_U = 4;            // symbols (lines) a thread has in flight
+// corrected A.
+//
+// Several workgroups share an item: each owns a slice of the columns (threads 0 .. RP_LINES - 1) and a slice of the
+// rows (the others), finds the hits for itself and takes every hit's footprint out of its own lines.  A column of
+// C or of A is a line of memory per row, and one compute unit keeps a few dozen of them on their way.  Between event pairs, one
+// workgroup -> sixteen at 4096^3 bf16: an error of A 28.3 -> 20.5 us, of B 49.4 -> 21.5, of both 53.3 -> 24.4; 256 items of 512^3
+// fp32 keep one workgroup each, 35.6 -> 32.0, since a load then waits for another and not for its turn.  What is left is that chain,
+// and where a symbol of C is evaluated again the 4096 lines of a column of B by one compute unit (15 us).  What concerns a hit's own line (its sums over all slices) and the symbols where the row of an A hit meets the
+// column of a B hit is left to the workgroup that comes last; it also puts the operands right, which the others read until then.
+constexpr int RP_LINES = 256;
+constexpr int RP_THREADS = 2 * RP_LINES;
+constexpr int RP_WGS = 64;         // workgroups of an item, at most
+struct RepairRecord {              // what a workgroup leaves to the last one
+  double sums[GECC_MAX_ERR][4];    // per hit: its footprint's squares, plain and weighted, and what the line's two sums lose
+  int32_t s, t, bad, reserved;     // lines of its slices that are still flagged; some of them not finite
+  int32_t rows[GECC_MAX_ERR], cols[GECC_MAX_ERR];
+};
 
 // SPLIT (blocked mode: several blocks share an operand line): this launch leaves the operands alone
 // and stops before Section V's second pass; patch_operands_kernel and final_decode_kernel follow.
-template <bool SPLIT>
-__global__ __launch_bounds__(RP_THREADS) void repair_kernel(DecodeArgs a) {
-  const int b = blockIdx.x;
+constexpr int RP_U = 2;            // lines a thread has in flight
+template <int DT, bool SPLIT>
+__global__ __launch_bounds__(RP_THREADS) void repair_kernel(DecodeArgs a, RepairRecord* records, uint32_t* done, int wgs) {
+  const int b = blockIdx.x / wgs, w = blockIdx.x % wgs;
   DecodeState* st = state_of(a, b);
   if (st->phase != PH_AUDIT) return;
   gecc_report* rep = a.report + b;
-  __shared__ double pool[4 * RP_THREADS];
-  __shared__ int ok, cnt_a, cnt_b;
-  __shared__ AuditHit ha[GECC_MAX_ERR], hb[GECC_MAX_ERR];
+  __shared__ double pool[POOL_DOUBLES];
+  __shared__ int ok, cnt_a, cnt_b, flag;
+  __shared__ AuditHit hit[2 * GECC_MAX_ERR];           // of A, then of B
+  __shared__ double own[GECC_MAX_ERR][5];              // per hit: its line's two syndromes, the parities it meets, the wrong symbol
+  __shared__ double cross[GECC_MAX_ERR * GECC_MAX_ERR / 4][3];   // where A hit x meets B hit y: C, the symbols of B and of A
+  __shared__ RepairRecord mine;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n = a.p.n, m = a.p.m, k = a.p.k;
-  if (threadIdx.x == 0) { cnt_a = 0; cnt_b = 0; }
+  AuditHit *ha = hit, *hb = hit + GECC_MAX_ERR;
+  if (tid == 0) { cnt_a = 0; cnt_b = 0; mine.s = 0; mine.t = 0; mine.bad = 0; }
   __syncthreads();
   {   // difference of the re-formed and the stored operand parities, line by line
     const double* cur_a = a.audit_a + (int64_t)item_i(a, b) * 2 * k;
     const double* cur_b = a.audit_b + (int64_t)item_j(a, b) * 2 * k;
     const double* ref_a = apar_of(a, b);
     const double* ref_b = bpar_of(a, b);
-#pragma unroll 4
-    for (int l = threadIdx.x; l < k; l += blockDim.x) {
-      bool hit;
-      AuditHit h = audit_line(cur_a, ref_a, k, l, n, a.p.tau_op, a.p.weighted != 0, &hit);
-      if (hit) { const int idx = atomicAdd(&cnt_a, 1); if (idx < GECC_MAX_ERR) ha[idx] = h; }
-      h = audit_line(cur_b, ref_b, k, l, m, a.p.tau_op, a.p.weighted != 0, &hit);
-      if (hit) { const int idx = atomicAdd(&cnt_b, 1); if (idx < GECC_MAX_ERR) hb[idx] = h; }
+    const bool wt = a.p.weighted != 0;
+    constexpr int U = 2;
+    for (int l0 = tid; l0 < k; l0 += U * RP_THREADS) {
+      double d[U][4];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int l = min(l0 + u * RP_THREADS, k - 1);
+        d[u][0] = cur_a[l] - ref_a[l]; d[u][1] = cur_a[k + l] - ref_a[k + l];
+        d[u][2] = cur_b[l] - ref_b[l]; d[u][3] = cur_b[k + l] - ref_b[k + l];
+      }
+#pragma unroll 1
+      for (int x = 0; x < 2 * U; ++x) {
+        const int l = l0 + (x >> 1) * RP_THREADS;
+        const double u1 = x == 0 ? d[0][0] : x == 1 ? d[0][2] : x == 2 ? d[1][0] : d[1][2];
+        const double u2 = x == 0 ? d[0][1] : x == 1 ? d[0][3] : x == 2 ? d[1][1] : d[1][3];
+        if (l < k && (outside(u1, a.p.tau_op) || (wt && outside(u2, a.p.tau_op)))) {
+          const int idx = atomicAdd(x & 1 ? &cnt_b : &cnt_a, 1);
+          if (idx < GECC_MAX_ERR) hit[(x & 1) * GECC_MAX_ERR + idx] = located(u1, u2, l, x & 1 ? m : n, a.p.tau_op);
+        }
+      }
     }
   }
   __syncthreads();
   const int na = cnt_a, nb = cnt_b;
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     ok = na + nb <= GECC_MAX_ERR;       // no hit at all: the pattern lies in C-bar alone (second pass below)
     // single-checksum mode: one parity names the line of a wrong operand symbol, not its place in it
     if (!a.p.weighted && na + nb > 0) ok = 0;
@@ -705,204 +767,245 @@ __global__ __launch_bounds__(RP_THREADS) void repair_kernel(DecodeArgs a) {
   }
   __syncthreads();
   if (!ok) {
-    if (threadIdx.x == 0) give_up(st, rep);
+    // (every workgroup comes to this; the last one says so, when none is left that has not read the phase)
+    const bool last = wgs == 1 || arrive_last(done + b, (uint32_t)wgs, &flag);
+    if (last && tid == 0) give_up(st, rep);
     return;
   }
   float* C = c_of(a, b);
   double* cpar = cpar_of(a, b);
-  const double* apar = apar_of(a, b);
-  const double* bpar = bpar_of(a, b);
   // threshold allowances of the lines a repair touches (rounding noise of the corrupted terms)
   double* al_r1 = allow_of(a, b);
-  double* al_r2 = al_r1 + n;
-  double* al_q1 = al_r1 + 2 * n;
-  double* al_q2 = al_r1 + 2 * n + m;
   const double cc = a.p.tau_rep * sqrt((double)k);
   // residual syndromes: every repair below also moves the syndromes by exactly what it changes
   // (the stored symbols' differences and the parity symbols), so that Section V can run again
   // without another pass over C
   double* sy_r1 = synd_of(a, b);
-  double* sy_r2 = sy_r1 + n;
-  double* sy_q1 = sy_r1 + 2 * n;
-  double* sy_q2 = sy_r1 + 2 * n + m;
-  double (*red)[RP_THREADS] = reinterpret_cast<double (*)[RP_THREADS]>(pool);
-  for (int o = threadIdx.x; o < 2 * n + 2 * m; o += blockDim.x) al_r1[o] = 0.0;
-  __syncthreads();
-  for (int x = 0; x < na; ++x) {
-    const int i = ha[x].pos, l = ha[x].line;
-    const double e = ha[x].e;
-    if (threadIdx.x == 0) {
-      cpar[i] -= e * bpar[l];              // cbar_{i,m+1}
-      cpar[n + i] -= e * bpar[k + l];      // cbar_{i,m+2}
-    }
-    double s2 = 0.0, w2 = 0.0, ds = 0.0, dw = 0.0;
-    // (RP_U symbols per thread at a time: all their loads are issued before the first store, one
-    // workgroup has nothing else to hide the memory latency with)
-    for (int j0 = threadIdx.x; j0 < m; j0 += RP_U * RP_THREADS) {
-      float cold[RP_U];
-      double bv[RP_U], q1[RP_U], q2[RP_U], g1[RP_U], g2[RP_U];
-#pragma unroll
-      for (int u = 0; u < RP_U; ++u) {
-        const int j = min(j0 + u * RP_THREADS, m - 1);
-        cold[u] = C[(int64_t)i * a.p.ldc + j];
-        bv[u] = load_elem(a.B, a.p.dtype, b_index(a, b, l, j));
-        q1[u] = sy_q1[j]; q2[u] = sy_q2[j]; g1[u] = al_q1[j]; g2[u] = al_q2[j];
-      }
-#pragma unroll
-      for (int u = 0; u < RP_U; ++u) {
-        const int j = j0 + u * RP_THREADS;
-        if (j >= m) break;
-        const double f = e * bv[u];
-        const float cnew = (float)((double)cold[u] - f);
-        C[(int64_t)i * a.p.ldc + j] = cnew;
-        const double d = (double)cold[u] - (double)cnew;   // what the sums of row i and column j lose
-        sy_q1[j] = q1[u] - d;
-        sy_q2[j] = q2[u] - (double)(i + 1) * d;
-        ds += d;
-        dw += (double)(j + 1) * d;
-        s2 += f * f;
-        w2 += (double)(j + 1) * (j + 1) * f * f;
-        al_q1[j] = g1[u] + cc * fabs(f);
-        al_q2[j] = g2[u] + cc * (double)(i + 1) * fabs(f);
-      }
-    }
-    red[0][threadIdx.x] = s2; red[1][threadIdx.x] = w2; red[2][threadIdx.x] = ds; red[3][threadIdx.x] = dw;
-    __syncthreads();
-    for (int w = RP_THREADS / 2; w > 0; w >>= 1) {
-      if ((int)threadIdx.x < w)
-        for (int q = 0; q < 4; ++q) red[q][threadIdx.x] += red[q][threadIdx.x + w];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-      al_r1[i] += cc * sqrt(red[0][0]); al_r2[i] += cc * sqrt(red[1][0]);
-      sy_r1[i] += e * bpar[l] - red[2][0];          // sum - parity: both moved
-      sy_r2[i] += e * bpar[k + l] - red[3][0];
-    }
-    __syncthreads();
-  }
-  for (int x = 0; x < nb; ++x) {
-    const int l = hb[x].line, j = hb[x].pos;
-    const double e = hb[x].e;
-    if (threadIdx.x == 0) {
-      cpar[2 * n + j] -= apar[l] * e;          // cbar_{n+1,j}
-      cpar[2 * n + m + j] -= apar[k + l] * e;  // cbar_{n+2,j}
-    }
-    double s2 = 0.0, w2 = 0.0, ds = 0.0, dw = 0.0;
-    for (int i0 = threadIdx.x; i0 < n; i0 += RP_U * RP_THREADS) {
-      float cold[RP_U];
-      double av[RP_U], r1[RP_U], r2[RP_U], g1[RP_U], g2[RP_U];
-#pragma unroll
-      for (int u = 0; u < RP_U; ++u) {
-        const int i = min(i0 + u * RP_THREADS, n - 1);
-        cold[u] = C[(int64_t)i * a.p.ldc + j];
-        av[u] = load_elem(a.A, a.p.dtype, a_index(a, b, i, l));
-        r1[u] = sy_r1[i]; r2[u] = sy_r2[i]; g1[u] = al_r1[i]; g2[u] = al_r2[i];
-      }
-#pragma unroll
-      for (int u = 0; u < RP_U; ++u) {
-        const int i = i0 + u * RP_THREADS;
-        if (i >= n) break;
-        double ai = av[u];
-        for (int z = 0; z < na; ++z)
-          if (ha[z].pos == i && ha[z].line == l) ai -= ha[z].e;   // corrected A
-        const double f = ai * e;
-        const float cnew = (float)((double)cold[u] - f);
-        C[(int64_t)i * a.p.ldc + j] = cnew;
-        const double d = (double)cold[u] - (double)cnew;
-        sy_r1[i] = r1[u] - d;
-        sy_r2[i] = r2[u] - (double)(j + 1) * d;
-        ds += d;
-        dw += (double)(i + 1) * d;
-        s2 += f * f;
-        w2 += (double)(i + 1) * (i + 1) * f * f;
-        al_r1[i] = g1[u] + cc * fabs(f);
-        al_r2[i] = g2[u] + cc * (double)(j + 1) * fabs(f);
-      }
-    }
-    red[0][threadIdx.x] = s2; red[1][threadIdx.x] = w2; red[2][threadIdx.x] = ds; red[3][threadIdx.x] = dw;
-    __syncthreads();
-    for (int w = RP_THREADS / 2; w > 0; w >>= 1) {
-      if ((int)threadIdx.x < w)
-        for (int q = 0; q < 4; ++q) red[q][threadIdx.x] += red[q][threadIdx.x + w];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-      al_q1[j] += cc * sqrt(red[0][0]); al_q2[j] += cc * sqrt(red[1][0]);
-      sy_q1[j] += apar[l] * e - red[2][0];
-      sy_q2[j] += apar[k + l] * e - red[3][0];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    for (int x = 0; x < na && !SPLIT; ++x) {
-      const int64_t ia = a_index(a, b, ha[x].pos, ha[x].line);
-      store_elem(a.A, a.p.dtype, ia, load_elem(a.A, a.p.dtype, ia) - ha[x].e);
-    }
-    for (int x = 0; x < nb && !SPLIT; ++x) {
-      const int64_t ib = b_index(a, b, hb[x].line, hb[x].pos);
-      store_elem(a.B, a.p.dtype, ib, load_elem(a.B, a.p.dtype, ib) - hb[x].e);
-    }
-    // located operand errors, sorted by (matrix, row, col)
-    int ne = 0;
-    for (int x = 0; x < na; ++x) {
-      gecc_err g;
-      g.matrix = GECC_MAT_A; g.row = ha[x].pos; g.col = ha[x].line; g.reserved = 0;
-      g.magnitude = ha[x].e;
-      st->errs[ne++] = g;
-    }
-    for (int x = 1; x < ne; ++x) {           // A hits were ordered by column: reorder by (row, col)
-      const gecc_err key = st->errs[x];
-      int y = x - 1;
-      while (y >= 0 && (st->errs[y].row > key.row ||
-                        (st->errs[y].row == key.row && st->errs[y].col > key.col))) {
-        st->errs[y + 1] = st->errs[y];
-        --y;
-      }
-      st->errs[y + 1] = key;
-    }
-    for (int x = 0; x < nb; ++x) {           // B hits are ordered by row l; one hit per row
-      gecc_err g;
-      g.matrix = GECC_MAT_B; g.row = hb[x].line; g.col = hb[x].pos; g.reserved = 0;
-      g.magnitude = hb[x].e;
-      st->errs[ne++] = g;
-    }
-    st->n_err = ne;
-  }
-  // Section V step 1 on the residual syndromes (thresholds widened by the allowances above) ...
-  __shared__ int res_s, res_t, res_bad;
   const bool wt = a.p.weighted != 0;
-  if (threadIdx.x == 0) { res_s = 0; res_t = 0; res_bad = 0; }
-  __syncthreads();
-  for (int o0 = threadIdx.x; o0 < n + m; o0 += 2 * RP_U * RP_THREADS) {
-    double y1[2 * RP_U], y2[2 * RP_U], g1[2 * RP_U], g2[2 * RP_U];
-#pragma unroll
-    for (int u = 0; u < 2 * RP_U; ++u) {
-      const int o = min(o0 + u * RP_THREADS, n + m - 1);
-      // row line o: r1 at [o], r2 at [n + o]; column line j = o - n: q1 at [2n + j], q2 at [2n + m + j]
-      const int p1 = o < n ? o : n + o, p2 = o < n ? n + o : n + m + o;
-      y1[u] = sy_r1[p1]; y2[u] = sy_r1[p2]; g1[u] = al_r1[p1]; g2[u] = al_r1[p2];
+  auto elem = [](const void* P, int64_t idx) { return load_elem(P, DT, idx); };
+  // Section V step 1 on a residual line (threshold widened by the allowance); the first of them go on the list
+  auto test = [&](bool is_row, int o, double y1, double y2, double g1, double g2) {
+    if (outside(y1, (is_row ? a.p.tau_r1 : a.p.tau_q1) + g1) || (wt && outside(y2, (is_row ? a.p.tau_r2 : a.p.tau_q2) + g2))) {
+      const int idx = atomicAdd(is_row ? &mine.s : &mine.t, 1);
+      if (idx < GECC_MAX_ERR) (is_row ? mine.rows : mine.cols)[idx] = o;
     }
+    if (!finite2(y1, wt ? y2 : 0.0)) mine.bad = 1;
+  };
+  // whether line o is the row of an A hit (the column of a B hit)
+  auto own_line = [&](bool is_row, int o) {
+    bool is = false;
+    for (int x = 0; x < (is_row ? na : nb); ++x) is = is || (is_row ? ha : hb)[x].pos == o;
+    return is;
+  };
+  auto hit_at = [&](int z) -> const AuditHit& { return z < na ? ha[z] : hb[z - na]; };
+  // What only the last workgroup needs, but nobody changes before it: loaded here, where the loads of the lines are in flight as well
+  double pre[5];
+  const bool pre_own = tid < na + nb, pre_cross = tid >= 64 && tid < 64 + na * nb;
+  if (pre_own) {
+    const bool za = tid < na;
+    const AuditHit h = hit_at(tid);
+    const double *y = sy_r1 + (za ? 0 : 2 * (int64_t)n) + h.pos, *par = (za ? bpar_of(a, b) : apar_of(a, b)) + h.line;
+    pre[0] = y[0]; pre[1] = y[za ? n : m]; pre[2] = par[0]; pre[3] = par[k];
+    pre[4] = za ? elem(a.A, a_index(a, b, h.pos, h.line)) : elem(a.B, b_index(a, b, h.line, h.pos));
+  }
+  if (pre_cross) {
+    const AuditHit x = ha[(tid - 64) / nb], y = hb[(tid - 64) % nb];
+    pre[0] = (double)C[(int64_t)x.pos * a.p.ldc + y.pos];
+    pre[1] = elem(a.B, b_index(a, b, x.line, y.pos));
+    pre[2] = elem(a.A, a_index(a, b, x.pos, y.line));
+  }
+  const int rows_per = (n + wgs - 1) / wgs, cols_per = (m + wgs - 1) / wgs;
+  const bool by_row = wave >= RP_LINES / 64;
+  const int t0 = by_row ? tid - RP_LINES : tid;
+  const int o_beg = by_row ? min(n, w * rows_per) : min(m, w * cols_per), o_end = by_row ? min(n, o_beg + rows_per) : min(m, o_beg + cols_per);
+  const int nh = by_row ? nb : na;          // hits whose footprint crosses these lines
+  const AuditHit* hits = by_row ? hb : ha;
+  const int len = by_row ? n : m;
+  double* y1p = sy_r1 + (by_row ? 0 : 2 * (int64_t)n);
+  double* g1p = al_r1 + (by_row ? 0 : 2 * (int64_t)n);
+  // (what another workgroup reads is written through)
+  constexpr int HALF_WAVES = RP_LINES / 64;
+  double* red = pool;                       // [halves][hits][4][wavefronts]
+  static_assert(2 * GECC_MAX_ERR * 4 * HALF_WAVES <= POOL_DOUBLES, "sums of the hits");
+  for (int x = 0; x < max(nh, 1); ++x) {    // (one round without a hit: the test and the allowances)
+    const bool last = x + 1 >= nh, some = x < nh;
+    const int pos = some ? hits[x].pos : 0, l = some ? hits[x].line : 0;
+    const double e = some ? hits[x].e : 0.0;
+    double sum[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int o0 = o_beg + t0; o0 < o_end; o0 += RP_U * RP_LINES) {
+      double y1[RP_U], y2[RP_U], g1[RP_U], g2[RP_U], v[RP_U];
+      float cold[RP_U];
 #pragma unroll
-    for (int u = 0; u < 2 * RP_U; ++u) {
-      const int o = o0 + u * RP_THREADS;
-      if (o >= n + m) break;
-      if (o < n) {
-        if (outside(y1[u], a.p.tau_r1 + g1[u]) || (wt && outside(y2[u], a.p.tau_r2 + g2[u]))) {
-          const int idx = atomicAdd(&res_s, 1);
-          if (idx < GECC_MAX_ERR) st->rows[idx] = o;
+      for (int u = 0; u < RP_U; ++u) {
+        const int o = min(o0 + u * RP_LINES, o_end - 1);
+        y1[u] = y1p[o]; y2[u] = y1p[len + o];
+        g1[u] = 0.0; g2[u] = 0.0; v[u] = 0.0; cold[u] = 0.f;
+        if (x > 0) { g1[u] = g1p[o]; g2[u] = g1p[len + o]; }
+        if (some) {
+          cold[u] = C[by_row ? (int64_t)o * a.p.ldc + pos : (int64_t)pos * a.p.ldc + o];
+          v[u] = by_row ? elem(a.A, a_index(a, b, o, l)) : elem(a.B, b_index(a, b, l, o));
         }
-      } else if (outside(y1[u], a.p.tau_q1 + g1[u]) || (wt && outside(y2[u], a.p.tau_q2 + g2[u]))) {
-        const int idx = atomicAdd(&res_t, 1);
-        if (idx < GECC_MAX_ERR) st->cols[idx] = o - n;
       }
-      if (!finite2(y1[u], wt ? y2[u] : 0.0)) res_bad = 1;
+#pragma unroll
+      for (int u = 0; u < RP_U; ++u) {
+        const int o = o0 + u * RP_LINES;
+        if (o >= o_end || own_line(by_row, o)) continue;
+        if (some) {
+          const double f = v[u] * e;
+          const float cnew = (float)((double)cold[u] - f);
+          store_dev(C + (by_row ? (int64_t)o * a.p.ldc + pos : (int64_t)pos * a.p.ldc + o), cnew);
+          const double d = (double)cold[u] - (double)cnew;   // what the sums of the symbol's row and column lose
+          y1[u] -= d;
+          y2[u] -= (double)(pos + 1) * d;
+          g1[u] += cc * fabs(f);
+          g2[u] += cc * (double)(pos + 1) * fabs(f);
+          sum[0] += f * f;
+          sum[1] += (double)(o + 1) * (o + 1) * f * f;
+          sum[2] += d;
+          sum[3] += (double)(o + 1) * d;
+          store_dev(y1p + o, y1[u]);
+          store_dev(y1p + len + o, y2[u]);
+        }
+        store_dev(g1p + o, g1[u]);
+        store_dev(g1p + len + o, g2[u]);
+        if (last) test(by_row, o, y1[u], y2[u], g1[u], g2[u]);
+      }
     }
+    if (!some) break;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) sum[q] += __shfl_down(sum[q], off, 64);
+    if (lane == 0)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) red[(((by_row ? GECC_MAX_ERR : 0) + x) * 4 + q) * HALF_WAVES + (wave % HALF_WAVES)] = sum[q];
+  }
+  if (pre_own)
+#pragma unroll
+    for (int q = 0; q < 5; ++q) own[tid][q] = pre[q];
+  if (pre_cross)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) cross[tid - 64][q] = pre[q];
+  __syncthreads();
+  // the sums of this workgroup: A hits first, then B hits
+  if (tid < 4 * (na + nb)) {
+    const int x = tid >> 2, q = tid & 3;
+    const double* r = red + (((x < na ? x : GECC_MAX_ERR + x - na)) * 4 + q) * HALF_WAVES;
+    static_assert(HALF_WAVES == 4, "wavefronts of a half");
+    mine.sums[x][q] = (r[0] + r[1]) + (r[2] + r[3]);
   }
   __syncthreads();
-  if (threadIdx.x == 0) { st->s_cnt = res_s; st->t_cnt = res_t; st->nonfinite = res_bad; st->phase = PH_REVERIFY; }
+  if (wgs > 1) {
+    static_assert(sizeof(RepairRecord) % 8 == 0 && sizeof(RepairRecord) / 8 <= RP_THREADS, "a word per thread");
+    unsigned long long* out = reinterpret_cast<unsigned long long*>(records + (int64_t)b * wgs + w);
+    if (tid < (int)(sizeof(RepairRecord) / 8)) store_dev(out + tid, reinterpret_cast<const unsigned long long*>(&mine)[tid]);
+    if (!arrive_last(done + b, (uint32_t)wgs, &flag)) return;
+    if (tid == 0) { mine.s = 0; mine.t = 0; mine.bad = 0; }
+    __syncthreads();
+    const RepairRecord* all = records + (int64_t)b * wgs;
+    if (tid < 4 * (na + nb)) {
+      double v[RP_WGS / 4], s = 0.0;
+      for (int r0 = 0; r0 < wgs; r0 += RP_WGS / 4) {
+#pragma unroll
+        for (int r = 0; r < RP_WGS / 4; ++r) v[r] = load_dev(&all[min(r0 + r, wgs - 1)].sums[tid >> 2][tid & 3]);
+#pragma unroll
+        for (int r = 0; r < RP_WGS / 4; ++r) s += r0 + r < wgs ? v[r] : 0.0;
+      }
+      mine.sums[tid >> 2][tid & 3] = s;
+    } else if (tid >= 64 && tid < 64 + wgs) {
+      const RepairRecord& r = all[tid - 64];
+      const int rs = load_dev(&r.s), rt = load_dev(&r.t), rb = load_dev(&r.bad);
+      if (rs > 0) { const int at = atomicAdd(&mine.s, rs); for (int z = 0; z < min(rs, GECC_MAX_ERR) && at + z < GECC_MAX_ERR; ++z) mine.rows[at + z] = load_dev(&r.rows[z]); }
+      if (rt > 0) { const int at = atomicAdd(&mine.t, rt); for (int z = 0; z < min(rt, GECC_MAX_ERR) && at + z < GECC_MAX_ERR; ++z) mine.cols[at + z] = load_dev(&r.cols[z]); }
+      if (rb) mine.bad = 1;
+    }
+    __syncthreads();
+  }
+  if (tid == 0) {
+    // The lines of the hits.  pool[4 z ..]: residuals and allowances of the line of hit z, kept at the first hit of that line
+    auto first_at = [&](int z) {
+      int x = z < na ? 0 : na;
+      while (hit_at(x).pos != hit_at(z).pos) ++x;
+      return x;
+    };
+    for (int z = 0; z < na + nb; ++z) { double* X = pool + 4 * z; X[0] = own[z][0]; X[1] = own[z][1]; X[2] = 0.0; X[3] = 0.0; }
+    // first the symbols where the row of an A hit meets the column of a B hit, which nobody has touched
+    for (int xy = 0; xy < na * nb; ++xy) {
+      const int x = xy / nb, y = na + xy % nb;
+      if (first_at(x) != x || first_at(y) != y) continue;
+      const int i = hit_at(x).pos, j = hit_at(y).pos;
+      float v = (float)cross[xy][0];
+      // (for an A hit the column is the crossed line and the row its own, for a B hit the other way round)
+      for (int z = 0; z < na + nb; ++z) {
+        const bool za = z < na;
+        const AuditHit h = hit_at(z);
+        if (first_at(z) != (za ? x : y)) continue;
+        double val = za ? cross[z * nb + y - na][1] : cross[x * nb + z - na][2];
+        for (int q = 0; q < na && !za; ++q)
+          if (ha[q].pos == i && ha[q].line == h.line) val -= ha[q].e;         // A as corrected
+        const double f = val * h.e;
+        const float cnew = (float)((double)v - f);
+        const double d = (double)v - (double)cnew;
+        v = cnew;
+        double* X = pool + 4 * (za ? y : x);
+        const int at = za ? i : j, other = za ? j : i;
+        X[0] -= d;
+        X[1] -= (double)(at + 1) * d;
+        X[2] += cc * fabs(f);
+        X[3] += cc * (double)(at + 1) * fabs(f);
+        double* S = mine.sums[z];
+        S[0] += f * f;
+        S[1] += (double)(other + 1) * (other + 1) * f * f;
+        S[2] += d;
+        S[3] += (double)(other + 1) * d;
+      }
+      store_dev(C + (int64_t)i * a.p.ldc + j, v);
+    }
+    for (int z = 0; z < na + nb; ++z) {
+      const bool za = z < na;
+      const AuditHit h = hit_at(z);
+      const double p1 = own[z][2] * h.e, p2 = own[z][3] * h.e, *S = mine.sums[z];
+      double* cp = cpar + (za ? 0 : 2 * (int64_t)n) + h.pos;
+      cp[0] -= p1;                           // cbar_{i,m+1} (cbar_{n+1,j})
+      cp[za ? n : m] -= p2;                  // cbar_{i,m+2} (cbar_{n+2,j})
+      double* X = pool + 4 * first_at(z);
+      X[0] += p1 - S[2];                     // sum - parity: both moved
+      X[1] += p2 - S[3];
+      X[2] += cc * sqrt(S[0]);
+      X[3] += cc * sqrt(S[1]);
+    }
+    // ... Section V step 1 on them, the operands, and the located errors, sorted by (matrix, row, col)
+    for (int z = 0; z < na + nb; ++z) {
+      const bool za = z < na;
+      const AuditHit h = hit_at(z);
+      if (first_at(z) == z) {
+        const double* X = pool + 4 * z;
+        double *y = sy_r1 + (za ? 0 : 2 * (int64_t)n) + h.pos, *g = al_r1 + (za ? 0 : 2 * (int64_t)n) + h.pos;
+        const int step = za ? n : m;
+        store_dev(y, X[0]); store_dev(y + step, X[1]); store_dev(g, X[2]); store_dev(g + step, X[3]);
+        test(za, h.pos, X[0], X[1], X[2], X[3]);
+      }
+      if (!SPLIT) {
+        if (za) store_elem(a.A, DT, a_index(a, b, h.pos, h.line), own[z][4] - h.e);
+        else    store_elem(a.B, DT, b_index(a, b, h.line, h.pos), own[z][4] - h.e);
+      }
+      // (A hits are ordered by column, B hits by row; one hit per row of B)
+      gecc_err g;
+      g.matrix = za ? GECC_MAT_A : GECC_MAT_B; g.row = za ? h.pos : h.line; g.col = za ? h.line : h.pos; g.reserved = 0;
+      g.magnitude = h.e;
+      int at = z;
+      for (int q = 0; q < na && za; ++q) at += q > z && ha[q].pos < h.pos ? 1 : q < z && ha[q].pos > h.pos ? -1 : 0;
+      st->errs[at] = g;
+    }
+    st->n_err = na + nb;
+    for (int x = 0; x < min(mine.s, GECC_MAX_ERR); ++x) st->rows[x] = mine.rows[x];
+    for (int x = 0; x < min(mine.t, GECC_MAX_ERR); ++x) st->cols[x] = mine.cols[x];
+    st->s_cnt = mine.s; st->t_cnt = mine.t; st->nonfinite = mine.bad; st->phase = PH_REVERIFY;
+  }
+  // ... and Section V step 2 on what is left, by the first DC_THREADS threads (the other wavefronts end here)
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // (it loads some of this past the caches)
   __syncthreads();
-  // ... and step 2, by the first DC_THREADS threads (the other wavefronts end here)
-  if (SPLIT || threadIdx.x >= DC_THREADS) return;
+  if (SPLIT || tid >= DC_THREADS) return;
   decode_c_body(a, b, st, rep, 1, pool);
 }
 
@@ -915,7 +1018,8 @@ __global__ __launch_bounds__(RP_THREADS) void repair_kernel(DecodeArgs a) {
 // A symbol of C that is evaluated again is a dot product whose one operand lies in memory with a stride: a
 // line per term, of which one compute unit keeps a few dozen on their way (k = 4096: 25 us a symbol).
 // The first workgroups of the item share it out, at least FINISH_TERMS terms each; the one that comes last
-// adds the shares up in order and patches.
+// adds the shares up, a lane each, and patches (two symbols at 16384 x 4096 x 14336, rocprofv3: by one thread and with a workgroup for
+// one symbol after the other 25.2 us, now 15).
 // A closed launch lasts as long as its dispatch, about 2 us per thousand workgroups (the caller keeps very
 // large pairs out).  Walking the rest with a grid that fits the chip was measured and is not kept: the
 // compiler then holds what every scan needs across the walk (226 registers instead of 168, and audits that
@@ -972,27 +1076,28 @@ __global__ __launch_bounds__(DC_THREADS, 3) void finish_kernel(FinishArgs) {
   const int per_item = f.audits.j[0].gx * f.audits.j[0].gy + f.audits.j[1].gx * f.audits.j[1].gy;
   const int shares = a.p.refine ? max(1, min(min(per_item, FINISH_SHARES), a.p.k / FINISH_TERMS)) : 1;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    plan_fixes(a, o.b, st, 0, fix, &nfix);
+  plan_fixes(a, o.b, st->s_cnt, st->t_cnt, st->rows, st->cols, 0, fix, &nfix);
+  if (threadIdx.x == 0)
     act = !st->nonfinite && nfix < 0 ? AUDIT : o.q == 0 || (!st->nonfinite && nfix > 0 && o.q < shares) ? PATCH : NOTHING;
-  }
   __syncthreads();
   const int todo = act;
   if (todo == NOTHING) return;
   bool writes = o.q == 0;
   const bool dot = todo == PATCH && !st->nonfinite && nfix > 0 && shares > 1;
   if (dot) {
+    // a wavefront per symbol; the shares are added up by its lanes, in a fixed order
+    static_assert(DC_THREADS / 64 >= 4 && FINISH_SHARES == 64, "a wavefront per fix, a lane per share");
     double* mine = f.shares + (int64_t)o.b * 2 * a.p.k;
     const int per = (a.p.k + shares - 1) / shares, l0 = min(a.p.k, o.q * per), l1 = min(a.p.k, l0 + per);
-    for (int e = 0; e < nfix; ++e) {
-      const double d = l0 < l1 ? block_dot(a, o.b, fix[e].i, fix[e].j, l0, l1, lds) : 0.0;
-      if (threadIdx.x == 0) store_dev(mine + e * shares + o.q, d);
+    const int e = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (e < nfix) {
+      const double d = wave_sum(wave_dot(a, o.b, fix[e].i, fix[e].j, l0, l1));
+      if (lane == 0) store_dev(mine + e * shares + o.q, d);
     }
     writes = arrive_last(f.share_done + o.b, (uint32_t)shares, &flag);
-    if (writes && (int)threadIdx.x < nfix) {
-      double d = 0.0;
-      for (int q = 0; q < shares; ++q) d += load_dev(mine + threadIdx.x * shares + q);
-      dots[threadIdx.x] = d;
+    if (writes && e < nfix) {
+      const double d = wave_sum(lane < shares ? load_dev(mine + e * shares + lane) : 0.0);
+      if (lane == 0) dots[e] = d;
     }
     __syncthreads();
   }
@@ -1023,9 +1128,11 @@ __global__ __launch_bounds__(256) void patch_operands_kernel(DecodeArgs a, int n
   if (threadIdx.x == 0) cnt = 0;
   __syncthreads();
   for (int l = threadIdx.x; l < k; l += blockDim.x) {
-    bool hit;
-    const AuditHit x = audit_line(cur, ref, k, l, len, a.p.tau_op, true, &hit);
-    if (hit) { const int idx = atomicAdd(&cnt, 1); if (idx < GECC_MAX_ERR) h[idx] = x; }
+    const double u1 = cur[l] - ref[l], u2 = cur[k + l] - ref[k + l];
+    if (outside(u1, a.p.tau_op) || outside(u2, a.p.tau_op)) {
+      const int idx = atomicAdd(&cnt, 1);
+      if (idx < GECC_MAX_ERR) h[idx] = located(u1, u2, l, len, a.p.tau_op);
+    }
   }
   __syncthreads();
   if (threadIdx.x != 0 || cnt == 0 || cnt > GECC_MAX_ERR) return;
@@ -1215,8 +1322,23 @@ hipError_t launch_decode_c(const DecodeArgs& a, int with_summary, hipStream_t st
   return hipGetLastError();
 }
 
-hipError_t launch_repair(const DecodeArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(repair_kernel<false>, dim3(a.p.batch), dim3(RP_THREADS), 0, st, a);
+// Workgroups of an item in the repair: one per RP_LINES rows and columns, at most 256 in all (a closed launch lasts as long
+// as its dispatch), as many as there are records and counters for
+static int repair_wgs(const DecodeArgs& a, const RepairScratch& s) {
+  const int len = a.p.n > a.p.m ? a.p.n : a.p.m;
+  int wgs = (len + RP_LINES - 1) / RP_LINES;
+  if (wgs > RP_WGS) wgs = RP_WGS;
+  if ((int64_t)wgs * a.p.batch > 256) wgs = 256 / a.p.batch;
+  while (wgs > 1 && (size_t)wgs * a.p.batch * sizeof(RepairRecord) > s.bytes) --wgs;
+  return wgs > 1 && a.p.batch <= s.counters ? wgs : 1;
+}
+
+hipError_t launch_repair(const DecodeArgs& a, const RepairScratch& s, hipStream_t st) {
+  const int wgs = repair_wgs(a, s);
+  const dim3 grid((unsigned)wgs * a.p.batch);
+  RepairRecord* records = static_cast<RepairRecord*>(s.records);
+  if (a.p.dtype == GECC_BF16) hipLaunchKernelGGL((repair_kernel<GECC_BF16, false>), grid, dim3(RP_THREADS), 0, st, a, records, s.done, wgs);
+  else                        hipLaunchKernelGGL((repair_kernel<GECC_F32, false>), grid, dim3(RP_THREADS), 0, st, a, records, s.done, wgs);
   return hipGetLastError();
 }
 
@@ -1228,8 +1350,12 @@ hipError_t launch_finish(const DecodeArgs& a, const PairArgs& audits, uint32_t* 
   return hipGetLastError();
 }
 
-hipError_t launch_repair_blocked(const DecodeArgs& a, int nbi, hipStream_t st) {
-  hipLaunchKernelGGL(repair_kernel<true>, dim3(a.p.batch), dim3(RP_THREADS), 0, st, a);
+hipError_t launch_repair_blocked(const DecodeArgs& a, const RepairScratch& s, int nbi, hipStream_t st) {
+  const int wgs = repair_wgs(a, s);
+  const dim3 grid((unsigned)wgs * a.p.batch);
+  RepairRecord* records = static_cast<RepairRecord*>(s.records);
+  if (a.p.dtype == GECC_BF16) hipLaunchKernelGGL((repair_kernel<GECC_BF16, true>), grid, dim3(RP_THREADS), 0, st, a, records, s.done, wgs);
+  else                        hipLaunchKernelGGL((repair_kernel<GECC_F32, true>), grid, dim3(RP_THREADS), 0, st, a, records, s.done, wgs);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(patch_operands_kernel, dim3(nbi + a.nbj), dim3(256), 0, st, a, nbi);

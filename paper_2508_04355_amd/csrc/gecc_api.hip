@@ -932,6 +932,9 @@ int correct_impl(gecc_ctx* ctx, void* dev_A, const double* dev_A_par, void* dev_
                  float* dev_C, double* dev_C_par, gecc_report* dev_report, int with_summary, hipStream_t st) {
   DecodeArgs d = decode_args(ctx, dev_A, dev_A_par, dev_B, dev_B_par, dev_C, dev_C_par, dev_report);
   const int32_t* gate = &d.state->phase;
+  // (the repair comes when no scan has anything left in its scratch, 16 bytes a line at the least)
+  const RepairScratch scratch{ctx->ws + ctx->lay.scan_a, ctx->lay.ksplit - ctx->lay.scan_a,
+                              reinterpret_cast<uint32_t*>(ctx->ws + ctx->lay.done), SCAN_DONE_WORDS};
   hipError_t e;
   // operand audit: re-form the parities of A and B as the product read them
   // (an encoding made by the tile scan is re-formed by the tile scan: same sums, same order)
@@ -953,7 +956,7 @@ int correct_impl(gecc_ctx* ctx, void* dev_A, const double* dev_A_par, void* dev_
         if ((e = ta.done(td.done(launch_finish(d, pair, q.done() + words, with_summary, st)))) != hipSuccess) return hip_rc(e);
       }
       Timed t(ctx, GECC_K_REPAIR, st);
-      return hip_rc(t.done(launch_repair(d, st)));
+      return hip_rc(t.done(launch_repair(d, scratch, st)));
     }
   }
   // Section V step 2 on the flagged lines; on failure the phase becomes PH_AUDIT
@@ -986,7 +989,7 @@ int correct_impl(gecc_ctx* ctx, void* dev_A, const double* dev_A_par, void* dev_
                    scan_b_over_m(&vb, dev_B, nullptr, const_cast<double*>(d.audit_b), gw), GECC_K_AUDIT_B)) != hipSuccess)
       return hip_rc(e);
     Timed t(ctx, GECC_K_REPAIR, st);
-    return hip_rc(t.done(launch_repair_blocked(d, ctx->nbi, st)));
+    return hip_rc(t.done(launch_repair_blocked(d, scratch, ctx->nbi, st)));
   }
   // (the coldot of the two first, so that the rowdot carries its second stage)
   if (tile) {
@@ -1001,7 +1004,7 @@ int correct_impl(gecc_ctx* ctx, void* dev_A, const double* dev_A_par, void* dev_
   // parity differences, operand patches, rank-one repair of C-bar with the residual syndromes
   // kept up to date, then Section V once more -- all in one workgroup per batch item
   Timed t(ctx, GECC_K_REPAIR, st);
-  return hip_rc(t.done(launch_repair(d, st)));
+  return hip_rc(t.done(launch_repair(d, scratch, st)));
 }
 
 }  // namespace

@@ -432,12 +432,14 @@ struct BlockedParityArgs {
   int32_t* gate_word;
 };
 hipError_t launch_blocked_parities(const BlockedParityArgs& a, hipStream_t st);
+// what the workgroups of a repair leave to the last one of their item: `bytes` for it, and zeroed counters
+struct RepairScratch { void* records; size_t bytes; uint32_t* done; int counters; };
 // fp64 parities [lines][2][k] -> operand-type rows [(line * 2 + t) * pieces + s][k] (k contiguous)
 hipError_t launch_split_parities(const double* par, void* W, int dtype, int lines, int k, int pieces, int rows_padded, hipStream_t st);
 // blocked mode: per-block syndromes and flags from the sub-tile partial sums
 hipError_t launch_threshold_blocked(const DecodeArgs& a, int n_full, int m_full, hipStream_t st);
 // blocked mode: the repair in three launches (own block of C-bar; operands; Section V on the rest)
-hipError_t launch_repair_blocked(const DecodeArgs& a, int nbi, hipStream_t st);
+hipError_t launch_repair_blocked(const DecodeArgs& a, const RepairScratch& s, int nbi, hipStream_t st);
 hipError_t launch_reset_state(const DecodeArgs& a, hipStream_t st);
 // partial sums -> syndromes -> threshold flags (Section V step 1) and max |syndrome| per family.  pr, pc: what is left
 // to add up of the parity blocks P_r and P_c, whose sums then go into C_par here
@@ -447,7 +449,7 @@ hipError_t launch_summarize(const DecodeArgs& a, hipStream_t st);
 // Section V step 2 right after detection.  with_summary = 1: also writes the first report
 hipError_t launch_decode_c(const DecodeArgs& a, int with_summary, hipStream_t st);
 // audit differences, operand patches, rank-one repair of C-bar and of the syndromes, Section V on the rest
-hipError_t launch_repair(const DecodeArgs& a, hipStream_t st);
+hipError_t launch_repair(const DecodeArgs& a, const RepairScratch& s, hipStream_t st);
 // launch_decode_c and both audits in one launch; share_done: p.batch zeroed counters
 hipError_t launch_finish(const DecodeArgs& a, const PairArgs& audits, uint32_t* share_done, int with_summary, hipStream_t st);
 
