@@ -52,47 +52,68 @@ template <> struct GT<GECC_F32> {
 
 // ---- staging of one operand tile: ROWS (m- or n-index) x BK ------------------------------------
 // KC: element (r, kk) lives at P[r * ld + kk]; otherwise at P[kk * ld + r].  Rows past the last one are
-// clamped to it (what they accumulate is masked in the epilogue), k past the end reads as zero.
-template <int DT, int ROWS, bool KC> struct Stager;
+// clamped to it (what they accumulate is masked in the epilogue), k past the end counts as zero.
+// D k-tiles are on their way at a time, each in registers of its own (d).  load() issues the same loads whatever k0 is, clamped
+// into the range (so that addresses stay a base and a stride), and fix() puts the last k-tile right in the registers: a branch
+// around a load makes every later wait one for all loads in flight, the next k-tile's included (bf16 1500 x 1000 x 1100:
+// 0.82 us per k-tile however many were on their way).  With and without the branches, product alone, bf16: 1500 x 1000 x 1100 19.6
+// -> 14.6 us (TN 23.2 -> 15.7, NT 15.2 -> 12.2), 2500^3 69.5 -> 56.0, 96 x 16384 x 4096 69.5 -> 49.7; fp32 2000 x 1000 x 2000 NT 63.5 -> 57.4.
+template <int DT, int ROWS, bool KC, int D> struct Stager;
 
 // k contiguous: 16-byte loads, eight lanes to a row
-template <int DT, int ROWS>
-struct Stager<DT, ROWS, true> {
+template <int DT, int ROWS, int D>
+struct Stager<DT, ROWS, true, D> {
   using T = typename GT<DT>::T;
   static constexpr int BK = GT<DT>::BK, V = 16 / (int)sizeof(T), N = ROWS * BK / V / THREADS;
   static constexpr int PLANE = ROWS * BK * 2;
   const T* src[N];
-  uint4 reg[N];
+  uint4 regs[D][N];
   Least least;      // of the values this thread has staged
   int kk, klim;
   __device__ __forceinline__ void init(const T* P, int64_t ld, int r0, int rlim, int k_end) {
     kk = (threadIdx.x & 7) * V;
     klim = k_end;
 #pragma unroll
-    for (int i = 0; i < N; ++i) src[i] = P + (int64_t)min(r0 + (int)(threadIdx.x >> 3) + 32 * i, rlim - 1) * ld + kk;
+    for (int i = 0; i < N; ++i) src[i] = P + (int64_t)min(r0 + (int)(threadIdx.x >> 3) + 32 * i, rlim - 1) * ld;
   }
-  __device__ __forceinline__ void load(int k0) {
-    if (k0 + BK <= klim) {
+  // (past the end: the row's last V elements)
+  __device__ __forceinline__ void load(int k0, int d) {
+    const int c = min(k0 + kk, klim - V);
 #pragma unroll
-      for (int i = 0; i < N; ++i) __builtin_memcpy(&reg[i], src[i] + k0, 16);
-    } else {
-#pragma unroll
-      for (int i = 0; i < N; ++i) {
-        T x[V];
-#pragma unroll
-        for (int e = 0; e < V; ++e) x[e] = k0 + kk + e < klim ? src[i][k0 + e] : (T)0;
-        __builtin_memcpy(&reg[i], x, 16);
-      }
-    }
+    for (int i = 0; i < N; ++i) __builtin_memcpy(&regs[d][i], src[i] + c, 16);
   }
-  __device__ __forceinline__ void store(char* S) {
+  __device__ __forceinline__ void fix(int k0, int d) {
+    const int drop = max(0, min(k0 + kk - (klim - V), V));      // elements that belong to a neighbour
 #pragma unroll
     for (int i = 0; i < N; ++i) {
+      uint4& r = regs[d][i];
+      uint64_t lo = (uint64_t)r.y << 32 | r.x, hi = (uint64_t)r.w << 32 | r.z;
+      int sh = drop * 8 * (int)sizeof(T);
+      if (sh >= 64) { lo = hi; hi = 0; sh -= 64; }
+      if (sh >= 64) { lo = 0; sh = 0; }
+      if (sh > 0) { lo = lo >> sh | hi << (64 - sh); hi >>= sh; }
+      r = make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+    }
+  }
+  // k < 16: all of the range, in the first registers
+  __device__ __forceinline__ void load_short(int k0) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      T x[V];
+#pragma unroll
+      for (int e = 0; e < V; ++e) x[e] = k0 + kk + e < klim ? src[i][k0 + kk + e] : (T)0;
+      __builtin_memcpy(&regs[0][i], x, 16);
+    }
+  }
+  __device__ __forceinline__ void store(char* S, int d) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const uint4 r = regs[d][i];
       const int row = (threadIdx.x >> 3) + 32 * i;
       if constexpr (DT == GECC_BF16) {
-        *reinterpret_cast<uint4*>(S + lds_at<BK>(row, threadIdx.x & 7)) = reg[i];
+        *reinterpret_cast<uint4*>(S + lds_at<BK>(row, threadIdx.x & 7)) = r;
       } else {
-        const float x[4] = {__uint_as_float(reg[i].x), __uint_as_float(reg[i].y), __uint_as_float(reg[i].z), __uint_as_float(reg[i].w)};
+        const float x[4] = {__uint_as_float(r.x), __uint_as_float(r.y), __uint_as_float(r.z), __uint_as_float(r.w)};
         uint32_t a[3], b[3];
         split2(x[0], x[1], a);
         split2(x[2], x[3], b);
@@ -109,21 +130,33 @@ struct Stager<DT, ROWS, true> {
   __device__ __forceinline__ void store_plain(float* S) const {
 #pragma unroll
     for (int i = 0; i < N; ++i) {
+      const uint4 r = regs[0][i];
       float* d = S + ((threadIdx.x >> 3) + 32 * i) * (BK + 1) + kk;
-      d[0] = __uint_as_float(reg[i].x); d[1] = __uint_as_float(reg[i].y);
-      d[2] = __uint_as_float(reg[i].z); d[3] = __uint_as_float(reg[i].w);
+      d[0] = __uint_as_float(r.x); d[1] = __uint_as_float(r.y);
+      d[2] = __uint_as_float(r.z); d[3] = __uint_as_float(r.w);
     }
   }
 };
 
+// r contiguous: a thread's KPT consecutive k end with the last one at the latest; what it then has of its neighbours' moves out
+template <class T, int KPT>
+__device__ __forceinline__ void shift_out(T (&r)[KPT], int drop) {
+#pragma unroll
+  for (int bit = KPT; bit > 0; bit >>= 1)
+    if (drop & bit) {
+#pragma unroll
+      for (int x = 0; x < KPT; ++x) r[x] = x + bit < KPT ? r[x + bit] : (T)0;
+    }
+}
+
 // r contiguous, fp32: a thread owns one row and KPT consecutive k (a wavefront reads 256 contiguous bytes
 // of a k-row per instruction), so that its stores are whole 16-byte chunks along k
-template <int ROWS>
-struct Stager<GECC_F32, ROWS, false> {
+template <int ROWS, int D>
+struct Stager<GECC_F32, ROWS, false, D> {
   static constexpr int BK = GT<GECC_F32>::BK, KPT = ROWS * BK / THREADS;
   static constexpr int PLANE = ROWS * BK * 2;
   const float* src;
-  float reg[KPT];
+  float regs[D][KPT];
   Least least;
   int64_t ld;
   int row, kg, klim;
@@ -133,25 +166,22 @@ struct Stager<GECC_F32, ROWS, false> {
     ld = ld_; klim = k_end;
     src = P + min(r0 + row, rlim - 1);
   }
-  __device__ __forceinline__ void load(int k0) {
-    if (k0 + BK <= klim) {
+  __device__ __forceinline__ void load(int k0, int d) {
 #pragma unroll
-      for (int x = 0; x < KPT; ++x) reg[x] = src[(int64_t)(k0 + kg + x) * ld];
-    } else {
-#pragma unroll
-      for (int x = 0; x < KPT; ++x) {
-        const int k = k0 + kg + x;
-        reg[x] = k < klim ? src[(int64_t)k * ld] : 0.f;
-      }
-    }
+    for (int x = 0; x < KPT; ++x) regs[d][x] = src[(int64_t)(min(k0 + kg, klim - KPT) + x) * ld];
   }
-  __device__ __forceinline__ void store(char* S) {
+  __device__ __forceinline__ void fix(int k0, int d) { shift_out(regs[d], max(0, min(k0 + kg - (klim - KPT), KPT))); }
+  __device__ __forceinline__ void load_short(int k0) {
+#pragma unroll
+    for (int x = 0; x < KPT; ++x) regs[0][x] = k0 + kg + x < klim ? src[(int64_t)(k0 + kg + x) * ld] : 0.f;
+  }
+  __device__ __forceinline__ void store(char* S, int d) {
 #pragma unroll
     for (int c = 0; c < KPT / 8; ++c) {
       uint32_t p[4][3];
 #pragma unroll
       for (int h = 0; h < 4; ++h) {
-        const float x0 = reg[c * 8 + 2 * h], x1 = reg[c * 8 + 2 * h + 1];
+        const float x0 = regs[d][c * 8 + 2 * h], x1 = regs[d][c * 8 + 2 * h + 1];
         split2(x0, x1, p[h]);
         least.see(x0, x1);
       }
@@ -163,17 +193,17 @@ struct Stager<GECC_F32, ROWS, false> {
   __device__ __forceinline__ bool tiny() const { return least.tiny(); }
   __device__ __forceinline__ void store_plain(float* S) const {
 #pragma unroll
-    for (int x = 0; x < KPT; ++x) S[row * (BK + 1) + kg + x] = reg[x];
+    for (int x = 0; x < KPT; ++x) S[row * (BK + 1) + kg + x] = regs[0][x];
   }
 };
 
 // r contiguous, bf16: a thread owns two neighbouring rows (one 4-byte load per k) and KPT consecutive k
-template <int ROWS>
-struct Stager<GECC_BF16, ROWS, false> {
+template <int ROWS, int D>
+struct Stager<GECC_BF16, ROWS, false, D> {
   static constexpr int BK = GT<GECC_BF16>::BK, KPT = ROWS * BK / THREADS / 2;
   static constexpr int PLANE = ROWS * BK * 2;
   const uint16_t* src;
-  uint32_t reg[KPT];
+  uint32_t regs[D][KPT];
   int64_t ld;
   int row, kg, klim, shift;
   bool single;
@@ -187,32 +217,34 @@ struct Stager<GECC_BF16, ROWS, false> {
     single = rlim < 2;
     src = P + base;
   }
-  __device__ __forceinline__ uint32_t pair(int k) const {
-    uint32_t v;
-    if (single) return src[(int64_t)k * ld];
-    __builtin_memcpy(&v, src + (int64_t)k * ld, 4);
-    return v >> shift;
-  }
-  __device__ __forceinline__ void load(int k0) {
-    if (k0 + BK <= klim && !single) {
+  __device__ __forceinline__ void load(int k0, int d) {
+    const uint16_t* p = src + (int64_t)min(k0 + kg, klim - KPT) * ld;
+    // (as many loads either way)
+    if (!single) {
 #pragma unroll
-      for (int x = 0; x < KPT; ++x) {
-        uint32_t v;
-        __builtin_memcpy(&v, src + (int64_t)(k0 + kg + x) * ld, 4);
-        reg[x] = v >> shift;
-      }
+      for (int x = 0; x < KPT; ++x) __builtin_memcpy(&regs[d][x], p + x * ld, 4);
     } else {
 #pragma unroll
-      for (int x = 0; x < KPT; ++x) reg[x] = k0 + kg + x < klim ? pair(k0 + kg + x) : 0u;
+      for (int x = 0; x < KPT; ++x) regs[d][x] = p[x * ld];
     }
   }
-  __device__ __forceinline__ void store(char* S) {
+  __device__ __forceinline__ void fix(int k0, int d) { shift_out(regs[d], max(0, min(k0 + kg - (klim - KPT), KPT))); }
+  __device__ __forceinline__ void load_short(int k0) {
+#pragma unroll
+    for (int x = 0; x < KPT; ++x) {
+      const uint16_t* p = src + (int64_t)(k0 + kg + x) * ld;
+      uint32_t v = 0;
+      if (k0 + kg + x < klim) { v = p[0]; if (!single) v |= (uint32_t)p[1] << 16; }
+      regs[0][x] = v;
+    }
+  }
+  __device__ __forceinline__ void store(char* S, int d) {
 #pragma unroll
     for (int c = 0; c < KPT / 8; ++c) {
       uint32_t lo[4], hi[4];
 #pragma unroll
       for (int h = 0; h < 4; ++h) {
-        const uint32_t v0 = reg[c * 8 + 2 * h], v1 = reg[c * 8 + 2 * h + 1];
+        const uint32_t v0 = regs[d][c * 8 + 2 * h] >> shift, v1 = regs[d][c * 8 + 2 * h + 1] >> shift;
         lo[h] = (v0 & 0xffffu) | (v1 << 16);
         hi[h] = (v0 >> 16) | (v1 & 0xffff0000u);
       }
@@ -221,6 +253,11 @@ struct Stager<GECC_BF16, ROWS, false> {
     }
   }
 };
+
+// k-tiles on their way, and of two halves of the LDS (then one barrier per k-tile instead of two): two for bf16 tiles of 64; those of
+// 128 would lose their third workgroup on a compute unit (1536 x 4224 x 768 with two 60.5 us a call, with one 58.6), and fp32, three
+// pieces per value, has neither the registers nor the LDS (1024^3 with two 42.5 us, with one 41.7).
+template <int DT, int TILE> constexpr int tile_depth() { return DT == GECC_BF16 && TILE == 64 ? 2 : 1; }
 
 // workgroup v of the scans that ride along (see GemmSide).  Fewer rows in flight than in the scans' own
 // launches: more registers here would cost the product workgroups per compute unit
@@ -278,11 +315,12 @@ __global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : 2) void gemm_tile(GemmArg
   constexpr int PLAIN = DT == GECC_F32 ? 2 * TILE * (BK + 1) * 4 : 0;
   constexpr int FAULTS = GECC_MAX_FAULTS * 8 + 16;        // list of the faults that strike this tile
   constexpr int SCAN = 8 * (CD_LDS_DOUBLES > RW_LDS_DOUBLES ? CD_LDS_DOUBLES : RW_LDS_DOUBLES);
-  constexpr int SM0 = 2 * OPERAND > PLAIN ? 2 * OPERAND : PLAIN;
+  constexpr int D = tile_depth<DT, TILE>();
+  constexpr bool TWICE = D == 2;
+  constexpr int TILES = (TWICE ? 4 : 2) * OPERAND;
+  constexpr int SM0 = TILES > PLAIN ? TILES : PLAIN;
   constexpr int SM1 = FAULTS > SCAN ? FAULTS : SCAN;      // (the sums of the wavefronts, 32 TILE bytes, are less)
   __shared__ __attribute__((aligned(16))) char smem[SM0 > SM1 ? SM0 : SM1];
-  char* As = smem;
-  char* Bs = smem + OPERAND;
 
   const int S = a.ksplit > 1 ? a.ksplit : 1;
   const int ntm = (a.n + TILE - 1) / TILE, ntn = (a.m + TILE - 1) / TILE;
@@ -348,29 +386,13 @@ __global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : 2) void gemm_tile(GemmArg
       for (int v = 0; v < 4; ++v) first[i][j][v] = 0.f;
   const int k_mid = k_begin + ((k_end - k_begin) / (2 * BK)) * BK;
 
-  Stager<DT, TILE, KCA> sa;
-  Stager<DT, TILE, KCB> sb;
+  Stager<DT, TILE, KCA, D> sa;
+  Stager<DT, TILE, KCB, D> sb;
   sa.init(A, a.lda, tile_r0, a.n, k_end);
   sb.init(B, a.ldb, tile_c0, a.m, k_end);
-  if (k_begin < k_end) { sa.load(k_begin); sb.load(k_begin); }
-
   const bool once = DT == GECC_F32 && a.k <= BK;       // (then k is not split)
-  for (int k0 = once ? k_end : k_begin; k0 < k_end; k0 += BK) {
-    __syncthreads();               // previous tile fully consumed
-    sa.store(As);
-    sb.store(Bs);
-    __syncthreads();
-    if (k0 + BK < k_end) { sa.load(k0 + BK); sb.load(k0 + BK); }
-    if constexpr (HALVES) {
-      if (k0 == k_mid) {
-#pragma unroll
-        for (int i = 0; i < NI; ++i)
-#pragma unroll
-          for (int j = 0; j < NI; ++j)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) { first[i][j][v] = acc[i][j][v]; acc[i][j][v] = 0.f; }
-      }
-    }
+  const bool is_short = a.k < 16;                      // (a row has no vector then, or a thread no KPT values of k)
+  auto multiply = [&](const char* As, const char* Bs) {
 #pragma unroll
     for (int ks = 0; ks < BK / 32; ++ks) {
       bf16x8_t fb[NI][PIECES];
@@ -399,6 +421,47 @@ __global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : 2) void gemm_tile(GemmArg
           sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[0], fb[j][0], sum, 0, 0, 0);
         }
       }
+    }
+  };
+  if (is_short) {
+    // (one k-tile, element by element)
+    sa.load_short(k_begin);
+    sb.load_short(k_begin);
+    if (!once) {
+      sa.store(smem, 0);
+      sb.store(smem + OPERAND, 0);
+      __syncthreads();
+      multiply(smem, smem + OPERAND);
+    }
+  } else {
+#pragma unroll
+    for (int d = 0; d < D; ++d) { sa.load(k_begin + d * BK, d); sb.load(k_begin + d * BK, d); }
+    if (once) { sa.fix(k_begin, 0); sb.fix(k_begin, 0); }
+    for (int kt = once ? k_end : k_begin; kt < k_end; kt += D * BK)
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      const int k0 = kt + d * BK;
+      if (d > 0 && k0 >= k_end) break;
+      char* As = smem + (TWICE && (d & 1) ? 2 * OPERAND : 0);
+      char* Bs = As + OPERAND;
+      if (!TWICE) __syncthreads();   // previous tile fully consumed
+      if (k0 + BK > k_end) { sa.fix(k0, d); sb.fix(k0, d); }
+      sa.store(As, d);
+      sb.store(Bs, d);
+      __syncthreads();
+      sa.load(k0 + D * BK, d);
+      sb.load(k0 + D * BK, d);
+      if constexpr (HALVES) {
+        if (k0 == k_mid) {
+#pragma unroll
+          for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+#pragma unroll
+              for (int v = 0; v < 4; ++v) { first[i][j][v] = acc[i][j][v]; acc[i][j][v] = 0.f; }
+        }
+      }
+      multiply(As, Bs);
     }
   }
 
@@ -480,8 +543,9 @@ __global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : 2) void gemm_tile(GemmArg
 #pragma unroll
           for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
       for (int k0 = k_begin; k0 < k_end; k0 += BK) {
-        sa.load(k0);
-        sb.load(k0);
+        sa.load(k0, 0);
+        sb.load(k0, 0);
+        if (k0 + BK > k_end) { sa.fix(k0, 0); sb.fix(k0, 0); }
         __syncthreads();
         sa.store_plain(Ap);
         sb.store_plain(Bp);

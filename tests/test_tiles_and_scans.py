@@ -60,6 +60,18 @@ def test_tiles_layouts_and_tails(shape, batch, dtype, trans):
     _check(_product(A, B, dtype, trans, pad=3, shift=1), A, B)       # rows that start at any element
 
 
+@pytest.mark.parametrize("trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n,m", [(1, 66), (65, 2), (3, 1), (70, 131)])
+def test_ends_of_the_k_range(n, m, dtype, trans):
+    """The last k-tile is loaded from the end of the range, whatever lies before it: ranges shorter than a vector or a thread's
+    share of k (below 16), one more and one less than a share, a k-tile and two of them."""
+    law = ("normal", 1.0)
+    for k in (2, 7, 8, 15, 16, 17, 31, 32, 34, 47, 63, 66, 95, 127, 128, 130, 193):
+        A, B = [x[None] for x in inputs.operands(inputs.rng_for(83, k), n, k, m, law, law, dtype)]
+        _check(_product(A, B, dtype, trans, pad=k % 3, shift=k % 2), A, B)
+
+
 # Batches that go in tiles of 128 x 256 (test_launch_plans.py holds them to it): every remainder of the k loop (three k-tiles of
 # 32 in flight), few rows, a second half with a single column, more tile columns than one, of which the last has no second half
 WIDE_CASES = [((128, 256, 256), 250), ((120, 257, 250), 250), ((127, 287, 1541), 73), ((128, 288, 193), 250), ((65, 319, 200), 250),
