@@ -63,12 +63,6 @@ __device__ __forceinline__ bool finite2(double a, double b) { return isfinite(a)
 __device__ __forceinline__ double max_nan(double a, double b) { return (a != a || a > b) ? a : b; }
 
 // -------------------------------------------------------------------------------------------
-__global__ void reset_state_kernel(DecodeArgs a) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= a.p.batch) return;
-  reset_state(state_of(a, b));
-}
-
 // partial sums -> syndromes (sum - parity, Section V step 1) -> flags
 constexpr int TH_SLICES = 4;    // wavefronts of a workgroup; each adds every 4th sub-tile of a line
 
@@ -88,72 +82,74 @@ __device__ __forceinline__ void threshold_body(const DecodeArgs& a, const Parts&
   const bool is_row = o < n, valid = o < n + m;
   const bool wt = a.p.weighted != 0;     // single-checksum mode: the weighted sums are not read
 
-  // partial sums of this line over the sub-tiles slice, slice + 4, ... (fixed order); all loads
-  // of a thread are issued before the first is used
+  // Partial sums of this line over the sub-tiles slice, slice + 4, ... (fixed order), and its parity symbols.  All loads are
+  // issued before the first is used (the kernel is a chain of latencies).
+  const int len_o = is_row ? n : m, i_o = is_row ? o : o - n;      // the line among its kind
+  const int at_o = is_row ? o : 2 * n + i_o;                        // its first parity symbol
+  // (lanes past the last line read the last line's data and drop the result; sub-tiles past
+  // the last one are clamped and count as zero: no load depends on a branch)
+  const int oo = min(o, n + m - 1);
+  const bool rowline = oo < n;
+  const int nt = rowline ? a.ntn : a.ntm, len = rowline ? a.rp_ld : a.cp_ld, tile = rowline ? a.tile_n : a.tile_m;
+  const float2* pp = rowline ? reinterpret_cast<const float2*>(a.rowpart) + (int64_t)b * a.ntn * a.rp_ld + oo
+                             : reinterpret_cast<const float2*>(a.colpart) + (int64_t)b * a.ntm * a.cp_ld + (oo - n);
+  float2 v[TH_MAXLOADS];
+  auto load = [&](int t0) {
+#pragma unroll
+    for (int u = 0; u < TH_MAXLOADS; ++u) v[u] = pp[(int64_t)min(t0 + u * TH_SLICES, nt - 1) * len];
+  };
+  load(slice);
+  // What the scans have left of this line's two parity symbols.  Chunks: a wavefront's slice is the second stage's own;
+  // segments: one wavefront per kind.  (A second stage in a launch of its own costs 5 us for the same loads.)
+  const Parts parts = {is_row ? pr.chunks : pc.chunks, is_row ? pr.segs : pc.segs, is_row ? pr.nchunk : pc.nchunk, is_row ? pr.nseg : pc.nseg};
+  const bool in_parts = PARTS && (parts.nchunk > 0 || parts.nseg > 0);
+  double stored[2] = {0.0, 0.0};
+  if (slice == 0 && valid && !in_parts) { stored[0] = cpar[at_o]; stored[1] = cpar[at_o + len_o]; }
+  __shared__ double par[PARTS ? 2 : 1][TH_SLICES][64];
+  if (PARTS && valid && in_parts) {
+    if (parts.nchunk > 0) {
+      const double* p0 = parts.chunks + (int64_t)b * parts.nchunk * 2 * len_o + i_o;
+      const double* p[2] = {p0, p0 + len_o};
+      double s[2];
+      static_assert(TH_SLICES == 4, "slices of a column scan's second stage");
+      slice_sums<2, false>(p, 2 * (int64_t)len_o, parts.nchunk, slice, s);
+      par[0][slice][lane] = s[0];
+      par[1][slice][lane] = s[1];
+    } else if (slice < 2) {
+      par[slice][0][lane] = parts_sum(parts, b, len_o, slice, i_o);
+    }
+  }
   double S = 0.0, W = 0.0;
-  {
-    // (lanes past the last line read the last line's data and drop the result; sub-tiles past
-    // the last one are clamped and count as zero: no load depends on a branch)
-    const int oo = min(o, n + m - 1);
-    const bool rowline = oo < n;
-    const int nt = rowline ? a.ntn : a.ntm, len = rowline ? a.rp_ld : a.cp_ld, tile = rowline ? a.tile_n : a.tile_m;
-    const float2* pp = rowline ? reinterpret_cast<const float2*>(a.rowpart) + (int64_t)b * a.ntn * a.rp_ld + oo
-                               : reinterpret_cast<const float2*>(a.colpart) + (int64_t)b * a.ntm * a.cp_ld + (oo - n);
-    for (int t0 = slice; t0 < nt; t0 += TH_SLICES * TH_MAXLOADS) {
-      float2 v[TH_MAXLOADS];
+  for (int t0 = slice; t0 < nt; t0 += TH_SLICES * TH_MAXLOADS) {
+    if (t0 != slice) load(t0);
 #pragma unroll
-      for (int u = 0; u < TH_MAXLOADS; ++u) v[u] = pp[(int64_t)min(t0 + u * TH_SLICES, nt - 1) * len];
-#pragma unroll
-      for (int u = 0; u < TH_MAXLOADS; ++u) {
-        const int t = t0 + u * TH_SLICES;
-        const double x = t < nt ? (double)v[u].x : 0.0, y = t < nt ? (double)v[u].y : 0.0;
-        S += x;
-        W += y + (double)(t * tile) * x;
-      }
+    for (int u = 0; u < TH_MAXLOADS; ++u) {
+      const int t = t0 + u * TH_SLICES;
+      const double x = t < nt ? (double)v[u].x : 0.0, y = t < nt ? (double)v[u].y : 0.0;
+      S += x;
+      W += y + (double)(t * tile) * x;
     }
   }
   __shared__ double red[2][TH_SLICES][64];
   red[0][slice][lane] = S;
   red[1][slice][lane] = W;
-  // What the scans have left of this line's two parity symbols.  Chunks: a wavefront's slice is the second stage's own;
-  // segments: one wavefront per kind.  (A second stage in a launch of its own costs 5 us for the same loads.)
-  const Parts parts = {is_row ? pr.chunks : pc.chunks, is_row ? pr.segs : pc.segs, is_row ? pr.nchunk : pc.nchunk, is_row ? pr.nseg : pc.nseg};
-  const bool in_parts = PARTS && (parts.nchunk > 0 || parts.nseg > 0);
-  __shared__ double par[PARTS ? 2 : 1][TH_SLICES][64];
-  if (PARTS && valid && in_parts) {
-    const int len = is_row ? n : m, i = is_row ? o : o - n;
-    if (parts.nchunk > 0) {
-      const double* p0 = parts.chunks + (int64_t)b * parts.nchunk * 2 * len + i;
-      const double* p[2] = {p0, p0 + len};
-      double s[2];
-      static_assert(TH_SLICES == 4, "slices of a column scan's second stage");
-      slice_sums<2, false>(p, 2 * (int64_t)len, parts.nchunk, slice, s);
-      par[0][slice][lane] = s[0];
-      par[1][slice][lane] = s[1];
-    } else if (slice < 2) {
-      par[slice][0][lane] = parts_sum(parts, b, len, slice, i);
-    }
-  }
   __syncthreads();
   if (slice != 0) return;
   double v1 = 0.0, v2 = 0.0;
   if (valid) {
-    double sum[2];
     if (PARTS && in_parts) {
-      const int at = is_row ? o : 2 * n + (o - n), step = is_row ? n : m;
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
-        sum[t] = parts.nchunk > 0 ? (par[t][0][lane] + par[t][1][lane]) + (par[t][2][lane] + par[t][3][lane]) : par[t][0][lane];
-        const_cast<double*>(cpar)[at + t * step] = sum[t];
+        stored[t] = parts.nchunk > 0 ? (par[t][0][lane] + par[t][1][lane]) + (par[t][2][lane] + par[t][3][lane]) : par[t][0][lane];
+        const_cast<double*>(cpar)[at_o + t * len_o] = stored[t];
       }
     }
-    auto parity = [&](int t, int at) { return PARTS && in_parts ? sum[t] : cpar[at]; };
     S = (red[0][0][lane] + red[0][1][lane]) + (red[0][2][lane] + red[0][3][lane]);
     W = (red[1][0][lane] + red[1][1][lane]) + (red[1][2][lane] + red[1][3][lane]);
     if (is_row) {
       const int i = o;
-      v1 = S - parity(0, i);
-      v2 = W - parity(1, n + i);
+      v1 = S - stored[0];
+      v2 = W - stored[1];
       synd[i] = v1;
       synd[n + i] = v2;
       if (outside(v1, a.p.tau_r1) || (wt && outside(v2, a.p.tau_r2))) {
@@ -162,8 +158,8 @@ __device__ __forceinline__ void threshold_body(const DecodeArgs& a, const Parts&
       }
     } else {
       const int j = o - n;
-      v1 = S - parity(0, 2 * n + j);
-      v2 = W - parity(1, 2 * n + m + j);
+      v1 = S - stored[0];
+      v2 = W - stored[1];
       synd[2 * n + j] = v1;
       synd[2 * n + m + j] = v2;
       if (outside(v1, a.p.tau_q1) || (wt && outside(v2, a.p.tau_q2))) {
@@ -198,42 +194,39 @@ __global__ __launch_bounds__(64 * TH_SLICES) void threshold_kernel(DecodeArgs a)
 template <int TH_MAXLOADS>
 __global__ __launch_bounds__(64 * TH_SLICES) void threshold_parts_kernel(DecodeArgs a, Parts pr, Parts pc) { threshold_body<TH_MAXLOADS, true>(a, pr, pc); }
 
-// first report after detection: CLEAN or DETECTED.  Called by every thread of a workgroup of 1
-// to 4 wavefronts (the family maxima are reduced over the threshold kernel's workgroups);
-// returns the status to all of them.
-__device__ int summarize(const DecodeArgs& a, int b, const DecodeState* st, gecc_report* rep) {
-  __shared__ double smx[4][4];
-  double mx[4] = {0.0, 0.0, 0.0, 0.0};
+// first report after detection: CLEAN or DETECTED.  Called by every thread of a workgroup of 1, 2 or 4 wavefronts, which
+// share the four families out; returns the status to all of them.  if_clean: nothing is written unless it is CLEAN.  (No
+// barrier, and the maxima do not wait for the counters: it is all that a clean product's last but one launch does, which
+// with one wait after the other took 3.8 us and takes 2.0.)
+__device__ __forceinline__ int summarize(const DecodeArgs& a, int b, const DecodeState* st, gecc_report* rep, bool if_clean = false) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
   const double* bm = a.blockmax + (int64_t)b * a.nblk * 4;
-  for (int i = threadIdx.x; i < a.nblk; i += blockDim.x)
+  const int sc = st->s_cnt, tc = st->t_cnt;
+  for (int f = wave; f < 4; f += nw) {
+    double mx = 0.0;
+    for (int i0 = lane; i0 < a.nblk; i0 += 4 * 64) {
+      double v[4];
 #pragma unroll
-    for (int f = 0; f < 4; ++f) mx[f] = max_nan(mx[f], bm[(int64_t)i * 4 + f]);
+      for (int u = 0; u < 4; ++u) v[u] = bm[(int64_t)min(i0 + 64 * u, a.nblk - 1) * 4 + f];
 #pragma unroll
-  for (int f = 0; f < 4; ++f)
+      for (int u = 0; u < 4; ++u) mx = max_nan(mx, v[u]);
+    }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mx[f] = max_nan(mx[f], __shfl_down(mx[f], off, 64));
-  const int wave = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
-  if ((threadIdx.x & 63) == 0)
-#pragma unroll
-    for (int f = 0; f < 4; ++f) smx[wave][f] = mx[f];
-  __syncthreads();
-  const int status = (st->s_cnt == 0 && st->t_cnt == 0) ? GECC_CLEAN : GECC_DETECTED;
-  if (threadIdx.x == 0) {
-    rep->s = st->s_cnt;
-    rep->t = st->t_cnt;
+    for (int off = 32; off > 0; off >>= 1) mx = max_nan(mx, __shfl_down(mx, off, 64));
+    if (lane == 0 && (!if_clean || (sc == 0 && tc == 0))) rep->max_abs_synd[f] = mx;
+  }
+  const int status = (sc == 0 && tc == 0) ? GECC_CLEAN : GECC_DETECTED;
+  if (threadIdx.x == 0 && (!if_clean || status == GECC_CLEAN)) {
+    rep->s = sc;
+    rep->t = tc;
     rep->n_err = 0;
     rep->n_total = 0;
     rep->reserved = 0;
-    for (int f = 0; f < 4; ++f) {
-      double v = smx[0][f];
-      for (int w = 1; w < nw; ++w) v = max_nan(v, smx[w][f]);
-      rep->max_abs_synd[f] = v;
-    }
     rep->status = status;
   }
   return status;
 }
-__global__ __launch_bounds__(64) void summarize_kernel(DecodeArgs a) {   // one wavefront per item
+__global__ __launch_bounds__(256) void summarize_kernel(DecodeArgs a) {   // four wavefronts per item
   const int b = blockIdx.x;
   summarize(a, b, state_of(a, b), a.report + b);
 }
@@ -1060,17 +1053,22 @@ __global__ __launch_bounds__(DC_THREADS, 3) void finish_kernel(FinishArgs) {
   __shared__ Est fix[4];
   __shared__ double dots[4];
   __shared__ int nfix, act, flag;
-  enum { NOTHING, CLEAN, PATCH, AUDIT };
+  enum { NOTHING, PATCH, AUDIT };
   const FinishWork o = finish_work(f.audits, blockIdx.x);
   DecodeState* st = state_of(a, o.b);
   gecc_report* rep = a.report + o.b;
-  // (one thread decides for the workgroup: the item's first workgroups may be writing the report meanwhile)
-  if (threadIdx.x == 0)
-    act = f.with_summary ? (st->s_cnt != 0 || st->t_cnt != 0 ? AUDIT : o.q == 0 ? CLEAN : NOTHING)
-                         : (rep->status == GECC_DETECTED ? AUDIT : NOTHING);
-  __syncthreads();
-  if (act == NOTHING) return;
-  if (act == CLEAN) { summarize(a, o.b, st, rep); return; }
+  if (f.with_summary) {
+    if (o.q == 0) {
+      if (summarize(a, o.b, st, rep, true) == GECC_CLEAN) return;
+    } else if (st->s_cnt == 0 && st->t_cnt == 0) {
+      return;
+    }
+  } else {
+    // (one thread decides for the workgroup: the item's first workgroups may be writing the report meanwhile)
+    if (threadIdx.x == 0) act = rep->status == GECC_DETECTED ? AUDIT : NOTHING;
+    __syncthreads();
+    if (act == NOTHING) return;
+  }
 
   // workgroups of an item that share a dot product
   const int per_item = f.audits.j[0].gx * f.audits.j[0].gy + f.audits.j[1].gx * f.audits.j[1].gy;
@@ -1292,11 +1290,6 @@ __global__ __launch_bounds__(256) void split_parities_kernel(const double* par, 
 
 }  // namespace
 
-hipError_t launch_reset_state(const DecodeArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(reset_state_kernel, dim3((a.p.batch + 63) / 64), dim3(64), 0, st, a);
-  return hipGetLastError();
-}
-
 hipError_t launch_threshold(const DecodeArgs& a, const Parts& pr, const Parts& pc, hipStream_t st) {
   dim3 grid((a.p.n + a.p.m + 63) / 64, a.p.batch);   // 64 lines per workgroup: spreads over all CUs
   const int nt = a.ntm > a.ntn ? a.ntm : a.ntn;
@@ -1313,7 +1306,7 @@ hipError_t launch_threshold(const DecodeArgs& a, const Parts& pr, const Parts& p
 }
 
 hipError_t launch_summarize(const DecodeArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(summarize_kernel, dim3(a.p.batch), dim3(64), 0, st, a);
+  hipLaunchKernelGGL(summarize_kernel, dim3(a.p.batch), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

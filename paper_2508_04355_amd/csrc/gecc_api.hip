@@ -903,17 +903,13 @@ int verify_impl(gecc_ctx* ctx, const float* dev_C, const double* dev_C_par, gecc
   if (!fused && blocked(ctx)) return GECC_ERR_ARG;   // (blocked mode verifies from the product's own partial sums)
   if (!fused) {
     // (the fused path had its state reset by gecc_multiply)
-    {
-      Timed t(ctx, GECC_K_DECODE, st);
-      if ((e = t.done(launch_reset_state(d, st))) != hipSuccess) return hip_rc(e);
-    }
     const gecc_params& p = ctx->p;
     PartialArgs pa{};
     pa.C = dev_C; pa.n = p.n; pa.m = p.m; pa.batch = p.batch; pa.ldc = p.ldc; pa.sc = p.stride_c;
     pa.rowpart = const_cast<float*>(d.rowpart); pa.colpart = const_cast<float*>(d.colpart);
     pa.tile_m = ctx->tile_m; pa.tile_n = ctx->tile_n; pa.ntm = ctx->ntm; pa.ntn = ctx->ntn;
     pa.rp_ld = ctx->rp_ld; pa.cp_ld = ctx->cp_ld;
-    pa.gate = nullptr;
+    pa.state = d.state;
     Timed t(ctx, GECC_K_PARTIALS, st);
     if ((e = t.done(launch_partials(pa, st))) != hipSuccess) return hip_rc(e);
   }

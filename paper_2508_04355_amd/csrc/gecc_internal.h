@@ -384,9 +384,7 @@ struct PartialArgs {
   float* colpart;
   int tile_m, tile_n, ntm, ntn;
   int rp_ld, cp_ld;
-  const int32_t* gate;
-  int64_t gate_stride;
-  int gate_value;
+  DecodeState* state;       // set to what it is before any verification
 };
 hipError_t launch_partials(const PartialArgs& a, hipStream_t st);
 // C += P (both n x m fp32, leading dimension ldc): the sum of per-panel partial products
@@ -440,7 +438,6 @@ hipError_t launch_split_parities(const double* par, void* W, int dtype, int line
 hipError_t launch_threshold_blocked(const DecodeArgs& a, int n_full, int m_full, hipStream_t st);
 // blocked mode: the repair in three launches (own block of C-bar; operands; Section V on the rest)
 hipError_t launch_repair_blocked(const DecodeArgs& a, const RepairScratch& s, int nbi, hipStream_t st);
-hipError_t launch_reset_state(const DecodeArgs& a, hipStream_t st);
 // partial sums -> syndromes -> threshold flags (Section V step 1) and max |syndrome| per family.  pr, pc: what is left
 // to add up of the parity blocks P_r and P_c, whose sums then go into C_par here
 hipError_t launch_threshold(const DecodeArgs& a, const Parts& pr, const Parts& pc, hipStream_t st);

@@ -726,12 +726,8 @@ template <int TILE, bool STREAM>
 __global__ __launch_bounds__(THREADS) void partials_kernel(PartialArgs a) {
   constexpr int CG = TILE / 4, RG = THREADS / CG, RPT = TILE / RG;   // column groups of 4, row groups of RPT
   const int b = blockIdx.z;
-  if (a.gate) {
-    const int32_t g = *reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(a.gate) +
-                                                        a.gate_stride * b);
-    if (g != a.gate_value) return;
-  }
   const int tm = blockIdx.y, tn = blockIdx.x;
+  if (tm == 0 && tn == 0 && threadIdx.x == 0) reset_state(a.state + b);      // (nothing in this launch reads it)
   const int tile_r0 = tm * TILE, tile_c0 = tn * TILE;
   const float* C = a.C + (int64_t)b * a.sc;
   const int tid = threadIdx.x;
