@@ -17,12 +17,12 @@ bool blocked(const gecc_ctx* c) { return c->nbi > 0; }
 int items_of(const gecc_ctx* c) { return blocked(c) ? c->nbi * c->nbj : c->p.batch; }
 
 // Workgroups per tile of a product whose tiles alone would leave compute units idle: as many as give `want`
-// workgroups in all, each with at least 128 terms of k.
-int ksplit_of(int64_t tiles, int want, int k) {
+// workgroups in all, each with at least `least` terms of k.
+int ksplit_of(int64_t tiles, int want, int k, int least = 128) {
   int s = (int)(want / tiles);
   if (s < 1) s = 1;
   if (s > 8) s = 8;
-  while (s > 1 && k / s < 128) --s;
+  while (s > 1 && k / s < least) --s;
   return s;
 }
 int ksplit_128(int64_t tiles, int k) { return ksplit_of(tiles, 256, k); }
@@ -95,14 +95,21 @@ int ksplit_bf16_128(int64_t t128, int k) {
 // Workgroups: fp32 tiles of 64 keep four per compute unit busy (1024^3: one workgroup per tile 40, two 31,
 // four 28, eight 38); up to one tile per compute unit three are enough, and leave the fourth place to the scans that
 // ride along (whole calls at 1024, 800 and 512 workgroups: 1024^3 48.4, 44.9 and 47.1, 900 x 1500 x 900 55.1, 53.1 and
-// 57.8, 1000 x 1031 x 777 TT 48.0, 46.4 and 50.6; with more tiles 800 are too few, 1300^3, 441 tiles, 74.0 and 80.9), bf16 ones two, to the nearest (1500 x 1000 x 1100, 432 tiles: 19.5, split in two 22),
+// 57.8, 1000 x 1031 x 777 TT 48.0, 46.4 and 50.6; with more tiles 800 are too few, 1300^3, 441 tiles, 74.0 and 80.9), bf16 ones two.
+// What the ranges of a tile exchange takes 3 to 4 us, so they have to be worth it: fp32 128 terms, of few tiles, whose compute units
+// have nothing else to do, fewer (whole calls, ranges of 128 -> 64: 128^3 20.9 -> 20.2, 256^3 23.1 -> 21.7, 100 x 300 x 100 23.8 -> 22.6; 70 and
+// 100 tiles, 128 -> 100: 25.1 -> 24.2, 25.6 -> 25.1), bf16 450 (ranges of 128 -> as many as then remain: 700^3 in 4 -> 1 26.9 -> 25.8, 400 x 700 x 800 in 5 -> 1
+// 26.7 -> 24.3, 600 x 1400 x 600 in 5 -> 3 28.6 -> 27.2, 300 x 2000 x 400 in 8 -> 4 28.4 -> 25.7, 1200 x 1800 x 400 TN in 4 -> 3 31.7 -> 30.1),
 // fp32 tiles of 128 two (2000 x 1000 x 2000: 83, split in two 67).
-ProductPlan plan_tiles(int dtype, int64_t n, int64_t k, int64_t m, int64_t batch) {
+// narrow: a side product of blocked mode, a few columns (rows) beside a whole operand; its bf16 ranges are as they were measured, two and
+// a half workgroups and 128 terms.
+ProductPlan plan_tiles(int dtype, int64_t n, int64_t k, int64_t m, int64_t batch, bool narrow = false) {
   const int64_t t128 = ((n + 127) / 128) * ((m + 127) / 128) * batch, t64 = ((n + 63) / 64) * ((m + 63) / 64) * batch;
   const int s_long = dtype == GECC_BF16 ? ksplit_bf16_128(t128, (int)k) : 0;
   if (s_long > 0) return {128, s_long, false};
   if (t128 >= 256 && k >= 256 && 3 * t128 < t64) return {128, dtype == GECC_F32 && t128 < 512 ? 2 : 1, false};
-  return {64, dtype == GECC_F32 ? ksplit_of(t64, t64 > 256 ? 1024 : 800, (int)k) : ksplit_of(t64, 512 + (int)(t64 < 512 ? t64 / 2 : 0), (int)k), false};
+  return {64, dtype == GECC_F32 ? ksplit_of(t64, t64 > 256 ? 1024 : 800, (int)k, t64 <= 64 ? 64 : t64 <= 128 ? 96 : 128) :
+              narrow ? ksplit_of(t64, 512 + (int)(t64 < 512 ? t64 / 2 : 0), (int)k) : ksplit_of(t64, 512, (int)k, 450), false};
 }
 
 // Whether the 256 x 256-tile kernel is the faster one for a bf16 product it can take: it needs a workgroup per
@@ -812,7 +819,7 @@ void narrow_plan(gecc_ctx* ctx, GemmArgs& g) {
   };
   take();
   if (!gemm_takes_256(g)) {
-    pl = plan_tiles(p.dtype, g.n, g.k, g.m, 1);
+    pl = plan_tiles(p.dtype, g.n, g.k, g.m, 1, true);
     take();
   }
   g.split_part = reinterpret_cast<float*>(ctx->ws + ctx->lay.rowpart);

@@ -301,6 +301,203 @@ __device__ __forceinline__ void side_job(const GemmArgs& a, const GemmSide& side
   else if constexpr (DT == GECC_F32) rowdot_wave_body<DT, false>(j.s, x, b, lds);
 }
 
+// The tile of this workgroup; false: it was one of the scans that ride along, which is done, or has no tile.
+struct Place { int tm, tn, b, split; };
+template <int DT, int TILE>
+__device__ __forceinline__ bool place(const GemmArgs& a, const GemmSide& side, int S, char* smem, Place& o) {
+  const int ntm = (a.n + TILE - 1) / TILE, ntn = (a.m + TILE - 1) / TILE;
+  int id = blockIdx.x;
+  if (side.groups > 0) {
+    // in whole groups of 8 workgroups (one per XCD): side.lead of P_g and, where they go first, the scans; then the
+    // product's; then the scans
+    const int first = side.lead * 8, own = (side.own + 7) / 8 * 8;
+    if (id < first || id >= first + own) {
+      const int v = id < first ? id : side.lead_blocks + id - first - own;
+      if (v < (id < first ? side.lead_blocks : side.blocks)) side_job<DT>(a, side, v, reinterpret_cast<double*>(smem));
+      return false;
+    }
+    id -= first;
+    if (id >= side.own) return false;
+  }
+  {
+    const int N = side.own, per = N / 8, rem = N - per * 8, x = id & 7;
+    id = x * per + min(x, rem) + (id >> 3);
+  }
+  const int bs = id / (ntn * ntm);
+  o.tn = id % ntn; o.tm = (id / ntn) % ntm;
+  o.b = bs / S; o.split = bs - o.b * S;
+  return true;
+}
+
+// Accumulators of a TILE x TILE tile, four wavefronts (2 x 2): acc[i][j][v] = C[16 i + 4 lg + v][16 j + l16] of a quarter
+
+// rows and columns past the end count as zero
+template <int TILE>
+__device__ __forceinline__ void mask_edges(const GemmArgs& a, int tile_r0, int tile_c0, f32x4_t (&acc)[TILE / 32][TILE / 32]) {
+  constexpr int W = TILE / 2, NI = W / 16;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r0 = tile_r0 + (wave >> 1) * W + (lane >> 4) * 4, c0 = tile_c0 + (wave & 1) * W + (lane & 15);
+  if (tile_r0 + TILE > a.n || tile_c0 + TILE > a.m) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (r0 + i * 16 + v >= a.n || c0 + j * 16 >= a.m) acc[i][j][v] = 0.f;
+  }
+}
+
+// k-split: every workgroup of the tile leaves its partial sums in memory (in register order, 16 bytes a lane: whole lines per
+// store), the one that arrives last adds them all up in the order of the k ranges (so the result does not depend on which
+// one that is) and goes on with the tile (true).  Written through and read past the caches, like store_dev and load_dev, for
+// which 16 bytes are too many.  (Whole calls, with 4 bytes a lane -> with 16: 300 x 2000 x 400 bf16 in
+// eight ranges 30.2 -> 28.4 us, 700^3 in four 28.6 -> 26.9, 512^3 fp32 in four 25.9 -> 25.4.)
+template <int TILE>
+__device__ __forceinline__ bool add_splits(const GemmArgs& a, int b, int tm, int tn, int split, int S, f32x4_t (&acc)[TILE / 32][TILE / 32], char* smem) {
+  constexpr int NI = TILE / 32, DEV = 16;         // (the bit of device scope among a buffer instruction's cache bits)
+  const int ntm = (a.n + TILE - 1) / TILE, ntn = (a.m + TILE - 1) / TILE;
+  const int64_t tile_id = ((int64_t)b * ntm + tm) * ntn + tn;
+  __amdgpu_buffer_rsrc_t part = __builtin_amdgcn_make_buffer_rsrc(a.split_part + tile_id * S * (TILE * TILE), 0, S * TILE * TILE * 4, 0x00027000);
+  const int at = threadIdx.x * 16;
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(stream_t, acc[i][j]), part, at + (i * NI + j) * THREADS * 16, split * TILE * TILE * 4, DEV);
+  if (!arrive_last(a.split_done + tile_id, (uint32_t)S, reinterpret_cast<int*>(smem))) return false;
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int j = 0; j < NI; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+  for (int q = 0; q < S; ++q)
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j) {
+        const f32x4_t x = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(part, at + (i * NI + j) * THREADS * 16, q * TILE * TILE * 4, DEV));
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[i][j][v] += x[v];
+      }
+  return true;
+}
+
+// C, and the tile's share of the syndromes
+template <int TILE>
+__device__ __forceinline__ void finish_tile(const GemmArgs& a, int b, int tm, int tn, f32x4_t (&acc)[TILE / 32][TILE / 32], char* smem) {
+  constexpr int W = TILE / 2, NI = W / 16;
+  const int tile_r0 = tm * TILE, tile_c0 = tn * TILE;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wr = wave >> 1, wc = wave & 1, l16 = lane & 15, lg = lane >> 4;
+  // ---- epilogue, from the accumulators -------------------------------------------------------------
+  // Test faults (none in production calls): the workgroup searches the list for those that strike its
+  // tile, then every wavefront adds them to its accumulators.
+  if (a.n_faults > 0) {
+    int* hits = reinterpret_cast<int*>(smem);
+    int2* hit = reinterpret_cast<int2*>(smem + 16);
+    __syncthreads();
+    if (tid == 0) *hits = 0;
+    __syncthreads();
+    for (int f = tid; f < a.n_faults; f += THREADS) {
+      const gecc_fault ft = a.faults[f];
+      const int r = ft.row - tile_r0, c = ft.col - tile_c0;
+      if (ft.batch == b + a.fault_bias && r >= 0 && r < min(TILE, a.n - tile_r0) && c >= 0 && c < min(TILE, a.m - tile_c0))
+        hit[atomicAdd(hits, 1)] = make_int2(r * TILE + c, __float_as_int(ft.offset));
+    }
+    __syncthreads();
+    const int nh = *hits;
+    for (int f = 0; f < nh; ++f) {
+      const int r = hit[f].x / TILE - wr * W, c = hit[f].x % TILE - wc * W;
+      const float off = __int_as_float(hit[f].y);
+      const bool mine = r >= 0 && r < W && c >= 0 && c < W && ((r >> 2) & 3) == lg && (c & 15) == l16;
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            if (mine && i == r >> 4 && j == c >> 4 && v == (r & 3)) acc[i][j][v] += off;
+    }
+  }
+
+  // C: the registers of two neighbouring 16-column blocks first trade their odd / even groups of 16 lanes
+  // (v_permlane16_swap): each then holds 2 rows x 32 consecutive columns, two full lines per store
+  {
+    const int R0 = tile_r0 + wr * W + (lg >> 1) * 8, C0 = tile_c0 + wc * W + (lg & 1) * 16 + l16;
+    float* C = a.C + (int64_t)b * a.sc + (int64_t)R0 * a.ldc + C0;
+    const bool whole = tile_r0 + TILE <= a.n && tile_c0 + TILE <= a.m;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int jp = 0; jp < NI / 2; ++jp) {
+          float t0 = acc[i][2 * jp][v], t1 = acc[i][2 * jp + 1][v];
+          // (inline: this compiler's builtin for the swap loses its second result; the wait states are the
+          // ones a swap needs after a vector instruction wrote its operands)
+          asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(t0), "+v"(t1));
+          float* dst = C + (int64_t)(i * 16 + v) * a.ldc + jp * 32;
+          if (whole) {
+            dst[0] = t0;
+            dst[4 * a.ldc] = t1;
+          } else if (C0 + jp * 32 < a.m) {
+            if (R0 + i * 16 + v < a.n) dst[0] = t0;
+            if (R0 + i * 16 + v + 4 < a.n) dst[4 * a.ldc] = t1;
+          }
+        }
+  }
+  if (!a.rowpart) return;
+
+  // Row sums: a lane adds its columns of a row (plain, and u = sum of j x_j: the block part of the column
+  // weight), the 16 lanes of a group are added across the lanes; lane l16 of a group keeps row number
+  // l16 = 4 i + v of its 4 NI.  Column sums: in the lane, then across the four groups; group lg keeps block lg.
+  float2* rowred = reinterpret_cast<float2*>(smem);          // [2: wc][TILE]
+  float2* colred = rowred + 2 * TILE;                         // [2: wr][TILE]
+  __syncthreads();
+  {
+    float ks = 0.f, kw = 0.f;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        float s = acc[i][0][v], u = 0.f;
+#pragma unroll
+        for (int j = 1; j < NI; ++j) { s += acc[i][j][v]; u = fmaf((float)j, acc[i][j][v], u); }
+        const float w = row16_sum(fmaf((float)(l16 + 1), s, 16.f * u));
+        s = row16_sum(s);
+        if (l16 == i * 4 + v) { ks = s; kw = w; }
+      }
+    if (l16 < 4 * NI)
+      rowred[wc * TILE + wr * W + (l16 >> 2) * 16 + lg * 4 + (l16 & 3)] = make_float2(ks, fmaf((float)(wc * W), ks, kw));
+    float cs = 0.f, cw = 0.f;
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      float s = 0.f, w = 0.f;
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) { s += acc[i][j][v]; w = fmaf((float)(i * 16 + v + 1), acc[i][j][v], w); }
+      w = fmaf((float)(lg * 4), s, w);
+      s += __shfl_xor(s, 16, 64); w += __shfl_xor(w, 16, 64);
+      s += __shfl_xor(s, 32, 64); w += __shfl_xor(w, 32, 64);
+      if (lg == j) { cs = s; cw = w; }
+    }
+    if (lg < NI) colred[wr * TILE + wc * W + lg * 16 + l16] = make_float2(cs, fmaf((float)(wr * W), cs, cw));
+  }
+  __syncthreads();
+  if (tid < TILE) {
+    if (tile_r0 + tid < a.n)
+      *reinterpret_cast<float2*>(a.rowpart + (((int64_t)b * a.ntn + tn) * a.rp_ld + tile_r0 + tid) * 2) =
+          make_float2(rowred[tid].x + rowred[TILE + tid].x, rowred[tid].y + rowred[TILE + tid].y);
+  } else if (tid < 2 * TILE) {
+    const int c = tid - TILE;
+    if (tile_c0 + c < a.m)
+      *reinterpret_cast<float2*>(a.colpart + (((int64_t)b * a.ntm + tm) * a.cp_ld + tile_c0 + c) * 2) =
+          make_float2(colred[c].x + colred[TILE + c].x, colred[c].y + colred[TILE + c].y);
+  }
+}
+
 // -------------------------------------------------------------------------------------------
 // Grid: one dimension, tiles x batch x ksplit workgroups, and the scans that ride along before or behind them.
 // Consecutive workgroups go to the 8 XCDs in turn, so every XCD is given a contiguous range of the (item,
@@ -308,7 +505,7 @@ __device__ __forceinline__ void side_job(const GemmArgs& a, const GemmSide& side
 // HBM-bound and the product is not: in one launch they cost little more than the
 // product alone, and a launch that waits for the one before it costs 4.5 us whatever it does.
 template <int DT, bool KCA, bool KCB, int TILE>
-__global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : 2) void gemm_tile(GemmArgs a, GemmSide side) {
+__global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : DT == GECC_BF16 ? 3 : 2) void gemm_tile(GemmArgs a, GemmSide side) {
   using T = typename GT<DT>::T;
   constexpr int BK = GT<DT>::BK, PIECES = GT<DT>::PIECES, W = TILE / 2, NI = W / 16;   // W x W per wavefront
   constexpr int PLANE = TILE * BK * 2, OPERAND = PIECES * PLANE;
@@ -323,26 +520,9 @@ __global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : 2) void gemm_tile(GemmArg
   __shared__ __attribute__((aligned(16))) char smem[SM0 > SM1 ? SM0 : SM1];
 
   const int S = a.ksplit > 1 ? a.ksplit : 1;
-  const int ntm = (a.n + TILE - 1) / TILE, ntn = (a.m + TILE - 1) / TILE;
-  int id = blockIdx.x;
-  if (side.groups > 0) {
-    // in whole groups of 8 workgroups (one per XCD): side.lead of P_g and, where they go first, the scans; then the
-    // product's; then the scans
-    const int first = side.lead * 8, own = (side.own + 7) / 8 * 8;
-    if (id < first || id >= first + own) {
-      const int v = id < first ? id : side.lead_blocks + id - first - own;
-      if (v < (id < first ? side.lead_blocks : side.blocks)) side_job<DT>(a, side, v, reinterpret_cast<double*>(smem));
-      return;
-    }
-    id -= first;
-    if (id >= side.own) return;
-  }
-  {
-    const int N = side.own, per = N / 8, rem = N - per * 8, x = id & 7;
-    id = x * per + min(x, rem) + (id >> 3);
-  }
-  const int tn = id % ntn, tm = (id / ntn) % ntm, bs = id / (ntn * ntm);
-  const int b = bs / S, split = bs - b * S;
+  Place o;
+  if (!place<DT, TILE>(a, side, S, smem, o)) return;
+  const int tm = o.tm, tn = o.tn, b = o.b, split = o.split;
   const int k_begin = S > 1 ? min(a.k, split * a.k_per) : 0;
   const int k_end = S > 1 ? min(a.k, k_begin + a.k_per) : a.k;
   const int tile_r0 = tm * TILE, tile_c0 = tn * TILE;
@@ -514,15 +694,7 @@ __global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : 2) void gemm_tile(GemmArg
     }
   }
   // rows and columns past the end count as zero
-  if (tile_r0 + TILE > a.n || tile_c0 + TILE > a.m) {
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-#pragma unroll
-      for (int j = 0; j < NI; ++j)
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          if (tile_r0 + wr * W + i * 16 + lg * 4 + v >= a.n || tile_c0 + wc * W + j * 16 + l16 >= a.m) acc[i][j][v] = 0.f;
-  }
+  mask_edges<TILE>(a, tile_r0, tile_c0, acc);
 
   if constexpr (DT == GECC_F32) {
     float worst = 0.f;             // 0, or NaN when some accumulator is not finite
@@ -563,155 +735,12 @@ __global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : 2) void gemm_tile(GemmArg
           }
         }
       }
-      if (tile_r0 + TILE > a.n || tile_c0 + TILE > a.m) {
-#pragma unroll
-        for (int i = 0; i < NI; ++i)
-#pragma unroll
-          for (int j = 0; j < NI; ++j)
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-              if (tile_r0 + wr * W + i * 16 + lg * 4 + v >= a.n || tile_c0 + wc * W + j * 16 + l16 >= a.m) acc[i][j][v] = 0.f;
-      }
+      mask_edges<TILE>(a, tile_r0, tile_c0, acc);
     }
   }
 
-  if (S > 1) {
-    // k-split: every workgroup of the tile leaves its partial sums in memory (in register order: whole
-    // lines per store); the one that arrives last adds them all up in the order of the k ranges (so the
-    // result does not depend on which one that is) and goes on with the tile.
-    const int64_t tile_id = ((int64_t)b * ntm + tm) * ntn + tn;
-    float* part = a.split_part + tile_id * S * (TILE * TILE);
-    float* mine = part + (int64_t)split * (TILE * TILE) + tid;
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-#pragma unroll
-      for (int j = 0; j < NI; ++j)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) store_dev(mine + ((i * NI + j) * 4 + v) * THREADS, acc[i][j][v]);
-    if (!arrive_last(a.split_done + tile_id, (uint32_t)S, reinterpret_cast<int*>(smem))) return;
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-#pragma unroll
-      for (int j = 0; j < NI; ++j)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
-    for (int q = 0; q < S; ++q) {
-      const float* src = part + (int64_t)q * (TILE * TILE) + tid;
-#pragma unroll
-      for (int i = 0; i < NI; ++i)
-#pragma unroll
-        for (int j = 0; j < NI; ++j)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) acc[i][j][v] += load_dev(src + ((i * NI + j) * 4 + v) * THREADS);
-    }
-  }
-
-  // ---- epilogue, from the accumulators -------------------------------------------------------------
-  // Test faults (none in production calls): the workgroup searches the list for those that strike its
-  // tile, then every wavefront adds them to its accumulators.
-  if (a.n_faults > 0) {
-    int* hits = reinterpret_cast<int*>(smem);
-    int2* hit = reinterpret_cast<int2*>(smem + 16);
-    __syncthreads();
-    if (tid == 0) *hits = 0;
-    __syncthreads();
-    for (int f = tid; f < a.n_faults; f += THREADS) {
-      const gecc_fault ft = a.faults[f];
-      const int r = ft.row - tile_r0, c = ft.col - tile_c0;
-      if (ft.batch == b + a.fault_bias && r >= 0 && r < min(TILE, a.n - tile_r0) && c >= 0 && c < min(TILE, a.m - tile_c0))
-        hit[atomicAdd(hits, 1)] = make_int2(r * TILE + c, __float_as_int(ft.offset));
-    }
-    __syncthreads();
-    const int nh = *hits;
-    for (int f = 0; f < nh; ++f) {
-      const int r = hit[f].x / TILE - wr * W, c = hit[f].x % TILE - wc * W;
-      const float off = __int_as_float(hit[f].y);
-      const bool mine = r >= 0 && r < W && c >= 0 && c < W && ((r >> 2) & 3) == lg && (c & 15) == l16;
-#pragma unroll
-      for (int i = 0; i < NI; ++i)
-#pragma unroll
-        for (int j = 0; j < NI; ++j)
-#pragma unroll
-          for (int v = 0; v < 4; ++v)
-            if (mine && i == r >> 4 && j == c >> 4 && v == (r & 3)) acc[i][j][v] += off;
-    }
-  }
-
-  // C: the registers of two neighbouring 16-column blocks first trade their odd / even groups of 16 lanes
-  // (v_permlane16_swap): each then holds 2 rows x 32 consecutive columns, two full lines per store
-  {
-    const int R0 = tile_r0 + wr * W + (lg >> 1) * 8, C0 = tile_c0 + wc * W + (lg & 1) * 16 + l16;
-    float* C = a.C + (int64_t)b * a.sc + (int64_t)R0 * a.ldc + C0;
-    const bool whole = tile_r0 + TILE <= a.n && tile_c0 + TILE <= a.m;
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-#pragma unroll
-        for (int jp = 0; jp < NI / 2; ++jp) {
-          float t0 = acc[i][2 * jp][v], t1 = acc[i][2 * jp + 1][v];
-          // (inline: this compiler's builtin for the swap loses its second result; the wait states are the
-          // ones a swap needs after a vector instruction wrote its operands)
-          asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(t0), "+v"(t1));
-          float* dst = C + (int64_t)(i * 16 + v) * a.ldc + jp * 32;
-          if (whole) {
-            dst[0] = t0;
-            dst[4 * a.ldc] = t1;
-          } else if (C0 + jp * 32 < a.m) {
-            if (R0 + i * 16 + v < a.n) dst[0] = t0;
-            if (R0 + i * 16 + v + 4 < a.n) dst[4 * a.ldc] = t1;
-          }
-        }
-  }
-  if (!a.rowpart) return;
-
-  // Row sums: a lane adds its columns of a row (plain, and u = sum of j x_j: the block part of the column
-  // weight), the 16 lanes of a group are added across the lanes; lane l16 of a group keeps row number
-  // l16 = 4 i + v of its 4 NI.  Column sums: in the lane, then across the four groups; group lg keeps block lg.
-  float2* rowred = reinterpret_cast<float2*>(smem);          // [2: wc][TILE]
-  float2* colred = rowred + 2 * TILE;                         // [2: wr][TILE]
-  __syncthreads();
-  {
-    float ks = 0.f, kw = 0.f;
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        float s = acc[i][0][v], u = 0.f;
-#pragma unroll
-        for (int j = 1; j < NI; ++j) { s += acc[i][j][v]; u = fmaf((float)j, acc[i][j][v], u); }
-        const float w = row16_sum(fmaf((float)(l16 + 1), s, 16.f * u));
-        s = row16_sum(s);
-        if (l16 == i * 4 + v) { ks = s; kw = w; }
-      }
-    if (l16 < 4 * NI)
-      rowred[wc * TILE + wr * W + (l16 >> 2) * 16 + lg * 4 + (l16 & 3)] = make_float2(ks, fmaf((float)(wc * W), ks, kw));
-    float cs = 0.f, cw = 0.f;
-#pragma unroll
-    for (int j = 0; j < NI; ++j) {
-      float s = 0.f, w = 0.f;
-#pragma unroll
-      for (int i = 0; i < NI; ++i)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) { s += acc[i][j][v]; w = fmaf((float)(i * 16 + v + 1), acc[i][j][v], w); }
-      w = fmaf((float)(lg * 4), s, w);
-      s += __shfl_xor(s, 16, 64); w += __shfl_xor(w, 16, 64);
-      s += __shfl_xor(s, 32, 64); w += __shfl_xor(w, 32, 64);
-      if (lg == j) { cs = s; cw = w; }
-    }
-    if (lg < NI) colred[wr * TILE + wc * W + lg * 16 + l16] = make_float2(cs, fmaf((float)(wr * W), cs, cw));
-  }
-  __syncthreads();
-  if (tid < TILE) {
-    if (tile_r0 + tid < a.n)
-      *reinterpret_cast<float2*>(a.rowpart + (((int64_t)b * a.ntn + tn) * a.rp_ld + tile_r0 + tid) * 2) =
-          make_float2(rowred[tid].x + rowred[TILE + tid].x, rowred[tid].y + rowred[TILE + tid].y);
-  } else if (tid < 2 * TILE) {
-    const int c = tid - TILE;
-    if (tile_c0 + c < a.m)
-      *reinterpret_cast<float2*>(a.colpart + (((int64_t)b * a.ntm + tm) * a.cp_ld + tile_c0 + c) * 2) =
-          make_float2(colred[c].x + colred[TILE + c].x, colred[c].y + colred[TILE + c].y);
-  }
+  if (S > 1 && !add_splits<TILE>(a, b, tm, tn, split, S, acc, smem)) return;
+  finish_tile<TILE>(a, b, tm, tn, acc, smem);
 }
 
 // -------------------------------------------------------------------------------------------
