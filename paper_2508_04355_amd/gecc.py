@@ -122,12 +122,20 @@ def _check(rc):
         raise GeccError("libgecc: %s (code %d)" % (lib().gecc_strerror(rc).decode(), rc))
 
 
+# The handle of the current stream without a torch.cuda.Stream around it: 0.1 us instead of 3, of the 20 to 30 us that the host
+# spends on a protected call (its five launches take 4 each).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is None or _device is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return C.c_void_p(0 if t is None else t.data_ptr())
+    return 0 if t is None else t.data_ptr()
 
 
 @dataclass
