@@ -297,7 +297,7 @@ __device__ __forceinline__ void side_job(const GemmArgs& a, const GemmSide& side
   const int per_item = j.gx * j.gy;
   const int b = v / per_item, x = (v % per_item) % j.gx, y = (v % per_item) / j.gx;
   if (j.kind == SIDE_ROW) rowdot_body<DT, false, side_rows<DT>(), 1>(j.s, x, b, lds);
-  else if (j.kind == SIDE_COL) coldot_body<DT, false, DT == GECC_F32 ? 4 : 2, CD_ASK, true>(j.s, j.w, j.gy, j.gx, x, y, b, lds);
+  else if (j.kind == SIDE_COL) coldot_body<Elem<DT>, false, DT == GECC_F32 ? 4 : 2, CD_ASK, true>(j.s, j.w, j.gy, j.gx, x, y, b, lds);
   else if constexpr (DT == GECC_F32) rowdot_wave_body<DT, false>(j.s, x, b, lds);
 }
 

@@ -49,6 +49,24 @@ template <> struct Elem<GECC_BF16> {
   }
 };
 
+// the same in vectors of 8 bytes
+template <int DT> struct ElemHalf;
+template <> struct ElemHalf<GECC_F32> : Elem<GECC_F32> {
+  static constexpr int VEC = 2;
+  using raw = float2;
+  static __device__ __forceinline__ raw load_raw(const float* p) { raw x; __builtin_memcpy(&x, p, 8); return x; }
+  static __device__ __forceinline__ void widen(const raw& x, double* v) { v[0] = x.x; v[1] = x.y; }
+};
+template <> struct ElemHalf<GECC_BF16> : Elem<GECC_BF16> {
+  static constexpr int VEC = 4;
+  using raw = uint2;
+  static __device__ __forceinline__ raw load_raw(const uint16_t* p) { raw x; __builtin_memcpy(&x, p, 8); return x; }
+  static __device__ __forceinline__ void widen(const raw& x, double* v) {
+    v[0] = (double)__uint_as_float(x.x << 16); v[1] = (double)__uint_as_float(x.x & 0xffff0000u);
+    v[2] = (double)__uint_as_float(x.y << 16); v[3] = (double)__uint_as_float(x.y & 0xffff0000u);
+  }
+};
+
 __device__ __forceinline__ bool gated_off(const int32_t* gate, int64_t stride, int b, int value) {
   if (!gate) return false;
   const int32_t g = *reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(gate) + stride * b);
@@ -465,16 +483,16 @@ constexpr int CD_FLAG_AT = 1024;     // (behind what coldot_finish_segment uses)
 // segment's last chunk also adds the chunks up (no second stage to launch).
 // CD_NB: rows a wavefront loads at once (its sums do not depend on it)
 // WPARTS: explicit weights that may still be in parts (wp).  Every workgroup adds up those of its own rows, which costs less
-// than the launch that would have to come first, and keeps them in LDS.  (Not in the scans' own launches: 117 MB bf16 29 us
-// instead of 25, for the registers.)
+// than the launch that would have to come first.  (Not in the scans' own launches, for the registers.)
 // ONE: whether the one chunk of a short column (nchunk == 1) is taken for the sums themselves: never, in this launch, or where
 // it turns out to be one (0.3 us of a long column's 6 to 10, for the question)
 constexpr int CD_ROWS = 8;
 enum : int { CD_CHUNKS = 0, CD_ONE = 1, CD_ASK = 2 };
-template <int DT, bool IDXW, int CD_NB, int ONE, bool WPARTS = false>
+// E: Elem, or ElemHalf for a scan of few workgroups: half the columns to each, so that twice as many share the rows out, and as many
+// bytes of a wavefront's rows on their way (the sums of a column are the same)
+template <class E, bool IDXW, int CD_NB, int ONE, bool WPARTS = false>
 __device__ __forceinline__ void coldot_body(const ScanArgs& a, const Parts& wp, int nchunk, int nsegx, int bx, int chunk,
                                             int b, double* lds) {
-  using E = Elem<DT>;
   using T = typename E::type;
   constexpr int VEC = E::VEC;
   const T* X = reinterpret_cast<const T*>(a.X) + (int64_t)b * a.xs;
@@ -489,56 +507,63 @@ __device__ __forceinline__ void coldot_body(const ScanArgs& a, const Parts& wp, 
   const bool owns = (bx * 64 + lane) * VEC < a.Cc;
   const double* w0 = IDXW ? nullptr : a.w + (int64_t)b * a.w_stride;
   const double* w1 = IDXW ? nullptr : w0 + a.R;
-  const double2* wl = reinterpret_cast<const double2*>(lds);      // weights of the chunk's rows
-  if constexpr (WPARTS) {
+  // Explicit weights of the chunk's rows go to LDS first: read where they are needed, every row waits for its own (bf16 4096^2 12.1 ->
+  // 8.8 us, 3001^2 10.3 -> 7.6, 4096 x 14336 25.4 -> 23.3, 16384 x 4096 30.3 -> 28.3)
+  const double2* wl = reinterpret_cast<const double2*>(lds);
+  auto load_weights = [&] {
     const int t = tid / SCAN_CHUNK_ROWS, row = rbeg + tid % SCAN_CHUNK_ROWS;
     static_assert(CD_THREADS == 2 * SCAN_CHUNK_ROWS, "a thread per weight");
     if (row < rend) {
-      const bool parts = wp.nchunk > 0 || wp.nseg > 0;
+      const bool parts = WPARTS && (wp.nchunk > 0 || wp.nseg > 0);
       lds[2 * (row - rbeg) + t] = parts ? parts_sum(wp, b, a.R, t, row) : (t ? w1 : w0)[row];
     }
     __syncthreads();
-  }
+  };
   auto weights = [&](int row, double& wa, double& wb) {
     if (IDXW) { wa = 1.0; wb = (double)(row + 1); }
-    else if (WPARTS) { const double2 w = wl[row - rbeg]; wa = w.x; wb = w.y; }
-    else { wa = w0[row]; wb = w1[row]; }
+    else { const double2 w = wl[row - rbeg]; wa = w.x; wb = w.y; }
   };
 
   double acc0[VEC], acc1[VEC];
 #pragma unroll
   for (int e = 0; e < VEC; ++e) { acc0[e] = 0.0; acc1[e] = 0.0; }
 
-  if (owns && a.Cc >= VEC) {
-    // Batches of CD_NB rows per wavefront, double buffered: the loads of the next batch are in
-    // flight while this one is added up (a wavefront walks its rows one batch after the other,
-    // so without this every batch would pay the full memory latency).
-    typename E::raw xa[CD_NB], xb[CD_NB];
-    const T* col = X + c;
-    auto load = [&](typename E::raw* x, int rr) {
+  // Batches of CD_NB rows per wavefront, double buffered: the loads of the next batch are in
+  // flight while this one is added up (a wavefront walks its rows one batch after the other,
+  // so without this every batch would pay the full memory latency).
+  typename E::raw xa[CD_NB], xb[CD_NB];
+  const bool vec = owns && a.Cc >= VEC;
+  const T* col = X + c;
+  auto load = [&](typename E::raw* x, int rr) {
 #pragma unroll
-      for (int u = 0; u < CD_NB; ++u) x[u] = E::load_raw(col + (int64_t)(rr + 4 * u) * a.ld);
+    for (int u = 0; u < CD_NB; ++u) x[u] = E::load_raw(col + (int64_t)(rr + 4 * u) * a.ld);
+  };
+  int r = rbeg + wave;
+  const int cnt = r < rend ? (rend - r + 3) / 4 : 0;   // rows of this wavefront
+  const int nb = cnt / CD_NB;
+  if (vec && nb > 0) load(xa, r);
+  if (!IDXW) load_weights();
+  if (vec) {
+    auto add_row = [&](const typename E::raw& x, int row) {
+      double v[VEC];
+      E::widen(x, v);
+      double wa, wb;
+      weights(row, wa, wb);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        acc0[e] = IDXW ? acc0[e] + v[e] : fma(wa, v[e], acc0[e]);
+        acc1[e] = fma(wb, v[e], acc1[e]);
+      }
     };
     auto add = [&](const typename E::raw* x, int rr) {
 #pragma unroll
       for (int u = 0; u < CD_NB; ++u) {
-        double v[VEC];
-        E::widen(x[u], v);
-        double wa, wb;
-        weights(rr + 4 * u, wa, wb);
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-          acc0[e] = IDXW ? acc0[e] + v[e] : fma(wa, v[e], acc0[e]);
-          acc1[e] = fma(wb, v[e], acc1[e]);
-        }
+        add_row(x[u], rr + 4 * u);
+        if (!IDXW && u % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // (weights of four rows at a time: registers)
       }
     };
-    int r = rbeg + wave;
-    const int cnt = r < rend ? (rend - r + 3) / 4 : 0;   // rows of this wavefront
-    const int nb = cnt / CD_NB;
     constexpr int STEP = 4 * CD_NB;
     if (nb > 0) {
-      load(xa, r);
       int bi = 0;
       for (; bi + 1 < nb; bi += 2) {
         load(xb, r + STEP);
@@ -549,19 +574,16 @@ __device__ __forceinline__ void coldot_body(const ScanArgs& a, const Parts& wp, 
       }
       if (bi < nb) { add(xa, r); r += STEP; }
     }
-    for (; r < rend; r += 4) {
-      double v[VEC];
-      E::load_vec(col + (int64_t)r * a.ld, v);
-      double wa, wb;
-      weights(r, wa, wb);
+    if (r < rend) {
+      // the last few rows, loaded together as well (one after the other they took a latency each)
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) {
-        acc0[e] = IDXW ? acc0[e] + v[e] : fma(wa, v[e], acc0[e]);
-        acc1[e] = fma(wb, v[e], acc1[e]);
-      }
+      for (int u = 0; u < CD_NB; ++u) xa[u] = E::load_raw(col + (int64_t)min(r + 4 * u, rend - 1) * a.ld);
+#pragma unroll
+      for (int u = 0; u < CD_NB; ++u)
+        if (r + 4 * u < rend) add_row(xa[u], r + 4 * u);
     }
   } else if (owns) {
-    for (int r = rbeg + wave; r < rend; r += 4) {
+    for (; r < rend; r += 4) {
       double wa, wb;
       weights(r, wa, wb);
 #pragma unroll
@@ -575,7 +597,7 @@ __device__ __forceinline__ void coldot_body(const ScanArgs& a, const Parts& wp, 
   }
 
   double (*red)[2][VEC][64] = reinterpret_cast<double (*)[2][VEC][64]>(lds);
-  if (WPARTS) __syncthreads();     // every wavefront is done with the weights
+  if (!IDXW) __syncthreads();      // every wavefront is done with the weights
 #pragma unroll
   for (int e = 0; e < VEC; ++e) { red[wave][0][e][lane] = acc0[e]; red[wave][1][e][lane] = acc1[e]; }
   __syncthreads();
@@ -824,7 +846,7 @@ __device__ __forceinline__ void pair_body(const PairJob& j, int x, int y, int b,
   if (j.kind == PJ_ROW) rowdot_body<DT, true, RD_SMALL_RB, RD_SMALL_U>(j.s, x, b, lds);
   else if (j.kind == PJ_ROW_BIG) rowdot_body<DT, true, RD_BIG_RB, RD_BIG_U>(j.s, x, b, lds);
   else if (j.kind == PJ_ROW_WAVE) rowdot_wave_body<DT, true>(j.s, x, b, lds);
-  else if (j.kind == PJ_COL) coldot_body<DT, true, CD_ROWS, CD_CHUNKS>(j.s, Parts{}, j.gy, j.gx, x, y, b, lds);
+  else if (j.kind == PJ_COL) coldot_body<Elem<DT>, true, CD_ROWS, CD_CHUNKS>(j.s, Parts{}, j.gy, j.gx, x, y, b, lds);
   else if (j.kind == PJ_TILE_COL) tile_scan_body<DT, true, false, true, true>(j.t, x, y, b, lds);
   else tile_scan_body<DT, false, true, true, true>(j.t, x, y, b, lds);
 }

@@ -37,12 +37,18 @@ __global__ __launch_bounds__(RD_THREADS) void rowdot_kernel(ScanArgs a) {
   rowdot_body<DT, IDXW, RD_RB, RD_U>(a, blockIdx.x, b, lds);
 }
 
-template <int DT, bool IDXW, bool GATED, bool ONE>
+// Column scans of few workgroups take vectors of 8 bytes and twice the rows at once (see coldot_body).  With 16 -> 8 bytes, bf16:
+// 4096^2 index weights 8.9 -> 7.9 us, explicit 8.8 either way; 4096 x 14336, 896 workgroups, 25.4 -> 23.3 with the weights in LDS
+// in both; two of 4096^2 in a launch 16.4 -> 23.0, of 2048^2 7.6 -> 7.0, of 3001^2 13.9 -> 11.8.
+template <int DT, bool HALF> using ColElem = std::conditional_t<HALF, ElemHalf<DT>, Elem<DT>>;
+constexpr int CD_HALF_BELOW = 1024, CD_PAIR_HALF_BELOW = 512;       // workgroups of the scan (of both of a pair) in vectors of 16 bytes
+
+template <int DT, bool IDXW, bool GATED, bool ONE, bool HALF>
 __global__ __launch_bounds__(CD_THREADS) void coldot_stage1(ScanArgs a, int nchunk) {
   __shared__ double lds[CD_LDS_DOUBLES];
   const int b = blockIdx.z;
   if (GATED && gated_off(a.gate, a.gate_stride, b, a.gate_value)) return;
-  coldot_body<DT, IDXW, CD_ROWS, ONE ? CD_ONE : CD_CHUNKS>(a, Parts{}, nchunk, gridDim.x, blockIdx.x, blockIdx.y, b, lds);
+  coldot_body<ColElem<DT, HALF>, IDXW, HALF ? 2 * CD_ROWS : CD_ROWS, ONE ? CD_ONE : CD_CHUNKS>(a, Parts{}, nchunk, gridDim.x, blockIdx.x, blockIdx.y, b, lds);
 }
 
 __global__ __launch_bounds__(256) void coldot_stage2(Stage2Job j) {
@@ -63,15 +69,15 @@ __global__ __launch_bounds__(256) void coldot_stage2_pair(Stage2Job j0, Stage2Jo
 
 // Two scans that do not read each other's results (both encodings, or both parity blocks): what each of them would
 // leave idle at its end the other one fills, and a launch that waits for the one before it costs 5 us whatever it does.
-// Two parity blocks are scans of one kind, and each kind has a kernel of its own: in one for both, 13 registers of the bf16 column
-// scan spilled at three wavefronts per SIMD (whole calls TN, 4096^3 155.2 -> 150.0 us, 2048^3 74.9 -> 73.1, 6144 x 2048 x 3072 148.9 ->
-// 146.9; row scans, 3072 x 2048 x 6144 NT 150.8 -> 150.0; with two per SIMD instead, those were slower, 152.5).
+// Two parity blocks are scans of one kind, and each kind has a kernel of its own (in one for both, registers of the bf16 column scan
+// spilled).  Row scans keep three wavefronts per SIMD (with two, 3072 x 2048 x 6144 NT 150.0 -> 152.5 us a call); column scans have the weights
+// of four rows in registers, which is worth more than the third wavefront (spilled for it, 4096^3 TN 25.6 us for 16.4).
 struct ScanPair { SideJob j[2]; };
 enum : int { PAIR_ANY = 0,       // (explicit weights: row scans)
              PAIR_WAVE = 1,      // one of them a row scan with a wavefront per RW_RB rows, a third more registers than the others
              PAIR_COLS = 2 };    // two column scans
-template <int DT, bool IDXW, int WHAT>
-__global__ __launch_bounds__(256, WHAT == PAIR_WAVE ? 2 : 3) void scan_pair(ScanPair p) {
+template <int DT, bool IDXW, int WHAT, bool HALF>
+__global__ __launch_bounds__(256, WHAT == PAIR_ANY ? 3 : 2) void scan_pair(ScanPair p) {
   constexpr bool WAVE = WHAT == PAIR_WAVE, COL = IDXW || WHAT == PAIR_COLS;
   constexpr int BIG = IDXW ? RD_BIG_RB : RD_BIG_RB_W;
   static_assert(BIG * RD_THREADS <= CD_LDS_DOUBLES, "LDS of a row scan");
@@ -84,7 +90,7 @@ __global__ __launch_bounds__(256, WHAT == PAIR_WAVE ? 2 : 3) void scan_pair(Scan
   const int b = v / per_item, x = (v % per_item) % j.gx, y = (v % per_item) / j.gx;
   if constexpr (COL) {
     if (WHAT == PAIR_COLS || j.kind == SIDE_COL) {
-      coldot_body<DT, IDXW, CD_ROWS, CD_ASK>(j.s, Parts{}, j.gy, j.gx, x, y, b, lds);
+      coldot_body<ColElem<DT, HALF>, IDXW, HALF ? 2 * CD_ROWS : CD_ROWS, CD_ASK>(j.s, Parts{}, j.gy, j.gx, x, y, b, lds);
       return;
     }
   }
@@ -109,6 +115,12 @@ __global__ __launch_bounds__(TS_THREADS) void tile_scan(TileScanArgs a) {
 // more loads in flight (4096 rows of 2048 fp32 7.7 against 12.1, 1024 of 1024 3.6 against 5.3).
 bool rowdot_wavewise(const ScanArgs& a) {
   return a.Cc <= 2048 && (int64_t)((a.R + 4 * RW_RB - 1) / (4 * RW_RB)) * a.batch >= 512;
+}
+
+// workgroups of a column scan in vectors of 16 bytes
+int64_t coldot_blocks(const ScanArgs& a) {
+  const int seg = 64 * (a.dtype == GECC_BF16 ? 8 : 4);
+  return (int64_t)((a.Cc + seg - 1) / seg) * ((a.R + SCAN_CHUNK_ROWS - 1) / SCAN_CHUNK_ROWS) * a.batch;
 }
 
 }  // namespace
@@ -173,20 +185,28 @@ hipError_t launch_coldot_stage1(const ScanArgs& a0, Stage2Job* pending, hipStrea
   a.carry_blocks = 0;
   const int vec = a.dtype == GECC_BF16 ? 8 : 4;
   const int nchunk = (a.R + SCAN_CHUNK_ROWS - 1) / SCAN_CHUNK_ROWS;
-  dim3 grid((a.Cc + 64 * vec - 1) / (64 * vec), nchunk, a.batch);
   const bool idx = a.w == nullptr, gated = a.gate != nullptr;
+  const bool half = !gated && !a.done && coldot_blocks(a) < CD_HALF_BELOW;
+  const int seg = 64 * (half ? vec / 2 : vec);
+  dim3 grid((a.Cc + seg - 1) / seg, nchunk, a.batch);
   if (gated && !idx) return hipErrorInvalidValue;
   if (a.done && coldot_done_words(a) == 0) return hipErrorInvalidValue;
   // (gated ones leave a chunk of any length to the counters or to the second stage)
   const bool one = nchunk == 1 && !gated && !a.done;
 #define GECC_LAUNCH_COLDOT(DT)                                                                                           \
   do {                                                                                                                   \
-    if (gated)           hipLaunchKernelGGL((coldot_stage1<DT, true, true, false>), grid, dim3(CD_THREADS), 0, st, a, nchunk);   \
-    else if (idx && one) hipLaunchKernelGGL((coldot_stage1<DT, true, false, true>), grid, dim3(CD_THREADS), 0, st, a, nchunk);   \
-    else if (idx)        hipLaunchKernelGGL((coldot_stage1<DT, true, false, false>), grid, dim3(CD_THREADS), 0, st, a, nchunk);  \
-    else if (one)        hipLaunchKernelGGL((coldot_stage1<DT, false, false, true>), grid, dim3(CD_THREADS), 0, st, a, nchunk);  \
-    else                 hipLaunchKernelGGL((coldot_stage1<DT, false, false, false>), grid, dim3(CD_THREADS), 0, st, a, nchunk); \
+    if (gated)           hipLaunchKernelGGL((coldot_stage1<DT, true, true, false, false>), grid, dim3(CD_THREADS), 0, st, a, nchunk);   \
+    else if (half)       launch(std::integral_constant<int, DT>{}, std::true_type{});                                    \
+    else                 launch(std::integral_constant<int, DT>{}, std::false_type{});                                   \
   } while (0)
+  auto launch = [&](auto dt, auto h) {
+    constexpr int DT = decltype(dt)::value;
+    constexpr bool H = decltype(h)::value;
+    if (idx && one)   hipLaunchKernelGGL((coldot_stage1<DT, true, false, true, H>), grid, dim3(CD_THREADS), 0, st, a, nchunk);
+    else if (idx)     hipLaunchKernelGGL((coldot_stage1<DT, true, false, false, H>), grid, dim3(CD_THREADS), 0, st, a, nchunk);
+    else if (one)     hipLaunchKernelGGL((coldot_stage1<DT, false, false, true, H>), grid, dim3(CD_THREADS), 0, st, a, nchunk);
+    else              hipLaunchKernelGGL((coldot_stage1<DT, false, false, false, H>), grid, dim3(CD_THREADS), 0, st, a, nchunk);
+  };
   if (a.dtype == GECC_BF16) GECC_LAUNCH_COLDOT(GECC_BF16); else GECC_LAUNCH_COLDOT(GECC_F32);
 #undef GECC_LAUNCH_COLDOT
   *pending = Stage2Job{};
@@ -335,8 +355,10 @@ bool make_side_job(const ScanArgs& s, const Parts& w, bool rowdot, uint32_t* don
 
 namespace {
 // the two scans as jobs of one grid; returns its workgroups
-int64_t plan_pair(const ScanArgs* s, const bool* rowdot, ScanPair& p, Parts* left) {
+int64_t plan_pair(const ScanArgs* s, const bool* rowdot, ScanPair& p, Parts* left, bool& half) {
   int64_t grid = 0;
+  const int64_t cols = (rowdot[0] ? 0 : coldot_blocks(s[0])) + (rowdot[1] ? 0 : coldot_blocks(s[1]));
+  half = cols > 0 && cols < CD_PAIR_HALF_BELOW;
   for (int i = 0; i < 2; ++i) {
     SideJob& j = p.j[i];
     j.s = s[i];
@@ -350,9 +372,9 @@ int64_t plan_pair(const ScanArgs* s, const bool* rowdot, ScanPair& p, Parts* lef
       j.kind = wavewise ? SIDE_ROW_WAVE : small ? SIDE_ROW : SIDE_ROW_BIG;
       j.gx = (s[i].R + rb - 1) / rb; j.gy = 1;
     } else {
-      const int vec = s[i].dtype == GECC_BF16 ? 8 : 4;
+      const int seg = 64 * (s[i].dtype == GECC_BF16 ? 8 : 4) / (half ? 2 : 1);
       j.kind = SIDE_COL;
-      j.gx = (s[i].Cc + 64 * vec - 1) / (64 * vec);
+      j.gx = (s[i].Cc + seg - 1) / seg;
       j.gy = (s[i].R + SCAN_CHUNK_ROWS - 1) / SCAN_CHUNK_ROWS;
       if (j.gy > 1) { left[i].chunks = s[i].scratch; left[i].nchunk = j.gy; }
     }
@@ -367,25 +389,30 @@ int64_t plan_pair(const ScanArgs* s, const bool* rowdot, ScanPair& p, Parts* lef
 bool scan_pair_fits(const ScanArgs* s, const bool* rowdot) {
   ScanPair p{};
   Parts left[2];
-  return plan_pair(s, rowdot, p, left) <= 0xffffff;          // (2^32 threads)
+  bool half;
+  return plan_pair(s, rowdot, p, left, half) <= 0xffffff;          // (2^32 threads)
 }
 
 hipError_t launch_scan_pair(const ScanArgs* s, const bool* rowdot, Parts* left, hipStream_t st) {
   for (int i = 0; i < 2; ++i)
     if (s[i].gate || s[i].dtype != s[0].dtype || (s[i].w == nullptr) != (s[0].w == nullptr)) return hipErrorInvalidValue;
   ScanPair p{};
-  const int64_t grid = plan_pair(s, rowdot, p, left);
+  bool half;
+  const int64_t grid = plan_pair(s, rowdot, p, left, half);
   if (grid > 0xffffff) return hipErrorInvalidValue;
   const dim3 g((unsigned)grid), block(256);
   const bool idx = s[0].w == nullptr, wave = p.j[0].kind == SIDE_ROW_WAVE || p.j[1].kind == SIDE_ROW_WAVE;
   if (!idx && rowdot[0] != rowdot[1]) return hipErrorInvalidValue;
 #define GECC_LAUNCH_PAIR(DT)                                                                            \
   do {                                                                                                  \
-    if (idx && wave)     hipLaunchKernelGGL((scan_pair<DT, true, PAIR_WAVE>), g, block, 0, st, p);      \
-    else if (idx)        hipLaunchKernelGGL((scan_pair<DT, true, PAIR_ANY>), g, block, 0, st, p);       \
-    else if (wave)       hipLaunchKernelGGL((scan_pair<DT, false, PAIR_WAVE>), g, block, 0, st, p);     \
-    else if (!rowdot[0]) hipLaunchKernelGGL((scan_pair<DT, false, PAIR_COLS>), g, block, 0, st, p);     \
-    else                 hipLaunchKernelGGL((scan_pair<DT, false, PAIR_ANY>), g, block, 0, st, p);      \
+    if (idx && wave && half)     hipLaunchKernelGGL((scan_pair<DT, true, PAIR_WAVE, true>), g, block, 0, st, p);   \
+    else if (idx && wave)        hipLaunchKernelGGL((scan_pair<DT, true, PAIR_WAVE, false>), g, block, 0, st, p);  \
+    else if (idx && half)        hipLaunchKernelGGL((scan_pair<DT, true, PAIR_ANY, true>), g, block, 0, st, p);    \
+    else if (idx)                hipLaunchKernelGGL((scan_pair<DT, true, PAIR_ANY, false>), g, block, 0, st, p);   \
+    else if (wave)               hipLaunchKernelGGL((scan_pair<DT, false, PAIR_WAVE, false>), g, block, 0, st, p); \
+    else if (!rowdot[0] && half) hipLaunchKernelGGL((scan_pair<DT, false, PAIR_COLS, true>), g, block, 0, st, p);  \
+    else if (!rowdot[0])         hipLaunchKernelGGL((scan_pair<DT, false, PAIR_COLS, false>), g, block, 0, st, p); \
+    else                         hipLaunchKernelGGL((scan_pair<DT, false, PAIR_ANY, false>), g, block, 0, st, p);  \
   } while (0)
   if (s[0].dtype == GECC_BF16) GECC_LAUNCH_PAIR(GECC_BF16); else GECC_LAUNCH_PAIR(GECC_F32);
 #undef GECC_LAUNCH_PAIR

@@ -296,3 +296,29 @@ def test_ragged_tiles_in_the_kernel_with_256_by_256_tiles(pad, trans, monkeypatc
     g = H.run_gpu(A, B, A, B, cf, tau, "bf16", trans[0], trans[1], ld_pad=pad)
     H.compare(g, H.run_oracle(A, B, A, B, cf, tau), 1e-5, what="256 tiles, pad %d" % pad)
     assert g.pad_untouched and [e[:3] for e in g.reports[0].errors()] == [(2, 256, 0), (2, n - 1, m - 1)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("trans", [(0, 0), (1, 0), (0, 1)])
+@pytest.mark.parametrize("shape", [(129, 130, 131), (255, 513, 3), (5, 640, 257), (96, 4133, 71),
+                                   (260, 300, 16200)])      # more column scan workgroups than take vectors of 8 bytes
+def test_column_scans_at_their_ends(shape, dtype, trans):
+    """Rows that end in the middle of a vector of 8 or 16 bytes, chunks whose last rows are no whole batch, rows shorter than a
+    vector: operand parities and parity blocks in fp64, rounded k times (n, m times) at most, in any order."""
+    import torch
+    import gpu_harness as H
+    n, k, m = shape
+    law = ("normal", 1.0)
+    A, B = inputs.operands(inputs.rng_for(84, n + k), n, k, m, law, law, dtype)
+    g = H.run_gpu(A, B, A, B, [], gecc.noise_thresholds(n, k, m, 1.0, 1.0), dtype, trans[0], trans[1])
+    A, B = A.astype(np.float64), B.astype(np.float64)
+    wn, wm = np.arange(1, n + 1.0), np.arange(1, m + 1.0)
+    aP, bP = np.stack([A.sum(0), wn @ A]), np.stack([B.sum(1), B @ wm])
+    mag_a, mag_b = np.stack([np.abs(A).sum(0), wn @ np.abs(A)]), np.stack([np.abs(B).sum(1), np.abs(B) @ wm])
+    eps = 2.0 ** -52
+    assert (np.abs(g.A_par[0] - aP) <= n * eps * mag_a).all() and (np.abs(g.B_par[0] - bP) <= m * eps * mag_b).all()
+    pr, pc = (A @ bP.T).T, aP @ B
+    mr, mc = (np.abs(A) @ mag_b.T).T, mag_a @ np.abs(B)
+    got = g.C_par[0]
+    assert (np.abs(got[:2 * n].reshape(2, n) - pr) <= 2 * (k + m) * eps * mr).all()
+    assert (np.abs(got[2 * n:2 * n + 2 * m].reshape(2, m) - pc) <= 2 * (k + n) * eps * mc).all()
