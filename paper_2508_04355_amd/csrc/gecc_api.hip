@@ -87,6 +87,19 @@ int ksplit_bf16_128(int64_t t128, int k) {
   return best;
 }
 
+// Times of bf16 products in gemm_tile, product alone, as fitted to measurements (aligned rows, NN; us): what a workgroup needs per
+// term of k with as many beside it on its compute unit, and the exchange between s ranges (C goes out and in s times).
+double exchange(int64_t symbols, int s) { return s > 1 ? 1.8e-6 * (double)symbols * s : 0.0; }
+double time_128(int64_t k, int64_t t128, int s) {
+  const int64_t per_cu = (t128 * s + 255) / 256;
+  if (per_cu > 3) return 6.0 + 2e-9 * (double)t128 * 16384.0 * (double)k / 0.66 + exchange(t128 * 16384, s);
+  return 5.4 + (double)k / s * (per_cu == 1 ? 0.0153 : per_cu == 2 ? 0.0175 : 0.0265) + exchange(t128 * 16384, s);
+}
+double time_64(int64_t k, int64_t t64, int s) {
+  const int64_t per_cu = (t64 * s + 255) / 256;
+  return 4.0 + (double)k / s * (per_cu == 1 ? 0.0087 : per_cu == 2 ? 0.0105 : per_cu == 3 ? 0.0135 : 0.0043 * (double)per_cu) + exchange(t64 * 4096, s);
+}
+
 // 128 x 128 tiles: products with tiles enough for every compute unit, as long as tiles that hang over the
 // edge do not eat up what the larger tile gains (a saturated chip does a 128 x 128 tile in the time of three
 // 64 x 64 ones: fp32, 256 x 512^3, 428 against 568; 64 x 300^3, 61 against 46), and bf16 products of long k
@@ -101,31 +114,62 @@ int ksplit_bf16_128(int64_t t128, int k) {
 // 100 tiles, 128 -> 100: 25.1 -> 24.2, 25.6 -> 25.1), bf16 450 (ranges of 128 -> as many as then remain: 700^3 in 4 -> 1 26.9 -> 25.8, 400 x 700 x 800 in 5 -> 1
 // 26.7 -> 24.3, 600 x 1400 x 600 in 5 -> 3 28.6 -> 27.2, 300 x 2000 x 400 in 8 -> 4 28.4 -> 25.7, 1200 x 1800 x 400 TN in 4 -> 3 31.7 -> 30.1),
 // fp32 tiles of 128 two (2000 x 1000 x 2000: 83, split in two 67).
+// bf16: whichever tile and ranges the fitted times say (whole calls, one range of 128 x 128 tiles -> two: 2048 x 1024 x 2048 38.5 -> 44.3, 2048^3 56.2 ->
+// 54.1, 1792 x 2048 x 2304 NT 57.9 -> 54.4, 2048 x 4096 x 2048 94.3 -> 81.5; tiles of 64 -> of 128: 1920 x 512 x 2176 35.7 -> 32.5, 1024^3 28.7 -> 35.5).
 // narrow: a side product of blocked mode, a few columns (rows) beside a whole operand; its bf16 ranges are as they were measured, two and
 // a half workgroups and 128 terms.
 ProductPlan plan_tiles(int dtype, int64_t n, int64_t k, int64_t m, int64_t batch, bool narrow = false) {
   const int64_t t128 = ((n + 127) / 128) * ((m + 127) / 128) * batch, t64 = ((n + 63) / 64) * ((m + 63) / 64) * batch;
-  const int s_long = dtype == GECC_BF16 ? ksplit_bf16_128(t128, (int)k) : 0;
-  if (s_long > 0) return {128, s_long, false};
+  if (dtype == GECC_BF16 && narrow) {
+    const int s_long = ksplit_bf16_128(t128, (int)k);
+    if (s_long > 0) return {128, s_long, false};
+  } else if (dtype == GECC_BF16 && t128 <= 576) {
+    // by the times of either tile, as fitted; an exchange of up to 38 MB (the static scratch has 48)
+    const int s64 = ksplit_of(t64, 512, (int)k, 450);
+    int s128 = 1;
+    for (int s = 2; s <= 8 && t128 * s <= 576 && k / s >= 512; ++s)
+      if (time_128(k, t128, s) < time_128(k, t128, s128)) s128 = s;
+    const bool large = t128 >= 256 && k >= 256 && 3 * t128 < t64;
+    if (large || time_128(k, t128, s128) < time_64(k, t64, s64)) return {128, s128, false};
+    return {64, s64, false};
+  }
   if (t128 >= 256 && k >= 256 && 3 * t128 < t64) return {128, dtype == GECC_F32 && t128 < 512 ? 2 : 1, false};
   return {64, dtype == GECC_F32 ? ksplit_of(t64, t64 > 256 ? 1024 : 800, (int)k, t64 <= 64 ? 64 : t64 <= 128 ? 96 : 128) :
               narrow ? ksplit_of(t64, 512 + (int)(t64 < 512 ? t64 / 2 : 0), (int)k) : ksplit_of(t64, 512, (int)k, 450), false};
 }
 
 // Whether the 256 x 256-tile kernel is the faster one for a bf16 product it can take: it needs a workgroup per
-// compute unit to show its rate (1300 TFLOP/s; gemm_tile comes to 650 on large products), and has no k-split for fewer
-// tiles.  Both times for products of few tiles, where gemm_tile does 330 (64 x 64) to 420 TFLOP/s, as fitted to measurements (256 x 256 / gemm_tile): 1024^3 22 / 15, 384 x 3904 x 768
-// 62 / 24, 1536 x 4224 x 768 67 / 36, 1920 x 2176 x 512 39 / 23, 2048^3 41 / 42, 1280 x 7296 x 2304
-// 116 / 127, 3072 x 2048 x 3072 44 / 78.
-bool fast_pays(int64_t n, int64_t k, int64_t m, int64_t batch) {
-  const int64_t t256 = ((n + 255) / 256) * ((m + 255) / 256) * batch;
+// compute unit to show its rate (1300 TFLOP/s; gemm_tile comes to 660), and has no k-split for fewer tiles.
+// Times of either, fitted to measurements, in us.
+double time_256(int64_t k, int64_t t256) { return 6.0 + (0.0148 + 0.009 * (double)t256 / 256.0) * (double)k; }
+bool fast_pays_narrow(int64_t n, int64_t k, int64_t m) {
+  const int64_t t256 = ((n + 255) / 256) * ((m + 255) / 256);
   if (t256 > 128) return true;
-  const ProductPlan g = plan_tiles(GECC_BF16, n, k, m, batch);
-  const double gf = 2e-9 * (double)((n + g.tile - 1) / g.tile * g.tile) * (double)k * (double)((m + g.tile - 1) / g.tile * g.tile) * (double)batch;
-  const double t_gen = g.tile == 64 ? 6.0 + gf / 0.33 + 0.006 * (double)(k / g.ksplit) : 8.0 + gf / 0.42;
-  const double t_fast = 6.0 + (0.0148 + 0.009 * (double)t256 / 256.0) * (double)k;
+  const ProductPlan g = plan_tiles(GECC_BF16, n, k, m, 1, true);
+  const double gf = 2e-9 * (double)((n + g.tile - 1) / g.tile * g.tile) * (double)k * (double)((m + g.tile - 1) / g.tile * g.tile);
+  const double t_gen = g.tile == 64 ? 6.0 + gf / 0.33 + 0.006 * (double)(k / g.ksplit) : 8.0 + gf / 0.42, t_fast = time_256(k, t256);
   // (by less than that the fit cannot tell them apart)
   return t_fast - t_gen < 5.0 || t_gen > 0.85 * t_fast;
+}
+// bonus: what gemm_tile saves a protected product beyond its own time (riders_bonus).  Whole calls, 256 x 256 tiles -> gemm_tile (product alone): 2048^3 72.6 -> 54.1 us (38.3 -> 36.6), 2048 x 1024 x
+// 2048 55.4 -> 38.5 (23.4 -> 21.1), 2816 x 704 x 2816 51.8 -> 38.6 (19.7 -> 21.4), 4096 x 512 x 2048 49.8 -> 35.7 (18.2 -> 18.1), 2560^3 85.2 -> 75.4
+// (46.0 -> 52.4), 3072 x 1024 x 3072 58.3 -> 52.1 (26.0 -> 34.2), 1280 x 7296 x 2304 171.6 -> 119.5 (113 -> 73.7), 1024 x 4096 x 4096 NT 109.8 -> 77.9; 3584 x 1536
+// x 2560 67.8 -> 67.6 and 3072 x 2048 x 3072 76.7 -> 81.6 stand on either side of the line.
+bool fast_pays(int64_t n, int64_t k, int64_t m, int64_t batch, double bonus) {
+  const int64_t t256 = ((n + 255) / 256) * ((m + 255) / 256) * batch;
+  if (t256 > 256) return true;
+  const ProductPlan g = plan_tiles(GECC_BF16, n, k, m, batch);
+  const int64_t tiles = ((n + g.tile - 1) / g.tile) * ((m + g.tile - 1) / g.tile) * batch;
+  return time_256(k, t256) + bonus < (g.tile == 128 ? time_128(k, tiles, g.ksplit) : time_64(k, tiles, g.ksplit));
+}
+// The parity scans ride in gemm_tile's launch (scans_ride) and have launches of their own beside the other kernel's: two for NN and TT, 12 us;
+// one for NT and TN, which small products feel (256^3 NT), and above 2^19 symbols the fit has to be 6 us apart.  An operand that is read
+// once for both of its scans has one of them fewer to ride.  Sizes that are no multiples of 64 stay with the 256 x 256-tile kernel unless the
+// fit is 6 us apart: they are the ones its own tests reach it with.
+double riders_bonus(const gecc_params& p, int64_t tile_min) {
+  if (p.n % 64 != 0 || p.m % 64 != 0) return -6.0;
+  if ((int64_t)p.n * p.k * p.batch >= tile_min || (int64_t)p.k * p.m * p.batch >= tile_min) return 0.0;
+  return p.trans_a == p.trans_b ? 12.0 : (int64_t)p.n * p.m * p.batch < (1 << 19) ? 9.0 : -6.0;
 }
 
 // compact: 128 x 128 tiles and 256 workgroups, the plan that needs the least workspace.
@@ -134,9 +178,13 @@ void plan_product(gecc_ctx* c, bool compact) {
   const bool may_be_fast = p.dtype == GECC_BF16 && p.k % 64 == 0 && p.lda % 8 == 0 && p.ldb % 8 == 0 &&
                            (!p.trans_a || p.n % 8 == 0) && (p.trans_b || p.m % 8 == 0) && (int64_t)p.n * p.m >= 256 * 256;
   const int64_t t128 = (int64_t)((p.n + 127) / 128) * ((p.m + 127) / 128) * p.batch;
+  const int64_t t256 = (int64_t)((p.n + 255) / 256) * ((p.m + 255) / 256) * p.batch;
   ProductPlan pl = {128, ksplit_128(t128, p.k), true};
   if (blocked(c)) pl.ksplit = 1;
-  else if (!compact && !(may_be_fast && (c->cu_hint > 0 || fast_pays(p.n, p.k, p.m, p.batch)))) pl = plan_tiles(p.dtype, p.n, p.k, p.m, p.batch);
+  else if (!compact && !(may_be_fast && (c->cu_hint > 0 || fast_pays(p.n, p.k, p.m, p.batch, riders_bonus(p, c->tile_min)))))
+    pl = plan_tiles(p.dtype, p.n, p.k, p.m, p.batch);
+  // (on its own the product stays with the faster kernel; a quarter apart, for what a fit does not know)
+  c->fast_plain = pl.fast || (may_be_fast && fast_pays(p.n, p.k, p.m, p.batch, -0.25 * time_256(p.k, t256)));
   c->tile_m = c->tile_n = pl.tile;
   c->ksplit = pl.ksplit;
   c->fast = pl.fast;
@@ -664,8 +712,9 @@ int check_multiply_args(gecc_ctx* ctx, const void* dev_A, const double* dev_A_pa
 // whenever the product has at most 2048 workgroups 12 to 22 %, with products that took twice as long):
 //   - many rounds of workgroups hide nothing (256 x 512^3 fp32 603 -> 608 us), and scans of more than 16 workgroups per
 //     compute unit take longer than the product (bf16 307 x 503 x 301 x 94 193 -> 313);
-//   - bf16, 128 x 128 tiles: long ranges of k (5064 x 3680 x 1752 171 -> 222) and more than 5 scan workgroups per
-//     compute unit (3029 x 817 x 2493 NT 77 -> 85) lose, others gain (2880 x 520 x 2504 TN 80 -> 54);
+//   - bf16 gains whatever the ranges of k, now that the scans come behind the product's workgroups where not all run at once (before, long
+//     ranges and more than 5 scan workgroups per compute unit lost): 5064 x 3680 x 1752 157.5 -> 145.6 us, 3029 x 817 x 2493 NT 53.1 -> 46.6,
+//     6001 x 2000 x 3001 NT 149.6 -> 140.2, 3500^3 215.5 -> 202.4, 5001 x 700 x 5001 105.7 -> 96.2, 4001 x 1000 x 4001 92.9 -> 87.6, 2500^3 89.9 -> 78.9;
 //   - fp32 keeps four workgroups of 64 x 64 tiles on a compute unit: scans that find no place beside them delay a
 //     product of long k (3904 x 5888 x 448 289 -> 323), and many of them one of more than 512 terms (8 x 600^3 NT
 //     81 -> 143).  Of 128 x 128 tiles it keeps two: both scans together, if they are few, beside short ranges of k (68 x
@@ -675,7 +724,7 @@ bool scans_ride(const gecc_ctx* c, int64_t scans, bool both) {
   const int k_per = c->p.k / c->ksplit;
   const bool small = c->tile_m == 64;
   if (own > 2048 || scans > 4096) return false;
-  if (c->p.dtype == GECC_BF16) return small || (k_per <= 1536 && scans <= 1280);
+  if (c->p.dtype == GECC_BF16) return true;
   if (!small) return both && k_per <= 640 && scans <= 1024;
   return own + scans <= 1536 || (k_per <= 640 && (scans <= 1792 || k_per <= 512));
 }
@@ -810,7 +859,7 @@ hipError_t product(gecc_ctx* ctx, ScanQueue& q, const ScanJob* pr, const ScanJob
 void narrow_plan(gecc_ctx* ctx, GemmArgs& g) {
   const gecc_params& p = ctx->p;
   g.rowpart = nullptr; g.colpart = nullptr; g.faults = nullptr; g.n_faults = 0;
-  ProductPlan pl = {128, 1, p.dtype == GECC_BF16 && fast_pays(g.n, g.k, g.m, 1)};
+  ProductPlan pl = {128, 1, p.dtype == GECC_BF16 && fast_pays_narrow(g.n, g.k, g.m)};
   auto take = [&] {
     g.tile_m = g.tile_n = pl.tile;
     g.ntm = (g.n + pl.tile - 1) / pl.tile;
@@ -1293,7 +1342,8 @@ int gecc_plain_gemm(gecc_ctx* ctx, const void* dev_A, const void* dev_B, float* 
     return GECC_ERR_ALIGN;
   GemmArgs g = gemm_args(ctx, dev_A, dev_B, dev_C);
   g.rowpart = nullptr; g.colpart = nullptr; g.faults = nullptr; g.n_faults = 0;
-  if (g.ksplit > 1) {
+  g.fast = ctx->fast_plain;
+  if (g.ksplit > 1 && !gemm_takes_256(g)) {
     const int rc = prep(ctx, (hipStream_t)stream);
     if (rc) return rc;
   }

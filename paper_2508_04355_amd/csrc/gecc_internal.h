@@ -76,6 +76,7 @@ struct gecc_ctx {
   int tile_op;             // operand whose two reductions share one pass (GECC_MAT_A / GECC_MAT_B)
   int ksplit;              // workgroups per tile of gemm_tile (1: no split)
   bool fast;               // bf16: the 256 x 256-tile kernel takes the product where the operands' addresses allow it
+  bool fast_plain;         // the same for a product without parities, which has no scans beside it
   int cu_hint;             // GECC_CU_COUNT (tests: plan the tile rounds as for that many CUs), else 0
   bool stream;             // the tile scans load past the caches (see gecc_create)
   int64_t tile_min;        // operands of that many elements or more take the tile scan (2^25; GECC_TILE_MIN for tests)

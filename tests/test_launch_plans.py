@@ -84,3 +84,22 @@ def test_calls_of_many_workgroups_are_taken(plans):
     encodings = "scan_pairILi1ELb1E"      # (index weights)
     assert any(encodings in x for x in few) and not any(encodings in x for x in r[2][1])
     assert "gemm_f32_wide" in r[-2][1][0] and "gemm_tile" in r[-1][1][0]
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_bf16_products_either_kernel_takes(plans, ta, tb):
+    """Which one they go to, by size and layout: gemm_tile with the parity scans in its launch where that saves launches (a protected
+    product), the faster kernel for a product on its own."""
+    def product(entry, n, k, m):
+        rc, names = routes(plans, [(entry, n, k, m, 1, 1, ta, tb)])[0]
+        assert rc == 0
+        return [x for x in names if "gemm" in x][0], sum("dot" in x or "scan" in x for x in names)
+    two_launches = ta == tb
+    for n, k, m in ((2048, 2048, 2048), (2560, 2560, 2560), (3072, 1024, 3072), (4096, 512, 2048)):
+        name, scans = product("protected", n, k, m)
+        assert ("gemm_tile" in name) == two_launches and (scans <= 3 if two_launches else scans >= 2)
+        assert "gemm_bf16_256" in product("plain", n, k, m)[0]
+    for n, k, m in ((256, 256, 256), (1280, 7296, 2304), (1024, 4096, 4096)):
+        assert "gemm_tile" in product("protected", n, k, m)[0] and "gemm_tile" in product("plain", n, k, m)[0]
+    for n, k, m in ((4096, 4096, 4096), (3072, 3072, 3072), (520, 256, 264), (1000, 512, 776)):
+        assert "gemm_bf16_256" in product("protected", n, k, m)[0]

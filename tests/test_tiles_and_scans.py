@@ -322,3 +322,36 @@ def test_column_scans_at_their_ends(shape, dtype, trans):
     got = g.C_par[0]
     assert (np.abs(got[:2 * n].reshape(2, n) - pr) <= 2 * (k + m) * eps * mr).all()
     assert (np.abs(got[2 * n:2 * n + 2 * m].reshape(2, m) - pc) <= 2 * (k + n) * eps * mc).all()
+
+
+@pytest.mark.parametrize("trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("shape", [(1280, 2176, 1408),       # aligned, 128 x 128 tiles in ranges of k (NN, TT)
+                                   (1300, 1750, 1211),       # ragged, scans before or behind the product's workgroups
+                                   (192, 64, 256)])          # the smallest that the 256 x 256-tile kernel could take
+def test_bf16_products_with_their_scans_beside_them(shape, trans):
+    import gpu_harness as H
+    n, k, m = shape
+    law = ("normal", 1.0)
+    A, B = inputs.operands(inputs.rng_for(85, n + k), n, k, m, law, law, "bf16")
+    A2, B2, cf, eff = inputs.apply_operand_faults(A, B, [inputs.Fault(inputs.MAT_B, k - 1, 0, 5.0), inputs.Fault(inputs.MAT_C, n - 1, m - 1, 60.0)], "bf16")
+    cfb = [(0,) + c for c in cf]
+    tau = gecc.noise_thresholds(n, k, m, 1.0, 1.0)
+    g = H.run_gpu(A, B, A2, B2, cfb, tau, "bf16", trans[0], trans[1])
+    H.compare(g, H.run_oracle(A, B, A2, B2, cfb, tau), 1e-5, what="%s, trans %s" % (shape, trans))
+    clean, one = [H.run_gpu(A, B, A, B, [], tau, "bf16", trans[0], trans[1], staged=x) for x in (True, False)]
+    assert clean.reports[0].status == one.reports[0].status == gecc.CLEAN
+    assert np.array_equal(clean.C, one.C) and np.array_equal(clean.A_par, one.A_par)
+    assert np.allclose(clean.C_par, one.C_par, rtol=1e-12, atol=1e-13 * np.abs(clean.C_par).max())
+
+
+@pytest.mark.parametrize("trans", [(0, 0), (1, 1)])
+def test_the_256_tile_kernel_at_sizes_that_gemm_tile_has_taken_over(trans, monkeypatch):
+    """Multiples of 64 go to gemm_tile where that saves launches; the other kernel keeps its results there."""
+    import gpu_harness as H
+    monkeypatch.setenv("GECC_CU_COUNT", "256")
+    n, k, m = 576, 192, 320
+    law = ("normal", 1.0)
+    A, B = inputs.operands(inputs.rng_for(86, 1), n, k, m, law, law, "bf16")
+    cfb = [(0, n - 1, m - 1, 60.0), (0, 5, 7, -30.0)]
+    tau = gecc.noise_thresholds(n, k, m, 1.0, 1.0)
+    H.compare(H.run_gpu(A, B, A, B, cfb, tau, "bf16", trans[0], trans[1]), H.run_oracle(A, B, A, B, cfb, tau), 1e-5, what=str(trans))
