@@ -156,7 +156,8 @@ typedef struct {
    bf16 product plans its rounds of tiles as for that many compute units instead of the
    device's own count (for tests of the k-split of a half-empty last round on small shapes;
    any value gives correct results).  Likewise GECC_TILE_MIN: operands of that many elements or
-   more are encoded by the one-pass scan (default 2^25; tests set 1 to reach it with small shapes). */
+   more are encoded by the one-pass scan (default 2^24 in fp32 and 2^25 in bf16, 64 MiB; tests
+   set 1 to reach it with small shapes). */
 int gecc_create(gecc_ctx** out, const gecc_params* p);
 void gecc_destroy(gecc_ctx* ctx);
 

@@ -392,10 +392,15 @@ TileScanJob tile_job(gecc_ctx* c, int op, const void* X, double* enc_out, const 
 // Whether the tile scan serves this operand: its rows have to allow it, and the operand has to be
 // large enough for one pass to beat two (small operands are bound by the number of dependent
 // launches, and the two separate scans need one launch less: a row scan carries the second stage
-// of a column scan).  A function of shape and alignment alone, so that an encoding and the audit
-// that re-forms it always take the same kernel.
+// of a column scan).  From 64 MiB on the one pass wins: fp32 products of 2^24 elements an operand
+// 512^3 x 64 NN 160.2 -> 150.5 us, NT 151.9 -> 148.5, 500^3 x 128 314.8 -> 294.8, 640 x 256 x 640
+// x 128 272.7 -> 262, while 256 x 512 x 384 x 200 stays; bf16 of as many elements +-1.5 %.  Rows
+// below 256 elements leave part of a tile row's 64 x 16 bytes idle and wait for 2^25 elements.  A
+// function of shape and alignment alone, so that an encoding and the audit that re-forms it always
+// take the same kernel.
 bool use_tile(const gecc_ctx* c, const TileScanJob& t) {
-  return tile_scan_ok(t) && (int64_t)t.R * t.Cc * t.batch >= c->tile_min;
+  const int64_t n = (int64_t)t.R * t.Cc * t.batch;
+  return tile_scan_ok(t) && n >= c->tile_min && (t.Cc >= 256 || n >= std::min<int64_t>(2 * c->tile_min, (int64_t)1 << 25));
 }
 
 // Scans in stream order.  The second stage of a coldot is held back: the next rowdot carries it in
@@ -533,7 +538,7 @@ int gecc_create(gecc_ctx** out, const gecc_params* p) {
     c->cu_hint = e ? atoi(e) : 0;
     if (c->cu_hint < 0) c->cu_hint = 0;
     const char* t = getenv("GECC_TILE_MIN");       // test hook: operands of that many elements or more take the one-pass scan
-    c->tile_min = (t && atoll(t) > 0) ? atoll(t) : ((int64_t)1 << 25);
+    c->tile_min = (t && atoll(t) > 0) ? atoll(t) : ((int64_t)64 << 20) / (int64_t)elem_size(p->dtype);    // 64 MiB
   }
   // Operands that fit the 256 MiB memory-side cache, or nearly so, are still there for the product when a scan has
   // read them; loads past the caches pay only beyond (clean passes, ordinary loads -> such loads: both operands

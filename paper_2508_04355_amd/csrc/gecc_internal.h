@@ -79,7 +79,7 @@ struct gecc_ctx {
   bool fast_plain;         // the same for a product without parities, which has no scans beside it
   int cu_hint;             // GECC_CU_COUNT (tests: plan the tile rounds as for that many CUs), else 0
   bool stream;             // the tile scans load past the caches (see gecc_create)
-  int64_t tile_min;        // operands of that many elements or more take the tile scan (2^25; GECC_TILE_MIN for tests)
+  int64_t tile_min;        // operands of that many elements or more take the tile scan (64 MiB; GECC_TILE_MIN for tests)
   char* ws;                // device workspace (caller's)
   size_t ws_bytes;
   char* ws_zeroed;         // the workspace whose "done" counters this context knows to be zero between launches

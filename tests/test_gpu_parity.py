@@ -111,7 +111,7 @@ def test_k_split_of_products_with_few_tiles(pattern, dtype, shape, batch, trans)
 def test_one_pass_scan_on_small_and_ragged_shapes(pattern, dtype, shape, trans, monkeypatch):
     """The scan that reads an operand once for both of its reductions (rows straight into LDS, a last
     column segment narrower than the others, chunks of rows that end in the middle of a block) serves
-    operands of 2^25 elements or more; GECC_TILE_MIN = 1 lets it serve these small ones, staged calls
+    operands of 64 MiB or more; GECC_TILE_MIN = 1 lets it serve these small ones, staged calls
     and the one-call chain alike, and the audit re-forms the same sums bit for bit."""
     monkeypatch.setenv("GECC_TILE_MIN", "1")
     try:

@@ -70,6 +70,16 @@ def test_two_parity_blocks_go_in_the_kernel_of_their_kind(plans, dtype):
         assert sum("scan_pairILi%dELb0ELi%dE" % (dtype, kind) in x for x in names) == 1, names
 
 
+@pytest.mark.parametrize("dtype,shape,batch,one_pass",
+                         [(0, (512, 512, 512), 64, True), (0, (512, 512, 512), 63, False), (0, (512, 252, 512), 260, False),
+                          (0, (512, 252, 512), 261, True), (1, (512, 512, 512), 127, False), (1, (512, 512, 512), 128, True)])
+def test_operands_that_the_one_pass_scan_takes(plans, dtype, shape, batch, one_pass):
+    """64 MiB, and 2^25 elements where the rows are shorter than 256."""
+    n, k, m = shape
+    (_, names), = routes(plans, [("protected", n, k, m, batch, dtype, 0, 1)])
+    assert any("tile_scan" in x for x in names) == one_pass, names
+
+
 def test_calls_of_many_workgroups_are_taken(plans):
     """Launches of which each fits what one may have (2^32 threads) are not put into one that does not: scans of many batch
     items, fp32 tiles of twice the threads."""
