@@ -224,12 +224,12 @@ struct TileScanArgs {
 struct ScanPairItem { int kind; ScanArgs s; TileScanJob t; };
 struct PairJob {
   int kind;          // PJ_x
-  ScanArgs s;        // PJ_ROW, PJ_COL
+  ScanArgs s;        // PJ_ROW, PJ_COL and their like
   TileScanArgs t;    // PJ_TILE_COL, PJ_TILE_ROW
   int nblk;          // workgroups of this job
   int gx, gy;        // workgroups per batch item: gx (rowdot) or gx x gy (segments x chunks)
 };
-enum : int { PJ_ROW = 0, PJ_COL = 1, PJ_TILE_COL = 2, PJ_TILE_ROW = 3, PJ_ROW_BIG = 4, PJ_ROW_WAVE = 5 };
+enum : int { PJ_ROW = 0, PJ_COL = 1, PJ_TILE_COL = 2, PJ_TILE_ROW = 3, PJ_ROW_BIG = 4, PJ_ROW_WAVE = 5, PJ_COL_HALF = 6 };
 struct PairArgs { PairJob j[2]; };
 // done: SCAN_DONE_WORDS zeroed counters, of which `words` are used.  false: some column reduction cannot finish
 // by itself, or there are too few counters

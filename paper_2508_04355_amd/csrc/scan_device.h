@@ -847,6 +847,7 @@ __device__ __forceinline__ void pair_body(const PairJob& j, int x, int y, int b,
   else if (j.kind == PJ_ROW_BIG) rowdot_body<DT, true, RD_BIG_RB, RD_BIG_U>(j.s, x, b, lds);
   else if (j.kind == PJ_ROW_WAVE) rowdot_wave_body<DT, true>(j.s, x, b, lds);
   else if (j.kind == PJ_COL) coldot_body<Elem<DT>, true, CD_ROWS, CD_CHUNKS>(j.s, Parts{}, j.gy, j.gx, x, y, b, lds);
+  else if (j.kind == PJ_COL_HALF) coldot_body<ElemHalf<DT>, true, CD_ROWS, CD_CHUNKS>(j.s, Parts{}, j.gy, j.gx, x, y, b, lds);
   else if (j.kind == PJ_TILE_COL) tile_scan_body<DT, true, false, true, true>(j.t, x, y, b, lds);
   else tile_scan_body<DT, false, true, true, true>(j.t, x, y, b, lds);
 }

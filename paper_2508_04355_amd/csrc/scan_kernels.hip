@@ -421,6 +421,11 @@ hipError_t launch_scan_pair(const ScanArgs* s, const bool* rowdot, Parts* left, 
 
 // ---- the two audits as jobs of the decoder's launch -----------------------------------------------
 constexpr int AUDIT_PAIR_MAX_BLOCKS = 5120;
+// A column audit of fewer workgroups than compute units goes in vectors of 8 bytes, twice the workgroups: the decoder's launch with an
+// operand error, us: bf16 1500 x 1000 of A 21.8 -> 17.2, 2048^2 22.0 -> 18.1, 4096 x 2048 26.1 -> 22.5, 4 x 1024^2 21.5 -> 17.8, fp32
+// 1024^2 16.6 -> 15.0, 3000 x 1000 19.2 -> 17.5; (16 x 256^2 as before, 8 x 500 x 700 18.4 -> 19.0).  From 256 on what the audit saves
+// is lost where C alone is patched and the others only decide that: bf16 4096^2 31.5 -> 29.1 and 20.7 -> 22.6.
+constexpr int CD_AUDIT_HALF_BELOW = 256;
 // fills j from x; returns the counters it uses, or -1 when x cannot finish by itself
 static int make_pair_job(const ScanPairItem& x, uint32_t* done, PairJob& j) {
   j = PairJob{};
@@ -452,16 +457,16 @@ static int make_pair_job(const ScanPairItem& x, uint32_t* done, PairJob& j) {
     j.nblk = j.gx * j.s.batch;
     return 0;
   }
-  const int words = coldot_done_words(j.s);
-  if (words == 0) return -1;
-  const int vec = j.s.dtype == GECC_BF16 ? 8 : 4;
-  j.kind = PJ_COL;
+  if (coldot_done_words(j.s) == 0) return -1;
+  const bool half = coldot_blocks(j.s) < CD_AUDIT_HALF_BELOW;
+  const int vec = (j.s.dtype == GECC_BF16 ? 8 : 4) / (half ? 2 : 1);
+  j.kind = half ? PJ_COL_HALF : PJ_COL;
   j.s.done = done;
   j.gx = (j.s.Cc + 64 * vec - 1) / (64 * vec);
   j.gy = (j.s.R + SCAN_CHUNK_ROWS - 1) / SCAN_CHUNK_ROWS;
   if ((int64_t)j.gx * j.gy * j.s.batch > (1 << 29)) return -1;
   j.nblk = j.gx * j.gy * j.s.batch;
-  return words;
+  return j.gx * j.s.batch;
 }
 
 static int pair_dtype(const ScanPairItem& x) { return x.kind == 2 ? x.t.dtype : x.s.dtype; }

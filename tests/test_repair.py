@@ -53,3 +53,27 @@ def test_operand_errors_repaired_by_several_workgroups(pattern, dtype, shape, ba
     if batch < 4:                                       # the order in which the workgroups come does not show
         g2 = H.run_gpu(A, B, A2, B2, cfb, tau, dtype, trans[0], trans[1])
         assert np.array_equal(g.C, g2.C) and np.array_equal(g.A, g2.A) and np.array_equal(g.C_par, g2.C_par)
+
+
+@pytest.mark.parametrize("trans", [(0, 0), (1, 1)])
+@pytest.mark.parametrize("dtype,shape,batch", [("f32", (129, 130, 131), 1), ("f32", (300, 385, 127), 2), ("bf16", (129, 260, 257), 1),
+                                               ("bf16", (260, 7, 64), 3), ("f32", (128, 64, 128), 255), ("f32", (128, 64, 128), 256)])
+def test_audits_by_column_scans_of_either_width(dtype, shape, batch, trans):
+    """The audit's column scans in vectors of 8 bytes (fewer than 256 workgroups of 16-byte ones) and of 16: errors in the first and
+    the last column come back exactly where they are, with an encoding that the 16-byte scans or others have made."""
+    import gpu_harness as H
+    n, k, m = shape
+    rng = inputs.rng_for(99, n + k + m)
+    law = ("normal", 1.0)
+    faults = [inputs.Fault(MAT_A, n - 1, k - 1, 17.0), inputs.Fault(MAT_B, 0, m - 1, -9.5)]
+    hit = batch - 1
+    A, B = [np.stack(x) for x in zip(*[inputs.operands(rng, n, k, m, law, law, dtype) for _ in range(batch)])]
+    A2, B2 = A.copy(), B.copy()
+    A2[hit], B2[hit], cf, eff = inputs.apply_operand_faults(A[hit], B[hit], faults, dtype)
+    tau = gecc.noise_thresholds(n, k, m, 1.0, 1.0)
+    g = H.run_gpu(A, B, A2, B2, [(hit,) + c for c in cf], tau, dtype, trans[0], trans[1])
+    o = H.run_oracle(A[hit], B[hit], A2[hit], B2[hit], [(0,) + c for c in cf], tau)
+    last = H.GpuResult(reports=g.reports[hit:], C=g.C[hit:], A=g.A[hit:], B=g.B[hit:], A_par=g.A_par[hit:], B_par=g.B_par[hit:],
+                       C_par=g.C_par[hit:], synd=g.synd)
+    H.compare(last, o, 1e-5, what="%s %s x %d, trans %s" % (dtype, shape, batch, trans))
+    assert o[0].status == gecc.CORRECTED and [(e[0], e[1], e[2]) for e in last.reports[0].errors()] == [(e[0], e[1], e[2]) for e in eff]
