@@ -1008,8 +1008,8 @@ __global__ __launch_bounds__(RP_THREADS) void repair_kernel(DecodeArgs a, Repair
 }
 
 // Section V step 2 and, where it fails, the two re-encodings of the operand audit in one launch: a launch that
-// waits for the one before it costs 4.5 us whatever it does, and after a clean product this one only has the
-// report to write.  Workgroup v of the audits decides from the counters and syndromes of the threshold pass,
+// waits for the one before it costs 2 to 5 us of the stream and 3 of the host whatever it does, and after a clean product this
+// one only has the report to write.  Workgroup v of the audits decides from the counters and syndromes of the threshold pass,
 // on its own and like all others, what Section V step 2 makes of its item: nothing or patches of C, or the
 // audit (done by all of them; the repair follows as a launch of its own, with more threads).  Nobody writes
 // what the others decide by.

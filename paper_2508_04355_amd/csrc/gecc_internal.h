@@ -102,7 +102,7 @@ namespace gecc {
 // byte stride gate_stride; the kernels return at once for items whose gate != gate_value.
 // Second stage of a column scan (chunks of rows) and / or of the row part of a tile scan (segments of
 // columns) that has not been launched yet: either launch_stage2() runs it as a kernel of its own,
-// or the next rowdot launch carries it (a dependent launch costs about 5 us of stream time
+// or the next rowdot launch carries it (a dependent launch costs 2 to 5 us of stream time
 // whatever it does, and this stage is tiny).
 struct Stage2Job {
   bool valid;

@@ -634,9 +634,9 @@ __device__ __forceinline__ void coldot_body(const ScanArgs& a, const Parts& wp, 
 //
 // A workgroup is four wavefronts on one segment of 64*VEC columns; each walks its own quarter of
 // the chunk's rows, TS_RB rows (loads) at a time; three wavefronts share a SIMD and cover each
-// other's waits.  The kernel is bound by its arithmetic as much as by memory: per 16 bytes a lane
-// spends 8 conversions and 32 fp64 operations, which issue at half rate, about 380 cycles per row
-// and wavefront (measured: its loads alone stream at 5.8 TB/s, the whole kernel at 4.2, and at 4.4 with
+// other's waits.  Per 16 bytes a lane spends 8 conversions and 32 fp64 operations of 4.4 cycles each, about
+// 220 cycles per row and wavefront, 9.8 TB/s if nothing else were to do; its loads alone stream at 5.8 TB/s, the
+// whole kernel at 4.2, and with eight rows on their way at all times (registers reloaded as they fall free) no faster.  (4.4 with
 // loads that are not kept in the caches: 470 MB 107 us instead of 114, the row part alone over 117 MB of 28 KiB rows
 // 22.5 instead of 27.7, for the whole step a gain only where the operands are beyond the caches anyway (stream, see
 // gecc_create); more loads in flight, 8-byte lanes, rows DMA'd into an LDS ring or workgroups that read 4 KiB of

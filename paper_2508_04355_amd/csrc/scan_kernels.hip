@@ -68,7 +68,7 @@ __global__ __launch_bounds__(256) void coldot_stage2_pair(Stage2Job j0, Stage2Jo
 }
 
 // Two scans that do not read each other's results (both encodings, or both parity blocks): what each of them would
-// leave idle at its end the other one fills, and a launch that waits for the one before it costs 5 us whatever it does.
+// leave idle at its end the other one fills, and a launch that waits for the one before it costs 2 to 5 us whatever it does.
 // Two parity blocks are scans of one kind, and each kind has a kernel of its own (in one for both, registers of the bf16 column scan
 // spilled).  Row scans keep three wavefronts per SIMD (with two, 3072 x 2048 x 6144 NT 150.0 -> 152.5 us a call); column scans have the weights
 // of four rows in registers, which is worth more than the third wavefront (spilled for it, 4096^3 TN 25.6 us for 16.4).
