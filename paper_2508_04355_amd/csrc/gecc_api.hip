@@ -87,8 +87,41 @@ int ksplit_bf16_128(int64_t t128, int k) {
   return best;
 }
 
-// Times of bf16 products in gemm_tile, product alone, as fitted to measurements (aligned rows, NN; us): what a workgroup needs per
-// term of k with as many beside it on its compute unit, and the exchange between s ranges (C goes out and in s times).
+// 128 x 128 tiles: products with tiles enough for every compute unit, as long as tiles that hang over the
+// edge do not eat up what the larger tile gains (a saturated chip does a 128 x 128 tile in the time of three
+// 64 x 64 ones: fp32, 256 x 512^3, 428 against 568; 64 x 300^3, 61 against 46), and bf16 products of long k
+// (1536 x 4224 x 768: 36 against 39, 16384 x 4096 x 88: 41 against 52).  64 x 64 tiles: the rest (fp32
+// 1024^3 28 against 37, 128^3 7.7 against 13.8; bf16 1500 x 1000 x 1100 19.5 against 28).
+//
+// Workgroups of fp32 tiles of 64: four per compute unit keep it busy (1024^3: one workgroup per tile 40, two 31, four 28, eight
+// 38); up to one tile per compute unit three are enough, and leave the fourth place to the scans that ride along (whole calls at
+// 1024, 800 and 512 workgroups: 1024^3 48.4, 44.9 and 47.1; with more tiles 800 are too few, 1300^3, 441 tiles, 74.0 and 80.9).
+// fp32 tiles of 128: two ranges below 512 tiles (2000 x 1000 x 2000: 83, split in two 67).
+//
+// What the ranges of a tile exchange takes 3 to 4 us, so they have to be worth it.  fp32: 128 terms, of few tiles, whose compute
+// units have nothing else to do, fewer (whole calls, ranges of 128 -> 64: 128^3 20.9 -> 20.2, 256^3 23.1 -> 21.7).  bf16 tiles of
+// 64: two workgroups per compute unit and 450 terms; of few tiles two and a half and 128 terms (whole calls, ranges of 450 -> of 128:
+// 4 tiles, 128 x 896 x 128, 23.5 -> 20.2; 16 tiles, 211 x 447 x 232, 23.5 -> 21.2; 36 tiles 26.4 -> 25.2; 72 tiles, 1152 x 704 x 256,
+// 23.0 -> 24.9; 104 tiles, 256 x 512 x 1664, 21.8 -> 26.3).
+//
+// bf16 tiles of 128 have one chain of sums over their range and no registers for another, so they are not taken where tiles of 64
+// would be but for the time (3440 x 240 x 2496: 34.5 us a call and 8.3e-8 from the fp64 product, tiles of 64 49.0 and 5.6e-8).  Nor are eight
+// ranges of them, the most a tile is cut into: tiles of 64 in two or three are both faster and closer (960 x 4352 x 960 NT 54.7 us and
+// 1.43e-7 -> 43.9 and 1.04e-7, 3328 x 4544 x 192 58.5 and 1.44e-7 -> 49.3 and 1.02e-7).
+//
+// narrow: a side product of blocked mode, a few columns (rows) beside a whole operand; its bf16 ranges are as they were measured, two and
+// a half workgroups and 128 terms.
+int ranges_64(int64_t t64, int k, bool few) { return few ? ksplit_of(t64, 512 + (int)(t64 < 512 ? t64 / 2 : 0), k) : ksplit_of(t64, 512, k, 450); }
+ProductPlan plan_tiles(int dtype, int64_t n, int64_t k, int64_t m, int64_t batch, bool narrow = false) {
+  const int64_t t128 = ((n + 127) / 128) * ((m + 127) / 128) * batch, t64 = ((n + 63) / 64) * ((m + 63) / 64) * batch;
+  const int s_long = dtype == GECC_BF16 ? ksplit_bf16_128(t128, (int)k) : 0;
+  if (s_long > 0 && (s_long < 8 || narrow)) return {128, s_long, false};
+  if (s_long == 0 && t128 >= 256 && k >= 256 && 3 * t128 < t64) return {128, dtype == GECC_F32 && t128 < 512 ? 2 : 1, false};
+  return {64, dtype == GECC_F32 ? ksplit_of(t64, t64 > 256 ? 1024 : 800, (int)k, t64 <= 64 ? 64 : t64 <= 128 ? 96 : 128) : ranges_64(t64, (int)k, narrow || t64 <= 48), false};
+}
+
+// bf16 products that the 256 x 256-tile kernel can take.  Times of either kernel, product alone, as fitted to measurements (aligned rows, NN; us): what
+// a workgroup needs per term of k with as many beside it on its compute unit, and the exchange between s ranges (C goes out and in s times).
 double exchange(int64_t symbols, int s) { return s > 1 ? 1.8e-6 * (double)symbols * s : 0.0; }
 double time_128(int64_t k, int64_t t128, int s) {
   const int64_t per_cu = (t128 * s + 255) / 256;
@@ -99,66 +132,41 @@ double time_64(int64_t k, int64_t t64, int s) {
   const int64_t per_cu = (t64 * s + 255) / 256;
   return 4.0 + (double)k / s * (per_cu == 1 ? 0.0087 : per_cu == 2 ? 0.0105 : per_cu == 3 ? 0.0135 : 0.0043 * (double)per_cu) + exchange(t64 * 4096, s);
 }
-
-// 128 x 128 tiles: products with tiles enough for every compute unit, as long as tiles that hang over the
-// edge do not eat up what the larger tile gains (a saturated chip does a 128 x 128 tile in the time of three
-// 64 x 64 ones: fp32, 256 x 512^3, 428 against 568; 64 x 300^3, 61 against 46), and bf16 products of long k
-// (1536 x 4224 x 768: 36 against 39, 16384 x 4096 x 88: 41 against 52).  64 x 64 tiles: the rest (fp32
-// 1024^3 28 against 37, 128^3 7.7 against 13.8; bf16 1500 x 1000 x 1100 19.5 against 28).
-// Workgroups: fp32 tiles of 64 keep four per compute unit busy (1024^3: one workgroup per tile 40, two 31,
-// four 28, eight 38); up to one tile per compute unit three are enough, and leave the fourth place to the scans that
-// ride along (whole calls at 1024, 800 and 512 workgroups: 1024^3 48.4, 44.9 and 47.1, 900 x 1500 x 900 55.1, 53.1 and
-// 57.8, 1000 x 1031 x 777 TT 48.0, 46.4 and 50.6; with more tiles 800 are too few, 1300^3, 441 tiles, 74.0 and 80.9), bf16 ones two.
-// What the ranges of a tile exchange takes 3 to 4 us, so they have to be worth it: fp32 128 terms, of few tiles, whose compute units
-// have nothing else to do, fewer (whole calls, ranges of 128 -> 64: 128^3 20.9 -> 20.2, 256^3 23.1 -> 21.7, 100 x 300 x 100 23.8 -> 22.6; 70 and
-// 100 tiles, 128 -> 100: 25.1 -> 24.2, 25.6 -> 25.1), bf16 450 (ranges of 128 -> as many as then remain: 700^3 in 4 -> 1 26.9 -> 25.8, 400 x 700 x 800 in 5 -> 1
-// 26.7 -> 24.3, 600 x 1400 x 600 in 5 -> 3 28.6 -> 27.2, 300 x 2000 x 400 in 8 -> 4 28.4 -> 25.7, 1200 x 1800 x 400 TN in 4 -> 3 31.7 -> 30.1),
-// fp32 tiles of 128 two (2000 x 1000 x 2000: 83, split in two 67).
-// bf16: whichever tile and ranges the fitted times say (whole calls, one range of 128 x 128 tiles -> two: 2048 x 1024 x 2048 38.5 -> 44.3, 2048^3 56.2 ->
-// 54.1, 1792 x 2048 x 2304 NT 57.9 -> 54.4, 2048 x 4096 x 2048 94.3 -> 81.5; tiles of 64 -> of 128: 1920 x 512 x 2176 35.7 -> 32.5, 1024^3 28.7 -> 35.5).
-// narrow: a side product of blocked mode, a few columns (rows) beside a whole operand; its bf16 ranges are as they were measured, two and
-// a half workgroups and 128 terms.
-ProductPlan plan_tiles(int dtype, int64_t n, int64_t k, int64_t m, int64_t batch, bool narrow = false) {
-  const int64_t t128 = ((n + 127) / 128) * ((m + 127) / 128) * batch, t64 = ((n + 63) / 64) * ((m + 63) / 64) * batch;
-  if (dtype == GECC_BF16 && narrow) {
-    const int s_long = ksplit_bf16_128(t128, (int)k);
-    if (s_long > 0) return {128, s_long, false};
-  } else if (dtype == GECC_BF16 && t128 <= 576) {
-    // by the times of either tile, as fitted; an exchange of up to 38 MB (the static scratch has 48)
-    const int s64 = ksplit_of(t64, 512, (int)k, 450);
-    int s128 = 1;
-    for (int s = 2; s <= 8 && t128 * s <= 576 && k / s >= 512; ++s)
-      if (time_128(k, t128, s) < time_128(k, t128, s128)) s128 = s;
-    const bool large = t128 >= 256 && k >= 256 && 3 * t128 < t64;
-    if (large || time_128(k, t128, s128) < time_64(k, t64, s64)) return {128, s128, false};
-    return {64, s64, false};
-  }
-  if (t128 >= 256 && k >= 256 && 3 * t128 < t64) return {128, dtype == GECC_F32 && t128 < 512 ? 2 : 1, false};
-  return {64, dtype == GECC_F32 ? ksplit_of(t64, t64 > 256 ? 1024 : 800, (int)k, t64 <= 64 ? 64 : t64 <= 128 ? 96 : 128) :
-              narrow ? ksplit_of(t64, 512 + (int)(t64 < 512 ? t64 / 2 : 0), (int)k) : ksplit_of(t64, 512, (int)k, 450), false};
-}
-
-// Whether the 256 x 256-tile kernel is the faster one for a bf16 product it can take: it needs a workgroup per
-// compute unit to show its rate (1300 TFLOP/s; gemm_tile comes to 660), and has no k-split for fewer tiles.
-// Times of either, fitted to measurements, in us.
 double time_256(int64_t k, int64_t t256) { return 6.0 + (0.0148 + 0.009 * (double)t256 / 256.0) * (double)k; }
-bool fast_pays_narrow(int64_t n, int64_t k, int64_t m) {
-  const int64_t t256 = ((n + 255) / 256) * ((m + 255) / 256);
+
+// Whether that kernel is worth a thought at all: it needs a workgroup per compute unit to show its rate (1300 TFLOP/s; gemm_tile comes
+// to 660), and has no k-split for fewer tiles.
+bool fast_may_pay(int64_t n, int64_t k, int64_t m, int64_t batch) {
+  const int64_t t256 = ((n + 255) / 256) * ((m + 255) / 256) * batch;
   if (t256 > 128) return true;
-  const ProductPlan g = plan_tiles(GECC_BF16, n, k, m, 1, true);
-  const double gf = 2e-9 * (double)((n + g.tile - 1) / g.tile * g.tile) * (double)k * (double)((m + g.tile - 1) / g.tile * g.tile);
+  const ProductPlan g = plan_tiles(GECC_BF16, n, k, m, batch, true);
+  const double gf = 2e-9 * (double)((n + g.tile - 1) / g.tile * g.tile) * (double)k * (double)((m + g.tile - 1) / g.tile * g.tile) * (double)batch;
   const double t_gen = g.tile == 64 ? 6.0 + gf / 0.33 + 0.006 * (double)(k / g.ksplit) : 8.0 + gf / 0.42, t_fast = time_256(k, t256);
   // (by less than that the fit cannot tell them apart)
   return t_fast - t_gen < 5.0 || t_gen > 0.85 * t_fast;
 }
-// bonus: what gemm_tile saves a protected product beyond its own time (riders_bonus).  Whole calls, 256 x 256 tiles -> gemm_tile (product alone): 2048^3 72.6 -> 54.1 us (38.3 -> 36.6), 2048 x 1024 x
-// 2048 55.4 -> 38.5 (23.4 -> 21.1), 2816 x 704 x 2816 51.8 -> 38.6 (19.7 -> 21.4), 4096 x 512 x 2048 49.8 -> 35.7 (18.2 -> 18.1), 2560^3 85.2 -> 75.4
-// (46.0 -> 52.4), 3072 x 1024 x 3072 58.3 -> 52.1 (26.0 -> 34.2), 1280 x 7296 x 2304 171.6 -> 119.5 (113 -> 73.7), 1024 x 4096 x 4096 NT 109.8 -> 77.9; 3584 x 1536
+// gemm_tile's plan for a product of which that is so: whichever tile and ranges the fitted times say.  (The other kernel has one chain of sums
+// over all of k: none of these is longer.)  Whole calls, one range of 128 x 128 tiles -> two: 2048 x 1024 x 2048 38.5 -> 44.3, 2048 x
+// 4096 x 2048 94.5 -> 81.4; tiles of 64 -> of 128: 1024^3 28.7 -> 35.5.
+ProductPlan plan_beside_256(int64_t n, int64_t k, int64_t m, int64_t batch) {
+  const int64_t t128 = ((n + 127) / 128) * ((m + 127) / 128) * batch, t64 = ((n + 63) / 64) * ((m + 63) / 64) * batch;
+  const int s64 = ranges_64(t64, (int)k, t64 <= 48);
+  const bool large = t128 >= 256 && k >= 256 && 3 * t128 < t64;
+  int s128 = 1;
+  for (int s = 2; s <= 8 && t128 * s <= 576 && k / s >= 512; ++s)       // (an exchange of up to 38 MB: the static scratch has 48)
+    if (time_128(k, t128, s) < time_128(k, t128, s128)) s128 = s;
+  if (large || (t128 <= 576 && time_128(k, t128, s128) < time_64(k, t64, s64))) return {128, s128, false};
+  return {64, s64, false};
+}
+// bonus: what gemm_tile saves a protected product beyond its own time (riders_bonus).  Whole calls, 256 x 256 tiles -> gemm_tile (product alone): 2048^3 72.0 -> 56.5 us (38.3 -> 36.6), 2048 x 1024 x
+// 2048 54.9 -> 39.2 (23.4 -> 21.1), 2816 x 704 x 2816 51.2 -> 38.4 (19.7 -> 21.4), 4096 x 512 x 2048 49.4 -> 35.3 (18.2 -> 18.1), 2560^3 84.3 -> 76.4
+// (46.0 -> 52.4), 3072 x 1024 x 3072 57.1 -> 50.3 (26.0 -> 34.2), 1280 x 7296 x 2304 171.6 -> 109.8 (113 -> 73.7), 1024 x 4096 x 4096 NT 109.0 -> 80.2; 3584 x 1536
 // x 2560 67.8 -> 67.6 and 3072 x 2048 x 3072 76.7 -> 81.6 stand on either side of the line.
 bool fast_pays(int64_t n, int64_t k, int64_t m, int64_t batch, double bonus) {
   const int64_t t256 = ((n + 255) / 256) * ((m + 255) / 256) * batch;
   if (t256 > 256) return true;
-  const ProductPlan g = plan_tiles(GECC_BF16, n, k, m, batch);
+  if (!fast_may_pay(n, k, m, batch)) return false;
+  const ProductPlan g = plan_beside_256(n, k, m, batch);
   const int64_t tiles = ((n + g.tile - 1) / g.tile) * ((m + g.tile - 1) / g.tile) * batch;
   return time_256(k, t256) + bonus < (g.tile == 128 ? time_128(k, tiles, g.ksplit) : time_64(k, tiles, g.ksplit));
 }
@@ -182,7 +190,7 @@ void plan_product(gecc_ctx* c, bool compact) {
   ProductPlan pl = {128, ksplit_128(t128, p.k), true};
   if (blocked(c)) pl.ksplit = 1;
   else if (!compact && !(may_be_fast && (c->cu_hint > 0 || fast_pays(p.n, p.k, p.m, p.batch, riders_bonus(p, c->tile_min)))))
-    pl = plan_tiles(p.dtype, p.n, p.k, p.m, p.batch);
+    pl = may_be_fast && fast_may_pay(p.n, p.k, p.m, p.batch) ? plan_beside_256(p.n, p.k, p.m, p.batch) : plan_tiles(p.dtype, p.n, p.k, p.m, p.batch);
   // (on its own the product stays with the faster kernel; a quarter apart, for what a fit does not know)
   c->fast_plain = pl.fast || (may_be_fast && fast_pays(p.n, p.k, p.m, p.batch, -0.25 * time_256(p.k, t256)));
   c->tile_m = c->tile_n = pl.tile;
@@ -864,7 +872,7 @@ hipError_t product(gecc_ctx* ctx, ScanQueue& q, const ScanJob* pr, const ScanJob
 void narrow_plan(gecc_ctx* ctx, GemmArgs& g) {
   const gecc_params& p = ctx->p;
   g.rowpart = nullptr; g.colpart = nullptr; g.faults = nullptr; g.n_faults = 0;
-  ProductPlan pl = {128, 1, p.dtype == GECC_BF16 && fast_pays_narrow(g.n, g.k, g.m)};
+  ProductPlan pl = {128, 1, p.dtype == GECC_BF16 && fast_may_pay(g.n, g.k, g.m, 1)};
   auto take = [&] {
     g.tile_m = g.tile_n = pl.tile;
     g.ntm = (g.n + pl.tile - 1) / pl.tile;

@@ -261,6 +261,7 @@ struct GemmArgs {
   // leave compute units idle); the last to finish adds their partial tiles up in a fixed order
   int ksplit;           // 0 or 1: off
   int k_per;            // set by the launcher: k range of one workgroup
+  int k_fold;           // set by the launcher, bf16 tiles of 64: terms after which a sum of them is put aside
   float* split_part;    // [tiles x batch][ksplit][tile_m x tile_n]
   size_t split_bytes;   // what there is room for behind split_part: the launcher refuses a plan that needs more
   uint32_t* split_done; // [tiles x batch] counters, zero between launches (shared with the scans)

@@ -33,6 +33,7 @@
 // closer than either on any operands (2.5e-8 for all three; normal ones, k = 32: 2.5e-8 against 3.9e-8 through pieces).
 // Bound there by the fp64 rate or by C's stores: 8192 x k x 8192 through fp64 and through pieces, k = 1 70 against
 // 80 us, k = 8 87 against 89, k = 32 111 against 78.
+#include <cmath>
 #include "gemm_device.h"
 
 namespace gecc {
@@ -554,17 +555,20 @@ __global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : DT == GECC_BF16 ? 3 : 2) 
 #pragma unroll
       for (int v = 0; v < 4; ++v) low[i][j][v] = 0.f;
 
-  // fp32, 64 x 64: the first half of the range in a third set, for shorter chains again (1024^3 in three ranges of k:
-  // 1.10e-7 from the fp64 product with one chain, 8.7e-8 with two; in four ranges with one 9.8e-8).
-  constexpr bool HALVES = PIECES > 1 && TILE == 64;
-  f32x4_t first[HALVES ? NI : 1][HALVES ? NI : 1];
+  // 64 x 64: a third set, for shorter chains again.  fp32: the first half of the range (1024^3 in three ranges of k:
+  // 1.10e-7 from the fp64 product with one chain, 8.7e-8 with two; in four ranges with one 9.8e-8).  bf16: what the other two hold is
+  // added to it every k_fold terms (k_fold_of), so that the error does not follow the number of ranges.
+  constexpr bool HALVES = PIECES > 1 && TILE == 64, FOLD = PIECES == 1 && TILE == 64;
+  constexpr int NT = TILE == 64 ? NI : 1;
+  f32x4_t third[NT][NT];
 #pragma unroll
-  for (int i = 0; i < (HALVES ? NI : 1); ++i)
+  for (int i = 0; i < NT; ++i)
 #pragma unroll
-    for (int j = 0; j < (HALVES ? NI : 1); ++j)
+    for (int j = 0; j < NT; ++j)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) first[i][j][v] = 0.f;
+      for (int v = 0; v < 4; ++v) third[i][j][v] = 0.f;
   const int k_mid = k_begin + ((k_end - k_begin) / (2 * BK)) * BK;
+  int k_next = k_begin + a.k_fold;
 
   Stager<DT, TILE, KCA, D> sa;
   Stager<DT, TILE, KCB, D> sb;
@@ -638,7 +642,18 @@ __global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : DT == GECC_BF16 ? 3 : 2) 
 #pragma unroll
             for (int j = 0; j < NI; ++j)
 #pragma unroll
-              for (int v = 0; v < 4; ++v) { first[i][j][v] = acc[i][j][v]; acc[i][j][v] = 0.f; }
+              for (int v = 0; v < 4; ++v) { third[i][j][v] = acc[i][j][v]; acc[i][j][v] = 0.f; }
+        }
+      }
+      if constexpr (FOLD) {
+        if (k0 == k_next) {
+          k_next += a.k_fold;
+#pragma unroll
+          for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+#pragma unroll
+              for (int v = 0; v < 4; ++v) { third[i][j][v] += acc[i][j][v] + low[i][j][v]; acc[i][j][v] = 0.f; low[i][j][v] = 0.f; }
         }
       }
       multiply(As, Bs);
@@ -651,7 +666,10 @@ __global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : DT == GECC_BF16 ? 3 : 2) 
 #pragma unroll
       for (int j = 0; j < NI; ++j)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) acc[i][j][v] = (HALVES ? acc[i][j][v] + first[HALVES ? i : 0][HALVES ? j : 0][v] : acc[i][j][v]) + low[i][j][v];
+        for (int v = 0; v < 4; ++v) {
+          const float x = TILE == 64 ? third[TILE == 64 ? i : 0][TILE == 64 ? j : 0][v] : 0.f;
+          acc[i][j][v] = HALVES ? (acc[i][j][v] + x) + low[i][j][v] : FOLD ? x + (acc[i][j][v] + low[i][j][v]) : acc[i][j][v] + low[i][j][v];
+        }
   }
   if constexpr (DT == GECC_F32) {
     if (once) {
@@ -838,6 +856,21 @@ __global__ __launch_bounds__(THREADS) void partials_kernel(PartialArgs a) {
 // 34.7 -> 34.1 at 1536 x 1280 x 256).
 template <int DT, int TILE> constexpr int at_once() { return 256 * (TILE == 64 ? 4 : DT == GECC_BF16 ? 3 : 2); }
 
+// bf16 tiles of 64: terms of k after which the accumulators are added to the third set and start anew, for a range of k_per terms.
+// A chain of N additions is off by N^2 / 2 squared last bits (a walk that grows); B pieces with a chain of their sums by
+// N^2 / 2B + NB / 2, least where B is about sqrt(N).  Distance of the product from the fp64 one, in 1e-8 (normal operands):
+//   terms of a piece    64   128   192   256   384   512   no pieces
+//   range of  260      5.9   6.0   6.1   6.8   6.6   6.6    6.6
+//   range of  700      7.6   7.1   7.1   7.3   8.0   8.7   10.5
+//   range of 1000      8.7   7.6   7.7   7.7   8.3   9.3   12.6
+//   range of 2112     11.8   9.9   9.2   9.3   9.6  10.5   19.1
+//   range of 5800     18.0  13.7  12.1  11.3  11.1  11.3   32.9
+// They cost nothing that shows: whole calls of 700^3 24.1 us and of 960 x 5800 x 900 81.2 us with any of them and without.
+int k_fold_of(int k_per) {
+  const int pieces = (int)(5.0 * sqrt((double)k_per) / 64.0 + 0.5);
+  return 64 * (pieces > 1 ? pieces : 1);
+}
+
 template <int DT, int TILE>
 hipError_t launch_tile(const GemmArgs& a0, const GemmSide* side0, hipStream_t st) {
   GemmArgs a = a0;
@@ -849,6 +882,7 @@ hipError_t launch_tile(const GemmArgs& a0, const GemmSide* side0, hipStream_t st
   } else {
     a.ksplit = 1;
   }
+  a.k_fold = k_fold_of(a.ksplit > 1 ? a.k_per : a.k);
   GemmSide side = side0 ? *side0 : GemmSide{};
   side.pg_items = a.pg_out ? a.batch : 0;
   side.blocks = side.pg_items + side.j[0].nblk + side.j[1].nblk;

@@ -355,3 +355,17 @@ def test_the_256_tile_kernel_at_sizes_that_gemm_tile_has_taken_over(trans, monke
     cfb = [(0, n - 1, m - 1, 60.0), (0, 5, 7, -30.0)]
     tau = gecc.noise_thresholds(n, k, m, 1.0, 1.0)
     H.compare(H.run_gpu(A, B, A, B, cfb, tau, "bf16", trans[0], trans[1]), H.run_oracle(A, B, A, B, cfb, tau), 1e-5, what=str(trans))
+
+
+@pytest.mark.parametrize("shape,trans,limit", [((700, 700, 700), (0, 0), 7.5e-8), ((128, 896, 640), (0, 0), 7.7e-8), ((1313, 1220, 2578), (0, 0), 1.48e-7),
+                                               ((3440, 240, 2496), (1, 1), 6.7e-8), ((2509, 3866, 266), (1, 0), 1.49e-7), ((776, 3240, 1496), (0, 1), 1.47e-7)])
+def test_distance_of_bf16_products_from_fp64(shape, trans, limit):
+    """What the order of a product's sums leaves, as |C - C64| / |C64| in 2-norms: with the whole range of k in as few chains as tiles and
+    ranges alone would give, these are 1.05e-7, 1.19e-7, 2.04e-7, 8.3e-8, 1.83e-7 and 1.52e-7.  The limits are 5 % above 7.1e-8, 7.3e-8,
+    1.41e-7, 6.4e-8, 1.42e-7 and 1.40e-7, the distances of plans with more ranges; over 80 000 symbols and more it varies by less than 1 %."""
+    n, k, m = shape
+    A, B = [x[None] for x in inputs.operands(inputs.rng_for(87, n), n, k, m, ("normal", 1.0), ("normal", 1.0), "bf16")]
+    C = _product(A, B, "bf16", trans)
+    _check(C, A, B)
+    ref = A.astype(np.float64) @ B.astype(np.float64)
+    assert np.linalg.norm(C - ref) <= limit * np.linalg.norm(ref)
