@@ -288,8 +288,9 @@ int gecc_protected_gemm_retry(gecc_ctx* ctx, void* dev_A, void* dev_B, float* de
                               gecc_report* host_report, int32_t max_retries, const gecc_fault* dev_faults,
                               int32_t n_faults, int32_t* attempts, void* stream);
 
-/* The same product kernel without parity work and without the syndrome epilogue:
-   the denominator of the overhead figure. */
+/* The product alone, without parity work and without the syndrome epilogue, by whichever of the library's product kernels is
+   the fastest for it: the denominator of the overhead figure.  (The protected product may go to another kernel, which has its
+   scans in the same launch; the two then need not agree to the last bit.) */
 int gecc_plain_gemm(gecc_ctx* ctx, const void* dev_A, const void* dev_B, float* dev_C, void* stream);
 
 /* Copies `count` reports device -> host on `stream` and waits for it. */

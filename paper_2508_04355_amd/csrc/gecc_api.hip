@@ -162,13 +162,22 @@ ProductPlan plan_beside_256(int64_t n, int64_t k, int64_t m, int64_t batch) {
 // 2048 54.9 -> 39.2 (23.4 -> 21.1), 2816 x 704 x 2816 51.2 -> 38.4 (19.7 -> 21.4), 4096 x 512 x 2048 49.4 -> 35.3 (18.2 -> 18.1), 2560^3 84.3 -> 76.4
 // (46.0 -> 52.4), 3072 x 1024 x 3072 57.1 -> 50.3 (26.0 -> 34.2), 1280 x 7296 x 2304 171.6 -> 109.8 (113 -> 73.7), 1024 x 4096 x 4096 NT 109.0 -> 80.2; 3584 x 1536
 // x 2560 67.8 -> 67.6 and 3072 x 2048 x 3072 76.7 -> 81.6 stand on either side of the line.
+double time_of(const ProductPlan& g, int64_t n, int64_t k, int64_t m, int64_t batch) {
+  const int64_t tiles = ((n + g.tile - 1) / g.tile) * ((m + g.tile - 1) / g.tile) * batch;
+  return g.tile == 128 ? time_128(k, tiles, g.ksplit) : time_64(k, tiles, g.ksplit);
+}
 bool fast_pays(int64_t n, int64_t k, int64_t m, int64_t batch, double bonus) {
   const int64_t t256 = ((n + 255) / 256) * ((m + 255) / 256) * batch;
   if (t256 > 256) return true;
-  if (!fast_may_pay(n, k, m, batch)) return false;
-  const ProductPlan g = plan_beside_256(n, k, m, batch);
-  const int64_t tiles = ((n + g.tile - 1) / g.tile) * ((m + g.tile - 1) / g.tile) * batch;
-  return time_256(k, t256) + bonus < (g.tile == 128 ? time_128(k, tiles, g.ksplit) : time_64(k, tiles, g.ksplit));
+  return fast_may_pay(n, k, m, batch) && time_256(k, t256) + bonus < time_of(plan_beside_256(n, k, m, batch), n, k, m, batch);
+}
+// The same for a product on its own.  Beside tiles of 64 the fit is good to a tenth (256 x 256 tiles / tiles of 64, measured: 1000 x 512 x 776
+// 14.7 / 8.0, 776 x 2048 x 1032 36.9 / 17.1, 1504 x 1024 x 1504 21.8 / 17.7, 4096 x 192 x 4096 18.4 / 23.0, 3072 x 128 x 4096 13.8 / 16.0); beside tiles of 128 they
+// have to be a quarter apart, for what it does not know (2560^3 46.0 / 52.4 where it says 52.9 / 50.2).
+bool fast_alone(int64_t n, int64_t k, int64_t m, int64_t batch) {
+  const int64_t t256 = ((n + 255) / 256) * ((m + 255) / 256) * batch;
+  const bool close = plan_beside_256(n, k, m, batch).tile == 128;
+  return fast_pays(n, k, m, batch, close ? -0.25 * time_256(k, t256) : 0.0);
 }
 // The parity scans ride in gemm_tile's launch (scans_ride) and have launches of their own beside the other kernel's: two for NN and TT, 12 us;
 // one for NT and TN, which small products feel (256^3 NT), and above 2^19 symbols the fit has to be 6 us apart.  An operand that is read
@@ -186,13 +195,12 @@ void plan_product(gecc_ctx* c, bool compact) {
   const bool may_be_fast = p.dtype == GECC_BF16 && p.k % 64 == 0 && p.lda % 8 == 0 && p.ldb % 8 == 0 &&
                            (!p.trans_a || p.n % 8 == 0) && (p.trans_b || p.m % 8 == 0) && (int64_t)p.n * p.m >= 256 * 256;
   const int64_t t128 = (int64_t)((p.n + 127) / 128) * ((p.m + 127) / 128) * p.batch;
-  const int64_t t256 = (int64_t)((p.n + 255) / 256) * ((p.m + 255) / 256) * p.batch;
   ProductPlan pl = {128, ksplit_128(t128, p.k), true};
   if (blocked(c)) pl.ksplit = 1;
   else if (!compact && !(may_be_fast && (c->cu_hint > 0 || fast_pays(p.n, p.k, p.m, p.batch, riders_bonus(p, c->tile_min)))))
     pl = may_be_fast && fast_may_pay(p.n, p.k, p.m, p.batch) ? plan_beside_256(p.n, p.k, p.m, p.batch) : plan_tiles(p.dtype, p.n, p.k, p.m, p.batch);
-  // (on its own the product stays with the faster kernel; a quarter apart, for what a fit does not know)
-  c->fast_plain = pl.fast || (may_be_fast && fast_pays(p.n, p.k, p.m, p.batch, -0.25 * time_256(p.k, t256)));
+  // (a product on its own stays with the faster kernel)
+  c->fast_plain = pl.fast || (may_be_fast && fast_alone(p.n, p.k, p.m, p.batch));
   c->tile_m = c->tile_n = pl.tile;
   c->ksplit = pl.ksplit;
   c->fast = pl.fast;
@@ -1355,7 +1363,16 @@ int gecc_plain_gemm(gecc_ctx* ctx, const void* dev_A, const void* dev_B, float* 
     return GECC_ERR_ALIGN;
   GemmArgs g = gemm_args(ctx, dev_A, dev_B, dev_C);
   g.rowpart = nullptr; g.colpart = nullptr; g.faults = nullptr; g.n_faults = 0;
-  g.fast = ctx->fast_plain;
+  if (ctx->fast_plain && !ctx->fast) {
+    // (there are no partial sums to go by the plan's tiles: the other kernel takes the operands in its own, if it takes them)
+    GemmArgs f = g;
+    f.fast = true;
+    f.tile_m = f.tile_n = 128;
+    f.ntm = (g.n + 127) / 128;
+    f.ntn = (g.m + 127) / 128;
+    f.ksplit = 0;
+    if (gemm_takes_256(f)) g = f;
+  }
   if (g.ksplit > 1 && !gemm_takes_256(g)) {
     const int rc = prep(ctx, (hipStream_t)stream);
     if (rc) return rc;
