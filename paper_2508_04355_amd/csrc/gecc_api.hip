@@ -158,7 +158,7 @@ ProductPlan plan_beside_256(int64_t n, int64_t k, int64_t m, int64_t batch) {
   if (large || (t128 <= 576 && time_128(k, t128, s128) < time_64(k, t64, s64))) return {128, s128, false};
   return {64, s64, false};
 }
-// bonus: what gemm_tile saves a protected product beyond its own time (riders_bonus).  Whole calls, 256 x 256 tiles -> gemm_tile (product alone): 2048^3 72.0 -> 56.5 us (38.3 -> 36.6), 2048 x 1024 x
+// bonus: what gemm_tile saves a protected product beyond its own time (fast_protected).  Whole calls, 256 x 256 tiles -> gemm_tile (product alone): 2048^3 72.0 -> 56.5 us (38.3 -> 36.6), 2048 x 1024 x
 // 2048 54.9 -> 39.2 (23.4 -> 21.1), 2816 x 704 x 2816 51.2 -> 38.4 (19.7 -> 21.4), 4096 x 512 x 2048 49.4 -> 35.3 (18.2 -> 18.1), 2560^3 84.3 -> 76.4
 // (46.0 -> 52.4), 3072 x 1024 x 3072 57.1 -> 50.3 (26.0 -> 34.2), 1280 x 7296 x 2304 171.6 -> 109.8 (113 -> 73.7), 1024 x 4096 x 4096 NT 109.0 -> 80.2; 3584 x 1536
 // x 2560 67.8 -> 67.6 and 3072 x 2048 x 3072 76.7 -> 81.6 stand on either side of the line.
@@ -179,14 +179,47 @@ bool fast_alone(int64_t n, int64_t k, int64_t m, int64_t batch) {
   const bool close = plan_beside_256(n, k, m, batch).tile == 128;
   return fast_pays(n, k, m, batch, close ? -0.25 * time_256(k, t256) : 0.0);
 }
-// The parity scans ride in gemm_tile's launch (scans_ride) and have launches of their own beside the other kernel's: two for NN and TT, 12 us;
-// one for NT and TN, which small products feel (256^3 NT), and above 2^19 symbols the fit has to be 6 us apart.  An operand that is read
-// once for both of its scans has one of them fewer to ride.  Sizes that are no multiples of 64 stay with the 256 x 256-tile kernel unless the
-// fit is 6 us apart: they are the ones its own tests reach it with.
-double riders_bonus(const gecc_params& p, int64_t tile_min) {
-  if (p.n % 64 != 0 || p.m % 64 != 0) return -6.0;
-  if ((int64_t)p.n * p.k * p.batch >= tile_min || (int64_t)p.k * p.m * p.batch >= tile_min) return 0.0;
-  return p.trans_a == p.trans_b ? 12.0 : (int64_t)p.n * p.m * p.batch < (1 << 19) ? 9.0 : -6.0;
+// Whether the scans of the parity blocks (`scans`: their workgroups) ride in the launch of gemm_tile.  Two launches
+// saved are 9 us and more (128^3 fp32 44 -> 31 us, bf16 1500 x 1501 x 1500 75 -> 61), but a scan's workgroup there takes
+// the place of a product's, with fewer rows in flight than in a launch of its own.  Clean passes, one after the other
+// -> in one launch, over 2300 products of all layouts (this rule 13 to 23 % faster on average, riding
+// whenever the product has at most 2048 workgroups 12 to 22 %, with products that took twice as long):
+//   - many rounds of workgroups hide nothing (256 x 512^3 fp32 603 -> 608 us), and scans of more than 16 workgroups per
+//     compute unit take longer than the product (bf16 307 x 503 x 301 x 94 193 -> 313);
+//   - bf16 gains whatever the ranges of k, now that the scans come behind the product's workgroups where not all run at once (before, long
+//     ranges and more than 5 scan workgroups per compute unit lost): 5064 x 3680 x 1752 157.5 -> 145.6 us, 3029 x 817 x 2493 NT 53.1 -> 46.6,
+//     6001 x 2000 x 3001 NT 149.6 -> 140.2, 3500^3 215.5 -> 202.4, 5001 x 700 x 5001 105.7 -> 96.2, 4001 x 1000 x 4001 92.9 -> 87.6, 2500^3 89.9 -> 78.9;
+//   - fp32 keeps four workgroups of 64 x 64 tiles on a compute unit: scans that find no place beside them delay a
+//     product of long k (3904 x 5888 x 448 289 -> 323), and many of them one of more than 512 terms (8 x 600^3 NT
+//     81 -> 143).  Of 128 x 128 tiles it keeps two: both scans together, if they are few, beside short ranges of k (68 x
+//     512 x 256 x 128 TN 90 -> 73; 2048^3 143 -> 190, 253 x 256 x 640 x 128 TN, where a tile scan has left one, 170 -> 327).
+bool scans_ride(const gecc_params& p, int tile, int ksplit, int64_t scans, bool both) {
+  const int64_t own = (int64_t)((p.n + tile - 1) / tile) * ((p.m + tile - 1) / tile) * p.batch * ksplit;
+  const int k_per = p.k / ksplit;
+  const bool small = tile == 64;
+  if (own > 2048 || scans > 4096) return false;
+  if (p.dtype == GECC_BF16) return true;
+  if (!small) return both && k_per <= 640 && scans <= 1024;
+  return own + scans <= 1536 || (k_per <= 640 && (scans <= 1792 || k_per <= 512));
+}
+
+// Whether the 256 x 256-tile kernel takes a protected product: where the parity scans ride in gemm_tile's launch, that saves the launches that
+// they have of their own beside the other kernel, two for NN and TT, 12 us; one for NT and TN, which small products feel (256^3 NT), and
+// above 2^19 symbols the fit has to be 6 us apart.  An operand that is read once for both of its scans has one of them fewer to ride.
+// Where they do not ride, the faster product it is (4096 x 192 x 4096, 256 x 256 tiles / tiles of 64: NN 47.5 / 55.5 us a call, NT 45.0 / 51.7; 3072 x 128 x 4096
+// 40.7 / 46.5).  Sizes that are no multiples of 64 stay with the 256 x 256-tile kernel unless the fit is 6 us apart: they are the ones its
+// own tests reach it with.
+bool fast_protected(const gecc_params& p, int64_t tile_min) {
+  const ProductPlan g = plan_beside_256(p.n, p.k, p.m, p.batch);
+  // (their workgroups as plan_riders counts them)
+  const int64_t chunks = (p.k + SCAN_CHUNK_ROWS - 1) / SCAN_CHUNK_ROWS;
+  const int64_t pr = p.trans_a ? (p.n + 511) / 512 * chunks : (p.n + 3) / 4, pc = p.trans_b ? (p.m + 3) / 4 : (p.m + 511) / 512 * chunks;
+  double bonus;
+  if (p.n % 64 != 0 || p.m % 64 != 0) bonus = -6.0;
+  else if (!scans_ride(p, g.tile, g.ksplit, (1 + pr + pc) * p.batch, true)) return fast_alone(p.n, p.k, p.m, p.batch);
+  else if ((int64_t)p.n * p.k * p.batch >= tile_min || (int64_t)p.k * p.m * p.batch >= tile_min) bonus = 0.0;
+  else bonus = p.trans_a == p.trans_b ? 12.0 : (int64_t)p.n * p.m * p.batch < (1 << 19) ? 9.0 : -6.0;
+  return fast_pays(p.n, p.k, p.m, p.batch, bonus);
 }
 
 // compact: 128 x 128 tiles and 256 workgroups, the plan that needs the least workspace.
@@ -197,7 +230,7 @@ void plan_product(gecc_ctx* c, bool compact) {
   const int64_t t128 = (int64_t)((p.n + 127) / 128) * ((p.m + 127) / 128) * p.batch;
   ProductPlan pl = {128, ksplit_128(t128, p.k), true};
   if (blocked(c)) pl.ksplit = 1;
-  else if (!compact && !(may_be_fast && (c->cu_hint > 0 || fast_pays(p.n, p.k, p.m, p.batch, riders_bonus(p, c->tile_min)))))
+  else if (!compact && !(may_be_fast && (c->cu_hint > 0 || fast_protected(p, c->tile_min))))
     pl = may_be_fast && fast_may_pay(p.n, p.k, p.m, p.batch) ? plan_beside_256(p.n, p.k, p.m, p.batch) : plan_tiles(p.dtype, p.n, p.k, p.m, p.batch);
   // (a product on its own stays with the faster kernel)
   c->fast_plain = pl.fast || (may_be_fast && fast_alone(p.n, p.k, p.m, p.batch));
@@ -726,30 +759,6 @@ int check_multiply_args(gecc_ctx* ctx, const void* dev_A, const double* dev_A_pa
   return GECC_OK;
 }
 
-// Whether the scans of the parity blocks (`scans`: their workgroups) ride in the launch of gemm_tile.  Two launches
-// saved are 9 us and more (128^3 fp32 44 -> 31 us, bf16 1500 x 1501 x 1500 75 -> 61), but a scan's workgroup there takes
-// the place of a product's, with fewer rows in flight than in a launch of its own.  Clean passes, one after the other
-// -> in one launch, over 2300 products of all layouts (this rule 13 to 23 % faster on average, riding
-// whenever the product has at most 2048 workgroups 12 to 22 %, with products that took twice as long):
-//   - many rounds of workgroups hide nothing (256 x 512^3 fp32 603 -> 608 us), and scans of more than 16 workgroups per
-//     compute unit take longer than the product (bf16 307 x 503 x 301 x 94 193 -> 313);
-//   - bf16 gains whatever the ranges of k, now that the scans come behind the product's workgroups where not all run at once (before, long
-//     ranges and more than 5 scan workgroups per compute unit lost): 5064 x 3680 x 1752 157.5 -> 145.6 us, 3029 x 817 x 2493 NT 53.1 -> 46.6,
-//     6001 x 2000 x 3001 NT 149.6 -> 140.2, 3500^3 215.5 -> 202.4, 5001 x 700 x 5001 105.7 -> 96.2, 4001 x 1000 x 4001 92.9 -> 87.6, 2500^3 89.9 -> 78.9;
-//   - fp32 keeps four workgroups of 64 x 64 tiles on a compute unit: scans that find no place beside them delay a
-//     product of long k (3904 x 5888 x 448 289 -> 323), and many of them one of more than 512 terms (8 x 600^3 NT
-//     81 -> 143).  Of 128 x 128 tiles it keeps two: both scans together, if they are few, beside short ranges of k (68 x
-//     512 x 256 x 128 TN 90 -> 73; 2048^3 143 -> 190, 253 x 256 x 640 x 128 TN, where a tile scan has left one, 170 -> 327).
-bool scans_ride(const gecc_ctx* c, int64_t scans, bool both) {
-  const int64_t own = (int64_t)c->ntm * c->ntn * c->p.batch * c->ksplit;
-  const int k_per = c->p.k / c->ksplit;
-  const bool small = c->tile_m == 64;
-  if (own > 2048 || scans > 4096) return false;
-  if (c->p.dtype == GECC_BF16) return true;
-  if (!small) return both && k_per <= 640 && scans <= 1024;
-  return own + scans <= 1536 || (k_per <= 640 && (scans <= 1792 || k_per <= 512));
-}
-
 // The scans that ride (side) and those of them that cannot finish by themselves and go first (alone).
 struct Riders { bool on; GemmSide side; const ScanJob* alone[2]; };
 // left: null, or what the operand parities have left (the riders' own chunks are then left to the threshold pass)
@@ -775,7 +784,7 @@ Riders plan_riders(const gecc_ctx* ctx, const GemmArgs& g, uint32_t* done, const
   // (the rule counts a row scan by fours of rows, which is how it was measured)
   int64_t scans = ctx->p.batch;
   for (const SideJob& j : r.side.j) scans += j.kind == SIDE_ROW ? (int64_t)((j.s.R + 3) / 4) * j.s.batch : j.nblk;
-  r.on = scans_ride(ctx, scans, pr && pc);
+  r.on = scans_ride(ctx->p, ctx->tile_m, ctx->ksplit, scans, pr && pc);
   return r;
 }
 

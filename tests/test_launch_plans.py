@@ -123,6 +123,14 @@ def test_products_on_their_own_go_to_the_faster_kernel(plans, ta, tb):
                               (ALONE_SHAPE, "gemm_bf16_256"), ((1024, 1024, 1024), "gemm_tile"), ((1536, 4224, 768), "gemm_tile")):
         (rc, names), = routes(plans, [("plain", n, k, m, 1, 1, ta, tb)])
         assert rc == 0 and len(names) == 1 + ("zero_words" in names[0]) and kernel in names[-1], names
-    if ta == tb:
+    if not ta and not tb:
         (_, names), = routes(plans, [("protected",) + ALONE_SHAPE + (1, 1, ta, tb)])
         assert any("gemm_tileILi1E" in x and "ELi64E" in x for x in names), names
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_products_whose_scans_do_not_ride_go_to_the_faster_kernel(plans, ta, tb):
+    """More than 2048 tiles of 64: the parity scans have launches of their own beside either kernel, and nothing is saved by the slower one."""
+    for n, k, m in ((4096, 192, 4096), (3072, 128, 4096)):
+        (rc, names), = routes(plans, [("protected", n, k, m, 1, 1, ta, tb)])
+        assert rc == 0 and any("gemm_bf16_256" in x for x in names), names

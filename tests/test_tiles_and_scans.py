@@ -377,7 +377,7 @@ ALONE_SHAPE = (448, 192, 18624)
 @pytest.mark.parametrize("trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
 @pytest.mark.parametrize("pad,shift", [(0, 0), (8, 0), (0, 1)])
 def test_a_product_on_its_own_in_another_kernel_than_its_plan_has(pad, shift, trans):
-    """Planned in tiles of 64 (NN, TT), on its own in tiles of 256 x 256 (test_launch_plans.py holds it to both); off a 16-byte boundary
+    """Planned in tiles of 64 (NN), on its own in tiles of 256 x 256 (test_launch_plans.py holds it to both); off a 16-byte boundary
     the plan's kernel takes it after all."""
     A, B = [x[None] for x in inputs.operands(inputs.rng_for(88, pad), *ALONE_SHAPE, ("normal", 1.0), ("normal", 1.0), "bf16")]
     _check(_product(A, B, "bf16", trans, pad=pad, shift=shift), A, B)
