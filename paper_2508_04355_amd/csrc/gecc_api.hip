@@ -207,16 +207,15 @@ bool scans_ride(const gecc_params& p, int tile, int ksplit, int64_t scans, bool 
 // they have of their own beside the other kernel, two for NN and TT, 12 us; one for NT and TN, which small products feel (256^3 NT), and
 // above 2^19 symbols the fit has to be 6 us apart.  An operand that is read once for both of its scans has one of them fewer to ride.
 // Where they do not ride, the faster product it is (4096 x 192 x 4096, 256 x 256 tiles / tiles of 64: NN 47.5 / 55.5 us a call, NT 45.0 / 51.7; 3072 x 128 x 4096
-// 40.7 / 46.5).  Sizes that are no multiples of 64 stay with the 256 x 256-tile kernel unless the fit is 6 us apart: they are the ones its
-// own tests reach it with.
+// 40.7 / 46.5).  Tiles that hang over the edge are in the fitted times of both kernels (whole calls NN, 256 x 256 tiles / gemm_tile: 2000 x 1024 x 2000
+// 54.6 / 41.6, 3000 x 512 x 3000 52.5 / 40.1, 2504 x 2496 x 2504 84.0 / 77.7, 1000 x 512 x 776 45.6 / 23.5, 520 x 256 x 264 40.6 / 22.1).
 bool fast_protected(const gecc_params& p, int64_t tile_min) {
   const ProductPlan g = plan_beside_256(p.n, p.k, p.m, p.batch);
   // (their workgroups as plan_riders counts them)
   const int64_t chunks = (p.k + SCAN_CHUNK_ROWS - 1) / SCAN_CHUNK_ROWS;
   const int64_t pr = p.trans_a ? (p.n + 511) / 512 * chunks : (p.n + 3) / 4, pc = p.trans_b ? (p.m + 3) / 4 : (p.m + 511) / 512 * chunks;
   double bonus;
-  if (p.n % 64 != 0 || p.m % 64 != 0) bonus = -6.0;
-  else if (!scans_ride(p, g.tile, g.ksplit, (1 + pr + pc) * p.batch, true)) return fast_alone(p.n, p.k, p.m, p.batch);
+  if (!scans_ride(p, g.tile, g.ksplit, (1 + pr + pc) * p.batch, true)) return fast_alone(p.n, p.k, p.m, p.batch);
   else if ((int64_t)p.n * p.k * p.batch >= tile_min || (int64_t)p.k * p.m * p.batch >= tile_min) bonus = 0.0;
   else bonus = p.trans_a == p.trans_b ? 12.0 : (int64_t)p.n * p.m * p.batch < (1 << 19) ? 9.0 : -6.0;
   return fast_pays(p.n, p.k, p.m, p.batch, bonus);

@@ -27,11 +27,10 @@ def _trial(rng, n, k, m, dtype, law_a, law_b, faults):
 
 
 # ---------------------------------------------------------------------------------------------
-# the last two reach the 256 x 256-tile bf16 kernel (k % 64 == 0, rows of 8 elements) with ragged
-# tiles on both edges; everything else goes to the generic kernel
+# the last four the 256 x 256-tile bf16 kernel can take as well (k % 64 == 0, rows of 8 elements), with ragged tiles on both edges
 SHAPES = [(128, 128, 128), (1, 1, 1), (3, 5, 2), (130, 70, 257), (300, 200, 260), (257, 1031, 129),
           (520, 256, 264), (1000, 320, 776),
-          (520, 64, 264), (264, 192, 520)]    # the 256 x 256 bf16 kernel at its shortest k (one pair of k-tiles), and three pairs
+          (520, 64, 264), (264, 192, 520)]    # its shortest k (one pair of k-tiles), and three pairs
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
@@ -59,10 +58,19 @@ def test_clean_product_blocks_match_the_oracle(shape, trans, dtype):
 
 
 @pytest.mark.parametrize("trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("shape", SHAPES[-4:])
+def test_clean_product_blocks_of_the_256_tile_kernel_match_the_oracle(shape, trans, monkeypatch):
+    """(GECC_CU_COUNT keeps the plan with 256 x 256 tiles for products this small.)"""
+    monkeypatch.setenv("GECC_CU_COUNT", "256")
+    test_clean_product_blocks_match_the_oracle(shape, trans, "bf16")
+
+
+@pytest.mark.parametrize("trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
 @pytest.mark.parametrize("pattern", ["C+C on the edges", "A+C", "B+C", "A+B"])
-def test_ragged_tiles_of_the_fast_bf16_kernel_with_errors(pattern, trans):
+def test_ragged_tiles_of_the_fast_bf16_kernel_with_errors(pattern, trans, monkeypatch):
     """Faults in the last row / column of C and of the operands, where the 256 x 256 tiles of the
     bf16 kernel hang over the edge (range-checked stores, zero-filled operand rows)."""
+    monkeypatch.setenv("GECC_CU_COUNT", "256")      # (keeps the plan with those tiles)
     n, k, m = 520, 256, 264
     rng = inputs.rng_for(92, 0)
     law = ("normal", 1.0)
@@ -173,7 +181,7 @@ def test_k_split_tail_of_the_fast_bf16_kernel(pattern, shape, cus, trans, monkey
         g3 = H.run_gpu(A, B, A, B, [], tau, "bf16", trans[0], trans[1], staged=False)
         assert np.array_equal(g.C, g3.C) and g3.reports[0].status == gecc.CLEAN
         # and the split changes C only by the rounding of one more fp32 addition per element
-        monkeypatch.delenv("GECC_CU_COUNT")
+        monkeypatch.setenv("GECC_CU_COUNT", "256")        # (one round: the same kernel, nothing split)
         g4 = H.run_gpu(A, B, A, B, [], tau, "bf16", trans[0], trans[1])
         assert not np.array_equal(g.C, g4.C)
         assert np.abs(g.C - g4.C).max() <= 4e-6 * np.abs(g4.C).max()
@@ -465,9 +473,10 @@ def test_unaligned_leading_dimensions_take_the_scalar_paths():
 
 
 @pytest.mark.parametrize("trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
-def test_padded_leading_dimensions_in_the_fast_bf16_kernel(trans):
+def test_padded_leading_dimensions_in_the_fast_bf16_kernel(trans, monkeypatch):
     """Leading dimensions larger than the rows (by a multiple of 8 elements, which keeps the 256 x 256
     kernel): operand panels and the stores of C, two rows x 32 columns each, walk the padded rows."""
+    monkeypatch.setenv("GECC_CU_COUNT", "256")      # (keeps the plan with those tiles)
     n, k, m = 520, 256, 264
     rng = inputs.rng_for(94, 1)
     law = ("normal", 1.0)

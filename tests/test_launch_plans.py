@@ -111,8 +111,13 @@ def test_bf16_products_either_kernel_takes(plans, ta, tb):
         assert "gemm_bf16_256" in product("plain", n, k, m)[0]
     for n, k, m in ((256, 256, 256), (1280, 7296, 2304), (1024, 4096, 4096)):
         assert "gemm_tile" in product("protected", n, k, m)[0] and "gemm_tile" in product("plain", n, k, m)[0]
-    for n, k, m in ((4096, 4096, 4096), (3072, 3072, 3072), (520, 256, 264), (1000, 512, 776)):
+    for n, k, m in ((4096, 4096, 4096), (3072, 3072, 3072), (4040, 4032, 4008)):
         assert "gemm_bf16_256" in product("protected", n, k, m)[0]
+    # sizes that are no multiples of a tile go by the same rule
+    for n, k, m in ((2000, 1024, 2000), (2000, 512, 2000), (3000, 512, 3000), (2056, 2048, 2056), (1000, 512, 776)):
+        name, scans = product("protected", n, k, m)
+        assert ("gemm_tile" in name) == two_launches and (scans <= 3 if two_launches else scans >= 2)
+    assert "gemm_tile" in product("protected", 520, 256, 264)[0]
 
 
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
