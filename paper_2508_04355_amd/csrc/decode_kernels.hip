@@ -1320,13 +1320,21 @@ hipError_t launch_decode_c(const DecodeArgs& a, int with_summary, hipStream_t st
   return hipGetLastError();
 }
 
-// Workgroups of an item in the repair: one per RP_LINES rows and columns, at most 256 in all (a closed launch lasts as long
-// as its dispatch), as many as there are records and counters for
+// Workgroups of an item in the repair: one per RP_LINES rows and columns, at most 256 in all, as many as there are records and counters
+// for.  More than 128 items of long lines would have one each for them: then at most 512.  Repair, us (at most 256 / 512 / 1024):
+//                                     an error of A in all items    in one item
+//   f32 4096 x 64 x 4096 x 129          48.4 / 39.8 / 49.0         39.4 / 26.4 / 21.7
+//   f32 8192 x 32 x 1024 x 256          55.8 / 44.4 / 53.6         40.4 / 28.6 / 22.4
+//   f32 2048 x 128 x 2048 x 200         37.6 / 35.6 / 45.4         26.5 / 22.0 / 19.7
+//   f32 1024 x 256 x 1024 x 200         31.4 / 31.8 / 41.4         21.7 / 19.6 / 18.3
+//   bf16, 128 blocks of 2048 x 512      34.2 / 35.4 / 45.0         23.8 / 25.3 / 28.0
+// Where no item is repaired it lasts 6.4 between event pairs with any of them.
 static int repair_wgs(const DecodeArgs& a, const RepairScratch& s) {
   const int len = a.p.n > a.p.m ? a.p.n : a.p.m;
   int wgs = (len + RP_LINES - 1) / RP_LINES;
   if (wgs > RP_WGS) wgs = RP_WGS;
-  if ((int64_t)wgs * a.p.batch > 256) wgs = 256 / a.p.batch;
+  const int most = len >= 2048 && a.p.batch > 128 ? 512 : 256;
+  if ((int64_t)wgs * a.p.batch > most) wgs = most / a.p.batch;
   while (wgs > 1 && (size_t)wgs * a.p.batch * sizeof(RepairRecord) > s.bytes) --wgs;
   return wgs > 1 && a.p.batch <= s.counters ? wgs : 1;
 }

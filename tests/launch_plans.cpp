@@ -6,7 +6,7 @@
 // lays them out, lie inside the part of the workspace that is theirs.
 //
 // With the argument "routes" it reads calls from its input, "entry n k m batch dtype trans_a trans_b" a line, and prints
-// for each the result and the kernels launched.
+// for each the result and the kernels launched; with "grids" each kernel's workgroups behind its name.
 #include <cstdio>
 #include <cstring>
 #include <map>
@@ -26,10 +26,11 @@ static long g_launches, g_scans, g_narrow_split, g_main_split, g_bad;
 static std::string g_case;
 
 static std::vector<std::string> g_names;      // kernels of the call, in order
+static bool g_grids;
 
 static void look_at(const std::string& name, void** args) {
   ++g_launches;
-  g_names.push_back(name);
+  g_names.push_back(g_grids ? name + ":" + std::to_string((long)g_cfg.grid.x * g_cfg.grid.y * g_cfg.grid.z) : name);
   if (name.find("rowdot") != std::string::npos || name.find("coldot") != std::string::npos) ++g_scans;
   if (name.find("gemm_tile") == std::string::npos) return;
   const GemmArgs& a = *static_cast<const GemmArgs*>(args[0]);
@@ -96,6 +97,7 @@ static int one(int n, int k, int m, int batch, int dtype, int ta, int tb, int bn
   float* C = static_cast<float*>(dev(6, 0));
   if (!rc && entry == "multiply") rc = gecc_multiply(g_ctx, A, ap, B, bp, C, cp, nullptr, 0, nullptr);
   if (!rc && entry == "plain") rc = gecc_plain_gemm(g_ctx, A, B, C, nullptr);
+  if (!rc && entry == "correct") rc = gecc_correct(g_ctx, A, ap, B, bp, C, cp, static_cast<gecc_report*>(dev(7, 0)), nullptr);
   if (!rc && entry == "protected") rc = gecc_protected_gemm(g_ctx, A, B, C, ap, bp, cp, static_cast<gecc_report*>(dev(7, 0)), nullptr);
   if (rc) { ++g_bad; printf("BAD %s: %s\n", g_case.c_str(), gecc_strerror(rc)); }
   gecc_destroy(g_ctx);
@@ -115,7 +117,8 @@ static int routes() {
 }
 
 int main(int argc, char** argv) {
-  if (argc > 1 && std::string(argv[1]) == "routes") return routes();
+  g_grids = argc > 1 && std::string(argv[1]) == "grids";
+  if (g_grids || (argc > 1 && std::string(argv[1]) == "routes")) return routes();
   // (the sizes of test_narrow_products_of_blocked_mode_with_a_split_k_range first)
   one(4096, 264, 4096, 1, GECC_BF16, 0, 0, 2048, 2048, 0, 0);       // k no multiple of 64
   one(4096, 256, 4096, 1, GECC_BF16, 0, 0, 4096, 4096, 0, 0);       // a narrow product below 256 x 256 symbols

@@ -23,9 +23,10 @@ def plans(tmp_path_factory):
     return exe
 
 
-def routes(exe, calls):
-    """[(result, [kernel names])] of calls (entry, n, k, m, batch, dtype, trans_a, trans_b)."""
-    r = subprocess.run([exe, "routes"], input="\n".join(" ".join(str(x) for x in c) for c in calls), capture_output=True, text=True, timeout=120)
+def routes(exe, calls, what="routes"):
+    """[(result, [kernel names])] of calls (entry, n, k, m, batch, dtype, trans_a, trans_b); what = "grids": a name is followed by ":" and
+    its workgroups."""
+    r = subprocess.run([exe, what], input="\n".join(" ".join(str(x) for x in c) for c in calls), capture_output=True, text=True, timeout=120)
     lines = [x.split() for x in r.stdout.splitlines() if not x.startswith("BAD")]
     assert r.returncode == 0 and len(lines) == len(calls), r.stdout + r.stderr
     return [(int(x[0]), x[1:]) for x in lines]
@@ -139,3 +140,13 @@ def test_products_whose_scans_do_not_ride_go_to_the_faster_kernel(plans, ta, tb)
     for n, k, m in ((4096, 192, 4096), (3072, 128, 4096)):
         (rc, names), = routes(plans, [("protected", n, k, m, 1, 1, ta, tb)])
         assert rc == 0 and any("gemm_bf16_256" in x for x in names), names
+
+
+@pytest.mark.parametrize("shape,batch,per_item", [((4096, 4096, 4096), 1, 16), ((512, 512, 512), 256, 1), ((512, 512, 512), 128, 2), ((1024, 256, 1024), 200, 1),
+                                                  ((2047, 24, 100), 130, 1), ((2048, 24, 100), 130, 3), ((100, 24, 4096), 256, 2), ((4096, 24, 100), 257, 1),
+                                                  ((16384, 32, 512), 60, 4), ((2048, 64, 512), 128, 2), ((2048, 64, 512), 129, 3), ((16384, 32, 512), 1, 64)])
+def test_workgroups_of_a_repair(plans, shape, batch, per_item):
+    """One for 256 lines of an item, at most 256 in all or, of more than 128 items of lines of 2048 and longer, 512."""
+    for dtype in (0, 1):
+        (rc, names), = routes(plans, [("correct",) + shape + (batch, dtype, 0, 0)], "grids")
+        assert rc == 0 and [x.split(":")[1] for x in names if "repair_kernel" in x] == [str(per_item * batch)], names

@@ -24,7 +24,8 @@ def _faults(pattern, n, k, m):
 
 @pytest.mark.parametrize("trans", [(0, 0), (1, 1)])
 @pytest.mark.parametrize("dtype,shape,batch", [("f32", (257, 64, 256), 1), ("bf16", (256, 96, 513), 2), ("f32", (1030, 72, 300), 3),
-                                               ("bf16", (64, 70, 1300), 1), ("f32", (257, 65, 260), 260)])   # (one workgroup an item)
+                                               ("bf16", (64, 70, 1300), 1), ("f32", (257, 65, 260), 260),    # (one workgroup an item)
+                                               ("f32", (2305, 24, 100), 130)])  # (three, where shorter lines would have one)
 @pytest.mark.parametrize("pattern", ["A", "B+C", "A+B, one term", "two of A in one row", "two of B in one column", "2 x 2 crossing",
                                      "A in a row, B twice across it", "two in one column of A"])
 def test_operand_errors_repaired_by_several_workgroups(pattern, dtype, shape, batch, trans):
