@@ -241,26 +241,17 @@ __global__ __launch_bounds__(256) void summarize_kernel(DecodeArgs a) {   // fou
 // (threadIdx.x < DC_THREADS; a larger workgroup lets its other wavefronts end first).
 constexpr int DC_THREADS = 256;
 
-__device__ void sort_small(int* v, int cnt) {
-  for (int x = 1; x < cnt; ++x) {
-    const int key = v[x];
-    int y = x - 1;
-    while (y >= 0 && v[y] > key) { v[y + 1] = v[y]; --y; }
-    v[y + 1] = key;
-  }
-}
-
 struct Synd {
   const double *r1, *r2, *q1, *q2;
   double b_r1, b_r2, b_q1, b_q2;            // thresholds of the four families
-  const double *a_r1, *a_r2, *a_q1, *a_q2;  // per-line allowances (null: none)
+  const double *a_r1, *a_r2, *a_q1, *a_q2;  // per-line allowances
   double rel;                               // relative rounding allowance of a syndrome value
   bool wt;                                  // false: single-checksum mode, r2 / q2 are not read
   // how far each syndrome value is trusted when an estimate is verified
-  __device__ double tr1(int i) const { return b_r1 + (a_r1 ? a_r1[i] : 0.0) + rel * fabs(r1[i]); }
-  __device__ double tr2(int i) const { return b_r2 + (a_r2 ? a_r2[i] : 0.0) + rel * fabs(r2[i]); }
-  __device__ double tq1(int j) const { return b_q1 + (a_q1 ? a_q1[j] : 0.0) + rel * fabs(q1[j]); }
-  __device__ double tq2(int j) const { return b_q2 + (a_q2 ? a_q2[j] : 0.0) + rel * fabs(q2[j]); }
+  __device__ double tr1(int i) const { return b_r1 + a_r1[i] + rel * fabs(r1[i]); }
+  __device__ double tr2(int i) const { return b_r2 + a_r2[i] + rel * fabs(r2[i]); }
+  __device__ double tq1(int j) const { return b_q1 + a_q1[j] + rel * fabs(q1[j]); }
+  __device__ double tq2(int j) const { return b_q2 + a_q2[j] + rel * fabs(q2[j]); }
 };
 
 // The syndromes of the flagged lines alone: kind 0 and 1 of a line and how far each is trusted, rows [0], columns [1], in the
@@ -417,7 +408,7 @@ struct LineEst { double x[2], u[2]; bool sig[2], flagged; };
 // pool: POOL_DOUBLES of LDS
 constexpr int POOL_DOUBLES = 2048 + 256;
 __device__ int known_lines_correct(const DecodeArgs& a, int b, DecodeState* st, gecc_report* rep,
-                                   const Synd& y, int final_pass, double* pool) {
+                                   const Synd& y, double* pool) {
   const int n = a.p.n, m = a.p.m;
   const int s = st->s_cnt, t = st->t_cnt;
   const bool rows_known = a.p.weighted ? s <= 2 : s == 1;
@@ -433,7 +424,7 @@ __device__ int known_lines_correct(const DecodeArgs& a, int b, DecodeState* st, 
 
   auto estimate = [&](int c) {
     LineEst e;
-    e.flagged = fabs(y1[c]) > b1 + (a1 ? a1[c] : 0.0) || (y.wt && fabs(y2[c]) > b2 + (a2 ? a2[c] : 0.0));
+    e.flagged = fabs(y1[c]) > b1 + a1[c] || (y.wt && fabs(y2[c]) > b2 + a2[c]);
     e.sig[0] = e.sig[1] = false; e.x[0] = e.x[1] = e.u[0] = e.u[1] = 0.0;
     if (!e.flagged) return e;
     const double u1 = rows_known ? y.tq1(c) : y.tr1(c), u2 = rows_known ? y.tq2(c) : y.tr2(c);
@@ -614,11 +605,10 @@ __device__ void decode_c_body(const DecodeArgs& a, int b, DecodeState* st, gecc_
       // (the launch's other workgroups have written through what this reads, by all of its lines)
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
       const double* sy = synd_of(a, b);
-      const double* al = final_pass ? allow_of(a, b) : nullptr;
+      const double* al = allow_of(a, b);
       const Synd y{sy, sy + n, sy + 2 * n, sy + 2 * n + m, a.p.tau_r1, a.p.tau_r2, a.p.tau_q1, a.p.tau_q2,
-                   al, al ? al + n : nullptr, al ? al + 2 * n : nullptr, al ? al + 2 * n + m : nullptr,
-                   a.p.tau_rel, a.p.weighted != 0};
-      const int k = known_lines_correct(a, b, st, rep, y, final_pass, pool);
+                   al, al + n, al + 2 * n, al + 2 * n + m, a.p.tau_rel, a.p.weighted != 0};
+      const int k = known_lines_correct(a, b, st, rep, y, pool);
       if (threadIdx.x == 0) {
         if (k < 0) {
           give_up(st, rep);

@@ -1,5 +1,6 @@
 // C ABI of libgecc: argument checking, workspace layout and the stream-ordered launch
 // sequences.  Host code only; all arithmetic of the path runs in the kernels.
+#include <algorithm>
 #include <cstdlib>
 #include <mutex>
 #include <new>

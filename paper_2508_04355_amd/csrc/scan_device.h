@@ -24,7 +24,6 @@ template <> struct Elem<GECC_F32> {
   static __device__ __forceinline__ void widen(const raw& x, double* v) {
     v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
   }
-  static __device__ __forceinline__ void load_vec(const float* p, double* v) { widen(load_raw(p), v); }
   static __device__ __forceinline__ double load_one(const float* p) { return (double)*p; }
 };
 template <> struct Elem<GECC_BF16> {
@@ -43,7 +42,6 @@ template <> struct Elem<GECC_BF16> {
       v[2 * i + 1] = (double)__uint_as_float(w[i] & 0xffff0000u);
     }
   }
-  static __device__ __forceinline__ void load_vec(const uint16_t* p, double* v) { widen(load_raw(p), v); }
   static __device__ __forceinline__ double load_one(const uint16_t* p) {
     return (double)__uint_as_float(((uint32_t)*p) << 16);
   }
