@@ -97,6 +97,7 @@ static int one(int n, int k, int m, int batch, int dtype, int ta, int tb, int bn
   float* C = static_cast<float*>(dev(6, 0));
   if (!rc && entry == "multiply") rc = gecc_multiply(g_ctx, A, ap, B, bp, C, cp, nullptr, 0, nullptr);
   if (!rc && entry == "plain") rc = gecc_plain_gemm(g_ctx, A, B, C, nullptr);
+  if (!rc && entry == "encode_a") rc = gecc_encode_a(g_ctx, A, ap, nullptr);
   if (!rc && entry == "correct") rc = gecc_correct(g_ctx, A, ap, B, bp, C, cp, static_cast<gecc_report*>(dev(7, 0)), nullptr);
   if (!rc && entry == "protected") rc = gecc_protected_gemm(g_ctx, A, B, C, ap, bp, cp, static_cast<gecc_report*>(dev(7, 0)), nullptr);
   if (rc) { ++g_bad; printf("BAD %s: %s\n", g_case.c_str(), gecc_strerror(rc)); }

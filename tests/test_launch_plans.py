@@ -150,3 +150,34 @@ def test_workgroups_of_a_repair(plans, shape, batch, per_item):
     for dtype in (0, 1):
         (rc, names), = routes(plans, [("correct",) + shape + (batch, dtype, 0, 0)], "grids")
         assert rc == 0 and [x.split(":")[1] for x in names if "repair_kernel" in x] == [str(per_item * batch)], names
+
+
+def _has(names, what):
+    return [x for x in names if what in x]
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_column_scans_in_vectors_of_either_width(plans, dtype):
+    """The sizes that tests of them use: index weights and explicit ones, in a launch of their own and two in one."""
+    from test_tiles_and_scans import WIDE_SCANS
+    (n, k, m), batch = WIDE_SCANS
+    for shape, b, half in (((n, k, m), batch, 0), ((129, 130, 131), 1, 1), ((260, 300, 16200), 1, 1)):
+        nn, nt, tn = [names for _, names in routes(plans, [("protected",) + shape + (b, dtype) + t for t in ((0, 0), (0, 1), (1, 0))])]
+        if not half:          # (elsewhere the parity scans ride, or the two encodings share a launch)
+            for idxw in (1, 0):
+                assert _has(nn, "coldot_stage1ILi%dELb%dELb0ELb0ELb0E" % (dtype, idxw)), nn
+            assert _has(tn, "scan_pairILi%dELb0ELi2ELb0E" % dtype), tn
+        assert _has(nt, "scan_pairILi%dELb1ELi0ELb%dE" % (dtype, half)) or _has(nt, "scan_pairILi%dELb1ELi1ELb%dE" % (dtype, half)), nt
+        staged = routes(plans, [("encode_a",) + shape + (b, dtype, 0, 0)])[0][1]
+        assert _has(staged, "coldot_stage1ILi%dELb1ELb0E" % dtype) and _has(staged, "ELb%dEEEv" % half), staged
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_bf16_products_that_carry_their_scans(plans, ta, tb):
+    """The sizes that a test of them uses: tiles and ranges (by the workgroups of the product alone), no scan behind the encodings."""
+    from test_tiles_and_scans import BESIDE_CASES
+    for (n, k, m), tile, ranges in BESIDE_CASES:
+        (_, plain), (_, multiply) = routes(plans, [(e, n, k, m, 1, 1, ta, tb) for e in ("plain", "multiply")], "grids")
+        assert not _has(multiply, "dot") and not _has(multiply, "scan") and len(_has(multiply, "gemm_tileILi1E")) == 1, multiply
+        name, grid = plain[-1].split(":")
+        assert "gemm_tileILi1E" in name and "ELi%dEEEv" % tile in name and int(grid) == -(-n // tile) * -(-m // tile) * ranges, plain
