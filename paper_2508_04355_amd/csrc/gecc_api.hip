@@ -72,7 +72,7 @@ void make_layout(gecc_ctx* c) {
 
 // Tile of the product kernel (= granularity of the partial sums), workgroups per tile, and whether the bf16
 // kernel with 256 x 256 tiles may take the product.  All figures: microseconds, product kernel alone.
-struct ProductPlan { int tile, ksplit; bool fast; };
+struct ProductPlan { int tile, ksplit; bool fast, fold; };
 
 // 128 x 128 tiles of a bf16 product, k split so that few compute units idle: the number of ranges with the
 // least (rounds of workgroups) / (ranges), at most 512 workgroups.  0: fewer than 384 workgroups, or
@@ -101,12 +101,13 @@ int ksplit_bf16_128(int64_t t128, int k) {
 //
 // What the ranges of a tile exchange takes 3 to 4 us, so they have to be worth it.  fp32: 128 terms, of few tiles, whose compute
 // units have nothing else to do, fewer (whole calls, ranges of 128 -> 64: 128^3 20.9 -> 20.2, 256^3 23.1 -> 21.7).  bf16 tiles of
-// 64: two workgroups per compute unit and 450 terms; of few tiles two and a half and 128 terms (whole calls, ranges of 450 -> of 128:
+// 64: two workgroups per compute unit and 450 terms (with the sums put aside every so often, where more ranges would have shorter
+// chains: GemmArgs::fold); of few tiles two and a half and 128 terms (whole calls, ranges of 450 -> of 128:
 // 4 tiles, 128 x 896 x 128, 23.5 -> 20.2; 16 tiles, 211 x 447 x 232, 23.5 -> 21.2; 36 tiles 26.4 -> 25.2; 72 tiles, 1152 x 704 x 256,
 // 23.0 -> 24.9; 104 tiles, 256 x 512 x 1664, 21.8 -> 26.3).
 //
 // bf16 tiles of 128 have one chain of sums over their range and no registers for another, so they are not taken where tiles of 64
-// would be but for the time (3440 x 240 x 2496: 34.5 us a call and 8.3e-8 from the fp64 product, tiles of 64 49.0 and 5.6e-8).  Nor are eight
+// would be but for the time (3440 x 240 x 2496: 34.5 us a call and 8.3e-8 from the fp64 product, tiles of 64 49.8 and 6.4e-8).  Nor are eight
 // ranges of them, the most a tile is cut into: tiles of 64 in two or three are both faster and closer (960 x 4352 x 960 NT 54.7 us and
 // 1.43e-7 -> 43.9 and 1.04e-7, 3328 x 4544 x 192 58.5 and 1.44e-7 -> 49.3 and 1.02e-7).
 //
@@ -116,9 +117,11 @@ int ranges_64(int64_t t64, int k, bool few) { return few ? ksplit_of(t64, 512 + 
 ProductPlan plan_tiles(int dtype, int64_t n, int64_t k, int64_t m, int64_t batch, bool narrow = false) {
   const int64_t t128 = ((n + 127) / 128) * ((m + 127) / 128) * batch, t64 = ((n + 63) / 64) * ((m + 63) / 64) * batch;
   const int s_long = dtype == GECC_BF16 ? ksplit_bf16_128(t128, (int)k) : 0;
-  if (s_long > 0 && (s_long < 8 || narrow)) return {128, s_long, false};
-  if (s_long == 0 && t128 >= 256 && k >= 256 && 3 * t128 < t64) return {128, dtype == GECC_F32 && t128 < 512 ? 2 : 1, false};
-  return {64, dtype == GECC_F32 ? ksplit_of(t64, t64 > 256 ? 1024 : 800, (int)k, t64 <= 64 ? 64 : t64 <= 128 ? 96 : 128) : ranges_64(t64, (int)k, narrow || t64 <= 48), false};
+  if (s_long > 0 && (s_long < 8 || narrow)) return {128, s_long, false, false};
+  if (s_long == 0 && t128 >= 256 && k >= 256 && 3 * t128 < t64) return {128, dtype == GECC_F32 && t128 < 512 ? 2 : 1, false, false};
+  if (dtype == GECC_F32) return {64, ksplit_of(t64, t64 > 256 ? 1024 : 800, (int)k, t64 <= 64 ? 64 : t64 <= 128 ? 96 : 128), false, false};
+  const int most = ranges_64(t64, (int)k, true), s = narrow || t64 <= 48 ? most : ranges_64(t64, (int)k, false);
+  return {64, s, false, s < most || s_long > 0};
 }
 
 // bf16 products that the 256 x 256-tile kernel can take.  Times of either kernel, product alone, as fitted to measurements (aligned rows, NN; us): what
@@ -228,7 +231,7 @@ void plan_product(gecc_ctx* c, bool compact) {
   const bool may_be_fast = p.dtype == GECC_BF16 && p.k % 64 == 0 && p.lda % 8 == 0 && p.ldb % 8 == 0 &&
                            (!p.trans_a || p.n % 8 == 0) && (p.trans_b || p.m % 8 == 0) && (int64_t)p.n * p.m >= 256 * 256;
   const int64_t t128 = (int64_t)((p.n + 127) / 128) * ((p.m + 127) / 128) * p.batch;
-  ProductPlan pl = {128, ksplit_128(t128, p.k), true};
+  ProductPlan pl = {128, ksplit_128(t128, p.k), true, false};
   if (blocked(c)) pl.ksplit = 1;
   else if (!compact && !(may_be_fast && (c->cu_hint > 0 || fast_protected(p, c->tile_min))))
     pl = may_be_fast && fast_may_pay(p.n, p.k, p.m, p.batch) ? plan_beside_256(p.n, p.k, p.m, p.batch) : plan_tiles(p.dtype, p.n, p.k, p.m, p.batch);
@@ -236,6 +239,7 @@ void plan_product(gecc_ctx* c, bool compact) {
   c->fast_plain = pl.fast || (may_be_fast && fast_alone(p.n, p.k, p.m, p.batch));
   c->tile_m = c->tile_n = pl.tile;
   c->ksplit = pl.ksplit;
+  c->fold = pl.fold;
   c->fast = pl.fast;
   c->ntm = (p.n + pl.tile - 1) / pl.tile;
   c->ntn = (p.m + pl.tile - 1) / pl.tile;
@@ -533,7 +537,7 @@ GemmArgs gemm_args(const gecc_ctx* c, const void* A, const void* B, float* C) {
   g.n = p.n; g.k = p.k; g.m = p.m; g.batch = p.batch;
   g.lda = p.lda; g.ldb = p.ldb; g.ldc = p.ldc;
   g.sa = p.stride_a; g.sb = p.stride_b; g.sc = p.stride_c;
-  g.tile_m = c->tile_m; g.tile_n = c->tile_n; g.ntm = c->ntm; g.ntn = c->ntn; g.fast = c->fast;
+  g.tile_m = c->tile_m; g.tile_n = c->tile_n; g.ntm = c->ntm; g.ntn = c->ntn; g.fast = c->fast; g.fold = c->fold;
   g.cu_hint = c->cu_hint; g.split_first = -1;
   if (c->ksplit > 1 && c->ws && c->ws_bytes >= c->lay.total) {
     g.ksplit = c->ksplit;
@@ -889,12 +893,13 @@ hipError_t product(gecc_ctx* ctx, ScanQueue& q, const ScanJob* pr, const ScanJob
 void narrow_plan(gecc_ctx* ctx, GemmArgs& g) {
   const gecc_params& p = ctx->p;
   g.rowpart = nullptr; g.colpart = nullptr; g.faults = nullptr; g.n_faults = 0;
-  ProductPlan pl = {128, 1, p.dtype == GECC_BF16 && fast_may_pay(g.n, g.k, g.m, 1)};
+  ProductPlan pl = {128, 1, p.dtype == GECC_BF16 && fast_may_pay(g.n, g.k, g.m, 1), false};
   auto take = [&] {
     g.tile_m = g.tile_n = pl.tile;
     g.ntm = (g.n + pl.tile - 1) / pl.tile;
     g.ntn = (g.m + pl.tile - 1) / pl.tile;
     g.fast = pl.fast;
+    g.fold = pl.fold;
   };
   take();
   if (!gemm_takes_256(g)) {

@@ -75,6 +75,7 @@ struct gecc_ctx {
   int w_cols_a, w_cols_b;  // rows of W_A (2 * pieces * nbi) and of W_B, padded to a multiple of 8
   int tile_op;             // operand whose two reductions share one pass (GECC_MAT_A / GECC_MAT_B)
   int ksplit;              // workgroups per tile of gemm_tile (1: no split)
+  bool fold;               // its sums are put aside every so often (see GemmArgs::fold)
   bool fast;               // bf16: the 256 x 256-tile kernel takes the product where the operands' addresses allow it
   bool fast_plain;         // the same for a product without parities, which has no scans beside it
   int cu_hint;             // GECC_CU_COUNT (tests: plan the tile rounds as for that many CUs), else 0
@@ -261,7 +262,8 @@ struct GemmArgs {
   // leave compute units idle); the last to finish adds their partial tiles up in a fixed order
   int ksplit;           // 0 or 1: off
   int k_per;            // set by the launcher: k range of one workgroup
-  int k_fold;           // set by the launcher, bf16 tiles of 64: terms after which a sum of them is put aside
+  bool fold;            // bf16 tiles of 64: sums are put aside ...
+  int k_fold;           // ... after so many terms (set by the launcher)
   float* split_part;    // [tiles x batch][ksplit][tile_m x tile_n]
   size_t split_bytes;   // what there is room for behind split_part: the launcher refuses a plan that needs more
   uint32_t* split_done; // [tiles x batch] counters, zero between launches (shared with the scans)

@@ -34,6 +34,7 @@
 // Bound there by the fp64 rate or by C's stores: 8192 x k x 8192 through fp64 and through pieces, k = 1 70 against
 // 80 us, k = 8 87 against 89, k = 32 111 against 78.
 #include <cmath>
+#include <type_traits>
 #include "gemm_device.h"
 
 namespace gecc {
@@ -505,8 +506,13 @@ __device__ __forceinline__ void finish_tile(const GemmArgs& a, int b, int tm, in
 // split, tile row, tile column) sequence: tiles that share operand panels share an L2.  The scans are
 // HBM-bound and the product is not: in one launch they cost little more than the
 // product alone, and a launch of their own 2 to 5 us of the stream and 3 of the host beside their time.
-template <int DT, bool KCA, bool KCB, int TILE>
-__global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : DT == GECC_BF16 ? 3 : 2) void gemm_tile(GemmArgs a, GemmSide side) {
+// WHAT: the operands' type, or BF16_FOLD (tiles of 64): the sums of every k_fold terms are put aside, so that the chains of additions are no longer than with
+// more ranges of k (k_fold_of).
+constexpr int BF16_FOLD = GECC_BF16 + 2;
+template <int WHAT, bool KCA, bool KCB, int TILE>
+__global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : WHAT == GECC_BF16 ? 3 : 2) void gemm_tile(GemmArgs a, GemmSide side) {
+  constexpr bool FOLD = WHAT == BF16_FOLD;
+  constexpr int DT = FOLD ? (int)GECC_BF16 : WHAT;
   using T = typename GT<DT>::T;
   constexpr int BK = GT<DT>::BK, PIECES = GT<DT>::PIECES, W = TILE / 2, NI = W / 16;   // W x W per wavefront
   constexpr int PLANE = TILE * BK * 2, OPERAND = PIECES * PLANE;
@@ -556,10 +562,10 @@ __global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : DT == GECC_BF16 ? 3 : 2) 
       for (int v = 0; v < 4; ++v) low[i][j][v] = 0.f;
 
   // 64 x 64: a third set, for shorter chains again.  fp32: the first half of the range (1024^3 in three ranges of k:
-  // 1.10e-7 from the fp64 product with one chain, 8.7e-8 with two; in four ranges with one 9.8e-8).  bf16: what the other two hold is
-  // added to it every k_fold terms (k_fold_of), so that the error does not follow the number of ranges.
-  constexpr bool HALVES = PIECES > 1 && TILE == 64, FOLD = PIECES == 1 && TILE == 64;
-  constexpr int NT = TILE == 64 ? NI : 1;
+  // 1.10e-7 from the fp64 product with one chain, 8.7e-8 with two; in four ranges with one 9.8e-8).  FOLD: what has been put aside.
+  constexpr bool HALVES = PIECES > 1 && TILE == 64;
+  static_assert(!FOLD || (PIECES == 1 && TILE == 64), "bf16 tiles of 64");
+  constexpr int NT = HALVES || FOLD ? NI : 1;
   f32x4_t third[NT][NT];
 #pragma unroll
   for (int i = 0; i < NT; ++i)
@@ -568,14 +574,13 @@ __global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : DT == GECC_BF16 ? 3 : 2) 
 #pragma unroll
       for (int v = 0; v < 4; ++v) third[i][j][v] = 0.f;
   const int k_mid = k_begin + ((k_end - k_begin) / (2 * BK)) * BK;
-  int k_next = k_begin + a.k_fold;
 
   Stager<DT, TILE, KCA, D> sa;
   Stager<DT, TILE, KCB, D> sb;
   sa.init(A, a.lda, tile_r0, a.n, k_end);
   sb.init(B, a.ldb, tile_c0, a.m, k_end);
   const bool once = DT == GECC_F32 && a.k <= BK;       // (then k is not split)
-  const bool is_short = a.k < 16;                      // (a row has no vector then, or a thread no KPT values of k)
+  const bool is_short = !FOLD && a.k < 16;             // (a row has no vector then, or a thread no KPT values of k)
   auto multiply = [&](const char* As, const char* Bs) {
 #pragma unroll
     for (int ks = 0; ks < BK / 32; ++ks) {
@@ -621,43 +626,47 @@ __global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : DT == GECC_BF16 ? 3 : 2) 
 #pragma unroll
     for (int d = 0; d < D; ++d) { sa.load(k_begin + d * BK, d); sb.load(k_begin + d * BK, d); }
     if (once) { sa.fix(k_begin, 0); sb.fix(k_begin, 0); }
-    for (int kt = once ? k_end : k_begin; kt < k_end; kt += D * BK)
+    // With FOLD the loop is left after every k_fold terms (two k-tiles or a multiple, so that the halves of the LDS take turns) and
+    // entered again: behind a test in it the same takes longer (1500 x 1000 x 1100, product alone, 14.7 us for 14.2; without, 13.8).
+    int k_from = once ? k_end : k_begin;
+    do {
+      const int k_to = FOLD ? min(k_end, k_from + a.k_fold) : k_end;
+      for (int kt = k_from; kt < k_to; kt += D * BK)
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-      const int k0 = kt + d * BK;
-      if (d > 0 && k0 >= k_end) break;
-      char* As = smem + (TWICE && (d & 1) ? 2 * OPERAND : 0);
-      char* Bs = As + OPERAND;
-      if (!TWICE) __syncthreads();   // previous tile fully consumed
-      if (k0 + BK > k_end) { sa.fix(k0, d); sb.fix(k0, d); }
-      sa.store(As, d);
-      sb.store(Bs, d);
-      __syncthreads();
-      sa.load(k0 + D * BK, d);
-      sb.load(k0 + D * BK, d);
-      if constexpr (HALVES) {
-        if (k0 == k_mid) {
+      for (int d = 0; d < D; ++d) {
+        const int k0 = kt + d * BK;
+        if (d > 0 && k0 >= k_end) break;
+        char* As = smem + (TWICE && (d & 1) ? 2 * OPERAND : 0);
+        char* Bs = As + OPERAND;
+        if (!TWICE) __syncthreads();   // previous tile fully consumed
+        if (k0 + BK > k_end) { sa.fix(k0, d); sb.fix(k0, d); }
+        sa.store(As, d);
+        sb.store(Bs, d);
+        __syncthreads();
+        sa.load(k0 + D * BK, d);
+        sb.load(k0 + D * BK, d);
+        if constexpr (HALVES) {
+          if (k0 == k_mid) {
 #pragma unroll
-          for (int i = 0; i < NI; ++i)
+            for (int i = 0; i < NI; ++i)
 #pragma unroll
-            for (int j = 0; j < NI; ++j)
+              for (int j = 0; j < NI; ++j)
 #pragma unroll
-              for (int v = 0; v < 4; ++v) { third[i][j][v] = acc[i][j][v]; acc[i][j][v] = 0.f; }
+                for (int v = 0; v < 4; ++v) { third[i][j][v] = acc[i][j][v]; acc[i][j][v] = 0.f; }
+          }
         }
+        multiply(As, Bs);
       }
       if constexpr (FOLD) {
-        if (k0 == k_next) {
-          k_next += a.k_fold;
 #pragma unroll
-          for (int i = 0; i < NI; ++i)
+        for (int i = 0; i < NI; ++i)
 #pragma unroll
-            for (int j = 0; j < NI; ++j)
+          for (int j = 0; j < NI; ++j)
 #pragma unroll
-              for (int v = 0; v < 4; ++v) { third[i][j][v] += acc[i][j][v] + low[i][j][v]; acc[i][j][v] = 0.f; low[i][j][v] = 0.f; }
-        }
+            for (int v = 0; v < 4; ++v) { third[i][j][v] += acc[i][j][v] + low[i][j][v]; acc[i][j][v] = 0.f; low[i][j][v] = 0.f; }
       }
-      multiply(As, Bs);
-    }
+      k_from = k_to;
+    } while (FOLD && k_from < k_end);
   }
 
   if constexpr (TWO) {
@@ -667,7 +676,7 @@ __global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : DT == GECC_BF16 ? 3 : 2) 
       for (int j = 0; j < NI; ++j)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          const float x = TILE == 64 ? third[TILE == 64 ? i : 0][TILE == 64 ? j : 0][v] : 0.f;
+          const float x = third[NT > 1 ? i : 0][NT > 1 ? j : 0][v];
           acc[i][j][v] = HALVES ? (acc[i][j][v] + x) + low[i][j][v] : FOLD ? x + (acc[i][j][v] + low[i][j][v]) : acc[i][j][v] + low[i][j][v];
         }
   }
@@ -856,19 +865,21 @@ __global__ __launch_bounds__(THREADS) void partials_kernel(PartialArgs a) {
 // 34.7 -> 34.1 at 1536 x 1280 x 256).
 template <int DT, int TILE> constexpr int at_once() { return 256 * (TILE == 64 ? 4 : DT == GECC_BF16 ? 3 : 2); }
 
-// bf16 tiles of 64: terms of k after which the accumulators are added to the third set and start anew, for a range of k_per terms.
-// A chain of N additions is off by N^2 / 2 squared last bits (a walk that grows); B pieces with a chain of their sums by
-// N^2 / 2B + NB / 2, least where B is about sqrt(N).  Distance of the product from the fp64 one, in 1e-8 (normal operands):
-//   terms of a piece    64   128   192   256   384   512   no pieces
-//   range of  260      5.9   6.0   6.1   6.8   6.6   6.6    6.6
-//   range of  700      7.6   7.1   7.1   7.3   8.0   8.7   10.5
-//   range of 1000      8.7   7.6   7.7   7.7   8.3   9.3   12.6
-//   range of 2112     11.8   9.9   9.2   9.3   9.6  10.5   19.1
-//   range of 5800     18.0  13.7  12.1  11.3  11.1  11.3   32.9
-// They cost nothing that shows: whole calls of 700^3 24.1 us and of 960 x 5800 x 900 81.2 us with any of them and without.
+// bf16 tiles of 64 in fewer ranges of k than they could have: terms after which the accumulators are added to the third set and start anew, for
+// a range of k_per terms.  A chain of N additions is off by N^2 / 2 squared last bits (a walk that grows); B pieces with a chain of their
+// sums by N^2 / 2B + NB / 2, least where B is about sqrt(N).  Distance of the product from the fp64 one, in 1e-8 (normal operands):
+//   terms of a piece   128   192   256   384   512   no pieces
+//   range of  260      6.0   6.1   6.8   6.6   6.6    6.6
+//   range of  700      7.1   7.1   7.3   8.0   8.7   10.5
+//   range of 1000      7.6   7.7   7.7   8.3   9.3   12.6
+//   range of 2112      9.9   9.2   9.3   9.6  10.5   19.1
+//   range of 5800     13.7  12.1  11.3  11.1  11.3   32.9
+// (700 terms in four ranges 7.1.)  The length does not show in the time, the pieces as such do: 0.4 us of the product at 700^3 and 1500 x 1000 x
+// 1100, so that they are a kernel of their own.
 int k_fold_of(int k_per) {
-  const int pieces = (int)(5.0 * sqrt((double)k_per) / 64.0 + 0.5);
-  return 64 * (pieces > 1 ? pieces : 1);
+  constexpr int STEP = 128;        // (two k-tiles, one to each half of the LDS)
+  const int steps = (int)(5.0 * sqrt((double)k_per) / STEP + 0.5);
+  return STEP * (steps > 1 ? steps : 1);
 }
 
 template <int DT, int TILE>
@@ -882,7 +893,6 @@ hipError_t launch_tile(const GemmArgs& a0, const GemmSide* side0, hipStream_t st
   } else {
     a.ksplit = 1;
   }
-  a.k_fold = k_fold_of(a.ksplit > 1 ? a.k_per : a.k);
   GemmSide side = side0 ? *side0 : GemmSide{};
   side.pg_items = a.pg_out ? a.batch : 0;
   side.blocks = side.pg_items + side.j[0].nblk + side.j[1].nblk;
@@ -898,10 +908,21 @@ hipError_t launch_tile(const GemmArgs& a0, const GemmSide* side0, hipStream_t st
   const dim3 grid((unsigned)grid_all);
   // k-contiguous storage: A when not transposed, B when transposed
   const bool kca = a.trans_a == 0, kcb = a.trans_b != 0;
-  if (kca && kcb)        hipLaunchKernelGGL((gemm_tile<DT, true, true, TILE>), grid, dim3(THREADS), 0, st, a, side);
-  else if (kca && !kcb)  hipLaunchKernelGGL((gemm_tile<DT, true, false, TILE>), grid, dim3(THREADS), 0, st, a, side);
-  else if (!kca && kcb)  hipLaunchKernelGGL((gemm_tile<DT, false, true, TILE>), grid, dim3(THREADS), 0, st, a, side);
-  else                   hipLaunchKernelGGL((gemm_tile<DT, false, false, TILE>), grid, dim3(THREADS), 0, st, a, side);
+  auto launch = [&](auto what) {
+    constexpr int WHAT = decltype(what)::value;
+    if (kca && kcb)        hipLaunchKernelGGL((gemm_tile<WHAT, true, true, TILE>), grid, dim3(THREADS), 0, st, a, side);
+    else if (kca && !kcb)  hipLaunchKernelGGL((gemm_tile<WHAT, true, false, TILE>), grid, dim3(THREADS), 0, st, a, side);
+    else if (!kca && kcb)  hipLaunchKernelGGL((gemm_tile<WHAT, false, true, TILE>), grid, dim3(THREADS), 0, st, a, side);
+    else                   hipLaunchKernelGGL((gemm_tile<WHAT, false, false, TILE>), grid, dim3(THREADS), 0, st, a, side);
+  };
+  if constexpr (DT == GECC_BF16 && TILE == 64) {
+    if (a.fold && a.k >= 16) {
+      a.k_fold = k_fold_of(a.ksplit > 1 ? a.k_per : a.k);
+      launch(std::integral_constant<int, BF16_FOLD>{});
+      return hipGetLastError();
+    }
+  }
+  launch(std::integral_constant<int, DT>{});
   return hipGetLastError();
 }
 

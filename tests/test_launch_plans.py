@@ -181,3 +181,16 @@ def test_bf16_products_that_carry_their_scans(plans, ta, tb):
         assert not _has(multiply, "dot") and not _has(multiply, "scan") and len(_has(multiply, "gemm_tileILi1E")) == 1, multiply
         name, grid = plain[-1].split(":")
         assert "gemm_tileILi1E" in name and "ELi%dEEEv" % tile in name and int(grid) == -(-n // tile) * -(-m // tile) * ranges, plain
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_bf16_products_whose_sums_are_put_aside(plans, ta, tb):
+    """In tiles of 64 with fewer ranges of k than they could have, and in place of eight ranges of tiles of 128; not where the ranges are as many as
+    they can be, nor beside the kernel with one chain over all of k."""
+    from test_tiles_and_scans import FOLD_KS
+    # (NT: aligned where k is a multiple of 64, which the other kernel may be asked about)
+    for n, k, m, folds in [(449, k, 450, True) for k in FOLD_KS if k % 64 > 0 or ta or not tb] + [(700, 700, 700, True), (3329, 4543, 190, True), (1500, 1000, 1100, False),
+                                                                   (128, 896, 640, False), (211, 447, 232, False), (1024, 512, 768, False)]:
+        for entry in ("plain", "multiply"):
+            (_, names), = routes(plans, [(entry, n, k, m, 1, 1, ta, tb)])
+            assert bool(_has(names, "gemm_tileILi3E")) == folds, (n, k, m, names)

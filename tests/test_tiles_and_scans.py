@@ -383,6 +383,19 @@ def test_the_256_tile_kernel_at_sizes_that_gemm_tile_has_taken_over(trans, monke
     H.compare(H.run_gpu(A, B, A, B, cfb, tau, "bf16", trans[0], trans[1]), H.run_oracle(A, B, A, B, cfb, tau), 1e-5, what=str(trans))
 
 
+# bf16 products of 449 x 450 in fewer ranges of k than they could have, whose sums are put aside every 128 or 256 terms
+# (test_launch_plans.py holds them to that kernel): pieces of which the last is a single term, a k-tile, one and a half, a whole one; two ranges
+FOLD_KS = (256, 257, 320, 383, 384, 385, 449, 513, 640, 901, 1100, 2049, 2500)
+
+
+@pytest.mark.parametrize("trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("k", FOLD_KS)
+def test_sums_put_aside(k, trans):
+    A, B = [x[None] for x in inputs.operands(inputs.rng_for(90, k), 449, k, 450, ("normal", 1.0), ("normal", 1.0), "bf16")]
+    _check(_product(A, B, "bf16", trans), A, B)
+    _check(_product(A, B, "bf16", trans, pad=3, shift=1), A, B)
+
+
 @pytest.mark.parametrize("shape,trans,limit", [((700, 700, 700), (0, 0), 7.5e-8), ((128, 896, 640), (0, 0), 7.7e-8), ((1313, 1220, 2578), (0, 0), 1.48e-7),
                                                ((3440, 240, 2496), (1, 1), 6.7e-8), ((2509, 3866, 266), (1, 0), 1.49e-7), ((776, 3240, 1496), (0, 1), 1.47e-7)])
 def test_distance_of_bf16_products_from_fp64(shape, trans, limit):
