@@ -88,6 +88,26 @@ int ksplit_bf16_128(int64_t t128, int k) {
   return best;
 }
 
+// Times of bf16 products in gemm_tile, product alone, as fitted to measurements (aligned rows, NN; us): what a workgroup needs per term of
+// k with as many beside it on its compute unit, and the exchange between s ranges (C goes out and in s times).
+double exchange(int64_t symbols, int s) { return s > 1 ? 1.8e-6 * (double)symbols * s : 0.0; }
+double time_128(int64_t k, int64_t t128, int s) {
+  const int64_t per_cu = (t128 * s + 255) / 256;
+  if (per_cu > 3) return 6.0 + 2e-9 * (double)t128 * 16384.0 * (double)k / 0.66 + exchange(t128 * 16384, s);
+  return 5.4 + (double)k / s * (per_cu == 1 ? 0.0153 : per_cu == 2 ? 0.0175 : 0.0265) + exchange(t128 * 16384, s);
+}
+double time_64(int64_t k, int64_t t64, int s) {
+  const int64_t per_cu = (t64 * s + 255) / 256;
+  return 4.0 + (double)k / s * (per_cu == 1 ? 0.0087 : per_cu == 2 ? 0.0105 : per_cu == 3 ? 0.0135 : 0.0043 * (double)per_cu) + exchange(t64 * 4096, s);
+}
+// the number of ranges with the least time: an exchange of up to 38 MB (the static scratch has 48)
+int ranges_128(int64_t k, int64_t t128) {
+  int best = 1;
+  for (int s = 2; s <= 8 && t128 * s <= 576 && k / s >= 512; ++s)
+    if (time_128(k, t128, s) < time_128(k, t128, best)) best = s;
+  return best;
+}
+
 // 128 x 128 tiles: products with tiles enough for every compute unit, as long as tiles that hang over the
 // edge do not eat up what the larger tile gains (a saturated chip does a 128 x 128 tile in the time of three
 // 64 x 64 ones: fp32, 256 x 512^3, 428 against 568; 64 x 300^3, 61 against 46), and bf16 products of long k
@@ -100,42 +120,38 @@ int ksplit_bf16_128(int64_t t128, int k) {
 // fp32 tiles of 128: two ranges below 512 tiles (2000 x 1000 x 2000: 83, split in two 67).
 //
 // What the ranges of a tile exchange takes 3 to 4 us, so they have to be worth it.  fp32: 128 terms, of few tiles, whose compute
-// units have nothing else to do, fewer (whole calls, ranges of 128 -> 64: 128^3 20.9 -> 20.2, 256^3 23.1 -> 21.7).  bf16 tiles of
-// 64: two workgroups per compute unit and 450 terms (with the sums put aside every so often, where more ranges would have shorter
-// chains: GemmArgs::fold); of few tiles two and a half and 128 terms (whole calls, ranges of 450 -> of 128:
-// 4 tiles, 128 x 896 x 128, 23.5 -> 20.2; 16 tiles, 211 x 447 x 232, 23.5 -> 21.2; 36 tiles 26.4 -> 25.2; 72 tiles, 1152 x 704 x 256,
-// 23.0 -> 24.9; 104 tiles, 256 x 512 x 1664, 21.8 -> 26.3).
+// units have nothing else to do, fewer (whole calls, ranges of 128 -> 64: 128^3 20.9 -> 20.2, 256^3 23.1 -> 21.7).
 //
-// bf16 tiles of 128 have one chain of sums over their range and no registers for another, so they are not taken where tiles of 64
-// would be but for the time (3440 x 240 x 2496: 34.5 us a call and 8.3e-8 from the fp64 product, tiles of 64 49.8 and 6.4e-8).  Nor are eight
-// ranges of them, the most a tile is cut into: tiles of 64 in two or three are both faster and closer (960 x 4352 x 960 NT 54.7 us and
-// 1.43e-7 -> 43.9 and 1.04e-7, 3328 x 4544 x 192 58.5 and 1.44e-7 -> 49.3 and 1.02e-7).
+// bf16 tiles of 64: two workgroups per compute unit and ranges of 450 terms, where that is one range two and a half and 600; up to 20
+// tiles two and a half and 128.  Where ranges of 128 terms would be more, the sums are put aside every so often, which keeps the error (GemmArgs::fold).
+// Whole calls with ranges of 128 terms / with these:
+//   4 tiles     128 x 896 x 128 TT    20.2 / 23.5        104 tiles  256 x 512 x 1664      26.3 / 21.8
+//   16 tiles    211 x 447 x 232       21.2 / 23.5        140 tiles  448 x 920 x 1248 TT   28.6 / 28.2
+//   36 tiles    102 x 1542 x 1096 TT  28.0 / 24.6        270 tiles  916 x 1817 x 1137     44.4 / 44.6 (in one range 47.1)
+//   72 tiles    1152 x 704 x 256      24.9 / 23.0        315 tiles  4017 x 1020 x 282     35.8 / 34.4
+//
+// bf16 tiles of 128 have one chain of sums over their range and no registers for another, so they are not taken where tiles of 64 would
+// be but for the time (3440 x 240 x 2496: 34.5 us a call and 8.3e-8 from the fp64 product, tiles of 64 49.8 and 6.4e-8), nor in fewer
+// ranges.  Tiles of 64 replace them, closer to the fp64 product as well, where the fitted times say so (144 x 3176 x 4952 NT 60.3 ->
+// 52.9), and in place of eight ranges, the most a tile is cut into (960 x 4352 x 960 NT 54.7 -> 43.9, 3328 x 4544 x 192 58.5 -> 49.3).
 //
 // narrow: a side product of blocked mode, a few columns (rows) beside a whole operand; its bf16 ranges are as they were measured, two and
 // a half workgroups and 128 terms.
-int ranges_64(int64_t t64, int k, bool few) { return few ? ksplit_of(t64, 512 + (int)(t64 < 512 ? t64 / 2 : 0), k) : ksplit_of(t64, 512, k, 450); }
+int most_ranges_64(int64_t t64, int k) { return ksplit_of(t64, 512 + (int)(t64 < 512 ? t64 / 2 : 0), k); }
+int ranges_64(int64_t t64, int k) {
+  const int two = ksplit_of(t64, 512, k, 450);
+  return t64 <= 20 ? most_ranges_64(t64, k) : two > 1 ? two : ksplit_of(t64, 512 + (int)(t64 < 512 ? t64 / 2 : 0), k, 600);
+}
 ProductPlan plan_tiles(int dtype, int64_t n, int64_t k, int64_t m, int64_t batch, bool narrow = false) {
   const int64_t t128 = ((n + 127) / 128) * ((m + 127) / 128) * batch, t64 = ((n + 63) / 64) * ((m + 63) / 64) * batch;
   const int s_long = dtype == GECC_BF16 ? ksplit_bf16_128(t128, (int)k) : 0;
-  if (s_long > 0 && (s_long < 8 || narrow)) return {128, s_long, false, false};
+  const int most = most_ranges_64(t64, (int)k), s64 = narrow ? most : ranges_64(t64, (int)k);
+  if (s_long > 0 && (narrow || (s_long < 8 && time_128(k, t128, ranges_128(k, t128)) <= time_64(k, t64, s64)))) return {128, s_long, false, false};
   if (s_long == 0 && t128 >= 256 && k >= 256 && 3 * t128 < t64) return {128, dtype == GECC_F32 && t128 < 512 ? 2 : 1, false, false};
   if (dtype == GECC_F32) return {64, ksplit_of(t64, t64 > 256 ? 1024 : 800, (int)k, t64 <= 64 ? 64 : t64 <= 128 ? 96 : 128), false, false};
-  const int most = ranges_64(t64, (int)k, true), s = narrow || t64 <= 48 ? most : ranges_64(t64, (int)k, false);
-  return {64, s, false, s < most || s_long > 0};
+  return {64, s64, false, s64 < most || s_long > 0};
 }
 
-// bf16 products that the 256 x 256-tile kernel can take.  Times of either kernel, product alone, as fitted to measurements (aligned rows, NN; us): what
-// a workgroup needs per term of k with as many beside it on its compute unit, and the exchange between s ranges (C goes out and in s times).
-double exchange(int64_t symbols, int s) { return s > 1 ? 1.8e-6 * (double)symbols * s : 0.0; }
-double time_128(int64_t k, int64_t t128, int s) {
-  const int64_t per_cu = (t128 * s + 255) / 256;
-  if (per_cu > 3) return 6.0 + 2e-9 * (double)t128 * 16384.0 * (double)k / 0.66 + exchange(t128 * 16384, s);
-  return 5.4 + (double)k / s * (per_cu == 1 ? 0.0153 : per_cu == 2 ? 0.0175 : 0.0265) + exchange(t128 * 16384, s);
-}
-double time_64(int64_t k, int64_t t64, int s) {
-  const int64_t per_cu = (t64 * s + 255) / 256;
-  return 4.0 + (double)k / s * (per_cu == 1 ? 0.0087 : per_cu == 2 ? 0.0105 : per_cu == 3 ? 0.0135 : 0.0043 * (double)per_cu) + exchange(t64 * 4096, s);
-}
 double time_256(int64_t k, int64_t t256) { return 6.0 + (0.0148 + 0.009 * (double)t256 / 256.0) * (double)k; }
 
 // Whether that kernel is worth a thought at all: it needs a workgroup per compute unit to show its rate (1300 TFLOP/s; gemm_tile comes
@@ -154,11 +170,8 @@ bool fast_may_pay(int64_t n, int64_t k, int64_t m, int64_t batch) {
 // 4096 x 2048 94.5 -> 81.4; tiles of 64 -> of 128: 1024^3 28.7 -> 35.5.
 ProductPlan plan_beside_256(int64_t n, int64_t k, int64_t m, int64_t batch) {
   const int64_t t128 = ((n + 127) / 128) * ((m + 127) / 128) * batch, t64 = ((n + 63) / 64) * ((m + 63) / 64) * batch;
-  const int s64 = ranges_64(t64, (int)k, t64 <= 48);
+  const int s64 = ranges_64(t64, (int)k), s128 = ranges_128(k, t128);
   const bool large = t128 >= 256 && k >= 256 && 3 * t128 < t64;
-  int s128 = 1;
-  for (int s = 2; s <= 8 && t128 * s <= 576 && k / s >= 512; ++s)       // (an exchange of up to 38 MB: the static scratch has 48)
-    if (time_128(k, t128, s) < time_128(k, t128, s128)) s128 = s;
   if (large || (t128 <= 576 && time_128(k, t128, s128) < time_64(k, t64, s64))) return {128, s128, false};
   return {64, s64, false};
 }

@@ -372,13 +372,27 @@ __device__ __forceinline__ bool add_splits(const GemmArgs& a, int b, int tm, int
   for (int i = 0; i < NI; ++i)
 #pragma unroll
     for (int j = 0; j < NI; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  auto load = [&](int q, int at_ij) { return __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(part, at + at_ij * THREADS * 16, q * TILE * TILE * 4, DEV)); };
+  // (tiles of 64: two ranges at a time, which halves the chain of additions)
+  int q = 0;
+  if constexpr (TILE == 64)
 #pragma unroll 2
-  for (int q = 0; q < S; ++q)
+    for (; q + 1 < S; q += 2)
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+          const f32x4_t x = load(q, i * NI + j), y = load(q + 1, i * NI + j);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) acc[i][j][v] += x[v] + y[v];
+        }
+#pragma unroll 2
+  for (; q < S; ++q)
 #pragma unroll
     for (int i = 0; i < NI; ++i)
 #pragma unroll
       for (int j = 0; j < NI; ++j) {
-        const f32x4_t x = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(part, at + (i * NI + j) * THREADS * 16, q * TILE * TILE * 4, DEV));
+        const f32x4_t x = load(q, i * NI + j);
 #pragma unroll
         for (int v = 0; v < 4; ++v) acc[i][j][v] += x[v];
       }
@@ -581,7 +595,10 @@ __global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : WHAT == GECC_BF16 ? 3 : 2
   sb.init(B, a.ldb, tile_c0, a.m, k_end);
   const bool once = DT == GECC_F32 && a.k <= BK;       // (then k is not split)
   const bool is_short = !FOLD && a.k < 16;             // (a row has no vector then, or a thread no KPT values of k)
-  auto multiply = [&](const char* As, const char* Bs) {
+  // fresh: whether the sums start anew with this k-tile
+  auto multiply = [&](const char* As, const char* Bs, auto fresh) {
+    constexpr bool NEW = decltype(fresh)::value;
+    static_assert(!NEW || BK == 64, "one step of either set");
 #pragma unroll
     for (int ks = 0; ks < BK / 32; ++ks) {
       bf16x8_t fb[NI][PIECES];
@@ -607,7 +624,7 @@ __global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : WHAT == GECC_BF16 ? 3 : 2
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
           f32x4_t& sum = PIECES == 1 && TWO && (ks & 1) ? low[i][j] : acc[i][j];
-          sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[0], fb[j][0], sum, 0, 0, 0);
+          sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[0], fb[j][0], NEW ? f32x4_t{0.f, 0.f, 0.f, 0.f} : sum, 0, 0, 0);
         }
       }
     }
@@ -620,53 +637,70 @@ __global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : WHAT == GECC_BF16 ? 3 : 2
       sa.store(smem, 0);
       sb.store(smem + OPERAND, 0);
       __syncthreads();
-      multiply(smem, smem + OPERAND);
+      multiply(smem, smem + OPERAND, std::false_type{});
     }
   } else {
 #pragma unroll
     for (int d = 0; d < D; ++d) { sa.load(k_begin + d * BK, d); sb.load(k_begin + d * BK, d); }
     if (once) { sa.fix(k_begin, 0); sb.fix(k_begin, 0); }
-    // With FOLD the loop is left after every k_fold terms (two k-tiles or a multiple, so that the halves of the LDS take turns) and
-    // entered again: behind a test in it the same takes longer (1500 x 1000 x 1100, product alone, 14.7 us for 14.2; without, 13.8).
-    int k_from = once ? k_end : k_begin;
-    do {
-      const int k_to = FOLD ? min(k_end, k_from + a.k_fold) : k_end;
-      for (int kt = k_from; kt < k_to; kt += D * BK)
-#pragma unroll
-      for (int d = 0; d < D; ++d) {
-        const int k0 = kt + d * BK;
-        if (d > 0 && k0 >= k_end) break;
-        char* As = smem + (TWICE && (d & 1) ? 2 * OPERAND : 0);
-        char* Bs = As + OPERAND;
-        if (!TWICE) __syncthreads();   // previous tile fully consumed
+    if constexpr (FOLD) {
+      // (a k-tile, in half d of the LDS; fresh: the first of a piece)
+      auto tile = [&](int k0, auto half, auto fresh) {
+        constexpr int d = decltype(half)::value;
+        char* As = smem + d * 2 * OPERAND;
         if (k0 + BK > k_end) { sa.fix(k0, d); sb.fix(k0, d); }
         sa.store(As, d);
-        sb.store(Bs, d);
+        sb.store(As + OPERAND, d);
         __syncthreads();
         sa.load(k0 + D * BK, d);
         sb.load(k0 + D * BK, d);
-        if constexpr (HALVES) {
-          if (k0 == k_mid) {
-#pragma unroll
-            for (int i = 0; i < NI; ++i)
-#pragma unroll
-              for (int j = 0; j < NI; ++j)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) { third[i][j][v] = acc[i][j][v]; acc[i][j][v] = 0.f; }
-          }
+        multiply(As, As + OPERAND, fresh);
+      };
+      const std::integral_constant<int, 0> even{};
+      const std::integral_constant<int, 1> odd{};
+      for (int k1 = k_begin; k1 < k_end; k1 += a.k_fold) {
+        const int k_to = min(k_end, k1 + a.k_fold);
+        tile(k1, even, std::true_type{});
+        if (k1 + BK < k_to) tile(k1 + BK, odd, std::false_type{});
+        for (int kt = k1 + 2 * BK; kt < k_to; kt += 2 * BK) {
+          tile(kt, even, std::false_type{});
+          if (kt + BK < k_to) tile(kt + BK, odd, std::false_type{});
         }
-        multiply(As, Bs);
-      }
-      if constexpr (FOLD) {
 #pragma unroll
         for (int i = 0; i < NI; ++i)
 #pragma unroll
           for (int j = 0; j < NI; ++j)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) { third[i][j][v] += acc[i][j][v] + low[i][j][v]; acc[i][j][v] = 0.f; low[i][j][v] = 0.f; }
+            for (int v = 0; v < 4; ++v) third[i][j][v] += acc[i][j][v] + low[i][j][v];
       }
-      k_from = k_to;
-    } while (FOLD && k_from < k_end);
+    } else {
+    for (int kt = once ? k_end : k_begin; kt < k_end; kt += D * BK)
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      const int k0 = kt + d * BK;
+      if (d > 0 && k0 >= k_end) break;
+      char* As = smem + (TWICE && (d & 1) ? 2 * OPERAND : 0);
+      char* Bs = As + OPERAND;
+      if (!TWICE) __syncthreads();   // previous tile fully consumed
+      if (k0 + BK > k_end) { sa.fix(k0, d); sb.fix(k0, d); }
+      sa.store(As, d);
+      sb.store(Bs, d);
+      __syncthreads();
+      sa.load(k0 + D * BK, d);
+      sb.load(k0 + D * BK, d);
+      if constexpr (HALVES) {
+        if (k0 == k_mid) {
+#pragma unroll
+          for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+#pragma unroll
+              for (int v = 0; v < 4; ++v) { third[i][j][v] = acc[i][j][v]; acc[i][j][v] = 0.f; }
+        }
+      }
+      multiply(As, Bs, std::false_type{});
+    }
+    }
   }
 
   if constexpr (TWO) {
@@ -677,7 +711,7 @@ __global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : WHAT == GECC_BF16 ? 3 : 2
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const float x = third[NT > 1 ? i : 0][NT > 1 ? j : 0][v];
-          acc[i][j][v] = HALVES ? (acc[i][j][v] + x) + low[i][j][v] : FOLD ? x + (acc[i][j][v] + low[i][j][v]) : acc[i][j][v] + low[i][j][v];
+          acc[i][j][v] = HALVES ? (acc[i][j][v] + x) + low[i][j][v] : FOLD ? x : acc[i][j][v] + low[i][j][v];
         }
   }
   if constexpr (DT == GECC_F32) {
@@ -874,8 +908,9 @@ template <int DT, int TILE> constexpr int at_once() { return 256 * (TILE == 64 ?
 //   range of 1000      7.6   7.7   7.7   8.3   9.3   12.6
 //   range of 2112      9.9   9.2   9.3   9.6  10.5   19.1
 //   range of 5800     13.7  12.1  11.3  11.1  11.3   32.9
-// (700 terms in four ranges 7.1.)  The length does not show in the time, the pieces as such do: 0.4 us of the product at 700^3 and 1500 x 1000 x
-// 1100, so that they are a kernel of their own.
+// (700 terms in four ranges 7.1.)  Products alone, pieces of 128, 256, 384 terms / in the kernel without pieces: 700^3 8.9, 8.7, 8.6 / 8.8 us,
+// 3976 x 456 x 176 TN 8.8, 8.5, 8.5 / 8.7, 2056 x 664 x 168 8.8, 8.7, 8.6 / 8.7.  (With the sums set to zero, and not begun by a product that adds
+// nothing, pieces of 128 terms 9.6 at 700^3.)  A kernel of its own all the same: the loop twice is more code than most products need.
 int k_fold_of(int k_per) {
   constexpr int STEP = 128;        // (two k-tiles, one to each half of the LDS)
   const int steps = (int)(5.0 * sqrt((double)k_per) / STEP + 0.5);

@@ -347,7 +347,7 @@ def test_column_scans_of_many_workgroups_at_their_ends(trans, dtype, staged):
 
 
 # (test_launch_plans.py holds them to the tiles and ranges, and to the scans in the product's launch)
-BESIDE_CASES = [((1020, 1540, 2040), 128, 3),       # 128 x 128 tiles, three ranges of k
+BESIDE_CASES = [((1530, 4222, 760), 128, 7),        # 128 x 128 tiles, seven ranges of k
                 ((1300, 1750, 1211), 64, 1),        # scans behind the product's workgroups
                 ((256, 64, 256), 64, 1)]            # the smallest that the 256 x 256-tile kernel could take
 
@@ -396,15 +396,18 @@ def test_sums_put_aside(k, trans):
     _check(_product(A, B, "bf16", trans, pad=3, shift=1), A, B)
 
 
-@pytest.mark.parametrize("shape,trans,limit", [((700, 700, 700), (0, 0), 7.5e-8), ((128, 896, 640), (0, 0), 7.7e-8), ((1313, 1220, 2578), (0, 0), 1.48e-7),
-                                               ((3440, 240, 2496), (1, 1), 6.7e-8), ((2509, 3866, 266), (1, 0), 1.49e-7), ((776, 3240, 1496), (0, 1), 1.47e-7)])
-def test_distance_of_bf16_products_from_fp64(shape, trans, limit):
-    """What the order of a product's sums leaves, as |C - C64| / |C64| in 2-norms: with the whole range of k in as few chains as tiles and
-    ranges alone would give, these are 1.05e-7, 1.19e-7, 2.04e-7, 8.3e-8, 1.83e-7 and 1.52e-7.  The limits are 5 % above 7.1e-8, 7.3e-8,
-    1.41e-7, 6.4e-8, 1.42e-7 and 1.40e-7, the distances of plans with more ranges; over 80 000 symbols and more it varies by less than 1 %."""
+@pytest.mark.parametrize("dtype,shape,trans,limit", [("bf16", (700, 700, 700), (0, 0), 7.5e-8), ("bf16", (128, 896, 640), (0, 0), 7.7e-8),
+                                                     ("bf16", (1313, 1220, 2578), (0, 0), 1.48e-7), ("bf16", (3440, 240, 2496), (1, 1), 6.7e-8),
+                                                     ("bf16", (2509, 3866, 266), (1, 0), 1.49e-7), ("bf16", (776, 3240, 1496), (0, 1), 1.47e-7),
+                                                     ("f32", (256, 512, 256), (0, 0), 7.05e-8), ("f32", (512, 512, 512), (0, 0), 7.1e-8)])
+def test_distance_from_fp64(dtype, shape, trans, limit):
+    """What the order of a product's sums leaves, as |C - C64| / |C64| in 2-norms.  With the whole range of k in as few chains as tiles and
+    ranges alone would give, the bf16 ones are 1.05e-7, 1.19e-7, 2.04e-7, 8.3e-8, 1.83e-7 and 1.52e-7; their limits are 5 % above 7.1e-8, 7.3e-8,
+    1.41e-7, 6.4e-8, 1.42e-7 and 1.40e-7, the distances of plans with more ranges.  fp32 in eight ranges that are added up one by one: 7.27e-8
+    and 7.31e-8, in four 6.92e-8 and 7.00e-8.  Over 65 000 symbols and more all of this varies by less than 1 %."""
     n, k, m = shape
-    A, B = [x[None] for x in inputs.operands(inputs.rng_for(87, n), n, k, m, ("normal", 1.0), ("normal", 1.0), "bf16")]
-    C = _product(A, B, "bf16", trans)
+    A, B = [x[None] for x in inputs.operands(inputs.rng_for(87, n), n, k, m, ("normal", 1.0), ("normal", 1.0), dtype)]
+    C = _product(A, B, dtype, trans)
     _check(C, A, B)
     ref = A.astype(np.float64) @ B.astype(np.float64)
     assert np.linalg.norm(C - ref) <= limit * np.linalg.norm(ref)
