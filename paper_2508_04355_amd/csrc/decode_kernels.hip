@@ -678,13 +678,16 @@ __device__ void sort_hits(AuditHit* h, int cnt) {
 // A hits first, using B as the product read it; then columns of the B hits, using the
 // corrected A.
 //
-// Several workgroups share an item: each owns a slice of the columns (threads 0 .. RP_LINES - 1) and a slice of the
-// rows (the others), finds the hits for itself and takes every hit's footprint out of its own lines.  A column of
-// C or of A is a line of memory per row, and one compute unit keeps a few dozen of them on their way.  Between event pairs, one
-// workgroup -> sixteen at 4096^3 bf16: an error of A 28.3 -> 20.5 us, of B 49.4 -> 21.5, of both 53.3 -> 24.4; 256 items of 512^3
-// fp32 keep one workgroup each, 35.6 -> 32.0, since a load then waits for another and not for its turn.  What is left is that chain,
-// and where a symbol of C is evaluated again the 4096 lines of a column of B by one compute unit (15 us).  What concerns a hit's own line (its sums over all slices) and the symbols where the row of an A hit meets the
-// column of a B hit is left to the workgroup that comes last; it also puts the operands right, which the others read until then.
+// Several workgroups share an item (how many: repair_wgs): each owns a slice of the columns (threads 0 .. RP_LINES - 1)
+// and a slice of the rows (the others), finds the hits for itself and takes every hit's footprint out of its own lines.
+// What concerns a hit's own line (its sums over all slices) and the symbols where the row of an A hit meets the column
+// of a B hit is left to the workgroup that comes last; it also puts the operands right, which the others read until then.
+//
+// What bounds it: a column of C or of A is a line of memory per row, and one compute unit keeps a few dozen of them on
+// their way.  Between event pairs, one workgroup -> sixteen at 4096^3 bf16: an error of A 28.3 -> 20.5 us, of B
+// 49.4 -> 21.5, of both 53.3 -> 24.4; 256 items of 512^3 fp32 keep one workgroup each, 35.6 -> 32.0, since a load then
+// waits for another and not for its turn.  What is left is that chain, and where a symbol of C is evaluated again the
+// 4096 lines of a column of B by one compute unit (15 us).
 constexpr int RP_LINES = 256;
 constexpr int RP_THREADS = 2 * RP_LINES;
 constexpr int RP_WGS = 64;         // workgroups of an item, at most

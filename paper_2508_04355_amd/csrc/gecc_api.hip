@@ -88,8 +88,9 @@ int ksplit_bf16_128(int64_t t128, int k) {
   return best;
 }
 
-// Times of bf16 products in gemm_tile, product alone, as fitted to measurements (aligned rows, NN; us): what a workgroup needs per term of
-// k with as many beside it on its compute unit, and the exchange between s ranges (C goes out and in s times).
+// Times of bf16 products in gemm_tile, product alone, as fitted to measurements (aligned rows, NN; us): what a
+// workgroup needs per term of k with as many beside it on its compute unit, and the exchange between s ranges (C goes
+// out and in s times).
 double exchange(int64_t symbols, int s) { return s > 1 ? 1.8e-6 * (double)symbols * s : 0.0; }
 double time_128(int64_t k, int64_t t128, int s) {
   const int64_t per_cu = (t128 * s + 255) / 256;
@@ -98,7 +99,8 @@ double time_128(int64_t k, int64_t t128, int s) {
 }
 double time_64(int64_t k, int64_t t64, int s) {
   const int64_t per_cu = (t64 * s + 255) / 256;
-  return 4.0 + (double)k / s * (per_cu == 1 ? 0.0087 : per_cu == 2 ? 0.0105 : per_cu == 3 ? 0.0135 : 0.0043 * (double)per_cu) + exchange(t64 * 4096, s);
+  const double per_term = per_cu == 1 ? 0.0087 : per_cu == 2 ? 0.0105 : per_cu == 3 ? 0.0135 : 0.0043 * (double)per_cu;
+  return 4.0 + (double)k / s * per_term + exchange(t64 * 4096, s);
 }
 // the number of ranges with the least time: an exchange of up to 38 MB (the static scratch has 48)
 int ranges_128(int64_t k, int64_t t128) {
@@ -108,66 +110,77 @@ int ranges_128(int64_t k, int64_t t128) {
   return best;
 }
 
-// 128 x 128 tiles: products with tiles enough for every compute unit, as long as tiles that hang over the
-// edge do not eat up what the larger tile gains (a saturated chip does a 128 x 128 tile in the time of three
-// 64 x 64 ones: fp32, 256 x 512^3, 428 against 568; 64 x 300^3, 61 against 46), and bf16 products of long k
-// (1536 x 4224 x 768: 36 against 39, 16384 x 4096 x 88: 41 against 52).  64 x 64 tiles: the rest (fp32
-// 1024^3 28 against 37, 128^3 7.7 against 13.8; bf16 1500 x 1000 x 1100 19.5 against 28).
+// 128 x 128 tiles: products with tiles enough for every compute unit, as long as tiles that hang over the edge do not
+// eat up what the larger tile gains (a saturated chip does a 128 x 128 tile in the time of three 64 x 64 ones), and
+// bf16 products of long k.  64 x 64 tiles: the rest.  Products alone, us, tiles of 64 (ranges of k) / of 128:
+//   fp32  128^3          7.2  / 13.1              bf16  1500 x 1000 x 1100       14.1 / 21.6
+//         1024^3         25.7 (3) / 34.2 (4)            16384 x 4096 x 88        39.9 (2) / 38.8 (4)
+//         64 x 300^3     42.0 / 60.3              whole call 1536 x 4224 x 768   53.1 (2) / 50.9 (7)
+//         256 x 512^3    536  / 400 (gemm_f32_wide)
 //
-// Workgroups of fp32 tiles of 64: four per compute unit keep it busy (1024^3: one workgroup per tile 40, two 31, four 28, eight
-// 38); up to one tile per compute unit three are enough, and leave the fourth place to the scans that ride along (whole calls at
-// 1024, 800 and 512 workgroups: 1024^3 48.4, 44.9 and 47.1; with more tiles 800 are too few, 1300^3, 441 tiles, 74.0 and 80.9).
-// fp32 tiles of 128: two ranges below 512 tiles (2000 x 1000 x 2000: 83, split in two 67).
+// Workgroups of fp32 tiles of 64: four per compute unit keep it busy (1024^3, when it took 28 us: one workgroup per
+// tile 40, two 31, four 28, eight 38); up to one tile per compute unit three are enough, and leave the fourth place to
+// the scans that ride along (whole calls at 800 and 1024 workgroups: 1024^3 40.2 and 41.5; with more tiles 800 are too
+// few, 1300^3, 441 tiles in one range 72.2, in two 65.1).  fp32 tiles of 128: two ranges below 512 tiles (whole call
+// 2000 x 1000 x 2000: one 106.7, two 83.1).
 //
-// What the ranges of a tile exchange takes 3 to 4 us, so they have to be worth it.  fp32: 128 terms, of few tiles, whose compute
-// units have nothing else to do, fewer (whole calls, ranges of 128 -> 64: 128^3 20.9 -> 20.2, 256^3 23.1 -> 21.7).
+// What the ranges of a tile exchange takes 3 to 4 us, so they have to be worth it.  fp32: 128 terms, of few tiles,
+// whose compute units have nothing else to do, fewer (whole calls, ranges of 128 -> 64: 128^3 20.9 -> 20.2, 256^3
+// 23.1 -> 21.7).
 //
-// bf16 tiles of 64: two workgroups per compute unit and ranges of 450 terms, where that is one range two and a half and 600; up to 20
-// tiles two and a half and 128.  Where ranges of 128 terms would be more, the sums are put aside every so often, which keeps the error (GemmArgs::fold).
-// Whole calls with ranges of 128 terms / with these:
-//   4 tiles     128 x 896 x 128 TT    20.2 / 23.5        104 tiles  256 x 512 x 1664      26.3 / 21.8
-//   16 tiles    211 x 447 x 232       21.2 / 23.5        140 tiles  448 x 920 x 1248 TT   28.6 / 28.2
-//   36 tiles    102 x 1542 x 1096 TT  28.0 / 24.6        270 tiles  916 x 1817 x 1137     44.4 / 44.6 (in one range 47.1)
-//   72 tiles    1152 x 704 x 256      24.9 / 23.0        315 tiles  4017 x 1020 x 282     35.8 / 34.4
+// bf16 tiles of 64: two workgroups per compute unit and ranges of 450 terms, where that is one range two and a half
+// and 600; up to 20 tiles two and a half and 128.  Where ranges of 128 terms would be more, the sums are put aside
+// every so often, which keeps the error (GemmArgs::fold).  Whole calls with ranges of 128 terms / with these:
+//   36 tiles    102 x 1542 x 1096 TT  28.5 / 25.6        140 tiles  448 x 920 x 1248 TT   28.7 / 26.6
+//   72 tiles    1152 x 704 x 256      24.9 / 22.7        270 tiles  916 x 1817 x 1137     44.4 (in one range 46.9)
+//   104 tiles   256 x 512 x 1664      26.6 / 21.2        315 tiles  4017 x 1020 x 282     35.3 / 34.3
+// and up to 20 tiles, with 450 terms / with these: 128 x 896 x 128 TT 20.7 / 19.7, 211 x 447 x 232 21.1 / 21.0.
 //
-// bf16 tiles of 128 have one chain of sums over their range and no registers for another, so they are not taken where tiles of 64 would
-// be but for the time (3440 x 240 x 2496: 34.5 us a call and 8.3e-8 from the fp64 product, tiles of 64 49.8 and 6.4e-8), nor in fewer
-// ranges.  Tiles of 64 replace them, closer to the fp64 product as well, where the fitted times say so (144 x 3176 x 4952 NT 60.3 ->
-// 52.9), and in place of eight ranges, the most a tile is cut into (960 x 4352 x 960 NT 54.7 -> 43.9, 3328 x 4544 x 192 58.5 -> 49.3).
+// bf16 tiles of 128 have one chain of sums over their range and no registers for another, so they are not taken where
+// tiles of 64 would be but for the time (3440 x 240 x 2496: 34.5 us a call and 8.3e-8 from the fp64 product, tiles of
+// 64 49.8 and 6.4e-8), nor in fewer ranges.  Tiles of 64 replace them, closer to the fp64 product as well, where the
+// fitted times say so (144 x 3176 x 4952 NT 60.3 -> 52.9), and in place of eight ranges, the most a tile is cut into
+// (960 x 4352 x 960 NT 54.7 -> 43.9, 3328 x 4544 x 192 58.5 -> 49.3).
 //
-// narrow: a side product of blocked mode, a few columns (rows) beside a whole operand; its bf16 ranges are as they were measured, two and
-// a half workgroups and 128 terms.
+// narrow: a side product of blocked mode, a few columns (rows) beside a whole operand; its bf16 ranges are as they were
+// measured, two and a half workgroups and 128 terms.
 int most_ranges_64(int64_t t64, int k) { return ksplit_of(t64, 512 + (int)(t64 < 512 ? t64 / 2 : 0), k); }
 int ranges_64(int64_t t64, int k) {
+  if (t64 <= 20) return most_ranges_64(t64, k);
   const int two = ksplit_of(t64, 512, k, 450);
-  return t64 <= 20 ? most_ranges_64(t64, k) : two > 1 ? two : ksplit_of(t64, 512 + (int)(t64 < 512 ? t64 / 2 : 0), k, 600);
+  return two > 1 ? two : ksplit_of(t64, 512 + (int)(t64 < 512 ? t64 / 2 : 0), k, 600);
 }
 ProductPlan plan_tiles(int dtype, int64_t n, int64_t k, int64_t m, int64_t batch, bool narrow = false) {
   const int64_t t128 = ((n + 127) / 128) * ((m + 127) / 128) * batch, t64 = ((n + 63) / 64) * ((m + 63) / 64) * batch;
+  const bool many = t128 >= 256 && k >= 256 && 3 * t128 < t64;
   const int s_long = dtype == GECC_BF16 ? ksplit_bf16_128(t128, (int)k) : 0;
   const int most = most_ranges_64(t64, (int)k), s64 = narrow ? most : ranges_64(t64, (int)k);
-  if (s_long > 0 && (narrow || (s_long < 8 && time_128(k, t128, ranges_128(k, t128)) <= time_64(k, t64, s64)))) return {128, s_long, false, false};
-  if (s_long == 0 && t128 >= 256 && k >= 256 && 3 * t128 < t64) return {128, dtype == GECC_F32 && t128 < 512 ? 2 : 1, false, false};
-  if (dtype == GECC_F32) return {64, ksplit_of(t64, t64 > 256 ? 1024 : 800, (int)k, t64 <= 64 ? 64 : t64 <= 128 ? 96 : 128), false, false};
+  if (s_long > 0 && (narrow || (s_long < 8 && time_128(k, t128, ranges_128(k, t128)) <= time_64(k, t64, s64))))
+    return {128, s_long, false, false};
+  if (s_long == 0 && many) return {128, dtype == GECC_F32 && t128 < 512 ? 2 : 1, false, false};
+  if (dtype == GECC_F32)
+    return {64, ksplit_of(t64, t64 > 256 ? 1024 : 800, (int)k, t64 <= 64 ? 64 : t64 <= 128 ? 96 : 128), false, false};
   return {64, s64, false, s64 < most || s_long > 0};
 }
 
 double time_256(int64_t k, int64_t t256) { return 6.0 + (0.0148 + 0.009 * (double)t256 / 256.0) * (double)k; }
 
-// Whether that kernel is worth a thought at all: it needs a workgroup per compute unit to show its rate (1300 TFLOP/s; gemm_tile comes
-// to 660), and has no k-split for fewer tiles.
+// Whether the 256 x 256-tile kernel is worth a thought at all: it needs a workgroup per compute unit to show its rate
+// (1300 TFLOP/s; gemm_tile comes to 660), and has no k-split for fewer tiles.
 bool fast_may_pay(int64_t n, int64_t k, int64_t m, int64_t batch) {
   const int64_t t256 = ((n + 255) / 256) * ((m + 255) / 256) * batch;
   if (t256 > 128) return true;
   const ProductPlan g = plan_tiles(GECC_BF16, n, k, m, batch, true);
-  const double gf = 2e-9 * (double)((n + g.tile - 1) / g.tile * g.tile) * (double)k * (double)((m + g.tile - 1) / g.tile * g.tile) * (double)batch;
-  const double t_gen = g.tile == 64 ? 6.0 + gf / 0.33 + 0.006 * (double)(k / g.ksplit) : 8.0 + gf / 0.42, t_fast = time_256(k, t256);
+  const int64_t rows = (n + g.tile - 1) / g.tile * g.tile, cols = (m + g.tile - 1) / g.tile * g.tile;
+  const double gf = 2e-9 * (double)rows * (double)k * (double)cols * (double)batch;
+  const double t_gen = g.tile == 64 ? 6.0 + gf / 0.33 + 0.006 * (double)(k / g.ksplit) : 8.0 + gf / 0.42;
+  const double t_fast = time_256(k, t256);
   // (by less than that the fit cannot tell them apart)
   return t_fast - t_gen < 5.0 || t_gen > 0.85 * t_fast;
 }
-// gemm_tile's plan for a product of which that is so: whichever tile and ranges the fitted times say.  (The other kernel has one chain of sums
-// over all of k: none of these is longer.)  Whole calls, one range of 128 x 128 tiles -> two: 2048 x 1024 x 2048 38.5 -> 44.3, 2048 x
-// 4096 x 2048 94.5 -> 81.4; tiles of 64 -> of 128: 1024^3 28.7 -> 35.5.
+// gemm_tile's plan for a product of which that is so: whichever tile and ranges the fitted times say.  (The other
+// kernel has one chain of sums over all of k: none of these is longer.)  Whole calls, one range of 128 x 128 tiles ->
+// two: 2048 x 1024 x 2048 38.5 -> 44.3, 2048 x 4096 x 2048 94.5 -> 81.4; tiles of 64 -> of 128: 1024^3 28.7 -> 35.5.
 ProductPlan plan_beside_256(int64_t n, int64_t k, int64_t m, int64_t batch) {
   const int64_t t128 = ((n + 127) / 128) * ((m + 127) / 128) * batch, t64 = ((n + 63) / 64) * ((m + 63) / 64) * batch;
   const int s64 = ranges_64(t64, (int)k), s128 = ranges_128(k, t128);
@@ -175,22 +188,26 @@ ProductPlan plan_beside_256(int64_t n, int64_t k, int64_t m, int64_t batch) {
   if (large || (t128 <= 576 && time_128(k, t128, s128) < time_64(k, t64, s64))) return {128, s128, false};
   return {64, s64, false};
 }
-// bonus: what gemm_tile saves a protected product beyond its own time (fast_protected).  Whole calls, 256 x 256 tiles -> gemm_tile (product alone): 2048^3 72.0 -> 56.5 us (38.3 -> 36.6), 2048 x 1024 x
-// 2048 54.9 -> 39.2 (23.4 -> 21.1), 2816 x 704 x 2816 51.2 -> 38.4 (19.7 -> 21.4), 4096 x 512 x 2048 49.4 -> 35.3 (18.2 -> 18.1), 2560^3 84.3 -> 76.4
-// (46.0 -> 52.4), 3072 x 1024 x 3072 57.1 -> 50.3 (26.0 -> 34.2), 1280 x 7296 x 2304 171.6 -> 109.8 (113 -> 73.7), 1024 x 4096 x 4096 NT 109.0 -> 80.2; 3584 x 1536
-// x 2560 67.8 -> 67.6 and 3072 x 2048 x 3072 76.7 -> 81.6 stand on either side of the line.
 double time_of(const ProductPlan& g, int64_t n, int64_t k, int64_t m, int64_t batch) {
   const int64_t tiles = ((n + g.tile - 1) / g.tile) * ((m + g.tile - 1) / g.tile) * batch;
   return g.tile == 128 ? time_128(k, tiles, g.ksplit) : time_64(k, tiles, g.ksplit);
 }
+// bonus: what gemm_tile saves a protected product beyond its own time (fast_protected).  Whole calls, us, 256 x 256
+// tiles -> gemm_tile (product alone):
+//   2048 x 1024 x 2048   54.9 -> 39.2  (23.4 -> 21.1)      2560^3               84.3 -> 76.4  (46.0 -> 52.4)
+//   2048^3               72.0 -> 56.5  (38.3 -> 36.6)      3072 x 1024 x 3072   57.1 -> 50.3  (26.0 -> 34.2)
+//   2816 x 704 x 2816    51.2 -> 38.4  (19.7 -> 21.4)      1280 x 7296 x 2304   171.6 -> 109.8 (113 -> 73.7)
+//   4096 x 512 x 2048    49.4 -> 35.3  (18.2 -> 18.1)      1024 x 4096 x 4096 NT 109.0 -> 80.2
+// and on either side of the line 3584 x 1536 x 2560 67.8 -> 67.6, 3072 x 2048 x 3072 76.7 -> 81.6.
 bool fast_pays(int64_t n, int64_t k, int64_t m, int64_t batch, double bonus) {
   const int64_t t256 = ((n + 255) / 256) * ((m + 255) / 256) * batch;
   if (t256 > 256) return true;
   return fast_may_pay(n, k, m, batch) && time_256(k, t256) + bonus < time_of(plan_beside_256(n, k, m, batch), n, k, m, batch);
 }
-// The same for a product on its own.  Beside tiles of 64 the fit is good to a tenth (256 x 256 tiles / tiles of 64, measured: 1000 x 512 x 776
-// 14.7 / 8.0, 776 x 2048 x 1032 36.9 / 17.1, 1504 x 1024 x 1504 21.8 / 17.7, 4096 x 192 x 4096 18.4 / 23.0, 3072 x 128 x 4096 13.8 / 16.0); beside tiles of 128 they
-// have to be a quarter apart, for what it does not know (2560^3 46.0 / 52.4 where it says 52.9 / 50.2).
+// The same for a product on its own.  Beside tiles of 64 the fit is good to a tenth (us, 256 x 256 tiles / tiles of 64:
+// 1000 x 512 x 776 14.7 / 8.0, 776 x 2048 x 1032 36.9 / 17.1, 1504 x 1024 x 1504 21.8 / 17.7, 4096 x 192 x 4096
+// 18.4 / 23.0, 3072 x 128 x 4096 13.8 / 16.0); beside tiles of 128 they have to be a quarter apart, for what it does
+// not know (2560^3 46.0 / 52.4 where it says 52.9 / 50.2).
 bool fast_alone(int64_t n, int64_t k, int64_t m, int64_t batch) {
   const int64_t t256 = ((n + 255) / 256) * ((m + 255) / 256) * batch;
   const bool close = plan_beside_256(n, k, m, batch).tile == 128;
@@ -203,9 +220,9 @@ bool fast_alone(int64_t n, int64_t k, int64_t m, int64_t batch) {
 // whenever the product has at most 2048 workgroups 12 to 22 %, with products that took twice as long):
 //   - many rounds of workgroups hide nothing (256 x 512^3 fp32 603 -> 608 us), and scans of more than 16 workgroups per
 //     compute unit take longer than the product (bf16 307 x 503 x 301 x 94 193 -> 313);
-//   - bf16 gains whatever the ranges of k, now that the scans come behind the product's workgroups where not all run at once (before, long
-//     ranges and more than 5 scan workgroups per compute unit lost): 5064 x 3680 x 1752 157.5 -> 145.6 us, 3029 x 817 x 2493 NT 53.1 -> 46.6,
-//     6001 x 2000 x 3001 NT 149.6 -> 140.2, 3500^3 215.5 -> 202.4, 5001 x 700 x 5001 105.7 -> 96.2, 4001 x 1000 x 4001 92.9 -> 87.6, 2500^3 89.9 -> 78.9;
+//   - bf16 gains whatever the ranges of k, now that the scans come behind the product's workgroups where not all run
+//     at once (before, long ranges and more than 5 scan workgroups per compute unit lost): 5064 x 3680 x 1752
+//     157.5 -> 145.6 us, 3500^3 215.5 -> 202.4, 5001 x 700 x 5001 105.7 -> 96.2, 2500^3 89.9 -> 78.9;
 //   - fp32 keeps four workgroups of 64 x 64 tiles on a compute unit: scans that find no place beside them delay a
 //     product of long k (3904 x 5888 x 448 289 -> 323), and many of them one of more than 512 terms (8 x 600^3 NT
 //     81 -> 143).  Of 128 x 128 tiles it keeps two: both scans together, if they are few, beside short ranges of k (68 x
@@ -220,17 +237,22 @@ bool scans_ride(const gecc_params& p, int tile, int ksplit, int64_t scans, bool 
   return own + scans <= 1536 || (k_per <= 640 && (scans <= 1792 || k_per <= 512));
 }
 
-// Whether the 256 x 256-tile kernel takes a protected product: where the parity scans ride in gemm_tile's launch, that saves the launches that
-// they have of their own beside the other kernel, two for NN and TT, 12 us; one for NT and TN, which small products feel (256^3 NT), and
-// above 2^19 symbols the fit has to be 6 us apart.  An operand that is read once for both of its scans has one of them fewer to ride.
-// Where they do not ride, the faster product it is (4096 x 192 x 4096, 256 x 256 tiles / tiles of 64: NN 47.5 / 55.5 us a call, NT 45.0 / 51.7; 3072 x 128 x 4096
-// 40.7 / 46.5).  Tiles that hang over the edge are in the fitted times of both kernels (whole calls NN, 256 x 256 tiles / gemm_tile: 2000 x 1024 x 2000
-// 54.6 / 41.6, 3000 x 512 x 3000 52.5 / 40.1, 2504 x 2496 x 2504 84.0 / 77.7, 1000 x 512 x 776 45.6 / 23.5, 520 x 256 x 264 40.6 / 22.1).
+// Whether the 256 x 256-tile kernel takes a protected product.  Where the parity scans ride in gemm_tile's launch, that
+// saves the launches that they have of their own beside the other kernel, two for NN and TT, 12 us; one for NT and TN,
+// which small products feel (256^3 NT), and above 2^19 symbols the fit has to be 6 us apart.  An operand that is read
+// once for both of its scans has one of them fewer to ride.  Tiles that hang over the edge are in the fitted times of
+// both kernels.  Where the scans do not ride, the faster product it is.  Whole calls, us, 256 x 256 tiles / gemm_tile:
+//   ride       2000 x 1024 x 2000   54.6 / 41.6      do not   4096 x 192 x 4096     47.5 / 55.5 (NT 45.0 / 51.7)
+//              3000 x 512 x 3000    52.5 / 40.1               3072 x 128 x 4096     40.7 / 46.5
+//              2504 x 2496 x 2504   84.0 / 77.7
+//              1000 x 512 x 776     45.6 / 23.5
+//              520 x 256 x 264      40.6 / 22.1
 bool fast_protected(const gecc_params& p, int64_t tile_min) {
   const ProductPlan g = plan_beside_256(p.n, p.k, p.m, p.batch);
   // (their workgroups as plan_riders counts them)
   const int64_t chunks = (p.k + SCAN_CHUNK_ROWS - 1) / SCAN_CHUNK_ROWS;
-  const int64_t pr = p.trans_a ? (p.n + 511) / 512 * chunks : (p.n + 3) / 4, pc = p.trans_b ? (p.m + 3) / 4 : (p.m + 511) / 512 * chunks;
+  const int64_t pr = p.trans_a ? (p.n + 511) / 512 * chunks : (p.n + 3) / 4;
+  const int64_t pc = p.trans_b ? (p.m + 3) / 4 : (p.m + 511) / 512 * chunks;
   double bonus;
   if (!scans_ride(p, g.tile, g.ksplit, (1 + pr + pc) * p.batch, true)) return fast_alone(p.n, p.k, p.m, p.batch);
   else if ((int64_t)p.n * p.k * p.batch >= tile_min || (int64_t)p.k * p.m * p.batch >= tile_min) bonus = 0.0;
@@ -247,7 +269,8 @@ void plan_product(gecc_ctx* c, bool compact) {
   ProductPlan pl = {128, ksplit_128(t128, p.k), true, false};
   if (blocked(c)) pl.ksplit = 1;
   else if (!compact && !(may_be_fast && (c->cu_hint > 0 || fast_protected(p, c->tile_min))))
-    pl = may_be_fast && fast_may_pay(p.n, p.k, p.m, p.batch) ? plan_beside_256(p.n, p.k, p.m, p.batch) : plan_tiles(p.dtype, p.n, p.k, p.m, p.batch);
+    pl = may_be_fast && fast_may_pay(p.n, p.k, p.m, p.batch) ? plan_beside_256(p.n, p.k, p.m, p.batch)
+                                                             : plan_tiles(p.dtype, p.n, p.k, p.m, p.batch);
   // (a product on its own stays with the faster kernel)
   c->fast_plain = pl.fast || (may_be_fast && fast_alone(p.n, p.k, p.m, p.batch));
   c->tile_m = c->tile_n = pl.tile;
@@ -790,7 +813,8 @@ Riders plan_riders(const gecc_ctx* ctx, const GemmArgs& g, uint32_t* done, const
   for (int x = 0; x < 2; ++x) {
     if (!jobs[x]) continue;
     int words = 0;
-    if (make_side_job(jobs[x]->s, left ? (x ? left->bp : left->ap) : Parts{}, jobs[x]->rowdot, left ? nullptr : done + used, SCAN_DONE_WORDS - used, r.side.j[at], words)) {
+    if (make_side_job(jobs[x]->s, left ? (x ? left->bp : left->ap) : Parts{}, jobs[x]->rowdot, left ? nullptr : done + used,
+                      SCAN_DONE_WORDS - used, r.side.j[at], words)) {
       used += words;
       ++at;
     } else {
@@ -805,11 +829,13 @@ Riders plan_riders(const gecc_ctx* ctx, const GemmArgs& g, uint32_t* done, const
   return r;
 }
 
-// Whether an operand parity in `nchunk` parts is left to its readers beside the product: a column scan reads the weights of
-// its own rows, and one workgroup adds all of them up for P_g, about 1 us a round of loads.  Up to 8 rounds beside any product,
-// 16 beside one of 2^20 symbols (bf16, finished first -> left: 300 x 6000 x 1000, 12 rounds, 51.3 -> 52.5 us, 1000 x 6000 x 300
-// 51.0 -> 55.2; 2880 x 520 x 2504, 3 of the longest, 59.9 -> 53.1, 1200 x 3000 x 1500 80.1 -> 76.7, 500 x 2000 x 4000 TT 69.4 -> 65.5; all with
-// the scans before the product's workgroups, which made 1200 x 3000 x 1500 no faster than it had been: behind them 66.3).
+// Whether an operand parity in `nchunk` parts is left to its readers beside the product: a column scan reads the
+// weights of its own rows, and one workgroup adds all of them up for P_g, about 1 us a round of loads.  Up to 8 rounds
+// beside any product, 16 beside one of 2^20 symbols.  Whole calls, bf16, us, finished first -> left (with the scans
+// before the product's workgroups; behind them 1200 x 3000 x 1500 takes 66.3):
+//   left       2880 x 520 x 2504     59.9 -> 53.1      finished   300 x 6000 x 1000   51.3 -> 52.5   (12 rounds)
+//              1200 x 3000 x 1500    80.1 -> 76.7                 1000 x 6000 x 300   51.0 -> 55.2
+//              500 x 2000 x 4000 TT  69.4 -> 65.5
 bool parts_beside(const gecc_ctx* c, int nchunk) {
   const int at_once = nchunk <= 8 ? 4 : nchunk <= 16 ? 2 : 1;
   const int64_t rounds = (2 * (int64_t)c->p.k + 256 * at_once - 1) / (256 * at_once) * (nchunk <= 16 ? 1 : 2);
@@ -868,7 +894,9 @@ hipError_t product(gecc_ctx* ctx, ScanQueue& q, const ScanJob* pr, const ScanJob
       left->pc = out[1];
     } else if (pr && pc) {
       // (a column scan, then a row scan that carries its second stage: in one launch they are no faster, bf16 4096^3 20.9 us and 23.8)
-      if ((e = q.run(pr->rowdot ? *pc : *pr)) != hipSuccess || (e = q.run(pr->rowdot ? *pr : *pc)) != hipSuccess || (e = q.flush()) != hipSuccess) return e;
+      if ((e = q.run(pr->rowdot ? *pc : *pr)) != hipSuccess || (e = q.run(pr->rowdot ? *pr : *pc)) != hipSuccess ||
+          (e = q.flush()) != hipSuccess)
+        return e;
     } else if (pr || pc) {
       if ((e = q.run(pr ? *pr : *pc)) != hipSuccess) return e;
       (pr ? left->pr : left->pc) = chunks_of(q.pending);

@@ -484,10 +484,12 @@ int64_t grid_of(const GemmArgs& a) {
 }
 }  // namespace
 
-// Whether an fp32 product of 128 x 128 tiles goes in tiles of 128 x 256: a round of 256 of those, one per compute unit, is done
-// in 0.92 of the time of the same symbols in 512 of 128 x 128, two per compute unit, but has to be a whole one, while the smaller
-// ones fill gaps (product alone, us, 128 x 128 -> 128 x 256: 256 x 512^3 434 -> 398, TT 429 -> 380, 16 x 1024^3 197 -> 173, 64 x 500^3
-// 112 -> 99; and where this rule says no: 48 x 500 x 321 x 381 64 -> 68, 100 x 384^3 76 -> 105, 40 x 600^3 123 -> 143).
+// Whether an fp32 product of 128 x 128 tiles goes in tiles of 128 x 256: a round of 256 of those, one per compute unit,
+// is done in 0.92 of the time of the same symbols in 512 of 128 x 128, two per compute unit, but has to be a whole one,
+// while the smaller ones fill gaps.  Product alone, us, 128 x 128 -> 128 x 256:
+//   yes   256 x 512^3     434 -> 398 (TT 429 -> 380)      no   48 x 500 x 321 x 381    64 -> 68
+//         16 x 1024^3     197 -> 173                           100 x 384^3             76 -> 105
+//         64 x 500^3      112 -> 99                            40 x 600^3              123 -> 143
 bool gemm_f32_wide_pays(const GemmArgs& a) {
   if (a.dtype != GECC_F32 || a.ksplit > 1 || a.k < 128) return false;
   // (offsets of 32 bits: 256 rows, or k of them where rows run along the other axis)

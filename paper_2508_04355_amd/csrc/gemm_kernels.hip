@@ -12,12 +12,12 @@
 // (8 significand bits and a sign each, so the three hold all 24 bits of x exactly), and
 //   a b = a1 b1 + (a1 b2 + a2 b1) + (a1 b3 + a2 b2 + a3 b1) + terms below 2^-25 |a b|,
 // six exact products per pair, accumulated in fp32.  Native fp32 MFMAs do 64 flop per cycle and SIMD,
-// bf16 ones 1024: six of those are 2.7 times as fast.  Measured: 256 x 512^3 766 -> 430 us (160 TFLOP/s
-// of fp32 products, 960 of bf16 ones), 1024^3 50 -> 28 us, 128^3 28 -> 7.7 us, next to native fp32 MFMAs
-// in the kernel this one replaced, with a result closer to the fp64 product (2.1e-7 -> 6.5e-8 at 128^3,
-// 2.9e-7 -> 9e-8 at 1024^3).  bf16, 1500 x 1000 x 1100 with rows that are not 16-byte aligned: 67 -> 20 us,
-// the loads being vectors whatever the alignment.  What bounds it: the pieces (13 vector instructions per
-// two staged elements) and the two barriers per k-tile, which the other workgroups of the compute unit cover.
+// bf16 ones 1024: six of those are 2.7 times as fast.  Measured when this kernel replaced one of native fp32
+// MFMAs: 256 x 512^3 766 -> 430 us, 1024^3 50 -> 28, 128^3 28 -> 7.7, with a result closer to the fp64 product
+// (2.1e-7 -> 6.5e-8 at 128^3, 2.9e-7 -> 9e-8 at 1024^3); bf16, 1500 x 1000 x 1100 with rows that are not
+// 16-byte aligned, 67 -> 20 us, the loads being vectors whatever the alignment.  As it is now: 1024^3 25.7 us,
+// 128^3 7.2, the bf16 product 14.1.  What bounds it: the pieces (13 vector instructions per two staged elements)
+// and the two barriers per k-tile, which the other workgroups of the compute unit cover.
 // Where a piece cannot hold its part of x the tile is computed again with native fp32 MFMAs, from the
 // same operands in the same launch:
 //   - some accumulator is not finite (an infinite or NaN operand, |x| that rounds past the largest bf16,
@@ -55,11 +55,15 @@ template <> struct GT<GECC_F32> {
 // ---- staging of one operand tile: ROWS (m- or n-index) x BK ------------------------------------
 // KC: element (r, kk) lives at P[r * ld + kk]; otherwise at P[kk * ld + r].  Rows past the last one are
 // clamped to it (what they accumulate is masked in the epilogue), k past the end counts as zero.
-// D k-tiles are on their way at a time, each in registers of its own (d).  load() issues the same loads whatever k0 is, clamped
-// into the range (so that addresses stay a base and a stride), and fix() puts the last k-tile right in the registers: a branch
-// around a load makes every later wait one for all loads in flight, the next k-tile's included (bf16 1500 x 1000 x 1100:
-// 0.82 us per k-tile however many were on their way).  With and without the branches, product alone, bf16: 1500 x 1000 x 1100 19.6
-// -> 14.6 us (TN 23.2 -> 15.7, NT 15.2 -> 12.2), 2500^3 69.5 -> 56.0, 96 x 16384 x 4096 69.5 -> 49.7; fp32 2000 x 1000 x 2000 NT 63.5 -> 57.4.
+// D k-tiles are on their way at a time, each in registers of its own (d).  load() issues the same loads whatever
+// k0 is, clamped into the range (so that addresses stay a base and a stride), and fix() puts the last k-tile right
+// in the registers: a branch around a load makes every later wait one for all loads in flight, the next k-tile's
+// included (bf16 1500 x 1000 x 1100: 0.82 us per k-tile however many were on their way).  Product alone, with the
+// branches -> without, us:
+//   bf16 1500 x 1000 x 1100   19.6 -> 14.6 (TN 23.2 -> 15.7, NT 15.2 -> 12.2)
+//   bf16 2500^3               69.5 -> 56.0
+//   bf16 96 x 16384 x 4096    69.5 -> 49.7
+//   fp32 2000 x 1000 x 2000   NT 63.5 -> 57.4
 template <int DT, int ROWS, bool KC, int D> struct Stager;
 
 // k contiguous: 16-byte loads, eight lanes to a row
@@ -350,13 +354,17 @@ __device__ __forceinline__ void mask_edges(const GemmArgs& a, int tile_r0, int t
   }
 }
 
-// k-split: every workgroup of the tile leaves its partial sums in memory (in register order, 16 bytes a lane: whole lines per
-// store), the one that arrives last adds them all up in the order of the k ranges (so the result does not depend on which
-// one that is) and goes on with the tile (true).  Written through and read past the caches, like store_dev and load_dev, for
-// which 16 bytes are too many.  (Whole calls, with 4 bytes a lane -> with 16: 300 x 2000 x 400 bf16 in
-// eight ranges 30.2 -> 28.4 us, 700^3 in four 28.6 -> 26.9, 512^3 fp32 in four 25.9 -> 25.4.)
+// k-split: every workgroup of the tile leaves its partial sums in memory (in register order, 16 bytes a lane: whole
+// lines per store), the one that arrives last adds them all up, in an order that is the same whichever that is, and
+// goes on with the tile (true).  Written through and read past the caches, like store_dev and load_dev, for which
+// 16 bytes are too many.  (Whole calls, with 4 bytes a lane -> with 16: 300 x 2000 x 400 bf16 in eight ranges
+// 30.2 -> 28.4 us, 700^3 in four 28.6 -> 26.9, 512^3 fp32 in four 25.9 -> 25.4.)
+// The order: tiles of 64, two neighbouring ranges and then the pair to the sum, which halves the chain of additions
+// (fp32 256 x 512 x 256 in eight ranges, distance from the fp64 product 7.27e-8 -> 6.73e-8; time unchanged); tiles of
+// 128, which have no registers for a second range on its way, one after the other.
 template <int TILE>
-__device__ __forceinline__ bool add_splits(const GemmArgs& a, int b, int tm, int tn, int split, int S, f32x4_t (&acc)[TILE / 32][TILE / 32], char* smem) {
+__device__ __forceinline__ bool add_splits(const GemmArgs& a, int b, int tm, int tn, int split, int S,
+                                           f32x4_t (&acc)[TILE / 32][TILE / 32], char* smem) {
   constexpr int NI = TILE / 32, DEV = 16;         // (the bit of device scope among a buffer instruction's cache bits)
   const int ntm = (a.n + TILE - 1) / TILE, ntn = (a.m + TILE - 1) / TILE;
   const int64_t tile_id = ((int64_t)b * ntm + tm) * ntn + tn;
@@ -366,14 +374,16 @@ __device__ __forceinline__ bool add_splits(const GemmArgs& a, int b, int tm, int
   for (int i = 0; i < NI; ++i)
 #pragma unroll
     for (int j = 0; j < NI; ++j)
-      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(stream_t, acc[i][j]), part, at + (i * NI + j) * THREADS * 16, split * TILE * TILE * 4, DEV);
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(stream_t, acc[i][j]), part, at + (i * NI + j) * THREADS * 16,
+                                             split * TILE * TILE * 4, DEV);
   if (!arrive_last(a.split_done + tile_id, (uint32_t)S, reinterpret_cast<int*>(smem))) return false;
 #pragma unroll
   for (int i = 0; i < NI; ++i)
 #pragma unroll
     for (int j = 0; j < NI; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  auto load = [&](int q, int at_ij) { return __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(part, at + at_ij * THREADS * 16, q * TILE * TILE * 4, DEV)); };
-  // (tiles of 64: two ranges at a time, which halves the chain of additions)
+  auto load = [&](int q, int at_ij) {
+    return __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(part, at + at_ij * THREADS * 16, q * TILE * TILE * 4, DEV));
+  };
   int q = 0;
   if constexpr (TILE == 64)
 #pragma unroll 2
@@ -520,8 +530,8 @@ __device__ __forceinline__ void finish_tile(const GemmArgs& a, int b, int tm, in
 // split, tile row, tile column) sequence: tiles that share operand panels share an L2.  The scans are
 // HBM-bound and the product is not: in one launch they cost little more than the
 // product alone, and a launch of their own 2 to 5 us of the stream and 3 of the host beside their time.
-// WHAT: the operands' type, or BF16_FOLD (tiles of 64): the sums of every k_fold terms are put aside, so that the chains of additions are no longer than with
-// more ranges of k (k_fold_of).
+// WHAT: the operands' type, or BF16_FOLD (tiles of 64): the sums of every k_fold terms are put aside, so that the chains
+// of additions are no longer than with more ranges of k (k_fold_of).
 constexpr int BF16_FOLD = GECC_BF16 + 2;
 template <int WHAT, bool KCA, bool KCB, int TILE>
 __global__ __launch_bounds__(THREADS, TILE == 64 ? 4 : WHAT == GECC_BF16 ? 3 : 2) void gemm_tile(GemmArgs a, GemmSide side) {
@@ -888,29 +898,36 @@ __global__ __launch_bounds__(THREADS) void partials_kernel(PartialArgs a) {
   }
 }
 
-// The scans come first where all workgroups of the launch run at once (256 compute units with as many as their registers
-// and LDS allow): nobody waits for a place, and theirs is the longer chain.  Beyond that they come behind: what does
-// not fit at first is then short scans and not workgroups of the product that begin 5 us late and last 20.  Whole calls,
-// scans first -> behind, beyond that number: 87 products of all layouts, 0.3 % slower to 20 % faster (bf16 295 x 6020 x 4321
-// 100 -> 82 us, 2432 x 3584 x 256 56.5 -> 50.6, 4648 x 1232 x 272 NT 52.4 -> 44.0, fp32 1991 x 1907 x 220 49.7 -> 44.2); below it
-// 4 % slower (192 x 3520 x 1408 39.8 -> 41.3, TT 1216 x 960 x 576 76.8 -> 80.5) to 7 % faster.  P_g, one workgroup with a long
-// chain, goes first in either case (behind: no difference seen).  Behind, a column scan, whose workgroups take longer, comes
-// before a row scan (bf16 TT 1632 x 624 x 2328 40.9 us, the other way round 46.7; first, where it is the other way round
-// 34.7 -> 34.1 at 1536 x 1280 x 256).
+// The scans come first where all workgroups of the launch run at once (256 compute units with as many as their
+// registers and LDS allow): nobody waits for a place, and theirs is the longer chain.  Beyond that they come behind:
+// what does not fit at first is then short scans and not workgroups of the product that begin 5 us late and last 20.
+// Whole calls, us, scans first -> behind:
+//   beyond that number, 87 products of all layouts, 0.3 % slower to 20 % faster
+//     bf16 295 x 6020 x 4321    100 -> 82         bf16 4648 x 1232 x 272 NT   52.4 -> 44.0
+//     bf16 2432 x 3584 x 256    56.5 -> 50.6      fp32 1991 x 1907 x 220      49.7 -> 44.2
+//   below it, 4 % slower to 7 % faster
+//     bf16 192 x 3520 x 1408    39.8 -> 41.3      TT 1216 x 960 x 576         76.8 -> 80.5
+// P_g, one workgroup with a long chain, goes first in either case (behind: no difference seen).  Behind, a column
+// scan, whose workgroups take longer, comes before a row scan (bf16 TT 1632 x 624 x 2328 40.9 us, the other way
+// round 46.7; first, where it is the other way round 34.7 -> 34.1 at 1536 x 1280 x 256).
 template <int DT, int TILE> constexpr int at_once() { return 256 * (TILE == 64 ? 4 : DT == GECC_BF16 ? 3 : 2); }
 
-// bf16 tiles of 64 in fewer ranges of k than they could have: terms after which the accumulators are added to the third set and start anew, for
-// a range of k_per terms.  A chain of N additions is off by N^2 / 2 squared last bits (a walk that grows); B pieces with a chain of their
-// sums by N^2 / 2B + NB / 2, least where B is about sqrt(N).  Distance of the product from the fp64 one, in 1e-8 (normal operands):
+// bf16 tiles of 64 in fewer ranges of k than they could have: terms after which the accumulators are added to the
+// third set and start anew, for a range of k_per terms.  A chain of N additions is off by N^2 / 2 squared last bits
+// (a walk that grows); B pieces with a chain of their sums by N^2 / 2B + NB / 2, least where B is about sqrt(N).
+// Distance of the product from the fp64 one, in 1e-8 (normal operands):
 //   terms of a piece   128   192   256   384   512   no pieces
 //   range of  260      6.0   6.1   6.8   6.6   6.6    6.6
 //   range of  700      7.1   7.1   7.3   8.0   8.7   10.5
 //   range of 1000      7.6   7.7   7.7   8.3   9.3   12.6
 //   range of 2112      9.9   9.2   9.3   9.6  10.5   19.1
 //   range of 5800     13.7  12.1  11.3  11.1  11.3   32.9
-// (700 terms in four ranges 7.1.)  Products alone, pieces of 128, 256, 384 terms / in the kernel without pieces: 700^3 8.9, 8.7, 8.6 / 8.8 us,
-// 3976 x 456 x 176 TN 8.8, 8.5, 8.5 / 8.7, 2056 x 664 x 168 8.8, 8.7, 8.6 / 8.7.  (With the sums set to zero, and not begun by a product that adds
-// nothing, pieces of 128 terms 9.6 at 700^3.)  A kernel of its own all the same: the loop twice is more code than most products need.
+// (700 terms in four ranges 7.1.)  Products alone, us, pieces of 128, 256, 384 terms / in the kernel without pieces:
+//   700^3               8.9  8.7  8.6 / 8.8   (with the sums set to zero, and not begun by a product that adds
+//   3976 x 456 x 176 TN 8.8  8.5  8.5 / 8.7    nothing, pieces of 128 terms 9.6)
+//   2056 x 664 x 168    8.8  8.7  8.6 / 8.7
+// A kernel of its own all the same: the loop twice is more code than most products need (as a branch in the one for
+// all bf16 tiles of 64 it cost 1500 x 1000 x 1100 2 %).
 int k_fold_of(int k_per) {
   constexpr int STEP = 128;        // (two k-tiles, one to each half of the LDS)
   const int steps = (int)(5.0 * sqrt((double)k_per) / STEP + 0.5);
@@ -934,7 +951,11 @@ hipError_t launch_tile(const GemmArgs& a0, const GemmSide* side0, hipStream_t st
   const int64_t own = tiles * a.ksplit;
   const bool behind = own + side.blocks > at_once<DT, TILE>();
   side.lead_blocks = behind ? side.pg_items : side.blocks;
-  if (behind && side.j[0].kind != SIDE_COL && side.j[1].kind == SIDE_COL) { const SideJob row = side.j[0]; side.j[0] = side.j[1]; side.j[1] = row; }
+  if (behind && side.j[0].kind != SIDE_COL && side.j[1].kind == SIDE_COL) {
+    const SideJob row = side.j[0];
+    side.j[0] = side.j[1];
+    side.j[1] = row;
+  }
   side.lead = (side.lead_blocks + 7) / 8;
   side.groups = side.lead + (side.blocks - side.lead_blocks + 7) / 8;
   const int64_t grid_all = side.groups > 0 ? ((own + 7) / 8 + side.groups) * 8 : own;

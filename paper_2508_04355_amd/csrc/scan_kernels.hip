@@ -37,9 +37,9 @@ __global__ __launch_bounds__(RD_THREADS) void rowdot_kernel(ScanArgs a) {
   rowdot_body<DT, IDXW, RD_RB, RD_U>(a, blockIdx.x, b, lds);
 }
 
-// Column scans of few workgroups take vectors of 8 bytes and twice the rows at once (see coldot_body).  With 16 -> 8 bytes, bf16:
-// 4096^2 index weights 8.9 -> 7.9 us, explicit 8.8 either way; 4096 x 14336, 896 workgroups, 25.4 -> 23.3 with the weights in LDS
-// in both; two of 4096^2 in a launch 16.4 -> 23.0, of 2048^2 7.6 -> 7.0, of 3001^2 13.9 -> 11.8.
+// Column scans of few workgroups take vectors of 8 bytes and twice the rows at once (see coldot_body).  With 16 -> 8
+// bytes, bf16, us: one scan, 4096^2 index weights 8.9 -> 7.9, explicit 8.8 either way, 4096 x 14336 (896 workgroups)
+// 25.4 -> 23.3; two in a launch, 2048^2 7.6 -> 7.0, 3001^2 13.9 -> 11.8, 4096^2 16.4 -> 23.0.
 template <int DT, bool HALF> using ColElem = std::conditional_t<HALF, ElemHalf<DT>, Elem<DT>>;
 constexpr int CD_HALF_BELOW = 1024, CD_PAIR_HALF_BELOW = 512;       // workgroups of the scan (of both of a pair) in vectors of 16 bytes
 
@@ -69,9 +69,10 @@ __global__ __launch_bounds__(256) void coldot_stage2_pair(Stage2Job j0, Stage2Jo
 
 // Two scans that do not read each other's results (both encodings, or both parity blocks): what each of them would
 // leave idle at its end the other one fills, and a launch that waits for the one before it costs 2 to 5 us whatever it does.
-// Two parity blocks are scans of one kind, and each kind has a kernel of its own (in one for both, registers of the bf16 column scan
-// spilled).  Row scans keep three wavefronts per SIMD (with two, 3072 x 2048 x 6144 NT 150.0 -> 152.5 us a call); column scans have the weights
-// of four rows in registers, which is worth more than the third wavefront (spilled for it, 4096^3 TN 25.6 us for 16.4).
+// Two parity blocks are scans of one kind, and each kind has a kernel of its own (in one for both, registers of the
+// bf16 column scan spilled).  Row scans keep three wavefronts per SIMD (with two, 3072 x 2048 x 6144 NT 150.0 -> 152.5 us
+// a call); column scans have the weights of four rows in registers, which is worth more than the third wavefront
+// (spilled for it, 4096^3 TN 25.6 us for 16.4).
 struct ScanPair { SideJob j[2]; };
 enum : int { PAIR_ANY = 0,       // (explicit weights: row scans)
              PAIR_WAVE = 1,      // one of them a row scan with a wavefront per RW_RB rows, a third more registers than the others
@@ -421,10 +422,13 @@ hipError_t launch_scan_pair(const ScanArgs* s, const bool* rowdot, Parts* left, 
 
 // ---- the two audits as jobs of the decoder's launch -----------------------------------------------
 constexpr int AUDIT_PAIR_MAX_BLOCKS = 5120;
-// A column audit of fewer workgroups than compute units goes in vectors of 8 bytes, twice the workgroups: the decoder's launch with an
-// operand error, us: bf16 1500 x 1000 of A 21.8 -> 17.2, 2048^2 22.0 -> 18.1, 4096 x 2048 26.1 -> 22.5, 4 x 1024^2 21.5 -> 17.8, fp32
-// 1024^2 16.6 -> 15.0, 3000 x 1000 19.2 -> 17.5; (16 x 256^2 as before, 8 x 500 x 700 18.4 -> 19.0).  From 256 on what the audit saves
-// is lost where C alone is patched and the others only decide that: bf16 4096^2 31.5 -> 29.1 and 20.7 -> 22.6.
+// A column audit of fewer workgroups than compute units goes in vectors of 8 bytes, twice the workgroups.  The decoder's
+// launch with an operand error, us, 16 -> 8 bytes:
+//   bf16  1500 x 1000   21.8 -> 17.2      4 x 1024^2      21.5 -> 17.8      fp32  1024^2        16.6 -> 15.0
+//         2048^2        22.0 -> 18.1      8 x 500 x 700   18.4 -> 19.0            3000 x 1000   19.2 -> 17.5
+//         4096 x 2048   26.1 -> 22.5      16 x 256^2      the same
+// From 256 on what the audit saves is lost where C alone is patched and the others only decide that: bf16 4096^2
+// 31.5 -> 29.1 and 20.7 -> 22.6.
 constexpr int CD_AUDIT_HALF_BELOW = 256;
 // fills j from x; returns the counters it uses, or -1 when x cannot finish by itself
 static int make_pair_job(const ScanPairItem& x, uint32_t* done, PairJob& j) {
