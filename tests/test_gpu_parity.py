@@ -67,10 +67,9 @@ def test_clean_product_blocks_of_the_256_tile_kernel_match_the_oracle(shape, tra
 
 @pytest.mark.parametrize("trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
 @pytest.mark.parametrize("pattern", ["C+C on the edges", "A+C", "B+C", "A+B"])
-def test_ragged_tiles_of_the_fast_bf16_kernel_with_errors(pattern, trans, monkeypatch):
+def test_ragged_tiles_of_the_fast_bf16_kernel_with_errors(pattern, trans):
     """Faults in the last row / column of C and of the operands, where the 256 x 256 tiles of the
     bf16 kernel hang over the edge (range-checked stores, zero-filled operand rows)."""
-    monkeypatch.setenv("GECC_CU_COUNT", "256")      # (keeps the plan with those tiles)
     n, k, m = 520, 256, 264
     rng = inputs.rng_for(92, 0)
     law = ("normal", 1.0)
@@ -86,6 +85,14 @@ def test_ragged_tiles_of_the_fast_bf16_kernel_with_errors(pattern, trans, monkey
     H.compare(g, o, 1e-5, what="ragged fast kernel, %s, trans %s" % (pattern, trans))
     assert g.reports[0].status == gecc.CORRECTED
     assert [(e[0], e[1], e[2]) for e in g.reports[0].errors()] == [(e[0], e[1], e[2]) for e in eff]
+
+
+@pytest.mark.parametrize("trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("pattern", ["C+C on the edges", "A+C", "B+C", "A+B"])
+def test_ragged_tiles_of_the_256_tile_kernel_with_errors(pattern, trans, monkeypatch):
+    """(GECC_CU_COUNT keeps the plan with those tiles for a product this small.)"""
+    monkeypatch.setenv("GECC_CU_COUNT", "256")
+    test_ragged_tiles_of_the_fast_bf16_kernel_with_errors(pattern, trans)
 
 
 @pytest.mark.parametrize("trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
@@ -473,10 +480,9 @@ def test_unaligned_leading_dimensions_take_the_scalar_paths():
 
 
 @pytest.mark.parametrize("trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
-def test_padded_leading_dimensions_in_the_fast_bf16_kernel(trans, monkeypatch):
+def test_padded_leading_dimensions_in_the_fast_bf16_kernel(trans):
     """Leading dimensions larger than the rows (by a multiple of 8 elements, which keeps the 256 x 256
     kernel): operand panels and the stores of C, two rows x 32 columns each, walk the padded rows."""
-    monkeypatch.setenv("GECC_CU_COUNT", "256")      # (keeps the plan with those tiles)
     n, k, m = 520, 256, 264
     rng = inputs.rng_for(94, 1)
     law = ("normal", 1.0)
@@ -488,6 +494,12 @@ def test_padded_leading_dimensions_in_the_fast_bf16_kernel(trans, monkeypatch):
     H.compare(g, H.run_oracle(A, B, A2, B2, cfb, tau), 1e-5, what="padded ld, trans %s" % (trans,))
     assert g.reports[0].status == gecc.CORRECTED and g.pad_untouched
     assert [(e[0], e[1], e[2]) for e in g.reports[0].errors()] == [(e[0], e[1], e[2]) for e in eff]
+
+
+@pytest.mark.parametrize("trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_padded_leading_dimensions_in_the_256_tile_kernel(trans, monkeypatch):
+    monkeypatch.setenv("GECC_CU_COUNT", "256")      # (keeps the plan with those tiles)
+    test_padded_leading_dimensions_in_the_fast_bf16_kernel(trans)
 
 
 def test_all_zero_operands_are_clean():

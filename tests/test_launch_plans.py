@@ -112,13 +112,20 @@ def test_bf16_products_either_kernel_takes(plans, ta, tb):
         assert "gemm_bf16_256" in product("plain", n, k, m)[0]
     for n, k, m in ((256, 256, 256), (1280, 7296, 2304), (1024, 4096, 4096)):
         assert "gemm_tile" in product("protected", n, k, m)[0] and "gemm_tile" in product("plain", n, k, m)[0]
-    for n, k, m in ((4096, 4096, 4096), (3072, 3072, 3072), (4040, 4032, 4008)):
+    for n, k, m in ((4096, 4096, 4096), (3072, 3072, 3072)):
         assert "gemm_bf16_256" in product("protected", n, k, m)[0]
-    # sizes that are no multiples of a tile go by the same rule
-    for n, k, m in ((2000, 1024, 2000), (2000, 512, 2000), (3000, 512, 3000), (2056, 2048, 2056), (1000, 512, 776)):
-        name, scans = product("protected", n, k, m)
-        assert ("gemm_tile" in name) == two_launches and (scans <= 3 if two_launches else scans >= 2)
-    assert "gemm_tile" in product("protected", 520, 256, 264)[0]
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_bf16_products_of_ragged_sizes_go_by_the_same_rule(plans, ta, tb):
+    """Aligned sizes that are no multiples of a tile."""
+    for n, k, m in ((2000, 1024, 2000), (2000, 512, 2000), (3000, 512, 3000), (2056, 2048, 2056), (1000, 512, 776), (520, 256, 264), (4040, 4032, 4008)):
+        (rc, names), = routes(plans, [("protected", n, k, m, 1, 1, ta, tb)])
+        assert rc == 0
+        scans = [x for x in names if "dot" in x or "scan" in x]
+        tile = bool(_has(names, "gemm_tile"))
+        assert tile != bool(_has(names, "gemm_bf16_256")) and tile == ((n, k, m) == (520, 256, 264) or (n < 4000 and ta == tb)), names
+        assert len(scans) <= 3 if tile else len(scans) >= 2, names
 
 
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])

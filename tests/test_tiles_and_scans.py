@@ -298,6 +298,32 @@ def test_ragged_tiles_in_the_kernel_with_256_by_256_tiles(pad, trans, monkeypatc
     assert g.pad_untouched and [e[:3] for e in g.reports[0].errors()] == [(2, 256, 0), (2, n - 1, m - 1)]
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("trans", [(0, 0), (1, 0), (0, 1)])
+@pytest.mark.parametrize("shape", [(129, 130, 131), (255, 513, 3), (5, 640, 257), (96, 4133, 71),
+                                   (260, 300, 16200)])      # the most workgroups of these (vectors of 8 bytes)
+def test_column_scans_at_their_ends(shape, dtype, trans):
+    """Rows that end in the middle of a vector of 8 or 16 bytes, chunks whose last rows are no whole batch, rows shorter than a
+    vector: operand parities and parity blocks in fp64, rounded k times (n, m times) at most, in any order."""
+    import torch
+    import gpu_harness as H
+    n, k, m = shape
+    law = ("normal", 1.0)
+    A, B = inputs.operands(inputs.rng_for(84, n + k), n, k, m, law, law, dtype)
+    g = H.run_gpu(A, B, A, B, [], gecc.noise_thresholds(n, k, m, 1.0, 1.0), dtype, trans[0], trans[1])
+    A, B = A.astype(np.float64), B.astype(np.float64)
+    wn, wm = np.arange(1, n + 1.0), np.arange(1, m + 1.0)
+    aP, bP = np.stack([A.sum(0), wn @ A]), np.stack([B.sum(1), B @ wm])
+    mag_a, mag_b = np.stack([np.abs(A).sum(0), wn @ np.abs(A)]), np.stack([np.abs(B).sum(1), np.abs(B) @ wm])
+    eps = 2.0 ** -52
+    assert (np.abs(g.A_par[0] - aP) <= n * eps * mag_a).all() and (np.abs(g.B_par[0] - bP) <= m * eps * mag_b).all()
+    pr, pc = (A @ bP.T).T, aP @ B
+    mr, mc = (np.abs(A) @ mag_b.T).T, mag_a @ np.abs(B)
+    got = g.C_par[0]
+    assert (np.abs(got[:2 * n].reshape(2, n) - pr) <= 2 * (k + m) * eps * mr).all()
+    assert (np.abs(got[2 * n:2 * n + 2 * m].reshape(2, m) - pc) <= 2 * (k + n) * eps * mc).all()
+
+
 def _check_parities(g, A, B):
     """Operand parities and parity blocks in fp64, rounded k times (n, m times) at most, in any order."""
     (_, n, k), m = A.shape, B.shape[2]
@@ -313,20 +339,6 @@ def _check_parities(g, A, B):
         got = g.C_par[b]
         assert (np.abs(got[:2 * n].reshape(2, n) - pr) <= 2 * (k + m) * eps * mr).all()
         assert (np.abs(got[2 * n:2 * n + 2 * m].reshape(2, m) - pc) <= 2 * (k + n) * eps * mc).all()
-
-
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("trans", [(0, 0), (1, 0), (0, 1)])
-@pytest.mark.parametrize("shape", [(129, 130, 131), (255, 513, 3), (5, 640, 257), (96, 4133, 71), (260, 300, 16200)])
-def test_column_scans_at_their_ends(shape, dtype, trans):
-    """Vectors of 8 bytes (fewer than 512 workgroups in all): rows that end in the middle of one, chunks whose last rows are no whole
-    batch, rows shorter than a vector."""
-    import gpu_harness as H
-    n, k, m = shape
-    law = ("normal", 1.0)
-    A, B = inputs.operands(inputs.rng_for(84, n + k), n, k, m, law, law, dtype)
-    g = H.run_gpu(A, B, A, B, [], gecc.noise_thresholds(n, k, m, 1.0, 1.0), dtype, trans[0], trans[1])
-    _check_parities(g, A[None], B[None])
 
 
 # Batches whose column scans go in vectors of 16 bytes, in launches of their own (test_launch_plans.py holds them to it): rows that end
@@ -348,12 +360,14 @@ def test_column_scans_of_many_workgroups_at_their_ends(trans, dtype, staged):
 
 # (test_launch_plans.py holds them to the tiles and ranges, and to the scans in the product's launch)
 BESIDE_CASES = [((1530, 4222, 760), 128, 7),        # 128 x 128 tiles, seven ranges of k
-                ((1300, 1750, 1211), 64, 1),        # scans behind the product's workgroups
                 ((256, 64, 256), 64, 1)]            # the smallest that the 256 x 256-tile kernel could take
 
 
 @pytest.mark.parametrize("trans", [(0, 0), (0, 1), (1, 0), (1, 1)])
-@pytest.mark.parametrize("shape", [x[0] for x in BESIDE_CASES])
+@pytest.mark.parametrize("shape", [(1280, 2176, 1408),       # aligned, tiles of 64 in one range
+                                   (1300, 1750, 1211),       # ragged, scans before or behind the product's workgroups
+                                   (192, 64, 256)] +         # too small for the 256 x 256-tile kernel
+                                  [x[0] for x in BESIDE_CASES])
 def test_bf16_products_with_their_scans_beside_them(shape, trans):
     import gpu_harness as H
     n, k, m = shape
