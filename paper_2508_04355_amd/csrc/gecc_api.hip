@@ -244,8 +244,8 @@ bool scans_ride(const gecc_params& p, int tile, int ksplit, int64_t scans, bool 
 // both kernels.  Where the scans do not ride, the faster product it is.  Whole calls, us, 256 x 256 tiles / gemm_tile:
 //   ride       2000 x 1024 x 2000   54.6 / 41.6      do not   4096 x 192 x 4096     47.5 / 55.5 (NT 45.0 / 51.7)
 //              3000 x 512 x 3000    52.5 / 40.1               3072 x 128 x 4096     40.7 / 46.5
-//              2504 x 2496 x 2504   84.0 / 77.7
-//              1000 x 512 x 776     45.6 / 23.5
+//              2504 x 2496 x 2504   84.0 / 77.7               128 x 1280 x 512 x 100   103.6 / 85.3
+//              1000 x 512 x 776     45.6 / 23.5               512 x 2432 x 128 x 53 NT 118.0 / 96.9
 //              520 x 256 x 264      40.6 / 22.1
 bool fast_protected(const gecc_params& p, int64_t tile_min) {
   const ProductPlan g = plan_beside_256(p.n, p.k, p.m, p.batch);
@@ -254,7 +254,7 @@ bool fast_protected(const gecc_params& p, int64_t tile_min) {
   const int64_t pr = p.trans_a ? (p.n + 511) / 512 * chunks : (p.n + 3) / 4;
   const int64_t pc = p.trans_b ? (p.m + 3) / 4 : (p.m + 511) / 512 * chunks;
   double bonus;
-  if (!scans_ride(p, g.tile, g.ksplit, (1 + pr + pc) * p.batch, true)) return fast_alone(p.n, p.k, p.m, p.batch);
+  if (!scans_ride(p, g.tile, g.ksplit, (1 + pr + pc) * p.batch, true)) bonus = 0.0;
   else if ((int64_t)p.n * p.k * p.batch >= tile_min || (int64_t)p.k * p.m * p.batch >= tile_min) bonus = 0.0;
   else bonus = p.trans_a == p.trans_b ? 12.0 : (int64_t)p.n * p.m * p.batch < (1 << 19) ? 9.0 : -6.0;
   return fast_pays(p.n, p.k, p.m, p.batch, bonus);

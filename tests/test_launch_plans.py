@@ -149,6 +149,14 @@ def test_products_whose_scans_do_not_ride_go_to_the_faster_kernel(plans, ta, tb)
         assert rc == 0 and any("gemm_bf16_256" in x for x in names), names
 
 
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_batches_whose_scans_do_not_ride_go_to_the_faster_kernel(plans, ta, tb):
+    """Items of 128 columns fill half of a 256 x 256 tile (128 x 1280 x 512 x 100 NN: 85 us in tiles of 128, 104 in those)."""
+    for n, k, m, batch in ((128, 1280, 512, 100), (128, 1664, 1024, 54), (1088, 1792, 128, 41), (4608, 1536, 128, 12)):
+        (rc, names), = routes(plans, [("protected", n, k, m, batch, 1, ta, tb)])
+        assert rc == 0 and _has(names, "gemm_tileILi1E") and not _has(names, "gemm_bf16_256"), names
+
+
 @pytest.mark.parametrize("shape,batch,per_item", [((4096, 4096, 4096), 1, 16), ((512, 512, 512), 256, 1), ((512, 512, 512), 128, 2), ((1024, 256, 1024), 200, 1),
                                                   ((2047, 24, 100), 130, 1), ((2048, 24, 100), 130, 3), ((100, 24, 4096), 256, 2), ((4096, 24, 100), 257, 1),
                                                   ((16384, 32, 512), 60, 4), ((2048, 64, 512), 128, 2), ((2048, 64, 512), 129, 3), ((16384, 32, 512), 1, 64)])
