@@ -129,8 +129,9 @@ int ranges_128(int64_t k, int64_t t128) {
 // 23.1 -> 21.7).
 //
 // bf16 tiles of 64: two workgroups per compute unit and ranges of 450 terms, where that is one range two and a half
-// and 600; up to 20 tiles two and a half and 128.  Where ranges of 128 terms would be more, the sums are put aside
-// every so often, which keeps the error (GemmArgs::fold).  Whole calls with ranges of 128 terms / with these:
+// and 600; up to 20 tiles two and a half and 128.  Where ranges of 128 terms would be more, or those of tiles of 128
+// shorter than half of these (which have two chains), the sums are put aside every so often, which keeps the error
+// (GemmArgs::fold; 1258 x 2122 x 1110 in one range 1.90e-7 from the fp64 product, in four of tiles of 128 1.36e-7).  Whole calls with ranges of 128 terms / with these:
 //   36 tiles    102 x 1542 x 1096 TT  28.5 / 25.6        140 tiles  448 x 920 x 1248 TT   28.7 / 26.6
 //   72 tiles    1152 x 704 x 256      24.9 / 22.7        270 tiles  916 x 1817 x 1137     44.4 (in one range 46.9)
 //   104 tiles   256 x 512 x 1664      26.6 / 21.2        315 tiles  4017 x 1020 x 282     35.3 / 34.3
@@ -160,7 +161,7 @@ ProductPlan plan_tiles(int dtype, int64_t n, int64_t k, int64_t m, int64_t batch
   if (s_long == 0 && many) return {128, dtype == GECC_F32 && t128 < 512 ? 2 : 1, false, false};
   if (dtype == GECC_F32)
     return {64, ksplit_of(t64, t64 > 256 ? 1024 : 800, (int)k, t64 <= 64 ? 64 : t64 <= 128 ? 96 : 128), false, false};
-  return {64, s64, false, s64 < most || s_long > 0};
+  return {64, s64, false, s64 < most || s_long > 0 || (!narrow && ranges_128(k, t128) > 2 * s64)};
 }
 
 double time_256(int64_t k, int64_t t256) { return 6.0 + (0.0148 + 0.009 * (double)t256 / 256.0) * (double)k; }
@@ -185,8 +186,8 @@ ProductPlan plan_beside_256(int64_t n, int64_t k, int64_t m, int64_t batch) {
   const int64_t t128 = ((n + 127) / 128) * ((m + 127) / 128) * batch, t64 = ((n + 63) / 64) * ((m + 63) / 64) * batch;
   const int s64 = ranges_64(t64, (int)k), s128 = ranges_128(k, t128);
   const bool large = t128 >= 256 && k >= 256 && 3 * t128 < t64;
-  if (large || (t128 <= 576 && time_128(k, t128, s128) < time_64(k, t64, s64))) return {128, s128, false};
-  return {64, s64, false};
+  if (large || (t128 <= 576 && time_128(k, t128, s128) < time_64(k, t64, s64))) return {128, s128, false, false};
+  return {64, s64, false, s128 > 2 * s64};
 }
 double time_of(const ProductPlan& g, int64_t n, int64_t k, int64_t m, int64_t batch) {
   const int64_t tiles = ((n + g.tile - 1) / g.tile) * ((m + g.tile - 1) / g.tile) * batch;

@@ -209,3 +209,10 @@ def test_bf16_products_whose_sums_are_put_aside(plans, ta, tb):
         for entry in ("plain", "multiply"):
             (_, names), = routes(plans, [(entry, n, k, m, 1, 1, ta, tb)])
             assert bool(_has(names, "gemm_tileILi3E")) == folds, (n, k, m, names)
+
+
+def test_bf16_products_whose_sums_are_put_aside_for_the_ranges_that_tiles_of_128_would_have(plans):
+    """Four or five against one or two of tiles of 64, which have two chains over each."""
+    for n, k, m, ta, tb, folds in ((1258, 2122, 1110, 1, 0, True), (768, 2816, 1408, 0, 1, True), (256, 2688, 4480, 0, 1, True), (2128, 840, 1544, 0, 0, False)):
+        (_, names), = routes(plans, [("plain", n, k, m, 1, 1, ta, tb)])
+        assert bool(_has(names, "gemm_tileILi3E")) == folds, (n, k, m, names)

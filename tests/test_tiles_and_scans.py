@@ -427,6 +427,13 @@ def test_distance_from_fp64(dtype, shape, trans, limit):
     assert np.linalg.norm(C - ref) <= limit * np.linalg.norm(ref)
 
 
+@pytest.mark.parametrize("shape,trans,limit", [((1258, 2122, 1110), (1, 0), 1.43e-7), ((768, 2816, 1408), (0, 1), 1.46e-7), ((256, 2688, 4480), (0, 1), 1.45e-7)])
+def test_distance_from_fp64_where_tiles_of_128_would_have_shorter_ranges(shape, trans, limit):
+    """5 % above the distances of tiles of 128 in four and five ranges, 1.36e-7, 1.39e-7 and 1.38e-7; tiles of 64 with two chains over one range
+    (1258 x 2122 x 1110) or two are 1.90e-7, 1.54e-7 and 1.50e-7 from the fp64 product."""
+    test_distance_from_fp64("bf16", shape, trans, limit)
+
+
 ALONE_SHAPE = (448, 192, 18624)
 
 
