@@ -142,6 +142,10 @@ int ranges_128(int64_t k, int64_t t128) {
 // 64 49.8 and 6.4e-8), nor in fewer ranges.  Tiles of 64 replace them, closer to the fp64 product as well, where the
 // fitted times say so (144 x 3176 x 4952 NT 60.3 -> 52.9), and in place of eight ranges, the most a tile is cut into
 // (960 x 4352 x 960 NT 54.7 -> 43.9, 3328 x 4544 x 192 58.5 -> 49.3).
+// Two ranges of tiles of 128 and one of more than 512 tiles of 64 are as far from the fp64 product: by the fitted times
+// (tiles of 64 / of 128, whole calls: 395 x 6072 x 5383 144.8 / 111.2, 1504 x 3076 x 1797 77.2 / 66.4, 2778 x 2582 x 909 TT
+// 59.0 / 61.7; 43 such 1.12 times as fast).  Single products: of narrow items tiles of 128 may fill half, and what they
+// exchange beside the batch's own scratch can be too much (232 x 5024 x 104 x 91 NT 88.3 / 129.5).
 //
 // narrow: a side product of blocked mode, a few columns (rows) beside a whole operand; its bf16 ranges are as they were
 // measured, two and a half workgroups and 128 terms.
@@ -159,6 +163,12 @@ ProductPlan plan_tiles(int dtype, int64_t n, int64_t k, int64_t m, int64_t batch
   if (s_long > 0 && (narrow || (s_long < 8 && time_128(k, t128, ranges_128(k, t128)) <= time_64(k, t64, s64))))
     return {128, s_long, false, false};
   if (s_long == 0 && many) return {128, dtype == GECC_F32 && t128 < 512 ? 2 : 1, false, false};
+  // tiles of 64 that fill a compute unit three times over without being split: two ranges of tiles of 128 have chains
+  // no longer than their two
+  if (dtype == GECC_BF16 && !narrow && batch == 1 && t64 > 512) {
+    const int s128 = ranges_128(k, t128);
+    if (s128 > 1 && time_128(k, t128, s128) < time_64(k, t64, s64)) return {128, s128, false, false};
+  }
   if (dtype == GECC_F32)
     return {64, ksplit_of(t64, t64 > 256 ? 1024 : 800, (int)k, t64 <= 64 ? 64 : t64 <= 128 ? 96 : 128), false, false};
   return {64, s64, false, s64 < most || s_long > 0 || (!narrow && ranges_128(k, t128) > 2 * s64)};

@@ -216,3 +216,12 @@ def test_bf16_products_whose_sums_are_put_aside_for_the_ranges_that_tiles_of_128
     for n, k, m, ta, tb, folds in ((1258, 2122, 1110, 1, 0, True), (768, 2816, 1408, 0, 1, True), (256, 2688, 4480, 0, 1, True), (2128, 840, 1544, 0, 0, False)):
         (_, names), = routes(plans, [("plain", n, k, m, 1, 1, ta, tb)])
         assert bool(_has(names, "gemm_tileILi3E")) == folds, (n, k, m, names)
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_bf16_products_in_two_ranges_of_tiles_of_128(plans, ta, tb):
+    """... where more than 512 tiles of 64 could not be split; 512 of them and batches stay with those."""
+    for n, k, m, batch, tile, ranges in ((1504, 3076, 1797, 1, 128, 2), (395, 6072, 5383, 1, 128, 2), (2047, 2500, 1023, 1, 64, 1), (232, 5030, 104, 91, 64, 1)):
+        (_, names), = routes(plans, [("plain", n, k, m, batch, 1, ta, tb)], "grids")
+        name, grid = names[-1].split(":")
+        assert "ELi%dEEEv" % tile in name and int(grid) == -(-n // tile) * -(-m // tile) * batch * ranges, names
