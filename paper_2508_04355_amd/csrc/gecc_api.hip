@@ -252,7 +252,8 @@ bool scans_ride(const gecc_params& p, int tile, int ksplit, int64_t scans, bool 
 // saves the launches that they have of their own beside the other kernel, two for NN and TT, 12 us; one for NT and TN,
 // which small products feel (256^3 NT), and above 2^19 symbols the fit has to be 6 us apart.  An operand that is read
 // once for both of its scans has one of them fewer to ride.  Tiles that hang over the edge are in the fitted times of
-// both kernels.  Where the scans do not ride, the faster product it is.  Whole calls, us, 256 x 256 tiles / gemm_tile:
+// both kernels.  Where the scans do not ride, the faster product it is; of single NT and TN products the fit has to be
+// 6 us apart there too (5056 x 64 x 2176 TN 32.6 / 36.1), while batches would lose by that (3 to 16 %).  Whole calls, us, 256 x 256 tiles / gemm_tile:
 //   ride       2000 x 1024 x 2000   54.6 / 41.6      do not   4096 x 192 x 4096     47.5 / 55.5 (NT 45.0 / 51.7)
 //              3000 x 512 x 3000    52.5 / 40.1               3072 x 128 x 4096     40.7 / 46.5
 //              2504 x 2496 x 2504   84.0 / 77.7               128 x 1280 x 512 x 100   103.6 / 85.3
@@ -265,7 +266,7 @@ bool fast_protected(const gecc_params& p, int64_t tile_min) {
   const int64_t pr = p.trans_a ? (p.n + 511) / 512 * chunks : (p.n + 3) / 4;
   const int64_t pc = p.trans_b ? (p.m + 3) / 4 : (p.m + 511) / 512 * chunks;
   double bonus;
-  if (!scans_ride(p, g.tile, g.ksplit, (1 + pr + pc) * p.batch, true)) bonus = 0.0;
+  if (!scans_ride(p, g.tile, g.ksplit, (1 + pr + pc) * p.batch, true)) bonus = p.trans_a != p.trans_b && p.batch == 1 ? -6.0 : 0.0;
   else if ((int64_t)p.n * p.k * p.batch >= tile_min || (int64_t)p.k * p.m * p.batch >= tile_min) bonus = 0.0;
   else bonus = p.trans_a == p.trans_b ? 12.0 : (int64_t)p.n * p.m * p.batch < (1 << 19) ? 9.0 : -6.0;
   return fast_pays(p.n, p.k, p.m, p.batch, bonus);

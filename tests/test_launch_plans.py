@@ -225,3 +225,11 @@ def test_bf16_products_in_two_ranges_of_tiles_of_128(plans, ta, tb):
         (_, names), = routes(plans, [("plain", n, k, m, batch, 1, ta, tb)], "grids")
         name, grid = names[-1].split(":")
         assert "ELi%dEEEv" % tile in name and int(grid) == -(-n // tile) * -(-m // tile) * batch * ranges, names
+
+
+@pytest.mark.parametrize("n,k,m", [(5056, 64, 2176), (4288, 64, 2112)])
+def test_single_products_of_short_k_whose_scans_do_not_ride(plans, n, k, m):
+    """NT and TN, where one launch at most is at stake (TN 32.6 us in tiles of 256 x 256, 36.1 in tiles of 64)."""
+    for ta, tb in ((0, 1), (1, 0)):
+        (_, names), = routes(plans, [("protected", n, k, m, 1, 1, ta, tb)])
+        assert _has(names, "gemm_bf16_256"), names
